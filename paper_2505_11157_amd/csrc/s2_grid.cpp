@@ -175,6 +175,55 @@ int s2_fail(int code, const std::string &msg)
 
 extern "C" const char *s2_last_error(void) { return g_last_error.c_str(); }
 
+// Owner rows, walked rows and arcs of S2BandSide, from the tables the kernels use (rows of weight zero left out).
+static void build_sides(s2_grid *g)
+{
+    const int ci = g->pscale, co = g->upscale, nU = std::min(g->nlon_in, g->nlon_out);
+    // arc of input class si as the outputs of class so see it: input column minus output column
+    auto arc_of = [&](int h, int b, int so, int si) -> int2 {
+        if (co > 1) {
+            const size_t at = (size_t(h) * co + so) * g->band_max + b;
+            int lo = g->ulo[at], c = g->ucnt[at];
+            return c >= nU ? make_int2(0, nU) : make_int2(lo, c);
+        }
+        const int c = g->cnt[size_t(h) * g->band_max + b];
+        if (c >= g->nlon_in) return make_int2(0, nU);
+        if (c <= 0) return make_int2(0, 0);
+        const int hw = (c - 1) / 2;                       // offsets -hw .. hw in input longitudes
+        auto floor_div = [](int x, int y) { return x >= 0 ? x / y : -((-x + y - 1) / y); };
+        const int lo = -floor_div(hw + si, ci), hi = floor_div(hw - si, ci);
+        return hi < lo ? make_int2(0, 0) : hi - lo + 1 >= nU ? make_int2(0, nU) : make_int2(lo, hi - lo + 1);
+    };
+    const int bo = std::max(g->band_max, 1) * ci, bi = std::max(g->tband_max, 1) * co;
+    g->vo_lo.assign(size_t(g->nlat_out) * co, 0);
+    g->vo_n = g->vo_lo;
+    g->vo_arc.assign(g->vo_lo.size() * bo, make_int2(0, 0));
+    g->vi_lo.assign(size_t(g->nlat_in) * ci, 0);
+    g->vi_n = g->vi_lo;
+    g->vi_arc.assign(g->vi_lo.size() * bi, make_int2(0, 0));
+    for (int hp = 0; hp < g->nlat_in; ++hp)
+        for (int si = 0; si < ci; ++si) {
+            g->vi_lo[hp * ci + si] = g->tband_lo[hp] * co;
+            g->vi_n[hp * ci + si] = g->tband_n[hp] * co;
+        }
+    for (int h = 0; h < g->nlat_out; ++h)
+        for (int so = 0; so < co; ++so) {
+            const int vo = h * co + so;
+            g->vo_lo[vo] = g->band_lo[h] * ci;
+            g->vo_n[vo] = g->band_n[h] * ci;
+            for (int b = 0; b < g->band_n[h]; ++b) {
+                const int hp = g->band_lo[h] + b, tb = h - g->tband_lo[hp];
+                for (int si = 0; si < ci; ++si) {
+                    const int2 a = arc_of(h, b, so, si);
+                    g->vo_arc[size_t(vo) * bo + b * ci + si] = a;
+                    if (a.y > 0)
+                        g->vi_arc[size_t(hp * ci + si) * bi + tb * co + so] =
+                            a.y >= nU ? a : make_int2(-(a.x + a.y - 1), a.y);
+                }
+            }
+        }
+}
+
 static int upload_tables(s2_grid *g)
 {
     int ndev = 0;
@@ -227,6 +276,12 @@ static int upload_tables(s2_grid *g)
         {&zero_word, sizeof(unsigned), 0},
         {g->ucnt.data(), g->ucnt.size() * sizeof(int), 0},
         {g->ulo.data(), g->ulo.size() * sizeof(int), 0},
+        {g->vo_lo.data(), g->vo_lo.size() * sizeof(int), 0},
+        {g->vo_n.data(), g->vo_n.size() * sizeof(int), 0},
+        {g->vo_arc.data(), g->vo_arc.size() * sizeof(int2), 0},
+        {g->vi_lo.data(), g->vi_lo.size() * sizeof(int), 0},
+        {g->vi_n.data(), g->vi_n.size() * sizeof(int), 0},
+        {g->vi_arc.data(), g->vi_arc.size() * sizeof(int2), 0},
     };
     size_t total = 0;
     for (auto &p : parts) {
@@ -265,6 +320,13 @@ static int upload_tables(s2_grid *g)
     t.nlat_in = g->nlat_in; t.nlon_in = g->nlon_in;
     t.nlat_out = g->nlat_out; t.nlon_out = g->nlon_out;
     t.pscale = g->pscale;
+    const int nU = std::min(g->nlon_in, g->nlon_out), ci = g->pscale, co = g->upscale;
+    auto ip = [&](int i) { return reinterpret_cast<const int *>(base + parts[i].off); };
+    auto ap = [&](int i) { return reinterpret_cast<const int2 *>(base + parts[i].off); };
+    t.side_out = {ip(15), ip(16), ap(17), int(g->vo_arc.size() / g->vo_lo.size()), int(g->vo_lo.size()), nU, co, ci,
+                  g->nlat_out, g->nlat_in};
+    t.side_in = {ip(18), ip(19), ap(20), int(g->vi_arc.size() / g->vi_lo.size()), int(g->vi_lo.size()), nU, ci, co,
+                 g->nlat_in, g->nlat_out};
     g->on_device = true;
     return S2_OK;
 }
@@ -598,22 +660,25 @@ extern "C" int s2_grid_init(int grid_type, int nlat_in, int nlon_in, int nlat_ou
         lo = first;
         hi = last + 1;
     };
-    auto rows_ok = [](int n_rows, const std::vector<int> &blo, const std::vector<int> &n) {
-        for (int f = 0; f < n_rows; f += 4) {
-            int rmin = 1 << 30, rmax = -1;
-            for (int r = f; r < std::min(f + 4, n_rows); ++r)
-                if (n[r] > 0) {
-                    rmin = std::min(rmin, blo[r]);
-                    rmax = std::max(rmax, blo[r] + n[r] - 1);
-                }
-            if (rmax - rmin + 1 > 64) return false;
-        }
-        return true;
-    };
-    g->dt.band_rows_ok = rows_ok(nlat_out, g->band_lo, g->band_n) && rows_ok(nlat_in, g->tband_lo, g->tband_n);
     light_range(nlat_out, g->band_lo, g->band_n, g->cnt, g->band_max, g->dt.bl_lo, g->dt.bl_hi);
     light_range(nlat_in, g->tband_lo, g->tband_n, g->tcnt, g->tband_max, g->dt.tbl_lo, g->dt.tbl_hi);
 
+    build_sides(g);
+    auto rows_ok = [](const std::vector<int> &lo, const std::vector<int> &n) {
+        for (size_t f = 0; f < lo.size(); f += 4) {
+            int rmin = 1 << 30, rmax = -1;
+            for (size_t r = f; r < std::min(f + 4, lo.size()); ++r)
+                if (n[r] > 0) {
+                    rmin = std::min(rmin, lo[r]);
+                    rmax = std::max(rmax, lo[r] + n[r] - 1);
+                }
+            if (rmax - rmin + 1 > 128) return false;
+        }
+        return true;
+    };
+    const int64_t most = std::max(int64_t(nlat_in) * nlon_in, int64_t(nlat_out) * nlon_out);
+    g->dt.band_rows_ok = rows_ok(g->vo_lo, g->vo_n) && rows_ok(g->vi_lo, g->vi_n) && std::min(nlon_in, nlon_out) < 32768 &&
+                         most * 64 * 4 < (int64_t(1) << 32);
     int rc = upload_tables(g);
     if (rc != S2_OK) { delete g; return rc; }
     *out_grid = g;

@@ -14,6 +14,18 @@
 // consecutive longitude offsets centred on w' = 0 (cnt odd), or the whole
 // circle (cnt == nlon_in).  tband_*/tcnt hold the same numbers indexed by the
 // input latitude (input point -> output latitudes), used by the dk/dv gather.
+// The same relation as the tile kernels walk it (s2_nattn_walk.h), for one kind of owners: outputs (forward, dq) or inputs
+// (dk/dv).  Where the longitude counts of the two grids differ, the latitudes of the finer one are cut into interleaved
+// classes, so that owner rows and walked rows all have nU = min(nlon_in, nlon_out) columns: owner row v is latitude
+// v / c_own, longitudes c_own * u + v % c_own; the same for walked rows with c_walk.
+struct S2BandSide {
+    const int *blo, *bn;      // [n_own]         first walked row and number of walked rows of an owner row
+    const int2 *arc;          // [n_own][bmax]   (first offset, number of offsets); (0, nU): the whole circle; .y may be 0
+    int bmax, n_own, nU;
+    int c_own, c_walk;
+    int nlat_own, nlat_walk;
+};
+
 struct S2DeviceTables {
     const float *omega_rel;   // [nlat_in]   omega[h'] / max omega
     const int *band_lo;       // [nlat_out]
@@ -44,8 +56,9 @@ struct S2DeviceTables {
     // arcs are all odd and at most 57 offsets long (0, 0 if the light latitudes do not have that structure);
     // tbl_*: the same for input latitudes and the transposed bands.
     int bl_lo, bl_hi, tbl_lo, tbl_hi;
-    // fp32 band-tile kernels: on both sides the bands of any four consecutive latitudes 4 s .. 4 s + 3 together span
-    // at most 64 rows (a workgroup keeps one row per lane)
+    S2BandSide side_out, side_in;       // owners = output points, owners = input points
+    // the tile kernels apply: on both sides the walked rows of any four consecutive owner rows 4 s .. 4 s + 3 span at most
+    // 128 rows (a workgroup keeps two rows per lane), nU < 2^15, and a slice of 64 channels is below 2^32 bytes
     int band_rows_ok;
     unsigned *dev_flags;      // one word in device memory: bit 0 = a bounded wait inside a kernel ran out
     const int *st_cum;        // [st_hi - st_lo + 1]   running cost of the light latitudes (for equal-work segments)
@@ -69,6 +82,8 @@ struct s2_grid {
     std::vector<int> band_lo, band_n, cnt, tband_lo, tband_n, tcnt, row_order, trow_order, st_cum, tst_cum;
     int upscale = 1;
     std::vector<int> ucnt, ulo;      // upsampling only (see S2DeviceTables)
+    std::vector<int> vo_lo, vo_n, vi_lo, vi_n;      // S2BandSide tables, owners = outputs / inputs
+    std::vector<int2> vo_arc, vi_arc;
     int band_max = 0, tband_max = 0;
     // the band and arc tables exactly as eq. (5) gives them (introspection); the tables above, which the kernels
     // use, leave out input latitudes of weight zero (listed in zero_lat)

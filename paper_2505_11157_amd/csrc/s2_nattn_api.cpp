@@ -27,14 +27,14 @@ extern "C" size_t s2_nattn_bwd_workspace_bytes(const s2_grid_t *g, int batch, in
     return size_t(batch) * heads * g->nlat_out * g->nlon_out * sizeof(float);
 }
 
-// The fp32 band-tile kernels take the head dimensions the hand-tuned d = 32 kernels do not cover, and d = 32 itself on
-// grids whose light latitudes do not have the structure the streaming kernels need (bands of more than nine rows,
-// e.g. the 64 x 128 Gauss grid: measured 0.41 against 0.71 ms per step there, but 2.9 against 2.5 ms on the
-// 129 x 256 grid, where the streaming kernels run).
+// The fp32 band-tile kernels take everything up to 64 channels except, for d = e = 32, what the kernels written for that
+// width still do better: equal grids whose light latitudes stream, 2:1 downsampling (257 x 512 -> 129 x 256, 8 slices: 1.5
+// against 2.1 ms per step) and upsampling.
 static bool use_band(const S2DeviceTables &t, int d, int e)
 {
     if (!s2_nattn_band_supported(t, d, e) || s2_debug_flag(S2_DEBUG_NO_BAND)) return false;
-    if (d != 32 || s2_debug_flag(S2_DEBUG_FORCE_BAND)) return true;
+    if (d != 32 || e != 32 || s2_debug_flag(S2_DEBUG_FORCE_BAND)) return true;
+    if (t.pscale > 1 || t.upscale > 1) return !s2_nattn_fwd_tiled_supported(t, d, e) || !s2_nattn_bwd_tiled_supported(t, d, e);
     return !(s2_nattn_stream_supported(t, d, e) && s2_nattn_stream_dq_supported(t, d, e) &&
              s2_nattn_stream_dkdv_supported(t, d, e));
 }

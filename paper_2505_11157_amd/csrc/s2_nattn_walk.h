@@ -1,0 +1,232 @@
+// How the tile kernels of the neighborhood attention walk a neighborhood (device side, shared by the float32 and the
+// bf16 matrix-core kernels).
+//
+// Both directions and all grid ratios are one problem (S2BandSide): owners (the points a wavefront accumulates for) and
+// walked points lie on grids of the same longitude count nU.  Equal grids are that already; where one grid has r times
+// the longitudes of the other, its latitude is cut into r interleaved classes s (longitudes r u + s, u < nU), each of
+// them a row of its own.  On walked row r the neighbors of owner u are the columns u + lo .. u + lo + cnt - 1 around the
+// circle of nU.
+//
+// A workgroup of four wavefronts owns OW consecutive columns of FOUR consecutive owner rows, one row per wavefront, and
+// walks the union of the four bands row by row in stages of SW = OW + 64 columns held in LDS:
+//   * rows whose arcs all fit (union of at most kSpan offsets) are ONE stage that holds the window of all owners; every
+//     16-owner tile walks its own key tiles from the first column of its band rounded down to a multiple of four;
+//   * rows with longer arcs or whole circles are walked in stages on a common 16-column grid: over the linear window
+//     while that is shorter than the circle, else over the circle itself, every column once, with distances taken
+//     around the circle.
+// For 16 owners the walked columns of one row form a band of the 16 x 16 score tiles: a tile the band does not touch is
+// skipped (wavefront-uniform), a tile it cuts gets a per-element mask, a tile inside it none.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include "s2_internal.h"
+
+namespace s2walk {
+
+constexpr int kSpan = 57;            // widest union of arcs that is served by a single stage
+
+__device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }
+__device__ __forceinline__ int imax(int a, int b) { return a > b ? a : b; }
+
+// x mod n for 0 <= x < 2^22: the float32 quotient is off by at most one
+__device__ __forceinline__ int wrap_col(int x, int n, float inv_n)
+{
+    const int r = x - int(float(x) * inv_n) * n;
+    return r < 0 ? r + n : r >= n ? r - n : r;
+}
+
+// (Xs + col) mod n, Xs uniform and below 4 n (2^22), 0 <= col < width
+__device__ __forceinline__ int wrap_stage(int Xs, int col, int width, int n, float inv_n)
+{
+    if (n < width) return wrap_col(Xs + col, n, inv_n);
+    int x = Xs >= 2 * n ? Xs - 2 * n : Xs;
+    x = (x >= n ? x - n : x) + col;
+    return x >= n ? x - n : x;
+}
+
+// polar segments (the heaviest) first, from both ends
+__device__ __forceinline__ int segment_of(int sk, int nseg) { return (sk & 1) ? nseg - 1 - (sk >> 1) : (sk >> 1); }
+
+// Rows a workgroup has to stage and their metadata, read from the grid tables once and kept one row per lane in two sets of
+// registers (a table read inside the row loop would be a vector load whose wait also waits for the prefetch in flight):
+// at most kMaxRows rows, longitude counts below 2^15.
+constexpr int kMaxRows = 128;
+struct BandRows {
+    int rmin, rmax;          // of the whole union
+    int arc_v[2];            // row rmin + 64 s + lane: own arc, first offset (low half) and number of offsets
+    int uni_v[2];            // ... first and last offset over the four owner rows (last < first: no arc; 0x7fff: the circle)
+    float omega_v[2];        // ... the row's relative quadrature weight (1 where the owners carry the weight)
+
+    __device__ __forceinline__ void load(const S2BandSide &b, int first, int own, const float *omega_rel, int lane)
+    {
+        rmin = 1 << 30;
+        rmax = -1;
+        for (int w = 0; w < 4; ++w) {
+            if (first + w >= b.n_own) break;
+            const int lo = b.blo[first + w], n = b.bn[first + w];
+            if (n > 0) {
+                rmin = imin(rmin, lo);
+                rmax = imax(rmax, lo + n - 1);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int r = rmin + 64 * s + lane;
+            int wlo = 0x7ffe, whi = -0x7fff;
+            arc_v[s] = 0;
+            omega_v[s] = 1.f;
+            if (64 * s <= rmax - rmin) {
+                for (int w = 0; w < 4; ++w) {
+                    const int vl = first + w;
+                    if (vl >= b.n_own) break;
+                    const int i = r - b.blo[vl];
+                    if (r <= rmax && i >= 0 && i < b.bn[vl]) {
+                        const int2 a = b.arc[vl * b.bmax + i];
+                        if (a.y > 0) {
+                            wlo = imin(wlo, a.x);
+                            whi = imax(whi, a.y >= b.nU ? 0x7fff : a.x + a.y - 1);
+                            if (vl == own) arc_v[s] = (a.x & 0xffff) | a.y << 16;
+                        }
+                    }
+                }
+                if (omega_rel && r <= rmax) omega_v[s] = omega_rel[r / b.c_walk];
+            }
+            uni_v[s] = (wlo & 0xffff) | whi << 16;
+        }
+    }
+    __device__ __forceinline__ int pick(const int (&v)[2], int r) const
+    {
+        const int i = r - rmin, x = __builtin_amdgcn_readlane(v[0], i & 63), y = __builtin_amdgcn_readlane(v[1], i & 63);
+        return i < 64 ? x : y;
+    }
+    __device__ __forceinline__ void arc(int r, int &lo, int &cnt) const
+    {
+        const int a = pick(arc_v, r);
+        lo = int(short(a & 0xffff));
+        cnt = a >> 16;
+    }
+    __device__ __forceinline__ float weight(int r) const
+    {
+        const int v[2] = {__builtin_bit_cast(int, omega_v[0]), __builtin_bit_cast(int, omega_v[1])};
+        return __builtin_bit_cast(float, pick(v, r));
+    }
+};
+
+// How one row is walked: first staged (unwrapped) column, end of the columns that count, number of stages, and whether
+// key tiles lie on the common grid (multi) and distances are taken around the circle (circle).  Unwrapped columns carry
+// an offset of nU, so that they stay non-negative; the owners sit at nU + W0 ... = Wb ....
+struct RowPlan {
+    int Xs0, Xend, nst;
+    bool multi, circle;
+    template <int OW, int SW>
+    __device__ __forceinline__ void set(const BandRows &rows, int r, int nU, int Wb)
+    {
+        const int u = rows.pick(rows.uni_v, r), wlo = int(short(u & 0xffff)), whi = u >> 16;
+        const bool full = whi == 0x7fff;
+        const int width = whi - wlo + 1;
+        if (width <= 0) {                    // no owner meets this row
+            multi = circle = false;
+            Xs0 = Xend = nst = 0;
+        } else if (!full && width <= kSpan) {
+            multi = circle = false;
+            Xs0 = (Wb + wlo) & ~3;
+            Xend = Xs0 + SW + 32;
+            nst = 1;
+        } else {
+            multi = true;
+            circle = full || OW + width + 31 >= nU;
+            Xs0 = circle ? nU : (Wb + wlo) & ~15;
+            Xend = circle ? 2 * nU : Wb + OW + whi;
+            nst = (Xend - Xs0 + SW - 1) / SW;
+        }
+    }
+};
+
+// The stages of a workgroup in order.
+struct Walker {
+    BandRows rows;
+    RowPlan cur;
+    int r, s;                            // current row and its current stage
+    template <int OW, int SW>
+    __device__ __forceinline__ bool settle(int nU, int Wb)
+    {
+        for (; r <= rows.rmax; ++r) {
+            cur.template set<OW, SW>(rows, r, nU, Wb);
+            if (cur.nst > 0) return true;
+        }
+        return false;
+    }
+    template <int OW, int SW>
+    __device__ __forceinline__ bool start(const S2BandSide &b, int first, int own, const float *omega_rel, int lane, int Wb)
+    {
+        rows.load(b, first, own, omega_rel, lane);
+        s = 0;
+        r = rows.rmin;
+        return settle<OW, SW>(b.nU, Wb);
+    }
+    template <int OW, int SW>
+    __device__ __forceinline__ bool next(int nU, int Wb)
+    {
+        if (++s < cur.nst) return true;
+        s = 0;
+        ++r;
+        return settle<OW, SW>(nU, Wb);
+    }
+};
+
+// Position of a key tile (columns Xt .. Xt + 15) relative to 16 owners at Wo: b = smallest offset in the tile minus the
+// arc's first offset (around the circle where the plan says so), whether the band touches it, whether it needs the mask.
+// KIND: rows whose tiles follow their owners (kOwnTiles), rows on the common grid (kGridTiles), or either (kAnyTiles: one
+// copy of the tile loop for both, for kernels that have no registers left for two).
+enum { kOwnTiles, kGridTiles, kAnyTiles };
+template <int KIND>
+__device__ __forceinline__ bool on_grid(const RowPlan &p) { return KIND == kAnyTiles ? p.multi : KIND == kGridTiles; }
+template <int KIND>
+struct TilePos {
+    int b;
+    bool touch, mask, tail;              // tail: columns past Xend inside the tile
+    __device__ __forceinline__ void set(const RowPlan &p, int Xt, int Wo, int lo, int cnt, int nU)
+    {
+        b = Xt - Wo - lo - 15;
+        tail = false;
+        if (KIND != kOwnTiles && p.circle) {
+            if (nU < 32) {
+                b = (b + 16 * nU) % nU;
+            } else {
+                b = b < 0 ? b + nU : b;
+                b = b < 0 ? b + nU : b;
+                b = b >= nU ? b - nU : b;
+                b = b >= nU ? b - nU : b;
+            }
+            tail = Xt + 16 > p.Xend;
+            touch = b < cnt || b + 30 >= nU;                    // always for a whole circle: b < nU = cnt
+            mask = tail || (cnt < nU && b + 30 >= cnt);
+        } else {
+            touch = KIND == kOwnTiles || (b + 30 >= 0 && b < cnt);       // a row of its own tiles starts and ends with the band
+            mask = b < 0 || b + 30 >= cnt;
+        }
+    }
+};
+// keep[rr]: is column Xt + k0 + rr a neighbor of owner Wo + n.
+template <int N, int KIND>
+__device__ __forceinline__ void band_mask(bool (&keep)[N], const RowPlan &p, const TilePos<KIND> &tp, int Xt, int cnt, int nU,
+                                          int k0, int n)
+{
+    const int uu = tp.b + k0 - n + 15;
+    if (KIND != kOwnTiles && p.circle && (tp.tail || nU < 32)) {
+        const int nvalid = p.Xend - Xt - k0;
+#pragma unroll
+        for (int rr = 0; rr < N; ++rr) keep[rr] = unsigned((uu + rr) % nU) < unsigned(cnt) && rr < nvalid;
+    } else if (KIND != kOwnTiles && p.circle) {
+#pragma unroll
+        for (int rr = 0; rr < N; ++rr) {
+            const int v = uu + rr;
+            keep[rr] = unsigned(v >= nU ? v - nU : v) < unsigned(cnt);
+        }
+    } else {
+#pragma unroll
+        for (int rr = 0; rr < N; ++rr) keep[rr] = unsigned(uu + rr) < unsigned(cnt);
+    }
+}
+
+}  // namespace s2walk

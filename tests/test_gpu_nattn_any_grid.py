@@ -1,0 +1,53 @@
+"""GPU parity of the tile kernels away from the longitude counts and grid pairs they were first written for: the edges of
+tiles, stages, classes and row tables, float32 and bf16 tensors, against the float64 oracle."""
+import math
+
+import pytest
+
+from paper_2505_11157_amd.workloads import make_inputs
+from test_gpu_nattn import C_DERIVED, run_case
+from test_gpu_nattn_bf16 import run_bf16
+
+pytestmark = pytest.mark.gpu
+
+
+def _c(gt, lat_in, lon_in, lat_out, lon_out, theta, heads=2, d=16):
+    return dict(kind="nattn", grid_type=gt, nlat_in=lat_in, nlon_in=lon_in, nlat_out=lat_out, nlon_out=lon_out, theta=theta,
+                batch=1, heads=heads, d=d, dtype="f32")
+
+
+SHAPES = [
+    # odd longitude counts: short arcs only / arcs on the common grid / whole circles with a ragged last tile
+    _c(0, 33, 65, 33, 65, 0.25), _c(0, 19, 129, 19, 129, 0.5, d=32), _c(1, 12, 101, 12, 101, 1.3, d=64),
+    # fewer longitudes than a tile, than 32, than a stage; one longitude
+    _c(0, 9, 10, 9, 10, 0.9), _c(0, 9, 17, 9, 17, 0.6, d=64), _c(1, 16, 31, 16, 31, 0.8, d=32), _c(0, 17, 33, 17, 33, math.pi),
+    _c(1, 4, 1, 4, 1, 0.9),
+    # channel counts between the instantiated ones
+    _c(0, 17, 40, 17, 40, 0.4, d=24), _c(0, 17, 45, 17, 45, 0.4, d=7), _c(1, 12, 26, 12, 26, 0.6, d=50),
+    # classes of a finer grid: ratio 2 with even and odd counts, 3, whole circles, either direction
+    _c(0, 33, 66, 17, 33, 0.4), _c(0, 17, 33, 33, 66, 0.4), _c(1, 24, 96, 12, 48, 0.5, d=64), _c(1, 12, 48, 24, 96, 0.5, d=64),
+    _c(0, 25, 93, 13, 31, 0.45, d=32), _c(0, 13, 31, 25, 93, 0.45, d=32), _c(0, 9, 24, 5, 12, math.pi), _c(3, 5, 12, 9, 24, math.pi),
+    # more than 64 walked rows per workgroup (two registers per lane), and exactly 64
+    _c(0, 97, 16, 97, 16, 1.2), _c(0, 66, 12, 66, 12, math.pi), _c(0, 65, 32, 33, 16, 1.2), _c(1, 64, 8, 64, 8, math.pi),
+    # a zero-weight pole row on a grid pair with classes
+    _c(2, 24, 56, 12, 28, 0.5), _c(2, 12, 28, 24, 56, 0.6),
+]
+
+
+@pytest.mark.parametrize("ci", range(len(SHAPES)))
+def test_any_grid_f32(ci):
+    c, arrs = make_inputs(SHAPES[ci], seed=4100 + ci)
+    run_case(c, arrs, range(2), C=C_DERIVED, case="any%d" % ci)
+
+
+@pytest.mark.parametrize("ci", range(len(SHAPES)))
+def test_any_grid_bf16(ci):
+    c, arrs = make_inputs(dict(SHAPES[ci], dtype="bf16"), seed=4200 + ci)
+    run_bf16(c, arrs, range(2), "any-bf16-%d" % ci)
+
+
+@pytest.mark.parametrize("batch,heads,d", [(4, 8, 16), (4, 8, 32), (4, 8, 64), (3, 5, 16)])
+def test_any_grid_many_slices(batch, heads, d):
+    # enough workgroups for several owner tiles per wavefront, on an odd longitude count
+    c, arrs = make_inputs(dict(_c(0, 41, 75, 41, 75, 0.3, d=d), batch=batch, heads=heads), seed=4300 + d)
+    run_case(c, arrs, [0, batch * heads - 1], C=C_DERIVED, case="any-many[d%d]" % d)
