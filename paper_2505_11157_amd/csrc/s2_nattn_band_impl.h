@@ -47,22 +47,6 @@ struct Geo {
     static_assert(PITCH % 32 == 16, "geometry");
 };
 
-__device__ __forceinline__ float ldx(const float *p) { return *p; }
-__device__ __forceinline__ float ldx(const bf16raw *p) { return __builtin_bit_cast(float, unsigned(*p) << 16); }
-__device__ __forceinline__ void stx(float *p, float x) { *p = x; }
-__device__ __forceinline__ void stx(bf16raw *p, float x)          // round to nearest even
-{
-    const unsigned u = __builtin_bit_cast(unsigned, x);
-    *p = bf16raw((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
-}
-__device__ __forceinline__ f32x4 ld4(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
-__device__ __forceinline__ f32x4 ld4(const bf16raw *p)
-{
-    const uint2 w = *reinterpret_cast<const uint2 *>(p);
-    return f32x4{__builtin_bit_cast(float, w.x << 16), __builtin_bit_cast(float, w.x & 0xffff0000u),
-                 __builtin_bit_cast(float, w.y << 16), __builtin_bit_cast(float, w.y & 0xffff0000u)};
-}
-
 __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -94,183 +78,64 @@ __device__ __forceinline__ void settle(f32x4 (&a)[N])
     asm volatile("s_nop 9" : "+v"(a[N - 1]));
 }
 
-struct BandArgs {
-    S2BandSide b;
-    const float *omega_rel;
-    float ln_omega_ref, omega_ref, scale;
-    int nbh, d, e;
-};
-
-// Where a wavefront's owners and the walked rows lie.
-struct BandWhere {
-    int nU, W0, Wb, grp, bh, first, own, lane, wave, n, g, tid;
-    bool active;
-    float inv_nU;
-    size_t plane_own, plane_walk;
-    size_t own_at;                 // offset of owner column 0 of the wavefront's row inside a plane
-    int nlon_walk, c_own, c_walk;
-    template <int OW>
-    __device__ __forceinline__ void set(const BandArgs &a)
-    {
-        nU = a.b.nU;
-        const int ngrp = (nU + OW - 1) / OW, nseg = (a.b.n_own + 3) >> 2;
-        int id = blockIdx.x;
-        grp = id % ngrp; id /= ngrp;
-        bh = id % a.nbh;
-        first = 4 * segment_of(id / a.nbh, nseg);
-        tid = threadIdx.x; lane = tid & 63; wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-        n = lane & 15; g = lane >> 4;
-        own = first + wave;
-        active = own < a.b.n_own;
-        W0 = grp * OW; Wb = nU + W0;
-        inv_nU = 1.f / float(nU);
-        c_own = a.b.c_own; c_walk = a.b.c_walk;
-        nlon_walk = nU * c_walk;
-        plane_own = size_t(a.b.nlat_own) * nU * c_own;
-        plane_walk = size_t(a.b.nlat_walk) * nlon_walk;
-        const int lat = own / c_own;
-        own_at = size_t(lat) * nU * c_own + (own - lat * c_own);
-    }
-    // offset of column 0 of walked row r inside a plane
-    __device__ __forceinline__ size_t walk_at(int r) const
-    {
-        if (c_walk == 1) return size_t(r) * nlon_walk;
-        const int lat = r / c_walk;
-        return size_t(lat) * nlon_walk + (r - lat * c_walk);
-    }
-};
-
-// One tensor's stage in registers, and its way to LDS.  The 32-bit offset of a lane inside a channel plane is computed once
-// per stage and serves all channels and both tensors (scalar base + vector offset addressing).
-template <int SW, bool WIDE>
-struct StageCols;
-template <int SW>
-struct StageCols<SW, true> {
-    int Xr;                              // first staged column, reduced to one turn
-    __device__ __forceinline__ void set(const BandWhere &w, int Xs)
-    {
-        Xr = Xs >= 2 * w.nU ? Xs - 2 * w.nU : Xs;
-        Xr = Xr >= w.nU ? Xr - w.nU : Xr;
-    }
-};
-template <>
-struct StageCols<128, true> {            // 32 pieces: half a wavefront on one channel
-    unsigned off;
-    __device__ __forceinline__ void set(const BandWhere &w, int Xs)
-    {
-        const int pc = w.lane & 31;
-        off = wrap_stage(Xs, 4 * pc, 128, w.nU, w.inv_nU) + (w.lane >> 5) * unsigned(w.plane_walk);
-    }
-};
-template <int SW>
-struct StageCols<SW, false> {            // a wavefront on 64 columns of one channel
-    static constexpr int NC = (SW + 63) / 64;
-    unsigned off[NC];
-    __device__ __forceinline__ void set(const BandWhere &w, int Xs)
-    {
-#pragma unroll
-        for (int i = 0; i < NC; ++i) {
-            const int col = w.lane + 64 * i;
-            off[i] = w.c_walk * wrap_stage(Xs, col < SW ? col : 0, SW, w.nU, w.inv_nU);
-        }
-    }
-};
+// One tensor's stage in registers, and its way to LDS.
 template <int D, int NO, int MODE>
-struct Stage;
-template <int D, int NO>
-struct Stage<D, NO, kWide> {             // pieces dealt out to the threads channel by channel
-    using G = Geo<D, NO>;
-    static constexpr int P4 = G::SW / 4, NP = (D * P4 + 255) / 256;
-    static constexpr bool EVEN = D * P4 % 256 == 0;
-    f32x4 r[NP];
-    template <class T>
-    __device__ __forceinline__ void load(const BandWhere &w, const StageCols<G::SW, true> &cols, const T *row, int)
-    {
-#pragma unroll
-        for (int j = 0; j < NP; ++j) {
-            const int i = w.tid + 256 * j, c = EVEN ? i / P4 : imin(i / P4, D - 1), pc = i % P4;
-            int x = cols.Xr + 4 * pc;
-            x = x >= w.nU ? x - w.nU : x;
-            if (w.nU < G::SW) x = wrap_col(x, w.nU, w.inv_nU);
-            r[j] = ld4(row + (unsigned(c) * unsigned(w.plane_walk) + unsigned(x)));
-        }
-    }
-    __device__ __forceinline__ void store(const BandWhere &w, float *tile, int, float factor = 1.f) const
-    {
-#pragma unroll
-        for (int j = 0; j < NP; ++j) {
-            const int i = w.tid + 256 * j, c = i / P4, pc = i % P4;
-            if (EVEN || i < D * P4) *reinterpret_cast<f32x4 *>(tile + c * G::PITCH + 4 * ((c >> 2) & 3) + 4 * pc) = r[j] * factor;
-        }
-    }
-};
-template <int D>
-struct Stage<D, 4, kWide> {
-    using G = Geo<D, 4>;
-    static_assert(G::SW == 128, "a row in 32 pieces");
-    static constexpr int NJ = D / 8;
-    f32x4 r[NJ];
-    template <class T>
-    __device__ __forceinline__ void load(const BandWhere &w, const StageCols<128, true> &cols, const T *row, int)
-    {
-        size_t step = w.plane_walk;
-        asm volatile("" : "+s"(step));       // else the compiler keeps every channel's address in (spilled) scalar registers
-        const T *p = row + 2 * w.wave * step;
-#pragma unroll
-        for (int j = 0; j < NJ; ++j, p += 8 * step) r[j] = ld4(p + cols.off);
-    }
-    __device__ __forceinline__ void store(const BandWhere &w, float *tile, int, float factor = 1.f) const
-    {
-        const int pc = w.lane & 31, c0 = 2 * w.wave + (w.lane >> 5);
-        float *p = tile + c0 * G::PITCH + 4 * (c0 >> 2) + 4 * pc;            // c0 < 8
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) *reinterpret_cast<f32x4 *>(p + 8 * j * G::PITCH + 8 * (j & 1)) = r[j] * factor;
-    }
-};
-template <int D, int NO, int MODE>           // kNarrow, kRagged
 struct Stage {
     using G = Geo<D, NO>;
-    static constexpr int NC = StageCols<G::SW, false>::NC, NJ = D / 4;
-    float r[NJ][NC];
-    template <class T>
-    __device__ __forceinline__ void load(const BandWhere &w, const StageCols<G::SW, false> &cols, const T *row, int nch)
+    using Idx = StageIdx<float, D, G::SW, MODE>;
+    static constexpr bool WIDE = MODE == kWide;
+    static constexpr int NC = Idx::NC, NJ = D / 4;
+    std::conditional_t<WIDE, f32x4, float> r[WIDE ? Idx::NP : NJ * NC];
+    __device__ __forceinline__ void load(const BandWhere &w, const Idx &at, const float *row, int nch)
     {
-        size_t step = w.plane_walk;
-        asm volatile("" : "+s"(step));
-        int c = MODE == kRagged ? imin(w.wave, nch - 1) : w.wave;
-        const T *p = row + c * step;
+        if constexpr (WIDE) {
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
+            for (int j = 0; j < Idx::NP; ++j) r[j] = load_at<f32x4>(row, at.off[j]);
+        } else {
+            size_t step = w.plane_walk;
+            asm volatile("" : "+s"(step));   // else the compiler keeps every channel's address in (spilled) scalar registers
+            int c = MODE == kRagged ? imin(w.wave, nch - 1) : w.wave;
+            const float *p = row + c * step;
 #pragma unroll
-            for (int i = 0; i < NC; ++i) r[j][i] = ldx(p + cols.off[i]);
-            // past the last channel: that channel again (not stored); a branch around a load would make the compiler wait
-            // for all loads in flight where its sides meet
-            const int up = MODE == kRagged ? imin(w.wave + 4 * j + 4, nch - 1) - c : 4;
-            p += up * step;
-            c += up;
+            for (int j = 0; j < NJ; ++j) {
+#pragma unroll
+                for (int i = 0; i < NC; ++i) r[j * NC + i] = load_at<float>(p, at.off[i]);
+                // past the last channel: that channel again (not stored); a branch around a load would make the compiler
+                // wait for all loads in flight where its sides meet
+                const int up = MODE == kRagged ? imin(w.wave + 4 * j + 4, nch - 1) - c : 4;
+                p += up * step;
+                c += up;
+            }
         }
     }
     __device__ __forceinline__ void store(const BandWhere &w, float *tile, int nch, float factor = 1.f) const
     {
-        float *p = tile + w.wave * G::PITCH + w.lane;
+        if constexpr (WIDE) {
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            if (MODE == kRagged && w.wave + 4 * j >= nch) break;
+            for (int j = 0; j < Idx::NP; ++j) {
+                const int i = w.tid + 256 * j, c = i / Idx::P4, pc = i % Idx::P4;
+                if (Idx::EVEN || i < D * Idx::P4)
+                    *reinterpret_cast<f32x4 *>(tile + c * G::PITCH + 4 * ((c >> 2) & 3) + 4 * pc) = r[j] * factor;
+            }
+        } else {
+            float *p = tile + w.wave * G::PITCH + w.lane;
 #pragma unroll
-            for (int i = 0; i < NC; ++i)
-                if (64 * i + 64 <= G::SW || w.lane + 64 * i < G::SW) p[4 * j * G::PITCH + 4 * (j & 3) + 64 * i] = r[j][i] * factor;
+            for (int i = 0; i < NC; ++i) {
+                if (64 * i + 64 > G::SW && w.lane + 64 * i >= G::SW) break;
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+                    if (MODE != kRagged || w.wave + 4 * j < nch)
+                        p[4 * j * G::PITCH + 4 * (j & 3) + 64 * i] = r[j * NC + i] * factor;
+            }
         }
     }
 };
-// is channel c one of the tensor's nch
-template <int MODE>
-__device__ __forceinline__ bool has(int c, int nch) { return MODE != kRagged || c < nch; }
 
 // ---------------------------------------------------------------------------------------------------------------
 // Forward.
-template <class T, int D, int NO, int MODE>
+template <int D, int NO, int MODE>
 __global__ void __launch_bounds__(256, 2)
-nattn_fwd_band(BandArgs a, const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, T *__restrict__ out,
+nattn_fwd_band(BandArgs a, const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v, float *__restrict__ out,
                float *__restrict__ lse)
 {
     using G = Geo<D, NO>;
@@ -280,8 +145,8 @@ nattn_fwd_band(BandArgs a, const T *__restrict__ q, const T *__restrict__ k, con
     w.set<G::OW>(a);
     const int nU = w.nU, n = w.n, g = w.g;
     const float c2 = a.scale * kLog2e;
-    const T *qs = q + size_t(w.bh) * (MODE == kRagged ? a.d : D) * w.plane_own + w.own_at;
-    const T *ks = k + size_t(w.bh) * (MODE == kRagged ? a.d : D) * w.plane_walk, *vs = v + size_t(w.bh) * (MODE == kRagged ? a.e : D) * w.plane_walk;
+    const float *qs = q + size_t(w.bh) * (MODE == kRagged ? a.d : D) * w.plane_own + w.own_at;
+    const float *ks = k + size_t(w.bh) * (MODE == kRagged ? a.d : D) * w.plane_walk, *vs = v + size_t(w.bh) * (MODE == kRagged ? a.e : D) * w.plane_walk;
 
     float qreg[NO][D / 4];
     f32x4 acc[NO][D / 16];
@@ -292,21 +157,22 @@ nattn_fwd_band(BandArgs a, const T *__restrict__ q, const T *__restrict__ k, con
         const bool own = w.active && u < nU;
 #pragma unroll
         for (int kb = 0; kb < D / 4; ++kb)
-            qreg[o][kb] = own && has<MODE>(4 * kb + g, a.d) ? ldx(qs + size_t(4 * kb + g) * w.plane_own + w.c_own * u) : 0.f;
+            qreg[o][kb] = own && has<MODE>(4 * kb + g, a.d) ? *(qs + size_t(4 * kb + g) * w.plane_own + w.c_own * u) : 0.f;
 #pragma unroll
         for (int mt = 0; mt < D / 16; ++mt) acc[o][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
         m[o] = kMinRef;
         l[o] = 0.f;
     }
     Walker wk;
-    StageCols<G::SW, MODE == kWide> cols;
+    typename Stage<D, NO, MODE>::Idx at;
+    at.init(w);
     Stage<D, NO, MODE> rk, rv;
     bool more = wk.start<G::OW, G::SW>(a.b, w.first, w.own, a.omega_rel, w.lane, w.Wb);
     if (more) {
         const size_t row = w.walk_at(wk.r);
-        cols.set(w, wk.cur.Xs0);
-        rk.load(w, cols, ks + row, a.d);
-        rv.load(w, cols, vs + row, a.e);
+        at.set(w, wk.cur.Xs0);
+        rk.load(w, at, ks + row, a.d);
+        rv.load(w, at, vs + row, a.e);
     }
     for (int i = w.tid; i < 2 * G::TILE; i += 256) lds[i] = 0.f;
     while (more) {
@@ -322,9 +188,9 @@ nattn_fwd_band(BandArgs a, const T *__restrict__ q, const T *__restrict__ k, con
         more = wk.next<G::OW, G::SW>(nU, w.Wb);
         if (more) {
             const size_t row = w.walk_at(wk.r);
-            cols.set(w, wk.cur.Xs0 + wk.s * G::SW);
-            rk.load(w, cols, ks + row, a.d);
-            rv.load(w, cols, vs + row, a.e);
+            at.set(w, wk.cur.Xs0 + wk.s * G::SW);
+            rk.load(w, at, ks + row, a.d);
+            rv.load(w, at, vs + row, a.e);
         }
         if (cnt <= 0) continue;
         // one copy of the tile loop for rows on the common grid, one for rows whose tiles follow their owners (backward: one
@@ -394,12 +260,12 @@ nattn_fwd_band(BandArgs a, const T *__restrict__ q, const T *__restrict__ k, con
         const int u = w.W0 + 16 * o + n;
         if (u >= nU) continue;
         const float inv = 1.f / lt;
-        T *ob = out + size_t(w.bh) * (MODE == kRagged ? a.e : D) * w.plane_own + w.own_at + w.c_own * u;
+        float *ob = out + size_t(w.bh) * (MODE == kRagged ? a.e : D) * w.plane_own + w.own_at + w.c_own * u;
 #pragma unroll
         for (int mt = 0; mt < D / 16; ++mt)
 #pragma unroll
             for (int rr = 0; rr < 4; ++rr)
-                if (has<MODE>(16 * mt + 4 * g + rr, a.e)) stx(ob + size_t(16 * mt + 4 * g + rr) * w.plane_own, acc[o][mt][rr] * inv);
+                if (has<MODE>(16 * mt + 4 * g + rr, a.e)) *(ob + size_t(16 * mt + 4 * g + rr) * w.plane_own) = acc[o][mt][rr] * inv;
         if (g == 0)
             lse[size_t(w.bh) * w.plane_own + w.own_at + w.c_own * u] = (m[o] + log2f(lt * a.omega_ref)) * 0.6931471805599453f;
     }
@@ -407,10 +273,10 @@ nattn_fwd_band(BandArgs a, const T *__restrict__ q, const T *__restrict__ k, con
 
 // ---------------------------------------------------------------------------------------------------------------
 // Backward, query side: dq and D_i = dout_i . out_i (written for the key-side launch).
-template <class T, int D, int NO, int MODE>
+template <int D, int NO, int MODE>
 __global__ void __launch_bounds__(256, 2)
-nattn_bwd_dq_band(BandArgs a, const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
-                  const T *__restrict__ o_, const float *__restrict__ lse, const T *__restrict__ go, T *__restrict__ dq,
+nattn_bwd_dq_band(BandArgs a, const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
+                  const float *__restrict__ o_, const float *__restrict__ lse, const float *__restrict__ go, float *__restrict__ dq,
                   float *__restrict__ Dws)
 {
     using G = Geo<D, NO>;
@@ -421,7 +287,7 @@ nattn_bwd_dq_band(BandArgs a, const T *__restrict__ q, const T *__restrict__ k, 
     const int nU = w.nU, n = w.n, g = w.g;
     const float c2 = a.scale * kLog2e;
     const size_t slice_q = size_t(w.bh) * (MODE == kRagged ? a.d : D) * w.plane_own + w.own_at, slice_o = size_t(w.bh) * (MODE == kRagged ? a.e : D) * w.plane_own + w.own_at;
-    const T *ks = k + size_t(w.bh) * (MODE == kRagged ? a.d : D) * w.plane_walk, *vs = v + size_t(w.bh) * (MODE == kRagged ? a.e : D) * w.plane_walk;
+    const float *ks = k + size_t(w.bh) * (MODE == kRagged ? a.d : D) * w.plane_walk, *vs = v + size_t(w.bh) * (MODE == kRagged ? a.e : D) * w.plane_walk;
 
     float qreg[NO][D / 4], greg[NO][D / 4];
     f32x4 acc[NO][D / 16];
@@ -439,9 +305,9 @@ nattn_bwd_dq_band(BandArgs a, const T *__restrict__ q, const T *__restrict__ k, 
         for (int kb = 0; kb < D / 4; ++kb) {
             const int c = 4 * kb + g;
             const size_t at = size_t(c) * w.plane_own + w.c_own * u;
-            qreg[o][kb] = own && has<MODE>(c, a.d) ? ldx(q + slice_q + at) : 0.f;
-            greg[o][kb] = own && has<MODE>(c, a.e) ? ldx(go + slice_o + at) : 0.f;
-            dsum = fmaf(greg[o][kb], own && has<MODE>(c, a.e) ? ldx(o_ + slice_o + at) : 0.f, dsum);
+            qreg[o][kb] = own && has<MODE>(c, a.d) ? *(q + slice_q + at) : 0.f;
+            greg[o][kb] = own && has<MODE>(c, a.e) ? *(go + slice_o + at) : 0.f;
+            dsum = fmaf(greg[o][kb], own && has<MODE>(c, a.e) ? *(o_ + slice_o + at) : 0.f, dsum);
         }
         dsum = group_sum(dsum);
         if (own) {
@@ -452,14 +318,15 @@ nattn_bwd_dq_band(BandArgs a, const T *__restrict__ q, const T *__restrict__ k, 
         }
     }
     Walker wk;
-    StageCols<G::SW, MODE == kWide> cols;
+    typename Stage<D, NO, MODE>::Idx at;
+    at.init(w);
     Stage<D, NO, MODE> rk, rv;
     bool more = wk.start<G::OW, G::SW>(a.b, w.first, w.own, a.omega_rel, w.lane, w.Wb);
     if (more) {
         const size_t row = w.walk_at(wk.r);
-        cols.set(w, wk.cur.Xs0);
-        rk.load(w, cols, ks + row, a.d);
-        rv.load(w, cols, vs + row, a.e);
+        at.set(w, wk.cur.Xs0);
+        rk.load(w, at, ks + row, a.d);
+        rv.load(w, at, vs + row, a.e);
     }
     for (int i = w.tid; i < 2 * G::TILE; i += 256) lds[i] = 0.f;
     while (more) {
@@ -475,9 +342,9 @@ nattn_bwd_dq_band(BandArgs a, const T *__restrict__ q, const T *__restrict__ k, 
         more = wk.next<G::OW, G::SW>(nU, w.Wb);
         if (more) {
             const size_t row = w.walk_at(wk.r);
-            cols.set(w, wk.cur.Xs0 + wk.s * G::SW);
-            rk.load(w, cols, ks + row, a.d);
-            rv.load(w, cols, vs + row, a.e);
+            at.set(w, wk.cur.Xs0 + wk.s * G::SW);
+            rk.load(w, at, ks + row, a.d);
+            rv.load(w, at, vs + row, a.e);
         }
         if (cnt <= 0) continue;
         // one copy of the tile loop for rows on the common grid, one for rows whose tiles follow their owners (backward: one
@@ -530,23 +397,23 @@ nattn_bwd_dq_band(BandArgs a, const T *__restrict__ q, const T *__restrict__ k, 
     for (int o = 0; o < NO; ++o) {
         const int u = w.W0 + 16 * o + n;
         if (u >= nU) continue;
-        T *ob = dq + slice_q + w.c_own * u;
+        float *ob = dq + slice_q + w.c_own * u;
 #pragma unroll
         for (int mt = 0; mt < D / 16; ++mt)
 #pragma unroll
             for (int rr = 0; rr < 4; ++rr)
-                if (has<MODE>(16 * mt + 4 * g + rr, a.d)) stx(ob + size_t(16 * mt + 4 * g + rr) * w.plane_own, acc[o][mt][rr] * a.scale);
+                if (has<MODE>(16 * mt + 4 * g + rr, a.d)) *(ob + size_t(16 * mt + 4 * g + rr) * w.plane_own) = acc[o][mt][rr] * a.scale;
     }
 }
 
 // ---------------------------------------------------------------------------------------------------------------
 // Backward, key side: owners are input points, the transposed band gives the output latitudes; q, dout, lse and D
 // of a stage's outputs are staged together.
-template <class T, int D, int NO, int MODE>
+template <int D, int NO, int MODE>
 __global__ void __launch_bounds__(256, 2)
-nattn_bwd_dkdv_band(BandArgs a, const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
-                    const float *__restrict__ lse, const T *__restrict__ go, const float *__restrict__ Dws,
-                    T *__restrict__ dk, T *__restrict__ dv)
+nattn_bwd_dkdv_band(BandArgs a, const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
+                    const float *__restrict__ lse, const float *__restrict__ go, const float *__restrict__ Dws,
+                    float *__restrict__ dk, float *__restrict__ dv)
 {
     using G = Geo<D, NO>;
     extern __shared__ __attribute__((aligned(16))) float lds[];
@@ -556,7 +423,7 @@ nattn_bwd_dkdv_band(BandArgs a, const T *__restrict__ q, const T *__restrict__ k
     const int nU = w.nU, n = w.n, g = w.g;
     const float c2 = a.scale * kLog2e, lref = a.ln_omega_ref;
     const size_t slice_k = size_t(w.bh) * (MODE == kRagged ? a.d : D) * w.plane_own + w.own_at, slice_v = size_t(w.bh) * (MODE == kRagged ? a.e : D) * w.plane_own + w.own_at;
-    const T *qs = q + size_t(w.bh) * (MODE == kRagged ? a.d : D) * w.plane_walk, *gs = go + size_t(w.bh) * (MODE == kRagged ? a.e : D) * w.plane_walk;
+    const float *qs = q + size_t(w.bh) * (MODE == kRagged ? a.d : D) * w.plane_walk, *gs = go + size_t(w.bh) * (MODE == kRagged ? a.e : D) * w.plane_walk;
     const float *ls = lse + size_t(w.bh) * w.plane_walk, *Ds = Dws + size_t(w.bh) * w.plane_walk;
     // the quadrature weight is the owner's own here: it multiplies the finished sums (one rounding instead of one in every
     // exponent; a latitude of weight zero has no arcs)
@@ -574,8 +441,8 @@ nattn_bwd_dkdv_band(BandArgs a, const T *__restrict__ q, const T *__restrict__ k
         for (int kb = 0; kb < D / 4; ++kb) {
             const int c = 4 * kb + g;
             const size_t at = size_t(c) * w.plane_own + w.c_own * u;
-            kreg[o][kb] = own && has<MODE>(c, a.d) ? ldx(k + slice_k + at) : 0.f;
-            vreg[o][kb] = own && has<MODE>(c, a.e) ? ldx(v + slice_v + at) : 0.f;
+            kreg[o][kb] = own && has<MODE>(c, a.d) ? *(k + slice_k + at) : 0.f;
+            vreg[o][kb] = own && has<MODE>(c, a.e) ? *(v + slice_v + at) : 0.f;
         }
     }
     // minus the logsumexp (base 2, relative) and -D of a stage's columns: one pair per thread
@@ -589,14 +456,15 @@ nattn_bwd_dkdv_band(BandArgs a, const T *__restrict__ q, const T *__restrict__ k
         }
     };
     Walker wk;
-    StageCols<G::SW, MODE == kWide> cols;
+    typename Stage<D, NO, MODE>::Idx at;
+    at.init(w);
     Stage<D, NO, MODE> rq, rg;
     bool more = wk.start<G::OW, G::SW>(a.b, w.first, w.own, nullptr, w.lane, w.Wb);
     if (more) {
         const size_t row = w.walk_at(wk.r);
-        cols.set(w, wk.cur.Xs0);
-        rq.load(w, cols, qs + row, a.d);
-        rg.load(w, cols, gs + row, a.e);
+        at.set(w, wk.cur.Xs0);
+        rq.load(w, at, qs + row, a.d);
+        rg.load(w, at, gs + row, a.e);
         load_stat(row, wk.cur.Xs0);
     }
     for (int i = w.tid; i < 2 * G::TILE + 2 * G::COLS; i += 256) lds[i] = 0.f;
@@ -616,9 +484,9 @@ nattn_bwd_dkdv_band(BandArgs a, const T *__restrict__ q, const T *__restrict__ k
         more = wk.next<G::OW, G::SW>(nU, w.Wb);
         if (more) {
             const size_t row = w.walk_at(wk.r);
-            cols.set(w, wk.cur.Xs0 + wk.s * G::SW);
-            rq.load(w, cols, qs + row, a.d);
-            rg.load(w, cols, gs + row, a.e);
+            at.set(w, wk.cur.Xs0 + wk.s * G::SW);
+            rq.load(w, at, qs + row, a.d);
+            rg.load(w, at, gs + row, a.e);
             load_stat(row, wk.cur.Xs0 + wk.s * G::SW);
         }
         if (cnt <= 0) continue;
@@ -690,8 +558,8 @@ nattn_bwd_dkdv_band(BandArgs a, const T *__restrict__ q, const T *__restrict__ k
             for (int rr = 0; rr < 4; ++rr) {
                 const int c = 16 * mt + 4 * g + rr;
                 const size_t at = size_t(c) * w.plane_own + w.c_own * u;
-                if (has<MODE>(c, a.d)) stx(dk + slice_k + at, adk[o][mt][rr] * (omega * a.scale));
-                if (has<MODE>(c, a.e)) stx(dv + slice_v + at, adv[o][mt][rr] * omega);
+                if (has<MODE>(c, a.d)) *(dk + slice_k + at) = adk[o][mt][rr] * (omega * a.scale);
+                if (has<MODE>(c, a.e)) *(dv + slice_v + at) = adv[o][mt][rr] * omega;
             }
     }
 }
@@ -701,15 +569,17 @@ constexpr size_t fwd_lds() { return size_t(2) * Geo<D, NO>::TILE * sizeof(float)
 template <int D, int NO>
 constexpr size_t dkdv_lds() { return (size_t(2) * Geo<D, NO>::TILE + 2 * Geo<D, NO>::COLS) * sizeof(float); }
 
-template <class T, int D, int NO, int MODE>
+template <int D, int NO, int MODE, bool BWD>
 int configure_one()
 {
     auto raise = [](const void *f, size_t bytes) {
         return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)) != hipSuccess;
     };
-    return raise(reinterpret_cast<const void *>(nattn_fwd_band<T, D, NO, MODE>), fwd_lds<D, NO>()) ||
-           raise(reinterpret_cast<const void *>(nattn_bwd_dq_band<T, D, NO, MODE>), fwd_lds<D, NO>()) ||
-           raise(reinterpret_cast<const void *>(nattn_bwd_dkdv_band<T, D, NO, MODE>), dkdv_lds<D, NO>());
+    int rc = 0;
+    if constexpr (BWD)
+        rc = raise(reinterpret_cast<const void *>(nattn_bwd_dq_band<D, NO, MODE>), fwd_lds<D, NO>()) ||
+             raise(reinterpret_cast<const void *>(nattn_bwd_dkdv_band<D, NO, MODE>), dkdv_lds<D, NO>());
+    return rc || raise(reinterpret_cast<const void *>(nattn_fwd_band<D, NO, MODE>), fwd_lds<D, NO>());
 }
 
 template <int D, int NO>
@@ -723,17 +593,16 @@ inline BandArgs band_args(const S2DeviceTables &t, const S2BandSide &b, int nbh,
 }
 inline double pair_count(const double (&p)[4], int nbh) { return nbh * (p[0] + p[1] + p[2] + p[3]); }
 
-// Calls f with the geometry for a head dimension and a launch: owner tiles per wavefront (NO).
-// d = 32 and 64: two (for d = 32 four were measured too: 3.13 against 2.88 ms on the 129 x 256 grid with 32 slices,
-// 0.58 against 0.41 ms on the 64 x 128 grid with 8: smaller tiles in LDS and fewer registers put more workgroups on a
-// compute unit, which outweighs staging 96 columns per 32 owners instead of 128 per 64).  d = 16: four, two while a
-// launch would have fewer than two workgroups per compute unit.  One where the launch would still leave the device half
-// empty (fewer than four workgroups per compute unit).
+// Calls f with the geometry for a head dimension and a launch: owner tiles per wavefront (NO), one or two.  Two share a
+// staged row, one makes twice the workgroups and needs fewer registers.  d = 16: two in the forward from four workgroups per
+// compute unit on (129 x 256, 32 slices: 0.43 against 0.50 ms), one in the backward (0.57 + 0.67 against 0.55 + 0.70; four were
+// slower throughout); d = 32: two from four, d = 64: two from two workgroups per compute unit on (129 x 256: 2.9 against 3.3 and
+// 6.3 against 7.5 ms per step; 64 x 128, 8 slices, d = 32: 0.41 against 0.33).
 template <int D_, int NO_>
 struct Shape {
     static constexpr int D = D_, NO = NO_;
 };
-template <class F>
+template <bool BWD, class F>
 void by_shape(const S2BandSide &b, int nbh, int dmax, F &&f)
 {
     static const unsigned ncu = [] {
@@ -743,59 +612,59 @@ void by_shape(const S2BandSide &b, int nbh, int dmax, F &&f)
             n = 256;
         return unsigned(n);
     }();
+    const unsigned two = blocks<16, 2>(b, nbh);
     if (dmax <= 16) {
-        if (blocks<16, 2>(b, nbh) < 2 * ncu) f(Shape<16, 1>());
-        else if (blocks<16, 4>(b, nbh) < 2 * ncu) f(Shape<16, 2>());
-        else f(Shape<16, 4>());
+        if constexpr (!BWD)
+            if (two >= 4 * ncu) return f(Shape<16, 2>());
+        f(Shape<16, 1>());
     } else if (dmax <= 32) {
-        if (blocks<32, 2>(b, nbh) < 4 * ncu) f(Shape<32, 1>());
-        else f(Shape<32, 2>());
+        if (two >= 4 * ncu) f(Shape<32, 2>());
+        else f(Shape<32, 1>());
     } else {
-        if (blocks<64, 2>(b, nbh) < 2 * ncu) f(Shape<64, 1>());
-        else f(Shape<64, 2>());
+        if (two >= 2 * ncu) f(Shape<64, 2>());
+        else f(Shape<64, 1>());
     }
 }
 
 }  // namespace
 
-// One instantiation (storage type, staging mode) per translation unit: BandSet<T, MODE> in s2_nattn_band.h.
-template <class T, int MODE>
-int BandSet<T, MODE>::configure()
+// One instantiation (storage type, staging mode) per translation unit: BandSet<MODE> in s2_nattn_band.h.
+template <int MODE>
+int BandSet<MODE>::configure()
 {
-    return configure_one<T, 16, 1, MODE>() || configure_one<T, 16, 2, MODE>() || configure_one<T, 16, 4, MODE>() ||
-           configure_one<T, 32, 1, MODE>() || configure_one<T, 32, 2, MODE>() || configure_one<T, 64, 1, MODE>() ||
-           configure_one<T, 64, 2, MODE>();
+    return configure_one<16, 1, MODE, true>() || configure_one<16, 2, MODE, false>() || configure_one<32, 1, MODE, true>() ||
+           configure_one<32, 2, MODE, true>() || configure_one<64, 1, MODE, true>() || configure_one<64, 2, MODE, true>();
 }
-template <class T, int MODE>
-void BandSet<T, MODE>::fwd(const S2DeviceTables &t, int nbh, int d, int e, float scale, const T *q, const T *k, const T *v,
-                          T *out, float *lse, hipStream_t st)
+template <int MODE>
+void BandSet<MODE>::fwd(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k, const float *v,
+                          float *out, float *lse, hipStream_t st)
 {
-    S2TraceScope tr(sizeof(T) == 2 ? "nattn_fwd_band<bf16>" : "nattn_fwd_band", pair_count(t.fwd_pairs, nbh), st);
-    by_shape(t.side_out, nbh, d > e ? d : e, [&](auto s) {
+    S2TraceScope tr("nattn_fwd_band", pair_count(t.fwd_pairs, nbh), st);
+    by_shape<false>(t.side_out, nbh, d > e ? d : e, [&](auto s) {
         constexpr int D = decltype(s)::D, NO = decltype(s)::NO;
-        hipLaunchKernelGGL((nattn_fwd_band<T, D, NO, MODE>), dim3(blocks<D, NO>(t.side_out, nbh)), dim3(256),
+        hipLaunchKernelGGL((nattn_fwd_band<D, NO, MODE>), dim3(blocks<D, NO>(t.side_out, nbh)), dim3(256),
                            (fwd_lds<D, NO>()), st, band_args(t, t.side_out, nbh, d, e, scale), q, k, v, out, lse);
     });
 }
-template <class T, int MODE>
-void BandSet<T, MODE>::dq(const S2DeviceTables &t, int nbh, int d, int e, float scale, const T *q, const T *k, const T *v,
-                         const T *o, const float *lse, const T *go, T *dq, float *Dws, hipStream_t st)
+template <int MODE>
+void BandSet<MODE>::dq(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k, const float *v,
+                         const float *o, const float *lse, const float *go, float *dq, float *Dws, hipStream_t st)
 {
-    S2TraceScope tr(sizeof(T) == 2 ? "nattn_bwd_dq_band<bf16>" : "nattn_bwd_dq_band", pair_count(t.fwd_pairs, nbh), st);
-    by_shape(t.side_out, nbh, d > e ? d : e, [&](auto s) {
+    S2TraceScope tr("nattn_bwd_dq_band", pair_count(t.fwd_pairs, nbh), st);
+    by_shape<true>(t.side_out, nbh, d > e ? d : e, [&](auto s) {
         constexpr int D = decltype(s)::D, NO = decltype(s)::NO;
-        hipLaunchKernelGGL((nattn_bwd_dq_band<T, D, NO, MODE>), dim3(blocks<D, NO>(t.side_out, nbh)), dim3(256),
+        hipLaunchKernelGGL((nattn_bwd_dq_band<D, NO, MODE>), dim3(blocks<D, NO>(t.side_out, nbh)), dim3(256),
                            (fwd_lds<D, NO>()), st, band_args(t, t.side_out, nbh, d, e, scale), q, k, v, o, lse, go, dq, Dws);
     });
 }
-template <class T, int MODE>
-void BandSet<T, MODE>::dkdv(const S2DeviceTables &t, int nbh, int d, int e, float scale, const T *q, const T *k, const T *v,
-                           const float *lse, const T *go, const float *Dws, T *dk, T *dv, hipStream_t st)
+template <int MODE>
+void BandSet<MODE>::dkdv(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k, const float *v,
+                           const float *lse, const float *go, const float *Dws, float *dk, float *dv, hipStream_t st)
 {
-    S2TraceScope tr(sizeof(T) == 2 ? "nattn_bwd_dkdv_band<bf16>" : "nattn_bwd_dkdv_band", pair_count(t.bwd_pairs, nbh), st);
-    by_shape(t.side_in, nbh, d > e ? d : e, [&](auto s) {
+    S2TraceScope tr("nattn_bwd_dkdv_band", pair_count(t.bwd_pairs, nbh), st);
+    by_shape<true>(t.side_in, nbh, d > e ? d : e, [&](auto s) {
         constexpr int D = decltype(s)::D, NO = decltype(s)::NO;
-        hipLaunchKernelGGL((nattn_bwd_dkdv_band<T, D, NO, MODE>), dim3(blocks<D, NO>(t.side_in, nbh)), dim3(256),
+        hipLaunchKernelGGL((nattn_bwd_dkdv_band<D, NO, MODE>), dim3(blocks<D, NO>(t.side_in, nbh)), dim3(256),
                            (dkdv_lds<D, NO>()), st, band_args(t, t.side_in, nbh, d, e, scale), q, k, v, lse, go, Dws, dk, dv);
     });
 }

@@ -77,8 +77,7 @@ int s2_nattn_bwd_dkdv_bf16(const S2DeviceTables &t, int nbh, int d, int e, float
                            const void *v, const float *lse, const void *go, const float *Dws, void *dk, void *dv,
                            hipStream_t st);
 
-// float32 tensors on the fp32 matrix cores (band tiles of 16 keys x 16 outputs) for head dimensions the hand-tuned
-// kernels do not cover: equal grids, d = e in {16, 32, 64}, longitude count a multiple of 16 (at least 64).
+// float32 tensors on the fp32 matrix cores (band tiles of 16 keys x 16 outputs), any grid pair, d and e up to 64.
 bool s2_nattn_band_supported(const S2DeviceTables &t, int d, int e);
 int s2_nattn_fwd_band(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k,
                       const float *v, float *out, float *lse, hipStream_t st);
@@ -86,14 +85,14 @@ int s2_nattn_bwd_band(const S2DeviceTables &t, int nbh, int d, int e, float scal
                       const float *v, const float *o, const float *lse, const float *go, float *dq, float *dk, float *dv,
                       float *Dws, hipStream_t st);
 
-// The same kernels on bf16 tensors (float32 arithmetic on the fp32 matrix cores, bf16 loads and stores): the head
-// dimensions and longitude counts the bf16 matrix-core kernels do not cover.
-int s2_nattn_fwd_band_bf16(const S2DeviceTables &t, int nbh, int d, int e, float scale, const void *q, const void *k,
+// bf16 tensors on the bf16 matrix cores, any grid pair, d and e up to 64.
+bool s2_nattn_tile_supported(const S2DeviceTables &t, int d, int e);
+int s2_nattn_fwd_tile_bf16(const S2DeviceTables &t, int nbh, int d, int e, float scale, const void *q, const void *k,
                            const void *v, void *out, float *lse, hipStream_t st);
-int s2_nattn_bwd_dq_band_bf16(const S2DeviceTables &t, int nbh, int d, int e, float scale, const void *q, const void *k,
+int s2_nattn_bwd_dq_tile_bf16(const S2DeviceTables &t, int nbh, int d, int e, float scale, const void *q, const void *k,
                               const void *v, const void *o, const float *lse, const void *go, void *dq, float *Dws,
                               hipStream_t st);
-int s2_nattn_bwd_dkdv_band_bf16(const S2DeviceTables &t, int nbh, int d, int e, float scale, const void *q, const void *k,
+int s2_nattn_bwd_dkdv_tile_bf16(const S2DeviceTables &t, int nbh, int d, int e, float scale, const void *q, const void *k,
                                 const void *v, const float *lse, const void *go, const float *Dws, void *dk, void *dv,
                                 hipStream_t st);
 

@@ -1,0 +1,4 @@
+// bf16 matrix-core tile kernels: staging mode kNarrow.
+#include "s2_nattn_tile_impl.h"
+
+template struct TileSet<kNarrow>;

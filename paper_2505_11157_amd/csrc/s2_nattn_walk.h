@@ -20,6 +20,7 @@
 #include <hip/hip_runtime.h>
 
 #include "s2_internal.h"
+#include "s2_nattn_band.h"
 
 namespace s2walk {
 
@@ -227,6 +228,101 @@ __device__ __forceinline__ void band_mask(bool (&keep)[N], const RowPlan &p, con
 #pragma unroll
         for (int rr = 0; rr < N; ++rr) keep[rr] = unsigned(uu + rr) < unsigned(cnt);
     }
+}
+
+// ---- kernel arguments and the place of a workgroup ----
+struct BandArgs {
+    S2BandSide b;
+    const float *omega_rel;
+    float ln_omega_ref, omega_ref, scale;
+    int nbh, d, e;
+};
+
+// Where a wavefront's owners and the walked rows lie.
+struct BandWhere {
+    int nU, W0, Wb, grp, bh, first, own, lane, wave, n, g, tid;
+    int no;                        // owner tiles of this workgroup that hold a point
+    bool active;
+    float inv_nU;
+    size_t plane_own, plane_walk;
+    size_t own_at;                 // offset of owner column 0 of the wavefront's row inside a plane
+    int nlon_walk, c_own, c_walk;
+    template <int OW>
+    __device__ __forceinline__ void set(const BandArgs &a)
+    {
+        nU = a.b.nU;
+        const int ngrp = (nU + OW - 1) / OW, nseg = (a.b.n_own + 3) >> 2;
+        int id = blockIdx.x;
+        grp = id % ngrp; id /= ngrp;
+        bh = id % a.nbh;
+        first = 4 * segment_of(id / a.nbh, nseg);
+        tid = threadIdx.x; lane = tid & 63; wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        n = lane & 15; g = lane >> 4;
+        own = first + wave;
+        active = own < a.b.n_own;
+        W0 = grp * OW; Wb = nU + W0;
+        no = (imin(OW, nU - W0) + 15) >> 4;
+        inv_nU = 1.f / float(nU);
+        c_own = a.b.c_own; c_walk = a.b.c_walk;
+        nlon_walk = nU * c_walk;
+        plane_own = size_t(a.b.nlat_own) * nU * c_own;
+        plane_walk = size_t(a.b.nlat_walk) * nlon_walk;
+        const int lat = own / c_own;
+        own_at = size_t(lat) * nU * c_own + (own - lat * c_own);
+    }
+    // offset of column 0 of walked row r inside a plane
+    __device__ __forceinline__ size_t walk_at(int r) const
+    {
+        if (c_walk == 1) return size_t(r) * nlon_walk;
+        const int lat = r / c_walk;
+        return size_t(lat) * nlon_walk + (r - lat * c_walk);
+    }
+};
+
+// is channel c one of the tensor's nch
+template <int MODE>
+__device__ __forceinline__ bool has(int c, int nch) { return MODE != kRagged || c < nch; }
+
+// Where a thread's pieces of a stage lie: byte offsets into the walked tensor's row, for all stages and both tensors.
+// kWide: pieces of four columns, dealt out to the threads channel by channel (past the last channel: that channel again, not
+// stored).  Otherwise a wavefront takes 64 columns of one channel at a time.
+template <class T, int D, int SW, int MODE>
+struct StageIdx {
+    static constexpr bool WIDE = MODE == kWide;
+    static constexpr int P4 = SW / 4, NP = (D * P4 + 255) / 256, NC = (SW + 63) / 64, N = WIDE ? NP : NC;
+    static constexpr bool EVEN = D * P4 % 256 == 0;
+    unsigned base[N], turn[N], off[N];       // channel, column reduced to one turn, sum of both for the current stage
+    __device__ __forceinline__ void init(const BandWhere &w)
+    {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            int col;
+            if constexpr (WIDE) {
+                const int i = w.tid + 256 * j, c = imin(i / P4, D - 1);
+                base[j] = unsigned(c) * unsigned(w.plane_walk) * unsigned(sizeof(T));
+                col = 4 * (i % P4);
+            } else {
+                col = w.lane + 64 * j < SW ? w.lane + 64 * j : 0;
+                base[j] = 0;
+            }
+            turn[j] = wrap_col(col, w.nU, w.inv_nU);
+        }
+    }
+    __device__ __forceinline__ void set(const BandWhere &w, int Xs)
+    {
+        int Xr = Xs >= 2 * w.nU ? Xs - 2 * w.nU : Xs;
+        Xr = Xr >= w.nU ? Xr - w.nU : Xr;
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const unsigned x = unsigned(Xr) + turn[j], y = x - unsigned(w.nU);       // y wraps to a large value if x < nU
+            off[j] = base[j] + (x < y ? x : y) * unsigned(WIDE ? sizeof(T) : sizeof(T) * w.c_walk);
+        }
+    }
+};
+template <class V>
+__device__ __forceinline__ V load_at(const void *row, unsigned off)
+{
+    return *reinterpret_cast<const V *>(static_cast<const char *>(row) + off);
 }
 
 }  // namespace s2walk

@@ -23,6 +23,7 @@ NEED = {
     "f32_4x4x1_16b_f32": 4,      # 2 passes
     "f32_32x32x16_bf16": 12,     # 8 passes
     "f32_16x16x32_bf16": 8,      # 4 passes
+    "f32_16x16x16_bf16": 8,      # 4 passes
 }
 DEFAULT_NEED = 20                # unknown shape: the longest rule
 
