@@ -5,27 +5,51 @@
 //     y[b, o, h, w]    = sum_{c, k} weight[o, c, k] z[b, c, k, h, w] + bias[o]
 // psi_k = hat_k(r) * omega[h'] with K piecewise-linear hats of the geodesic distance r (hat_k(r) = max(0,
 // 1 - |r K / theta_cutoff - k|): isotropic filters that vanish on the rim of the disk); the paper leaves the basis
-// open.  Equal longitude counts (at least 64, a multiple of 16; batch * channels a multiple of 16) run the contraction
-// with psi on the fp32 matrix cores (disco_z_band, disco_dx_band below); other shapes use a gather per point (lanes on
+// open.  The contraction with psi is disco_gather below; grids with rows too long for it take a gather per point (lanes on
 // consecutive longitudes, the basis values of a (latitude, offset) uniform over a wavefront).  The channel mixing is a
-// channel matrix on the fp32 matrix cores.  Backward: dx goes through the transposed neighborhood (no atomics), dweight
-// is the split-K weight-gradient product summed in a fixed order.
+// channel matrix on the fp32 matrix cores.  Backward, equal grids: psi is applied to dy through the transposed
+// neighborhood (the same kernel on the transposed tables, no atomics) and the channel mixing follows,
+//     dx[b, c] = sum_{o, k} weight[o, c, k] (psi_k^T dy)[b, o];
+// downsampling mixes first (its output grid has a quarter of the points) and gathers dx from the K planes of dz.  dweight is
+// the split-K weight-gradient product summed in a fixed order.
+#include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <new>
+#include <utility>
 
 #include "s2_nattn_kernels.h"
+
+namespace {
+
+// One direction of the contraction with psi as disco_gather walks it: for every owner latitude a list of chunks, a chunk
+// being some rows that fit into a wavefront's share of LDS and the (row, offset) entries on them, sorted by the interval
+// j <= r K / theta < j + 1 in which only the hats j and j + 1 differ from zero.
+struct GatherRow {
+    int lat, left, ncols, base;       // walked latitude, staged columns in front of the first owner's, staged columns, LDS position
+};
+struct GatherEntry {
+    int plus, minus;                  // LDS byte offsets of the columns +d and -d of owner 0
+    float lo, hi;                     // psi_j, psi_{j+1} (halved where +d and -d are the same column)
+};
+struct GatherTables {
+    void *blob = nullptr;
+    const int *chunk_of = nullptr;    // [owner latitudes + 1]
+    const int *chunk = nullptr;       // [chunks][K + 3]: first row, end row, first entry, end of the entries of interval j
+    const GatherRow *row = nullptr;
+    const GatherEntry *entry = nullptr;
+    const int *order = nullptr;       // owner latitudes, heaviest first
+    int lds_bytes = 0, W = 1;         // 0: not available; owners per lane
+};
+
+}  // namespace
 
 struct s2_disco {
     const s2_grid_t *g;
     int K;
     float *dev_psi = nullptr;     // [entry][KP], KP = K rounded up to a multiple of 4; entry = poff[h * band_max + b] + offset
     int *dev_poff = nullptr;      // [nlat_out * band_max]
-    // matrix-core path (equal longitude counts): the same values with 16 floats per offset and every arc padded with
-    // zero entries to a multiple of four offsets; row pitch (floats) of the staged input rows
-    float *dev_psi16 = nullptr;
-    int *dev_poff16 = nullptr;
-    int pitch16 = 0;
-    int dx_lds_bytes = 0;         // dynamic LDS of the matrix-core dx kernel (0: not available)
+    GatherTables fwd, bwd;        // owners = outputs; owners = inputs (equal grids only)
 };
 
 namespace {
@@ -131,144 +155,110 @@ disco_dx(S2DeviceTables t, const float *__restrict__ psi, const int *__restrict_
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// z on the fp32 matrix cores (equal longitude counts).  For ONE output point the contraction over the offsets of an
-// arc is a small dense product: Z[k][c] += sum_d psi[d][k] x[c][w + lo + d] -- basis index k as the row dimension
-// of v_mfma_f32_16x16x4_f32 (16 rows: the basis count padded), 16 channels as its columns, four offsets per
-// instruction.  No mask is needed (the arcs are exact; only their length is padded to a multiple of four, with zero
-// basis values) and A = psi[d0 + g][k = lane & 15] is one coalesced 256-byte read shared by every output point of the
-// latitude.  A wavefront owns 16 consecutive output longitudes (16 accumulators), a workgroup 64 longitudes x 16
-// channels of one latitude; each input row of the band is copied to LDS once (channel-major, pitch 4 mod 64 words:
-// B = x[c = lane & 15][w + lo + d0 + g] is conflict-free).  Lane (c, g) ends with z[k = 4 g + 0..3][c] of its 16
-// points: 64 contiguous bytes per (k, c).
-__global__ void __launch_bounds__(256)
-disco_z_band(S2DeviceTables t, const float *__restrict__ psi16, const int *__restrict__ poff16, int K, int pitch,
-             const float *__restrict__ x, float *__restrict__ z)
+// Contraction with psi: out[ch][k][lat][u] = sum over the entries of owner latitude lat.  At a distance r only two of the K
+// hats differ from zero, and the columns +d and -d of a row carry the same values, so two neighbors cost one add and two
+// multiply-adds per channel instead of 2 K multiply-adds (a dense contraction with the basis on the matrix cores, 16 rows
+// for 9 functions, took 0.62 ms on 129 x 256 with 4 x 64 channels).  Which two accumulators an entry goes to is known at
+// compile time: the entries of a chunk are sorted by interval and the loop over the intervals is unrolled.
+// One wavefront: 64 W consecutive owners of one latitude, four channels.  It stages the rows of a chunk for itself,
+// position-major with the four channels of a column side by side, so that a neighbor is one 16-byte LDS read per lane at
+// consecutive addresses; with P input columns per owner the columns of one remainder mod P lie together.  Entries and basis
+// values are uniform and come through the scalar cache.  Bound: the 16-byte LDS reads (8 cycles each) and the vector ALU
+// (13 instructions per entry and owner), about equal.
+template <int K, int W>
+__global__ void __launch_bounds__(64)
+disco_gather(GatherTables t, int P, int nlon_own, int nlon_walk, int nlat_own, int nlat_walk, int nch,
+             const float *__restrict__ x, float *__restrict__ out)
 {
-    extern __shared__ __attribute__((aligned(16))) float xs[];       // [16 channels][pitch]
-    const int nlon = t.nlon_in;
-    const int h = blockIdx.y, bc0 = blockIdx.z * 16;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n = lane & 15, g = lane >> 4;
-    const int w0g = blockIdx.x * 64, w0 = w0g + 16 * wave;
-    const bool active = w0 < nlon;
-    const size_t si = size_t(t.nlat_in) * nlon, so = size_t(t.nlat_out) * nlon;
-    f32x4 acc[16];
+    extern __shared__ __attribute__((aligned(16))) f32x4 xs[];
+    const int lane = threadIdx.x;
+    const int ntile = (nlon_own + 64 * W - 1) / (64 * W), nquad = (nch + 3) / 4;
+    int id = blockIdx.x;
+    const int tile = id % ntile; id /= ntile;
+    const int quad = id % nquad, lat = t.order[id / nquad];
+    const int u0 = tile * 64 * W;
+    const size_t plane_walk = size_t(nlat_walk) * nlon_walk, plane_own = size_t(nlat_own) * nlon_own;
+    const float *xc[4];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int nb = t.band_n[h], hp0 = t.band_lo[h];
-    const int sc = tid >> 4, sp = tid & 15;         // staging: channel, first 16-byte piece
-    for (int b = 0; b < nb; ++b) {
-        const int cnt = t.cnt[h * t.band_max + b];
-        const int lo = cnt == nlon ? 0 : -((cnt - 1) >> 1), npad = (cnt + 3) & ~3;
-        const int Xs = (w0g + lo + nlon) & ~3;                                // first staged column (unwrapped)
-        const int np4 = (w0g + 63 + lo + nlon + npad - Xs + 3) >> 2;           // 16-byte pieces per channel row
-        __syncthreads();                            // the previous row has been consumed
-        const float *xr = x + size_t(bc0 + sc) * si + size_t(hp0 + b) * nlon;
-        for (int pc = sp; pc < np4; pc += 16) {
-            int col = Xs + 4 * pc;
-            col = col >= 2 * nlon ? col - 2 * nlon : col;
-            col = col >= nlon ? col - nlon : col;
-            col = col >= nlon ? col - nlon : col;
-            *reinterpret_cast<f32x4 *>(xs + sc * pitch + 4 * pc) = *reinterpret_cast<const f32x4 *>(xr + col);
+    for (int c = 0; c < 4; ++c) xc[c] = x + size_t(min(4 * quad + c, nch - 1)) * plane_walk;
+
+    f32x4 acc[K][W];
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int i = 0; i < W; ++i) acc[k][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const char *lds = reinterpret_cast<const char *>(xs) + 16 * lane;
+    const int c_end = t.chunk_of[lat + 1];
+    for (int ci = t.chunk_of[lat]; ci < c_end; ++ci) {
+        const int *ch = t.chunk + size_t(ci) * (K + 3);
+        const int r_end = ch[1];
+        __syncthreads();                                 // one wavefront: its reads of the previous chunk are done
+        for (int r = ch[0]; r < r_end; ++r) {
+            const GatherRow row = t.row[r];
+            const size_t at = size_t(row.lat) * nlon_walk;
+            const int sub = row.ncols / P;
+            int first = u0 * P - row.left;               // in (-nlon, nlon)
+            first = first < 0 ? first + nlon_walk : first;
+            for (int i0 = 0; i0 < row.ncols; i0 += 192) {
+                float v[3][4];
+#pragma unroll
+                for (int b = 0; b < 3; ++b) {
+                    int col = first + min(i0 + 64 * b + lane, row.ncols - 1);
+                    col = col >= 2 * nlon_walk ? col % nlon_walk : col >= nlon_walk ? col - nlon_walk : col;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) v[b][c] = xc[c][at + col];
+                }
+#pragma unroll
+                for (int b = 0; b < 3; ++b) {
+                    const int i = i0 + 64 * b + lane;
+                    const int pos = P == 1 ? i : (i % P) * sub + i / P;
+                    if (i < row.ncols) xs[row.base + pos] = f32x4{v[b][0], v[b][1], v[b][2], v[b][3]};
+                }
+            }
         }
         __syncthreads();
-        if (!active) continue;
-        const float *pa = psi16 + size_t(poff16[h * t.band_max + b]) * 16 + lane;
-        const float *xb = xs + n * pitch + (w0 + lo + nlon - Xs) + g;
-        float a = pa[0];
-        for (int d0 = 0; d0 < npad; d0 += 4) {
-            const float an = d0 + 4 < npad ? pa[(d0 + 4) * 16] : 0.f;          // next step's basis values
+        int e = ch[2];
 #pragma unroll
-            for (int wi = 0; wi < 16; ++wi)
-                acc[wi] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, xb[d0 + wi], acc[wi], 0, 0, 0);
-            a = an;
+        for (int j = 0; j < K; ++j) {
+            const int e_end = ch[3 + j];
+            for (; e < e_end; ++e) {
+                const GatherEntry en = t.entry[e];
+#pragma unroll
+                for (int i = 0; i < W; ++i) {
+                    const f32x4 a = *reinterpret_cast<const f32x4 *>(lds + en.plus + 1024 * i);
+                    const f32x4 b = *reinterpret_cast<const f32x4 *>(lds + en.minus + 1024 * i);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const float s = a[c] + b[c];
+                        acc[j][i][c] = fmaf(en.lo, s, acc[j][i][c]);
+                        if (j + 1 < K) acc[j + 1 < K ? j + 1 : 0][i][c] = fmaf(en.hi, s, acc[j + 1 < K ? j + 1 : 0][i][c]);
+                    }
+                }
+            }
         }
     }
-    if (!active) return;
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-        const int k = 4 * g + rr;
-        if (k < K) {
-            float *zo = z + (size_t(bc0 + n) * K + k) * so + size_t(h) * nlon + w0;
+    for (int i = 0; i < W; ++i) {
+        const int u = u0 + 64 * i + lane;
+        if (u >= nlon_own) continue;
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<f32x4 *>(zo + 4 * q) =
-                    f32x4{acc[4 * q][rr], acc[4 * q + 1][rr], acc[4 * q + 2][rr], acc[4 * q + 3][rr]};
+        for (int c = 0; c < 4; ++c) {
+            if (4 * quad + c >= nch) continue;
+            float *o = out + size_t(4 * quad + c) * K * plane_own + size_t(lat) * nlon_own + u;
+#pragma unroll
+            for (int k = 0; k < K; ++k) o[size_t(k) * plane_own] = acc[k][i][c];
         }
     }
 }
 
-// dx on the fp32 matrix cores (equal longitude counts, at most 512 longitudes).  For 16 consecutive input
-// longitudes x of latitude h' and 16 channels, one output latitude h of the transposed band contributes
-//     dx[c][x] += sum_{w, k} dz[c][h][w][k] psi[h, h'][x - w - lo][k],
-// a product of the 16 x (w, k) slab of dz (basis index innermost: A = dzt[c = lane & 15][w][4 q + g], one LDS word per
-// lane) with the banded matrix psi[x - w - lo][k] (B, taken from a copy of the arc's basis values in LDS that carries
-// 16 zero entries on either side, so that offsets outside the arc need no mask; entry stride 20 words: the 16 x 4
-// words a wavefront reads fall into 64 different banks).  dz is walked in chunks of 32 output longitudes; a
-// wavefront skips the output longitudes whose arcs miss its 16 inputs.  No atomics: every dx element is owned by one
-// lane.
-template <int KP>
+// weight[o][c][k] -> wt[c][o][k], the channel matrix that follows the transposed contraction
 __global__ void __launch_bounds__(256)
-disco_dx_band(S2DeviceTables t, const float *__restrict__ psi, const int *__restrict__ poff,
-              const float *__restrict__ dzt, float *__restrict__ dx)
+disco_weight_transpose(int cout, int cin, int K, const float *__restrict__ w, float *__restrict__ wt)
 {
-    constexpr int kChunk = 32, kPitchG = kChunk * KP + 4, kStride = 20, kMargin = 16, kQ = KP / 4;
-    extern __shared__ __attribute__((aligned(16))) float lds[];
-    float *G = lds, *P = lds + 16 * kPitchG;            // dz chunk [16 channels][32 w * KP]; basis values of the arc
-    const int nlon = t.nlon_in;
-    const int hp = blockIdx.y, bc0 = blockIdx.z * 16;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n = lane & 15, g = lane >> 4;
-    const int x0g = blockIdx.x * 64, x0 = x0g + 16 * wave;
-    const bool active = x0 < nlon;
-    const size_t si = size_t(t.nlat_in) * nlon, so = size_t(t.nlat_out) * nlon;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    const int nb = t.omega_rel[hp] > 0.f ? t.tband_n[hp] : 0;       // a latitude of weight zero receives nothing
-    const int h0 = t.tband_lo[hp];
-    const int sc = tid >> 4, sp = tid & 15;
-    for (int b = 0; b < nb; ++b) {
-        const int h = h0 + b;
-        const int bf = hp - t.band_lo[h];
-        const int cnt = t.cnt[h * t.band_max + bf];
-        const int lo = cnt == nlon ? 0 : -((cnt - 1) >> 1);
-        const float *pr = psi + size_t(poff[h * t.band_max + bf]) * KP;
-        __syncthreads();                               // the previous row's basis values are no longer read
-        for (int i = tid; i < (cnt + 2 * kMargin) * kStride; i += 256) P[i] = 0.f;
-        __syncthreads();
-        for (int i = tid; i < cnt * KP; i += 256) P[(i / KP + kMargin) * kStride + i % KP] = pr[i];
-        // output longitudes (unwrapped, offset by 2 nlon so that they stay positive) whose arcs meet the workgroup's /
-        // the wavefront's inputs: x - w - lo in [0, cnt)
-        const int base = 2 * nlon;
-        const int wg_lo = base + x0g - lo - cnt + 1, wg_hi = base + x0g + 63 - lo;
-        const int wv_lo = base + x0 - lo - cnt + 1, wv_hi = base + x0 + 15 - lo;
-        for (int wc = wg_lo; wc <= wg_hi; wc += kChunk) {
-            __syncthreads();                           // the previous chunk has been consumed (and P is complete)
-            {
-                const float *src = dzt + (size_t(bc0 + sc) * so + size_t(h) * nlon) * KP;
-#pragma unroll
-                for (int j = 0; j < KP / 2; ++j) {
-                    const int pc = sp + 16 * j, wo = pc / kQ, part = pc % kQ;
-                    int wphys = wc + wo;
-                    wphys -= (wphys / nlon) * nlon;
-                    *reinterpret_cast<f32x4 *>(G + sc * kPitchG + wo * KP + 4 * part) =
-                        *reinterpret_cast<const f32x4 *>(src + size_t(wphys) * KP + 4 * part);
-                }
-            }
-            __syncthreads();
-            if (!active) continue;
-            const int a = max(wc, wv_lo), e = min(wc + kChunk - 1, wv_hi);
-            for (int w = a; w <= e; ++w) {
-                const float *ga = G + n * kPitchG + (w - wc) * KP + g;
-                const float *pb = P + (base + x0 + n - w - lo + kMargin) * kStride + g;
-#pragma unroll
-                for (int q = 0; q < kQ; ++q) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ga[4 * q], pb[4 * q], acc, 0, 0, 0);
-            }
-        }
-    }
-    if (!active) return;
-    // lane (x = n, g) holds channels 4 g + 0..3
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) dx[size_t(bc0 + 4 * g + rr) * si + size_t(hp) * nlon + x0 + n] = acc[rr];
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= cout * cin * K) return;
+    const int k = i % K, o = i / K % cout, c = i / K / cout;
+    wt[i] = w[(o * cin + c) * K + k];
 }
 
 int check(const s2_disco_t *dc, int batch, int cin, int cout, const void *ws, size_t ws_bytes)
@@ -295,14 +285,112 @@ void by_basis(int K, F f)       // f(KP), KP = the basis count rounded up to a m
     else f(std::integral_constant<int, 16>());
 }
 
-int raise_dx_lds(int K, int bytes)
+template <int K = 1, class F>
+void by_count(int n, F &&f)       // f(K) for the basis count n = 1 .. kMaxBasis
 {
-    int rc = 0;
-    by_basis(K, [&](auto KP) {
-        rc = hipFuncSetAttribute(reinterpret_cast<const void *>(disco_dx_band<decltype(KP)::value>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess;
+    if (n == K) return f(std::integral_constant<int, K>());
+    if constexpr (K < kMaxBasis) by_count<K + 1>(n, f);
+}
+
+void launch_gather(const GatherTables &t, int K, int P, int nlon_own, int nlon_walk, int nlat_own, int nlat_walk, int nch,
+                   const float *x, float *out, hipStream_t st)
+{
+    const unsigned blocks = unsigned((nlon_own + 64 * t.W - 1) / (64 * t.W)) * unsigned((nch + 3) / 4) * unsigned(nlat_own);
+    by_count(K, [&](auto k) {
+        constexpr int KK = decltype(k)::value;
+        if (t.W == 2)
+            hipLaunchKernelGGL((disco_gather<KK, 2>), dim3(blocks), dim3(64), size_t(t.lds_bytes), st, t, P, nlon_own, nlon_walk,
+                               nlat_own, nlat_walk, nch, x, out);
+        else
+            hipLaunchKernelGGL((disco_gather<KK, 1>), dim3(blocks), dim3(64), size_t(t.lds_bytes), st, t, P, nlon_own, nlon_walk,
+                               nlat_own, nlat_walk, nch, x, out);
     });
-    return rc;
+}
+
+// A wavefront's share of LDS: twelve of them on a compute unit; one row may take more (up to what needs no raised limit).
+constexpr int kGatherLds = 13 * 1024, kGatherLdsMost = 64 * 1024;
+
+// Tables for owners on `nlat_own` latitudes; walked(lat, f) calls f(walked latitude, psi of its offsets 0 .. nlon / 2 at
+// [offset * KP + k], offset count of the arc) for every row of owner latitude lat.  P walked columns per owner.
+// 0: built (or the rows are too long: lds_bytes stays 0), else an error code.
+template <class Walk>
+int build_gather(GatherTables &t, int K, int KP, int P, int nlat_own, int nlon_own, int nlon_walk, Walk &&walked)
+{
+    // two owners per lane halve the staged columns that are not owners' own; one where a second set would mostly be idle
+    t.W = nlon_own % 128 > 0 && nlon_own % 128 <= 64 ? 1 : 2;
+    std::vector<int> chunk_of(1, 0), chunk, order;
+    std::vector<GatherRow> rows;
+    std::vector<GatherEntry> entries;
+    std::vector<std::pair<long, int>> cost;
+    int most = 0;
+    for (int lat = 0; lat < nlat_own; ++lat) {
+        const size_t first_entry = entries.size();
+        std::vector<std::vector<GatherEntry>> by_interval(K);
+        int row0 = int(rows.size()), base = 0;
+        auto flush = [&]() {
+            if (int(rows.size()) == row0) return;
+            chunk.push_back(row0);
+            chunk.push_back(int(rows.size()));
+            chunk.push_back(int(entries.size()));
+            for (auto &v : by_interval) {
+                entries.insert(entries.end(), v.begin(), v.end());
+                chunk.push_back(int(entries.size()));
+                v.clear();
+            }
+            most = std::max(most, base * 16);
+            row0 = int(rows.size());
+            base = 0;
+        };
+        walked(lat, [&](int wl, const float *psi, int cnt) {
+            const bool full = cnt == nlon_walk;
+            const int hw = full ? nlon_walk / 2 : (cnt - 1) / 2;
+            const int left = (hw + P - 1) / P * P, ncols = (64 * t.W + 2 * (left / P)) * P;
+            if (base > 0 && (base + ncols) * 16 > kGatherLds) flush();
+            const int sub = ncols / P;
+            rows.push_back({wl, left, ncols, base});
+            for (int d = 0; d <= hw; ++d) {
+                const float *p = psi + size_t(d) * KP;
+                int j = 0;
+                while (j < K && p[j] == 0.f) ++j;
+                if (j == K) continue;
+                // d = 0, and half a turn on an even circle: +d and -d are the same column
+                const float f = d == 0 || (full && 2 * d == nlon_walk) ? 0.5f : 1.f;
+                auto at = [&](int col) { return 16 * (base + (col % P) * sub + col / P); };
+                by_interval[j].push_back({at(left + d), at(left - d), f * p[j], j + 1 < K ? f * p[j + 1] : 0.f});
+            }
+            base += ncols;
+        });
+        flush();
+        chunk_of.push_back(int(chunk.size() / (K + 3)));
+        cost.push_back({-long(entries.size() - first_entry), lat});
+    }
+    if (most > kGatherLdsMost) return 0;
+    std::stable_sort(cost.begin(), cost.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
+    for (auto &c : cost) order.push_back(c.second);
+    const size_t bytes[5] = {chunk_of.size() * 4, chunk.size() * 4, rows.size() * sizeof(GatherRow),
+                             entries.size() * sizeof(GatherEntry), order.size() * 4};
+    size_t off[6] = {0};
+    for (int i = 0; i < 5; ++i) off[i + 1] = off[i] + (bytes[i] + 255) / 256 * 256;
+    std::vector<char> host(off[5], 0);
+    const void *src[5] = {chunk_of.data(), chunk.data(), rows.data(), entries.data(), order.data()};
+    for (int i = 0; i < 5; ++i) std::memcpy(host.data() + off[i], src[i], bytes[i]);
+    if (hipMalloc(&t.blob, off[5]) != hipSuccess ||
+        hipMemcpy(t.blob, host.data(), off[5], hipMemcpyHostToDevice) != hipSuccess)
+        return S2_ERR_ALLOC;
+    char *b = static_cast<char *>(t.blob);
+    t.chunk_of = reinterpret_cast<const int *>(b);
+    t.chunk = reinterpret_cast<const int *>(b + off[1]);
+    t.row = reinterpret_cast<const GatherRow *>(b + off[2]);
+    t.entry = reinterpret_cast<const GatherEntry *>(b + off[3]);
+    t.order = reinterpret_cast<const int *>(b + off[4]);
+    t.lds_bytes = std::max(most, 16);
+    return 0;
+}
+
+// Does the backward pass apply psi^T before the channel mixing?  The channel matrices take multiples of 16.
+bool transposed_first(const s2_disco_t *dc, int cin)
+{
+    return dc->bwd.lds_bytes > 0 && cin % 16 == 0 && dc->g->nlat_in * dc->g->nlon_in % 16 == 0;
 }
 
 }  // namespace
@@ -335,37 +423,31 @@ extern "C" int s2_disco_init(const s2_grid_t *g, int nbasis, s2_disco_t **out)
                     psi.push_back(k < nbasis ? float(std::max(0.0, 1.0 - std::fabs(r / dr - k)) * g->omega_in[hp]) : 0.f);
             }
         }
-    // matrix-core path: 16 floats per offset, arcs padded to a multiple of four offsets
-    std::vector<int> poff16(poff.size(), 0);
-    std::vector<float> psi16;
-    int maxnpad = 4;
-    const bool band_ok = g->pscale == 1 && g->nlon_in == g->nlon_out && g->nlon_in % 16 == 0 && g->nlon_in >= 64 &&
-                         g->nlon_in <= 2048;
-    if (band_ok)
-        for (int h = 0; h < g->nlat_out; ++h)
-            for (int b = 0; b < g->band_n[h]; ++b) {
-                const int c = g->cnt[size_t(h) * g->band_max + b], npad = (c + 3) / 4 * 4;
-                const size_t src = size_t(poff[size_t(h) * g->band_max + b]) * KP;
-                poff16[size_t(h) * g->band_max + b] = int(psi16.size() / 16);
-                maxnpad = std::max(maxnpad, npad);
-                for (int tt = 0; tt < npad; ++tt)
-                    for (int k = 0; k < 16; ++k) psi16.push_back(tt < c && k < nbasis ? psi[src + size_t(tt) * KP + k] : 0.f);
-            }
-    dc->pitch16 = band_ok ? (64 + maxnpad + 8 + 63) / 64 * 64 + 4 : 0;
-    if (band_ok && g->nlon_in <= 512) dc->dx_lds_bytes = (16 * (32 * KP + 4) + (maxnpad + 32) * 20) * int(sizeof(float));
     if (g->on_device) {
-        if (band_ok) {
-            if (hipMalloc(&dc->dev_psi16, std::max<size_t>(psi16.size(), 1) * sizeof(float)) != hipSuccess ||
-                hipMalloc(&dc->dev_poff16, poff16.size() * sizeof(int)) != hipSuccess ||
-                hipMemcpy(dc->dev_psi16, psi16.data(), psi16.size() * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
-                hipMemcpy(dc->dev_poff16, poff16.data(), poff16.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess ||
-                hipFuncSetAttribute(reinterpret_cast<const void *>(disco_z_band), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    16 * dc->pitch16 * int(sizeof(float))) != hipSuccess ||
-                (dc->dx_lds_bytes && raise_dx_lds(nbasis, dc->dx_lds_bytes))) {
-                (void)hipGetLastError();
-                s2_disco_destroy(dc);
-                return s2_fail(S2_ERR_ALLOC, "set-up of the matrix-core basis tables failed");
+        // psi of the offsets 0, 1, ... of an arc (it is symmetric)
+        auto arc = [&](int h, int b) -> const float * {
+            const int c = g->cnt[size_t(h) * g->band_max + b], mid = c == g->nlon_in ? 0 : (c - 1) / 2;
+            return psi.data() + (size_t(poff[size_t(h) * g->band_max + b]) + mid) * KP;
+        };
+        int rc = build_gather(dc->fwd, nbasis, KP, g->pscale, g->nlat_out, g->nlon_out, g->nlon_in, [&](int h, auto &&f) {
+            for (int b = 0; b < g->band_n[h]; ++b) {
+                const int c = g->cnt[size_t(h) * g->band_max + b];
+                if (c > 0) f(g->band_lo[h] + b, arc(h, b), c);
             }
+        });
+        if (!rc && g->pscale == 1)
+            rc = build_gather(dc->bwd, nbasis, KP, 1, g->nlat_in, g->nlon_in, g->nlon_out, [&](int hp, auto &&f) {
+                for (int i = 0; i < g->tband_n[hp]; ++i) {
+                    const int h = g->tband_lo[hp] + i, b = hp - g->band_lo[h];
+                    if (b < 0 || b >= g->band_n[h]) continue;            // a latitude of weight zero is in no band
+                    const int c = g->cnt[size_t(h) * g->band_max + b];
+                    if (c > 0) f(h, arc(h, b), c);
+                }
+            });
+        if (rc) {
+            (void)hipGetLastError();
+            s2_disco_destroy(dc);
+            return s2_fail(S2_ERR_ALLOC, "set-up of the contraction tables failed");
         }
         if (hipMalloc(&dc->dev_psi, std::max<size_t>(psi.size(), 1) * sizeof(float)) != hipSuccess ||
             hipMalloc(&dc->dev_poff, poff.size() * sizeof(int)) != hipSuccess) {
@@ -389,20 +471,22 @@ extern "C" void s2_disco_destroy(s2_disco_t *dc)
     if (!dc) return;
     if (dc->dev_psi) (void)hipFree(dc->dev_psi);
     if (dc->dev_poff) (void)hipFree(dc->dev_poff);
-    if (dc->dev_psi16) (void)hipFree(dc->dev_psi16);
-    if (dc->dev_poff16) (void)hipFree(dc->dev_poff16);
+    if (dc->fwd.blob) (void)hipFree(dc->fwd.blob);
+    if (dc->bwd.blob) (void)hipFree(dc->bwd.blob);
     delete dc;
 }
 
 extern "C" size_t s2_disco_workspace_bytes(const s2_disco_t *dc, int batch, int cin, int cout)
 {
     if (!dc || batch < 1 || cin < 1 || cout < 1) return 0;
-    const size_t n_out = size_t(dc->g->nlat_out) * dc->g->nlon_out;
+    const size_t n_out = size_t(dc->g->nlat_out) * dc->g->nlon_out, n_in = size_t(dc->g->nlat_in) * dc->g->nlon_in;
     auto up = [](size_t x) { return (x + 63) / 64 * 64; };
-    // z, dz: [batch][cin * K][n_out]; dz with the basis index innermost [batch * cin][n_out][KP]; partial sums of the
-    // weight gradient
-    return (2 * up(size_t(batch) * cin * dc->K * n_out) + up(size_t(batch) * cin * padded(dc->K) * n_out) +
-            up(s2_wgrad_part_floats(cout, cin * dc->K))) * sizeof(float);
+    // z [batch][cin * K][n_out]; psi^T dy [batch][cout * K][n_in] and the transposed weight, or dz like z and dz with the
+    // basis index innermost [batch * cin][n_out][KP]; partial sums of the weight gradient
+    const size_t zs = up(size_t(batch) * cin * dc->K * n_out);
+    const size_t mid = transposed_first(dc, cin) ? up(size_t(batch) * cout * dc->K * n_in) + up(size_t(cout) * cin * dc->K)
+                                                 : zs + up(size_t(batch) * cin * padded(dc->K) * n_out);
+    return (zs + mid + up(s2_wgrad_part_floats(cout, cin * dc->K))) * sizeof(float);
 }
 
 extern "C" int s2_disco_fwd(const s2_disco_t *dc, int batch, int cin, int cout, const float *x, const float *weight,
@@ -420,10 +504,8 @@ extern "C" int s2_disco_fwd(const s2_disco_t *dc, int batch, int cin, int cout, 
     const int n_out = g->nlat_out * g->nlon_out, K = dc->K;
     {
         S2TraceScope tr("disco_z_fwd", 0.0, st);
-        if (dc->dev_psi16 && (batch * cin) % 16 == 0) {
-            const dim3 grid((g->nlon_out + 63) / 64, g->nlat_out, batch * cin / 16);
-            hipLaunchKernelGGL(disco_z_band, grid, dim3(256), size_t(16) * dc->pitch16 * sizeof(float), st, g->dt,
-                               dc->dev_psi16, dc->dev_poff16, K, dc->pitch16, x, z);
+        if (dc->fwd.lds_bytes) {
+            launch_gather(dc->fwd, K, g->pscale, g->nlon_out, g->nlon_in, g->nlat_out, g->nlat_in, batch * cin, x, z, st);
         } else {
             const dim3 grid((g->nlon_out + 63) / 64, g->nlat_out, batch * cin);
             by_basis(K, [&](auto KB) {
@@ -452,27 +534,37 @@ extern "C" int s2_disco_bwd(const s2_disco_t *dc, int batch, int cin, int cout, 
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const int n_out = g->nlat_out * g->nlon_out, K = dc->K;
     auto up = [](size_t v) { return (v + 63) / 64 * 64; };
-    float *z = static_cast<float *>(workspace), *dz = z + up(size_t(batch) * cin * K * n_out);
-    float *dzt = dz + up(size_t(batch) * cin * K * n_out), *part = dzt + up(size_t(batch) * cin * padded(K) * n_out);
+    float *z = static_cast<float *>(workspace), *mid = z + up(size_t(batch) * cin * K * n_out);
+    const bool first = transposed_first(dc, cin);
+    const size_t mids = first ? up(size_t(batch) * cout * K * g->nlat_in * g->nlon_in) : up(size_t(batch) * cin * K * n_out);
+    float *second = mid + mids;               // transposed weight, or dz with the basis index innermost
+    float *part = second + up(first ? size_t(cout) * cin * K : size_t(batch) * cin * padded(K) * n_out);
     {
         S2TraceScope tr("disco_bwd mix", 0.0, st);
         if (dweight) s2_wgrad_f32(cout, cin * K, n_out, batch, dy, z, part, dweight, st);
         if (dbias) s2_channel_sum_f32(batch, cout, n_out, dy, dbias, part, s2_wgrad_part_floats(cout, cin * K), st);
-        s2_gemm_f32(true, cin * K, n_out, cout, batch, weight, dy, nullptr, nullptr, dz, false, st);
+        if (!first) s2_gemm_f32(true, cin * K, n_out, cout, batch, weight, dy, nullptr, nullptr, mid, false, st);
+    }
+    if (first) {
+        {
+            S2TraceScope tr("disco_dx", 0.0, st);
+            launch_gather(dc->bwd, K, 1, g->nlon_in, g->nlon_out, g->nlat_in, g->nlat_out, batch * cout, dy, mid, st);
+        }
+        S2TraceScope tr("disco_dx mix", 0.0, st);
+        hipLaunchKernelGGL(disco_weight_transpose, dim3((cout * cin * K + 255) / 256), dim3(256), 0, st, cout, cin, K, weight, second);
+        s2_gemm_f32(false, cin, g->nlat_in * g->nlon_in, cout * K, batch, second, mid, nullptr, nullptr, dx, false, st);
+        S2_HIP_CHECK(hipGetLastError());
+        return S2_OK;
     }
     S2TraceScope tr("disco_dx", 0.0, st);
     const dim3 grid((g->nlon_in + 63) / 64, g->nlat_in, batch * cin);
     by_basis(K, [&](auto KP) {
         const dim3 tgrid(unsigned((size_t(n_out) + 255) / 256), batch * cin);
-        hipLaunchKernelGGL((disco_dz_transpose<decltype(KP)::value>), tgrid, dim3(256), 0, st, K, size_t(n_out), dz, dzt);
-        if (dc->dx_lds_bytes && (batch * cin) % 16 == 0) {
-            const dim3 bgrid((g->nlon_in + 63) / 64, g->nlat_in, batch * cin / 16);
-            hipLaunchKernelGGL((disco_dx_band<decltype(KP)::value>), bgrid, dim3(256), size_t(dc->dx_lds_bytes), st, g->dt,
-                               dc->dev_psi, dc->dev_poff, dzt, dx);
-        } else if (g->pscale == 1)
-            hipLaunchKernelGGL((disco_dx<decltype(KP)::value, true>), grid, dim3(64), 0, st, g->dt, dc->dev_psi, dc->dev_poff, dzt, dx);
+        hipLaunchKernelGGL((disco_dz_transpose<decltype(KP)::value>), tgrid, dim3(256), 0, st, K, size_t(n_out), mid, second);
+        if (g->pscale == 1)
+            hipLaunchKernelGGL((disco_dx<decltype(KP)::value, true>), grid, dim3(64), 0, st, g->dt, dc->dev_psi, dc->dev_poff, second, dx);
         else
-            hipLaunchKernelGGL((disco_dx<decltype(KP)::value, false>), grid, dim3(64), 0, st, g->dt, dc->dev_psi, dc->dev_poff, dzt, dx);
+            hipLaunchKernelGGL((disco_dx<decltype(KP)::value, false>), grid, dim3(64), 0, st, g->dt, dc->dev_psi, dc->dev_poff, second, dx);
     });
     S2_HIP_CHECK(hipGetLastError());
     return S2_OK;
