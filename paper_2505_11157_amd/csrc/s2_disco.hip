@@ -7,11 +7,11 @@
 // 1 - |r K / theta_cutoff - k|): isotropic filters that vanish on the rim of the disk); the paper leaves the basis
 // open.  The contraction with psi is disco_gather below; grids with rows too long for it take a gather per point (lanes on
 // consecutive longitudes, the basis values of a (latitude, offset) uniform over a wavefront).  The channel mixing is a
-// channel matrix on the fp32 matrix cores.  Backward, equal grids: psi is applied to dy through the transposed
+// channel matrix on the fp32 matrix cores.  Backward: psi is applied to dy through the transposed
 // neighborhood (the same kernel on the transposed tables, no atomics) and the channel mixing follows,
 //     dx[b, c] = sum_{o, k} weight[o, c, k] (psi_k^T dy)[b, o];
-// downsampling mixes first (its output grid has a quarter of the points) and gathers dx from the K planes of dz.  dweight is
-// the split-K weight-gradient product summed in a fixed order.
+// where the channel counts do not allow that, channels are mixed first and dx is gathered from the K planes of dz.  dweight
+// is the split-K weight-gradient product summed in a fixed order.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -49,7 +49,7 @@ struct s2_disco {
     int K;
     float *dev_psi = nullptr;     // [entry][KP], KP = K rounded up to a multiple of 4; entry = poff[h * band_max + b] + offset
     int *dev_poff = nullptr;      // [nlat_out * band_max]
-    GatherTables fwd, bwd;        // owners = outputs; owners = inputs (equal grids only)
+    GatherTables fwd, bwd;        // owners = outputs; owners = inputs
 };
 
 namespace {
@@ -162,12 +162,13 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // compile time: the entries of a chunk are sorted by interval and the loop over the intervals is unrolled.
 // One wavefront: 64 W consecutive owners of one latitude, four channels.  It stages the rows of a chunk for itself,
 // position-major with the four channels of a column side by side, so that a neighbor is one 16-byte LDS read per lane at
-// consecutive addresses; with P input columns per owner the columns of one remainder mod P lie together.  Entries and basis
+// consecutive addresses; with P walked columns per owner the columns of one remainder mod P lie together, and where the owner
+// grid is the finer one (C owner columns per walked column) the owner latitudes are its classes of every C-th column.  Entries and basis
 // values are uniform and come through the scalar cache.  Bound: the 16-byte LDS reads (8 cycles each) and the vector ALU
 // (13 instructions per entry and owner), about equal.
 template <int K, int W>
 __global__ void __launch_bounds__(64)
-disco_gather(GatherTables t, int P, int nlon_own, int nlon_walk, int nlat_own, int nlat_walk, int nch,
+disco_gather(GatherTables t, int P, int C, int nlon_own, int nlon_walk, int nlat_own, int nlat_walk, int nch,
              const float *__restrict__ x, float *__restrict__ out)
 {
     extern __shared__ __attribute__((aligned(16))) f32x4 xs[];
@@ -177,7 +178,7 @@ disco_gather(GatherTables t, int P, int nlon_own, int nlon_walk, int nlat_own, i
     const int tile = id % ntile; id /= ntile;
     const int quad = id % nquad, lat = t.order[id / nquad];
     const int u0 = tile * 64 * W;
-    const size_t plane_walk = size_t(nlat_walk) * nlon_walk, plane_own = size_t(nlat_own) * nlon_own;
+    const size_t plane_walk = size_t(nlat_walk) * nlon_walk, plane_own = size_t(nlat_own / C) * nlon_own * C;
     const float *xc[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) xc[c] = x + size_t(min(4 * quad + c, nch - 1)) * plane_walk;
@@ -211,18 +212,20 @@ disco_gather(GatherTables t, int P, int nlon_own, int nlon_walk, int nlat_own, i
 #pragma unroll
                 for (int b = 0; b < 3; ++b) {
                     const int i = i0 + 64 * b + lane;
-                    const int pos = P == 1 ? i : (i % P) * sub + i / P;
+                    const int pos = P == 1 ? i : P == 2 ? (i & 1) * sub + (i >> 1) : (i % P) * sub + i / P;
                     if (i < row.ncols) xs[row.base + pos] = f32x4{v[b][0], v[b][1], v[b][2], v[b][3]};
                 }
             }
         }
         __syncthreads();
         int e = ch[2];
+        GatherEntry next = t.entry[e];                   // one ahead (the table ends with a spare entry)
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             const int e_end = ch[3 + j];
             for (; e < e_end; ++e) {
-                const GatherEntry en = t.entry[e];
+                const GatherEntry en = next;
+                next = t.entry[e + 1];
 #pragma unroll
                 for (int i = 0; i < W; ++i) {
                     const f32x4 a = *reinterpret_cast<const f32x4 *>(lds + en.plus + 1024 * i);
@@ -244,7 +247,7 @@ disco_gather(GatherTables t, int P, int nlon_own, int nlon_walk, int nlat_own, i
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             if (4 * quad + c >= nch) continue;
-            float *o = out + size_t(4 * quad + c) * K * plane_own + size_t(lat) * nlon_own + u;
+            float *o = out + size_t(4 * quad + c) * K * plane_own + size_t(lat / C) * nlon_own * C + lat % C + size_t(C) * u;
 #pragma unroll
             for (int k = 0; k < K; ++k) o[size_t(k) * plane_own] = acc[k][i][c];
         }
@@ -292,17 +295,17 @@ void by_count(int n, F &&f)       // f(K) for the basis count n = 1 .. kMaxBasis
     if constexpr (K < kMaxBasis) by_count<K + 1>(n, f);
 }
 
-void launch_gather(const GatherTables &t, int K, int P, int nlon_own, int nlon_walk, int nlat_own, int nlat_walk, int nch,
+void launch_gather(const GatherTables &t, int K, int P, int C, int nlon_own, int nlon_walk, int nlat_own, int nlat_walk, int nch,
                    const float *x, float *out, hipStream_t st)
 {
     const unsigned blocks = unsigned((nlon_own + 64 * t.W - 1) / (64 * t.W)) * unsigned((nch + 3) / 4) * unsigned(nlat_own);
     by_count(K, [&](auto k) {
         constexpr int KK = decltype(k)::value;
         if (t.W == 2)
-            hipLaunchKernelGGL((disco_gather<KK, 2>), dim3(blocks), dim3(64), size_t(t.lds_bytes), st, t, P, nlon_own, nlon_walk,
+            hipLaunchKernelGGL((disco_gather<KK, 2>), dim3(blocks), dim3(64), size_t(t.lds_bytes), st, t, P, C, nlon_own, nlon_walk,
                                nlat_own, nlat_walk, nch, x, out);
         else
-            hipLaunchKernelGGL((disco_gather<KK, 1>), dim3(blocks), dim3(64), size_t(t.lds_bytes), st, t, P, nlon_own, nlon_walk,
+            hipLaunchKernelGGL((disco_gather<KK, 1>), dim3(blocks), dim3(64), size_t(t.lds_bytes), st, t, P, C, nlon_own, nlon_walk,
                                nlat_own, nlat_walk, nch, x, out);
     });
 }
@@ -310,11 +313,13 @@ void launch_gather(const GatherTables &t, int K, int P, int nlon_own, int nlon_w
 // A wavefront's share of LDS: twelve of them on a compute unit; one row may take more (up to what needs no raised limit).
 constexpr int kGatherLds = 13 * 1024, kGatherLdsMost = 64 * 1024;
 
-// Tables for owners on `nlat_own` latitudes; walked(lat, f) calls f(walked latitude, psi of its offsets 0 .. nlon / 2 at
-// [offset * KP + k], offset count of the arc) for every row of owner latitude lat.  P walked columns per owner.
+// Tables for owners on `nlat_own` latitudes (classes of latitudes); walked(lat, f) calls f(walked latitude, psi of its input
+// offsets 0 .. nlon_in / 2 at [offset * KP + k], offset count of the arc) for every row of owner latitude lat.  P walked columns
+// per owner, or C owner columns per walked one: the owner u of class s is input column C u + s, and input offset d leads to
+// walked column u + (s - d) / C where C divides s - d.
 // 0: built (or the rows are too long: lds_bytes stays 0), else an error code.
 template <class Walk>
-int build_gather(GatherTables &t, int K, int KP, int P, int nlat_own, int nlon_own, int nlon_walk, Walk &&walked)
+int build_gather(GatherTables &t, int K, int KP, int P, int C, int nlat_own, int nlon_own, int nlon_walk, Walk &&walked)
 {
     // two owners per lane halve the staged columns that are not owners' own; one where a second set would mostly be idle
     t.W = nlon_own % 128 > 0 && nlon_own % 128 <= 64 ? 1 : 2;
@@ -342,9 +347,10 @@ int build_gather(GatherTables &t, int K, int KP, int P, int nlat_own, int nlon_o
             base = 0;
         };
         walked(lat, [&](int wl, const float *psi, int cnt) {
-            const bool full = cnt == nlon_walk;
-            const int hw = full ? nlon_walk / 2 : (cnt - 1) / 2;
-            const int left = (hw + P - 1) / P * P, ncols = (64 * t.W + 2 * (left / P)) * P;
+            const int nlon_in = nlon_walk * C, sc = lat % C;
+            const bool full = cnt == nlon_in;
+            const int hw = full ? nlon_in / 2 : (cnt - 1) / 2, reach = C == 1 ? hw : hw / C + 1;
+            const int left = (reach + P - 1) / P * P, ncols = (64 * t.W + 2 * (left / P)) * P;
             if (base > 0 && (base + ncols) * 16 > kGatherLds) flush();
             const int sub = ncols / P;
             rows.push_back({wl, left, ncols, base});
@@ -354,9 +360,12 @@ int build_gather(GatherTables &t, int K, int KP, int P, int nlat_own, int nlon_o
                 while (j < K && p[j] == 0.f) ++j;
                 if (j == K) continue;
                 // d = 0, and half a turn on an even circle: +d and -d are the same column
-                const float f = d == 0 || (full && 2 * d == nlon_walk) ? 0.5f : 1.f;
-                auto at = [&](int col) { return 16 * (base + (col % P) * sub + col / P); };
-                by_interval[j].push_back({at(left + d), at(left - d), f * p[j], j + 1 < K ? f * p[j + 1] : 0.f});
+                const bool once = d == 0 || (full && 2 * d == nlon_in), one = (sc - d) % C == 0, two = !once && (sc + d) % C == 0;
+                if (!one && !two) continue;
+                const int first = one ? (sc - d) / C : (sc + d) / C, second = two ? (sc + d) / C : first;
+                const float f = one && two ? 1.f : 0.5f;        // a column of its own is added to itself
+                auto at = [&](int off) { return 16 * (base + ((left + off) % P) * sub + (left + off) / P); };
+                by_interval[j].push_back({at(first), at(second), f * p[j], j + 1 < K ? f * p[j + 1] : 0.f});
             }
             base += ncols;
         });
@@ -365,6 +374,7 @@ int build_gather(GatherTables &t, int K, int KP, int P, int nlat_own, int nlon_o
         cost.push_back({-long(entries.size() - first_entry), lat});
     }
     if (most > kGatherLdsMost) return 0;
+    entries.push_back({0, 0, 0.f, 0.f});
     std::stable_sort(cost.begin(), cost.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
     for (auto &c : cost) order.push_back(c.second);
     const size_t bytes[5] = {chunk_of.size() * 4, chunk.size() * 4, rows.size() * sizeof(GatherRow),
@@ -429,14 +439,15 @@ extern "C" int s2_disco_init(const s2_grid_t *g, int nbasis, s2_disco_t **out)
             const int c = g->cnt[size_t(h) * g->band_max + b], mid = c == g->nlon_in ? 0 : (c - 1) / 2;
             return psi.data() + (size_t(poff[size_t(h) * g->band_max + b]) + mid) * KP;
         };
-        int rc = build_gather(dc->fwd, nbasis, KP, g->pscale, g->nlat_out, g->nlon_out, g->nlon_in, [&](int h, auto &&f) {
+        int rc = build_gather(dc->fwd, nbasis, KP, g->pscale, 1, g->nlat_out, g->nlon_out, g->nlon_in, [&](int h, auto &&f) {
             for (int b = 0; b < g->band_n[h]; ++b) {
                 const int c = g->cnt[size_t(h) * g->band_max + b];
                 if (c > 0) f(g->band_lo[h] + b, arc(h, b), c);
             }
         });
-        if (!rc && g->pscale == 1)
-            rc = build_gather(dc->bwd, nbasis, KP, 1, g->nlat_in, g->nlon_in, g->nlon_out, [&](int hp, auto &&f) {
+        if (!rc)
+            rc = build_gather(dc->bwd, nbasis, KP, 1, g->pscale, g->nlat_in * g->pscale, g->nlon_out, g->nlon_out, [&](int v, auto &&f) {
+                const int hp = v / g->pscale;
                 for (int i = 0; i < g->tband_n[hp]; ++i) {
                     const int h = g->tband_lo[hp] + i, b = hp - g->band_lo[h];
                     if (b < 0 || b >= g->band_n[h]) continue;            // a latitude of weight zero is in no band
@@ -505,7 +516,7 @@ extern "C" int s2_disco_fwd(const s2_disco_t *dc, int batch, int cin, int cout, 
     {
         S2TraceScope tr("disco_z_fwd", 0.0, st);
         if (dc->fwd.lds_bytes) {
-            launch_gather(dc->fwd, K, g->pscale, g->nlon_out, g->nlon_in, g->nlat_out, g->nlat_in, batch * cin, x, z, st);
+            launch_gather(dc->fwd, K, g->pscale, 1, g->nlon_out, g->nlon_in, g->nlat_out, g->nlat_in, batch * cin, x, z, st);
         } else {
             const dim3 grid((g->nlon_out + 63) / 64, g->nlat_out, batch * cin);
             by_basis(K, [&](auto KB) {
@@ -548,7 +559,7 @@ extern "C" int s2_disco_bwd(const s2_disco_t *dc, int batch, int cin, int cout, 
     if (first) {
         {
             S2TraceScope tr("disco_dx", 0.0, st);
-            launch_gather(dc->bwd, K, 1, g->nlon_in, g->nlon_out, g->nlat_in, g->nlat_out, batch * cout, dy, mid, st);
+            launch_gather(dc->bwd, K, 1, g->pscale, g->nlon_out, g->nlon_out, g->nlat_in * g->pscale, g->nlat_out, batch * cout, dy, mid, st);
         }
         S2TraceScope tr("disco_dx mix", 0.0, st);
         hipLaunchKernelGGL(disco_weight_transpose, dim3((cout * cin * K + 255) / 256), dim3(256), 0, st, cout, cin, K, weight, second);
