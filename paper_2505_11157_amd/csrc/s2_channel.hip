@@ -1,0 +1,429 @@
+// Products with channel matrices (1x1 convolutions), float32 on the matrix cores (v_mfma_f32_32x32x2_f32), shared by the
+// attention sub-block and the DISCO convolution:
+//   forward / input gradients   C[b][m][n] = sum_k A(m, k) X[b][k][n] + bias[m] + R[b][m][n]
+//   weight gradients            dW[m][k] = sum_{b, n} dY[b][m][n] X[b][k][n],  dbias[m] = sum_{b, n} dY[b][m][n]
+// One launch takes up to three products side by side (q, k and v from the same X), and a forward product may sum over up
+// to three (matrix, tensor) pairs (the gradient that q, k and v send back to the same input).
+#include <algorithm>
+#include <type_traits>
+
+#include "s2_internal.h"
+
+namespace {
+
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+
+__device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// Products with a matrix.  A workgroup of four wavefronts owns 32 MT rows and 128 grid points; a wavefront owns 32 of
+// the points and all the rows (MT accumulators).  The matrix goes through LDS in double-buffered slices of 16 along k
+// ([k][m], rows 33 mod 64 words apart: the two k rows one instruction reads lie 33 banks apart, and the transposing
+// store spreads over the banks); X does not: lane (column, half) reads X[k0 + 2 j + half][n0 + column] straight into
+// the operand, a whole slice ahead of its use, every element once, in 128-byte row pieces.
+// Bound by the matrix cores (MT instructions of 64 cycles per LDS word and lane), 63 % busy over the launch.  The rows per
+// workgroup follow M, so 64-row products leave no half of a tile empty, and any k fits: 64 x 576 onto 4 x 33024 points went
+// from 230 us (128-row tiles, X through LDS) to 118 us, three 128 x 128 products of one X from 3 x 56 us to 135 us, their
+// sum back from 167 us to 125 us.
+constexpr int kSlice = 16;
+constexpr int slice_pitch(int m) { return (m + 30) / 64 * 64 + 33; }      // smallest p >= m with p = 33 mod 64
+
+template <bool TRANS, int MT>
+__device__ __forceinline__ void product_strip(const S2ChannelProduct &a, int strip, int strips_per_batch, int set, int m0, float *lds)
+{
+    constexpr int MB = 32 * MT, PITCH = slice_pitch(MB), PIECES = MB * kSlice / 4, NP = (PIECES + 255) / 256;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, kk = lane >> 5;
+    const int b = strip / strips_per_batch, n = (strip - b * strips_per_batch) * 128 + wave * 32 + col;
+    const bool ok = n < a.N;
+    unsigned lane_off = (unsigned(kk) * unsigned(a.N) + unsigned(ok ? n : 0)) * 4u;      // past the last column: column 0, not stored
+    asm volatile("" : "+v"(lane_off));
+    const size_t step = size_t(2) * a.N * sizeof(float);
+    const int M = a.M, K = a.K;
+
+    // where the thread's pieces of a slice of the matrix come from (rows past M: the last one, feeding results that are not
+    // stored) and go to
+    float4 rw[NP];
+    unsigned w_off[NP], w_at[NP];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+        const int i = min(tid + 256 * j, PIECES - 1);
+        if constexpr (TRANS) {
+            const int k = i / (8 * MT), m = 4 * (i % (8 * MT));
+            w_off[j] = unsigned(k) * unsigned(M) + unsigned(min(m0 + m, M - 4));
+            w_at[j] = k * PITCH + m;
+        } else {
+            const int m = i >> 2, k = 4 * (i & 3);
+            w_off[j] = unsigned(min(m0 + m, M - 1)) * unsigned(K) + unsigned(k);
+            w_at[j] = k * PITCH + m;
+        }
+    }
+    auto load_w = [&](const float *W) {
+#pragma unroll
+        for (int j = 0; j < NP; ++j) rw[j] = *reinterpret_cast<const float4 *>(W + w_off[j]);
+    };
+    auto store_w = [&](int buf) {
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            if (256 * (j + 1) > PIECES && tid + 256 * j >= PIECES) break;
+            float *d = lds + buf * kSlice * PITCH + w_at[j];
+            constexpr int S = TRANS ? 1 : PITCH;
+            d[0] = rw[j].x; d[S] = rw[j].y; d[2 * S] = rw[j].z; d[3 * S] = rw[j].w;
+        }
+    };
+    f32x16 acc[MT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
+
+    float xa[kSlice / 2], xb[kSlice / 2];
+    auto fetch = [&](float (&x)[kSlice / 2], const char *r, size_t d) {
+        // a uniform running row pointer plus one 32-bit lane offset, opaque so that no 64-bit address per load is kept;
+        // explicitly global: a flat load also counts as an LDS access, and waits for LDS would wait for it
+        asm volatile("" : "+s"(r));
+#pragma unroll
+        for (int j = 0; j < kSlice / 2; ++j) {
+            x[j] = *(const __attribute__((address_space(1))) float *)(r + lane_off);
+            r += d;
+        }
+    };
+    int seg = a.nset > 1 ? set : 0, k0 = 0, buf = 0;
+    const int end = seg + (a.nset > 1 ? 1 : a.npair);
+    const float *W = a.W[seg];
+    const char *row = reinterpret_cast<const char *>(a.X[seg] + size_t(b) * K * a.N);
+    load_w(W);
+    fetch(xa, row, step);
+    store_w(0);
+    __syncthreads();
+    auto advance = [&]() {
+        if (k0 + kSlice < K) {
+            k0 += kSlice;
+            W += TRANS ? size_t(kSlice) * M : kSlice;
+            row += kSlice / 2 * step;
+            return true;
+        }
+        if (seg + 1 >= end) return false;
+        k0 = 0;
+        W = a.W[++seg];
+        row = reinterpret_cast<const char *>(a.X[seg] + size_t(b) * K * a.N);
+        return true;
+    };
+    // Nothing branches around the requests (the compiler would wait for all of them where the paths meet): behind the
+    // last slice they go to one address, for nothing.
+    auto slice = [&](float (&cur)[kSlice / 2], float (&nxt)[kSlice / 2]) {
+        const bool more = advance();
+        load_w(W);
+        fetch(nxt, row, more ? step : 0);
+        __builtin_amdgcn_sched_barrier(0);          // the requests stay in front of the arithmetic they overlap
+        const float *wl = lds + buf * kSlice * PITCH + kk * PITCH + col;
+        float w[2][4][MT];                          // operands of the matrix, read four steps ahead of their instructions
+        auto read = [&](int g) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < MT; ++i) w[g][j][i] = wl[2 * (4 * g + j) * PITCH + 32 * i];
+        };
+        read(0);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (j == 2) {
+                read(1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int i = 0; i < MT; ++i) acc[i] = mfma32(w[j >> 2][j & 3][i], cur[j], acc[i]);
+        }
+        store_w(buf ^ 1);
+        __syncthreads();
+        buf ^= 1;
+        return more;
+    };
+    while (slice(xa, xb) && slice(xb, xa)) {}
+    if (!ok) return;
+    // per half row block all the reads (bias, residual) are issued before the first store, so that they overlap
+    const float *bias = a.bias[set];
+    float *Cb = a.C[set] + size_t(b) * M * a.N + n;
+    const float *Rb = a.R ? a.R + size_t(b) * M * a.N + n : nullptr;
+#pragma unroll
+    for (int i = 0; i < 2 * MT; ++i) {
+        if (m0 + 16 * i >= M) break;
+        float add[8], res[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int m = m0 + 16 * i + 8 * (e >> 2) + 4 * kk + (e & 3);
+            add[e] = bias ? bias[m] : 0.f;
+            res[e] = Rb ? Rb[size_t(m) * a.N] : 0.f;
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int m = m0 + 16 * i + 8 * (e >> 2) + 4 * kk + (e & 3);
+            Cb[size_t(m) * a.N] = (acc[i >> 1][8 * (i & 1) + e] + add[e]) + res[e];
+        }
+    }
+}
+
+// Strips of the whole rounds of workgroups at MT row blocks, those of the last, partial round cut into single row blocks.
+// The workgroups of one strip of X are eight apart: they run on the same die and share its L2.
+template <bool TRANS, int MT>
+__global__ void __launch_bounds__(256, MT == 1 ? 8 : 4)
+channel_product(S2ChannelProduct a, int strips_per_batch, int nstrips, int mblocks, int whole_groups)
+{
+    extern __shared__ float lds[];
+    const int parts = a.nset * mblocks, whole = whole_groups * 8 * parts, lo = blockIdx.x & 7;
+    int id = blockIdx.x;
+    if (id < whole || MT == 1) {
+        id >>= 3;
+        const int part = id % parts, strip = (id / parts) * 8 + lo;
+        if (strip < nstrips)
+            product_strip<TRANS, MT>(a, strip, strips_per_batch, part / mblocks, (part % mblocks) * 32 * MT, lds);
+    } else {
+        id = (id - whole) >> 3;
+        const int part = id % (parts * MT), strip = (whole_groups + id / (parts * MT)) * 8 + lo, m0 = (part % (mblocks * MT)) * 32;
+        if (strip < nstrips && m0 < a.M) product_strip<TRANS, 1>(a, strip, strips_per_batch, part / (mblocks * MT), m0, lds);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// Weight gradients: partial sums over a share of (batch, grid point), added in a fixed order by a second launch, so every
+// result is bit-reproducible.  A workgroup of WR x WN wavefronts owns 32 MT WR rows of dY and 32 WN rows of X, a
+// wavefront 32 MT rows of dY and 32 of X; slices of 32 grid points (whole 128-byte lines of every row) go through double-buffered
+// LDS, row by row, 36 words apart: stores and loads are 16 bytes and free of bank conflicts.  Instruction j of a group
+// of eight points contracts over points j and 4 + j, so that one 16-byte read per operand serves four instructions.  The
+// row sums of dY come from the pieces on their way to LDS.
+// Bound by the matrix cores.  Rows per workgroup by M, columns by whichever width pads K least: 64 x 576 over 4 x 33024
+// points 230 -> 111 us, three 128 x 128 3 x 56 -> 135 us (with the row sums that used to be three more launches).
+constexpr int kPoints = 32, kPitch = kPoints + 4;
+
+template <int MT, int WR, int WN>
+__global__ void __launch_bounds__(64 * WR * WN)
+channel_wgrad(S2ChannelGrad a, int ktiles, int mblocks, int nsplit, float *__restrict__ part)
+{
+    constexpr int YR = 32 * MT * WR, ROWS = YR + 32 * WN, NT = 64 * WR * WN, NP = (ROWS * 8 + NT - 1) / NT, NA = (YR * 8 + NT - 1) / NT;
+    __shared__ __attribute__((aligned(16))) float S[2][ROWS * kPitch];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, kk = lane >> 5, M = a.M, K = a.K, N = a.N;
+    const int wr = wave % WR, wn = wave / WR;
+    // the tiles of one share of the points are eight workgroups apart: same die, same L2
+    int id = blockIdx.x;
+    const int slo = id & 7;
+    id >>= 3;
+    const int tiles = ktiles * mblocks * a.nset;
+    int tile = id % tiles;
+    const int split = (id / tiles) * 8 + slo;
+    const int set = tile / (ktiles * mblocks);
+    tile -= set * ktiles * mblocks;
+    const int m0 = (tile / ktiles) * YR, k0 = (tile % ktiles) * 32 * WN;
+    const int per = (N + kPoints - 1) / kPoints;
+    const long slices = long(a.batch) * per;
+    long s = slices * split / nsplit;
+    const long s_end = slices * (split + 1) / nsplit;
+    const float *dY = a.dY[set], *X = a.X[set];
+
+    float4 r[NP];
+    unsigned off[NP];          // row inside the tile (rows past the end: the last one, feeding results that are not stored)
+    float bsum[NA];
+    const int pc = 4 * (tid & 7);
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+        const int row = min((tid >> 3) + (NT / 8) * j, ROWS - 1);
+        off[j] = unsigned(row < YR ? min(row, M - 1 - m0) : min(row - YR, K - 1 - k0)) * unsigned(N) + pc;
+    }
+#pragma unroll
+    for (int j = 0; j < NA; ++j) bsum[j] = 0.f;
+    bool in = false;           // is the piece inside the row (the last slice of a row may be half a slice)
+    auto load = [&](long c) {
+        const int b = int(c / per), n = int(c - long(b) * per) * kPoints;
+        const float *y = dY + (size_t(b) * M + m0) * N + n, *x = X + (size_t(b) * K + k0) * N + n;
+        in = n + pc < N;
+        const int back = in ? 0 : pc;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            const bool isy = (tid >> 3) + (NT / 8) * j < YR;
+            r[j] = *reinterpret_cast<const float4 *>((isy ? y : x) + (off[j] - back));
+        }
+    };
+    auto store = [&](int buf) {
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            const int row = min((tid >> 3) + (NT / 8) * j, ROWS - 1);
+            float4 v = r[j];
+            if (!in) v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (j < NA) bsum[j < NA ? j : 0] += (v.x + v.y) + (v.z + v.w);
+            *reinterpret_cast<float4 *>(&S[buf][row * kPitch + pc]) = v;
+        }
+    };
+    f32x16 acc[MT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
+    if (s < s_end) {
+        load(s);
+        store(0);
+    }
+    __syncthreads();
+    int buf = 0;
+    for (; s < s_end; ++s) {
+        const bool more = s + 1 < s_end;
+        if (more) {
+            load(s + 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const float *sb = &S[buf][col * kPitch + 4 * kk], *ya = sb + wr * 32 * MT * kPitch, *xa = sb + (YR + 32 * wn) * kPitch;
+#pragma unroll
+        for (int q = 0; q < kPoints / 8; ++q) {
+            const float4 x4 = *reinterpret_cast<const float4 *>(xa + 8 * q);
+            float4 y4[MT];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) y4[i] = *reinterpret_cast<const float4 *>(ya + 32 * i * kPitch + 8 * q);
+#pragma unroll
+            for (int i = 0; i < MT; ++i) acc[i] = mfma32(y4[i].x, x4.x, acc[i]);
+#pragma unroll
+            for (int i = 0; i < MT; ++i) acc[i] = mfma32(y4[i].y, x4.y, acc[i]);
+#pragma unroll
+            for (int i = 0; i < MT; ++i) acc[i] = mfma32(y4[i].z, x4.z, acc[i]);
+#pragma unroll
+            for (int i = 0; i < MT; ++i) acc[i] = mfma32(y4[i].w, x4.w, acc[i]);
+        }
+        if (more) {
+            store(buf ^ 1);
+            __syncthreads();
+            buf ^= 1;
+        }
+    }
+    float *P = part + (size_t(set) * nsplit + split) * (size_t(M) * K + M);
+    const int k = k0 + 32 * wn + col;
+    if (k < K) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int m = m0 + 32 * (MT * wr + i) + 8 * (e >> 2) + 4 * kk + (e & 3);
+                if (m < M) P[size_t(m) * K + k] = acc[i][e];
+            }
+    }
+    if (k0 == 0) {
+#pragma unroll
+        for (int j = 0; j < NA; ++j) {
+            float t = bsum[j];
+            t += __shfl_xor(t, 1);
+            t += __shfl_xor(t, 2);
+            t += __shfl_xor(t, 4);
+            const int row = (tid >> 3) + (NT / 8) * j;
+            if ((tid & 7) == 0 && row < YR && m0 + row < M) P[size_t(M) * K + m0 + row] = t;
+        }
+    }
+}
+
+// Adds the partials of element i in order.  A workgroup owns 64 elements; thread (q, e) adds the partials q, q + 4,
+// q + 8, ... of element e (four chains of loads in flight per element), then the four sums are added.
+__global__ void __launch_bounds__(256)
+channel_sum_partials(S2ChannelGrad a, int nsplit, const float *__restrict__ part)
+{
+    __shared__ float red[4][64];
+    const int e = threadIdx.x & 63, q = threadIdx.x >> 6, set = blockIdx.y;
+    const size_t MK = size_t(a.M) * a.K, count = MK + a.M, i = size_t(blockIdx.x) * 64 + e;
+    const float *p0 = part + size_t(set) * nsplit * count + i;
+    float s = 0.f;
+    if (i < count) {
+#pragma unroll 8
+        for (int p = q; p < nsplit; p += 4) s += p0[size_t(p) * count];
+    }
+    red[q][e] = s;
+    __syncthreads();
+    if (q != 0 || i >= count) return;
+    const float t = (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
+    if (i < MK) {
+        if (a.dW[set]) a.dW[set][i] = t;
+    } else if (a.dbias[set]) {
+        a.dbias[set][i - MK] = t;
+    }
+}
+
+// 32-row blocks per workgroup: all of M up to 128 rows, else the block size that pads M least (the larger one on a tie)
+inline int row_blocks(int M)
+{
+    if (M <= 128) return (M + 31) / 32;
+    int best = 4;
+    for (int mt = 3; mt >= 2; --mt)
+        if ((M + 32 * mt - 1) / (32 * mt) * mt < (M + 32 * best - 1) / (32 * best) * best) best = mt;
+    return best;
+}
+// Weight gradients: wavefronts per workgroup side by side.  Two row blocks take one each (three pairs, two or one: the
+// width that pads K least, the largest on a tie), so that the number of wavefronts is a multiple of four and every SIMD
+// gets the same share; otherwise one wavefront takes all the row blocks, four of them side by side.
+inline int col_waves(int mt, int K)
+{
+    if (mt != 2) return 4;
+    int best = 6;
+    for (int wn = 4; wn >= 2; wn -= 2)
+        if ((K + 32 * wn - 1) / (32 * wn) * wn < (K + 32 * best - 1) / (32 * best) * best) best = wn;
+    return best;
+}
+struct GradPlan { int mt, wn, mblocks, ktiles, nsplit; };
+// Splits: as many workgroups over all products of the launch as are resident at once (by their LDS), in multiples of eight
+// (one per die).
+inline GradPlan grad_plan(int M, int K, int nset)
+{
+    GradPlan p;
+    p.mt = row_blocks(M);
+    p.wn = col_waves(p.mt, K);
+    p.mblocks = (M + 32 * p.mt - 1) / (32 * p.mt);
+    p.ktiles = (K + 32 * p.wn - 1) / (32 * p.wn);
+    const int lds = 2 * 32 * (p.mt + p.wn) * kPitch * int(sizeof(float)), want = 256 * std::min(4, 160 * 1024 / lds);
+    p.nsplit = std::max(8, want / (p.mblocks * p.ktiles * nset) / 8 * 8);
+    return p;
+}
+
+}  // namespace
+
+void s2_channel_product(bool trans, const S2ChannelProduct &a, hipStream_t st)
+{
+    const int mt = row_blocks(a.M), mblocks = (a.M + 32 * mt - 1) / (32 * mt), spb = (a.N + 127) / 128, nstrips = spb * a.batch;
+    // Four workgroups per compute unit (eight with one row block), held to by the LDS they ask for: with room for more the
+    // dispatcher fills some units with five and leaves others three.
+    const int occ = mt == 1 ? 8 : 4, parts = mblocks * a.nset, round = 256 * occ, groups = (nstrips + 7) / 8;
+    const int per_round = std::max(1, round / (8 * parts)), rest = groups % per_round;
+    const bool split = mt > 1 && rest * 8 * parts * mt <= round;
+    const int whole = split ? groups - rest : groups;
+    const dim3 grid(unsigned(whole + (groups - whole) * mt) * 8 * parts);
+    const size_t lds = mt == 1 ? 19 * 1024 : 38 * 1024;
+#define S2_PRODUCT(T, MT) hipLaunchKernelGGL((channel_product<T, MT>), grid, dim3(256), lds, st, a, spb, nstrips, mblocks, whole)
+    switch (mt + (trans ? 4 : 0)) {
+    case 1: S2_PRODUCT(false, 1); break;
+    case 2: S2_PRODUCT(false, 2); break;
+    case 3: S2_PRODUCT(false, 3); break;
+    case 4: S2_PRODUCT(false, 4); break;
+    case 5: S2_PRODUCT(true, 1); break;
+    case 6: S2_PRODUCT(true, 2); break;
+    case 7: S2_PRODUCT(true, 3); break;
+    default: S2_PRODUCT(true, 4); break;
+    }
+#undef S2_PRODUCT
+}
+
+size_t s2_channel_grad_floats(int M, int K, int nset)
+{
+    return size_t(nset) * grad_plan(M, K, nset).nsplit * (size_t(M) * K + M);
+}
+
+void s2_channel_grad(const S2ChannelGrad &a, float *part, hipStream_t st)
+{
+    const GradPlan p = grad_plan(a.M, a.K, a.nset);
+    const dim3 grid(unsigned(p.ktiles) * p.mblocks * a.nset * p.nsplit);
+#define S2_GRAD(MT, WR, WN) \
+    hipLaunchKernelGGL((channel_wgrad<MT, WR, WN>), grid, dim3(64 * WR * WN), 0, st, a, p.ktiles, p.mblocks, p.nsplit, part)
+    if (p.mt == 1) S2_GRAD(1, 1, 4);
+    else if (p.mt == 2 && p.wn == 2) S2_GRAD(1, 2, 2);
+    else if (p.mt == 2 && p.wn == 4) S2_GRAD(1, 2, 4);
+    else if (p.mt == 2) S2_GRAD(1, 2, 6);
+    else if (p.mt == 3) S2_GRAD(3, 1, 4);
+    else S2_GRAD(4, 1, 4);
+#undef S2_GRAD
+    const size_t count = size_t(a.M) * a.K + a.M;
+    hipLaunchKernelGGL(channel_sum_partials, dim3(unsigned((count + 63) / 64), a.nset), dim3(256), 0, st, a, p.nsplit, part);
+}

@@ -497,7 +497,7 @@ extern "C" size_t s2_disco_workspace_bytes(const s2_disco_t *dc, int batch, int 
     const size_t zs = up(size_t(batch) * cin * dc->K * n_out);
     const size_t mid = transposed_first(dc, cin) ? up(size_t(batch) * cout * dc->K * n_in) + up(size_t(cout) * cin * dc->K)
                                                  : zs + up(size_t(batch) * cin * padded(dc->K) * n_out);
-    return (zs + mid + up(s2_wgrad_part_floats(cout, cin * dc->K))) * sizeof(float);
+    return (zs + mid + up(s2_channel_grad_floats(cout, cin * dc->K, 1))) * sizeof(float);
 }
 
 extern "C" int s2_disco_fwd(const s2_disco_t *dc, int batch, int cin, int cout, const float *x, const float *weight,
@@ -525,7 +525,7 @@ extern "C" int s2_disco_fwd(const s2_disco_t *dc, int batch, int cin, int cout, 
         }
     }
     S2TraceScope tr("disco_mix", 0.0, st);
-    s2_gemm_f32(false, cout, n_out, cin * K, batch, weight, z, bias, nullptr, y, false, st);
+    s2_channel_product(false, {cout, n_out, cin * K, batch, 1, 1, {weight}, {z}, {bias}, nullptr, {y}}, st);
     S2_HIP_CHECK(hipGetLastError());
     return S2_OK;
 }
@@ -552,9 +552,8 @@ extern "C" int s2_disco_bwd(const s2_disco_t *dc, int batch, int cin, int cout, 
     float *part = second + up(first ? size_t(cout) * cin * K : size_t(batch) * cin * padded(K) * n_out);
     {
         S2TraceScope tr("disco_bwd mix", 0.0, st);
-        if (dweight) s2_wgrad_f32(cout, cin * K, n_out, batch, dy, z, part, dweight, st);
-        if (dbias) s2_channel_sum_f32(batch, cout, n_out, dy, dbias, part, s2_wgrad_part_floats(cout, cin * K), st);
-        if (!first) s2_gemm_f32(true, cin * K, n_out, cout, batch, weight, dy, nullptr, nullptr, mid, false, st);
+        if (dweight || dbias) s2_channel_grad({cout, n_out, cin * K, batch, 1, {dy}, {z}, {dweight}, {dbias}}, part, st);
+        if (!first) s2_channel_product(true, {cin * K, n_out, cout, batch, 1, 1, {weight}, {dy}, {nullptr}, nullptr, {mid}}, st);
     }
     if (first) {
         {
@@ -563,7 +562,7 @@ extern "C" int s2_disco_bwd(const s2_disco_t *dc, int batch, int cin, int cout, 
         }
         S2TraceScope tr("disco_dx mix", 0.0, st);
         hipLaunchKernelGGL(disco_weight_transpose, dim3((cout * cin * K + 255) / 256), dim3(256), 0, st, cout, cin, K, weight, second);
-        s2_gemm_f32(false, cin, g->nlat_in * g->nlon_in, cout * K, batch, second, mid, nullptr, nullptr, dx, false, st);
+        s2_channel_product(false, {cin, g->nlat_in * g->nlon_in, cout * K, batch, 1, 1, {second}, {mid}, {nullptr}, nullptr, {dx}}, st);
         S2_HIP_CHECK(hipGetLastError());
         return S2_OK;
     }

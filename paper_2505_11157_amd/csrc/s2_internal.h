@@ -146,24 +146,30 @@ int s2_nattn_stream_configure();
 int s2_nattn_mfma_configure();
 int s2_nattn_band_configure();
 int s2_nattn_tile_configure();
-int s2_mha_configure();
 
 // great-circle angle between two points given by their colatitudes and their difference in longitude (float64)
 double s2_great_circle(double colat_a, double colat_b, double dphi);
 
-// Channel matrices on the fp32 matrix cores (s2_mha.hip), all tensors [batch][channels][N] contiguous:
-//   s2_gemm_f32:  C[b][m][n] (+)= sum_k A(m, k) X[b][k][n] + bias[m] + R[b][m][n],  A = W (M x K) or W^T (W is K x M)
-//   s2_wgrad_f32: dW[m][k] = sum_{b, n} dY[b][m][n] X[b][k][n]  (partial sums in `part`, s2_wgrad_part_floats(M, K)
-//                 floats, added in a fixed order)
-//   s2_channel_sum_f32: out[c] = sum_{b, n} u[b][c][n]  (`part`: scratch of part_floats floats for partial sums, may be
-//                       NULL: then one workgroup per channel does the whole sum)
-// M, K multiples of 16 and N a multiple of 16.
-void s2_gemm_f32(bool trans_a, int M, int N, int K, int batch, const float *W, const float *X, const float *bias,
-                 const float *R, float *C, bool accumulate, hipStream_t st);
-size_t s2_wgrad_part_floats(int M, int K);
-void s2_wgrad_f32(int M, int K, int N, int batch, const float *dY, const float *X, float *part, float *dW, hipStream_t st);
-void s2_channel_sum_f32(int batch, int C, int N, const float *u, float *out, float *part, size_t part_floats,
-                        hipStream_t st);
+// Channel matrices on the fp32 matrix cores (s2_channel.hip), all tensors [batch][channels][N] contiguous and 16-byte
+// aligned, M, K and N multiples of 16.
+//   s2_channel_product: nset products side by side, C[i] = A[i] X[i] + bias[i], or (nset = 1) one over npair pairs,
+//                       C[0] = sum_i A[i] X[i] + bias[0] + R;  A = W (M x K) or W^T (trans, W is K x M)
+//   s2_channel_grad:    nset times dW[i] (M x K) = sum_{b, n} dY[i] X[i]^T, dbias[i] = sum_{b, n} dY[i] (either may be
+//                       NULL); `part`: s2_channel_grad_floats(M, K, nset) floats of scratch
+struct S2ChannelProduct {
+    int M, N, K, batch, nset, npair;
+    const float *W[3], *X[3], *bias[3];
+    const float *R;
+    float *C[3];
+};
+struct S2ChannelGrad {
+    int M, N, K, batch, nset;
+    const float *dY[3], *X[3];
+    float *dW[3], *dbias[3];
+};
+void s2_channel_product(bool trans, const S2ChannelProduct &a, hipStream_t st);
+size_t s2_channel_grad_floats(int M, int K, int nset);
+void s2_channel_grad(const S2ChannelGrad &a, float *part, hipStream_t st);
 
 void s2_set_error(const std::string &msg);
 int s2_fail(int code, const std::string &msg);
