@@ -20,7 +20,11 @@ void by_mode(int mode, F &&f)
 
 }  // namespace
 
-int s2_nattn_band_configure() { return BandSet<kWide>::configure() || BandSet<kNarrow>::configure() || BandSet<kRagged>::configure(); }
+// the band-tile kernels of both element types
+int s2_nattn_band_configure()
+{
+    return BandSet<kWide>::configure() || BandSet<kNarrow>::configure() || BandSet<kRagged>::configure() || s2_nattn_tile_configure();
+}
 
 bool s2_nattn_band_supported(const S2DeviceTables &t, int d, int e)
 {
