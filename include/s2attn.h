@@ -121,6 +121,10 @@ size_t s2_nattn_bwd_workspace_bytes(const s2_grid_t *g, int batch, int heads, in
  * bf16 matrix cores where the shape allows - equal grids, d_qk = d_v = 32, longitude count a multiple of 64 - with
  * float32 accumulation and softmax, otherwise float32 arithmetic on bf16 loads; lse float32 either way).
  * d_qk, d_v in [1, 128].
+ * Non-finite inputs (both directions): a NaN or an infinity at a point reaches the results whose sums hold that point
+ * and no others.  Exception: with d_qk = d_v = 32, float32 tensors on equal, 2:1 and 1:2 grids and bf16 tensors on
+ * equal grids with a longitude count that is a multiple of 64 may also lose results of points close by (masked
+ * products there are multiplied by zero).
  * Errors: S2_ERR_INVALID_ARG (NULL or not 16-byte aligned pointers, sizes < 1),
  * S2_ERR_UNSUPPORTED (dtype, head dims), S2_ERR_DEVICE (host-only handle or
  * launch failure).

@@ -28,6 +28,7 @@
 
 #include "s2_internal.h"
 #include "s2_nattn_band.h"
+#include "s2_nattn_exact.h"
 #include "s2_nattn_walk.h"
 
 namespace {
@@ -132,9 +133,10 @@ struct Stage {
 };
 
 // ---------------------------------------------------------------------------------------------------------------
-// Forward.
+// Forward.  Up to 32 channels four wavefronts per SIMD, as many as the two tiles in LDS allow (91 x 181, 32 slices: 424 us; with 129
+// registers, three wavefronts, 465 us).
 template <int D, int NO, int MODE>
-__global__ void __launch_bounds__(256, 2)
+__global__ void __launch_bounds__(256, D <= 32 ? 4 : 2)
 nattn_fwd_band(BandArgs a, const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v, float *__restrict__ out,
                float *__restrict__ lse)
 {
@@ -254,11 +256,13 @@ nattn_fwd_band(BandArgs a, const float *__restrict__ q, const float *__restrict_
         else tiles(std::integral_constant<int, kOwnTiles>());
     }
     if (!w.active) return;
+    unsigned again[NO];                  // owners whose sums took in a non-finite value (s2_nattn_exact.h)
 #pragma unroll
     for (int o = 0; o < NO; ++o) {
         const float lt = group_sum(l[o]);
         const int u = w.W0 + 16 * o + n;
-        if (u >= nU) continue;
+        again[o] = not_finite(acc[o], u < nU);
+        if (u >= nU || (again[o] >> n & 1)) continue;
         const float inv = 1.f / lt;
         float *ob = out + size_t(w.bh) * (MODE == kRagged ? a.e : D) * w.plane_own + w.own_at + w.c_own * u;
 #pragma unroll
@@ -269,12 +273,13 @@ nattn_fwd_band(BandArgs a, const float *__restrict__ q, const float *__restrict_
         if (g == 0)
             lse[size_t(w.bh) * w.plane_own + w.own_at + w.c_own * u] = (m[o] + log2f(lt * a.omega_ref)) * 0.6931471805599453f;
     }
+    exact_fwd<float, G::OW>(again, w.wave);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
 // Backward, query side: dq and D_i = dout_i . out_i (written for the key-side launch).
 template <int D, int NO, int MODE>
-__global__ void __launch_bounds__(256, 2)
+__global__ void __launch_bounds__(256, D <= 32 ? 4 : 2)
 nattn_bwd_dq_band(BandArgs a, const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
                   const float *__restrict__ o_, const float *__restrict__ lse, const float *__restrict__ go, float *__restrict__ dq,
                   float *__restrict__ Dws)
@@ -393,10 +398,12 @@ nattn_bwd_dq_band(BandArgs a, const float *__restrict__ q, const float *__restri
         tiles(std::integral_constant<int, kAnyTiles>());
     }
     if (!w.active) return;
+    unsigned again[NO];                  // owners whose sums took in a non-finite value (s2_nattn_exact.h)
 #pragma unroll
     for (int o = 0; o < NO; ++o) {
         const int u = w.W0 + 16 * o + n;
-        if (u >= nU) continue;
+        again[o] = not_finite(acc[o], u < nU);
+        if (u >= nU || (again[o] >> n & 1)) continue;
         float *ob = dq + slice_q + w.c_own * u;
 #pragma unroll
         for (int mt = 0; mt < D / 16; ++mt)
@@ -404,6 +411,7 @@ nattn_bwd_dq_band(BandArgs a, const float *__restrict__ q, const float *__restri
             for (int rr = 0; rr < 4; ++rr)
                 if (has<MODE>(16 * mt + 4 * g + rr, a.d)) *(ob + size_t(16 * mt + 4 * g + rr) * w.plane_own) = acc[o][mt][rr] * a.scale;
     }
+    exact_dq<float, G::OW>(again, w.wave);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -548,10 +556,12 @@ nattn_bwd_dkdv_band(BandArgs a, const float *__restrict__ q, const float *__rest
         tiles(std::integral_constant<int, kAnyTiles>());
     }
     if (!w.active) return;
+    unsigned again[NO];                  // owners whose sums took in a non-finite value (s2_nattn_exact.h)
 #pragma unroll
     for (int o = 0; o < NO; ++o) {
         const int u = w.W0 + 16 * o + n;
-        if (u >= nU) continue;
+        again[o] = not_finite(adk[o], u < nU) | not_finite(adv[o], u < nU);
+        if (u >= nU || (again[o] >> n & 1)) continue;
 #pragma unroll
         for (int mt = 0; mt < D / 16; ++mt)
 #pragma unroll
@@ -562,6 +572,7 @@ nattn_bwd_dkdv_band(BandArgs a, const float *__restrict__ q, const float *__rest
                 if (has<MODE>(c, a.e)) *(dv + slice_v + at) = adv[o][mt][rr] * omega;
             }
     }
+    exact_dkdv<float, G::OW>(again, w.wave);
 }
 
 template <int D, int NO>

@@ -21,6 +21,7 @@
 
 #include "s2_internal.h"
 #include "s2_nattn_tile.h"
+#include "s2_nattn_exact.h"
 #include "s2_nattn_walk.h"
 
 namespace {
@@ -376,11 +377,13 @@ nattn_fwd_tile(BandArgs a, const bf16raw *__restrict__ q, const bf16raw *__restr
         if (more) store(buf ^ 1);
     }
     if (!w.active) return;
+    unsigned again[NO];                  // owners whose sums took in a non-finite value (s2_nattn_exact.h)
 #pragma unroll
     for (int o = 0; o < NO; ++o) {
         const float lt = group_sum(l[o]);
         const int u = w.W0 + 16 * o + n;
-        if (u >= nU) continue;
+        again[o] = not_finite(acc[o], u < nU);
+        if (u >= nU || (again[o] >> n & 1)) continue;
         const float inv = 1.f / lt;
         bf16raw *ob = out + size_t(w.bh) * (MODE == kRagged ? a.e : D) * w.plane_own + w.own_at + w.c_own * u;
 #pragma unroll
@@ -391,6 +394,7 @@ nattn_fwd_tile(BandArgs a, const bf16raw *__restrict__ q, const bf16raw *__restr
         if (g == 0)
             lse[size_t(w.bh) * w.plane_own + w.own_at + w.c_own * u] = (m[o] + log2f(lt * a.omega_ref)) * 0.6931471805599453f;
     }
+    exact_fwd<bf16raw, G::OW>(again, w.wave);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -496,10 +500,12 @@ nattn_bwd_dq_tile(BandArgs a, const bf16raw *__restrict__ q, const bf16raw *__re
         if (more) store(buf ^ 1);
     }
     if (!w.active) return;
+    unsigned again[NO];                  // owners whose sums took in a non-finite value (s2_nattn_exact.h)
 #pragma unroll
     for (int o = 0; o < NO; ++o) {
         const int u = w.W0 + 16 * o + n;
-        if (u >= nU) continue;
+        again[o] = not_finite(acc[o], u < nU);
+        if (u >= nU || (again[o] >> n & 1)) continue;
         bf16raw *ob = dq + slice_q + w.c_own * u;
 #pragma unroll
         for (int mt = 0; mt < D / 16; ++mt)
@@ -507,6 +513,7 @@ nattn_bwd_dq_tile(BandArgs a, const bf16raw *__restrict__ q, const bf16raw *__re
             for (int rr = 0; rr < 4; ++rr)
                 if (has<MODE>(16 * mt + 4 * g + rr, a.d)) stx(ob + size_t(16 * mt + 4 * g + rr) * w.plane_own, acc[o][mt][rr] * a.scale);
     }
+    exact_dq<bf16raw, G::OW>(again, w.wave);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -621,10 +628,12 @@ nattn_bwd_dkdv_tile(BandArgs a, const bf16raw *__restrict__ q, const bf16raw *__
         if (more) store(buf ^ 1);
     }
     if (!w.active) return;
+    unsigned again[NO];                  // owners whose sums took in a non-finite value (s2_nattn_exact.h)
 #pragma unroll
     for (int o = 0; o < NO; ++o) {
         const int u = w.W0 + 16 * o + n;
-        if (u >= nU) continue;
+        again[o] = not_finite(adk[o], u < nU) | not_finite(adv[o], u < nU);
+        if (u >= nU || (again[o] >> n & 1)) continue;
 #pragma unroll
         for (int mt = 0; mt < D / 16; ++mt)
 #pragma unroll
@@ -635,6 +644,7 @@ nattn_bwd_dkdv_tile(BandArgs a, const bf16raw *__restrict__ q, const bf16raw *__
                 if (has<MODE>(c, a.e)) stx(dv + slice_v + at, adv[o][mt][rr] * omega);
             }
     }
+    exact_dkdv<bf16raw, G::OW>(again, w.wave);
 }
 
 template <int D, int NO>

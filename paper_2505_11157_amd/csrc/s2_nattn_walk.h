@@ -248,7 +248,7 @@ struct BandWhere {
     size_t own_at;                 // offset of owner column 0 of the wavefront's row inside a plane
     int nlon_walk, c_own, c_walk;
     template <int OW>
-    __device__ __forceinline__ void set(const BandArgs &a)
+    __device__ __forceinline__ void set(const BandArgs &a, int thread = threadIdx.x)
     {
         nU = a.b.nU;
         const int ngrp = (nU + OW - 1) / OW, nseg = (a.b.n_own + 3) >> 2;
@@ -256,7 +256,7 @@ struct BandWhere {
         grp = id % ngrp; id /= ngrp;
         bh = id % a.nbh;
         first = 4 * segment_of(id / a.nbh, nseg);
-        tid = threadIdx.x; lane = tid & 63; wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        tid = thread; lane = tid & 63; wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         n = lane & 15; g = lane >> 4;
         own = first + wave;
         active = own < a.b.n_own;
