@@ -2,8 +2,11 @@
 // outputs, two key tiles (32 keys) per step, for d, e <= 64 (rounded up to 16, 32 or 64 channels) and any pair of grids.
 // s2_nattn_walk.h describes the walk.
 //
-// Precision.  q, k, v and dout enter the matrix cores as they are; probabilities and dS, which multiply them, as two bf16 terms
-// each (2^-17); logits, softmax, logsumexp, D and all accumulators are float32.
+// Precision.  q, k, v and dout enter the matrix cores as they are; probabilities and dS, which multiply them, are float32
+// values cut into three bf16 terms, which hold the 24 bits exactly, so that every product is the float32 one; logits, softmax,
+// logsumexp, D and all accumulators are float32.  Share of `out` and dv that differ from the correctly rounded result: 1.3e-4
+// and 3e-4, as on the fp32 matrix cores (with two terms 2.3e-3 both).  The third term costs 4 to 14 % (129 x 256, 32 slices,
+// d = 16: 0.93 -> 1.03 ms per step, d = 64: 3.11 -> 3.23 ms); cut off bit by bit it is cheaper than rounded (1.06 ms).
 //
 // Operands of v_mfma_f32_16x16x32_bf16 (A: 16 x 32, lane (row n = lane & 15, g = lane >> 4) holds k = 8 g .. 8 g + 7; B the
 // same with columns; C/D: lane holds rows 4 g .. 4 g + 3 of column n):
@@ -28,8 +31,6 @@ namespace {
 
 using namespace s2walk;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -51,6 +52,7 @@ template <int D, int NO, int MODE>
 struct Occ {
     static constexpr int regs = D * NO + (MODE != kWide && D == 64 ? 64 : 0);
     static constexpr int fwd = regs <= 64 ? 4 : regs <= 128 ? 3 : 2, bwd = regs <= 48 ? 4 : regs <= 64 ? 3 : 2;
+    static constexpr int dq = D <= 32 && NO <= 2 ? 4 : bwd;
 };
 // first-product operand of one point or one key: 8 channels per lane and step (16 channels: 4)
 template <int D>
@@ -65,20 +67,6 @@ struct Chan<16> {
 __device__ __forceinline__ float ldx(const bf16raw *p) { return __builtin_bit_cast(float, unsigned(*p) << 16); }
 __device__ __forceinline__ void stx(bf16raw *p, float x) { *p = __builtin_bit_cast(bf16raw, (__bf16)x); }
 
-// two floats as N packed pairs of bf16 terms: t[0] nearest, t[1] nearest to the rest, ...
-template <int N>
-__device__ __forceinline__ void terms2(float x, float y, unsigned (&t)[N])
-{
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        t[k] = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{x, y}), bf16x2));
-        if (k + 1 < N) {
-            x -= __builtin_bit_cast(float, t[k] << 16);
-            y -= __builtin_bit_cast(float, t[k] & 0xffff0000u);
-        }
-    }
-}
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ f32x4 mma(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 __device__ __forceinline__ f32x4 mma(bf16x4 a, bf16x4 b, f32x4 c)
@@ -109,8 +97,8 @@ struct Tile {
         }
         return acc;
     }
-    // acc[mt] += (channels 16 mt ..) . (the lane's eight values of the columns of two tiles, two terms)
-    static __device__ __forceinline__ void sum(const __bf16 *tile, int col, const bf16x8 (&b)[2], f32x4 (&acc)[D / 16], int n, int g)
+    // acc[mt] += (channels 16 mt ..) . (the lane's eight float32 values of the columns of two tiles), smallest terms first
+    static __device__ __forceinline__ void sum(const __bf16 *tile, int col, const bf16x8 (&b)[3], f32x4 (&acc)[D / 16], int n, int g)
     {
         const __bf16 *p = tile + n * G::PITCH + col + 4 * g;
         bf16x8 a[D / 16];
@@ -120,7 +108,7 @@ struct Tile {
             a[mt] = join(*reinterpret_cast<const bf16x4 *>(q), *reinterpret_cast<const bf16x4 *>(q + 16));
         }
 #pragma unroll
-        for (int k = 1; k >= 0; --k)
+        for (int k = 2; k >= 0; --k)
 #pragma unroll
             for (int mt = 0; mt < D / 16; ++mt) acc[mt] = mma(a[mt], b[k], acc[mt]);
     }
@@ -142,14 +130,23 @@ struct Tile {
         }
     }
 };
-// eight float32 values as two bf16 terms
-__device__ __forceinline__ void pack(const float (&x)[8], bf16x8 (&b)[2])
+// eight float32 values as three bf16 terms, cut off bit by bit (8 of the 24 each), so that the last one is exact as well
+__device__ __forceinline__ void pack(const float (&x)[8], bf16x8 (&b)[3])
 {
-    unsigned u[4][2];
+    unsigned u[3][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) terms2<2>(x[2 * i], x[2 * i + 1], u[i]);
+    for (int i = 0; i < 4; ++i) {
+        float lo = x[2 * i], hi = x[2 * i + 1];
 #pragma unroll
-    for (int k = 0; k < 2; ++k) b[k] = __builtin_bit_cast(bf16x8, u32x4{u[0][k], u[1][k], u[2][k], u[3][k]});
+        for (int k = 0; k < 3; ++k) {
+            const unsigned a = __builtin_bit_cast(unsigned, lo), c = __builtin_bit_cast(unsigned, hi);
+            u[k][i] = __builtin_amdgcn_perm(c, a, 0x07060302u);           // the two upper halves
+            lo -= __builtin_bit_cast(float, a & 0xffff0000u);
+            hi -= __builtin_bit_cast(float, c & 0xffff0000u);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) b[k] = __builtin_bit_cast(bf16x8, u32x4{u[k][0], u[k][1], u[k][2], u[k][3]});
 }
 
 __device__ __forceinline__ float group_max(float x)     // over the four lanes (g = 0..3) of a point
@@ -369,7 +366,7 @@ nattn_fwd_tile(BandArgs a, const bf16raw *__restrict__ q, const bf16raw *__restr
                 sum = probabilities();
             }
             l[o] += sum;
-            bf16x8 pb[2];
+            bf16x8 pb[3];
             pack(x, pb);
             TL::sum(Vc, col0, pb, acc[o], n, g);
             settle(acc[o]);
@@ -400,7 +397,7 @@ nattn_fwd_tile(BandArgs a, const bf16raw *__restrict__ q, const bf16raw *__restr
 // ---------------------------------------------------------------------------------------------------------------
 // Backward, query side: dq and D_i = dout_i . out_i (written for the key-side launch).
 template <int D, int NO, int MODE>
-__global__ void __launch_bounds__(256, (Occ<D, NO, MODE>::bwd))
+__global__ void __launch_bounds__(256, (Occ<D, NO, MODE>::dq))
 nattn_bwd_dq_tile(BandArgs a, const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const bf16raw *__restrict__ v,
                   const bf16raw *__restrict__ o_, const float *__restrict__ lse, const bf16raw *__restrict__ go, bf16raw *__restrict__ dq,
                   float *__restrict__ Dws)
@@ -492,7 +489,7 @@ nattn_bwd_dq_tile(BandArgs a, const bf16raw *__restrict__ q, const bf16raw *__re
                 const float y = __builtin_amdgcn_exp2f(fmaf(s1[i], c2, bias)) * e1[i];
                 ds[4 + i] = keep[4 + i] ? y : 0.f;
             }
-            bf16x8 db[2];
+            bf16x8 db[3];
             pack(ds, db);
             TL::sum(Kc, col0, db, acc[o], n, g);
             settle(acc[o]);
@@ -617,7 +614,7 @@ nattn_bwd_dkdv_tile(BandArgs a, const bf16raw *__restrict__ q, const bf16raw *__
                 pr[4 + i] = keep[4 + i] ? y : 0.f;
                 ds[4 + i] = pr[4 + i] * e1[i];
             }
-            bf16x8 pb[2];
+            bf16x8 pb[3];
             pack(pr, pb);
             TL::sum(Gc, col0, pb, adv[o], n, g);
             pack(ds, pb);

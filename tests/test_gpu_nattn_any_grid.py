@@ -2,9 +2,13 @@
 tiles, stages, classes and row tables, float32 and bf16 tensors, against the float64 oracle."""
 import math
 
+import numpy as np
 import pytest
+import torch
 
-from paper_2505_11157_amd.workloads import make_inputs
+import oracle as O
+import paper_2505_11157_amd as S
+from paper_2505_11157_amd.workloads import grid_dict, make_inputs, round_to_bf16
 from test_gpu_nattn import C_DERIVED, run_case
 from test_gpu_nattn_bf16 import run_bf16
 
@@ -51,3 +55,21 @@ def test_any_grid_many_slices(batch, heads, d):
     # enough workgroups for several owner tiles per wavefront, on an odd longitude count
     c, arrs = make_inputs(dict(_c(0, 41, 75, 41, 75, 0.3, d=d), batch=batch, heads=heads), seed=4300 + d)
     run_case(c, arrs, [0, batch * heads - 1], C=C_DERIVED, case="any-many[d%d]" % d)
+
+
+@pytest.mark.parametrize("lon,d", [(80, 16), (75, 32), (80, 64), (75, 24)])
+def test_bf16_sums_carry_float32_weights(lon, d):
+    # The weights of the bf16 sums (probabilities) are float32 values.  A relative error u of a sum moves its rounding to 8 bits
+    # with a probability of about u / 2^-8: float32 sums (u of some 2^-24 .. 2^-21) give shares of 1e-4 to 4e-4 of results that
+    # are not the correctly rounded ones, weights of 16 or 17 bits (u of about 2^-17) 2e-3.
+    c, arrs = make_inputs(dict(_c(0, 41, lon, 41, lon, 0.3, heads=4, d=d), dtype="bf16"), seed=4500 + d)
+    arrs, gd, scale = [round_to_bf16(a) for a in arrs], grid_dict(c), 1 / math.sqrt(d)
+    g = S.s2_grid_init(0, 41, lon, 41, lon, 0.3)
+    q, k, v, dout = (torch.from_numpy(a).to("cuda:0")[None].to(torch.bfloat16).contiguous() for a in arrs)
+    out, lse = S.s2_nattn_fwd(g, q, k, v, scale)
+    dv = S.s2_nattn_bwd(g, q, k, v, out, lse, dout, scale)[2]
+    a64 = [a.astype(np.float64) for a in arrs]
+    for name, x, ref in (("out", out, O.nattn_fwd(gd, *a64[:3], scale)[0]), ("dv", dv, O.nattn_bwd(gd, *a64, scale)[2])):
+        share = (x[0].float().cpu().numpy() != round_to_bf16(ref.astype(np.float32))).mean()
+        print("not correctly rounded: %s %.2e" % (name, share))
+        assert share < 8e-4, (name, share)
