@@ -69,6 +69,21 @@ __device__ __forceinline__ float max4(float a, float b, float c, float d)
     return r;
 }
 
+// The reads of a first product's operands up to AHEAD of the matrix instructions that use them (left alone, the compiler waits
+// for every single one: 64 x 128, 8 slices, d = 32 forward 83.2 against 81.7 us).
+template <int READS, int AHEAD = READS < 8 ? READS : 8>
+__device__ __forceinline__ void read_ahead()
+{
+    constexpr int STEP = AHEAD < 4 ? AHEAD : 4;
+    __builtin_amdgcn_sched_group_barrier(0x100, AHEAD, 0);
+#pragma unroll
+    for (int i = AHEAD; i < READS; i += STEP) {
+        __builtin_amdgcn_sched_group_barrier(0x008, STEP, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, STEP, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, AHEAD, 0);
+}
+
 // Matrix results that a branch may lead to a reader of: the compiler pads the wait states of an instruction on one side of
 // a branch only.  Ten wait states here, after the last instruction of the tile.
 template <int N>
@@ -91,7 +106,7 @@ struct Stage {
     {
         if constexpr (WIDE) {
 #pragma unroll
-            for (int j = 0; j < Idx::NP; ++j) r[j] = load_at<f32x4>(row, at.off[j]);
+            for (int j = 0; j < Idx::NP; ++j) r[j] = load_at<f32x4>(row, at.at(j));
         } else {
             size_t step = w.plane_walk;
             asm volatile("" : "+s"(step));   // else the compiler keeps every channel's address in (spilled) scalar registers
@@ -100,7 +115,7 @@ struct Stage {
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
 #pragma unroll
-                for (int i = 0; i < NC; ++i) r[j * NC + i] = load_at<float>(p, at.off[i]);
+                for (int i = 0; i < NC; ++i) r[j * NC + i] = load_at<float>(p, at.at(i));
                 // past the last channel: that channel again (not stored); a branch around a load would make the compiler
                 // wait for all loads in flight where its sides meet
                 const int up = MODE == kRagged ? imin(w.wave + 4 * j + 4, nch - 1) - c : 4;
@@ -196,7 +211,7 @@ nattn_fwd_band(BandArgs a, const float *__restrict__ q, const float *__restrict_
         }
         if (cnt <= 0) continue;
         // one copy of the tile loop for rows on the common grid, one for rows whose tiles follow their owners (backward: one
-        // copy for both)
+        // copy for both; two take the registers of a wavefront: d = 64 dk/dv on 129 x 256, 32 slices, 3.67 against 2.47 ms)
         auto tiles = [&](auto kind) {
             constexpr int KIND = decltype(kind)::value;
 #pragma unroll
@@ -205,21 +220,22 @@ nattn_fwd_band(BandArgs a, const float *__restrict__ q, const float *__restrict_
                 const int Wo = w.Wb + 16 * o;
                 const int T0 = on_grid<KIND>(p) ? Xst : (Wo + lo) & ~3;
                 const int Tend = on_grid<KIND>(p) ? imin(Xst + G::SW, p.Xend) : Wo + 15 + lo + cnt;
-                for (int Xt = T0; Xt < Tend; Xt += 16) {
-                    TilePos<KIND> tp;
-                    tp.set(p, Xt, Wo, lo, cnt, nU);
-                    if (!tp.touch) continue;
+                TileRow<KIND> tr;
+                tr.start(p, T0, Wo, lo, cnt, nU);
+                for (int Xt = T0; Xt < Tend; Xt += 16, tr.next()) {
+                    if (!tr.touch()) continue;
                     const int col0 = Xt - Xst;
                     const float *kp = Kc + g * G::PITCH + col0 + n;
                     f32x4 sc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int kb = 0; kb < D / 4; ++kb) sc = mfma4(kp[kb * 4 * G::PITCH + 4 * (kb & 3)], qreg[o][kb], sc);
+                    read_ahead<D / 4>();
                     float x[4];
 #pragma unroll
                     for (int rr = 0; rr < 4; ++rr) x[rr] = sc[rr] * c2;
-                    if (tp.mask) {
+                    if (tr.mask(Xt)) {
                         bool keep[4];
-                        band_mask(keep, p, tp, Xt, cnt, nU, 4 * g, n);
+                        tr.keep(keep, Xt, 4 * g, n);
 #pragma unroll
                         for (int rr = 0; rr < 4; ++rr) x[rr] = keep[rr] ? x[rr] : -INFINITY;
                     }
@@ -353,7 +369,7 @@ nattn_bwd_dq_band(BandArgs a, const float *__restrict__ q, const float *__restri
         }
         if (cnt <= 0) continue;
         // one copy of the tile loop for rows on the common grid, one for rows whose tiles follow their owners (backward: one
-        // copy for both)
+        // copy for both; two take the registers of a wavefront: d = 64 dk/dv on 129 x 256, 32 slices, 3.67 against 2.47 ms)
         auto tiles = [&](auto kind) {
             constexpr int KIND = decltype(kind)::value;
 #pragma unroll
@@ -363,10 +379,10 @@ nattn_bwd_dq_band(BandArgs a, const float *__restrict__ q, const float *__restri
                 const int T0 = on_grid<KIND>(p) ? Xst : (Wo + lo) & ~3;
                 const int Tend = on_grid<KIND>(p) ? imin(Xst + G::SW, p.Xend) : Wo + 15 + lo + cnt;
                 const float Dw = Dn[o] * omega;
-                for (int Xt = T0; Xt < Tend; Xt += 16) {
-                    TilePos<KIND> tp;
-                    tp.set(p, Xt, Wo, lo, cnt, nU);
-                    if (!tp.touch) continue;
+                TileRow<KIND> tr;
+                tr.start(p, T0, Wo, lo, cnt, nU);
+                for (int Xt = T0; Xt < Tend; Xt += 16, tr.next()) {
+                    if (!tr.touch()) continue;
                     const int col0 = Xt - Xst;
                     const float *kp = Kc + g * G::PITCH + col0 + n, *vp = Vc + g * G::PITCH + col0 + n;
                     f32x4 sc = {0.f, 0.f, 0.f, 0.f}, dp = {Dw, Dw, Dw, Dw};
@@ -375,19 +391,20 @@ nattn_bwd_dq_band(BandArgs a, const float *__restrict__ q, const float *__restri
                         sc = mfma4(kp[kb * 4 * G::PITCH + 4 * (kb & 3)], qreg[o][kb], sc);
                         dp = mfma4(vp[kb * 4 * G::PITCH + 4 * (kb & 3)], greg[o][kb], dp);
                     }
-                    float ds[4];
-#pragma unroll
-                    for (int rr = 0; rr < 4; ++rr) ds[rr] = __builtin_amdgcn_exp2f(fmaf(sc[rr], c2, -L2[o])) * dp[rr];
-                    if (tp.mask) {
-                        bool keep[4];
-                        band_mask(keep, p, tp, Xt, cnt, nU, 4 * g, n);
-#pragma unroll
-                        for (int rr = 0; rr < 4; ++rr) ds[rr] = keep[rr] ? ds[rr] : 0.f;
-                    }
+                    read_ahead<D / 2>();
                     const float *kq = Kc + n * G::PITCH + 4 * ((n >> 2) & 3) + col0 + 4 * g;
                     f32x4 ka[D / 16];
 #pragma unroll
                     for (int mt = 0; mt < D / 16; ++mt) ka[mt] = *reinterpret_cast<const f32x4 *>(kq + mt * 16 * G::PITCH);
+                    float ds[4];
+#pragma unroll
+                    for (int rr = 0; rr < 4; ++rr) ds[rr] = __builtin_amdgcn_exp2f(fmaf(sc[rr], c2, -L2[o])) * dp[rr];
+                    if (tr.mask(Xt)) {
+                        bool keep[4];
+                        tr.keep(keep, Xt, 4 * g, n);
+#pragma unroll
+                        for (int rr = 0; rr < 4; ++rr) ds[rr] = keep[rr] ? ds[rr] : 0.f;
+                    }
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -418,7 +435,7 @@ nattn_bwd_dq_band(BandArgs a, const float *__restrict__ q, const float *__restri
 // Backward, key side: owners are input points, the transposed band gives the output latitudes; q, dout, lse and D
 // of a stage's outputs are staged together.
 template <int D, int NO, int MODE>
-__global__ void __launch_bounds__(256, 2)
+__global__ void __launch_bounds__(256, D == 16 && MODE != kRagged ? 6 : 2)
 nattn_bwd_dkdv_band(BandArgs a, const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
                     const float *__restrict__ lse, const float *__restrict__ go, const float *__restrict__ Dws,
                     float *__restrict__ dk, float *__restrict__ dv)
@@ -453,14 +470,15 @@ nattn_bwd_dkdv_band(BandArgs a, const float *__restrict__ q, const float *__rest
             vreg[o][kb] = own && has<MODE>(c, a.e) ? *(v + slice_v + at) : 0.f;
         }
     }
-    // minus the logsumexp (base 2, relative) and -D of a stage's columns: one pair per thread
+    // minus the logsumexp (base 2, relative) and -D of a stage's columns: one pair per thread, turned into that on the way to LDS
+    // (arithmetic on a value just requested would wait for it and for the whole stage requested before it)
     static_assert(G::SW <= 256, "stage width");
     float rl = 0.f, rd = 0.f;
     auto load_stat = [&](size_t row, int Xs) {
         if (w.tid < G::SW) {
             const size_t at = row + w.c_walk * wrap_stage(Xs, w.tid, G::SW, nU, w.inv_nU);
-            rl = (lref - ls[at]) * kLog2e;
-            rd = -Ds[at];
+            rl = ls[at];
+            rd = Ds[at];
         }
     };
     Walker wk;
@@ -481,8 +499,8 @@ nattn_bwd_dkdv_band(BandArgs a, const float *__restrict__ q, const float *__rest
         rq.store(w, Qc, a.d);
         rg.store(w, Gc, a.e);
         if (w.tid < G::SW) {
-            Ls[w.tid] = rl;
-            Dn[w.tid] = rd;
+            Ls[w.tid] = (lref - rl) * kLog2e;
+            Dn[w.tid] = -rd;
         }
         __syncthreads();
         const RowPlan p = wk.cur;
@@ -499,7 +517,7 @@ nattn_bwd_dkdv_band(BandArgs a, const float *__restrict__ q, const float *__rest
         }
         if (cnt <= 0) continue;
         // one copy of the tile loop for rows on the common grid, one for rows whose tiles follow their owners (backward: one
-        // copy for both)
+        // copy for both; two take the registers of a wavefront: d = 64 dk/dv on 129 x 256, 32 slices, 3.67 against 2.47 ms)
         auto tiles = [&](auto kind) {
             constexpr int KIND = decltype(kind)::value;
 #pragma unroll
@@ -508,10 +526,10 @@ nattn_bwd_dkdv_band(BandArgs a, const float *__restrict__ q, const float *__rest
                 const int Wo = w.Wb + 16 * o;
                 const int T0 = on_grid<KIND>(p) ? Xst : (Wo + lo) & ~3;
                 const int Tend = on_grid<KIND>(p) ? imin(Xst + G::SW, p.Xend) : Wo + 15 + lo + cnt;
-                for (int Xt = T0; Xt < Tend; Xt += 16) {
-                    TilePos<KIND> tp;
-                    tp.set(p, Xt, Wo, lo, cnt, nU);
-                    if (!tp.touch) continue;
+                TileRow<KIND> tr;
+                tr.start(p, T0, Wo, lo, cnt, nU);
+                for (int Xt = T0; Xt < Tend; Xt += 16, tr.next()) {
+                    if (!tr.touch()) continue;
                     const int col0 = Xt - Xst;
                     const float *qp = Qc + g * G::PITCH + col0 + n, *gp = Gc + g * G::PITCH + col0 + n;
                     const f32x4 L = *reinterpret_cast<const f32x4 *>(Ls + col0 + 4 * g);
@@ -521,15 +539,16 @@ nattn_bwd_dkdv_band(BandArgs a, const float *__restrict__ q, const float *__rest
                         sc = mfma4(qp[kb * 4 * G::PITCH + 4 * (kb & 3)], kreg[o][kb], sc);
                         dp = mfma4(gp[kb * 4 * G::PITCH + 4 * (kb & 3)], vreg[o][kb], dp);
                     }
+                    if constexpr (D < 64 || MODE == kWide) read_ahead<D / 2>();       // else no registers left for it
                     float pr[4], ds[4];
 #pragma unroll
                     for (int rr = 0; rr < 4; ++rr) {
                         pr[rr] = __builtin_amdgcn_exp2f(fmaf(sc[rr], c2, L[rr]));
                         ds[rr] = pr[rr] * dp[rr];
                     }
-                    if (tp.mask) {
+                    if (tr.mask(Xt)) {
                         bool keep[4];
-                        band_mask(keep, p, tp, Xt, cnt, nU, 4 * g, n);
+                        tr.keep(keep, Xt, 4 * g, n);
 #pragma unroll
                         for (int rr = 0; rr < 4; ++rr) {
                             pr[rr] = keep[rr] ? pr[rr] : 0.f;
@@ -580,17 +599,16 @@ constexpr size_t fwd_lds() { return size_t(2) * Geo<D, NO>::TILE * sizeof(float)
 template <int D, int NO>
 constexpr size_t dkdv_lds() { return (size_t(2) * Geo<D, NO>::TILE + 2 * Geo<D, NO>::COLS) * sizeof(float); }
 
-template <int D, int NO, int MODE, bool BWD>
+template <int D, int NO, int MODE, bool DKDV>
 int configure_one()
 {
     auto raise = [](const void *f, size_t bytes) {
         return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)) != hipSuccess;
     };
     int rc = 0;
-    if constexpr (BWD)
-        rc = raise(reinterpret_cast<const void *>(nattn_bwd_dq_band<D, NO, MODE>), fwd_lds<D, NO>()) ||
-             raise(reinterpret_cast<const void *>(nattn_bwd_dkdv_band<D, NO, MODE>), dkdv_lds<D, NO>());
-    return rc || raise(reinterpret_cast<const void *>(nattn_fwd_band<D, NO, MODE>), fwd_lds<D, NO>());
+    if constexpr (DKDV) rc = raise(reinterpret_cast<const void *>(nattn_bwd_dkdv_band<D, NO, MODE>), dkdv_lds<D, NO>());
+    return rc || raise(reinterpret_cast<const void *>(nattn_bwd_dq_band<D, NO, MODE>), fwd_lds<D, NO>()) ||
+           raise(reinterpret_cast<const void *>(nattn_fwd_band<D, NO, MODE>), fwd_lds<D, NO>());
 }
 
 template <int D, int NO>
@@ -605,15 +623,16 @@ inline BandArgs band_args(const S2DeviceTables &t, const S2BandSide &b, int nbh,
 inline double pair_count(const double (&p)[4], int nbh) { return nbh * (p[0] + p[1] + p[2] + p[3]); }
 
 // Calls f with the geometry for a head dimension and a launch: owner tiles per wavefront (NO), one or two.  Two share a
-// staged row, one makes twice the workgroups and needs fewer registers.  d = 16: two in the forward from four workgroups per
-// compute unit on (129 x 256, 32 slices: 0.43 against 0.50 ms), one in the backward (0.57 + 0.67 against 0.55 + 0.70; four were
-// slower throughout); d = 32: two from four, d = 64: two from two workgroups per compute unit on (129 x 256: 2.9 against 3.3 and
-// 6.3 against 7.5 ms per step; 64 x 128, 8 slices, d = 32: 0.41 against 0.33).
+// staged row, one makes twice the workgroups and needs fewer registers.  d = 16: two in the forward and dq from four workgroups
+// per compute unit on (129 x 256, 32 slices: 0.43 against 0.50 and 0.53 against 0.56 ms), one in dk/dv (0.66 against 0.70; four
+// were slower throughout); d = 32: two from four, d = 64: two from two workgroups per compute unit on (129 x 256: 2.8 against
+// 3.3 and 5.9 against 7.5 ms per step; 64 x 128, 8 slices, d = 32: 0.41 against 0.31).
 template <int D_, int NO_>
 struct Shape {
     static constexpr int D = D_, NO = NO_;
 };
-template <bool BWD, class F>
+enum Launch { kFwd, kDq, kDkdv };
+template <Launch WHICH, class F>
 void by_shape(const S2BandSide &b, int nbh, int dmax, F &&f)
 {
     static const unsigned ncu = [] {
@@ -625,7 +644,7 @@ void by_shape(const S2BandSide &b, int nbh, int dmax, F &&f)
     }();
     const unsigned two = blocks<16, 2>(b, nbh);
     if (dmax <= 16) {
-        if constexpr (!BWD)
+        if constexpr (WHICH != kDkdv)
             if (two >= 4 * ncu) return f(Shape<16, 2>());
         f(Shape<16, 1>());
     } else if (dmax <= 32) {
@@ -651,7 +670,7 @@ void BandSet<MODE>::fwd(const S2DeviceTables &t, int nbh, int d, int e, float sc
                           float *out, float *lse, hipStream_t st)
 {
     S2TraceScope tr("nattn_fwd_band", pair_count(t.fwd_pairs, nbh), st);
-    by_shape<false>(t.side_out, nbh, d > e ? d : e, [&](auto s) {
+    by_shape<kFwd>(t.side_out, nbh, d > e ? d : e, [&](auto s) {
         constexpr int D = decltype(s)::D, NO = decltype(s)::NO;
         hipLaunchKernelGGL((nattn_fwd_band<D, NO, MODE>), dim3(blocks<D, NO>(t.side_out, nbh)), dim3(256),
                            (fwd_lds<D, NO>()), st, band_args(t, t.side_out, nbh, d, e, scale), q, k, v, out, lse);
@@ -662,7 +681,7 @@ void BandSet<MODE>::dq(const S2DeviceTables &t, int nbh, int d, int e, float sca
                          const float *o, const float *lse, const float *go, float *dq, float *Dws, hipStream_t st)
 {
     S2TraceScope tr("nattn_bwd_dq_band", pair_count(t.fwd_pairs, nbh), st);
-    by_shape<true>(t.side_out, nbh, d > e ? d : e, [&](auto s) {
+    by_shape<kDq>(t.side_out, nbh, d > e ? d : e, [&](auto s) {
         constexpr int D = decltype(s)::D, NO = decltype(s)::NO;
         hipLaunchKernelGGL((nattn_bwd_dq_band<D, NO, MODE>), dim3(blocks<D, NO>(t.side_out, nbh)), dim3(256),
                            (fwd_lds<D, NO>()), st, band_args(t, t.side_out, nbh, d, e, scale), q, k, v, o, lse, go, dq, Dws);
@@ -673,7 +692,7 @@ void BandSet<MODE>::dkdv(const S2DeviceTables &t, int nbh, int d, int e, float s
                            const float *lse, const float *go, const float *Dws, float *dk, float *dv, hipStream_t st)
 {
     S2TraceScope tr("nattn_bwd_dkdv_band", pair_count(t.bwd_pairs, nbh), st);
-    by_shape<true>(t.side_in, nbh, d > e ? d : e, [&](auto s) {
+    by_shape<kDkdv>(t.side_in, nbh, d > e ? d : e, [&](auto s) {
         constexpr int D = decltype(s)::D, NO = decltype(s)::NO;
         hipLaunchKernelGGL((nattn_bwd_dkdv_band<D, NO, MODE>), dim3(blocks<D, NO>(t.side_in, nbh)), dim3(256),
                            (dkdv_lds<D, NO>()), st, band_args(t, t.side_in, nbh, d, e, scale), q, k, v, lse, go, Dws, dk, dv);

@@ -181,7 +181,7 @@ struct Stage {
     {
         if constexpr (WIDE) {
 #pragma unroll
-            for (int j = 0; j < Idx::NP; ++j) r[j] = load_at<uint2>(row, at.off[j]);
+            for (int j = 0; j < Idx::NP; ++j) r[j] = load_at<uint2>(row, at.at(j));
         } else {
             size_t step = w.plane_walk;
             asm volatile("" : "+s"(step));   // else the compiler keeps every channel's address in (spilled) scalar registers
@@ -190,7 +190,7 @@ struct Stage {
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
 #pragma unroll
-                for (int i = 0; i < NC; ++i) r[j * NC + i] = load_at<bf16raw>(p, at.off[i]);
+                for (int i = 0; i < NC; ++i) r[j * NC + i] = load_at<bf16raw>(p, at.at(i));
                 // past the last channel: that channel again (not stored); a branch around a load would make the compiler
                 // wait for all loads in flight where its sides meet
                 const int up = MODE == kRagged ? imin(w.wave + 4 * j + 4, nch - 1) - c : 4;
@@ -221,6 +221,56 @@ struct Stage {
     }
 };
 
+// Position of a tile on the common grid (columns Xt .. Xt + 15) relative to 16 owners at Wo: b = smallest offset in the tile
+// minus the arc's first offset (around the circle where the plan says so), whether the band touches it, whether it needs the
+// mask.  Found anew for every tile: the owner tiles of a step follow each other here, and a position kept for each of them
+// (TileRow) costs more scalar registers than it saves instructions (91 x 180, 16 slices, d = 16: 347 against 328 us per step).
+struct GridTile {
+    int b;
+    bool touch, mask, tail;              // tail: columns past Xend inside the tile
+    __device__ __forceinline__ void set(const RowPlan &p, int Xt, int Wo, int lo, int cnt, int nU)
+    {
+        b = Xt - Wo - lo - 15;
+        tail = false;
+        if (p.circle) {
+            if (nU < 32) {
+                b = (b + 16 * nU) % nU;
+            } else {
+                b = b < 0 ? b + nU : b;
+                b = b < 0 ? b + nU : b;
+                b = b >= nU ? b - nU : b;
+                b = b >= nU ? b - nU : b;
+            }
+            tail = Xt + 16 > p.Xend;
+            touch = b < cnt || b + 30 >= nU;                    // always for a whole circle: b < nU = cnt
+            mask = tail || (cnt < nU && b + 30 >= cnt);
+        } else {
+            touch = b + 30 >= 0 && b < cnt;
+            mask = b < 0 || b + 30 >= cnt;
+        }
+    }
+    // keep[rr]: is column Xt + k0 + rr a neighbor of owner Wo + n
+    template <int N>
+    __device__ __forceinline__ void keep(bool (&keep)[N], const RowPlan &p, int Xt, int cnt, int nU, int k0, int n) const
+    {
+        const int uu = b + k0 - n + 15;
+        if (p.circle && (tail || nU < 32)) {
+            const int nvalid = p.Xend - Xt - k0;
+#pragma unroll
+            for (int rr = 0; rr < N; ++rr) keep[rr] = unsigned((uu + rr) % nU) < unsigned(cnt) && rr < nvalid;
+        } else if (p.circle) {
+#pragma unroll
+            for (int rr = 0; rr < N; ++rr) {
+                const int v = uu + rr;
+                keep[rr] = unsigned(v >= nU ? v - nU : v) < unsigned(cnt);
+            }
+        } else {
+#pragma unroll
+            for (int rr = 0; rr < N; ++rr) keep[rr] = unsigned(uu + rr) < unsigned(cnt);
+        }
+    }
+};
+
 // Walks one staged row: calls f(o, col0, keep) for every step (32 walked columns from staged column col0 on) that touches
 // owner tile o.  keep[0..3], keep[4..7]: are the lane's columns 4 g + 0..3 of the step's two tiles neighbors of the lane's
 // owner.  On rows whose tiles follow their owners every owner tile sees the same masks (Wo + lo is the same mod 4 for all
@@ -245,7 +295,7 @@ __device__ __forceinline__ void walk_row(const BandWhere &w, const RowPlan &p, i
             if (o >= w.no) break;
             if (p.multi) {
                 const int Xt = Xst + x;
-                TilePos<kGridTiles> ta, tb;
+                GridTile ta, tb;
                 ta.set(p, Xt, w.Wb + 16 * o, lo, cnt, nU);
                 tb.set(p, Xt + 16, w.Wb + 16 * o, lo, cnt, nU);
                 const bool second = x + 16 < xend;
@@ -254,8 +304,8 @@ __device__ __forceinline__ void walk_row(const BandWhere &w, const RowPlan &p, i
                 for (int i = 0; i < 8; ++i) keep[i] = true;
                 if (ta.mask || tb.mask || !second) {
                     bool ka[4], kb[4];
-                    band_mask(ka, p, ta, Xt, cnt, nU, 4 * w.g, w.n);
-                    band_mask(kb, p, tb, Xt + 16, cnt, nU, 4 * w.g, w.n);
+                    ta.keep(ka, p, Xt, cnt, nU, 4 * w.g, w.n);
+                    tb.keep(kb, p, Xt + 16, cnt, nU, 4 * w.g, w.n);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         keep[i] = ka[i];
@@ -548,14 +598,15 @@ nattn_bwd_dkdv_tile(BandArgs a, const bf16raw *__restrict__ q, const bf16raw *__
         TL::template own_point<MODE>(kf[o], k + slice_k + at, w.plane_own, a.d, own, g);
         TL::template own_point<MODE>(vf[o], v + slice_v + at, w.plane_own, a.e, own, g);
     }
-    // minus the logsumexp (base 2, relative) and -D of a stage's columns: one pair per thread
+    // minus the logsumexp (base 2, relative) and -D of a stage's columns: one pair per thread, turned into that on the way to LDS
+    // (arithmetic on a value just requested would wait for it and for the whole stage requested before it)
     static_assert(G::SW <= 256, "stage width");
     float rl = 0.f, rd = 0.f;
     auto load_stat = [&](size_t row, int Xs) {
         if (w.tid < G::SW) {
             const size_t at = row + w.c_walk * wrap_stage(Xs, w.tid, G::SW, nU, w.inv_nU);
-            rl = (lref - ls[at]) * kLog2e;
-            rd = -Ds[at];
+            rl = ls[at];
+            rd = Ds[at];
         }
     };
     Walker wk;
@@ -575,8 +626,8 @@ nattn_bwd_dkdv_tile(BandArgs a, const bf16raw *__restrict__ q, const bf16raw *__
         rq.store(w, lds + b * 2 * G::TILE, a.d);
         rg.store(w, lds + b * 2 * G::TILE + G::TILE, a.e);
         if (w.tid < G::SW) {
-            Ls[b * 2 * G::COLS + w.tid] = rl;
-            Ls[b * 2 * G::COLS + G::COLS + w.tid] = rd;
+            Ls[b * 2 * G::COLS + w.tid] = (lref - rl) * kLog2e;
+            Ls[b * 2 * G::COLS + G::COLS + w.tid] = -rd;
         }
     };
     // two stages in LDS: while one is worked on the next is stored and the one after is on its way to the registers; one

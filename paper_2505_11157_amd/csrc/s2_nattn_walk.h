@@ -175,60 +175,81 @@ struct Walker {
     }
 };
 
-// Position of a key tile (columns Xt .. Xt + 15) relative to 16 owners at Wo: b = smallest offset in the tile minus the
-// arc's first offset (around the circle where the plan says so), whether the band touches it, whether it needs the mask.
+// The key tiles (16 columns from Xt on) of one row as 16 owners at Wo see them, one after the other.
 // KIND: rows whose tiles follow their owners (kOwnTiles), rows on the common grid (kGridTiles), or either (kAnyTiles: one
 // copy of the tile loop for both, for kernels that have no registers left for two).
+// v = (offset of the tile's first column to the last owner) - (the arc's first offset) + 30: the tile's 16 x 16 offsets, counted
+// from the arc's first, are v - 30 .. v.  Around the circle v is kept in 0 .. nU - 1 (an offset below zero is then one turn more).
+// v moves from tile to tile instead of being found anew from Xt (16 wavefront-uniform instructions, one after the other): together
+// with the reads ahead of the products (s2_nattn_band_impl.h) 181 x 360, 2 slices, d = 32: 0.56 -> 0.51 ms per step.
 enum { kOwnTiles, kGridTiles, kAnyTiles };
 template <int KIND>
 __device__ __forceinline__ bool on_grid(const RowPlan &p) { return KIND == kAnyTiles ? p.multi : KIND == kGridTiles; }
 template <int KIND>
-struct TilePos {
-    int b;
-    bool touch, mask, tail;              // tail: columns past Xend inside the tile
-    __device__ __forceinline__ void set(const RowPlan &p, int Xt, int Wo, int lo, int cnt, int nU)
+struct TileRow {
+    int v, cnt, nU;
+    int step, lim, turn;                 // to the next tile; v wraps at lim; what an offset below zero lacks to its place on the circle
+    int low, top;                        // a tile with v in low .. top - 1 lies inside the band
+    int tail;                            // a tile from past this column on has columns past the row
+    __device__ __forceinline__ void start(const RowPlan &p, int Xt, int Wo, int lo, int count, int n)
     {
-        b = Xt - Wo - lo - 15;
-        tail = false;
-        if (KIND != kOwnTiles && p.circle) {
+        v = Xt - Wo - lo + 15;
+        cnt = count;
+        nU = n;
+        step = 16;
+        low = 30;
+        top = cnt;
+        if (KIND == kOwnTiles) return;
+        lim = tail = 0x7fffffff;
+        turn = 0;
+        if (p.circle) {
             if (nU < 32) {
-                b = (b + 16 * nU) % nU;
+                v = (v + 16 * nU) % nU;
+                step = 16 % nU;
             } else {
-                b = b < 0 ? b + nU : b;
-                b = b < 0 ? b + nU : b;
-                b = b >= nU ? b - nU : b;
-                b = b >= nU ? b - nU : b;
+                v = v < 0 ? v + nU : v;
+                v = v < 0 ? v + nU : v;
+                v = v >= nU ? v - nU : v;
+                v = v >= nU ? v - nU : v;
             }
-            tail = Xt + 16 > p.Xend;
-            touch = b < cnt || b + 30 >= nU;                    // always for a whole circle: b < nU = cnt
-            mask = tail || (cnt < nU && b + 30 >= cnt);
+            lim = turn = nU;
+            tail = p.Xend - 16;
+            low = cnt >= nU ? 0 : low;
+            top = cnt >= nU ? 0x7fffffff : top;
+        }
+    }
+    __device__ __forceinline__ void next()
+    {
+        v += step;
+        if (KIND != kOwnTiles) v = v >= lim ? v - nU : v;
+    }
+    // does the band touch the tile (rows of own tiles start and end with the band)
+    __device__ __forceinline__ bool touch() const { return KIND == kOwnTiles || unsigned(v) < unsigned(cnt + 30); }
+    // does a part of the tile lie outside the band
+    __device__ __forceinline__ bool mask(int Xt) const
+    {
+        return v < low || v >= top || (KIND != kOwnTiles && Xt > tail);
+    }
+    // keep[rr]: is column Xt + k0 + rr a neighbor of owner Wo + n
+    template <int N>
+    __device__ __forceinline__ void keep(bool (&keep)[N], int Xt, int k0, int n) const
+    {
+        const int x = v - 15 + k0 - n;
+        if (KIND != kOwnTiles && (Xt > tail || (turn > 0 && nU < 32))) {
+            int rest = tail + 16 - Xt;
+            asm volatile("" : "+s"(rest));   // found here, not kept in step with Xt in a register of its own
+            const int nvalid = rest - k0;
+#pragma unroll
+            for (int rr = 0; rr < N; ++rr) keep[rr] = unsigned((x + rr + 32 * nU) % nU) < unsigned(cnt) && rr < nvalid;
         } else {
-            touch = KIND == kOwnTiles || (b + 30 >= 0 && b < cnt);       // a row of its own tiles starts and ends with the band
-            mask = b < 0 || b + 30 >= cnt;
+#pragma unroll
+            for (int rr = 0; rr < N; ++rr) {
+                const int y = x + rr;
+                keep[rr] = unsigned(KIND != kOwnTiles && y < 0 ? y + turn : y) < unsigned(cnt);
+            }
         }
     }
 };
-// keep[rr]: is column Xt + k0 + rr a neighbor of owner Wo + n.
-template <int N, int KIND>
-__device__ __forceinline__ void band_mask(bool (&keep)[N], const RowPlan &p, const TilePos<KIND> &tp, int Xt, int cnt, int nU,
-                                          int k0, int n)
-{
-    const int uu = tp.b + k0 - n + 15;
-    if (KIND != kOwnTiles && p.circle && (tp.tail || nU < 32)) {
-        const int nvalid = p.Xend - Xt - k0;
-#pragma unroll
-        for (int rr = 0; rr < N; ++rr) keep[rr] = unsigned((uu + rr) % nU) < unsigned(cnt) && rr < nvalid;
-    } else if (KIND != kOwnTiles && p.circle) {
-#pragma unroll
-        for (int rr = 0; rr < N; ++rr) {
-            const int v = uu + rr;
-            keep[rr] = unsigned(v >= nU ? v - nU : v) < unsigned(cnt);
-        }
-    } else {
-#pragma unroll
-        for (int rr = 0; rr < N; ++rr) keep[rr] = unsigned(uu + rr) < unsigned(cnt);
-    }
-}
 
 // ---- kernel arguments and the place of a workgroup ----
 struct BandArgs {
@@ -291,11 +312,16 @@ struct StageIdx {
     static constexpr bool WIDE = MODE == kWide;
     static constexpr int P4 = SW / 4, NP = (D * P4 + 255) / 256, NC = (SW + 63) / 64, N = WIDE ? NP : NC;
     static constexpr bool EVEN = D * P4 % 256 == 0;
-    unsigned base[N], turn[N], off[N];       // channel, column reduced to one turn, sum of both for the current stage
+    // pieces of a thread repeat their columns every PER (the channel moves on by 256 PER / P4): only PER of them are kept
+    static constexpr int gcd(int a, int b) { return b ? gcd(b, a % b) : a; }
+    static constexpr int ROUND = P4 / gcd(P4, 256), PER = WIDE && EVEN && ROUND < N ? ROUND : N;
+    unsigned base[PER], turn[PER], off[PER];         // channel, column reduced to one turn, sum of both for the current stage
+    unsigned up;                                     // from a piece to the one PER pieces later
     __device__ __forceinline__ void init(const BandWhere &w)
     {
+        up = WIDE ? unsigned(256 * PER / P4) * unsigned(w.plane_walk) * unsigned(sizeof(T)) : 0u;
 #pragma unroll
-        for (int j = 0; j < N; ++j) {
+        for (int j = 0; j < PER; ++j) {
             int col;
             if constexpr (WIDE) {
                 const int i = w.tid + 256 * j, c = imin(i / P4, D - 1);
@@ -313,11 +339,12 @@ struct StageIdx {
         int Xr = Xs >= 2 * w.nU ? Xs - 2 * w.nU : Xs;
         Xr = Xr >= w.nU ? Xr - w.nU : Xr;
 #pragma unroll
-        for (int j = 0; j < N; ++j) {
+        for (int j = 0; j < PER; ++j) {
             const unsigned x = unsigned(Xr) + turn[j], y = x - unsigned(w.nU);       // y wraps to a large value if x < nU
             off[j] = base[j] + (x < y ? x : y) * unsigned(WIDE ? sizeof(T) : sizeof(T) * w.c_walk);
         }
     }
+    __device__ __forceinline__ unsigned at(int j) const { return off[j % PER] + unsigned(j / PER) * up; }
 };
 template <class V>
 __device__ __forceinline__ V load_at(const void *row, unsigned off)
