@@ -10,11 +10,12 @@
 // channel matrix on the fp32 matrix cores.  Backward: psi is applied to dy through the transposed
 // neighborhood (the same kernel on the transposed tables, no atomics) and the channel mixing follows,
 //     dx[b, c] = sum_{o, k} weight[o, c, k] (psi_k^T dy)[b, o];
-// where the channel counts do not allow that, channels are mixed first and dx is gathered from the K planes of dz.  dweight
-// is the split-K weight-gradient product summed in a fixed order.
+// or, where that is cheaper (transposed_first), the channels are mixed first and psi^T gathers dx from the K planes of dz
+// (disco_gather_planes).  dweight is the split-K weight-gradient product summed in a fixed order.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <initializer_list>
 #include <new>
 #include <utility>
 
@@ -42,6 +43,21 @@ struct GatherTables {
     int lds_bytes = 0, W = 1;         // 0: not available; owners per lane
 };
 
+// The same contraction summed over the K planes (disco_gather_planes): per owner latitude a list of terms, padded to whole
+// batches for the four wavefronts of a workgroup.
+struct PlaneTerm {
+    long at;                          // plane j and walked latitude, as an offset into the K planes of one channel
+    int plus, minus;                  // walked columns of owner 0, in 0 .. columns - 1
+    float w;                          // psi_j (halved where both columns are the same one)
+    int pad;
+};
+struct PlaneTables {
+    void *blob = nullptr;
+    const int *first = nullptr;       // [owner latitudes + 1]
+    const PlaneTerm *term = nullptr;
+    const int *order = nullptr;       // owner latitudes, heaviest first
+};
+
 }  // namespace
 
 struct s2_disco {
@@ -50,6 +66,8 @@ struct s2_disco {
     float *dev_psi = nullptr;     // [entry][KP], KP = K rounded up to a multiple of 4; entry = poff[h * band_max + b] + offset
     int *dev_poff = nullptr;      // [nlat_out * band_max]
     GatherTables fwd, bwd;        // owners = outputs; owners = inputs
+    PlaneTables planes;           // owners = inputs
+    int compute_units = 256;
 };
 
 namespace {
@@ -92,65 +110,6 @@ disco_z_fwd(S2DeviceTables t, const float *__restrict__ psi, const int *__restri
 #pragma unroll
     for (int k = 0; k < KP; ++k)
         if (k < K) z[(size_t(bc) * K + k) * so + size_t(h) * t.nlon_out + w] = acc[k];
-}
-
-// dz[bc][k][n] -> dzt[bc][n][KP] (zeros behind the K-th value): the gather of disco_dx then reads the K values of an
-// output point as KP/4 16-byte loads instead of K loads from K planes
-template <int KP>
-__global__ void __launch_bounds__(256)
-disco_dz_transpose(int K, size_t so, const float *__restrict__ dz, float *__restrict__ dzt)
-{
-    const size_t n = size_t(blockIdx.x) * 256 + threadIdx.x;
-    const int bc = blockIdx.y;
-    if (n >= so) return;
-    float v[KP];
-#pragma unroll
-    for (int k = 0; k < KP; ++k) v[k] = k < K ? dz[(size_t(bc) * K + k) * so + n] : 0.f;
-    float4 *o = reinterpret_cast<float4 *>(dzt + (size_t(bc) * so + n) * KP);
-#pragma unroll
-    for (int q = 0; q < KP / 4; ++q) o[q] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-}
-
-// dx[bc][h'][w_in] = sum over the output points (h, w) whose disk holds the input point, and over k, of
-// psi_k[h, h', w_in - w pscale] dz[bc][k][h][w]: one lane per input point; dzt is dz with the basis index innermost
-template <int KP, bool PS1>      // PS1: equal longitude counts (no division in the walk over the arc)
-__global__ void __launch_bounds__(64)
-disco_dx(S2DeviceTables t, const float *__restrict__ psi, const int *__restrict__ poff,
-         const float *__restrict__ dzt, float *__restrict__ dx)
-{
-    const int win = blockIdx.x * 64 + threadIdx.x, hp = blockIdx.y, bc = blockIdx.z;
-    if (win >= t.nlon_in) return;
-    const size_t si = size_t(t.nlat_in) * t.nlon_in, so = size_t(t.nlat_out) * t.nlon_out;
-    float acc = 0.f;
-    const int ps = PS1 ? 1 : t.pscale;
-    const int nb = t.omega_rel[hp] > 0.f ? t.tband_n[hp] : 0;       // a latitude of weight zero receives nothing
-    const int h0 = t.tband_lo[hp];
-    for (int b = 0; b < nb; ++b) {
-        const int h = h0 + b;
-        const int bf = hp - t.band_lo[h];                            // row of h' in the band of h
-        const int c = t.cnt[h * t.band_max + bf];
-        const int lo = c == t.nlon_in ? 0 : -((c - 1) >> 1);
-        const float *pr = psi + size_t(poff[h * t.band_max + bf]) * KP;
-        const float *dr = dzt + (size_t(bc) * so + size_t(h) * t.nlon_out) * KP;
-        // offset tt of the arc of output w is input column w ps + lo + tt: w ps = win - lo - tt (mod nlon_in)
-        int xw = wrapn(win - lo, t.nlon_in);
-        for (int tt = 0; tt < c; ++tt) {
-            if (PS1 || xw % ps == 0) {
-                const int w = PS1 ? xw : xw / ps;
-                const float4 *dp = reinterpret_cast<const float4 *>(dr + size_t(w) * KP);
-#pragma unroll
-                for (int q = 0; q < KP / 4; ++q) {
-                    const float4 v = dp[q];
-                    acc = fmaf(pr[tt * KP + 4 * q + 0], v.x, acc);
-                    acc = fmaf(pr[tt * KP + 4 * q + 1], v.y, acc);
-                    acc = fmaf(pr[tt * KP + 4 * q + 2], v.z, acc);
-                    acc = fmaf(pr[tt * KP + 4 * q + 3], v.w, acc);
-                }
-            }
-            xw = xw == 0 ? t.nlon_in - 1 : xw - 1;
-        }
-    }
-    dx[size_t(bc) * si + size_t(hp) * t.nlon_in + win] = acc;
 }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -254,6 +213,57 @@ disco_gather(GatherTables t, int P, int C, int nlon_own, int nlon_walk, int nlat
     }
 }
 
+// dx[ch][lat][u] = sum over the terms of owner latitude lat of w (dz[plane j][plus + u] + dz[plane j][minus + u]): each hat
+// reads a plane of its own here, so a neighbor costs up to four loads per channel where disco_gather has two LDS reads, and
+// nothing is worth staging (a staged row would serve some two terms per plane).  Loads are coalesced over the owners and hit
+// the caches; a workgroup's four wavefronts share 64 owners and four channels and take a quarter of the terms each (a polar
+// owner has a thousand), four terms in flight at a time.
+template <int CH>
+__global__ void __launch_bounds__(256)
+disco_gather_planes(PlaneTables t, int C, size_t planes, int nlon_own, int nlon_walk, size_t plane_own, int nch, const float *__restrict__ dz,
+                    float *__restrict__ dx)
+{
+    constexpr int B = 4;
+    __shared__ float part[3][CH][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ntile = (nlon_own + 63) / 64, ngrp = (nch + CH - 1) / CH;
+    int id = blockIdx.x;
+    const int u = (id % ntile) * 64 + lane; id /= ntile;
+    const int ch = id % ngrp * CH, lat = t.order[id / ngrp];
+    const int uc = u < nlon_own ? u : nlon_own - 1;
+    const float *x[CH];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) x[c] = dz + size_t(min(ch + c, nch - 1)) * planes;
+    float acc[CH] = {};
+    const int first = t.first[lat], quarter = (t.first[lat + 1] - first) / 4;         // a multiple of B
+    for (int e = first + wave * quarter, end = e + quarter; e < end; e += B) {
+        float v[B][CH];
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const PlaneTerm m = t.term[e + b];
+            int p = uc + m.plus, q = uc + m.minus;
+            p = p >= nlon_walk ? p - nlon_walk : p;
+            q = q >= nlon_walk ? q - nlon_walk : q;
+#pragma unroll
+            for (int c = 0; c < CH; ++c) v[b][c] = x[c][m.at + p] + x[c][m.at + q];
+        }
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+#pragma unroll
+            for (int c = 0; c < CH; ++c) acc[c] = fmaf(t.term[e + b].w, v[b][c], acc[c]);
+    }
+    if (wave > 0)
+#pragma unroll
+        for (int c = 0; c < CH; ++c) part[wave - 1][c][lane] = acc[c];
+    __syncthreads();
+    if (wave > 0 || u >= nlon_own) return;
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+        if (ch + c < nch)
+            dx[size_t(ch + c) * plane_own + size_t(lat / C) * nlon_own * C + lat % C + size_t(C) * u] =
+                acc[c] + part[0][c][lane] + part[1][c][lane] + part[2][c][lane];
+}
+
 // weight[o][c][k] -> wt[c][o][k], the channel matrix that follows the transposed contraction
 __global__ void __launch_bounds__(256)
 disco_weight_transpose(int cout, int cin, int K, const float *__restrict__ w, float *__restrict__ wt)
@@ -310,6 +320,46 @@ void launch_gather(const GatherTables &t, int K, int P, int C, int nlon_own, int
     });
 }
 
+// arrays one behind the other in device memory: array i at off[i]
+int upload(void *&blob, size_t *off, std::initializer_list<std::pair<const void *, size_t>> arrays)
+{
+    size_t n = 0;
+    int i = 0;
+    for (auto &a : arrays) {
+        off[i++] = n;
+        n += (a.second + 255) / 256 * 256;
+    }
+    std::vector<char> host(n, 0);
+    i = 0;
+    for (auto &a : arrays) {
+        if (a.second) std::memcpy(host.data() + off[i], a.first, a.second);
+        ++i;
+    }
+    if (hipMalloc(&blob, std::max<size_t>(n, 1)) != hipSuccess) return S2_ERR_ALLOC;
+    return hipMemcpy(blob, host.data(), n, hipMemcpyHostToDevice) == hipSuccess ? 0 : S2_ERR_ALLOC;
+}
+
+// psi of one row as pairs of input offsets +d and -d for the owner class sc of C (input offset d leads to walked column
+// (sc - d) / C of owner 0, where C divides sc - d): f(first column, second column, psi of +-d, factor), only for offsets with a
+// hat that is not zero.  A column of its own (d = 0, half a turn on an even circle, one of the two not on the walked grid) is
+// both columns, and the factor is one half.
+template <class F>
+void for_offsets(const float *psi, int cnt, int nlon_in, int K, int KP, int C, int sc, F &&f)
+{
+    const bool full = cnt == nlon_in;
+    const int hw = full ? nlon_in / 2 : (cnt - 1) / 2;
+    for (int d = 0; d <= hw; ++d) {
+        const float *p = psi + size_t(d) * KP;
+        int j = 0;
+        while (j < K && p[j] == 0.f) ++j;
+        if (j == K) continue;
+        const bool once = d == 0 || (full && 2 * d == nlon_in), one = (sc - d) % C == 0, two = !once && (sc + d) % C == 0;
+        if (!one && !two) continue;
+        const int first = one ? (sc - d) / C : (sc + d) / C, second = two ? (sc + d) / C : first;
+        f(first, second, j, p, one && two ? 1.f : 0.5f);
+    }
+}
+
 // A wavefront's share of LDS: twelve of them on a compute unit; one row may take more (up to what needs no raised limit).
 constexpr int kGatherLds = 13 * 1024, kGatherLdsMost = 64 * 1024;
 
@@ -354,19 +404,10 @@ int build_gather(GatherTables &t, int K, int KP, int P, int C, int nlat_own, int
             if (base > 0 && (base + ncols) * 16 > kGatherLds) flush();
             const int sub = ncols / P;
             rows.push_back({wl, left, ncols, base});
-            for (int d = 0; d <= hw; ++d) {
-                const float *p = psi + size_t(d) * KP;
-                int j = 0;
-                while (j < K && p[j] == 0.f) ++j;
-                if (j == K) continue;
-                // d = 0, and half a turn on an even circle: +d and -d are the same column
-                const bool once = d == 0 || (full && 2 * d == nlon_in), one = (sc - d) % C == 0, two = !once && (sc + d) % C == 0;
-                if (!one && !two) continue;
-                const int first = one ? (sc - d) / C : (sc + d) / C, second = two ? (sc + d) / C : first;
-                const float f = one && two ? 1.f : 0.5f;        // a column of its own is added to itself
-                auto at = [&](int off) { return 16 * (base + ((left + off) % P) * sub + (left + off) / P); };
+            auto at = [&](int off) { return 16 * (base + ((left + off) % P) * sub + (left + off) / P); };
+            for_offsets(psi, cnt, nlon_in, K, KP, C, sc, [&](int first, int second, int j, const float *p, float f) {
                 by_interval[j].push_back({at(first), at(second), f * p[j], j + 1 < K ? f * p[j + 1] : 0.f});
-            }
+            });
             base += ncols;
         });
         flush();
@@ -377,15 +418,9 @@ int build_gather(GatherTables &t, int K, int KP, int P, int C, int nlat_own, int
     entries.push_back({0, 0, 0.f, 0.f});
     std::stable_sort(cost.begin(), cost.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
     for (auto &c : cost) order.push_back(c.second);
-    const size_t bytes[5] = {chunk_of.size() * 4, chunk.size() * 4, rows.size() * sizeof(GatherRow),
-                             entries.size() * sizeof(GatherEntry), order.size() * 4};
-    size_t off[6] = {0};
-    for (int i = 0; i < 5; ++i) off[i + 1] = off[i] + (bytes[i] + 255) / 256 * 256;
-    std::vector<char> host(off[5], 0);
-    const void *src[5] = {chunk_of.data(), chunk.data(), rows.data(), entries.data(), order.data()};
-    for (int i = 0; i < 5; ++i) std::memcpy(host.data() + off[i], src[i], bytes[i]);
-    if (hipMalloc(&t.blob, off[5]) != hipSuccess ||
-        hipMemcpy(t.blob, host.data(), off[5], hipMemcpyHostToDevice) != hipSuccess)
+    size_t off[6];
+    if (upload(t.blob, off, {{chunk_of.data(), chunk_of.size() * 4}, {chunk.data(), chunk.size() * 4}, {rows.data(), rows.size() * sizeof(GatherRow)},
+                             {entries.data(), entries.size() * sizeof(GatherEntry)}, {order.data(), order.size() * 4}}))
         return S2_ERR_ALLOC;
     char *b = static_cast<char *>(t.blob);
     t.chunk_of = reinterpret_cast<const int *>(b);
@@ -397,10 +432,59 @@ int build_gather(GatherTables &t, int K, int KP, int P, int C, int nlat_own, int
     return 0;
 }
 
-// Does the backward pass apply psi^T before the channel mixing?  The channel matrices take multiples of 16.
-bool transposed_first(const s2_disco_t *dc, int cin)
+// Tables of disco_gather_planes; `walked` as for build_gather.
+template <class Walk>
+int build_planes(PlaneTables &t, int K, int KP, int C, int nlat_own, int nlat_walk, int nlon_walk, Walk &&walked)
 {
-    return dc->bwd.lds_bytes > 0 && cin % 16 == 0 && dc->g->nlat_in * dc->g->nlon_in % 16 == 0;
+    constexpr int BATCH = 16;                         // four wavefronts, four terms each
+    std::vector<int> first(1, 0), order;
+    std::vector<PlaneTerm> terms;
+    std::vector<std::pair<long, int>> cost;
+    for (int lat = 0; lat < nlat_own; ++lat) {
+        walked(lat, [&](int wl, const float *psi, int cnt) {
+            for_offsets(psi, cnt, nlon_walk * C, K, KP, C, lat % C, [&](int one, int two, int j, const float *p, float f) {
+                auto col = [&](int x) { return (x % nlon_walk + nlon_walk) % nlon_walk; };
+                for (int k = j; k <= j + 1 && k < K; ++k)
+                    if (p[k] != 0.f) terms.push_back({(long(k) * nlat_walk + wl) * nlon_walk, col(one), col(two), f * p[k], 0});
+            });
+        });
+        const int n = int(terms.size()) - first.back();
+        if (n > 0)                                    // whole batches: the last term again, without weight
+            for (int i = n; i % BATCH; ++i) {
+                terms.push_back(terms.back());
+                terms.back().w = 0.f;
+            }
+        first.push_back(int(terms.size()));
+        cost.push_back({-long(n), lat});
+    }
+    std::stable_sort(cost.begin(), cost.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
+    for (auto &c : cost) order.push_back(c.second);
+    size_t off[3];
+    if (upload(t.blob, off, {{first.data(), first.size() * 4}, {terms.data(), terms.size() * sizeof(PlaneTerm)}, {order.data(), order.size() * 4}}))
+        return S2_ERR_ALLOC;
+    char *b = static_cast<char *>(t.blob);
+    t.first = reinterpret_cast<const int *>(b);
+    t.term = reinterpret_cast<const PlaneTerm *>(b + off[1]);
+    t.order = reinterpret_cast<const int *>(b + off[2]);
+    return 0;
+}
+
+// Does the backward pass apply psi^T before the channel mixing?  Before it, disco_gather takes cout channels and the mixing runs
+// over cout K planes on the input points; after it, disco_gather_planes takes cin channels, which cost it about three times as
+// much each on equal grids and less than disco_gather's on 2:1 grids (two classes of owners stage every row), and the mixing
+// runs over cin K planes on the output points.  Hence after it from cout = 3 cin on, on 2:1 grids from cout = cin on, and there
+// also where disco_gather would not fill the device (twelve wavefronts per compute unit) and takes as long as its longest one.
+// Steps with psi^T first / after, us, batch 4: 129 x 256, 16 -> 96 channels, K = 9 625 / 408; 32 -> 96, K = 9 701 / 623;
+// 32 -> 64, K = 4 369 / 389; 48 -> 96, K = 9 816 / 908; 64 -> 64, K = 9 691 / 1041; 257 x 512 -> 129 x 256, 16 -> 96, K = 9
+// 2154 / 540; 64 -> 64, K = 9 1726 / 1257, K = 4 885 / 928; 64 -> 32, K = 4 576 / 878; 64 x 128, 16 -> 16, K = 9 131 / 117,
+// 64 -> 64, K = 9 197 / 240.  The channel matrices take multiples of 16.
+bool transposed_first(const s2_disco_t *dc, int batch, int cin, int cout)
+{
+    const s2_grid_t *g = dc->g;
+    if (dc->bwd.lds_bytes == 0 || cin % 16 != 0 || g->nlat_in * g->nlon_in % 16 != 0 || cout >= 3 * cin) return false;
+    const int tile = 64 * dc->bwd.W;
+    const long waves = long((g->nlon_out + tile - 1) / tile) * ((long(batch) * cout + 3) / 4) * g->nlat_in * g->pscale;
+    return cout < cin || (g->pscale == 1 && waves >= 12l * dc->compute_units);
 }
 
 }  // namespace
@@ -434,6 +518,8 @@ extern "C" int s2_disco_init(const s2_grid_t *g, int nbasis, s2_disco_t **out)
             }
         }
     if (g->on_device) {
+        int n = 0;
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, g->device) == hipSuccess && n > 0) dc->compute_units = n;
         // psi of the offsets 0, 1, ... of an arc (it is symmetric)
         auto arc = [&](int h, int b) -> const float * {
             const int c = g->cnt[size_t(h) * g->band_max + b], mid = c == g->nlon_in ? 0 : (c - 1) / 2;
@@ -445,16 +531,18 @@ extern "C" int s2_disco_init(const s2_grid_t *g, int nbasis, s2_disco_t **out)
                 if (c > 0) f(g->band_lo[h] + b, arc(h, b), c);
             }
         });
-        if (!rc)
-            rc = build_gather(dc->bwd, nbasis, KP, 1, g->pscale, g->nlat_in * g->pscale, g->nlon_out, g->nlon_out, [&](int v, auto &&f) {
-                const int hp = v / g->pscale;
-                for (int i = 0; i < g->tband_n[hp]; ++i) {
-                    const int h = g->tband_lo[hp] + i, b = hp - g->band_lo[h];
-                    if (b < 0 || b >= g->band_n[h]) continue;            // a latitude of weight zero is in no band
-                    const int c = g->cnt[size_t(h) * g->band_max + b];
-                    if (c > 0) f(h, arc(h, b), c);
-                }
-            });
+        auto transposed = [&](int v, auto &&f) {
+            const int hp = v / g->pscale;
+            for (int i = 0; i < g->tband_n[hp]; ++i) {
+                const int h = g->tband_lo[hp] + i, b = hp - g->band_lo[h];
+                if (b < 0 || b >= g->band_n[h]) continue;            // a latitude of weight zero is in no band
+                const int c = g->cnt[size_t(h) * g->band_max + b];
+                if (c > 0) f(h, arc(h, b), c);
+            }
+        };
+        const int classes = g->nlat_in * g->pscale;
+        if (!rc) rc = build_gather(dc->bwd, nbasis, KP, 1, g->pscale, classes, g->nlon_out, g->nlon_out, transposed);
+        if (!rc) rc = build_planes(dc->planes, nbasis, KP, g->pscale, classes, g->nlat_out, g->nlon_out, transposed);
         if (rc) {
             (void)hipGetLastError();
             s2_disco_destroy(dc);
@@ -484,6 +572,7 @@ extern "C" void s2_disco_destroy(s2_disco_t *dc)
     if (dc->dev_poff) (void)hipFree(dc->dev_poff);
     if (dc->fwd.blob) (void)hipFree(dc->fwd.blob);
     if (dc->bwd.blob) (void)hipFree(dc->bwd.blob);
+    if (dc->planes.blob) (void)hipFree(dc->planes.blob);
     delete dc;
 }
 
@@ -492,11 +581,11 @@ extern "C" size_t s2_disco_workspace_bytes(const s2_disco_t *dc, int batch, int 
     if (!dc || batch < 1 || cin < 1 || cout < 1) return 0;
     const size_t n_out = size_t(dc->g->nlat_out) * dc->g->nlon_out, n_in = size_t(dc->g->nlat_in) * dc->g->nlon_in;
     auto up = [](size_t x) { return (x + 63) / 64 * 64; };
-    // z [batch][cin * K][n_out]; psi^T dy [batch][cout * K][n_in] and the transposed weight, or dz like z and dz with the
-    // basis index innermost [batch * cin][n_out][KP]; partial sums of the weight gradient
+    // z [batch][cin * K][n_out]; psi^T dy [batch][cout * K][n_in] and the transposed weight, or dz like z; partial sums of the
+    // weight gradient
     const size_t zs = up(size_t(batch) * cin * dc->K * n_out);
-    const size_t mid = transposed_first(dc, cin) ? up(size_t(batch) * cout * dc->K * n_in) + up(size_t(cout) * cin * dc->K)
-                                                 : zs + up(size_t(batch) * cin * padded(dc->K) * n_out);
+    const size_t mid = transposed_first(dc, batch, cin, cout) ? up(size_t(batch) * cout * dc->K * n_in) + up(size_t(cout) * cin * dc->K)
+                                                 : zs;
     return (zs + mid + up(s2_channel_grad_floats(cout, cin * dc->K, 1))) * sizeof(float);
 }
 
@@ -546,10 +635,10 @@ extern "C" int s2_disco_bwd(const s2_disco_t *dc, int batch, int cin, int cout, 
     const int n_out = g->nlat_out * g->nlon_out, K = dc->K;
     auto up = [](size_t v) { return (v + 63) / 64 * 64; };
     float *z = static_cast<float *>(workspace), *mid = z + up(size_t(batch) * cin * K * n_out);
-    const bool first = transposed_first(dc, cin);
+    const bool first = transposed_first(dc, batch, cin, cout);
     const size_t mids = first ? up(size_t(batch) * cout * K * g->nlat_in * g->nlon_in) : up(size_t(batch) * cin * K * n_out);
-    float *second = mid + mids;               // transposed weight, or dz with the basis index innermost
-    float *part = second + up(first ? size_t(cout) * cin * K : size_t(batch) * cin * padded(K) * n_out);
+    float *wt = mid + mids;                   // transposed weight (psi^T first)
+    float *part = wt + (first ? up(size_t(cout) * cin * K) : 0);
     {
         S2TraceScope tr("disco_bwd mix", 0.0, st);
         if (dweight || dbias) s2_channel_grad({cout, n_out, cin * K, batch, 1, {dy}, {z}, {dweight}, {dbias}}, part, st);
@@ -561,21 +650,16 @@ extern "C" int s2_disco_bwd(const s2_disco_t *dc, int batch, int cin, int cout, 
             launch_gather(dc->bwd, K, 1, g->pscale, g->nlon_out, g->nlon_out, g->nlat_in * g->pscale, g->nlat_out, batch * cout, dy, mid, st);
         }
         S2TraceScope tr("disco_dx mix", 0.0, st);
-        hipLaunchKernelGGL(disco_weight_transpose, dim3((cout * cin * K + 255) / 256), dim3(256), 0, st, cout, cin, K, weight, second);
-        s2_channel_product(false, {cin, g->nlat_in * g->nlon_in, cout * K, batch, 1, 1, {second}, {mid}, {nullptr}, nullptr, {dx}}, st);
+        hipLaunchKernelGGL(disco_weight_transpose, dim3((cout * cin * K + 255) / 256), dim3(256), 0, st, cout, cin, K, weight, wt);
+        s2_channel_product(false, {cin, g->nlat_in * g->nlon_in, cout * K, batch, 1, 1, {wt}, {mid}, {nullptr}, nullptr, {dx}}, st);
         S2_HIP_CHECK(hipGetLastError());
         return S2_OK;
     }
-    S2TraceScope tr("disco_dx", 0.0, st);
-    const dim3 grid((g->nlon_in + 63) / 64, g->nlat_in, batch * cin);
-    by_basis(K, [&](auto KP) {
-        const dim3 tgrid(unsigned((size_t(n_out) + 255) / 256), batch * cin);
-        hipLaunchKernelGGL((disco_dz_transpose<decltype(KP)::value>), tgrid, dim3(256), 0, st, K, size_t(n_out), mid, second);
-        if (g->pscale == 1)
-            hipLaunchKernelGGL((disco_dx<decltype(KP)::value, true>), grid, dim3(64), 0, st, g->dt, dc->dev_psi, dc->dev_poff, second, dx);
-        else
-            hipLaunchKernelGGL((disco_dx<decltype(KP)::value, false>), grid, dim3(64), 0, st, g->dt, dc->dev_psi, dc->dev_poff, second, dx);
-    });
+    S2TraceScope tr("disco_dx planes", 0.0, st);
+    constexpr int CH = 4;
+    const unsigned blocks = unsigned((g->nlon_out + 63) / 64) * unsigned((batch * cin + CH - 1) / CH) * unsigned(g->nlat_in * g->pscale);
+    hipLaunchKernelGGL(disco_gather_planes<CH>, dim3(blocks), dim3(256), 0, st, dc->planes, g->pscale, size_t(K) * n_out, g->nlon_out,
+                       g->nlon_out, size_t(g->nlat_in) * g->nlon_in, batch * cin, mid, dx);
     S2_HIP_CHECK(hipGetLastError());
     return S2_OK;
 }

@@ -199,14 +199,56 @@ DISCO_CASES = [
     # 9 and 16 basis functions: the counts the paper pairs with 3 x 3 and 4 x 4 planar kernels (App. C)
     (dict(grid_type=0, nlat_in=17, nlon_in=32, nlat_out=17, nlon_out=32, theta=0.5), 1, 16, 9, 16),
     (dict(grid_type=1, nlat_in=16, nlon_in=32, nlat_out=8, nlon_out=16, theta=0.6), 2, 2, 16, 16),
-    # equal longitude counts of at least 64 and batch * channels a multiple of 16: the matrix-core kernels (short arcs
-    # and whole circles, 80 longitudes = a ragged last group, fewer output than input latitudes, the zero-weight pole row)
+    # equal longitude counts from 64 on: short arcs and whole circles, 80 longitudes (a ragged last group), fewer output than
+    # input latitudes, the zero-weight pole row
     (dict(grid_type=0, nlat_in=17, nlon_in=64, nlat_out=17, nlon_out=64, theta=0.5), 2, 8, 4, 16),
     (dict(grid_type=1, nlat_in=16, nlon_in=128, nlat_out=16, nlon_out=128, theta=0.3), 1, 16, 9, 16),
     (dict(grid_type=0, nlat_in=9, nlon_in=80, nlat_out=9, nlon_out=80, theta=1.2), 1, 16, 3, 32),
     (dict(grid_type=0, nlat_in=33, nlon_in=64, nlat_out=17, nlon_out=64, theta=0.4), 1, 32, 16, 16),
     (dict(grid_type=2, nlat_in=32, nlon_in=192, nlat_out=32, nlon_out=192, theta=0.25), 1, 16, 5, 16),
+    # two owners per lane with two walked columns per owner (z) and with two classes of owners (psi^T before the mixing)
+    (dict(grid_type=0, nlat_in=17, nlon_in=256, nlat_out=9, nlon_out=128, theta=0.5), 1, 32, 3, 16),
+    (dict(grid_type=1, nlat_in=12, nlon_in=320, nlat_out=6, nlon_out=160, theta=0.7), 1, 32, 2, 16),
+    # mixing before psi^T: channels that are no multiple of 16 or of four, an odd longitude count with a last owner of its own,
+    # classes 2 and 3, the zero-weight pole row with classes, many more output than input channels
+    (dict(grid_type=0, nlat_in=16, nlon_in=129, nlat_out=16, nlon_out=129, theta=0.5), 1, 4, 4, 16),
+    (dict(grid_type=0, nlat_in=17, nlon_in=96, nlat_out=17, nlon_out=96, theta=0.4), 3, 2, 8, 32),
+    (dict(grid_type=1, nlat_in=16, nlon_in=200, nlat_out=8, nlon_out=100, theta=0.6), 1, 16, 4, 16),
+    (dict(grid_type=0, nlat_in=16, nlon_in=99, nlat_out=16, nlon_out=33, theta=0.5), 1, 1, 16, 16),
+    (dict(grid_type=2, nlat_in=24, nlon_in=64, nlat_out=12, nlon_out=32, theta=0.5), 2, 4, 4, 16),
+    (dict(grid_type=0, nlat_in=17, nlon_in=64, nlat_out=17, nlon_out=64, theta=0.5), 1, 16, 3, 64),
+    # rows too long for the staged contraction
+    (dict(grid_type=1, nlat_in=2, nlon_in=4112, nlat_out=2, nlon_out=4112, theta=1.95), 1, 8, 2, 16),
 ]
+
+
+def _disco_routes(sizes, theta, B, cin, K, cout):
+    g = S.s2_grid_init(0, *sizes, theta)
+    dc = S.s2_disco_init(g, K)
+    dev = torch.device("cuda:0")
+    x, w, dy = (torch.zeros(s, device=dev) for s in ((B, cin) + sizes[:2], (cout, cin, K), (B, cout) + sizes[2:]))
+    S.s2_trace_reset()
+    S.s2_trace_enable(True)
+    try:
+        _, ws = S.s2_disco_fwd(dc, x, w)
+        S.s2_disco_bwd(dc, x, w, dy, ws)
+        return {n for n, _, _ in S.s2_trace_entries()}, S.s2_disco_workspace_bytes(dc, B, cin, cout)
+    finally:
+        S.s2_trace_enable(False)
+        S.s2_trace_reset()
+
+
+def test_disco_backward_order():
+    # which of the two orders the backward takes, and that the workspace follows: z and as much again for dz where the mixing
+    # comes first, whatever the number of output channels
+    equal, half = (65, 128, 65, 128), (65, 128, 33, 64)
+    names, _ = _disco_routes(equal, 0.2, 4, 32, 4, 64)
+    assert "disco_dx mix" in names and "disco_dx planes" not in names
+    for sizes, cin, cout in ((equal, 8, 32), (equal, 16, 96), (half, 32, 32), (half, 16, 96)):
+        names, size = _disco_routes(sizes, 0.2, 4, cin, 4, cout)
+        assert "disco_dx planes" in names and "disco_dx mix" not in names, (sizes, cin, cout)
+        z = 4 * 4 * cin * 4 * sizes[2] * sizes[3]
+        assert size <= 2 * z + (16 << 20), (sizes, cin, cout, size, z)
 
 
 @pytest.mark.parametrize("ci", range(len(DISCO_CASES)))
