@@ -5,8 +5,8 @@
 //     y[b, o, h, w]    = sum_{c, k} weight[o, c, k] z[b, c, k, h, w] + bias[o]
 // psi_k = hat_k(r) * omega[h'] with K piecewise-linear hats of the geodesic distance r (hat_k(r) = max(0,
 // 1 - |r K / theta_cutoff - k|): isotropic filters that vanish on the rim of the disk); the paper leaves the basis
-// open.  The contraction with psi is disco_gather below; grids with rows too long for it take a gather per point (lanes on
-// consecutive longitudes, the basis values of a (latitude, offset) uniform over a wavefront).  The channel mixing is a
+// open.  The contraction with psi is disco_gather below; grids with too many input columns per output column for it take a gather
+// per point (lanes on consecutive longitudes, the basis values of a (latitude, offset) uniform over a wavefront).  The channel mixing is a
 // channel matrix on the fp32 matrix cores.  Backward: psi is applied to dy through the transposed
 // neighborhood (the same kernel on the transposed tables, no atomics) and the channel mixing follows,
 //     dx[b, c] = sum_{o, k} weight[o, c, k] (psi_k^T dy)[b, o];
@@ -24,10 +24,10 @@
 namespace {
 
 // One direction of the contraction with psi as disco_gather walks it: for every owner latitude a list of chunks, a chunk
-// being some rows that fit into a wavefront's share of LDS and the (row, offset) entries on them, sorted by the interval
+// being some rows (or parts of long ones) that fit into a wavefront's share of LDS and the (row, offset) entries on them, sorted by the interval
 // j <= r K / theta < j + 1 in which only the hats j and j + 1 differ from zero.
 struct GatherRow {
-    int lat, left, ncols, base;       // walked latitude, staged columns in front of the first owner's, staged columns, LDS position
+    int lat, left, ncols, base;       // walked latitude, staged columns in front of the first owner's (may be negative), staged columns, LDS position
 };
 struct GatherEntry {
     int plus, minus;                  // LDS byte offsets of the columns +d and -d of owner 0
@@ -157,7 +157,7 @@ disco_gather(GatherTables t, int P, int C, int nlon_own, int nlon_walk, int nlat
             const GatherRow row = t.row[r];
             const size_t at = size_t(row.lat) * nlon_walk;
             const int sub = row.ncols / P;
-            int first = u0 * P - row.left;               // in (-nlon, nlon)
+            int first = u0 * P - row.left;               // in (-nlon, 2 nlon)
             first = first < 0 ? first + nlon_walk : first;
             for (int i0 = 0; i0 < row.ncols; i0 += 192) {
                 float v[3][4];
@@ -360,14 +360,17 @@ void for_offsets(const float *psi, int cnt, int nlon_in, int K, int KP, int C, i
     }
 }
 
-// A wavefront's share of LDS: twelve of them on a compute unit; one row may take more (up to what needs no raised limit).
+// A wavefront's share of LDS: twelve of them on a compute unit.  Longer rows are staged in parts: with a larger share for the
+// polar rows the wavefronts of every latitude would have it (721 x 1440, 32 channels, K = 4: z 1.33 against 0.77 ms), and a launch of
+// their own would run by itself as long as its longest wavefront (361 x 720: z 276 -> 424 us).  From nine walked columns per
+// owner on, even a part with a single offset takes more; it may up to what needs no raised limit.
 constexpr int kGatherLds = 13 * 1024, kGatherLdsMost = 64 * 1024;
 
 // Tables for owners on `nlat_own` latitudes (classes of latitudes); walked(lat, f) calls f(walked latitude, psi of its input
 // offsets 0 .. nlon_in / 2 at [offset * KP + k], offset count of the arc) for every row of owner latitude lat.  P walked columns
 // per owner, or C owner columns per walked one: the owner u of class s is input column C u + s, and input offset d leads to
 // walked column u + (s - d) / C where C divides s - d.
-// 0: built (or the rows are too long: lds_bytes stays 0), else an error code.
+// 0: built (or a row needs too much LDS: lds_bytes stays 0), else an error code.
 template <class Walk>
 int build_gather(GatherTables &t, int K, int KP, int P, int C, int nlat_own, int nlon_own, int nlon_walk, Walk &&walked)
 {
@@ -397,18 +400,65 @@ int build_gather(GatherTables &t, int K, int KP, int P, int C, int nlat_own, int
             base = 0;
         };
         walked(lat, [&](int wl, const float *psi, int cnt) {
-            const int nlon_in = nlon_walk * C, sc = lat % C;
-            const bool full = cnt == nlon_in;
-            const int hw = full ? nlon_in / 2 : (cnt - 1) / 2, reach = C == 1 ? hw : hw / C + 1;
-            const int left = (reach + P - 1) / P * P, ncols = (64 * t.W + 2 * (left / P)) * P;
-            if (base > 0 && (base + ncols) * 16 > kGatherLds) flush();
-            const int sub = ncols / P;
-            rows.push_back({wl, left, ncols, base});
-            auto at = [&](int off) { return 16 * (base + ((left + off) % P) * sub + (left + off) / P); };
-            for_offsets(psi, cnt, nlon_in, K, KP, C, sc, [&](int first, int second, int j, const float *p, float f) {
-                by_interval[j].push_back({at(first), at(second), f * p[j], j + 1 < K ? f * p[j + 1] : 0.f});
+            struct Pair {
+                int first, second, j;
+                float lo, hi;
+            };
+            std::vector<Pair> pairs;
+            for_offsets(psi, cnt, nlon_walk * C, K, KP, C, lat % C, [&](int first, int second, int j, const float *p, float f) {
+                pairs.push_back({first, second, j, f * p[j], j + 1 < K ? f * p[j + 1] : 0.f});
             });
-            base += ncols;
+            // Staged columns for the offsets lo .. hi of 64 W owners, owner by owner those of one remainder mod P together.
+            struct Window {
+                int left, sub;
+                Window(int lo, int hi, int P, int owners)
+                {
+                    left = lo <= 0 ? (-lo + P - 1) / P * P : -(lo / P * P);
+                    sub = owners - 1 + (left + hi) / P + 1;
+                }
+            };
+            const int owners = 64 * t.W, room = kGatherLds / 16;
+            for (size_t i = 0; i < pairs.size();) {
+                // as many pairs as fit: in one window over all their columns, or in one for the first and one for the second ones
+                int lo[2] = {pairs[i].first, pairs[i].second}, hi[2] = {lo[0], lo[1]}, size = 0;
+                bool one = true;
+                size_t end = i;
+                for (size_t k = i; k < pairs.size(); ++k) {
+                    const int l[2] = {std::min(lo[0], pairs[k].first), std::min(lo[1], pairs[k].second)};
+                    const int h[2] = {std::max(hi[0], pairs[k].first), std::max(hi[1], pairs[k].second)};
+                    const int whole = P * Window(std::min(l[0], l[1]), std::max(h[0], h[1]), P, owners).sub;
+                    const int apart = P * (Window(l[0], h[0], P, owners).sub + Window(l[1], h[1], P, owners).sub);
+                    if (k > i && std::min(whole, apart) > room) break;
+                    one = whole <= apart;
+                    size = std::min(whole, apart);
+                    for (int s = 0; s < 2; ++s) {
+                        lo[s] = l[s];
+                        hi[s] = h[s];
+                    }
+                    end = k + 1;
+                }
+                if (base > 0 && base + size > room) flush();
+                if (one) {
+                    lo[0] = lo[1] = std::min(lo[0], lo[1]);
+                    hi[0] = hi[1] = std::max(hi[0], hi[1]);
+                }
+                int at[2][2];                                    // LDS position and left margin of either column's window
+                for (int s = 0; s < (one ? 1 : 2); ++s) {
+                    const Window w(lo[s], hi[s], P, owners);
+                    rows.push_back({wl, w.left, w.sub * P, base});
+                    at[s][0] = base;
+                    at[s][1] = w.left;
+                    base += w.sub * P;
+                }
+                auto place = [&](int s, int off) {
+                    const int w = one ? 0 : s, x = at[w][1] + off, sub = Window(lo[w], hi[w], P, owners).sub;
+                    return 16 * (at[w][0] + x % P * sub + x / P);
+                };
+                for (; i < end; ++i) {
+                    const Pair &p = pairs[i];
+                    by_interval[p.j].push_back({place(0, p.first), place(1, p.second), p.lo, p.hi});
+                }
+            }
         });
         flush();
         chunk_of.push_back(int(chunk.size() / (K + 3)));

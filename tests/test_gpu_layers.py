@@ -217,8 +217,12 @@ DISCO_CASES = [
     (dict(grid_type=0, nlat_in=16, nlon_in=99, nlat_out=16, nlon_out=33, theta=0.5), 1, 1, 16, 16),
     (dict(grid_type=2, nlat_in=24, nlon_in=64, nlat_out=12, nlon_out=32, theta=0.5), 2, 4, 4, 16),
     (dict(grid_type=0, nlat_in=17, nlon_in=64, nlat_out=17, nlon_out=64, theta=0.5), 1, 16, 3, 64),
-    # rows too long for the staged contraction
+    # rows staged in parts: whole circles and arcs, with one and two owners per lane, with two columns per owner, with classes
     (dict(grid_type=1, nlat_in=2, nlon_in=4112, nlat_out=2, nlon_out=4112, theta=1.95), 1, 8, 2, 16),
+    (dict(grid_type=1, nlat_in=3, nlon_in=1152, nlat_out=3, nlon_out=1152, theta=1.2), 1, 32, 2, 16),
+    (dict(grid_type=1, nlat_in=4, nlon_in=2048, nlat_out=2, nlon_out=1024, theta=1.2), 1, 32, 1, 16),
+    # more columns per output column than the staged contraction takes
+    (dict(grid_type=1, nlat_in=8, nlon_in=128, nlat_out=8, nlon_out=2, theta=0.6), 1, 4, 4, 16),
 ]
 
 
