@@ -598,17 +598,15 @@ extern "C" int s2_disco_init(const s2_grid_t *g, int nbasis, s2_disco_t **out)
             s2_disco_destroy(dc);
             return s2_fail(S2_ERR_ALLOC, "set-up of the contraction tables failed");
         }
-        if (hipMalloc(&dc->dev_psi, std::max<size_t>(psi.size(), 1) * sizeof(float)) != hipSuccess ||
-            hipMalloc(&dc->dev_poff, poff.size() * sizeof(int)) != hipSuccess) {
+        // the basis values themselves only for the gather per point
+        if (dc->fwd.lds_bytes == 0 &&
+            (hipMalloc(&dc->dev_psi, std::max<size_t>(psi.size(), 1) * sizeof(float)) != hipSuccess ||
+             hipMalloc(&dc->dev_poff, poff.size() * sizeof(int)) != hipSuccess ||
+             hipMemcpy(dc->dev_psi, psi.data(), psi.size() * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
+             hipMemcpy(dc->dev_poff, poff.data(), poff.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)) {
             (void)hipGetLastError();
             s2_disco_destroy(dc);
-            return s2_fail(S2_ERR_ALLOC, "hipMalloc of the basis tables failed");
-        }
-        if (hipMemcpy(dc->dev_psi, psi.data(), psi.size() * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
-            hipMemcpy(dc->dev_poff, poff.data(), poff.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess) {
-            (void)hipGetLastError();
-            s2_disco_destroy(dc);
-            return s2_fail(S2_ERR_DEVICE, "upload of the basis tables failed");
+            return s2_fail(S2_ERR_ALLOC, "set-up of the basis tables failed");
         }
     }
     *out = dc;
