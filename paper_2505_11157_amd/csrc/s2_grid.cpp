@@ -676,9 +676,7 @@ extern "C" int s2_grid_init(int grid_type, int nlat_in, int nlon_in, int nlat_ou
         }
         return true;
     };
-    const int64_t most = std::max(int64_t(nlat_in) * nlon_in, int64_t(nlat_out) * nlon_out);
-    g->dt.band_rows_ok = rows_ok(g->vo_lo, g->vo_n) && rows_ok(g->vi_lo, g->vi_n) && std::min(nlon_in, nlon_out) < 32768 &&
-                         most * 64 * 4 < (int64_t(1) << 32);
+    g->dt.band_rows_ok = rows_ok(g->vo_lo, g->vo_n) && rows_ok(g->vi_lo, g->vi_n) && std::min(nlon_in, nlon_out) < 32768;
     int rc = upload_tables(g);
     if (rc != S2_OK) { delete g; return rc; }
     *out_grid = g;

@@ -58,7 +58,7 @@ struct S2DeviceTables {
     int bl_lo, bl_hi, tbl_lo, tbl_hi;
     S2BandSide side_out, side_in;       // owners = output points, owners = input points
     // the tile kernels apply: on both sides the walked rows of any four consecutive owner rows 4 s .. 4 s + 3 span at most
-    // 128 rows (a workgroup keeps two rows per lane), nU < 2^15, and a slice of 64 channels is below 2^32 bytes
+    // 128 rows (a workgroup keeps two rows per lane), and nU < 2^15
     int band_rows_ok;
     unsigned *dev_flags;      // one word in device memory: bit 0 = a bounded wait inside a kernel ran out
     const int *st_cum;        // [st_hi - st_lo + 1]   running cost of the light latitudes (for equal-work segments)

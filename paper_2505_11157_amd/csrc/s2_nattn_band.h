@@ -3,7 +3,25 @@
 #pragma once
 #include "s2_internal.h"
 
+// Staging mode: kWide, four columns at a time with 32-bit offsets into a slice; kNarrow, column by column of one channel at a
+// time; kRagged, kNarrow with channel counts that are not the kernel's.
 enum { kWide, kNarrow, kRagged };
+inline int s2_band_mode(const S2BandSide &b, int d, int e, size_t element)
+{
+    if (d != e || (d != 16 && d != 32 && d != 64)) return kRagged;
+    const size_t slice = size_t(d) * b.nlat_walk * b.nU * b.c_walk * element;
+    return b.c_walk == 1 && b.nU % 4 == 0 && slice < size_t(1) << 32 ? kWide : kNarrow;
+}
+// f(set) with the launchers of a staging mode
+template <template <int> class Set, class F>
+void s2_by_band_mode(int mode, F &&f)
+{
+    if (mode == kWide) f(Set<kWide>());
+    else if (mode == kNarrow) f(Set<kNarrow>());
+    else f(Set<kRagged>());
+}
+// compute units of the device, for rules on the size of a launch
+unsigned s2_compute_units();
 
 template <int MODE>
 struct BandSet {

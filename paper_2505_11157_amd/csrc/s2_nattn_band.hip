@@ -2,23 +2,16 @@
 #include "s2_nattn_band.h"
 #include "s2_nattn_kernels.h"
 
-namespace {
-
-int mode_of(const S2BandSide &b, int d, int e)
+unsigned s2_compute_units()
 {
-    if (d != e || (d != 16 && d != 32 && d != 64)) return kRagged;
-    return b.c_walk == 1 && b.nU % 4 == 0 ? kWide : kNarrow;
+    static const unsigned ncu = [] {
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
+            n = 256;
+        return unsigned(n);
+    }();
+    return ncu;
 }
-// f(set) with the launchers of a staging mode
-template <class F>
-void by_mode(int mode, F &&f)
-{
-    if (mode == kWide) f(BandSet<kWide>());
-    else if (mode == kNarrow) f(BandSet<kNarrow>());
-    else f(BandSet<kRagged>());
-}
-
-}  // namespace
 
 // the band-tile kernels of both element types
 int s2_nattn_band_configure()
@@ -35,7 +28,7 @@ int s2_nattn_fwd_band(const S2DeviceTables &t, int nbh, int d, int e, float scal
                       const float *v, float *out, float *lse, hipStream_t st)
 {
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
-    by_mode(mode_of(t.side_out, d, e), [&](auto set) { set.fwd(t, nbh, d, e, scale, q, k, v, out, lse, st); });
+    s2_by_band_mode<BandSet>(s2_band_mode(t.side_out, d, e, sizeof(float)), [&](auto set) { set.fwd(t, nbh, d, e, scale, q, k, v, out, lse, st); });
     return 0;
 }
 
@@ -44,7 +37,7 @@ int s2_nattn_bwd_band(const S2DeviceTables &t, int nbh, int d, int e, float scal
                       float *Dws, hipStream_t st)
 {
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
-    by_mode(mode_of(t.side_out, d, e), [&](auto set) { set.dq(t, nbh, d, e, scale, q, k, v, o, lse, go, dq, Dws, st); });
-    by_mode(mode_of(t.side_in, d, e), [&](auto set) { set.dkdv(t, nbh, d, e, scale, q, k, v, lse, go, Dws, dk, dv, st); });
+    s2_by_band_mode<BandSet>(s2_band_mode(t.side_out, d, e, sizeof(float)), [&](auto set) { set.dq(t, nbh, d, e, scale, q, k, v, o, lse, go, dq, Dws, st); });
+    s2_by_band_mode<BandSet>(s2_band_mode(t.side_in, d, e, sizeof(float)), [&](auto set) { set.dkdv(t, nbh, d, e, scale, q, k, v, lse, go, Dws, dk, dv, st); });
     return 0;
 }

@@ -635,13 +635,7 @@ enum Launch { kFwd, kDq, kDkdv };
 template <Launch WHICH, class F>
 void by_shape(const S2BandSide &b, int nbh, int dmax, F &&f)
 {
-    static const unsigned ncu = [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
-            n = 256;
-        return unsigned(n);
-    }();
+    const unsigned ncu = s2_compute_units();
     const unsigned two = blocks<16, 2>(b, nbh);
     if (dmax <= 16) {
         if constexpr (WHICH != kDkdv)

@@ -2,24 +2,6 @@
 #include "s2_nattn_tile.h"
 #include "s2_nattn_kernels.h"
 
-namespace {
-
-int mode_of(const S2BandSide &b, int d, int e)
-{
-    if (d != e || (d != 16 && d != 32 && d != 64)) return kRagged;
-    return b.c_walk == 1 && b.nU % 4 == 0 ? kWide : kNarrow;
-}
-// f(set) with the launchers of a staging mode
-template <class F>
-void by_mode(int mode, F &&f)
-{
-    if (mode == kWide) f(TileSet<kWide>());
-    else if (mode == kNarrow) f(TileSet<kNarrow>());
-    else f(TileSet<kRagged>());
-}
-
-}  // namespace
-
 int s2_nattn_tile_configure() { return TileSet<kWide>::configure() || TileSet<kNarrow>::configure() || TileSet<kRagged>::configure(); }
 
 bool s2_nattn_tile_supported(const S2DeviceTables &t, int d, int e)
@@ -36,7 +18,7 @@ int s2_nattn_fwd_tile_bf16(const S2DeviceTables &t, int nbh, int d, int e, float
                            const void *v, void *out, float *lse, hipStream_t st)
 {
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
-    by_mode(mode_of(t.side_out, d, e), [&](auto set) { set.fwd(t, nbh, d, e, scale, in(q), in(k), in(v), res(out), lse, st); });
+    s2_by_band_mode<TileSet>(s2_band_mode(t.side_out, d, e, sizeof(bf16raw)), [&](auto set) { set.fwd(t, nbh, d, e, scale, in(q), in(k), in(v), res(out), lse, st); });
     return 0;
 }
 int s2_nattn_bwd_dq_tile_bf16(const S2DeviceTables &t, int nbh, int d, int e, float scale, const void *q, const void *k,
@@ -44,7 +26,7 @@ int s2_nattn_bwd_dq_tile_bf16(const S2DeviceTables &t, int nbh, int d, int e, fl
                               hipStream_t st)
 {
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
-    by_mode(mode_of(t.side_out, d, e), [&](auto set) {
+    s2_by_band_mode<TileSet>(s2_band_mode(t.side_out, d, e, sizeof(bf16raw)), [&](auto set) {
         set.dq(t, nbh, d, e, scale, in(q), in(k), in(v), in(o), lse, in(go), res(dq), Dws, st);
     });
     return 0;
@@ -54,7 +36,7 @@ int s2_nattn_bwd_dkdv_tile_bf16(const S2DeviceTables &t, int nbh, int d, int e, 
                                 hipStream_t st)
 {
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
-    by_mode(mode_of(t.side_in, d, e), [&](auto set) {
+    s2_by_band_mode<TileSet>(s2_band_mode(t.side_in, d, e, sizeof(bf16raw)), [&](auto set) {
         set.dkdv(t, nbh, d, e, scale, in(q), in(k), in(v), lse, in(go), Dws, res(dk), res(dv), st);
     });
     return 0;

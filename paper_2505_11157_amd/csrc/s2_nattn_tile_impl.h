@@ -737,13 +737,7 @@ struct Shape {
 template <bool BWD, class F>
 void by_shape(const S2BandSide &b, int nbh, int dmax, F &&f)
 {
-    static const unsigned ncu = [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
-            n = 256;
-        return unsigned(n);
-    }();
+    const unsigned ncu = s2_compute_units();
     const bool two = blocks<2>(b, nbh) >= 3 * ncu, four = blocks<4>(b, nbh) >= 8 * ncu;
     if (dmax <= 16) {
         if (four) f(Shape<16, 4>());

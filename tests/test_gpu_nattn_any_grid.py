@@ -73,3 +73,33 @@ def test_bf16_sums_carry_float32_weights(lon, d):
         share = (x[0].float().cpu().numpy() != round_to_bf16(ref.astype(np.float32))).mean()
         print("not correctly rounded: %s %.2e" % (name, share))
         assert share < 8e-4, (name, share)
+
+
+@pytest.mark.parametrize("dtype,d", [(torch.float32, 16), (torch.float32, 64), (torch.bfloat16, 64)])
+def test_slices_of_more_than_four_gigabytes_stay_on_the_tiles(dtype, d):
+    # 16.8 million points: 64 float32 channels of a slice are more than 32-bit offsets reach (staged column by column then, 16
+    # channels four columns at a time).  Against the shape-agnostic kernels; both are held to 1e-6 + 1e-5 |ref| elsewhere.
+    nlat, nlon = 2900, 5800
+    g = S.s2_grid_init(0, nlat, nlon, nlat, nlon, 1.5 * math.pi / (nlat - 1))
+    gen = torch.Generator(device="cuda:0").manual_seed(46)
+    q, k, v, dout = (torch.randn((1, 1, d, nlat, nlon), generator=gen, device="cuda:0", dtype=dtype) for _ in range(4))
+    res, scale = [], 1 / math.sqrt(d)
+    for flag in (0, S.S2_DEBUG_NO_BAND):
+        S.s2_debug_control(flag, S.S2_DEBUG_NO_BAND & ~flag)
+        S.s2_trace_reset()
+        S.s2_trace_enable(True)
+        try:
+            out, lse = S.s2_nattn_fwd(g, q, k, v, scale)
+            saved = res[0][:2] if res else (out, lse)   # one forward result for both backward passes
+            res.append((out, lse) + S.s2_nattn_bwd(g, q, k, v, *saved, dout, scale))
+            names = {n for n, _, _ in S.s2_trace_entries()}
+        finally:
+            S.s2_trace_enable(False)
+            S.s2_trace_reset()
+            S.s2_debug_control(0, S.S2_DEBUG_NO_BAND)
+        assert all(("generic" in n) == bool(flag) for n in names), names
+    for name, a, b in zip(("out", "lse", "dq", "dk", "dv"), *res):
+        rel = 2e-2 if a.dtype == torch.bfloat16 else 2e-5
+        for x, y in zip(a.reshape(-1, nlat, nlon), b.reshape(-1, nlat, nlon)):
+            x, y = x.float(), y.float()
+            assert bool(((x - y).abs() <= 2e-6 + rel * (y.abs() + y.square().mean().sqrt())).all()), name
