@@ -34,9 +34,6 @@
 namespace {
 
 using namespace s2walk;
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kMinRef = -1e30f;    // start value of the reference maximum: finite, so that x - m needs no guard (exp2(-inf) = 0)
 
 template <int D, int NO>
 struct Geo {
@@ -51,16 +48,6 @@ struct Geo {
 __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ float group_max(float x)     // over the four lanes (g = 0..3) of a point
-{
-    x = fmaxf(x, __shfl_xor(x, 16));
-    return fmaxf(x, __shfl_xor(x, 32));
-}
-__device__ __forceinline__ float group_sum(float x)
-{
-    x += __shfl_xor(x, 16);
-    return x + __shfl_xor(x, 32);
 }
 __device__ __forceinline__ float max4(float a, float b, float c, float d)
 {
@@ -84,15 +71,6 @@ __device__ __forceinline__ void read_ahead()
     __builtin_amdgcn_sched_group_barrier(0x008, AHEAD, 0);
 }
 
-// Matrix results that a branch may lead to a reader of: the compiler pads the wait states of an instruction on one side of
-// a branch only.  Ten wait states here, after the last instruction of the tile.
-template <int N>
-__device__ __forceinline__ void settle(f32x4 (&a)[N])
-{
-#pragma unroll
-    for (int i = 0; i + 1 < N; ++i) asm volatile("" : "+v"(a[i]));
-    asm volatile("s_nop 9" : "+v"(a[N - 1]));
-}
 
 // One tensor's stage in registers, and its way to LDS.
 template <int D, int NO, int MODE>

@@ -12,8 +12,8 @@
 namespace s2walk {
 
 // owners (bit n) of a 16-owner tile with a sum that is not finite; own: the lane's owner is a point of the grid
-template <int N, class V>
-__device__ __forceinline__ unsigned not_finite(const V (&acc)[N], bool own)
+template <int N>
+__device__ __forceinline__ unsigned not_finite(const f32x4 (&acc)[N], bool own)
 {
     float t = 0.f;
 #pragma unroll
@@ -154,12 +154,12 @@ __device__ __forceinline__ void exact_fwd(const unsigned (&owners)[NO], int wave
     BandWhere w;
     w.set<OW>(p.a, 64 * wave + lane_here());
     const BandArgs &a = p.a;
-    const float c2 = a.scale * 1.4426950408889634f;
+    const float c2 = a.scale * kLog2e;
     const size_t qs = size_t(w.bh) * a.d * w.plane_own + w.own_at, os = size_t(w.bh) * a.e * w.plane_own + w.own_at;
     const T *ks = p.k + size_t(w.bh) * a.d * w.plane_walk, *vs = p.v + size_t(w.bh) * a.e * w.plane_walk;
     exact_owners(owners, w.W0, [&](int u) {
         const size_t at_own = size_t(w.c_own) * u;
-        float m = -1e30f, l = 0.f, acc = 0.f;
+        float m = kMinRef, l = 0.f, acc = 0.f;
         exact_neighbors(a, w, u, [&](int row, size_t at, bool in) {
             const float s = exact_dot(p.q + qs + at_own, w.plane_own, ks + at, w.plane_walk, a.d) * c2;
             const float m_new = fmaxf(m, wave_max(in ? s : -INFINITY, w.lane)), corr = __builtin_amdgcn_exp2f(m - m_new);
@@ -192,13 +192,13 @@ __device__ __forceinline__ void exact_dq(const unsigned (&owners)[NO], int wave)
     BandWhere w;
     w.set<OW>(p.a, 64 * wave + lane_here());
     const BandArgs &a = p.a;
-    const float c2 = a.scale * 1.4426950408889634f;
+    const float c2 = a.scale * kLog2e;
     const size_t qs = size_t(w.bh) * a.d * w.plane_own + w.own_at, os = size_t(w.bh) * a.e * w.plane_own + w.own_at;
     const T *ks = p.k + size_t(w.bh) * a.d * w.plane_walk, *vs = p.v + size_t(w.bh) * a.e * w.plane_walk;
     exact_owners(owners, w.W0, [&](int u) {
         const size_t at_own = size_t(w.c_own) * u, c = os + imin(w.lane, a.e - 1) * w.plane_own + at_own;
         const float D = wave_sum(w.lane < a.e ? exact_load(p.go + c) * exact_load(p.o + c) : 0.f, w.lane);
-        const float L2 = (p.lse[size_t(w.bh) * w.plane_own + w.own_at + at_own] - a.ln_omega_ref) * 1.4426950408889634f;
+        const float L2 = (p.lse[size_t(w.bh) * w.plane_own + w.own_at + at_own] - a.ln_omega_ref) * kLog2e;
         float acc = 0.f;
         exact_neighbors(a, w, u, [&](int row, size_t at, bool in) {
             const float s = exact_dot(p.q + qs + at_own, w.plane_own, ks + at, w.plane_walk, a.d);
@@ -227,7 +227,7 @@ __device__ __forceinline__ void exact_dkdv(const unsigned (&owners)[NO], int wav
     BandWhere w;
     w.set<OW>(p.a, 64 * wave + lane_here());
     const BandArgs &a = p.a;
-    const float c2 = a.scale * 1.4426950408889634f, omega = a.omega_rel[w.own / w.c_own];
+    const float c2 = a.scale * kLog2e, omega = a.omega_rel[w.own / w.c_own];
     const size_t kv = size_t(w.bh) * w.plane_own, stat = size_t(w.bh) * w.plane_walk;
     const T *qs = p.q + a.d * stat, *gs = p.go + a.e * stat;
     exact_owners(owners, w.W0, [&](int u) {
@@ -236,7 +236,7 @@ __device__ __forceinline__ void exact_dkdv(const unsigned (&owners)[NO], int wav
         exact_neighbors(a, w, u, [&](int, size_t at, bool in) {
             const float s = exact_dot(p.k + ko, w.plane_own, qs + at, w.plane_walk, a.d);
             const float dp = exact_dot(p.v + vo, w.plane_own, gs + at, w.plane_walk, a.e) - p.Dws[stat + at];
-            const float x = __builtin_amdgcn_exp2f(fmaf(s, c2, (a.ln_omega_ref - p.lse[stat + at]) * 1.4426950408889634f));
+            const float x = __builtin_amdgcn_exp2f(fmaf(s, c2, (a.ln_omega_ref - p.lse[stat + at]) * kLog2e));
             exact_add(adk, x * dp, in, qs + at, w.plane_walk, a.d, w.lane);
             exact_add(adv, x, in, gs + at, w.plane_walk, a.e, w.lane);
         });

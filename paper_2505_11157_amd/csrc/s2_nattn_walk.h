@@ -26,6 +26,30 @@ namespace s2walk {
 
 constexpr int kSpan = 57;            // widest union of arcs that is served by a single stage
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kMinRef = -1e30f;    // start value of the reference maximum: finite, so that x - m needs no guard (exp2(-inf) = 0)
+
+__device__ __forceinline__ float group_max(float x)     // over the four lanes (g = 0..3) of a point
+{
+    x = fmaxf(x, __shfl_xor(x, 16));
+    return fmaxf(x, __shfl_xor(x, 32));
+}
+__device__ __forceinline__ float group_sum(float x)
+{
+    x += __shfl_xor(x, 16);
+    return x + __shfl_xor(x, 32);
+}
+// Matrix results that a branch may lead to a reader of: the compiler pads the wait states of an instruction on one side of
+// a branch only.  Ten wait states here, after the last instruction of the tile.
+template <int N>
+__device__ __forceinline__ void settle(f32x4 (&a)[N])
+{
+#pragma unroll
+    for (int i = 0; i + 1 < N; ++i) asm volatile("" : "+v"(a[i]));
+    asm volatile("s_nop 9" : "+v"(a[N - 1]));
+}
+
 __device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }
 __device__ __forceinline__ int imax(int a, int b) { return a > b ? a : b; }
 
