@@ -43,7 +43,7 @@ def build(verbose=False, extra=(), jobs=None):
             asm = os.path.join(HERE, "_build", os.path.basename(s)[:-4] + "-hip-amdgcn-amd-amdhsa-gfx950.s")
             findings = isa_check.scan_file(asm)
             if findings:
-                raise RuntimeError("matrix-core result read too early in " + os.path.basename(s) + ":\n" + "\n".join(findings))
+                raise RuntimeError("unsafe code emitted for " + os.path.basename(s) + ":\n" + "\n".join(findings))
         return o
 
     jobs = jobs or min(8, os.cpu_count() or 1)

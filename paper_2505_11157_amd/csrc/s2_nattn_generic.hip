@@ -225,6 +225,42 @@ nattn_bwd_dq_generic(S2DeviceTables t, int nbh, int d, int e, float scale,
         if (l < d) stf(dq + (size_t(bh) * d + l) * so + io, dqr[l] * scale);
 }
 
+// visit(w): the longitudes on output latitude h (row b of the transposed band of hp) whose disk holds the input point (hp, win)
+template <class V>
+__device__ __forceinline__ void outputs_on_row(const S2DeviceTables &t, int hp, int h, int b, int win, V &&visit)
+{
+    if (t.upscale > 1) {
+        // upsampling: output longitude w = upscale*m + s holds this input point iff win - m lies in the arc
+        // of class s, i.e. m = win - lo - tt for tt = 0 .. c-1
+        const int bf = hp - t.band_lo[h];
+        for (int sc = 0; sc < t.upscale; ++sc) {
+            const int at = (h * t.upscale + sc) * t.band_max + bf;
+            const int cu = t.ucnt[at], lo = t.ulo[at];
+            for (int tt = 0; tt < cu; ++tt) {
+                int m = (win - lo - tt) % t.nlon_in;
+                m = m < 0 ? m + t.nlon_in : m;
+                visit(m * t.upscale + sc);
+            }
+        }
+    } else {
+        const int ps = t.pscale;
+        const int c = t.tcnt[hp * t.tband_max + b];
+        // x = w*pscale runs over the multiples of pscale in [win-hw, win+hw] (whole circle if c == nlon_in)
+        // (whole circle: start at the lane's own longitude so that the summation order is shift invariant)
+        const int hw = (c == t.nlon_in) ? 0 : (c - 1) >> 1;
+        int x = win - hw + t.nlon_in;             // shifted by nlon_in (a multiple of pscale) to stay positive
+        const int r = x % ps;
+        if (r) x += ps - r;
+        const int x_end = (c == t.nlon_in) ? x + t.nlon_in - ps : win + hw + t.nlon_in;
+        for (; x <= x_end; x += ps) {
+            int w = x / ps;
+            w = w >= t.nlon_out ? w - t.nlon_out : w;
+            w = w >= t.nlon_out ? w - t.nlon_out : w;
+            visit(w);
+        }
+    }
+}
+
 // Backward, key/value side (App. B.4): one lane per INPUT point j gathers
 //   dk_j = scale * sum_i dS_ij q_i,   dv_j = sum_i p_ij dout_i
 // over the output points whose disk contains j.  By the symmetry of the
@@ -259,18 +295,9 @@ nattn_bwd_dkdv_generic(S2DeviceTables t, int nbh, int d, int e, float scale,
     }
     const float wq = t.omega_rel[hp];
     const float lref2 = t.ln_omega_ref * log2e;
-    const int ps = t.pscale;
     const int nb = t.tband_n[hp], h0 = t.tband_lo[hp];
     for (int b = 0; b < nb; ++b) {
         const int h = h0 + b;
-        const int c = t.tcnt[hp * t.tband_max + b];
-        // x = w*pscale runs over the multiples of pscale in [win-hw, win+hw] (whole circle if c == nlon_in)
-        // (whole circle: start at the lane's own longitude so that the summation order is shift invariant)
-        const int hw = (c == t.nlon_in) ? 0 : (c - 1) >> 1;
-        int x = win - hw + t.nlon_in;             // shifted by nlon_in (a multiple of pscale) to stay positive
-        const int r = x % ps;
-        if (r) x += ps - r;
-        const int x_end = (c == t.nlon_in) ? x + t.nlon_in - ps : win + hw + t.nlon_in;
         const T *qb = q + size_t(bh) * d * so + size_t(h) * t.nlon_out;
         const T *gb = go + size_t(bh) * e * so + size_t(h) * t.nlon_out;
         const float *lb = lse + size_t(bh) * so + size_t(h) * t.nlon_out;
@@ -294,32 +321,73 @@ nattn_bwd_dkdv_generic(S2DeviceTables t, int nbh, int d, int e, float scale,
                 dvr[l] = fmaf(p, gr[l], dvr[l]);
             }
         };
-        if (t.upscale > 1) {
-            // upsampling: output longitude w = upscale*m + s holds this input point iff win - m lies in the arc
-            // of class s, i.e. m = win - lo - tt for tt = 0 .. c-1
-            const int bf = hp - t.band_lo[h];
-            for (int sc = 0; sc < t.upscale; ++sc) {
-                const int at = (h * t.upscale + sc) * t.band_max + bf;
-                const int cu = t.ucnt[at], lo = t.ulo[at];
-                for (int tt = 0; tt < cu; ++tt) {
-                    int m = (win - lo - tt) % t.nlon_in;
-                    m = m < 0 ? m + t.nlon_in : m;
-                    visit(m * t.upscale + sc);
-                }
-            }
-        } else {
-            for (; x <= x_end; x += ps) {
-                int w = x / ps;
-                w = w >= t.nlon_out ? w - t.nlon_out : w;
-                w = w >= t.nlon_out ? w - t.nlon_out : w;
-                visit(w);
-            }
-        }
+        outputs_on_row(t, hp, h, b, win, visit);
     }
 #pragma unroll
     for (int l = 0; l < DMAX; ++l) {
         if (l < d) stf(dk + (size_t(bh) * d + l) * si + ii, dkr[l] * scale);
         if (l < e) stf(dv + (size_t(bh) * e + l) * si + ii, dvr[l]);
+    }
+}
+
+// The same for more than 64 channels.  A lane cannot hold six sets of them (with 128 the registers overflow so far that the
+// compiler keeps scalar registers in vector lanes, saves those with all lanes switched on, and lets moves and spills of
+// ordinary values slip in between: lanes that have left the walk early lose theirs).  Here a workgroup accumulates kWideOut channels of dk
+// and dv; the dot products read their channels from memory, once per such block.
+constexpr int kWideOut = 32;
+template <typename T>
+__global__ void __launch_bounds__(64)
+nattn_bwd_dkdv_wide(S2DeviceTables t, int nbh, int d, int e, float scale,
+                    const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
+                    const float *__restrict__ lse, const T *__restrict__ go, const float *__restrict__ Dws,
+                    T *__restrict__ dk, T *__restrict__ dv)
+{
+    const int ntile = (t.nlon_in + 63) / 64, nblock = ((d > e ? d : e) + kWideOut - 1) / kWideOut;
+    int id = blockIdx.x;
+    const int tile = id % ntile; id /= ntile;
+    const int l0 = id % nblock * kWideOut; id /= nblock;
+    const int bh = id % nbh;
+    const int hp = t.trow_order[id / nbh];
+    const int win = tile * 64 + threadIdx.x;
+    if (win >= t.nlon_in) return;
+
+    const float log2e = 1.4426950408889634f;
+    const float qscale = scale * log2e;
+    const size_t so = size_t(t.nlat_out) * t.nlon_out, si = size_t(t.nlat_in) * t.nlon_in;
+    const size_t ii = size_t(hp) * t.nlon_in + win;
+    const T *kp = k + size_t(bh) * d * si + ii, *vp = v + size_t(bh) * e * si + ii;
+    float dkr[kWideOut], dvr[kWideOut];
+#pragma unroll
+    for (int l = 0; l < kWideOut; ++l) dkr[l] = dvr[l] = 0.f;
+    const float wq = t.omega_rel[hp];
+    const float lref2 = t.ln_omega_ref * log2e;
+    const int nb = t.tband_n[hp], h0 = t.tband_lo[hp];
+    for (int b = 0; b < nb; ++b) {
+        const int h = h0 + b;
+        const T *qb = q + size_t(bh) * d * so + size_t(h) * t.nlon_out;
+        const T *gb = go + size_t(bh) * e * so + size_t(h) * t.nlon_out;
+        const float *lb = lse + size_t(bh) * so + size_t(h) * t.nlon_out;
+        const float *Db = Dws + size_t(bh) * so + size_t(h) * t.nlon_out;
+        outputs_on_row(t, hp, h, b, win, [&](int w) {
+            float dot = 0.f, gv = -Db[w];
+#pragma unroll 4
+            for (int l = 0; l < d; ++l) dot = fmaf(ldf(qb + l * so + w), ldf(kp + l * si) * qscale, dot);
+#pragma unroll 4
+            for (int l = 0; l < e; ++l) gv = fmaf(ldf(gb + l * so + w), ldf(vp + l * si), gv);
+            const float p = wq * __builtin_amdgcn_exp2f(dot - fmaf(lb[w], log2e, -lref2));
+            const float dS = p * gv;
+#pragma unroll
+            for (int l = 0; l < kWideOut; ++l) {
+                // past the last channel: that channel again (not stored)
+                dkr[l] = fmaf(dS, ldf(qb + size_t(l0 + l < d ? l0 + l : d - 1) * so + w), dkr[l]);
+                dvr[l] = fmaf(p, ldf(gb + size_t(l0 + l < e ? l0 + l : e - 1) * so + w), dvr[l]);
+            }
+        });
+    }
+#pragma unroll
+    for (int l = 0; l < kWideOut; ++l) {
+        if (l0 + l < d) stf(dk + (size_t(bh) * d + l0 + l) * si + ii, dkr[l] * scale);
+        if (l0 + l < e) stf(dv + (size_t(bh) * e + l0 + l) * si + ii, dvr[l]);
     }
 }
 
@@ -364,8 +432,14 @@ int launch_dkdv(const S2DeviceTables &t, int nbh, int d, int e, float scale, con
 {
     const int nti = (t.nlon_in + 63) / 64;
     S2TraceScope tr("nattn_bwd_dkdv_generic", nbh * (t.fwd_pairs[0] + t.fwd_pairs[1] + t.fwd_pairs[2] + t.fwd_pairs[3]), st);
-    hipLaunchKernelGGL((nattn_bwd_dkdv_generic<DMAX, T>), dim3((unsigned)(long(nti) * nbh * t.nlat_in)), dim3(64), 0, st,
-                       t, nbh, d, e, scale, q, k, v, lse, go, Dws, dk, dv);
+    if constexpr (DMAX > 64) {
+        const int nblock = ((d > e ? d : e) + kWideOut - 1) / kWideOut;
+        hipLaunchKernelGGL((nattn_bwd_dkdv_wide<T>), dim3((unsigned)(long(nti) * nblock * nbh * t.nlat_in)), dim3(64), 0, st,
+                           t, nbh, d, e, scale, q, k, v, lse, go, Dws, dk, dv);
+    } else {
+        hipLaunchKernelGGL((nattn_bwd_dkdv_generic<DMAX, T>), dim3((unsigned)(long(nti) * nbh * t.nlat_in)), dim3(64), 0, st,
+                           t, nbh, d, e, scale, q, k, v, lse, go, Dws, dk, dv);
+    }
     return 0;
 }
 

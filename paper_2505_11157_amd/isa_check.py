@@ -13,6 +13,11 @@ states and reports the first non-MFMA instruction that names one of its destinat
 Required wait states before a VALU / LDS / memory access (CDNA3 ISA guide, "manually inserted wait states", with the
 one extra state gfx950 needs for matrix instructions of four or more passes): passes + 2 for fp32 inputs,
 passes + 3 (+ 1) otherwise; passes = cycles / 4.
+
+A kernel that runs out of scalar registers keeps some in lanes of vector registers, and moves those with all lanes switched on
+(exec = -1).  In a kernel that is out of vector registers as well, the compiler has been seen to put copies and spills of
+ordinary per-lane values between the switch and its end, where they overwrite the values of lanes that left a loop early:
+wrong gradients and a memory fault.  The scan reports a vector instruction there that touches no such lane register.
 """
 import re
 
@@ -39,6 +44,10 @@ def _regs(text):
     for m in _SINGLE.finditer(text):
         out.add(int(m.group(1)))
     return out
+
+
+def _acc(text):
+    return {int(m) for m in re.findall(r"\ba(\d+)\b", text)}
 
 
 def _is_instruction(line):
@@ -108,6 +117,35 @@ def scan(asm_text):
     return findings
 
 
+def scan_whole_wave(asm_text):
+    """Findings: ordinary vector instructions between exec = -1 and its end, one per kernel (the first, and how many)."""
+    findings = []
+    for m in re.finditer(r"^(_Z\w+):.*?^\.Lfunc_end", asm_text, re.M | re.S):
+        lines = [l.split(";")[0].strip() for l in m.group(0).split("\n")[1:]]
+        held, saved = set(), set()       # vector registers whose lanes hold scalars; accumulation registers they are saved in
+        for l in lines:
+            if l.startswith("v_writelane_b32"):
+                held |= _regs(l.split(None, 1)[1].split(",")[0])
+            elif l.startswith("v_readlane_b32"):
+                held |= _regs(l.split(",")[1])
+        for l in lines:
+            if l.startswith("v_accvgpr_write_b32") and _regs(l.split(",")[1]) & held:
+                saved |= _acc(l.split(",")[0])
+        inside, found = False, []
+        for l in lines:
+            if re.match(r"s_or_saveexec_b64 \S+, -1$|s_mov_b64 exec, -1$", l):
+                inside = True
+            elif l.startswith("s_mov_b64 exec,"):
+                inside = False
+            elif inside and l.startswith(("v_", "ds_", "global_", "buffer_", "flat_", "scratch_")) and not (
+                    _regs(l) & held or (not _regs(l) and _acc(l) & saved)):
+                found.append(l)
+        if found:
+            findings.append(f"{m.group(1)}: {len(found)} per-lane instructions with all lanes switched on, first: {found[0]}")
+    return findings
+
+
 def scan_file(path):
     with open(path) as f:
-        return scan(f.read())
+        text = f.read()
+    return scan(text) + scan_whole_wave(text)

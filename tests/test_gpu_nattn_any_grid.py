@@ -57,6 +57,21 @@ def test_any_grid_many_slices(batch, heads, d):
     run_case(c, arrs, [0, batch * heads - 1], C=C_DERIVED, case="any-many[d%d]" % d)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,e", [(65, 65), (80, 24), (16, 128), (128, 128)])
+def test_more_than_64_channels(d, e, dtype):
+    # grids on which the lanes of a wavefront leave the walk over a disk at different times (3:1, upsampling), equal ones, and
+    # a partly filled wavefront; 33 .. 128 channels in one to four blocks of dk and dv
+    for ci, c in enumerate((_c(0, 12, 15, 7, 5, 1.1), _c(0, 9, 12, 9, 24, 0.6), _c(1, 8, 70, 8, 70, 0.5))):
+        c, arrs = make_inputs(dict(c, d=max(d, e), dtype=dtype), seed=4900 + d)
+        c["d"] = d
+        arrs = [np.ascontiguousarray(a[:, :n]) for a, n in zip(arrs, (d, d, e, e))]
+        if dtype == "bf16":
+            run_bf16(c, arrs, range(2), "wide%d[%d,%d]" % (ci, d, e))
+        else:
+            run_case(c, arrs, range(2), C=C_DERIVED, case="wide%d[%d,%d]" % (ci, d, e))
+
+
 @pytest.mark.parametrize("lon,d", [(80, 16), (75, 32), (80, 64), (75, 24)])
 def test_bf16_sums_carry_float32_weights(lon, d):
     # The weights of the bf16 sums (probabilities) are float32 values.  A relative error u of a sum moves its rounding to 8 bits

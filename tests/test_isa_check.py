@@ -33,3 +33,13 @@ def test_wait_states_by_shape():
     assert len(isa_check.scan(f32)) == 1            # 16 of 18
     f32ok = HEAD + "\tv_mfma_f32_32x32x2_f32 v[0:15], v35, v21, v[0:15]\n\ts_nop 7\n\ts_nop 7\n\ts_nop 1\n\tv_mov_b32_e32 v20, v15\n\ts_endpgm\n"
     assert isa_check.scan(f32ok) == []
+
+
+def test_per_lane_instruction_with_all_lanes_on_is_found():
+    save = "\tv_writelane_b32 v247, s0, 63\n\ts_or_saveexec_b64 s[100:101], -1\n\tv_accvgpr_write_b32 a0, v247\n"
+    end = "\ts_mov_b64 exec, s[100:101]\n\tv_mov_b32_e32 v3, v4\n\ts_endpgm\n.Lfunc_end0:\n"
+    assert isa_check.scan_whole_wave(HEAD + save + end) == []
+    found = isa_check.scan_whole_wave(HEAD + save + "\tscratch_store_dword off, v70, off offset:2440 ; 4-byte Folded Spill\n" + end)
+    assert len(found) == 1 and "scratch_store_dword off, v70" in found[0]
+    restore = "\ts_mov_b64 s[100:101], exec\n\ts_mov_b64 exec, -1\n\tscratch_load_dword v251, off, off\n\ts_mov_b64 exec, s[100:101]\n\tv_readlane_b32 s0, v251, 3\n"
+    assert isa_check.scan_whole_wave(HEAD + restore + end) == []
