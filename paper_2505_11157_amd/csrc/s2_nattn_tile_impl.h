@@ -745,7 +745,7 @@ template <int MODE>
 void TileSet<MODE>::fwd(const S2DeviceTables &t, int nbh, int d, int e, float scale, const bf16raw *q, const bf16raw *k, const bf16raw *v,
                            bf16raw *out, float *lse, hipStream_t st)
 {
-    S2TraceScope tr("nattn_fwd_band<bf16>", pair_count(t.fwd_pairs, nbh), st);
+    S2TraceScope tr("nattn_fwd_tile", pair_count(t.fwd_pairs, nbh), st);
     by_shape<false>(t.side_out, nbh, d > e ? d : e, [&](auto s) {
         constexpr int D = decltype(s)::D, NO = decltype(s)::NO;
         hipLaunchKernelGGL((nattn_fwd_tile<D, NO, MODE>), dim3(blocks<NO>(t.side_out, nbh)), dim3(256), (fwd_lds<D, NO>()), st,
@@ -756,7 +756,7 @@ template <int MODE>
 void TileSet<MODE>::dq(const S2DeviceTables &t, int nbh, int d, int e, float scale, const bf16raw *q, const bf16raw *k, const bf16raw *v,
                           const bf16raw *o, const float *lse, const bf16raw *go, bf16raw *dq, float *Dws, hipStream_t st)
 {
-    S2TraceScope tr("nattn_bwd_dq_band<bf16>", pair_count(t.fwd_pairs, nbh), st);
+    S2TraceScope tr("nattn_bwd_dq_tile", pair_count(t.fwd_pairs, nbh), st);
     by_shape<true>(t.side_out, nbh, d > e ? d : e, [&](auto s) {
         constexpr int D = decltype(s)::D, NO = decltype(s)::NO;
         hipLaunchKernelGGL((nattn_bwd_dq_tile<D, NO, MODE>), dim3(blocks<NO>(t.side_out, nbh)), dim3(256), (fwd_lds<D, NO>()), st,
@@ -767,7 +767,7 @@ template <int MODE>
 void TileSet<MODE>::dkdv(const S2DeviceTables &t, int nbh, int d, int e, float scale, const bf16raw *q, const bf16raw *k, const bf16raw *v,
                             const float *lse, const bf16raw *go, const float *Dws, bf16raw *dk, bf16raw *dv, hipStream_t st)
 {
-    S2TraceScope tr("nattn_bwd_dkdv_band<bf16>", pair_count(t.bwd_pairs, nbh), st);
+    S2TraceScope tr("nattn_bwd_dkdv_tile", pair_count(t.bwd_pairs, nbh), st);
     by_shape<true>(t.side_in, nbh, d > e ? d : e, [&](auto s) {
         constexpr int D = decltype(s)::D, NO = decltype(s)::NO;
         hipLaunchKernelGGL((nattn_bwd_dkdv_tile<D, NO, MODE>), dim3(blocks<NO>(t.side_in, nbh)), dim3(256), (dkdv_lds<D, NO>()), st,

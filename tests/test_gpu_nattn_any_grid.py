@@ -57,6 +57,49 @@ def test_any_grid_many_slices(batch, heads, d):
     run_case(c, arrs, [0, batch * heads - 1], C=C_DERIVED, case="any-many[d%d]" % d)
 
 
+def _launches(f):
+    S.s2_trace_reset()
+    S.s2_trace_enable(True)
+    try:
+        f()
+        return {n for n, _, _ in S.s2_trace_entries()}
+    finally:
+        S.s2_trace_enable(False)
+        S.s2_trace_reset()
+
+
+@pytest.mark.parametrize("batch", [3, 12])
+@pytest.mark.parametrize("lon,d", [(76, 16), (75, 16), (75, 7), (76, 32), (75, 32), (76, 24), (76, 64), (75, 64), (75, 50)])
+def test_any_grid_many_slices_bf16(lon, d, batch):
+    # 24 slices make two owner tiles per wavefront, 96 make four (forward and, for 16 channels, backward), in each way a row is
+    # staged: four columns at a time (76 longitudes), column by column (75), and with channels missing
+    c, arrs = make_inputs(dict(_c(0, 41, lon, 41, lon, 0.3, heads=8, d=d), batch=batch, dtype="bf16"), seed=4600 + d)
+    names = _launches(lambda: run_bf16(c, arrs, [0, 8 * batch - 1], "any-many-bf16[%d,d%d,b%d]" % (lon, d, batch)))
+    assert names == {"nattn_fwd_tile", "nattn_bwd_dq_tile", "nattn_bwd_dkdv_tile"}, names
+
+
+@pytest.mark.parametrize("lon", [76, 75])
+@pytest.mark.parametrize("d", [16, 32, 64])
+def test_any_grid_many_slices_f32(lon, d):
+    # 32 slices: two owner tiles per wavefront (16 channels: in the forward and dq)
+    c, arrs = make_inputs(dict(_c(0, 41, lon, 41, lon, 0.3, heads=8, d=d), batch=4), seed=4700 + d)
+    names = _launches(lambda: run_case(c, arrs, [0, 31], C=C_DERIVED, case="any-many[%d,d%d]" % (lon, d)))
+    assert names == {"nattn_fwd_band", "nattn_bwd_dq_band", "nattn_bwd_dkdv_band"}, names
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,e", [(16, 32), (32, 16), (64, 8), (5, 64), (24, 17)])
+def test_value_width_other_than_key_width(d, e, dtype):
+    for ci, heads in ((0, 2), (17, 2), (1, 24)):
+        c, arrs = make_inputs(dict(SHAPES[ci], d=max(d, e), heads=heads, dtype=dtype), seed=4800 + d)
+        c["d"] = d
+        arrs = [np.ascontiguousarray(a[:, :n]) for a, n in zip(arrs, (d, d, e, e))]
+        kind = "tile" if dtype == "bf16" else "band"
+        run = (lambda: run_bf16(c, arrs, [0, heads - 1], "e%d-bf16" % ci)) if dtype == "bf16" else \
+            (lambda: run_case(c, arrs, [0, heads - 1], C=C_DERIVED, case="e%d" % ci))
+        assert _launches(run) == {"nattn_fwd_" + kind, "nattn_bwd_dq_" + kind, "nattn_bwd_dkdv_" + kind}
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("d,e", [(65, 65), (80, 24), (16, 128), (128, 128)])
 def test_more_than_64_channels(d, e, dtype):

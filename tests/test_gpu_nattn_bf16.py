@@ -9,9 +9,9 @@ error enters dS_ij = p_ij (dout_i.v_j - D_i) for every j at once and propagates 
 |d dq_il| <= |scale| dD_i sum_j p_ij |k_jl|,  |d dk_jl| <= |scale| sum_i p_ij dD_i |q_il|  (both sums come from the
 oracle: its forward with |k| in place of v, and the dv output of its backward with dD_i |q_i| in place of dout).
 It matters only where the softmax is nearly one-hot (a handful of elements per million on the workloads).
-Shapes with equal grids, d = e = 32 and a longitude count that is a multiple of 64 run on the bf16 matrix cores
-(band tiles); d = e = 16, 32, 64 on other multiples of 16 on the fp32 band tiles with bf16 loads and stores; every other
-shape on the shape-agnostic kernels with bf16 loads and stores.
+Shapes with equal grids, d = e = 32 and a longitude count that is a multiple of 64 run on the kernels written for them
+(FAST); every other shape with d and e up to 64 on the tile kernels for any grid pair (TILE, ANY); wider heads on the
+shape-agnostic kernels with bf16 loads and stores (test_gpu_nattn_any_grid).  All products but those of the last run on the bf16 matrix cores.
 """
 import json
 import math
@@ -98,8 +98,8 @@ FAST = [
     _c(2, 32, 128, 0.3), _c(3, 17, 64, 0.45), _c(0, 9, 64, math.pi), _c(1, 24, 256, 0.12), _c(0, 65, 256, 2 * math.pi / 64),
     _c(0, 13, 512, 0.2, H=1),
 ]
-# shape-agnostic kernels on bf16 tensors: other head widths, 2:1 grids, upsampling, ragged longitude counts
-GENERIC = [
+# other head widths, 2:1 grids, upsampling, ragged longitude counts
+ANY = [
     _c(0, 12, 15, 1.1, B=2, H=1, d=5, nlat_out=7, nlon_out=5), _c(1, 24, 70, 0.4, H=1, d=64),
     _c(0, 19, 152, 0.3, H=3, nlat_out=10, nlon_out=76), _c(0, 9, 16, 0.5, d=8, nlat_out=17, nlon_out=32),
     _c(0, 33, 100, 0.3, H=2), _c(2, 16, 32, 0.45, d=8),
@@ -120,17 +120,17 @@ def test_bf16_matrix_core_path(ci):
     assert names and all(n.split("<")[0] in ("nattn_fwd_bf16", "nattn_bwd_dq_bf16", "nattn_bwd_dkdv_bf16") for n in names), names
 
 
-# fp32 band tiles with bf16 loads and stores: head widths 16 and 64, and d = 32 on longitude counts that are multiples of
-# 16 but not of 64 (whole circles near the poles, short arcs, a ragged last group, the zero-weight pole row)
-BAND = [
+# head widths 16 and 64, and d = 32 on longitude counts that are multiples of 16 but not of 64 (whole circles near the poles,
+# short arcs, a ragged last group, the zero-weight pole row)
+TILE = [
     _c(0, 17, 64, 0.5, d=16), _c(0, 33, 192, 0.3, H=2, d=64), _c(1, 16, 128, 0.3, B=2, H=1, d=16), _c(0, 21, 80, 0.4, d=32),
     _c(2, 32, 144, 0.3, d=64), _c(0, 9, 64, math.pi, d=64),
 ]
 
 
-@pytest.mark.parametrize("ci", range(len(BAND)))
+@pytest.mark.parametrize("ci", range(len(TILE)))
 def test_bf16_band_tile_path(ci):
-    c, arrs = make_inputs(BAND[ci], seed=870 + ci)
+    c, arrs = make_inputs(TILE[ci], seed=870 + ci)
     S.s2_trace_reset()
     S.s2_trace_enable(True)
     try:
@@ -139,13 +139,19 @@ def test_bf16_band_tile_path(ci):
     finally:
         S.s2_trace_enable(False)
         S.s2_trace_reset()
-    assert names == {"nattn_fwd_band<bf16>", "nattn_bwd_dq_band<bf16>", "nattn_bwd_dkdv_band<bf16>"}, names
+    assert names == {"nattn_fwd_tile", "nattn_bwd_dq_tile", "nattn_bwd_dkdv_tile"}, names
 
 
-@pytest.mark.parametrize("ci", range(len(GENERIC)))
+@pytest.mark.parametrize("ci", range(len(ANY)))
 def test_bf16_shape_agnostic_path(ci):
-    c, arrs = make_inputs(GENERIC[ci], seed=850 + ci)
-    run_bf16(c, arrs, range(c["batch"] * c["heads"]), "bf16-gen%d" % ci)
+    # the shapes that other kernels took over from the shape-agnostic ones: on the tiles, and kept on those by the test switch
+    c, arrs = make_inputs(ANY[ci], seed=850 + ci)
+    run_bf16(c, arrs, range(c["batch"] * c["heads"]), "bf16-any%d" % ci)
+    S.s2_debug_control(S.S2_DEBUG_NO_BAND, 0)
+    try:
+        run_bf16(c, arrs, range(c["batch"] * c["heads"]), "bf16-gen%d" % ci)
+    finally:
+        S.s2_debug_control(0, S.S2_DEBUG_NO_BAND)
 
 
 @pytest.mark.parametrize("cfg,slices", [(2, range(8)), (3, [0, 9, 18, 27, 4, 13, 22, 31])])
