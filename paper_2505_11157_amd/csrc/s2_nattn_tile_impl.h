@@ -706,8 +706,10 @@ inline double pair_count(const double (&p)[4], int nbh) { return nbh * (p[0] + p
 // Calls f with the geometry for a head dimension and a launch: owner tiles per wavefront (NO).  More of them share a staged
 // row and its masks, fewer make more workgroups.  Measured on seven grids with 6 to 32 slices: four from eight workgroups per
 // compute unit on (129 x 256, 32 slices, d = 16: 0.95 against 1.04 ms per step; 91 x 180, 16 slices: 0.32 against 0.31), two
-// from three per compute unit on (91 x 181, 8 slices, d = 32: 0.24 against 0.28; 64 x 128, 8 slices: 0.24 against 0.21), 64
-// channels always two.  The backward keeps 32 channels at two (0.86 against 0.90 ms on 161 x 320 with 18 slices).
+// from three per compute unit on (91 x 181, 8 slices, d = 32: 0.24 against 0.28; 64 x 128, 8 slices: 0.24 against 0.21).  The
+// backward keeps 32 channels at two (0.86 against 0.90 ms on 161 x 320 with 18 slices).  64 channels: two from two per compute
+// unit on (64 x 128, 8 slices: 302 against 341 us per step; 91 x 181, 4 slices: 319 against 383), else one (64 x 128, 4 slices:
+// 208 against 282; 91 x 180, 2 slices: 205 against 264; 46 x 90, 4 slices: 156 against 180).
 template <int D_, int NO_>
 struct Shape {
     static constexpr int D = D_, NO = NO_;
@@ -727,7 +729,8 @@ void by_shape(const S2BandSide &b, int nbh, int dmax, F &&f)
         if (two) f(Shape<32, 2>());
         else f(Shape<32, 1>());
     } else {
-        f(Shape<64, 2>());
+        if (blocks<2>(b, nbh) >= 2 * ncu) f(Shape<64, 2>());
+        else f(Shape<64, 1>());
     }
 }
 
@@ -739,7 +742,7 @@ int TileSet<MODE>::configure()
 {
     return configure_one<16, 1, MODE, true>() || configure_one<16, 2, MODE, true>() || configure_one<16, 4, MODE, true>() ||
            configure_one<32, 1, MODE, true>() || configure_one<32, 2, MODE, true>() || configure_one<32, 4, MODE, false>() ||
-           configure_one<64, 2, MODE, true>();
+           configure_one<64, 1, MODE, true>() || configure_one<64, 2, MODE, true>();
 }
 template <int MODE>
 void TileSet<MODE>::fwd(const S2DeviceTables &t, int nbh, int d, int e, float scale, const bf16raw *q, const bf16raw *k, const bf16raw *v,
