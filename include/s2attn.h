@@ -117,9 +117,11 @@ size_t s2_nattn_bwd_workspace_bytes(const s2_grid_t *g, int batch, int heads, in
  * Layouts (contiguous): q, out [batch][heads][d][nlat_out][nlon_out] (out has
  * d_v channels); k [batch][heads][d_qk][nlat_in][nlon_in]; v likewise with d_v;
  * lse float32 [batch][heads][nlat_out][nlon_out].
- * dtype: S2_F32 (float32 tensors, float32 arithmetic throughout) or S2_BF16 (q, k, v, out bf16; products on the
- * bf16 matrix cores where the shape allows - equal grids, d_qk = d_v = 32, longitude count a multiple of 64 - with
- * float32 accumulation and softmax, otherwise float32 arithmetic on bf16 loads; lse float32 either way).
+ * dtype: S2_F32 (float32 tensors, float32 arithmetic throughout) or S2_BF16 (q, k, v, out bf16; up to 64 channels the
+ * products run on the bf16 matrix cores with float32 accumulation and softmax - probabilities enter them as bf16 on equal
+ * grids with d_qk = d_v = 32 and a longitude count that is a multiple of 64, as exact sums of three bf16 terms on all other
+ * shapes; above 64 channels, or with more than 128 walked latitudes per output latitude, float32 arithmetic on bf16 loads;
+ * lse float32 either way).
  * d_qk, d_v in [1, 128].
  * Non-finite inputs (both directions): a NaN or an infinity at a point reaches the results whose sums hold that point
  * and no others.  Exception: with d_qk = d_v = 32, float32 tensors on equal, 2:1 and 1:2 grids and bf16 tensors on
@@ -300,9 +302,11 @@ int s2_grid_device_flags(const s2_grid_t *g, unsigned *flags);
  *   S2_DEBUG_NO_ROW_GROUPS  matrix-core kernels never start a second set of wavefronts per workgroup
  *   S2_DEBUG_FAIL_LAUNCH    the launchers of the tuned neighborhood kernels report failure before launching
  *                           anything: s2_nattn_fwd / s2_nattn_bwd then return S2_ERR_DEVICE
- *   S2_DEBUG_FORCE_BAND     float32 tensors with d = e = 32 always run on the band-tile matrix-core kernels that
- *                           serve d = e = 16 and 64 (by default only where the streaming kernels do not apply)
- *   S2_DEBUG_NO_BAND        the band-tile matrix-core kernels are never used (d = 16, 64: shape-agnostic kernels)
+ *   S2_DEBUG_FORCE_BAND     float32 tensors with d = e = 32 always run on the band-tile matrix-core kernels that serve
+ *                           every other pair of widths up to 64 (by default neither on equal grids whose light latitudes
+ *                           stream nor on the 2:1 and upsampling grids the split vector kernels take)
+ *   S2_DEBUG_NO_BAND        the matrix-core tiles for any grid pair and width are never used, on float32 or bf16 tensors
+ *                           (all but d = e = 32: shape-agnostic kernels)
  */
 enum { S2_DEBUG_NO_MFMA = 1, S2_DEBUG_NO_STREAM = 2, S2_DEBUG_NO_ROW_GROUPS = 4, S2_DEBUG_FAIL_LAUNCH = 8, S2_DEBUG_FORCE_BAND = 16, S2_DEBUG_NO_BAND = 32 };
 unsigned s2_debug_control(unsigned set_bits, unsigned clear_bits);

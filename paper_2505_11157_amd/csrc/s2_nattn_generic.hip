@@ -473,15 +473,6 @@ int s2_nattn_fwd_generic(const S2DeviceTables &t, int nbh, int d, int e, float s
     return by_width(d, e, [&](auto W) { return launch_fwd<decltype(W)::value, float>(t, nbh, d, e, scale, q, k, v, out, lse, st); });
 }
 
-int s2_nattn_bwd_dkdv_generic(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q,
-                              const float *k, const float *v, const float *lse, const float *go, const float *Dws,
-                              float *dk, float *dv, hipStream_t st)
-{
-    return by_width(d, e, [&](auto W) {
-        return launch_dkdv<decltype(W)::value, float>(t, nbh, d, e, scale, q, k, v, lse, go, Dws, dk, dv, st);
-    });
-}
-
 int s2_nattn_bwd_generic(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q,
                          const float *k, const float *v, const float *o, const float *lse, const float *go,
                          float *dq, float *dk, float *dv, float *Dws, hipStream_t st)

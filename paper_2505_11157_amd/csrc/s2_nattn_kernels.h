@@ -23,16 +23,12 @@ int s2_nattn_bwd_dkdv_generic_bf16(const S2DeviceTables &t, int nbh, int d, int 
                                    const void *k, const void *v, const float *lse, const void *go, const float *Dws,
                                    void *dk, void *dv, hipStream_t st);
 
-// Tuned float32 forward for d = e = 32, nlon_in / nlon_out in {1, 2}, longitudes a multiple of 4.
+// Split vector float32 forward for d = e = 32, nlon_in / nlon_out in {1, 2} or upsampling, longitudes a multiple of 4.
 bool s2_nattn_fwd_tiled_supported(const S2DeviceTables &t, int d, int e);
 int s2_nattn_fwd_tiled(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k,
                        const float *v, float *out, float *lse, hipStream_t st);
 
-// dk/dv part of the shape-agnostic backward alone (D_i must already be in Dws).
-int s2_nattn_bwd_dkdv_generic(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q,
-                              const float *k, const float *v, const float *lse, const float *go, const float *Dws,
-                              float *dk, float *dv, hipStream_t st);
-// Tuned float32 backward for d = e = 32 (dq for nlon_in / nlon_out in {1, 2}; dk/dv tuned on equal grids).
+// Split vector float32 backward for d = e = 32, the same shapes.
 bool s2_nattn_bwd_tiled_supported(const S2DeviceTables &t, int d, int e);
 int s2_nattn_bwd_tiled(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k,
                        const float *v, const float *o, const float *lse, const float *go, float *dq, float *dk,

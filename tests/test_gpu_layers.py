@@ -46,23 +46,22 @@ def close(x, ref, what, case, abs_sum=None):
 
 
 MHA_CASES = [
-    # (grid, batch, channels, heads): d = 16 on 32 / 48 longitudes runs the shape-agnostic attention kernels, d = 32 on
-    # 192 / 256 longitudes the matrix-core and streaming ones, d = 16 and 64 on 192 / 128 longitudes the fp32 band
-    # tiles; 48 channels leave the 128 x 128 tiles of the channel matrices ragged
+    # (grid, batch, channels, heads): d = 32 on 192 / 256 longitudes runs the matrix-core and streaming attention kernels,
+    # d = 16 and 64 the fp32 band tiles; 48 and 160 channels leave row tiles of the channel products ragged
     (dict(grid_type=0, nlat_in=17, nlon_in=32, nlat_out=17, nlon_out=32, theta=0.5), 2, 32, 2),
     (dict(grid_type=1, nlat_in=16, nlon_in=48, nlat_out=16, nlon_out=48, theta=0.4), 1, 48, 3),
     (dict(grid_type=0, nlat_in=33, nlon_in=192, nlat_out=33, nlon_out=192, theta=0.3), 2, 64, 2),
     (dict(grid_type=0, nlat_in=25, nlon_in=256, nlat_out=25, nlon_out=256, theta=0.25), 1, 160, 5),
     (dict(grid_type=0, nlat_in=33, nlon_in=192, nlat_out=33, nlon_out=192, theta=0.3), 1, 48, 3),
     (dict(grid_type=1, nlat_in=16, nlon_in=128, nlat_out=16, nlon_out=128, theta=0.45), 1, 128, 2),
-    # 64 channels on 816 grid points: the weight-resident channel products with a last tile of 16 of 32 points
+    # 64 channels on 816 grid points: channel products with a last strip of 48 of 128 points
     (dict(grid_type=0, nlat_in=17, nlon_in=48, nlat_out=17, nlon_out=48, theta=0.5), 1, 64, 4),
 ]
 
 
 def _random_mha_case(seed):
     # seeded random sub-blocks: equal grids with 9 to 24 latitudes and 32 to 160 longitudes (multiples of 16), 64 or 128
-    # channels (weight-resident channel products: ragged last tiles, one or several rounds) or 32, 96, 160 (tiled ones)
+    # channels, or 32, 96, 160 (channel products with a ragged last strip of points and row tiles of 32 to 128)
     rng = np.random.default_rng(9900 + seed)
     C = (64, 128, 32, 96, 128, 64, 160, 128)[seed % 8]
     d = int(rng.choice([8, 16, 32]))

@@ -128,15 +128,15 @@ SMALL = [
     dict(kind="nattn", grid_type=0, nlat_in=33, nlon_in=192, nlat_out=33, nlon_out=192, theta=0.3, batch=9, heads=2, d=32, dtype="f32"),
     # a handful of light latitudes with bands of three rows (two wavefronts per workgroup, more segments than fit)
     dict(kind="nattn", grid_type=0, nlat_in=9, nlon_in=256, nlat_out=9, nlon_out=256, theta=0.5, batch=1, heads=2, d=32, dtype="f32"),
-    # the equiangular grid as the paper prints it (no south pole, zero weight on the pole row): generic, tuned
+    # the equiangular grid as the paper prints it (no south pole, zero weight on the pole row): band tiles, tuned
     # equal-grid and tuned 2:1 kernels
     dict(kind="nattn", grid_type=2, nlat_in=16, nlon_in=32, nlat_out=16, nlon_out=32, theta=0.45, batch=1, heads=2, d=8, dtype="f32"),
     dict(kind="nattn", grid_type=2, nlat_in=64, nlon_in=256, nlat_out=64, nlon_out=256, theta=4 * math.pi / 64, batch=1, heads=2, d=32, dtype="f32"),
     dict(kind="nattn", grid_type=2, nlat_in=40, nlon_in=160, nlat_out=20, nlon_out=80, theta=0.35, batch=1, heads=3, d=32, dtype="f32"),
-    # Gauss-Lobatto grid (both poles, Gaussian spacing): generic and tuned kernels
+    # Gauss-Lobatto grid (both poles, Gaussian spacing): band tiles and tuned kernels
     dict(kind="nattn", grid_type=3, nlat_in=17, nlon_in=32, nlat_out=17, nlon_out=32, theta=0.45, batch=1, heads=2, d=8, dtype="f32"),
     dict(kind="nattn", grid_type=3, nlat_in=65, nlon_in=256, nlat_out=65, nlon_out=256, theta=4 * math.pi / 64, batch=1, heads=2, d=32, dtype="f32"),
-    # upsampling (nlon_out = 2, 3, 4 x nlon_in): shape-agnostic kernels with one list per longitude class
+    # upsampling (nlon_out = 2, 3, 4 x nlon_in), narrow grids: band tiles with one row per longitude class
     dict(kind="nattn", grid_type=0, nlat_in=9, nlon_in=16, nlat_out=17, nlon_out=32, theta=0.5, batch=1, heads=2, d=8, dtype="f32"),
     dict(kind="nattn", grid_type=1, nlat_in=12, nlon_in=24, nlat_out=16, nlon_out=72, theta=0.4, batch=2, heads=1, d=32, dtype="f32"),
     dict(kind="nattn", grid_type=0, nlat_in=9, nlon_in=20, nlat_out=17, nlon_out=80, theta=0.6, batch=1, heads=1, d=5, dtype="f32"),
@@ -150,7 +150,7 @@ SMALL = [
     # larger and odd longitude ratios (8x, 5x)
     dict(kind="nattn", grid_type=0, nlat_in=7, nlon_in=72, nlat_out=9, nlon_out=576, theta=0.7, batch=1, heads=2, d=32, dtype="f32"),
     dict(kind="nattn", grid_type=1, nlat_in=10, nlon_in=84, nlat_out=6, nlon_out=420, theta=0.45, batch=2, heads=1, d=32, dtype="f32"),
-    # upsampling on the grid of App. A.1 (zero-weight pole row): shape-agnostic kernels and the class view
+    # upsampling on the grid of App. A.1 (zero-weight pole row): band tiles and the class view
     dict(kind="nattn", grid_type=2, nlat_in=8, nlon_in=16, nlat_out=12, nlon_out=32, theta=0.7, batch=1, heads=2, d=8, dtype="f32"),
     dict(kind="nattn", grid_type=2, nlat_in=12, nlon_in=72, nlat_out=16, nlon_out=144, theta=0.5, batch=1, heads=2, d=32, dtype="f32"),
 ]
@@ -300,9 +300,9 @@ def test_launcher_failure_is_reported():
 
 # Peaked softmax: q and k scaled by 6 put the logits tens of units apart (nearly one-hot probabilities), so the lazily
 # moved reference maximum of every kernel family has to move many times; a negative scale flips which logits are the
-# large ones.  Shapes: matrix-core + streaming (65x256), split vector kernels on a 2:1 grid, shape-agnostic kernels
+# large ones.  Shapes: matrix-core + streaming (65x256), split vector kernels on a 2:1 grid, band tiles
 # (d = 12, 2:1; d = 64), the grid of App. A.1 with its zero-weight pole row on the tuned (equal, 2:1, upsampling) and the
-# shape-agnostic kernels (a pole logit far above all others must not drown the positive-weight terms), upsampling in
+# band-tile kernels (a pole logit far above all others must not drown the positive-weight terms), upsampling in
 # the class view.
 PEAKED = [13, 9, 3, 4, 17, 16, 18, 25, 31, 32]
 

@@ -1,5 +1,6 @@
-"""GPU parity of the fp32 band-tile matrix-core kernels (head dimensions 16 and 64 on equal grids; 32 when a test
-switch routes it there) against the float64 oracle, through the C ABI, at the stated bound
+"""GPU parity of the fp32 band-tile matrix-core kernels on equal grids whose longitude counts are multiples of 16 (head
+dimensions 16 and 64; 32 when a test switch routes it there; every other width, count and grid pair in
+test_gpu_nattn_any_grid.py) against the float64 oracle, through the C ABI, at the stated bound
 |x - ref| <= 1e-6 + 1e-5 |ref| (plus the derived rounding allowance of test_gpu_nattn on the peaked cases)."""
 import math
 
@@ -41,8 +42,7 @@ def test_band_kernels(i, d):
 
 @pytest.mark.parametrize("i", [1, 12])
 def test_band_kernels_d32_many_slices(i):
-    # 20 slices (more than two workgroups per compute unit; d = 16 switches from two to four owner tiles per wavefront
-    # at that point, see the random shapes): three of them against the oracle
+    # 20 slices: more workgroups than one per compute unit; three of the slices against the oracle
     gt, nlat, nlon, theta = SHAPES[i]
     c, arrs = make_inputs(_c(gt, nlat, nlon, theta, 4, 5, 32), seed=930 + i)
     with debug_switches(S.S2_DEBUG_FORCE_BAND):
