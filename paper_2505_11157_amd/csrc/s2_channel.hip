@@ -24,7 +24,7 @@ __device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c)
 // ([k][m], rows 33 mod 64 words apart: the two k rows one instruction reads lie 33 banks apart, and the transposing
 // store spreads over the banks); X does not: lane (column, half) reads X[k0 + 2 j + half][n0 + column] straight into
 // the operand, a whole slice ahead of its use, every element once, in 128-byte row pieces.
-// Bound by the matrix cores (MT instructions of 64 cycles per LDS word and lane), 63 % busy over the launch.  The rows per
+// Bound by the matrix cores (MT instructions of 64 cycles per LDS word and lane), 60 to 67 % busy over the launch by the counters.  The rows per
 // workgroup follow M, so 64-row products leave no half of a tile empty, and any k fits: 64 x 576 onto 4 x 33024 points went
 // from 230 us (128-row tiles, X through LDS) to 118 us, three 128 x 128 products of one X from 3 x 56 us to 135 us, their
 // sum back from 167 us to 125 us.
