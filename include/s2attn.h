@@ -302,10 +302,9 @@ int s2_grid_device_flags(const s2_grid_t *g, unsigned *flags);
  *   S2_DEBUG_NO_ROW_GROUPS  matrix-core kernels never start a second set of wavefronts per workgroup
  *   S2_DEBUG_FAIL_LAUNCH    the launchers of the tuned neighborhood kernels report failure before launching
  *                           anything: s2_nattn_fwd / s2_nattn_bwd then return S2_ERR_DEVICE
- *   S2_DEBUG_FORCE_BAND     float32 tensors with d = e = 32 always run on the band-tile matrix-core kernels that serve
- *                           every other pair of widths up to 64 (by default neither on equal grids whose light latitudes
- *                           stream nor on the 2:1 and upsampling grids the split vector kernels take)
- *   S2_DEBUG_NO_BAND        the matrix-core tiles for any grid pair and width are never used, on float32 or bf16 tensors
+ *   S2_DEBUG_FORCE_BAND     the forward of float32 tensors with d = e = 32 on upsampling grids runs on the matrix-core patches too,
+ *                           like every other pair of widths up to 64 (by default on the split vector kernel)
+ *   S2_DEBUG_NO_BAND        the matrix-core kernels for any grid pair and width are never used, on float32 or bf16 tensors
  *                           (all but d = e = 32: shape-agnostic kernels)
  */
 enum { S2_DEBUG_NO_MFMA = 1, S2_DEBUG_NO_STREAM = 2, S2_DEBUG_NO_ROW_GROUPS = 4, S2_DEBUG_FAIL_LAUNCH = 8, S2_DEBUG_FORCE_BAND = 16, S2_DEBUG_NO_BAND = 32 };

@@ -224,6 +224,108 @@ static void build_sides(s2_grid *g)
         }
 }
 
+// Segments and workgroups of the patch kernels for one kind of owners.  A wavefront owns 16 points, 1 x 16, 2 x 8 or 4 x 4 rows x
+// columns: a square patch meets the fewest walked columns where arcs are short; where they are long, owners of one row share
+// more of theirs.  Each group of four rows takes the shape with the fewest chunks of four columns to walk (counted, not measured).
+static void build_patches(const std::vector<int> &blo, const std::vector<int> &bn, const std::vector<int2> &arc, int nU, const float *omega,
+                          int c_walk, s2_grid::Patches &p)
+{
+    const int n_own = int(blo.size()), bmax = int(arc.size() / blo.size()), ngrp = (n_own + 3) / 4;
+    struct Row {
+        int lo, hi;
+        bool any;
+        int2 own[4];
+    };
+    auto walk = [&](int first, int last, int &rmin, std::vector<Row> &rows) {      // owner rows first .. last - 1
+        int rmax = -1;
+        rmin = 1 << 30;
+        for (int v = first; v < last; ++v)
+            if (bn[v] > 0) {
+                rmin = std::min(rmin, blo[v]);
+                rmax = std::max(rmax, blo[v] + bn[v] - 1);
+            }
+        rows.assign(size_t(std::max(rmax - rmin + 1, 0)), Row{1 << 30, -(1 << 30), false, {}});
+        for (int v = first; v < last; ++v)
+            for (int i = 0; i < bn[v]; ++i) {
+                const int2 a = arc[size_t(v) * bmax + i];
+                Row &r = rows[blo[v] + i - rmin];
+                if (a.y <= 0) continue;
+                r.own[v - first] = a;
+                r.any = true;
+                r.lo = std::min(r.lo, a.x);
+                r.hi = std::max(r.hi, a.x + a.y - 1);
+            }
+    };
+    int rmin;
+    std::vector<Row> rows;
+    std::vector<int> shape(ngrp, 0), seg_of(ngrp + 1, 0);
+    for (int s = 0; s < ngrp; ++s) {
+        double least = -1.0;
+        for (int lg = 0; lg < 3; ++lg) {
+            const int W = 16 >> lg;
+            double chunks = 0.0;
+            for (int f = 4 * s; f < std::min(4 * s + 4, n_own); f += 1 << lg) {
+                walk(f, std::min(f + (1 << lg), n_own), rmin, rows);
+                for (const Row &r : rows)
+                    if (r.any) chunks += std::min((W + r.hi - r.lo + 3) / 4.0, (nU + 3) / 4.0) / W;
+            }
+            if (least < 0.0 || chunks < least) {
+                least = chunks;
+                shape[s] = lg;
+            }
+        }
+    }
+    p.seg.clear();
+    p.rows.clear();
+    // A row of whole circles, every column once: no owner's mask excludes anything.  Offsets stay within 16 bits.
+    constexpr unsigned kAlways = 0xffff8000u;
+    const bool once = nU % 4 == 0 && nU <= 32000;
+    for (int s = 0; s < ngrp; ++s) {
+        const int lg = shape[s], OW = std::min(kS2PatchWaves * (16 >> lg), nU);
+        seg_of[s] = int(p.seg.size() / 2);
+        for (int f = 4 * s; f < std::min(4 * s + 4, n_own); f += 1 << lg) {
+            const int l = std::min(f + (1 << lg), n_own);
+            walk(f, l, rmin, rows);
+            int before = 0;
+            const int at = int(p.rows.size());
+            for (size_t i = 0; i < rows.size(); ++i) {
+                Row &r = rows[i];
+                bool always = once && r.any;
+                for (int k = 0; k < l - f; ++k) {
+                    always &= r.own[k].y >= nU;
+                    if (r.own[k].y >= nU) r.own[k] = make_int2(-(nU / 2), nU);
+                }
+                r.lo = 1 << 30;
+                r.hi = -(1 << 30);
+                for (int k = 0; k < l - f; ++k)
+                    if (r.own[k].y > 0) {
+                        r.lo = std::min(r.lo, r.own[k].x);
+                        r.hi = std::max(r.hi, r.own[k].x + r.own[k].y - 1);
+                    }
+                const int c0 = always || !r.any ? 0 : r.lo & ~3;
+                auto pack = [](int lo, int n) { return unsigned(lo & 0xffff) | unsigned(n) << 16; };
+                S2PatchRow o{};
+                o.col = c0 - 4 * before;
+                o.uni = int(!r.any ? 0u : always ? kAlways : pack(r.lo, r.hi - r.lo + 1));
+                o.before = before;
+                o.omega = omega ? omega[(rmin + int(i)) / c_walk] : 1.f;
+                for (int k = 0; k < l - f; ++k) o.arc[k] = always ? kAlways : pack(r.own[k].x, r.own[k].y);
+                p.rows.push_back(o);
+                before += !r.any ? 0 : always ? nU / 4 : (OW + r.hi - c0 + 3) / 4;
+            }
+            p.seg.push_back(make_int4(f, lg, rows.empty() ? 0 : rmin, int(rows.size())));
+            p.seg.push_back(make_int4(before, at, 0, 0));
+        }
+    }
+    seg_of[ngrp] = int(p.seg.size() / 2);
+    p.list.clear();
+    for (int k = 0; k < ngrp; ++k) {
+        const int s = (k & 1) ? ngrp - 1 - (k >> 1) : k >> 1;                          // the polar rows are the heaviest
+        for (int t = seg_of[s]; t < seg_of[s + 1]; ++t)
+            for (int c = 0; c < nU; c += kS2PatchWaves * (16 >> shape[s])) p.list.push_back(make_int2(t, c));
+    }
+}
+
 static int upload_tables(s2_grid *g)
 {
     int ndev = 0;
@@ -283,6 +385,11 @@ static int upload_tables(s2_grid *g)
         {g->vi_n.data(), g->vi_n.size() * sizeof(int), 0},
         {g->vi_arc.data(), g->vi_arc.size() * sizeof(int2), 0},
     };
+    for (const s2_grid::Patches *p : {&g->vo_patch, &g->vi_patch}) {
+        parts.push_back({p->seg.data(), p->seg.size() * sizeof(int4), 0});
+        parts.push_back({p->rows.data(), p->rows.size() * sizeof(S2PatchRow), 0});
+        parts.push_back({p->list.data(), p->list.size() * sizeof(int2), 0});
+    }
     size_t total = 0;
     for (auto &p : parts) {
         p.off = total;
@@ -327,6 +434,14 @@ static int upload_tables(s2_grid *g)
                   g->nlat_out, g->nlat_in};
     t.side_in = {ip(18), ip(19), ap(20), int(g->vi_arc.size() / g->vi_lo.size()), int(g->vi_lo.size()), nU, ci, co,
                  g->nlat_in, g->nlat_out};
+    for (int i = 0; i < 2; ++i) {
+        const s2_grid::Patches &p = i ? g->vi_patch : g->vo_patch;
+        S2BandSide::Patches &q = (i ? t.side_in : t.side_out).patches;
+        q.seg = reinterpret_cast<const int4 *>(base + parts[21 + 3 * i].off);
+        q.row_rec = reinterpret_cast<const int4 *>(base + parts[22 + 3 * i].off);
+        q.patch = ap(23 + 3 * i);
+        q.npatch = int(p.list.size());
+    }
     g->on_device = true;
     return S2_OK;
 }
@@ -677,6 +792,14 @@ extern "C" int s2_grid_init(int grid_type, int nlat_in, int nlon_in, int nlat_ou
         return true;
     };
     g->dt.band_rows_ok = rows_ok(g->vo_lo, g->vo_n) && rows_ok(g->vi_lo, g->vi_n) && std::min(nlon_in, nlon_out) < 32768;
+    if (g->dt.band_rows_ok) {
+        const double most = *std::max_element(g->omega_in.begin(), g->omega_in.end());
+        std::vector<float> omega(nlat_in);
+        for (int h = 0; h < nlat_in; ++h) omega[h] = float(g->omega_in[h] / most);
+        const int nU = std::min(nlon_in, nlon_out);
+        build_patches(g->vo_lo, g->vo_n, g->vo_arc, nU, omega.data(), g->pscale, g->vo_patch);
+        build_patches(g->vi_lo, g->vi_n, g->vi_arc, nU, nullptr, g->upscale, g->vi_patch);
+    }
     int rc = upload_tables(g);
     if (rc != S2_OK) { delete g; return rc; }
     *out_grid = g;

@@ -24,6 +24,24 @@ struct S2BandSide {
     int bmax, n_own, nU;
     int c_own, c_walk;
     int nlat_own, nlat_walk;
+    // the patch kernels (s2_nattn_patch_impl.h)
+    struct Patches {
+        const int4 *seg;      // 2 per segment: (first owner row, log2(owner rows), first walked row, walked rows), (chunks, place in row_rec, -, -)
+        const int4 *row_rec;  // 2 per walked row of a segment: S2PatchRow
+        const int2 *patch;    // workgroups of a slice, heaviest first: segment, first column
+        int npatch;
+    } patches;
+};
+
+// A walked row as the owners of a segment see it.  The columns that any of a workgroup's owners meets on it are cut into chunks
+// of four; the chunks of all rows are numbered in order.  Columns are relative to the workgroup's first.
+constexpr int kS2PatchWaves = 4;         // wavefronts of a workgroup
+struct S2PatchRow {
+    int col;                  // first column of chunk X of the row = col + 4 X
+    int uni;                  // union of the owner rows' arcs: first offset (16 bits), length (16 bits)
+    int before;               // chunks of the rows before
+    float omega;              // the row's relative quadrature weight (owners = inputs: 1)
+    unsigned arc[4];          // per owner row: first offset (16 bits), length (16 bits)
 };
 
 struct S2DeviceTables {
@@ -84,6 +102,11 @@ struct s2_grid {
     std::vector<int> ucnt, ulo;      // upsampling only (see S2DeviceTables)
     std::vector<int> vo_lo, vo_n, vi_lo, vi_n;      // S2BandSide tables, owners = outputs / inputs
     std::vector<int2> vo_arc, vi_arc;
+    struct Patches {
+        std::vector<int4> seg;
+        std::vector<S2PatchRow> rows;
+        std::vector<int2> list;
+    } vo_patch, vi_patch;
     int band_max = 0, tband_max = 0;
     // the band and arc tables exactly as eq. (5) gives them (introspection); the tables above, which the kernels
     // use, leave out input latitudes of weight zero (listed in zero_lat)

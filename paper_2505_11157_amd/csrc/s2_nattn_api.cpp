@@ -27,28 +27,18 @@ extern "C" size_t s2_nattn_bwd_workspace_bytes(const s2_grid_t *g, int batch, in
     return size_t(batch) * heads * g->nlat_out * g->nlon_out * sizeof(float);
 }
 
-// The fp32 band-tile kernels take everything up to 64 channels except, for d = e = 32, equal grids whose light latitudes
-// stream, 2:1 downsampling and upsampling: there the kernels written for that width sum each owner in shorter chains.  Root
-// mean square error against float64 of unit-variance tensors, 12 grid pairs of 9 to 65 latitudes, those kernels - band tiles:
-//   downsampling   out 2.2e-8..2.8e-8 - 3.9e-8..4.2e-8,  dq 3.6e-8..5.1e-8 - 4.8e-8..6.1e-8,  dk, dv equal within 30 %
-//   upsampling     out 4.1e-8..4.5e-8 - 4.8e-8..5.3e-8,  dq equal within 13 %,  dk, dv 1.0e-7..2.4e-7 - 1.5e-7..5.2e-7
-// and the plain bound of 1e-6 + 1e-5 |ref| on dv is passed on 13 x 76 -> 25 x 152.  It is not the faster side everywhere:
-// forward / dq / dk/dv, us, those kernels - band tiles:
-//   257 x 512 -> 129 x 256:  4 slices 351 / 461 / 466 - 334 / 386 / 259;  8: 399 / 509 / 689 - 528 / 597 / 501;
-//                            32: 1664 / 2383 / 3040 - 1928 / 2166 / 1940
-//   129 x 256 -> 65 x 128:   4: 202 / 200 / 180 - 119 / 138 / 81;  8: 204 / 205 / 205 - 219 / 243 / 135;
-//                            32: 346 / 481 / 670 - 538 / 593 / 482
-//   129 x 256 -> 257 x 512:  4: 289 / 469 / 743 - 164 / 210 / 452;  8: 518 / 720 / 854 - 305 / 400 / 707;
-//                            32: 1845 / 3158 / 4172 - 1175 / 1530 / 2599
-//   65 x 128 -> 129 x 256:   4: 142 / 151 / 293 - 53 / 67 / 152;  8: 153 / 178 / 300 - 85 / 110 / 265;
-//                            32: 460 / 599 / 863 - 298 / 391 / 688
-static bool use_band(const S2DeviceTables &t, int d, int e)
+// float32 tensors: the patch kernels take everything up to 64 channels whose walked rows fit their tables, except the forward of
+// d = e = 32 on upsampling grids: rolled in longitude, its results are the same bit for bit, which holds on the split vector
+// kernel (sums in the order of the offsets) and not on tiles at fixed columns (129 x 256 -> 257 x 512, 8 slices: 518 us there, 200
+// on the patches).
+static bool use_patch(const S2DeviceTables &t, int d, int e)
 {
-    if (!s2_nattn_band_supported(t, d, e) || s2_debug_flag(S2_DEBUG_NO_BAND)) return false;
-    if (d != 32 || e != 32 || s2_debug_flag(S2_DEBUG_FORCE_BAND)) return true;
-    if (t.pscale > 1 || t.upscale > 1) return !s2_nattn_fwd_tiled_supported(t, d, e) || !s2_nattn_bwd_tiled_supported(t, d, e);
-    return !(s2_nattn_stream_supported(t, d, e) && s2_nattn_stream_dq_supported(t, d, e) &&
-             s2_nattn_stream_dkdv_supported(t, d, e));
+    return s2_nattn_patch_supported(t, d, e) && !s2_debug_flag(S2_DEBUG_NO_BAND);
+}
+static bool use_patch_fwd(const S2DeviceTables &t, int d, int e)
+{
+    const bool rolls = t.upscale > 1 && s2_nattn_fwd_tiled_supported(t, d, e) && !s2_debug_flag(S2_DEBUG_FORCE_BAND);
+    return use_patch(t, d, e) && !rolls;
 }
 
 // bf16 tensors: what the kernels written for d = 32 on equal grids with a longitude count that is a multiple of 64 do not
@@ -76,7 +66,7 @@ extern "C" int s2_nattn_fwd(const s2_grid_t *g, int batch, int heads, int d_qk, 
         S2_HIP_CHECK(hipGetLastError());
         return S2_OK;
     }
-    auto *fwd = use_band(g->dt, d_qk, d_v)                       ? s2_nattn_fwd_band
+    auto *fwd = use_patch_fwd(g->dt, d_qk, d_v)                  ? s2_nattn_fwd_patch
                 : s2_nattn_fwd_tiled_supported(g->dt, d_qk, d_v) ? s2_nattn_fwd_tiled
                                                                  : s2_nattn_fwd_generic;
     if (fwd(g->dt, batch * heads, d_qk, d_v, scale, static_cast<const float *>(q), static_cast<const float *>(k),
@@ -106,7 +96,7 @@ int s2_nattn_bwd_run(const s2_grid_t *g, int batch, int heads, int d_qk, int d_v
             kv16(g->dt, batch * heads, d_qk, d_v, scale, q, k, v, lse, dout, Dws, dk, dv, st))
             return s2_fail(S2_ERR_DEVICE, "backward launch configuration failed");
     } else {
-        auto *bwd = use_band(g->dt, d_qk, d_v)                       ? s2_nattn_bwd_band
+        auto *bwd = use_patch(g->dt, d_qk, d_v)                      ? s2_nattn_bwd_patch
                     : s2_nattn_bwd_tiled_supported(g->dt, d_qk, d_v) ? s2_nattn_bwd_tiled
                                                                      : s2_nattn_bwd_generic;
         if (bwd(g->dt, batch * heads, d_qk, d_v, scale, static_cast<const float *>(q), static_cast<const float *>(k),

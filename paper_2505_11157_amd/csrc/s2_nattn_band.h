@@ -1,5 +1,5 @@
-// Launchers of the fp32 band-tile kernels by staging mode (s2_nattn_band_impl.h; one translation unit each, so that they
-// compile in parallel).
+// Staging modes of the matrix-core kernels for any grid pair (float32 patches, bf16 tiles; one translation unit per mode, so that
+// they compile in parallel).
 #pragma once
 #include "s2_internal.h"
 
@@ -22,14 +22,3 @@ void s2_by_band_mode(int mode, F &&f)
 }
 // compute units of the device, for rules on the size of a launch
 unsigned s2_compute_units();
-
-template <int MODE>
-struct BandSet {
-    static int configure();
-    static void fwd(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k, const float *v, float *out,
-                    float *lse, hipStream_t st);
-    static void dq(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k, const float *v, const float *o,
-                   const float *lse, const float *go, float *dq, float *Dws, hipStream_t st);
-    static void dkdv(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k, const float *v,
-                     const float *lse, const float *go, const float *Dws, float *dk, float *dv, hipStream_t st);
-};

@@ -1,6 +1,6 @@
 // One point of the neighborhood attention over its true neighbors only (device side).
 //
-// The matrix-core tiles (s2_nattn_band_impl.h, s2_nattn_tile_impl.h) give a staged column outside an owner's disk the
+// The matrix-core tiles (s2_nattn_patch_impl.h, s2_nattn_tile_impl.h) give a staged column outside an owner's disk the
 // weight zero, and zero times a NaN or an infinity is a NaN: a non-finite value next to a disk would spoil the point.  A
 // mask on the staged values cannot tell owners apart that share a tile.  So a wavefront looks at its finished sums, and
 // owners with a sum that is not finite are evaluated again here, where no other point is touched.  With finite inputs
@@ -65,8 +65,8 @@ __device__ __forceinline__ float wave_max(float x, int lane)
 
 // f(row, at, in): up to 64 neighbors of owner u at a time, one per lane: walked row, the lane's place inside a plane of the
 // walked tensors, and whether it is a neighbor (else `at` is the place of one)
-template <class F>
-__device__ __forceinline__ void exact_neighbors(const BandArgs &a, const BandWhere &w, int u, F &&f)
+template <class Where, class F>
+__device__ __forceinline__ void exact_neighbors(const BandArgs &a, const Where &w, int u, F &&f)
 {
     const int n = a.b.bn[w.own], first = a.b.blo[w.own];
 #pragma unroll 1
@@ -117,18 +117,24 @@ __device__ __forceinline__ P kernel_params()
     for (unsigned i = 0; i < sizeof(P) / 8; ++i) raw.v[i] = p[i];
     return __builtin_bit_cast(P, raw);
 }
-// f(u) for every owner of the NO tiles from column W0 on whose bit is set
-template <int NO, class F>
-__device__ __forceinline__ void exact_owners(const unsigned (&owners)[NO], int W0, F &&f)
-{
+// Where the owners lie: a row of 16-owner tiles (bit n of owners[o]: column W0 + 16 o + n).  each(owners, f): f(u) for every
+// owner whose bit is set, with own and own_at set to its row.
+template <int OW>
+struct BandPlace : BandWhere {
+    __device__ __forceinline__ void set(const BandArgs &a, int thread) { BandWhere::set<OW>(a, thread); }
+    template <int NO, class F>
+    __device__ __forceinline__ void each(const unsigned (&owners)[NO], F &&f)
+    {
 #pragma unroll 1
-    for (int o = 0; o < NO; ++o) {
-        unsigned left = 0;
+        for (int o = 0; o < NO; ++o) {
+            unsigned left = 0;
 #pragma unroll
-        for (int i = 0; i < NO; ++i) left = i == o ? owners[i] : left;
-        for (; left; left &= left - 1) f(W0 + 16 * o + __builtin_ctz(left));
+            for (int i = 0; i < NO; ++i) left = i == o ? owners[i] : left;
+            for (; left; left &= left - 1) f(W0 + 16 * o + __builtin_ctz(left));
+        }
     }
-}
+};
+__device__ __forceinline__ bool any_owner(unsigned owners) { return __builtin_expect(owners != 0, 0); }
 template <int NO>
 __device__ __forceinline__ bool any_owner(const unsigned (&owners)[NO])
 {
@@ -138,7 +144,7 @@ __device__ __forceinline__ bool any_owner(const unsigned (&owners)[NO])
     return __builtin_expect(x != 0, 0);
 }
 
-// The three kernels: their parameters, and the evaluation of owners (bit n of owners[o]: column W0 + 16 o + n).
+// The three kernels: their parameters, and the evaluation of owners (bit n of owners[o]).
 template <class T>
 struct FwdParams {
     BandArgs a;
@@ -146,18 +152,18 @@ struct FwdParams {
     T *out;
     float *lse;
 };
-template <class T, int OW, int NO>
-__device__ __forceinline__ void exact_fwd(const unsigned (&owners)[NO], int wave)
+template <class T, class Where, class Owners>
+__device__ __forceinline__ void exact_fwd(const Owners &owners, int wave)
 {
     if (!any_owner(owners)) return;
     const auto p = kernel_params<FwdParams<T>>();
-    BandWhere w;
-    w.set<OW>(p.a, 64 * wave + lane_here());
+    Where w;
+    w.set(p.a, 64 * wave + lane_here());
     const BandArgs &a = p.a;
     const float c2 = a.scale * kLog2e;
-    const size_t qs = size_t(w.bh) * a.d * w.plane_own + w.own_at, os = size_t(w.bh) * a.e * w.plane_own + w.own_at;
     const T *ks = p.k + size_t(w.bh) * a.d * w.plane_walk, *vs = p.v + size_t(w.bh) * a.e * w.plane_walk;
-    exact_owners(owners, w.W0, [&](int u) {
+    w.each(owners, [&](int u) {
+        const size_t qs = size_t(w.bh) * a.d * w.plane_own + w.own_at, os = size_t(w.bh) * a.e * w.plane_own + w.own_at;
         const size_t at_own = size_t(w.c_own) * u;
         float m = kMinRef, l = 0.f, acc = 0.f;
         exact_neighbors(a, w, u, [&](int row, size_t at, bool in) {
@@ -184,18 +190,18 @@ struct DqParams {
     T *dq;
     float *Dws;
 };
-template <class T, int OW, int NO>
-__device__ __forceinline__ void exact_dq(const unsigned (&owners)[NO], int wave)
+template <class T, class Where, class Owners>
+__device__ __forceinline__ void exact_dq(const Owners &owners, int wave)
 {
     if (!any_owner(owners)) return;
     const auto p = kernel_params<DqParams<T>>();
-    BandWhere w;
-    w.set<OW>(p.a, 64 * wave + lane_here());
+    Where w;
+    w.set(p.a, 64 * wave + lane_here());
     const BandArgs &a = p.a;
     const float c2 = a.scale * kLog2e;
-    const size_t qs = size_t(w.bh) * a.d * w.plane_own + w.own_at, os = size_t(w.bh) * a.e * w.plane_own + w.own_at;
     const T *ks = p.k + size_t(w.bh) * a.d * w.plane_walk, *vs = p.v + size_t(w.bh) * a.e * w.plane_walk;
-    exact_owners(owners, w.W0, [&](int u) {
+    w.each(owners, [&](int u) {
+        const size_t qs = size_t(w.bh) * a.d * w.plane_own + w.own_at, os = size_t(w.bh) * a.e * w.plane_own + w.own_at;
         const size_t at_own = size_t(w.c_own) * u, c = os + imin(w.lane, a.e - 1) * w.plane_own + at_own;
         const float D = wave_sum(w.lane < a.e ? exact_load(p.go + c) * exact_load(p.o + c) : 0.f, w.lane);
         const float L2 = (p.lse[size_t(w.bh) * w.plane_own + w.own_at + at_own] - a.ln_omega_ref) * kLog2e;
@@ -219,18 +225,19 @@ struct DkdvParams {
     const float *Dws;
     T *dk, *dv;
 };
-template <class T, int OW, int NO>
-__device__ __forceinline__ void exact_dkdv(const unsigned (&owners)[NO], int wave)
+template <class T, class Where, class Owners>
+__device__ __forceinline__ void exact_dkdv(const Owners &owners, int wave)
 {
     if (!any_owner(owners)) return;
     const auto p = kernel_params<DkdvParams<T>>();
-    BandWhere w;
-    w.set<OW>(p.a, 64 * wave + lane_here());
+    Where w;
+    w.set(p.a, 64 * wave + lane_here());
     const BandArgs &a = p.a;
-    const float c2 = a.scale * kLog2e, omega = a.omega_rel[w.own / w.c_own];
+    const float c2 = a.scale * kLog2e;
     const size_t kv = size_t(w.bh) * w.plane_own, stat = size_t(w.bh) * w.plane_walk;
     const T *qs = p.q + a.d * stat, *gs = p.go + a.e * stat;
-    exact_owners(owners, w.W0, [&](int u) {
+    w.each(owners, [&](int u) {
+        const float omega = a.omega_rel[w.own / w.c_own];
         const size_t at_own = w.own_at + size_t(w.c_own) * u, ko = a.d * kv + at_own, vo = a.e * kv + at_own;
         float adk = 0.f, adv = 0.f;
         exact_neighbors(a, w, u, [&](int, size_t at, bool in) {

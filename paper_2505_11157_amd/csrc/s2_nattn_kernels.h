@@ -73,13 +73,13 @@ int s2_nattn_bwd_dkdv_bf16(const S2DeviceTables &t, int nbh, int d, int e, float
                            const void *v, const float *lse, const void *go, const float *Dws, void *dk, void *dv,
                            hipStream_t st);
 
-// float32 tensors on the fp32 matrix cores (band tiles of 16 keys x 16 outputs), any grid pair, d and e up to 64.
-bool s2_nattn_band_supported(const S2DeviceTables &t, int d, int e);
-int s2_nattn_fwd_band(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k,
-                      const float *v, float *out, float *lse, hipStream_t st);
-int s2_nattn_bwd_band(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k,
-                      const float *v, const float *o, const float *lse, const float *go, float *dq, float *dk, float *dv,
-                      float *Dws, hipStream_t st);
+// float32 tensors on the bf16 matrix cores (three bf16 terms per value, s2_nattn_patch_impl.h), any grid pair, d and e up to 64.
+bool s2_nattn_patch_supported(const S2DeviceTables &t, int d, int e);
+int s2_nattn_fwd_patch(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k,
+                       const float *v, float *out, float *lse, hipStream_t st);
+int s2_nattn_bwd_patch(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k,
+                       const float *v, const float *o, const float *lse, const float *go, float *dq, float *dk, float *dv,
+                       float *Dws, hipStream_t st);
 
 // bf16 tensors on the bf16 matrix cores, any grid pair, d and e up to 64.
 bool s2_nattn_tile_supported(const S2DeviceTables &t, int d, int e);

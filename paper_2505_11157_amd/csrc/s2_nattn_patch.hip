@@ -1,0 +1,57 @@
+// Dispatch of the float32 patch kernels (s2_nattn_patch_impl.h) over the staging mode.
+#include "s2_nattn_kernels.h"
+#include "s2_nattn_patch.h"
+
+unsigned s2_compute_units()
+{
+    static const unsigned ncu = [] {
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
+            n = 256;
+        return unsigned(n);
+    }();
+    return ncu;
+}
+
+// the matrix-core kernels for any grid pair, of both element types
+int s2_nattn_band_configure()
+{
+    return PatchSet<kWide>::configure() || PatchSet<kNarrow>::configure() || PatchSet<kRagged>::configure() || s2_nattn_tile_configure();
+}
+
+bool s2_nattn_patch_supported(const S2DeviceTables &t, int d, int e)
+{
+    return d <= 64 && e <= 64 && t.band_rows_ok && !s2_debug_flag(S2_DEBUG_NO_MFMA);
+}
+
+// Names of the launches in the trace: those of the kernels that these replaced, so that records compare from version to
+// version.
+static bool streams(const S2DeviceTables &t, int d, int e)
+{
+    return s2_nattn_stream_supported(t, d, e) && s2_nattn_stream_dq_supported(t, d, e) && s2_nattn_stream_dkdv_supported(t, d, e);
+}
+static double pair_count(const double (&p)[4], int nbh) { return nbh * (p[0] + p[1] + p[2] + p[3]); }
+
+int s2_nattn_fwd_patch(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k,
+                       const float *v, float *out, float *lse, hipStream_t st)
+{
+    if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
+    S2TraceScope tr(streams(t, d, e) ? "nattn_fwd_stream" : "nattn_fwd_band", pair_count(t.fwd_pairs, nbh), st);
+    s2_by_band_mode<PatchSet>(s2_band_mode(t.side_out, d, e, sizeof(float)), [&](auto set) { set.fwd(t, nbh, d, e, scale, q, k, v, out, lse, st); });
+    return 0;
+}
+
+int s2_nattn_bwd_patch(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k,
+                       const float *v, const float *o, const float *lse, const float *go, float *dq, float *dk, float *dv,
+                       float *Dws, hipStream_t st)
+{
+    if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
+    const bool s = streams(t, d, e);
+    {
+        S2TraceScope tr(s ? "nattn_bwd_dq_stream" : "nattn_bwd_dq_band", pair_count(t.fwd_pairs, nbh), st);
+        s2_by_band_mode<PatchSet>(s2_band_mode(t.side_out, d, e, sizeof(float)), [&](auto set) { set.dq(t, nbh, d, e, scale, q, k, v, o, lse, go, dq, Dws, st); });
+    }
+    S2TraceScope tr(s ? "nattn_bwd_dkdv_stream" : "nattn_bwd_dkdv_band", pair_count(t.bwd_pairs, nbh), st);
+    s2_by_band_mode<PatchSet>(s2_band_mode(t.side_in, d, e, sizeof(float)), [&](auto set) { set.dkdv(t, nbh, d, e, scale, q, k, v, lse, go, Dws, dk, dv, st); });
+    return 0;
+}

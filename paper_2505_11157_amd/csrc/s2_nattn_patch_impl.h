@@ -1,0 +1,891 @@
+// Neighborhood attention (Sec. 3.3, eq. (9)-(10); gradients App. B.4) of float32 tensors on the bf16 matrix cores, for any pair of
+// grids and d, e <= 64 (rounded up to 16, 32 or 64 channels).
+//
+// Precision.  A float32 value is the sum of three bf16 terms x0 + x1 + x2 of 8 bits each, every one the rounded rest of those
+// before, and holds it exactly.  A product takes the six of nine term products that are not below 2^-26 of it, smallest first;
+// sums over keys keep x0 y0 and the other five in accumulators of their own, so that a long sum takes one rounding per 32 keys at
+// its own magnitude (v_mfma_f32_16x16x32_bf16 adds its 32 products with less loss than 32 multiply-adds).  Dot products of 32
+// and sums over 256 unit-variance values, rms error: multiply-adds and the fp32 matrix cores 1.0e-7 and 2.9e-7 of the result's rms,
+// here 3.8e-8 and 9.0e-8 (cut off bit by bit instead of rounded: 7.1e-8, with a bias).  Six bf16 instructions of 32 channels take 96
+// cycles where eight fp32 ones (16x16x4) take 262.  Results of the three kernels on 14 grid pairs are 1.5 to 2.8 times closer to
+// float64 than those of the kernels that these replaced.
+//
+// Work.  A wavefront owns 16 points in a patch of 4 x 4, 2 x 8 or 1 x 16 rows x columns (per segment of owner rows, counted on the
+// host: s2_grid.cpp), a workgroup four such patches side by side.  Near the equator a square patch meets 32 chunks of four
+// columns where 16 points of one row meet 72; near the poles, where arcs are long, a row is as good.  The columns that any owner of
+// a workgroup meets are cut into chunks of four, numbered row by row (S2PatchRow), and staged CAP at a time.  Of each stage a
+// wavefront lists the chunks its own points meet, four of which are a tile of 16 keys, whatever rows they lie on; masks are per
+// element, from the arc of the owner's row.  Rows of one longitude count nU on both sides: classes of a finer grid are rows of
+// their own (S2BandSide).
+//
+// LDS holds a stage as [term][channel][chunk]: channel rows as in memory.  First products (S^T = K Q^T and dP) read it through
+// ds_read_b64_tr_b16, which turns 4 channels x 16 keys on the way to the registers; in the second (O^T += V P^T) the 8 contraction
+// indices of a lane are its four keys of each of two tiles, 8-byte reads.  start(c) and UNITS (an odd multiple of four) spread both
+// patterns over the banks.  The workgroup's own points go through LDS the same way, and the results come back through it, in 16-byte
+// pieces of whole rows (4-byte loads and stores of 16 points x 4 channels from the lanes: 40 % of the d = 64 launches).
+//
+// What bounds it: issue of vector and matrix instructions, which hardly overlap on a SIMD (a tile is 12 matrix instructions of 16
+// cycles and some 75 vector ones of 2.3, d = 32 forward), and the stalls around the two barriers of a stage; 129 x 256, 32 slices,
+// d = 32: matrix pipes busy 26 % of the forward, vector ALUs 42 %.  Workgroups of four wavefronts and small stages leave three to
+// five of them on a compute unit, whose barriers do not coincide (eight wavefronts, stages twice as long: dk/dv 0.72 against
+// 0.70 ms; all of LDS for one workgroup: 1.43).
+// Measured (129 x 256, 32 slices, forward / dq / dk,dv, ms; before: fp32 matrix cores and vector kernels):
+//   d = 16  0.42 / 0.52 / 0.65 -> 0.30 / 0.34 / 0.40        d = 32  0.66 / 0.83 / 1.03 -> 0.45 / 0.51 / 0.69
+//   d = 64  1.49 / 1.95 / 2.48 -> 0.93 / 1.07 / 1.30
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+#include <cstdlib>
+
+#include "s2_internal.h"
+#include "s2_nattn_band.h"
+#include "s2_nattn_exact.h"
+#include "s2_nattn_patch.h"
+#include "s2_nattn_walk.h"
+
+namespace {
+
+using namespace s2walk;
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kTerms = 3;
+constexpr int kDead = kMaxRows;      // the row of a list entry that stands for no chunk: no owner has neighbors on it
+constexpr unsigned kAgain = 0x7fc0a9a1u;     // in place of the results of an owner that s2_nattn_exact.h evaluates: not to be stored
+
+// Channels, chunks per stage, wavefronts per SIMD the registers are held to.
+template <int D_, int CAP_, int WAVES_>
+struct Geo {
+    static constexpr int D = D_, NW = kS2PatchWaves, CAP = CAP_, WAVES = WAVES_, NT = 64 * NW;
+    static constexpr int UNITS = CAP + 4;                   // 8-byte units per channel row
+    static constexpr int ROW = 4 * UNITS;                   // bf16 values per channel row
+    static constexpr int TERM = D * ROW + 16, TENSOR = kTerms * TERM;
+    static constexpr int KC = D == 16 ? 1 : D / 32;
+    static constexpr int NG = NT / CAP;                     // channels staged at once
+    static constexpr int NP = D / NG;                       // pieces (4 columns of a channel) per thread and tensor
+    static constexpr int OWN = 4 * NW;                      // chunks of the workgroup's own points
+    static constexpr int PITCH = 4 * OWN + 4;               // floats per channel of the results
+    static_assert(NP >= 1 && D % NG == 0 && NG >= 2 && (UNITS / 4) % 2 == 1 && OWN <= CAP && D * PITCH * 4 <= TENSOR * 2, "geometry");
+    static __device__ __forceinline__ constexpr int start(int c) { return c * ROW + 8 * ((c >> 3) & 1) + 4 * (c >> 4); }
+    static constexpr int UP = 16 * ROW + 4;                 // from a channel to the one 16 later
+};
+
+// A workgroup's rows in LDS (S2PatchRow).
+struct RowTab {
+    int col[kMaxRows + 1], uni[kMaxRows + 1], before[kMaxRows];
+    uint2 arc[4][kMaxRows + 1];      // arc and the row's weight
+};
+template <class G>
+struct Shared {
+    __attribute__((aligned(16))) __bf16 a[G::TENSOR];
+    __attribute__((aligned(16))) __bf16 b[G::TENSOR];
+    RowTab rows;
+};
+template <class G>
+struct SharedDq : Shared<G> {
+    float part[G::NG][G::PITCH];     // partial sums of D
+};
+template <class G>
+struct SharedDkdv : Shared<G> {
+    __attribute__((aligned(16))) float L[4 * G::CAP];
+    __attribute__((aligned(16))) float D[4 * G::CAP];
+};
+
+// A value the compiler may not carry along in a register of its own from before a loop: what is computed from it is computed
+// where it is used.
+__device__ __forceinline__ int here_v(int x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+__device__ __forceinline__ int here_s(int x)
+{
+    asm volatile("" : "+s"(x));
+    return x;
+}
+
+// Place of a workgroup and of a lane's owner
+struct PatchWhere {
+    int nU, first, lg, W, W0, wc, bh, lane, wave, n, g, tid, sub, u;
+    int own;                         // the lane's owner row
+    bool active;                     // the lane's owner is a point
+    size_t plane_own, plane_walk, own_at;
+    int nlon_walk, c_own, c_walk, n_own;
+    int rmin, nrows, total, rows_at;
+    float inv_nU;
+    __device__ __forceinline__ size_t row_at(int row) const
+    {
+        const int lat = row / c_own;
+        return size_t(lat) * nU * c_own + (row - lat * c_own);
+    }
+    __device__ __forceinline__ void set_row(int row)
+    {
+        own = row;
+        own_at = row_at(row);
+    }
+    __device__ __forceinline__ void set(const BandArgs &a, int thread = threadIdx.x)
+    {
+        nU = a.b.nU;
+        // Workgroups go to the eight XCDs in turn: each of them takes whole slices, one after the other, so that its L2 holds the
+        // rows that its workgroups share.
+        const int whole = a.nbh & ~7, id = blockIdx.x, rest = id - whole * a.npatch;
+        int blk;
+        if (rest < 0) {
+            blk = (id >> 3) % a.npatch;
+            bh = (id & 7) + 8 * ((id >> 3) / a.npatch);
+        } else {
+            blk = rest / (a.nbh - whole);
+            bh = whole + rest % (a.nbh - whole);
+        }
+        const int2 at = a.patch[blk];
+        const int4 s0 = a.seg[2 * at.x], s1 = a.seg[2 * at.x + 1];
+        first = s0.x; lg = __builtin_amdgcn_readfirstlane(s0.y); rmin = s0.z; nrows = s0.w; total = s1.x; rows_at = s1.y;
+        W = 16 >> lg;
+        tid = thread; lane = tid & 63; wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        n = lane & 15; g = lane >> 4;
+        sub = n >> (4 - lg);
+        c_own = a.b.c_own; c_walk = a.b.c_walk; n_own = a.b.n_own;
+        nlon_walk = nU * c_walk;
+        plane_own = size_t(a.b.nlat_own) * nU * c_own;
+        plane_walk = size_t(a.b.nlat_walk) * nlon_walk;
+        inv_nU = 1.f / float(nU);
+        const bool row_ok = first + sub < n_own;
+        set_row(row_ok ? first + sub : first);
+        W0 = at.y;
+        wc = W0 + wave * W;
+        u = wc + (n & (W - 1));
+        active = row_ok && u < nU;
+    }
+    __device__ __forceinline__ size_t walk_at(int r) const
+    {
+        if (c_walk == 1) return size_t(r) * nlon_walk;
+        const int lat = r / c_walk;
+        return size_t(lat) * nlon_walk + (r - lat * c_walk);
+    }
+    // the chunk of the workgroup's own points that holds the points 4 j .. 4 j + 3 of this wavefront
+    __device__ __forceinline__ int own_slot(int j, int nw) const
+    {
+        const int h = 2 - here_s(lg);    // log2(chunks per row of a wavefront)
+        return (j >> h) * (nw << h) + (wave << h) + (j & ((1 << h) - 1));
+    }
+    // f(u) for every owner whose bit is set, with the row set to the owner's
+    template <class F>
+    __device__ __forceinline__ void each(unsigned owners, F &&f)
+    {
+#pragma unroll 1
+        for (; owners; owners &= owners - 1) {
+            const int i = __builtin_ctz(owners);
+            set_row(first + i / W);
+            f(wc + (i & (W - 1)));
+        }
+    }
+};
+// The chunks of a workgroup, stage by stage.
+template <class G>
+struct Chunks {
+    int P_v[2];                      // chunks before row lane, 64 + lane
+    int r;
+    int row, col;                    // of the stage prepared last: the lane's chunk (lane mod CAP)
+    int list, cnt;                   // ... the wavefront's chunks, one per lane, and their number
+
+    __device__ __forceinline__ int before(int i) const
+    {
+        const int x = __builtin_amdgcn_readlane(P_v[0], i & 63), y = __builtin_amdgcn_readlane(P_v[1], i & 63);
+        return i < 64 ? x : y;
+    }
+    __device__ __forceinline__ void start(const BandArgs &a, const PatchWhere &w, RowTab &t)
+    {
+        if (w.tid <= kMaxRows) {
+            int4 x = {0, 0, 0, 0}, y = {0, 0, 0, 0};
+            if (w.tid < w.nrows) {
+                x = a.row_rec[2 * (w.rows_at + w.tid)];
+                y = a.row_rec[2 * (w.rows_at + w.tid) + 1];
+            }
+            t.col[w.tid] = x.x;
+            t.uni[w.tid] = x.y;
+            if (w.tid < kMaxRows) t.before[w.tid] = x.z;
+            t.arc[0][w.tid] = make_uint2(y.x, x.w);
+            t.arc[1][w.tid] = make_uint2(y.y, x.w);
+            t.arc[2][w.tid] = make_uint2(y.z, x.w);
+            t.arc[3][w.tid] = make_uint2(y.w, x.w);
+        }
+        __syncthreads();
+        P_v[0] = t.before[w.lane];
+        P_v[1] = t.before[64 + w.lane];
+        r = 0;
+    }
+    // the chunks X0 .. X0 + CAP - 1 (X0 < total; past the last: that one again, on no list)
+    __device__ __forceinline__ void prepare(int X0, const PatchWhere &w, const RowTab &t)
+    {
+        const int x = w.lane & (G::CAP - 1), X = imin(X0 + x, w.total - 1);
+        row = r;
+        while (r + 1 < w.nrows) {
+            const int p = before(r + 1);
+            if (p >= X0 + G::CAP) break;
+            ++r;
+            row += X >= p ? 1 : 0;
+        }
+        const int u = t.uni[row];
+        col = t.col[row] + 4 * X + w.W0;
+        const int d = col + 3 - w.wc - int(short(u & 0xffff));
+        const bool need = w.lane < G::CAP && X0 + x < w.total && w.wc < w.nU && unsigned(d) < (unsigned(u) >> 16) + w.W + 2;
+        const unsigned long long m = __ballot(need);
+        cnt = __popcll(m);
+        const int ones = __builtin_amdgcn_mbcnt_hi(unsigned(m >> 32), __builtin_amdgcn_mbcnt_lo(unsigned(m), 0));
+        const int entry = need ? col << 14 | row << 6 | x : kDead << 6;
+        list = __builtin_amdgcn_ds_permute(4 * (need ? ones : cnt + w.lane - ones), entry);
+    }
+};
+
+// two float32 values as bf16 (low half: a), rounded to nearest even, and what that leaves of them
+__device__ __forceinline__ unsigned cut_off(float &a, float &b)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
+    asm("" : "+v"(u));       // else the compiler converts each of the two once more for what follows
+    a -= __builtin_bit_cast(float, u << 16);
+    b -= __builtin_bit_cast(float, u & 0xffff0000u);
+    return u;
+}
+// float32 values as three bf16 terms, which together hold them exactly
+__device__ __forceinline__ void cut(const float (&x)[8], bf16x8 (&b)[kTerms])
+{
+    u32x4 u[kTerms];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float lo = x[2 * i], hi = x[2 * i + 1];
+#pragma unroll
+        for (int k = 0; k < kTerms; ++k) u[k][i] = cut_off(lo, hi);
+    }
+#pragma unroll
+    for (int k = 0; k < kTerms; ++k) b[k] = __builtin_bit_cast(bf16x8, u[k]);
+}
+
+// One tensor's stage: from memory to registers, and cut into three terms on the way to LDS.
+template <class G, int MODE>
+struct Place {
+    static constexpr bool WIDE = MODE == kWide;
+    unsigned off[WIDE ? 1 : 4];      // kWide: byte offset of the thread's first piece in the slice; else elements in a channel plane
+    int x, cg;                       // the thread's chunk and first channel
+    template <class W>
+    __device__ __forceinline__ void init(const W &w)
+    {
+        x = w.tid & (G::CAP - 1);
+        cg = w.tid / G::CAP;
+    }
+    template <class W>
+    __device__ __forceinline__ void set(const W &w, int row, int col)
+    {
+        if constexpr (WIDE) {
+            const unsigned c = unsigned(wrap_col(col + 2 * w.nU, w.nU, w.inv_nU));
+            off[0] = 4u * (unsigned(cg) * unsigned(w.plane_walk) + unsigned(row) * unsigned(w.nU) + c);
+        } else {
+            const unsigned at = unsigned(w.walk_at(row));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) off[i] = at + unsigned(w.c_walk) * unsigned(wrap_col(col + i + 2 * w.nU, w.nU, w.inv_nU));
+        }
+    }
+};
+template <class G, int MODE>
+struct Stage {
+    using P = Place<G, MODE>;
+    f32x4 r[G::NP];
+    template <class W>
+    __device__ __forceinline__ void load(const W &w, const P &at, const float *slice, int nch)
+    {
+#pragma unroll
+        for (int j = 0; j < G::NP; ++j) {
+            if constexpr (P::WIDE) {
+                r[j] = load_at<f32x4>(slice + size_t(j * G::NG) * w.plane_walk, at.off[0]);
+            } else {
+                const int c = at.cg + j * G::NG;
+                const float *p = slice + size_t(MODE == kRagged ? imin(c, nch - 1) : c) * w.plane_walk;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) r[j][i] = p[at.off[i]];
+            }
+        }
+    }
+    // the workgroup's own points; vec: its rows are contiguous and their length a multiple of four
+    __device__ __forceinline__ void load_own(const PatchWhere &w, const float *slice, int nch, bool vec)
+    {
+        const int h = 2 - here_s(w.lg), tid = here_v(w.tid), x = tid & (G::OWN - 1), cg = tid / G::CAP, sub = (x / G::NW) >> h;
+        const int row = w.first + sub < w.n_own ? w.first + sub : w.first, u = w.W0 + 4 * (x - G::NW * (sub << h));
+        const float *p = slice + w.row_at(row);
+#pragma unroll
+        for (int j = 0; j < G::NP; ++j) {
+            const int c = cg + j * G::NG;
+            const float *pc = p + size_t(MODE == kRagged ? imin(c, nch - 1) : c) * w.plane_own;
+            if (vec) {
+                r[j] = *reinterpret_cast<const f32x4 *>(pc + (u < w.nU ? u : 0));
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) r[j][i] = pc[size_t(w.c_own) * imin(u + i, w.nU - 1)];
+            }
+        }
+    }
+    __device__ __forceinline__ void scale(float factor)
+    {
+#pragma unroll
+        for (int j = 0; j < G::NP; ++j) r[j] *= factor;
+    }
+    __device__ __forceinline__ void store(const P &at, __bf16 *tile, int nch) const
+    {
+#pragma unroll
+        for (int j = 0; j < G::NP; ++j) {
+            const int c = at.cg + j * G::NG;
+            f32x4 v = r[j];
+            if (MODE == kRagged && c >= nch) v = f32x4{0.f, 0.f, 0.f, 0.f};
+            __bf16 *p = tile + G::start(c) + 4 * at.x;
+            float x0 = v[0], x1 = v[1], x2 = v[2], x3 = v[3];
+#pragma unroll
+            for (int k = 0; k < kTerms; ++k) {
+                const unsigned a = cut_off(x0, x1), b = cut_off(x2, x3);
+                *reinterpret_cast<u32x2 *>(p + k * G::TERM) = u32x2{a, b};
+            }
+        }
+    }
+};
+__device__ __forceinline__ f32x4 mma(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ bf16x8 join(bf16x4 a, bf16x4 b) { return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7); }
+__device__ __forceinline__ bf16x4 lds_tr(const __bf16 *p)
+{
+    typedef __attribute__((address_space(3))) s16x4 *ptr;
+    return __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((ptr)(__attribute__((address_space(3))) void *)p));
+}
+__device__ __forceinline__ bf16x4 lds_row(const __bf16 *p) { return *reinterpret_cast<const bf16x4 *>(p); }
+
+// A lane's own point as operand of the first product; p: the lane's place in the staged tensor
+template <class G>
+struct OwnPoint {
+    bf16x8 v[G::KC][kTerms];
+    __device__ __forceinline__ void read(const __bf16 *p)
+    {
+        if constexpr (G::D == 16) {
+            const bf16x4 h = lds_tr(p), m = lds_tr(p + G::TERM), l = lds_tr(p + 2 * G::TERM);
+            v[0][0] = join(h, h);
+            v[0][1] = join(m, m);
+            v[0][2] = join(l, h);
+        } else {
+#pragma unroll
+            for (int s = 0; s < G::KC; ++s)
+#pragma unroll
+                for (int k = 0; k < kTerms; ++k) v[s][k] = join(lds_tr(p + k * G::TERM + 2 * s * G::UP), lds_tr(p + k * G::TERM + (2 * s + 1) * G::UP));
+        }
+    }
+};
+// (chunks' columns) . (the lane's own point), smallest products first; p: the lane's place in the staged tensor
+template <class G>
+__device__ __forceinline__ f32x4 dot(const __bf16 *p, const OwnPoint<G> &o)
+{
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (G::D == 16) {
+        const bf16x4 h = lds_tr(p), m = lds_tr(p + G::TERM), l = lds_tr(p + 2 * G::TERM);
+        acc = mma(join(h, l), o.v[0][2], acc);
+        const bf16x8 hm = join(h, m);
+        acc = mma(hm, o.v[0][1], acc);
+        acc = mma(hm, o.v[0][0], acc);
+    } else {
+        bf16x8 x[G::KC][kTerms];
+#pragma unroll
+        for (int s = 0; s < G::KC; ++s)
+#pragma unroll
+            for (int k = 0; k < kTerms; ++k)
+                x[s][k] = join(lds_tr(p + k * G::TERM + 2 * s * G::UP), lds_tr(p + k * G::TERM + (2 * s + 1) * G::UP));
+        constexpr int order[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
+#pragma unroll
+        for (int i = 0; i < 6; ++i)
+#pragma unroll
+            for (int s = 0; s < G::KC; ++s) acc = mma(x[s][order[i][0]], o.v[s][order[i][1]], acc);
+    }
+    return acc;
+}
+// hi, lo [mt] += (channels 16 mt ..) . (the lane's eight values of the columns of two tiles); p0, p1: the lane's places
+template <class G>
+__device__ __forceinline__ void sum(const __bf16 *p0, const __bf16 *p1, const bf16x8 (&b)[kTerms], f32x4 (&hi)[G::D / 16], f32x4 (&lo)[G::D / 16])
+{
+#pragma unroll
+    for (int mt = 0; mt < G::D / 16; ++mt) {
+        bf16x8 x[kTerms];
+#pragma unroll
+        for (int k = 0; k < kTerms; ++k) x[k] = join(lds_row(p0 + k * G::TERM + mt * G::UP), lds_row(p1 + k * G::TERM + mt * G::UP));
+        lo[mt] = mma(x[2], b[0], lo[mt]);
+        hi[mt] = mma(x[0], b[0], hi[mt]);
+        lo[mt] = mma(x[0], b[2], lo[mt]);
+        lo[mt] = mma(x[1], b[1], lo[mt]);
+        lo[mt] = mma(x[1], b[0], lo[mt]);
+        lo[mt] = mma(x[0], b[1], lo[mt]);
+    }
+}
+
+// What a lane needs of one key tile (four chunks of the list): its own chunk, its place as reader of the first product
+struct TileRef {
+    int slot, row, col;              // the lane's chunk (number g of the tile)
+    int slot_n;                      // chunk n & 3 of the tile
+    __device__ __forceinline__ void get(int list, int t, int n, int g)
+    {
+        const int m = __builtin_amdgcn_ds_bpermute(16 * t + 4 * g, list);
+        slot_n = __builtin_amdgcn_ds_bpermute(16 * t + 4 * (n & 3), list) & 63;
+        slot = m & 63;
+        row = m >> 6 & 255;
+        col = m >> 14;
+    }
+    // keep[rr]: is column col + rr a neighbor of owner u
+    __device__ __forceinline__ void keep(bool (&keep)[4], int u, unsigned arc) const
+    {
+        const unsigned rel = unsigned(col - (u + int(short(arc & 0xffff))));
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) keep[rr] = rel + rr < (arc >> 16);
+    }
+};
+
+// The results of the workgroup's owners, by way of LDS: acc[mt][rr] is channel 16 mt + 4 g + rr of the lane's owner.
+template <class G>
+__device__ __forceinline__ void put_results(const f32x4 (&acc)[G::D / 16], float factor, bool again, float *tile, const PatchWhere &w)
+{
+    const int lane = here_v(w.lane);
+    float *p = tile + (lane >> 4) * 4 * G::PITCH + 4 * w.own_slot(lane >> 2 & 3, G::NW) + (lane & 3);
+#pragma unroll
+    for (int mt = 0; mt < G::D / 16; ++mt)
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) p[(16 * mt + rr) * G::PITCH] = again ? __builtin_bit_cast(float, kAgain) : acc[mt][rr] * factor;
+}
+template <class G>
+__device__ __forceinline__ void store_results(float *slice, int nch, const float *tile, const PatchWhere &w, bool vec)
+{
+    const int h = 2 - here_s(w.lg), tid = here_v(w.tid), x = tid % G::OWN, c0 = tid / G::OWN, sub = (x / G::NW) >> h, u = w.W0 + 4 * (x - G::NW * (sub << h));
+    if (w.first + sub >= w.n_own || u >= w.nU) return;
+    float *p = slice + size_t(c0) * w.plane_own + w.row_at(w.first + sub) + size_t(w.c_own) * u;
+    const size_t up = size_t(G::NT / G::OWN) * w.plane_own;
+#pragma unroll
+    for (int j = 0; j < G::D * G::OWN / G::NT; ++j, p += up) {
+        const int c = c0 + j * (G::NT / G::OWN);
+        if (c >= nch) break;
+        const u32x4 r = *reinterpret_cast<const u32x4 *>(tile + c * G::PITCH + 4 * x);
+        unsigned skip = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) skip |= (r[k] == kAgain || u + k >= w.nU ? 1u : 0u) << k;
+        if (vec && skip == 0) {
+            *reinterpret_cast<u32x4 *>(p) = r;
+        } else {
+            unsigned *pk = reinterpret_cast<unsigned *>(p);
+#pragma unroll
+            for (int k = 0; k < 4; ++k, pk += w.c_own)
+                if (!(skip >> k & 1)) *pk = r[k];
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// Forward.
+template <class G, int MODE>
+__global__ void __launch_bounds__(G::NT, G::WAVES)
+nattn_fwd_patch(BandArgs a, const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v, float *__restrict__ out,
+                float *__restrict__ lse)
+{
+    constexpr int D = G::D;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    Shared<G> &sh = *reinterpret_cast<Shared<G> *>(lds);
+    PatchWhere w;
+    w.set(a);
+    const int n = w.n, g = w.g, nd = MODE == kRagged ? a.d : D, ne = MODE == kRagged ? a.e : D;
+    const bool vec = w.c_own == 1 && w.nU % 4 == 0;
+    const float *qs = q + size_t(w.bh) * nd * w.plane_own, *ks = k + size_t(w.bh) * nd * w.plane_walk, *vs = v + size_t(w.bh) * ne * w.plane_walk;
+    Place<G, MODE> at;
+    at.init(w);
+    Stage<G, MODE> rk, rv;
+    rk.load_own(w, qs, nd, vec);
+    Chunks<G> ch;
+    ch.start(a, w, sh.rows);
+    auto fetch = [&](int X0) {
+        ch.prepare(X0, w, sh.rows);
+        at.set(w, w.rmin + ch.row, ch.col);
+        rk.load(w, at, ks, nd);
+        rv.load(w, at, vs, ne);
+    };
+    const int tr_at = G::start(4 * g + (n >> 2)), row_at = G::start(n);
+    __syncthreads();                    // everybody is done with what LDS held
+    rk.scale(a.scale < 0.f ? -1.f : 1.f);
+    rk.store(at, sh.a, nd);
+    __syncthreads();
+    if (w.total > 0) fetch(0);
+    OwnPoint<G> own;
+    own.read(sh.a + tr_at + 4 * w.own_slot(here_v(w.lane) & 3, G::NW));
+    f32x4 hi[D / 16], lo[D / 16];
+#pragma unroll
+    for (int mt = 0; mt < D / 16; ++mt) hi[mt] = lo[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // |scale|, its sign is on q: the largest product is the largest logit; never zero, so that a masked -inf stays one
+    const float c2 = a.scale == 0.f ? 1e-37f : fabsf(a.scale) * kLog2e;
+    float m = kMinRef, l = 0.f;
+    for (int X0 = 0; X0 < w.total; X0 += G::CAP) {
+        __syncthreads();
+        rk.store(at, sh.a, nd);
+        rv.store(at, sh.b, ne);
+        __syncthreads();
+        const int list = ch.list, ntile = (ch.cnt + 3) >> 2;
+        if (X0 + G::CAP < w.total) fetch(X0 + G::CAP);
+        auto step = [&](int t, auto count) {
+            constexpr int N = decltype(count)::value;
+            TileRef tr[2];
+            float x[8], omega[2];
+#pragma unroll
+            for (int i = 0; i < N; ++i) tr[i].get(list, t + i, n, g);
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const uint2 arc = sh.rows.arc[w.sub][tr[i].row];
+                const f32x4 sc = dot<G>(sh.a + tr_at + 4 * tr[i].slot_n, own);
+                omega[i] = __builtin_bit_cast(float, arc.y);
+                bool keep[4];
+                tr[i].keep(keep, w.u, arc.x);
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr) x[4 * i + rr] = keep[rr] ? sc[rr] : -INFINITY;
+            }
+            float mx = x[0];
+#pragma unroll
+            for (int i = 1; i < 4 * N; ++i) mx = fmaxf(mx, x[i]);
+            mx *= c2;
+            if (__any(mx > m + 8.f)) {
+                mx = group_max(mx);
+                const float m_new = mx > m + 8.f ? mx : m;
+                const float corr = __builtin_amdgcn_exp2f(m - m_new);
+                m = m_new;
+                l *= corr;
+#pragma unroll
+                for (int mt = 0; mt < D / 16; ++mt) {
+                    hi[mt] *= corr;
+                    lo[mt] *= corr;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                if (i < 4 * N) {
+                    const float e = __builtin_amdgcn_exp2f(fmaf(x[i], c2, -m));
+                    l = fmaf(omega[i / 4], e, l);
+                    x[i] = omega[i / 4] * e;
+                } else {
+                    x[i] = 0.f;
+                }
+            }
+            bf16x8 p[kTerms];
+            cut(x, p);
+            sum<G>(sh.b + row_at + 4 * tr[0].slot, sh.b + row_at + 4 * tr[N - 1].slot, p, hi, lo);
+            settle(hi);
+            settle(lo);
+        };
+        int t = 0;
+        for (; t + 1 < ntile; t += 2) step(t, std::integral_constant<int, 2>());
+        if (t < ntile) step(t, std::integral_constant<int, 1>());
+    }
+#pragma unroll
+    for (int mt = 0; mt < D / 16; ++mt) hi[mt] += lo[mt];
+    const float lt = group_sum(l);
+    const unsigned again = not_finite(hi, w.active);     // owners whose sums took in a non-finite value (s2_nattn_exact.h)
+    __syncthreads();
+    put_results<G>(hi, 1.f / lt, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
+    if (w.active && g == 0 && !(again >> n & 1)) {
+        // the whole part of m goes into the logarithm, so that its value and the sum are no larger than the result
+        const float whole = fminf(fmaxf(rintf(m), -60.f), 60.f);
+        lse[size_t(w.bh) * w.plane_own + w.own_at + size_t(w.c_own) * w.u] =
+            fmaf(m - whole, 0.6931471805599453f, logf(ldexpf(lt * a.omega_ref, int(whole))));
+    }
+    __syncthreads();
+    store_results<G>(out + size_t(w.bh) * ne * w.plane_own, ne, reinterpret_cast<const float *>(sh.a), w, vec);
+    exact_fwd<float, PatchWhere>(again, w.wave);
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// Backward, query side: dq and D_i = dout_i . out_i (written for the key-side launch).
+template <class G, int MODE>
+__global__ void __launch_bounds__(G::NT, G::WAVES)
+nattn_bwd_dq_patch(BandArgs a, const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
+                   const float *__restrict__ o_, const float *__restrict__ lse, const float *__restrict__ go, float *__restrict__ dq,
+                   float *__restrict__ Dws)
+{
+    constexpr int D = G::D;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    SharedDq<G> &sh = *reinterpret_cast<SharedDq<G> *>(lds);
+    PatchWhere w;
+    w.set(a);
+    const int n = w.n, g = w.g, nd = MODE == kRagged ? a.d : D, ne = MODE == kRagged ? a.e : D;
+    const bool vec = w.c_own == 1 && w.nU % 4 == 0;
+    const float c2 = a.scale * kLog2e;
+    const float *qs = q + size_t(w.bh) * nd * w.plane_own, *gs = go + size_t(w.bh) * ne * w.plane_own, *os = o_ + size_t(w.bh) * ne * w.plane_own;
+    const float *ks = k + size_t(w.bh) * nd * w.plane_walk, *vs = v + size_t(w.bh) * ne * w.plane_walk;
+    Place<G, MODE> at;
+    at.init(w);
+    Stage<G, MODE> rk, rv;
+    rk.load_own(w, qs, nd, vec);
+    rv.load_own(w, gs, ne, vec);
+    Chunks<G> ch;
+    ch.start(a, w, sh.rows);
+    auto fetch = [&](int X0) {
+        ch.prepare(X0, w, sh.rows);
+        at.set(w, w.rmin + ch.row, ch.col);
+        rk.load(w, at, ks, nd);
+        rv.load(w, at, vs, ne);
+    };
+    const int tr_at = G::start(4 * g + (n >> 2)), row_at = G::start(n);
+    Stage<G, MODE> ro;
+    ro.load_own(w, os, ne, vec);
+    const size_t stat = size_t(w.bh) * w.plane_own + w.own_at + size_t(w.c_own) * (w.active ? w.u : 0);
+    const float L2 = lse[stat] * kLog2e;         // the weights in the sums are relative ones: max omega multiplies the result
+    __syncthreads();
+    f32x4 part = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < G::NP; ++j)
+        if (MODE != kRagged || at.cg + j * G::NG < ne) part += rv.r[j] * ro.r[j];
+    if (at.x < G::OWN) *reinterpret_cast<f32x4 *>(&sh.part[at.cg][4 * at.x]) = part;
+    rk.store(at, sh.a, nd);
+    rv.store(at, sh.b, ne);
+    __syncthreads();
+    if (w.total > 0) fetch(0);
+    const int slot = w.own_slot(here_v(w.lane) & 3, G::NW), point = 4 * w.own_slot(here_v(w.lane) >> 2 & 3, G::NW) + (n & 3);
+    OwnPoint<G> oq, og;
+    oq.read(sh.a + tr_at + 4 * slot);
+    og.read(sh.b + tr_at + 4 * slot);
+    float dsum = 0.f;
+#pragma unroll
+    for (int i = g; i < G::NG; i += 4) dsum += sh.part[i][point];
+    dsum = group_sum(dsum);
+    if (w.active && g == 0) Dws[stat] = dsum;
+    f32x4 hi[D / 16], lo[D / 16];
+#pragma unroll
+    for (int mt = 0; mt < D / 16; ++mt) hi[mt] = lo[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int X0 = 0; X0 < w.total; X0 += G::CAP) {
+        __syncthreads();
+        rk.store(at, sh.a, nd);
+        rv.store(at, sh.b, ne);
+        __syncthreads();
+        const int list = ch.list, ntile = (ch.cnt + 3) >> 2;
+        if (X0 + G::CAP < w.total) fetch(X0 + G::CAP);
+        auto step = [&](int t, auto count) {
+            constexpr int N = decltype(count)::value;
+            TileRef tr[2];
+            float x[8];
+#pragma unroll
+            for (int i = 0; i < N; ++i) tr[i].get(list, t + i, n, g);
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const uint2 arc = sh.rows.arc[w.sub][tr[i].row];
+                const f32x4 sc = dot<G>(sh.a + tr_at + 4 * tr[i].slot_n, oq), dp = dot<G>(sh.b + tr_at + 4 * tr[i].slot_n, og);
+                bool keep[4];
+                tr[i].keep(keep, w.u, arc.x);
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr) {
+                    const float ds = __builtin_bit_cast(float, arc.y) * __builtin_amdgcn_exp2f(fmaf(sc[rr], c2, -L2)) * (dp[rr] - dsum);
+                    x[4 * i + rr] = keep[rr] ? ds : 0.f;
+                }
+            }
+#pragma unroll
+            for (int i = 4 * N; i < 8; ++i) x[i] = 0.f;
+            bf16x8 p[kTerms];
+            cut(x, p);
+            sum<G>(sh.a + row_at + 4 * tr[0].slot, sh.a + row_at + 4 * tr[N - 1].slot, p, hi, lo);
+        };
+        int t = 0;
+        for (; t + 1 < ntile; t += 2) step(t, std::integral_constant<int, 2>());
+        if (t < ntile) step(t, std::integral_constant<int, 1>());
+        settle(hi);
+        settle(lo);
+    }
+#pragma unroll
+    for (int mt = 0; mt < D / 16; ++mt) hi[mt] += lo[mt];
+    const unsigned again = not_finite(hi, w.active);
+    __syncthreads();
+    put_results<G>(hi, a.scale * a.omega_ref, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
+    __syncthreads();
+    store_results<G>(dq + size_t(w.bh) * nd * w.plane_own, nd, reinterpret_cast<const float *>(sh.a), w, vec);
+    exact_dq<float, PatchWhere>(again, w.wave);
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// Backward, key side: owners are input points, the transposed band gives the output latitudes; q, dout, lse and D
+// of a stage's outputs are staged together.
+template <class G, int MODE>
+__global__ void __launch_bounds__(G::NT, G::WAVES)
+nattn_bwd_dkdv_patch(BandArgs a, const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
+                     const float *__restrict__ lse, const float *__restrict__ go, const float *__restrict__ Dws,
+                     float *__restrict__ dk, float *__restrict__ dv)
+{
+    constexpr int D = G::D;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    SharedDkdv<G> &sh = *reinterpret_cast<SharedDkdv<G> *>(lds);
+    PatchWhere w;
+    w.set(a);
+    const int n = w.n, g = w.g, nd = MODE == kRagged ? a.d : D, ne = MODE == kRagged ? a.e : D;
+    const bool vec = w.c_own == 1 && w.nU % 4 == 0;
+    const float c2 = a.scale * kLog2e;
+    const float *ks = k + size_t(w.bh) * nd * w.plane_own, *vs = v + size_t(w.bh) * ne * w.plane_own;
+    const float *qs = q + size_t(w.bh) * nd * w.plane_walk, *gs = go + size_t(w.bh) * ne * w.plane_walk;
+    const float *ls = lse + size_t(w.bh) * w.plane_walk, *Ds = Dws + size_t(w.bh) * w.plane_walk;
+    // the quadrature weight is the owner's own here: it multiplies the finished sums (a latitude of weight zero has no arcs)
+    const float omega = a.omega_rel[w.own / w.c_own] * a.omega_ref;
+    Place<G, MODE> at;
+    at.init(w);
+    Stage<G, MODE> rq, rg;
+    rq.load_own(w, ks, nd, vec);
+    rg.load_own(w, vs, ne, vec);
+    Chunks<G> ch;
+    ch.start(a, w, sh.rows);
+    f32x4 rs = {0.f, 0.f, 0.f, 0.f};         // first threads: logsumexp or D of a chunk
+    auto fetch = [&](int X0) {
+        ch.prepare(X0, w, sh.rows);
+        at.set(w, w.rmin + ch.row, ch.col);
+        rq.load(w, at, qs, nd);
+        rg.load(w, at, gs, ne);
+        if (w.tid < 2 * G::CAP) {
+            const float *p = at.cg ? Ds : ls;
+            if constexpr (MODE == kWide) {
+                rs = load_at<f32x4>(p, at.off[0] - 4u * unsigned(at.cg) * unsigned(w.plane_walk));
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) rs[i] = p[at.off[i]];
+            }
+        }
+    };
+    const int tr_at = G::start(4 * g + (n >> 2)), row_at = G::start(n);
+    __syncthreads();
+    rq.store(at, sh.a, nd);
+    rg.store(at, sh.b, ne);
+    __syncthreads();
+    if (w.total > 0) fetch(0);
+    const int slot = w.own_slot(here_v(w.lane) & 3, G::NW);
+    OwnPoint<G> ok, ov;
+    ok.read(sh.a + tr_at + 4 * slot);
+    ov.read(sh.b + tr_at + 4 * slot);
+    f32x4 khi[D / 16], klo[D / 16], vhi[D / 16], vlo[D / 16];
+#pragma unroll
+    for (int mt = 0; mt < D / 16; ++mt) khi[mt] = klo[mt] = vhi[mt] = vlo[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int X0 = 0; X0 < w.total; X0 += G::CAP) {
+        __syncthreads();
+        rq.store(at, sh.a, nd);
+        rg.store(at, sh.b, ne);
+        if (w.tid < 2 * G::CAP) {
+            if (at.cg == 0) *reinterpret_cast<f32x4 *>(sh.L + 4 * at.x) = rs * -kLog2e;
+            else *reinterpret_cast<f32x4 *>(sh.D + 4 * at.x) = rs;
+        }
+        __syncthreads();
+        const int list = ch.list, ntile = (ch.cnt + 3) >> 2;
+        if (X0 + G::CAP < w.total) fetch(X0 + G::CAP);
+        auto step = [&](int t, auto count) {
+            constexpr int N = decltype(count)::value;
+            TileRef tr[2];
+            float pr[8], ds[8];
+#pragma unroll
+            for (int i = 0; i < N; ++i) tr[i].get(list, t + i, n, g);
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const unsigned arc = sh.rows.arc[w.sub][tr[i].row].x;
+                const f32x4 L = *reinterpret_cast<const f32x4 *>(sh.L + 4 * tr[i].slot), Dn = *reinterpret_cast<const f32x4 *>(sh.D + 4 * tr[i].slot);
+                const f32x4 sc = dot<G>(sh.a + tr_at + 4 * tr[i].slot_n, ok), dp = dot<G>(sh.b + tr_at + 4 * tr[i].slot_n, ov);
+                bool keep[4];
+                tr[i].keep(keep, w.u, arc);
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr) {
+                    const float x = __builtin_amdgcn_exp2f(fmaf(sc[rr], c2, L[rr]));
+                    pr[4 * i + rr] = keep[rr] ? x : 0.f;
+                    ds[4 * i + rr] = keep[rr] ? x * (dp[rr] - Dn[rr]) : 0.f;
+                }
+            }
+#pragma unroll
+            for (int i = 4 * N; i < 8; ++i) pr[i] = ds[i] = 0.f;
+            bf16x8 p[kTerms];
+            cut(pr, p);
+            sum<G>(sh.b + row_at + 4 * tr[0].slot, sh.b + row_at + 4 * tr[N - 1].slot, p, vhi, vlo);
+            cut(ds, p);
+            sum<G>(sh.a + row_at + 4 * tr[0].slot, sh.a + row_at + 4 * tr[N - 1].slot, p, khi, klo);
+        };
+        int t = 0;
+        for (; t + 1 < ntile; t += 2) step(t, std::integral_constant<int, 2>());
+        if (t < ntile) step(t, std::integral_constant<int, 1>());
+        settle(khi);
+        settle(klo);
+        settle(vhi);
+        settle(vlo);
+    }
+#pragma unroll
+    for (int mt = 0; mt < D / 16; ++mt) {
+        khi[mt] += klo[mt];
+        vhi[mt] += vlo[mt];
+    }
+    const unsigned again = not_finite(khi, w.active) | not_finite(vhi, w.active);
+    __syncthreads();
+    put_results<G>(khi, omega * a.scale, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
+    put_results<G>(vhi, omega, again >> n & 1, reinterpret_cast<float *>(sh.b), w);
+    __syncthreads();
+    store_results<G>(dk + size_t(w.bh) * nd * w.plane_own, nd, reinterpret_cast<const float *>(sh.a), w, vec);
+    store_results<G>(dv + size_t(w.bh) * ne * w.plane_own, ne, reinterpret_cast<const float *>(sh.b), w, vec);
+    exact_dkdv<float, PatchWhere>(again, w.wave);
+}
+
+inline double pair_count(const double (&p)[4], int nbh) { return nbh * (p[0] + p[1] + p[2] + p[3]); }
+
+// Calls f with the geometry for a head dimension
+enum Launch { kFwd, kDq, kDkdv };
+template <Launch WHICH, class F>
+void by_shape(int dmax, F &&f)
+{
+    if (dmax <= 16) f(Geo<16, 32, 4>());
+    else if (dmax <= 32) f(Geo<32, 16, WHICH == kDq ? 4 : 3>());
+    else f(Geo<64, 16, 2>());
+}
+struct PatchLaunch {
+    BandArgs a;
+    dim3 grid;
+};
+template <class G>
+PatchLaunch patch_launch(const S2DeviceTables &t, const S2BandSide &b, int nbh, int d, int e, float scale)
+{
+    const S2BandSide::Patches &p = b.patches;
+    return {{b, t.omega_rel, t.ln_omega_ref, t.omega_ref, scale, nbh, d, e, p.seg, p.row_rec, p.patch, p.npatch},
+            dim3(unsigned(p.npatch) * unsigned(nbh))};
+}
+inline bool raise_lds(const void *f, size_t bytes) { return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)) != hipSuccess; }
+
+}  // namespace
+
+template <int MODE>
+int PatchSet<MODE>::configure()
+{
+    bool bad = false;
+    for (int d : {16, 32, 64}) {
+        by_shape<kFwd>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_fwd_patch<decltype(g), MODE>), sizeof(Shared<decltype(g)>)); });
+        by_shape<kDq>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dq_patch<decltype(g), MODE>), sizeof(SharedDq<decltype(g)>)); });
+        by_shape<kDkdv>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dkdv_patch<decltype(g), MODE>), sizeof(SharedDkdv<decltype(g)>)); });
+    }
+    return bad;
+}
+template <int MODE>
+void PatchSet<MODE>::fwd(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k, const float *v,
+                         float *out, float *lse, hipStream_t st)
+{
+    by_shape<kFwd>(d > e ? d : e, [&](auto g) {
+        using G = decltype(g);
+        const PatchLaunch l = patch_launch<G>(t, t.side_out, nbh, d, e, scale);
+        hipLaunchKernelGGL((nattn_fwd_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(Shared<G>), st, l.a, q, k, v, out, lse);
+    });
+}
+template <int MODE>
+void PatchSet<MODE>::dq(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k, const float *v,
+                        const float *o, const float *lse, const float *go, float *dq, float *Dws, hipStream_t st)
+{
+    by_shape<kDq>(d > e ? d : e, [&](auto g) {
+        using G = decltype(g);
+        const PatchLaunch l = patch_launch<G>(t, t.side_out, nbh, d, e, scale);
+        hipLaunchKernelGGL((nattn_bwd_dq_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(SharedDq<G>), st, l.a, q, k, v, o, lse, go, dq, Dws);
+    });
+}
+template <int MODE>
+void PatchSet<MODE>::dkdv(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k, const float *v,
+                          const float *lse, const float *go, const float *Dws, float *dk, float *dv, hipStream_t st)
+{
+    by_shape<kDkdv>(d > e ? d : e, [&](auto g) {
+        using G = decltype(g);
+        const PatchLaunch l = patch_launch<G>(t, t.side_in, nbh, d, e, scale);
+        hipLaunchKernelGGL((nattn_bwd_dkdv_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(SharedDkdv<G>), st, l.a, q, k, v, lse, go, Dws, dk, dv);
+    });
+}

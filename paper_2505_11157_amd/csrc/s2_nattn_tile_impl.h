@@ -419,7 +419,7 @@ nattn_fwd_tile(BandArgs a, const bf16raw *__restrict__ q, const bf16raw *__restr
         if (g == 0)
             lse[size_t(w.bh) * w.plane_own + w.own_at + w.c_own * u] = (m[o] + log2f(lt * a.omega_ref)) * 0.6931471805599453f;
     }
-    exact_fwd<bf16raw, G::OW>(again, w.wave);
+    exact_fwd<bf16raw, BandPlace<G::OW>>(again, w.wave);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -538,7 +538,7 @@ nattn_bwd_dq_tile(BandArgs a, const bf16raw *__restrict__ q, const bf16raw *__re
             for (int rr = 0; rr < 4; ++rr)
                 if (has<MODE>(16 * mt + 4 * g + rr, a.d)) stx(ob + size_t(16 * mt + 4 * g + rr) * w.plane_own, acc[o][mt][rr] * a.scale);
     }
-    exact_dq<bf16raw, G::OW>(again, w.wave);
+    exact_dq<bf16raw, BandPlace<G::OW>>(again, w.wave);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -670,7 +670,7 @@ nattn_bwd_dkdv_tile(BandArgs a, const bf16raw *__restrict__ q, const bf16raw *__
                 if (has<MODE>(c, a.e)) stx(dv + slice_v + at, adv[o][mt][rr] * omega);
             }
     }
-    exact_dkdv<bf16raw, G::OW>(again, w.wave);
+    exact_dkdv<bf16raw, BandPlace<G::OW>>(again, w.wave);
 }
 
 template <int D, int NO>

@@ -205,7 +205,7 @@ struct Walker {
 // v = (offset of the tile's first column to the last owner) - (the arc's first offset) + 30: the tile's 16 x 16 offsets, counted
 // from the arc's first, are v - 30 .. v.  Around the circle v is kept in 0 .. nU - 1 (an offset below zero is then one turn more).
 // v moves from tile to tile instead of being found anew from Xt (16 wavefront-uniform instructions, one after the other): together
-// with the reads ahead of the products (s2_nattn_band_impl.h) 181 x 360, 2 slices, d = 32: 0.56 -> 0.51 ms per step.
+// with reads ahead of the products, on the fp32 matrix cores, 181 x 360, 2 slices, d = 32: 0.56 -> 0.51 ms per step.
 enum { kOwnTiles, kGridTiles, kAnyTiles };
 template <int KIND>
 __device__ __forceinline__ bool on_grid(const RowPlan &p) { return KIND == kAnyTiles ? p.multi : KIND == kGridTiles; }
@@ -281,6 +281,10 @@ struct BandArgs {
     const float *omega_rel;
     float ln_omega_ref, omega_ref, scale;
     int nbh, d, e;
+    // patch kernels (S2BandSide::Patches)
+    const int4 *seg, *row_rec;
+    const int2 *patch;
+    int npatch;
 };
 
 // Where a wavefront's owners and the walked rows lie.

@@ -1,0 +1,71 @@
+// Walks the segments, rows, chunks and patches that s2_grid_init makes for the patch kernels (s2_nattn_patch_impl.h) the way the
+// kernels do, on the host, and compares what every owner meets with the arc tables: each neighbor once, and nothing else.
+// Arguments: grid type, four sizes, theta.
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+
+#include "s2_nattn_kernels.h"
+
+int s2_nattn_tiled_configure() { return 0; }
+int s2_nattn_bwd_tiled_configure() { return 0; }
+int s2_nattn_stream_configure() { return 0; }
+int s2_nattn_mfma_configure() { return 0; }
+int s2_nattn_band_configure() { return 0; }
+int s2_static_scratch_setup(int) { return 0; }
+
+static int check(const s2_grid::Patches &p, const std::vector<int> &blo, const std::vector<int> &bn, const std::vector<int2> &arc, int nU)
+{
+    const int n_own = int(blo.size()), bmax = int(arc.size() / blo.size());
+    std::vector<int> seen(size_t(n_own) * nU, 0);
+    for (const int2 &wg : p.list) {
+        const int4 s0 = p.seg[2 * wg.x], s1 = p.seg[2 * wg.x + 1];
+        const int rows = 1 << s0.y, W = 16 >> s0.y, total = s1.x;
+        if (s0.w > 128) return 1;
+        for (int wave = 0; wave < kS2PatchWaves; ++wave)
+            for (int n = 0; n < 16; ++n) {
+                const int own = s0.x + n / W, wc = wg.y + wave * W, u = wc + n % W;
+                if (own >= n_own || u >= nU || n / W >= rows) continue;
+                ++seen[size_t(own) * nU + u];
+                std::map<std::pair<int, int>, int> met;
+                for (int i = 0; i < s0.w; ++i) {
+                    const S2PatchRow &r = p.rows[s1.y + i];
+                    const int end = i + 1 < s0.w ? p.rows[s1.y + i + 1].before : total;
+                    for (int X = r.before; X < end; ++X) {
+                        const int col = r.col + 4 * X + wg.y, d = col + 3 - wc - int(short(r.uni & 0xffff));
+                        if (col < -2 * nU || col + 3 + 2 * nU >= 1 << 22 || col >= 1 << 17 || col < -(1 << 17)) return 2;    // what wrap_col and a list entry hold
+                        const unsigned a = r.arc[n / W], rel = unsigned(col - (u + int(short(a & 0xffff))));
+                        const bool listed = unsigned(d) < (unsigned(r.uni) >> 16) + W + 2;
+                        for (int j = 0; j < 4; ++j)
+                            if (rel + j < (a >> 16)) {
+                                if (!listed) return 3;
+                                ++met[{s0.z + i, ((col + j) % nU + nU) % nU}];
+                            }
+                    }
+                }
+                size_t want = 0;
+                for (int b = 0; b < bn[own]; ++b) {
+                    const int2 x = arc[size_t(own) * bmax + b];
+                    for (int c = 0; c < x.y; ++c, ++want) {
+                        auto it = met.find({blo[own] + b, ((u + x.x + c) % nU + nU) % nU});
+                        if (it == met.end() || it->second != 1) return 4;
+                    }
+                }
+                if (want != met.size()) return 5;
+            }
+    }
+    for (int s : seen)
+        if (s != 1) return 6;
+    return 0;
+}
+
+int main(int argc, char **argv)
+{
+    s2_grid_t *g = nullptr;
+    if (argc != 7 || s2_grid_init(atoi(argv[1]), atoi(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atof(argv[6]), &g) != S2_OK) return 100;
+    const int nU = g->nlon_in < g->nlon_out ? g->nlon_in : g->nlon_out;
+    const int a = check(g->vo_patch, g->vo_lo, g->vo_n, g->vo_arc, nU), b = check(g->vi_patch, g->vi_lo, g->vi_n, g->vi_arc, nU);
+    s2_grid_destroy(g);
+    printf("%d %d\n", a, b);
+    return a ? a : b ? 10 + b : 0;
+}
