@@ -120,6 +120,7 @@ struct PatchWhere {
     float inv_nU;
     __device__ __forceinline__ size_t row_at(int row) const
     {
+        if (c_own == 1) return size_t(row) * nU;
         const int lat = row / c_own;
         return size_t(lat) * nU * c_own + (row - lat * c_own);
     }
@@ -185,13 +186,16 @@ struct PatchWhere {
         }
     }
 };
-// The chunks of a workgroup, stage by stage.
+// The chunks of a workgroup: looked up 64 at a time, one per lane, and staged CAP at a time.
 template <class G>
 struct Chunks {
     int P_v[2];                      // chunks before row lane, 64 + lane
     int r;
-    int row, col;                    // of the stage prepared last: the lane's chunk (lane mod CAP)
-    int list, cnt;                   // ... the wavefront's chunks, one per lane, and their number
+    int entry;                       // of the 64 looked up last: the lane's chunk, its column, row and place in its stage
+    int list;                        // ... those that the wavefront's points meet, in order
+    unsigned long long met;          // ... which they are
+    int row, col;                    // of the stage set last: the chunk that the thread stages
+    int first, cnt;                  // ... where the list has its chunks, and how many
 
     __device__ __forceinline__ int before(int i) const
     {
@@ -219,26 +223,34 @@ struct Chunks {
         P_v[1] = t.before[64 + w.lane];
         r = 0;
     }
-    // the chunks X0 .. X0 + CAP - 1 (X0 < total; past the last: that one again, on no list)
-    __device__ __forceinline__ void prepare(int X0, const PatchWhere &w, const RowTab &t)
+    // the chunks X0 .. X0 + 63 (X0 < total; past the last: that one again, not met)
+    __device__ __forceinline__ void look(int X0, const PatchWhere &w, const RowTab &t)
     {
-        const int x = w.lane & (G::CAP - 1), X = imin(X0 + x, w.total - 1);
-        row = r;
+        const int X = imin(X0 + w.lane, w.total - 1);
+        int at = r;
         while (r + 1 < w.nrows) {
             const int p = before(r + 1);
-            if (p >= X0 + G::CAP) break;
+            if (p >= X0 + 64) break;
             ++r;
-            row += X >= p ? 1 : 0;
+            at += X >= p ? 1 : 0;
         }
-        const int u = t.uni[row];
-        col = t.col[row] + 4 * X + w.W0;
-        const int d = col + 3 - w.wc - int(short(u & 0xffff));
-        const bool need = w.lane < G::CAP && X0 + x < w.total && w.wc < w.nU && unsigned(d) < (unsigned(u) >> 16) + w.W + 2;
-        const unsigned long long m = __ballot(need);
-        cnt = __popcll(m);
-        const int ones = __builtin_amdgcn_mbcnt_hi(unsigned(m >> 32), __builtin_amdgcn_mbcnt_lo(unsigned(m), 0));
-        const int entry = need ? col << 14 | row << 6 | x : kDead << 6;
-        list = __builtin_amdgcn_ds_permute(4 * (need ? ones : cnt + w.lane - ones), entry);
+        const int u = t.uni[at], c = t.col[at] + 4 * X + w.W0, d = c + 3 - w.wc - int(short(u & 0xffff));
+        const bool need = X0 + w.lane < w.total && w.wc < w.nU && unsigned(d) < (unsigned(u) >> 16) + w.W + 2;
+        met = __ballot(need);
+        const int ones = __builtin_amdgcn_mbcnt_hi(unsigned(met >> 32), __builtin_amdgcn_mbcnt_lo(unsigned(met), 0));
+        entry = c << 14 | at << 6 | (w.lane & (G::CAP - 1));
+        list = __builtin_amdgcn_ds_permute(4 * (need ? ones : __popcll(met) + w.lane - ones), entry);
+    }
+    // the stage of chunks X0 .. X0 + CAP - 1
+    __device__ __forceinline__ void set(int X0, const PatchWhere &w, const RowTab &t)
+    {
+        const int sh = X0 & 63;
+        if (sh == 0) look(X0, w, t);
+        const int e = __builtin_amdgcn_ds_bpermute(4 * (sh + (w.lane & (G::CAP - 1))), entry);
+        row = e >> 6 & 255;
+        col = e >> 14;
+        first = __popcll(met & ((1ull << sh) - 1));
+        cnt = __popcll(met >> sh & ((1ull << G::CAP) - 1));
     }
 };
 
@@ -426,12 +438,13 @@ __device__ __forceinline__ void sum(const __bf16 *p0, const __bf16 *p1, const bf
 struct TileRef {
     int slot, row, col;              // the lane's chunk (number g of the tile)
     int slot_n;                      // chunk n & 3 of the tile
-    __device__ __forceinline__ void get(int list, int t, int n, int g)
+    // the tile's chunks are entries at .. at + 3 of the list, those below end
+    __device__ __forceinline__ void get(int list, int at, int end, int n, int g)
     {
-        const int m = __builtin_amdgcn_ds_bpermute(16 * t + 4 * g, list);
-        slot_n = __builtin_amdgcn_ds_bpermute(16 * t + 4 * (n & 3), list) & 63;
+        const int m = __builtin_amdgcn_ds_bpermute(4 * (at + g), list);
+        slot_n = __builtin_amdgcn_ds_bpermute(4 * (at + (n & 3)), list) & 63;
         slot = m & 63;
-        row = m >> 6 & 255;
+        row = at + g < end ? m >> 6 & 255 : kDead;
         col = m >> 14;
     }
     // keep[rr]: is column col + rr a neighbor of owner u
@@ -502,7 +515,7 @@ nattn_fwd_patch(BandArgs a, const float *__restrict__ q, const float *__restrict
     Chunks<G> ch;
     ch.start(a, w, sh.rows);
     auto fetch = [&](int X0) {
-        ch.prepare(X0, w, sh.rows);
+        ch.set(X0, w, sh.rows);
         at.set(w, w.rmin + ch.row, ch.col);
         rk.load(w, at, ks, nd);
         rv.load(w, at, vs, ne);
@@ -526,14 +539,14 @@ nattn_fwd_patch(BandArgs a, const float *__restrict__ q, const float *__restrict
         rk.store(at, sh.a, nd);
         rv.store(at, sh.b, ne);
         __syncthreads();
-        const int list = ch.list, ntile = (ch.cnt + 3) >> 2;
+        const int list = ch.list, first = ch.first, end = ch.first + ch.cnt, ntile = (ch.cnt + 3) >> 2;
         if (X0 + G::CAP < w.total) fetch(X0 + G::CAP);
         auto step = [&](int t, auto count) {
             constexpr int N = decltype(count)::value;
             TileRef tr[2];
             float x[8], omega[2];
 #pragma unroll
-            for (int i = 0; i < N; ++i) tr[i].get(list, t + i, n, g);
+            for (int i = 0; i < N; ++i) tr[i].get(list, first + 4 * (t + i), end, n, g);
 #pragma unroll
             for (int i = 0; i < N; ++i) {
                 const uint2 arc = sh.rows.arc[w.sub][tr[i].row];
@@ -623,7 +636,7 @@ nattn_bwd_dq_patch(BandArgs a, const float *__restrict__ q, const float *__restr
     Chunks<G> ch;
     ch.start(a, w, sh.rows);
     auto fetch = [&](int X0) {
-        ch.prepare(X0, w, sh.rows);
+        ch.set(X0, w, sh.rows);
         at.set(w, w.rmin + ch.row, ch.col);
         rk.load(w, at, ks, nd);
         rv.load(w, at, vs, ne);
@@ -660,14 +673,14 @@ nattn_bwd_dq_patch(BandArgs a, const float *__restrict__ q, const float *__restr
         rk.store(at, sh.a, nd);
         rv.store(at, sh.b, ne);
         __syncthreads();
-        const int list = ch.list, ntile = (ch.cnt + 3) >> 2;
+        const int list = ch.list, first = ch.first, end = ch.first + ch.cnt, ntile = (ch.cnt + 3) >> 2;
         if (X0 + G::CAP < w.total) fetch(X0 + G::CAP);
         auto step = [&](int t, auto count) {
             constexpr int N = decltype(count)::value;
             TileRef tr[2];
             float x[8];
 #pragma unroll
-            for (int i = 0; i < N; ++i) tr[i].get(list, t + i, n, g);
+            for (int i = 0; i < N; ++i) tr[i].get(list, first + 4 * (t + i), end, n, g);
 #pragma unroll
             for (int i = 0; i < N; ++i) {
                 const uint2 arc = sh.rows.arc[w.sub][tr[i].row];
@@ -733,7 +746,7 @@ nattn_bwd_dkdv_patch(BandArgs a, const float *__restrict__ q, const float *__res
     ch.start(a, w, sh.rows);
     f32x4 rs = {0.f, 0.f, 0.f, 0.f};         // first threads: logsumexp or D of a chunk
     auto fetch = [&](int X0) {
-        ch.prepare(X0, w, sh.rows);
+        ch.set(X0, w, sh.rows);
         at.set(w, w.rmin + ch.row, ch.col);
         rq.load(w, at, qs, nd);
         rg.load(w, at, gs, ne);
@@ -769,14 +782,14 @@ nattn_bwd_dkdv_patch(BandArgs a, const float *__restrict__ q, const float *__res
             else *reinterpret_cast<f32x4 *>(sh.D + 4 * at.x) = rs;
         }
         __syncthreads();
-        const int list = ch.list, ntile = (ch.cnt + 3) >> 2;
+        const int list = ch.list, first = ch.first, end = ch.first + ch.cnt, ntile = (ch.cnt + 3) >> 2;
         if (X0 + G::CAP < w.total) fetch(X0 + G::CAP);
         auto step = [&](int t, auto count) {
             constexpr int N = decltype(count)::value;
             TileRef tr[2];
             float pr[8], ds[8];
 #pragma unroll
-            for (int i = 0; i < N; ++i) tr[i].get(list, t + i, n, g);
+            for (int i = 0; i < N; ++i) tr[i].get(list, first + 4 * (t + i), end, n, g);
 #pragma unroll
             for (int i = 0; i < N; ++i) {
                 const unsigned arc = sh.rows.arc[w.sub][tr[i].row].x;
