@@ -286,10 +286,16 @@ static void build_patches(const std::vector<int> &blo, const std::vector<int> &b
         for (int f = 4 * s; f < std::min(4 * s + 4, n_own); f += 1 << lg) {
             const int l = std::min(f + (1 << lg), n_own);
             walk(f, l, rmin, rows);
-            int before = 0;
-            const int at = int(p.rows.size());
+            int before = 0, at = int(p.rows.size()), part = 0;
             for (size_t i = 0; i < rows.size(); ++i) {
                 Row &r = rows[i];
+                if (i == size_t(part) + kS2PatchRows) {
+                    p.seg.push_back(make_int4(f, lg, rmin + part, kS2PatchRows));
+                    p.seg.push_back(make_int4(before, at, 1, 0));
+                    part = int(i);
+                    at = int(p.rows.size());
+                    before = 0;
+                }
                 bool always = once && r.any;
                 for (int k = 0; k < l - f; ++k) {
                     always &= r.own[k].y >= nU;
@@ -313,7 +319,7 @@ static void build_patches(const std::vector<int> &blo, const std::vector<int> &b
                 p.rows.push_back(o);
                 before += !r.any ? 0 : always ? nU / 4 : (OW + r.hi - c0 + 3) / 4;
             }
-            p.seg.push_back(make_int4(f, lg, rows.empty() ? 0 : rmin, int(rows.size())));
+            p.seg.push_back(make_int4(f, lg, rows.empty() ? 0 : rmin + part, int(rows.size()) - part));
             p.seg.push_back(make_int4(before, at, 0, 0));
         }
     }
@@ -322,7 +328,8 @@ static void build_patches(const std::vector<int> &blo, const std::vector<int> &b
     for (int k = 0; k < ngrp; ++k) {
         const int s = (k & 1) ? ngrp - 1 - (k >> 1) : k >> 1;                          // the polar rows are the heaviest
         for (int t = seg_of[s]; t < seg_of[s + 1]; ++t)
-            for (int c = 0; c < nU; c += kS2PatchWaves * (16 >> shape[s])) p.list.push_back(make_int2(t, c));
+            if (t == seg_of[s] || p.seg[2 * t - 1].z == 0)                             // else a further part of the one before
+                for (int c = 0; c < nU; c += kS2PatchWaves * (16 >> shape[s])) p.list.push_back(make_int2(t, c));
     }
 }
 
@@ -741,57 +748,8 @@ extern "C" int s2_grid_init(int grid_type, int nlat_in, int nlon_in, int nlat_ou
     stream_plan(nlat_in, g->tband_lo, g->tband_n, g->tcnt, g->tband_max, g->dt.tst_lo, g->dt.tst_hi, g->dt.tst_nw,
                 g->tst_cum);
 
-    // light range for the bf16 band-tile kernels: the latitudes of the last class must be one contiguous range with
-    // odd arcs of at most 57 offsets (a 128-column stage then holds the window of 64 owners on every band row), and
-    // the bands of four consecutive latitudes together span at most 64 rows (a workgroup keeps one row per lane)
-    auto light_range = [](int n_rows, const std::vector<int> &blo, const std::vector<int> &n, const std::vector<int> &tab,
-                          int bmax, int &lo, int &hi) {
-        lo = hi = 0;
-        int first = -1, last = -1, count = 0;
-        for (int r = 0; r < n_rows; ++r) {
-            long work = 0;
-            for (int b = 0; b < n[r]; ++b) work += tab[size_t(r) * bmax + b];
-            if (work > T) continue;
-            if (first < 0) first = r;
-            last = r;
-            ++count;
-        }
-        if (count == 0 || last - first + 1 != count) return;
-        for (int r = first; r <= last; ++r) {
-            if (n[r] < 1) return;
-            for (int b = 0; b < n[r]; ++b) {
-                const int c = tab[size_t(r) * bmax + b];
-                if (c < 1 || c > 57 || c % 2 == 0) return;
-            }
-        }
-        for (int f = first; f <= last; f += 4) {
-            int rmin = 1 << 30, rmax = -1;
-            for (int r = f; r <= std::min(f + 3, last); ++r) {
-                rmin = std::min(rmin, blo[r]);
-                rmax = std::max(rmax, blo[r] + n[r] - 1);
-            }
-            if (rmax - rmin + 1 > 64) return;
-        }
-        lo = first;
-        hi = last + 1;
-    };
-    light_range(nlat_out, g->band_lo, g->band_n, g->cnt, g->band_max, g->dt.bl_lo, g->dt.bl_hi);
-    light_range(nlat_in, g->tband_lo, g->tband_n, g->tcnt, g->tband_max, g->dt.tbl_lo, g->dt.tbl_hi);
-
     build_sides(g);
-    auto rows_ok = [](const std::vector<int> &lo, const std::vector<int> &n) {
-        for (size_t f = 0; f < lo.size(); f += 4) {
-            int rmin = 1 << 30, rmax = -1;
-            for (size_t r = f; r < std::min(f + 4, lo.size()); ++r)
-                if (n[r] > 0) {
-                    rmin = std::min(rmin, lo[r]);
-                    rmax = std::max(rmax, lo[r] + n[r] - 1);
-                }
-            if (rmax - rmin + 1 > 128) return false;
-        }
-        return true;
-    };
-    g->dt.band_rows_ok = rows_ok(g->vo_lo, g->vo_n) && rows_ok(g->vi_lo, g->vi_n) && std::min(nlon_in, nlon_out) < 32768;
+    g->dt.band_rows_ok = std::min(nlon_in, nlon_out) < 32768;
     if (g->dt.band_rows_ok) {
         const double most = *std::max_element(g->omega_in.begin(), g->omega_in.end());
         std::vector<float> omega(nlat_in);

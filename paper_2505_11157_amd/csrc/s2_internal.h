@@ -26,7 +26,7 @@ struct S2BandSide {
     int nlat_own, nlat_walk;
     // the patch kernels (s2_nattn_patch_impl.h)
     struct Patches {
-        const int4 *seg;      // 2 per segment: (first owner row, log2(owner rows), first walked row, walked rows), (chunks, place in row_rec, -, -)
+        const int4 *seg;      // 2 per segment: (first owner row, log2(owner rows), first walked row, walked rows), (chunks, place in row_rec, another part follows, -)
         const int4 *row_rec;  // 2 per walked row of a segment: S2PatchRow
         const int2 *patch;    // workgroups of a slice, heaviest first: segment, first column
         int npatch;
@@ -36,6 +36,7 @@ struct S2BandSide {
 // A walked row as the owners of a segment see it.  The columns that any of a workgroup's owners meets on it are cut into chunks
 // of four; the chunks of all rows are numbered in order.  Columns are relative to the workgroup's first.
 constexpr int kS2PatchWaves = 4;         // wavefronts of a workgroup
+constexpr int kS2PatchRows = 128;        // walked rows of a part of a segment
 struct S2PatchRow {
     int col;                  // first column of chunk X of the row = col + 4 X
     int uni;                  // union of the owner rows' arcs: first offset (16 bits), length (16 bits)
@@ -70,13 +71,8 @@ struct S2DeviceTables {
     // tst_*: the same for input latitudes and the transposed bands.
     int st_lo, st_hi, st_nw;
     int tst_lo, tst_hi, tst_nw;
-    // bf16 band-tile kernels, light variant: contiguous range [bl_lo, bl_hi) of output latitudes of the last class whose
-    // arcs are all odd and at most 57 offsets long (0, 0 if the light latitudes do not have that structure);
-    // tbl_*: the same for input latitudes and the transposed bands.
-    int bl_lo, bl_hi, tbl_lo, tbl_hi;
     S2BandSide side_out, side_in;       // owners = output points, owners = input points
-    // the tile kernels apply: on both sides the walked rows of any four consecutive owner rows 4 s .. 4 s + 3 span at most
-    // 128 rows (a workgroup keeps two rows per lane), and nU < 2^15
+    // the patch kernels apply: nU < 2^15
     int band_rows_ok;
     unsigned *dev_flags;      // one word in device memory: bit 0 = a bounded wait inside a kernel ran out
     const int *st_cum;        // [st_hi - st_lo + 1]   running cost of the light latitudes (for equal-work segments)
@@ -168,7 +164,6 @@ int s2_nattn_bwd_tiled_configure();
 int s2_nattn_stream_configure();
 int s2_nattn_mfma_configure();
 int s2_nattn_band_configure();
-int s2_nattn_tile_configure();
 
 // great-circle angle between two points given by their colatitudes and their difference in longitude (float64)
 double s2_great_circle(double colat_a, double colat_b, double dphi);

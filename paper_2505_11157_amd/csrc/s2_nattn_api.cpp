@@ -27,7 +27,7 @@ extern "C" size_t s2_nattn_bwd_workspace_bytes(const s2_grid_t *g, int batch, in
     return size_t(batch) * heads * g->nlat_out * g->nlon_out * sizeof(float);
 }
 
-// float32 tensors: the patch kernels take everything up to 64 channels whose walked rows fit their tables, except the forward of
+// The patch kernels take everything up to 64 channels whose walked rows fit their tables, except the float32 forward of
 // d = e = 32 on upsampling grids: rolled in longitude, its results are the same bit for bit, which holds on the split vector
 // kernel (sums in the order of the offsets) and not on tiles at fixed columns (129 x 256 -> 257 x 512, 8 slices: 518 us there, 200
 // on the patches).
@@ -41,13 +41,6 @@ static bool use_patch_fwd(const S2DeviceTables &t, int d, int e)
     return use_patch(t, d, e) && !rolls;
 }
 
-// bf16 tensors: what the kernels written for d = 32 on equal grids with a longitude count that is a multiple of 64 do not
-// cover goes to the tile kernels for any grid pair.
-static bool tile_bf16(const S2DeviceTables &t, int d, int e)
-{
-    return s2_nattn_tile_supported(t, d, e) && !s2_debug_flag(S2_DEBUG_NO_BAND);
-}
-
 extern "C" int s2_nattn_fwd(const s2_grid_t *g, int batch, int heads, int d_qk, int d_v, int dtype, float scale,
                             const void *q, const void *k, const void *v, void *out, float *lse, void *hip_stream)
 {
@@ -58,9 +51,7 @@ extern "C" int s2_nattn_fwd(const s2_grid_t *g, int batch, int heads, int d_qk, 
         return s2_fail(S2_ERR_INVALID_ARG, "tensor pointers must be 16-byte aligned");
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     if (dtype == S2_BF16) {
-        auto *fwd16 = s2_nattn_bf16_supported(g->dt, d_qk, d_v) ? s2_nattn_fwd_bf16
-                      : tile_bf16(g->dt, d_qk, d_v)             ? s2_nattn_fwd_tile_bf16
-                                                                : s2_nattn_fwd_generic_bf16;
+        auto *fwd16 = use_patch(g->dt, d_qk, d_v) ? s2_nattn_fwd_patch_bf16 : s2_nattn_fwd_generic_bf16;
         if (fwd16(g->dt, batch * heads, d_qk, d_v, scale, q, k, v, out, lse, st))
             return s2_fail(S2_ERR_DEVICE, "forward launch configuration failed");
         S2_HIP_CHECK(hipGetLastError());
@@ -89,9 +80,9 @@ int s2_nattn_bwd_run(const s2_grid_t *g, int batch, int heads, int d_qk, int d_v
         misaligned(dq) || misaligned(dk) || misaligned(dv))
         return s2_fail(S2_ERR_INVALID_ARG, "tensor pointers must be 16-byte aligned");
     if (dtype == S2_BF16) {
-        const bool fast = s2_nattn_bf16_supported(g->dt, d_qk, d_v), tile = !fast && tile_bf16(g->dt, d_qk, d_v);
-        auto *dq16 = fast ? s2_nattn_bwd_dq_bf16 : tile ? s2_nattn_bwd_dq_tile_bf16 : s2_nattn_bwd_dq_generic_bf16;
-        auto *kv16 = fast ? s2_nattn_bwd_dkdv_bf16 : tile ? s2_nattn_bwd_dkdv_tile_bf16 : s2_nattn_bwd_dkdv_generic_bf16;
+        const bool patch = use_patch(g->dt, d_qk, d_v);
+        auto *dq16 = patch ? s2_nattn_bwd_dq_patch_bf16 : s2_nattn_bwd_dq_generic_bf16;
+        auto *kv16 = patch ? s2_nattn_bwd_dkdv_patch_bf16 : s2_nattn_bwd_dkdv_generic_bf16;
         if (dq16(g->dt, batch * heads, d_qk, d_v, scale, q, k, v, out, lse, dout, dq, Dws, st) ||
             kv16(g->dt, batch * heads, d_qk, d_v, scale, q, k, v, lse, dout, Dws, dk, dv, st))
             return s2_fail(S2_ERR_DEVICE, "backward launch configuration failed");

@@ -1,5 +1,4 @@
-// Staging modes of the matrix-core kernels for any grid pair (float32 patches, bf16 tiles; one translation unit per mode, so that
-// they compile in parallel).
+// Staging modes of the patch kernels.
 #pragma once
 #include "s2_internal.h"
 

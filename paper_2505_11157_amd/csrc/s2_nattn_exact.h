@@ -1,6 +1,6 @@
 // One point of the neighborhood attention over its true neighbors only (device side).
 //
-// The matrix-core tiles (s2_nattn_patch_impl.h, s2_nattn_tile_impl.h) give a staged column outside an owner's disk the
+// The matrix-core tiles (s2_nattn_patch_impl.h) give a staged column outside an owner's disk the
 // weight zero, and zero times a NaN or an infinity is a NaN: a non-finite value next to a disk would spoil the point.  A
 // mask on the staged values cannot tell owners apart that share a tile.  So a wavefront looks at its finished sums, and
 // owners with a sum that is not finite are evaluated again here, where no other point is touched.  With finite inputs
@@ -117,33 +117,7 @@ __device__ __forceinline__ P kernel_params()
     for (unsigned i = 0; i < sizeof(P) / 8; ++i) raw.v[i] = p[i];
     return __builtin_bit_cast(P, raw);
 }
-// Where the owners lie: a row of 16-owner tiles (bit n of owners[o]: column W0 + 16 o + n).  each(owners, f): f(u) for every
-// owner whose bit is set, with own and own_at set to its row.
-template <int OW>
-struct BandPlace : BandWhere {
-    __device__ __forceinline__ void set(const BandArgs &a, int thread) { BandWhere::set<OW>(a, thread); }
-    template <int NO, class F>
-    __device__ __forceinline__ void each(const unsigned (&owners)[NO], F &&f)
-    {
-#pragma unroll 1
-        for (int o = 0; o < NO; ++o) {
-            unsigned left = 0;
-#pragma unroll
-            for (int i = 0; i < NO; ++i) left = i == o ? owners[i] : left;
-            for (; left; left &= left - 1) f(W0 + 16 * o + __builtin_ctz(left));
-        }
-    }
-};
 __device__ __forceinline__ bool any_owner(unsigned owners) { return __builtin_expect(owners != 0, 0); }
-template <int NO>
-__device__ __forceinline__ bool any_owner(const unsigned (&owners)[NO])
-{
-    unsigned x = 0;
-#pragma unroll
-    for (int i = 0; i < NO; ++i) x |= owners[i];
-    return __builtin_expect(x != 0, 0);
-}
-
 // The three kernels: their parameters, and the evaluation of owners (bit n of owners[o]).
 template <class T>
 struct FwdParams {
@@ -152,8 +126,8 @@ struct FwdParams {
     T *out;
     float *lse;
 };
-template <class T, class Where, class Owners>
-__device__ __forceinline__ void exact_fwd(const Owners &owners, int wave)
+template <class T, class Where>
+__device__ __forceinline__ void exact_fwd(unsigned owners, int wave)
 {
     if (!any_owner(owners)) return;
     const auto p = kernel_params<FwdParams<T>>();
@@ -190,8 +164,8 @@ struct DqParams {
     T *dq;
     float *Dws;
 };
-template <class T, class Where, class Owners>
-__device__ __forceinline__ void exact_dq(const Owners &owners, int wave)
+template <class T, class Where>
+__device__ __forceinline__ void exact_dq(unsigned owners, int wave)
 {
     if (!any_owner(owners)) return;
     const auto p = kernel_params<DqParams<T>>();
@@ -225,8 +199,8 @@ struct DkdvParams {
     const float *Dws;
     T *dk, *dv;
 };
-template <class T, class Where, class Owners>
-__device__ __forceinline__ void exact_dkdv(const Owners &owners, int wave)
+template <class T, class Where>
+__device__ __forceinline__ void exact_dkdv(unsigned owners, int wave)
 {
     if (!any_owner(owners)) return;
     const auto p = kernel_params<DkdvParams<T>>();

@@ -61,18 +61,6 @@ int s2_nattn_bwd_dkdv_stream(const S2DeviceTables &t, int nbh, float scale, cons
                              const float *v, const float *lse, const float *go, const float *Dws, float *dk, float *dv,
                              hipStream_t st);
 
-// bf16 tensors on the bf16 matrix cores (band tiles of 16 keys x 16 outputs, float32 softmax and accumulation): equal
-// grids, d = e = 32, longitude count a multiple of 64.
-bool s2_nattn_bf16_supported(const S2DeviceTables &t, int d, int e);
-int s2_nattn_fwd_bf16(const S2DeviceTables &t, int nbh, int d, int e, float scale, const void *q, const void *k,
-                      const void *v, void *out, float *lse, hipStream_t st);
-int s2_nattn_bwd_dq_bf16(const S2DeviceTables &t, int nbh, int d, int e, float scale, const void *q, const void *k,
-                         const void *v, const void *o, const float *lse, const void *go, void *dq, float *Dws,
-                         hipStream_t st);
-int s2_nattn_bwd_dkdv_bf16(const S2DeviceTables &t, int nbh, int d, int e, float scale, const void *q, const void *k,
-                           const void *v, const float *lse, const void *go, const float *Dws, void *dk, void *dv,
-                           hipStream_t st);
-
 // float32 tensors on the bf16 matrix cores (three bf16 terms per value, s2_nattn_patch_impl.h), any grid pair, d and e up to 64.
 bool s2_nattn_patch_supported(const S2DeviceTables &t, int d, int e);
 int s2_nattn_fwd_patch(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k,
@@ -81,14 +69,13 @@ int s2_nattn_bwd_patch(const S2DeviceTables &t, int nbh, int d, int e, float sca
                        const float *v, const float *o, const float *lse, const float *go, float *dq, float *dk, float *dv,
                        float *Dws, hipStream_t st);
 
-// bf16 tensors on the bf16 matrix cores, any grid pair, d and e up to 64.
-bool s2_nattn_tile_supported(const S2DeviceTables &t, int d, int e);
-int s2_nattn_fwd_tile_bf16(const S2DeviceTables &t, int nbh, int d, int e, float scale, const void *q, const void *k,
+// The same of bf16 tensors.
+int s2_nattn_fwd_patch_bf16(const S2DeviceTables &t, int nbh, int d, int e, float scale, const void *q, const void *k,
                            const void *v, void *out, float *lse, hipStream_t st);
-int s2_nattn_bwd_dq_tile_bf16(const S2DeviceTables &t, int nbh, int d, int e, float scale, const void *q, const void *k,
+int s2_nattn_bwd_dq_patch_bf16(const S2DeviceTables &t, int nbh, int d, int e, float scale, const void *q, const void *k,
                               const void *v, const void *o, const float *lse, const void *go, void *dq, float *Dws,
                               hipStream_t st);
-int s2_nattn_bwd_dkdv_tile_bf16(const S2DeviceTables &t, int nbh, int d, int e, float scale, const void *q, const void *k,
+int s2_nattn_bwd_dkdv_patch_bf16(const S2DeviceTables &t, int nbh, int d, int e, float scale, const void *q, const void *k,
                                 const void *v, const float *lse, const void *go, const float *Dws, void *dk, void *dv,
                                 hipStream_t st);
 

@@ -1,4 +1,4 @@
-// Dispatch of the float32 patch kernels (s2_nattn_patch_impl.h) over the staging mode.
+// Dispatch of the patch kernels (s2_nattn_patch_impl.h) over the staging mode.
 #include "s2_nattn_kernels.h"
 #include "s2_nattn_patch.h"
 
@@ -16,7 +16,8 @@ unsigned s2_compute_units()
 // the matrix-core kernels for any grid pair, of both element types
 int s2_nattn_band_configure()
 {
-    return PatchSet<kWide>::configure() || PatchSet<kNarrow>::configure() || PatchSet<kRagged>::configure() || s2_nattn_tile_configure();
+    return PatchSet<kWide>::configure() || PatchSet<kNarrow>::configure() || PatchSet<kRagged>::configure() || PatchSet16<kWide>::configure() ||
+           PatchSet16<kNarrow>::configure() || PatchSet16<kRagged>::configure();
 }
 
 bool s2_nattn_patch_supported(const S2DeviceTables &t, int d, int e)
@@ -53,5 +54,43 @@ int s2_nattn_bwd_patch(const S2DeviceTables &t, int nbh, int d, int e, float sca
     }
     S2TraceScope tr(s ? "nattn_bwd_dkdv_stream" : "nattn_bwd_dkdv_band", pair_count(t.bwd_pairs, nbh), st);
     s2_by_band_mode<PatchSet>(s2_band_mode(t.side_in, d, e, sizeof(float)), [&](auto set) { set.dkdv(t, nbh, d, e, scale, q, k, v, lse, go, Dws, dk, dv, st); });
+    return 0;
+}
+
+// (names, as above)
+static bool was_fast(const S2DeviceTables &t, int d, int e)
+{
+    return d == 32 && e == 32 && t.nlat_in == t.nlat_out && t.nlon_in == t.nlon_out && t.nlon_in % 64 == 0;
+}
+static const unsigned short *in16(const void *p) { return static_cast<const unsigned short *>(p); }
+
+int s2_nattn_fwd_patch_bf16(const S2DeviceTables &t, int nbh, int d, int e, float scale, const void *q, const void *k, const void *v,
+                            void *out, float *lse, hipStream_t st)
+{
+    if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
+    S2TraceScope tr(was_fast(t, d, e) ? "nattn_fwd_bf16" : "nattn_fwd_tile", pair_count(t.fwd_pairs, nbh), st);
+    s2_by_band_mode<PatchSet16>(s2_band_mode(t.side_out, d, e, 2), [&](auto set) {
+        set.fwd(t, nbh, d, e, scale, in16(q), in16(k), in16(v), static_cast<unsigned short *>(out), lse, st);
+    });
+    return 0;
+}
+int s2_nattn_bwd_dq_patch_bf16(const S2DeviceTables &t, int nbh, int d, int e, float scale, const void *q, const void *k, const void *v,
+                               const void *o, const float *lse, const void *go, void *dq, float *Dws, hipStream_t st)
+{
+    if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
+    S2TraceScope tr(was_fast(t, d, e) ? "nattn_bwd_dq_bf16" : "nattn_bwd_dq_tile", pair_count(t.fwd_pairs, nbh), st);
+    s2_by_band_mode<PatchSet16>(s2_band_mode(t.side_out, d, e, 2), [&](auto set) {
+        set.dq(t, nbh, d, e, scale, in16(q), in16(k), in16(v), in16(o), lse, in16(go), static_cast<unsigned short *>(dq), Dws, st);
+    });
+    return 0;
+}
+int s2_nattn_bwd_dkdv_patch_bf16(const S2DeviceTables &t, int nbh, int d, int e, float scale, const void *q, const void *k, const void *v,
+                                 const float *lse, const void *go, const float *Dws, void *dk, void *dv, hipStream_t st)
+{
+    if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
+    S2TraceScope tr(was_fast(t, d, e) ? "nattn_bwd_dkdv_bf16" : "nattn_bwd_dkdv_tile", pair_count(t.bwd_pairs, nbh), st);
+    s2_by_band_mode<PatchSet16>(s2_band_mode(t.side_in, d, e, 2), [&](auto set) {
+        set.dkdv(t, nbh, d, e, scale, in16(q), in16(k), in16(v), lse, in16(go), Dws, static_cast<unsigned short *>(dk), static_cast<unsigned short *>(dv), st);
+    });
     return 0;
 }

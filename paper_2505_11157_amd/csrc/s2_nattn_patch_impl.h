@@ -1,5 +1,5 @@
-// Neighborhood attention (Sec. 3.3, eq. (9)-(10); gradients App. B.4) of float32 tensors on the bf16 matrix cores, for any pair of
-// grids and d, e <= 64 (rounded up to 16, 32 or 64 channels).
+// Neighborhood attention (Sec. 3.3, eq. (9)-(10); gradients App. B.4) of float32 and bf16 tensors on the bf16 matrix cores, for any
+// pair of grids and d, e <= 64 (rounded up to 16, 32 or 64 channels).
 //
 // Precision.  A float32 value is the sum of three bf16 terms x0 + x1 + x2 of 8 bits each, every one the rounded rest of those
 // before, and holds it exactly.  A product takes the six of nine term products that are not below 2^-26 of it, smallest first;
@@ -32,6 +32,12 @@
 // Measured (129 x 256, 32 slices, forward / dq / dk,dv, ms; before: fp32 matrix cores and vector kernels):
 //   d = 16  0.42 / 0.52 / 0.65 -> 0.30 / 0.34 / 0.40        d = 32  0.66 / 0.83 / 1.03 -> 0.45 / 0.51 / 0.69
 //   d = 64  1.49 / 1.95 / 2.48 -> 0.93 / 1.07 / 1.30
+//
+// bf16 tensors are one term; probabilities and dS, which multiply them, are cut into three, so that every product is the float32
+// one (share of `out` and dv that are not the correctly rounded result: 1e-4 to 4e-4; with two terms 2e-3).  Before, bf16 tiles
+// of one row; d = 32 on 64 n longitudes: kernels that rounded the forward's probabilities to bf16:
+//   d = 16  0.29 / 0.34 / 0.41 -> 0.20 / 0.21 / 0.27        d = 32  0.28 / 0.35 / 0.51 -> 0.24 / 0.26 / 0.34
+//   d = 64  0.83 / 1.17 / 1.12 -> 0.42 / 0.47 / 0.56
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -53,18 +59,22 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kTerms = 3;
+typedef unsigned short bf16raw;      // storage of a bf16 tensor
+constexpr int kTerms = 3;            // bf16 terms of a float32 value
 constexpr int kDead = kMaxRows;      // the row of a list entry that stands for no chunk: no owner has neighbors on it
 constexpr unsigned kAgain = 0x7fc0a9a1u;     // in place of the results of an owner that s2_nattn_exact.h evaluates: not to be stored
 
 // Channels, chunks per stage, wavefronts per SIMD the registers are held to.
-template <int D_, int CAP_, int WAVES_>
+template <class T_, int D_, int CAP_, int WAVES_>
 struct Geo {
+    using T = T_;
+    static constexpr int TERMS = sizeof(T) == 4 ? kTerms : 1;
     static constexpr int D = D_, NW = kS2PatchWaves, CAP = CAP_, WAVES = WAVES_, NT = 64 * NW;
     static constexpr int UNITS = CAP + 4;                   // 8-byte units per channel row
     static constexpr int ROW = 4 * UNITS;                   // bf16 values per channel row
-    static constexpr int TERM = D * ROW + 16, TENSOR = kTerms * TERM;
+    static constexpr int TERM = D * ROW + 16, TENSOR = TERMS * TERM;
     static constexpr int KC = D == 16 ? 1 : D / 32;
     static constexpr int NG = NT / CAP;                     // channels staged at once
     static constexpr int NP = D / NG;                       // pieces (4 columns of a channel) per thread and tensor
@@ -116,7 +126,7 @@ struct PatchWhere {
     bool active;                     // the lane's owner is a point
     size_t plane_own, plane_walk, own_at;
     int nlon_walk, c_own, c_walk, n_own;
-    int rmin, nrows, total, rows_at;
+    int seg, rmin, nrows, total, rows_at, more;
     float inv_nU;
     __device__ __forceinline__ size_t row_at(int row) const
     {
@@ -128,6 +138,11 @@ struct PatchWhere {
     {
         own = row;
         own_at = row_at(row);
+    }
+    __device__ __forceinline__ void set_part(const BandArgs &a)
+    {
+        const int4 s0 = a.seg[2 * seg], s1 = a.seg[2 * seg + 1];
+        rmin = s0.z; nrows = s0.w; total = s1.x; rows_at = s1.y; more = s1.z;
     }
     __device__ __forceinline__ void set(const BandArgs &a, int thread = threadIdx.x)
     {
@@ -144,8 +159,9 @@ struct PatchWhere {
             bh = whole + rest % (a.nbh - whole);
         }
         const int2 at = a.patch[blk];
-        const int4 s0 = a.seg[2 * at.x], s1 = a.seg[2 * at.x + 1];
-        first = s0.x; lg = __builtin_amdgcn_readfirstlane(s0.y); rmin = s0.z; nrows = s0.w; total = s1.x; rows_at = s1.y;
+        seg = at.x;
+        first = a.seg[2 * seg].x; lg = __builtin_amdgcn_readfirstlane(a.seg[2 * seg].y);
+        set_part(a);
         W = 16 >> lg;
         tid = thread; lane = tid & 63; wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         n = lane & 15; g = lane >> 4;
@@ -250,7 +266,7 @@ struct Chunks {
         row = e >> 6 & 255;
         col = e >> 14;
         first = __popcll(met & ((1ull << sh) - 1));
-        cnt = __popcll(met >> sh & ((1ull << G::CAP) - 1));
+        cnt = __popcll(met >> sh & (~0ull >> (64 - G::CAP)));
     }
 };
 
@@ -278,90 +294,120 @@ __device__ __forceinline__ void cut(const float (&x)[8], bf16x8 (&b)[kTerms])
     for (int k = 0; k < kTerms; ++k) b[k] = __builtin_bit_cast(bf16x8, u[k]);
 }
 
-// One tensor's stage: from memory to registers, and cut into three terms on the way to LDS.
+// One tensor's stage: from memory to registers, and (float32: cut into three terms) on to LDS.
 template <class G, int MODE>
 struct Place {
     static constexpr bool WIDE = MODE == kWide;
     unsigned off[WIDE ? 1 : 4];      // kWide: byte offset of the thread's first piece in the slice; else elements in a channel plane
     int x, cg;                       // the thread's chunk and first channel
-    template <class W>
-    __device__ __forceinline__ void init(const W &w)
+    __device__ __forceinline__ void init(const PatchWhere &w)
     {
         x = w.tid & (G::CAP - 1);
         cg = w.tid / G::CAP;
     }
-    template <class W>
-    __device__ __forceinline__ void set(const W &w, int row, int col)
+    __device__ __forceinline__ void set(const PatchWhere &w, int row, int col)
     {
         if constexpr (WIDE) {
             const unsigned c = unsigned(wrap_col(col + 2 * w.nU, w.nU, w.inv_nU));
-            off[0] = 4u * (unsigned(cg) * unsigned(w.plane_walk) + unsigned(row) * unsigned(w.nU) + c);
+            off[0] = unsigned(sizeof(typename G::T)) * (unsigned(cg) * unsigned(w.plane_walk) + unsigned(row) * unsigned(w.nU) + c);
         } else {
             const unsigned at = unsigned(w.walk_at(row));
 #pragma unroll
             for (int i = 0; i < 4; ++i) off[i] = at + unsigned(w.c_walk) * unsigned(wrap_col(col + i + 2 * w.nU, w.nU, w.inv_nU));
         }
     }
+    // the same place in a float32 plane
+    __device__ __forceinline__ f32x4 stat(const PatchWhere &w, const float *plane) const
+    {
+        f32x4 s;
+        if constexpr (WIDE) {
+            s = load_at<f32x4>(plane, off[0] / unsigned(sizeof(typename G::T)) * 4u - 4u * unsigned(cg) * unsigned(w.plane_walk));
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[i] = plane[off[i]];
+        }
+        return s;
+    }
 };
 template <class G, int MODE>
 struct Stage {
+    using T = typename G::T;
+    using Piece = std::conditional_t<sizeof(T) == 4, f32x4, u16x4>;
     using P = Place<G, MODE>;
-    f32x4 r[G::NP];
-    template <class W>
-    __device__ __forceinline__ void load(const W &w, const P &at, const float *slice, int nch)
+    Piece r[G::NP];
+    __device__ __forceinline__ void load(const PatchWhere &w, const P &at, const T *slice, int nch)
     {
 #pragma unroll
         for (int j = 0; j < G::NP; ++j) {
             if constexpr (P::WIDE) {
-                r[j] = load_at<f32x4>(slice + size_t(j * G::NG) * w.plane_walk, at.off[0]);
+                r[j] = load_at<Piece>(slice + size_t(j * G::NG) * w.plane_walk, at.off[0]);
             } else {
                 const int c = at.cg + j * G::NG;
-                const float *p = slice + size_t(MODE == kRagged ? imin(c, nch - 1) : c) * w.plane_walk;
+                const T *p = slice + size_t(MODE == kRagged ? imin(c, nch - 1) : c) * w.plane_walk;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) r[j][i] = p[at.off[i]];
             }
         }
     }
     // the workgroup's own points; vec: its rows are contiguous and their length a multiple of four
-    __device__ __forceinline__ void load_own(const PatchWhere &w, const float *slice, int nch, bool vec)
+    __device__ __forceinline__ void load_own(const PatchWhere &w, const T *slice, int nch, bool vec)
     {
         const int h = 2 - here_s(w.lg), tid = here_v(w.tid), x = tid & (G::OWN - 1), cg = tid / G::CAP, sub = (x / G::NW) >> h;
         const int row = w.first + sub < w.n_own ? w.first + sub : w.first, u = w.W0 + 4 * (x - G::NW * (sub << h));
-        const float *p = slice + w.row_at(row);
+        const T *p = slice + w.row_at(row);
 #pragma unroll
         for (int j = 0; j < G::NP; ++j) {
             const int c = cg + j * G::NG;
-            const float *pc = p + size_t(MODE == kRagged ? imin(c, nch - 1) : c) * w.plane_own;
+            const T *pc = p + size_t(MODE == kRagged ? imin(c, nch - 1) : c) * w.plane_own;
             if (vec) {
-                r[j] = *reinterpret_cast<const f32x4 *>(pc + (u < w.nU ? u : 0));
+                r[j] = *reinterpret_cast<const Piece *>(pc + (u < w.nU ? u : 0));
             } else {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) r[j][i] = pc[size_t(w.c_own) * imin(u + i, w.nU - 1)];
             }
         }
     }
-    __device__ __forceinline__ void scale(float factor)
+    __device__ __forceinline__ void negate()
     {
 #pragma unroll
-        for (int j = 0; j < G::NP; ++j) r[j] *= factor;
+        for (int j = 0; j < G::NP; ++j) {
+            if constexpr (sizeof(T) == 4) r[j] = -r[j];
+            else r[j] ^= static_cast<unsigned short>(0x8000);
+        }
+    }
+    __device__ __forceinline__ f32x4 value(int j) const
+    {
+        if constexpr (sizeof(T) == 4) {
+            return r[j];
+        } else {
+            f32x4 v;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = __builtin_bit_cast(float, unsigned(r[j][i]) << 16);
+            return v;
+        }
     }
     __device__ __forceinline__ void store(const P &at, __bf16 *tile, int nch) const
     {
 #pragma unroll
         for (int j = 0; j < G::NP; ++j) {
             const int c = at.cg + j * G::NG;
-            f32x4 v = r[j];
-            if (MODE == kRagged && c >= nch) v = f32x4{0.f, 0.f, 0.f, 0.f};
+            Piece v = r[j];
+            if (MODE == kRagged && c >= nch) v = Piece{0, 0, 0, 0};
             __bf16 *p = tile + G::start(c) + 4 * at.x;
-            float x0 = v[0], x1 = v[1], x2 = v[2], x3 = v[3];
+            if constexpr (sizeof(T) == 4) {
+                float x0 = v[0], x1 = v[1], x2 = v[2], x3 = v[3];
 #pragma unroll
-            for (int k = 0; k < kTerms; ++k) {
-                const unsigned a = cut_off(x0, x1), b = cut_off(x2, x3);
-                *reinterpret_cast<u32x2 *>(p + k * G::TERM) = u32x2{a, b};
+                for (int k = 0; k < kTerms; ++k) {
+                    const unsigned a = cut_off(x0, x1), b = cut_off(x2, x3);
+                    *reinterpret_cast<u32x2 *>(p + k * G::TERM) = u32x2{a, b};
+                }
+            } else {
+                *reinterpret_cast<u16x4 *>(p) = v;
             }
         }
     }
 };
+
 __device__ __forceinline__ f32x4 mma(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 __device__ __forceinline__ bf16x8 join(bf16x4 a, bf16x4 b) { return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7); }
 __device__ __forceinline__ bf16x4 lds_tr(const __bf16 *p)
@@ -374,10 +420,12 @@ __device__ __forceinline__ bf16x4 lds_row(const __bf16 *p) { return *reinterpret
 // A lane's own point as operand of the first product; p: the lane's place in the staged tensor
 template <class G>
 struct OwnPoint {
-    bf16x8 v[G::KC][kTerms];
+    bf16x8 v[G::KC][G::TERMS];
     __device__ __forceinline__ void read(const __bf16 *p)
     {
-        if constexpr (G::D == 16) {
+        if constexpr (G::D == 16 && G::TERMS == 1) {
+            v[0][0] = join(lds_tr(p), bf16x4{});
+        } else if constexpr (G::D == 16) {
             const bf16x4 h = lds_tr(p), m = lds_tr(p + G::TERM), l = lds_tr(p + 2 * G::TERM);
             v[0][0] = join(h, h);
             v[0][1] = join(m, m);
@@ -386,7 +434,7 @@ struct OwnPoint {
 #pragma unroll
             for (int s = 0; s < G::KC; ++s)
 #pragma unroll
-                for (int k = 0; k < kTerms; ++k) v[s][k] = join(lds_tr(p + k * G::TERM + 2 * s * G::UP), lds_tr(p + k * G::TERM + (2 * s + 1) * G::UP));
+                for (int k = 0; k < G::TERMS; ++k) v[s][k] = join(lds_tr(p + k * G::TERM + 2 * s * G::UP), lds_tr(p + k * G::TERM + (2 * s + 1) * G::UP));
         }
     }
 };
@@ -395,44 +443,82 @@ template <class G>
 __device__ __forceinline__ f32x4 dot(const __bf16 *p, const OwnPoint<G> &o)
 {
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    if constexpr (G::D == 16) {
+    if constexpr (G::D == 16 && G::TERMS == 1) {
+        acc = mma(join(lds_tr(p), bf16x4{}), o.v[0][0], acc);
+    } else if constexpr (G::D == 16) {
         const bf16x4 h = lds_tr(p), m = lds_tr(p + G::TERM), l = lds_tr(p + 2 * G::TERM);
         acc = mma(join(h, l), o.v[0][2], acc);
         const bf16x8 hm = join(h, m);
         acc = mma(hm, o.v[0][1], acc);
         acc = mma(hm, o.v[0][0], acc);
     } else {
-        bf16x8 x[G::KC][kTerms];
+        bf16x8 x[G::KC][G::TERMS];
 #pragma unroll
         for (int s = 0; s < G::KC; ++s)
 #pragma unroll
-            for (int k = 0; k < kTerms; ++k)
+            for (int k = 0; k < G::TERMS; ++k)
                 x[s][k] = join(lds_tr(p + k * G::TERM + 2 * s * G::UP), lds_tr(p + k * G::TERM + (2 * s + 1) * G::UP));
         constexpr int order[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
 #pragma unroll
-        for (int i = 0; i < 6; ++i)
+        for (int i = G::TERMS == 1 ? 5 : 0; i < 6; ++i)
 #pragma unroll
             for (int s = 0; s < G::KC; ++s) acc = mma(x[s][order[i][0]], o.v[s][order[i][1]], acc);
     }
     return acc;
 }
-// hi, lo [mt] += (channels 16 mt ..) . (the lane's eight values of the columns of two tiles); p0, p1: the lane's places
+// Sums over keys, per lane 16 mt + 4 g + rr; float32: the products of first terms apart from the others
 template <class G>
-__device__ __forceinline__ void sum(const __bf16 *p0, const __bf16 *p1, const bf16x8 (&b)[kTerms], f32x4 (&hi)[G::D / 16], f32x4 (&lo)[G::D / 16])
-{
+struct Sums {
+    f32x4 hi[G::D / 16], lo[G::TERMS == 1 ? 1 : G::D / 16];
+    __device__ __forceinline__ void zero()
+    {
 #pragma unroll
-    for (int mt = 0; mt < G::D / 16; ++mt) {
-        bf16x8 x[kTerms];
+        for (auto &x : hi) x = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int k = 0; k < kTerms; ++k) x[k] = join(lds_row(p0 + k * G::TERM + mt * G::UP), lds_row(p1 + k * G::TERM + mt * G::UP));
-        lo[mt] = mma(x[2], b[0], lo[mt]);
-        hi[mt] = mma(x[0], b[0], hi[mt]);
-        lo[mt] = mma(x[0], b[2], lo[mt]);
-        lo[mt] = mma(x[1], b[1], lo[mt]);
-        lo[mt] = mma(x[1], b[0], lo[mt]);
-        lo[mt] = mma(x[0], b[1], lo[mt]);
+        for (auto &x : lo) x = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-}
+    __device__ __forceinline__ void wait()
+    {
+        settle(hi);
+        if constexpr (G::TERMS > 1) settle(lo);
+    }
+    __device__ __forceinline__ void scale(float f)
+    {
+#pragma unroll
+        for (auto &x : hi) x *= f;
+        if constexpr (G::TERMS > 1)
+#pragma unroll
+            for (auto &x : lo) x *= f;
+    }
+    __device__ __forceinline__ void join_terms()
+    {
+        if constexpr (G::TERMS > 1)
+#pragma unroll
+            for (int mt = 0; mt < G::D / 16; ++mt) hi[mt] += lo[mt];
+    }
+    // += (channels 16 mt ..) . (the lane's eight values of the columns of two tiles); p0, p1: the lane's places
+    __device__ __forceinline__ void add(const __bf16 *p0, const __bf16 *p1, const bf16x8 (&b)[kTerms])
+    {
+#pragma unroll
+        for (int mt = 0; mt < G::D / 16; ++mt) {
+            bf16x8 x[G::TERMS];
+#pragma unroll
+            for (int k = 0; k < G::TERMS; ++k) x[k] = join(lds_row(p0 + k * G::TERM + mt * G::UP), lds_row(p1 + k * G::TERM + mt * G::UP));
+            if constexpr (G::TERMS == 1) {
+                hi[mt] = mma(x[0], b[2], hi[mt]);
+                hi[mt] = mma(x[0], b[1], hi[mt]);
+                hi[mt] = mma(x[0], b[0], hi[mt]);
+            } else {
+                lo[mt] = mma(x[2], b[0], lo[mt]);
+                hi[mt] = mma(x[0], b[0], hi[mt]);
+                lo[mt] = mma(x[0], b[2], lo[mt]);
+                lo[mt] = mma(x[1], b[1], lo[mt]);
+                lo[mt] = mma(x[1], b[0], lo[mt]);
+                lo[mt] = mma(x[0], b[1], lo[mt]);
+            }
+        }
+    }
+};
 
 // What a lane needs of one key tile (four chunks of the list): its own chunk, its place as reader of the first product
 struct TileRef {
@@ -468,11 +554,12 @@ __device__ __forceinline__ void put_results(const f32x4 (&acc)[G::D / 16], float
         for (int rr = 0; rr < 4; ++rr) p[(16 * mt + rr) * G::PITCH] = again ? __builtin_bit_cast(float, kAgain) : acc[mt][rr] * factor;
 }
 template <class G>
-__device__ __forceinline__ void store_results(float *slice, int nch, const float *tile, const PatchWhere &w, bool vec)
+__device__ __forceinline__ void store_results(typename G::T *slice, int nch, const float *tile, const PatchWhere &w, bool vec)
 {
     const int h = 2 - here_s(w.lg), tid = here_v(w.tid), x = tid % G::OWN, c0 = tid / G::OWN, sub = (x / G::NW) >> h, u = w.W0 + 4 * (x - G::NW * (sub << h));
     if (w.first + sub >= w.n_own || u >= w.nU) return;
-    float *p = slice + size_t(c0) * w.plane_own + w.row_at(w.first + sub) + size_t(w.c_own) * u;
+    using T = typename G::T;
+    T *p = slice + size_t(c0) * w.plane_own + w.row_at(w.first + sub) + size_t(w.c_own) * u;
     const size_t up = size_t(G::NT / G::OWN) * w.plane_own;
 #pragma unroll
     for (int j = 0; j < G::D * G::OWN / G::NT; ++j, p += up) {
@@ -482,13 +569,16 @@ __device__ __forceinline__ void store_results(float *slice, int nch, const float
         unsigned skip = 0;
 #pragma unroll
         for (int k = 0; k < 4; ++k) skip |= (r[k] == kAgain || u + k >= w.nU ? 1u : 0u) << k;
+        typename Stage<G, kWide>::Piece y;
+        if constexpr (sizeof(T) == 4) y = __builtin_bit_cast(f32x4, r);
+        else y = __builtin_bit_cast(u16x4, __builtin_convertvector(__builtin_bit_cast(f32x4, r), bf16x4));
         if (vec && skip == 0) {
-            *reinterpret_cast<u32x4 *>(p) = r;
+            *reinterpret_cast<decltype(y) *>(p) = y;
         } else {
-            unsigned *pk = reinterpret_cast<unsigned *>(p);
+            T *pk = p;
 #pragma unroll
             for (int k = 0; k < 4; ++k, pk += w.c_own)
-                if (!(skip >> k & 1)) *pk = r[k];
+                if (!(skip >> k & 1)) *pk = y[k];
         }
     }
 }
@@ -497,17 +587,18 @@ __device__ __forceinline__ void store_results(float *slice, int nch, const float
 // Forward.
 template <class G, int MODE>
 __global__ void __launch_bounds__(G::NT, G::WAVES)
-nattn_fwd_patch(BandArgs a, const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v, float *__restrict__ out,
-                float *__restrict__ lse)
+nattn_fwd_patch(BandArgs a, const typename G::T *__restrict__ q, const typename G::T *__restrict__ k, const typename G::T *__restrict__ v,
+                typename G::T *__restrict__ out, float *__restrict__ lse)
 {
     constexpr int D = G::D;
+    using T = typename G::T;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     Shared<G> &sh = *reinterpret_cast<Shared<G> *>(lds);
     PatchWhere w;
     w.set(a);
     const int n = w.n, g = w.g, nd = MODE == kRagged ? a.d : D, ne = MODE == kRagged ? a.e : D;
     const bool vec = w.c_own == 1 && w.nU % 4 == 0;
-    const float *qs = q + size_t(w.bh) * nd * w.plane_own, *ks = k + size_t(w.bh) * nd * w.plane_walk, *vs = v + size_t(w.bh) * ne * w.plane_walk;
+    const T *qs = q + size_t(w.bh) * nd * w.plane_own, *ks = k + size_t(w.bh) * nd * w.plane_walk, *vs = v + size_t(w.bh) * ne * w.plane_walk;
     Place<G, MODE> at;
     at.init(w);
     Stage<G, MODE> rk, rv;
@@ -522,83 +613,85 @@ nattn_fwd_patch(BandArgs a, const float *__restrict__ q, const float *__restrict
     };
     const int tr_at = G::start(4 * g + (n >> 2)), row_at = G::start(n);
     __syncthreads();                    // everybody is done with what LDS held
-    rk.scale(a.scale < 0.f ? -1.f : 1.f);
+    if (a.scale < 0.f) rk.negate();
     rk.store(at, sh.a, nd);
     __syncthreads();
     if (w.total > 0) fetch(0);
     OwnPoint<G> own;
     own.read(sh.a + tr_at + 4 * w.own_slot(here_v(w.lane) & 3, G::NW));
-    f32x4 hi[D / 16], lo[D / 16];
-#pragma unroll
-    for (int mt = 0; mt < D / 16; ++mt) hi[mt] = lo[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    Sums<G> acc;
+    acc.zero();
     // |scale|, its sign is on q: the largest product is the largest logit; never zero, so that a masked -inf stays one
     const float c2 = a.scale == 0.f ? 1e-37f : fabsf(a.scale) * kLog2e;
     float m = kMinRef, l = 0.f;
-    for (int X0 = 0; X0 < w.total; X0 += G::CAP) {
-        __syncthreads();
-        rk.store(at, sh.a, nd);
-        rv.store(at, sh.b, ne);
-        __syncthreads();
-        const int list = ch.list, first = ch.first, end = ch.first + ch.cnt, ntile = (ch.cnt + 3) >> 2;
-        if (X0 + G::CAP < w.total) fetch(X0 + G::CAP);
-        auto step = [&](int t, auto count) {
-            constexpr int N = decltype(count)::value;
-            TileRef tr[2];
-            float x[8], omega[2];
+    for (;;) {
+        for (int X0 = 0; X0 < w.total; X0 += G::CAP) {
+            __syncthreads();
+            rk.store(at, sh.a, nd);
+            rv.store(at, sh.b, ne);
+            __syncthreads();
+            const int list = ch.list, first = ch.first, end = ch.first + ch.cnt, ntile = (ch.cnt + 3) >> 2;
+            if (X0 + G::CAP < w.total) fetch(X0 + G::CAP);
+            auto step = [&](int t, auto count) {
+                constexpr int N = decltype(count)::value;
+                TileRef tr[2];
+                float x[8], omega[2];
 #pragma unroll
-            for (int i = 0; i < N; ++i) tr[i].get(list, first + 4 * (t + i), end, n, g);
+                for (int i = 0; i < N; ++i) tr[i].get(list, first + 4 * (t + i), end, n, g);
 #pragma unroll
-            for (int i = 0; i < N; ++i) {
-                const uint2 arc = sh.rows.arc[w.sub][tr[i].row];
-                const f32x4 sc = dot<G>(sh.a + tr_at + 4 * tr[i].slot_n, own);
-                omega[i] = __builtin_bit_cast(float, arc.y);
-                bool keep[4];
-                tr[i].keep(keep, w.u, arc.x);
+                for (int i = 0; i < N; ++i) {
+                    const uint2 arc = sh.rows.arc[w.sub][tr[i].row];
+                    const f32x4 sc = dot<G>(sh.a + tr_at + 4 * tr[i].slot_n, own);
+                    omega[i] = __builtin_bit_cast(float, arc.y);
+                    bool keep[4];
+                    tr[i].keep(keep, w.u, arc.x);
 #pragma unroll
-                for (int rr = 0; rr < 4; ++rr) x[4 * i + rr] = keep[rr] ? sc[rr] : -INFINITY;
-            }
-            float mx = x[0];
-#pragma unroll
-            for (int i = 1; i < 4 * N; ++i) mx = fmaxf(mx, x[i]);
-            mx *= c2;
-            if (__any(mx > m + 8.f)) {
-                mx = group_max(mx);
-                const float m_new = mx > m + 8.f ? mx : m;
-                const float corr = __builtin_amdgcn_exp2f(m - m_new);
-                m = m_new;
-                l *= corr;
-#pragma unroll
-                for (int mt = 0; mt < D / 16; ++mt) {
-                    hi[mt] *= corr;
-                    lo[mt] *= corr;
+                    for (int rr = 0; rr < 4; ++rr) x[4 * i + rr] = keep[rr] ? sc[rr] : -INFINITY;
                 }
-            }
+                float mx = x[0];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                if (i < 4 * N) {
-                    const float e = __builtin_amdgcn_exp2f(fmaf(x[i], c2, -m));
-                    l = fmaf(omega[i / 4], e, l);
-                    x[i] = omega[i / 4] * e;
-                } else {
-                    x[i] = 0.f;
+                for (int i = 1; i < 4 * N; ++i) mx = fmaxf(mx, x[i]);
+                mx *= c2;
+                if (__any(mx > m + 8.f)) {
+                    acc.wait();              // (the step before may have ended just now)
+                    mx = group_max(mx);
+                    const float m_new = mx > m + 8.f ? mx : m;
+                    const float corr = __builtin_amdgcn_exp2f(m - m_new);
+                    m = m_new;
+                    l *= corr;
+                    acc.scale(corr);
                 }
-            }
-            bf16x8 p[kTerms];
-            cut(x, p);
-            sum<G>(sh.b + row_at + 4 * tr[0].slot, sh.b + row_at + 4 * tr[N - 1].slot, p, hi, lo);
-            settle(hi);
-            settle(lo);
-        };
-        int t = 0;
-        for (; t + 1 < ntile; t += 2) step(t, std::integral_constant<int, 2>());
-        if (t < ntile) step(t, std::integral_constant<int, 1>());
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    if (i < 4 * N) {
+                        const float e = __builtin_amdgcn_exp2f(fmaf(x[i], c2, -m));
+                        l = fmaf(omega[i / 4], e, l);
+                        x[i] = omega[i / 4] * e;
+                    } else {
+                        x[i] = 0.f;
+                    }
+                }
+                bf16x8 p[kTerms];
+                cut(x, p);
+                acc.add(sh.b + row_at + 4 * tr[0].slot, sh.b + row_at + 4 * tr[N - 1].slot, p);
+            };
+            int t = 0;
+            for (; t + 1 < ntile; t += 2) step(t, std::integral_constant<int, 2>());
+            if (t < ntile) step(t, std::integral_constant<int, 1>());
+            acc.wait();
+        }
+        if (!w.more) break;
+        ++w.seg;                           // more walked rows than the tables hold: the next part of them
+        w.set_part(a);
+        __syncthreads();
+        ch.start(a, w, sh.rows);
+        if (w.total > 0) fetch(0);
     }
-#pragma unroll
-    for (int mt = 0; mt < D / 16; ++mt) hi[mt] += lo[mt];
+    acc.join_terms();
     const float lt = group_sum(l);
-    const unsigned again = not_finite(hi, w.active);     // owners whose sums took in a non-finite value (s2_nattn_exact.h)
+    const unsigned again = not_finite(acc.hi, w.active);     // owners whose sums took in a non-finite value (s2_nattn_exact.h)
     __syncthreads();
-    put_results<G>(hi, 1.f / lt, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
+    put_results<G>(acc.hi, 1.f / lt, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
     if (w.active && g == 0 && !(again >> n & 1)) {
         // the whole part of m goes into the logarithm, so that its value and the sum are no larger than the result
         const float whole = fminf(fmaxf(rintf(m), -60.f), 60.f);
@@ -607,18 +700,19 @@ nattn_fwd_patch(BandArgs a, const float *__restrict__ q, const float *__restrict
     }
     __syncthreads();
     store_results<G>(out + size_t(w.bh) * ne * w.plane_own, ne, reinterpret_cast<const float *>(sh.a), w, vec);
-    exact_fwd<float, PatchWhere>(again, w.wave);
+    exact_fwd<T, PatchWhere>(again, w.wave);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
 // Backward, query side: dq and D_i = dout_i . out_i (written for the key-side launch).
 template <class G, int MODE>
 __global__ void __launch_bounds__(G::NT, G::WAVES)
-nattn_bwd_dq_patch(BandArgs a, const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
-                   const float *__restrict__ o_, const float *__restrict__ lse, const float *__restrict__ go, float *__restrict__ dq,
-                   float *__restrict__ Dws)
+nattn_bwd_dq_patch(BandArgs a, const typename G::T *__restrict__ q, const typename G::T *__restrict__ k, const typename G::T *__restrict__ v,
+                   const typename G::T *__restrict__ o_, const float *__restrict__ lse, const typename G::T *__restrict__ go,
+                   typename G::T *__restrict__ dq, float *__restrict__ Dws)
 {
     constexpr int D = G::D;
+    using T = typename G::T;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     SharedDq<G> &sh = *reinterpret_cast<SharedDq<G> *>(lds);
     PatchWhere w;
@@ -626,8 +720,8 @@ nattn_bwd_dq_patch(BandArgs a, const float *__restrict__ q, const float *__restr
     const int n = w.n, g = w.g, nd = MODE == kRagged ? a.d : D, ne = MODE == kRagged ? a.e : D;
     const bool vec = w.c_own == 1 && w.nU % 4 == 0;
     const float c2 = a.scale * kLog2e;
-    const float *qs = q + size_t(w.bh) * nd * w.plane_own, *gs = go + size_t(w.bh) * ne * w.plane_own, *os = o_ + size_t(w.bh) * ne * w.plane_own;
-    const float *ks = k + size_t(w.bh) * nd * w.plane_walk, *vs = v + size_t(w.bh) * ne * w.plane_walk;
+    const T *qs = q + size_t(w.bh) * nd * w.plane_own, *gs = go + size_t(w.bh) * ne * w.plane_own, *os = o_ + size_t(w.bh) * ne * w.plane_own;
+    const T *ks = k + size_t(w.bh) * nd * w.plane_walk, *vs = v + size_t(w.bh) * ne * w.plane_walk;
     Place<G, MODE> at;
     at.init(w);
     Stage<G, MODE> rk, rv;
@@ -650,7 +744,7 @@ nattn_bwd_dq_patch(BandArgs a, const float *__restrict__ q, const float *__restr
     f32x4 part = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int j = 0; j < G::NP; ++j)
-        if (MODE != kRagged || at.cg + j * G::NG < ne) part += rv.r[j] * ro.r[j];
+        if (MODE != kRagged || at.cg + j * G::NG < ne) part += rv.value(j) * ro.value(j);
     if (at.x < G::OWN) *reinterpret_cast<f32x4 *>(&sh.part[at.cg][4 * at.x]) = part;
     rk.store(at, sh.a, nd);
     rv.store(at, sh.b, ne);
@@ -665,54 +759,59 @@ nattn_bwd_dq_patch(BandArgs a, const float *__restrict__ q, const float *__restr
     for (int i = g; i < G::NG; i += 4) dsum += sh.part[i][point];
     dsum = group_sum(dsum);
     if (w.active && g == 0) Dws[stat] = dsum;
-    f32x4 hi[D / 16], lo[D / 16];
+    Sums<G> acc;
+    acc.zero();
+    for (;;) {
+        for (int X0 = 0; X0 < w.total; X0 += G::CAP) {
+            __syncthreads();
+            rk.store(at, sh.a, nd);
+            rv.store(at, sh.b, ne);
+            __syncthreads();
+            const int list = ch.list, first = ch.first, end = ch.first + ch.cnt, ntile = (ch.cnt + 3) >> 2;
+            if (X0 + G::CAP < w.total) fetch(X0 + G::CAP);
+            auto step = [&](int t, auto count) {
+                constexpr int N = decltype(count)::value;
+                TileRef tr[2];
+                float x[8];
 #pragma unroll
-    for (int mt = 0; mt < D / 16; ++mt) hi[mt] = lo[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int X0 = 0; X0 < w.total; X0 += G::CAP) {
-        __syncthreads();
-        rk.store(at, sh.a, nd);
-        rv.store(at, sh.b, ne);
-        __syncthreads();
-        const int list = ch.list, first = ch.first, end = ch.first + ch.cnt, ntile = (ch.cnt + 3) >> 2;
-        if (X0 + G::CAP < w.total) fetch(X0 + G::CAP);
-        auto step = [&](int t, auto count) {
-            constexpr int N = decltype(count)::value;
-            TileRef tr[2];
-            float x[8];
+                for (int i = 0; i < N; ++i) tr[i].get(list, first + 4 * (t + i), end, n, g);
 #pragma unroll
-            for (int i = 0; i < N; ++i) tr[i].get(list, first + 4 * (t + i), end, n, g);
+                for (int i = 0; i < N; ++i) {
+                    const uint2 arc = sh.rows.arc[w.sub][tr[i].row];
+                    const f32x4 sc = dot<G>(sh.a + tr_at + 4 * tr[i].slot_n, oq), dp = dot<G>(sh.b + tr_at + 4 * tr[i].slot_n, og);
+                    bool keep[4];
+                    tr[i].keep(keep, w.u, arc.x);
 #pragma unroll
-            for (int i = 0; i < N; ++i) {
-                const uint2 arc = sh.rows.arc[w.sub][tr[i].row];
-                const f32x4 sc = dot<G>(sh.a + tr_at + 4 * tr[i].slot_n, oq), dp = dot<G>(sh.b + tr_at + 4 * tr[i].slot_n, og);
-                bool keep[4];
-                tr[i].keep(keep, w.u, arc.x);
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr) {
-                    const float ds = __builtin_bit_cast(float, arc.y) * __builtin_amdgcn_exp2f(fmaf(sc[rr], c2, -L2)) * (dp[rr] - dsum);
-                    x[4 * i + rr] = keep[rr] ? ds : 0.f;
+                    for (int rr = 0; rr < 4; ++rr) {
+                        const float ds = __builtin_bit_cast(float, arc.y) * __builtin_amdgcn_exp2f(fmaf(sc[rr], c2, -L2)) * (dp[rr] - dsum);
+                        x[4 * i + rr] = keep[rr] ? ds : 0.f;
+                    }
                 }
-            }
 #pragma unroll
-            for (int i = 4 * N; i < 8; ++i) x[i] = 0.f;
-            bf16x8 p[kTerms];
-            cut(x, p);
-            sum<G>(sh.a + row_at + 4 * tr[0].slot, sh.a + row_at + 4 * tr[N - 1].slot, p, hi, lo);
-        };
-        int t = 0;
-        for (; t + 1 < ntile; t += 2) step(t, std::integral_constant<int, 2>());
-        if (t < ntile) step(t, std::integral_constant<int, 1>());
-        settle(hi);
-        settle(lo);
+                for (int i = 4 * N; i < 8; ++i) x[i] = 0.f;
+                bf16x8 p[kTerms];
+                cut(x, p);
+                acc.add(sh.a + row_at + 4 * tr[0].slot, sh.a + row_at + 4 * tr[N - 1].slot, p);
+            };
+            int t = 0;
+            for (; t + 1 < ntile; t += 2) step(t, std::integral_constant<int, 2>());
+            if (t < ntile) step(t, std::integral_constant<int, 1>());
+            acc.wait();
+        }
+        if (!w.more) break;
+        ++w.seg;                           // more walked rows than the tables hold: the next part of them
+        w.set_part(a);
+        __syncthreads();
+        ch.start(a, w, sh.rows);
+        if (w.total > 0) fetch(0);
     }
-#pragma unroll
-    for (int mt = 0; mt < D / 16; ++mt) hi[mt] += lo[mt];
-    const unsigned again = not_finite(hi, w.active);
+    acc.join_terms();
+    const unsigned again = not_finite(acc.hi, w.active);
     __syncthreads();
-    put_results<G>(hi, a.scale * a.omega_ref, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
+    put_results<G>(acc.hi, a.scale * a.omega_ref, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
     __syncthreads();
     store_results<G>(dq + size_t(w.bh) * nd * w.plane_own, nd, reinterpret_cast<const float *>(sh.a), w, vec);
-    exact_dq<float, PatchWhere>(again, w.wave);
+    exact_dq<T, PatchWhere>(again, w.wave);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -720,11 +819,12 @@ nattn_bwd_dq_patch(BandArgs a, const float *__restrict__ q, const float *__restr
 // of a stage's outputs are staged together.
 template <class G, int MODE>
 __global__ void __launch_bounds__(G::NT, G::WAVES)
-nattn_bwd_dkdv_patch(BandArgs a, const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
-                     const float *__restrict__ lse, const float *__restrict__ go, const float *__restrict__ Dws,
-                     float *__restrict__ dk, float *__restrict__ dv)
+nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const typename G::T *__restrict__ k, const typename G::T *__restrict__ v,
+                     const float *__restrict__ lse, const typename G::T *__restrict__ go, const float *__restrict__ Dws,
+                     typename G::T *__restrict__ dk, typename G::T *__restrict__ dv)
 {
     constexpr int D = G::D;
+    using T = typename G::T;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     SharedDkdv<G> &sh = *reinterpret_cast<SharedDkdv<G> *>(lds);
     PatchWhere w;
@@ -732,8 +832,8 @@ nattn_bwd_dkdv_patch(BandArgs a, const float *__restrict__ q, const float *__res
     const int n = w.n, g = w.g, nd = MODE == kRagged ? a.d : D, ne = MODE == kRagged ? a.e : D;
     const bool vec = w.c_own == 1 && w.nU % 4 == 0;
     const float c2 = a.scale * kLog2e;
-    const float *ks = k + size_t(w.bh) * nd * w.plane_own, *vs = v + size_t(w.bh) * ne * w.plane_own;
-    const float *qs = q + size_t(w.bh) * nd * w.plane_walk, *gs = go + size_t(w.bh) * ne * w.plane_walk;
+    const T *ks = k + size_t(w.bh) * nd * w.plane_own, *vs = v + size_t(w.bh) * ne * w.plane_own;
+    const T *qs = q + size_t(w.bh) * nd * w.plane_walk, *gs = go + size_t(w.bh) * ne * w.plane_walk;
     const float *ls = lse + size_t(w.bh) * w.plane_walk, *Ds = Dws + size_t(w.bh) * w.plane_walk;
     // the quadrature weight is the owner's own here: it multiplies the finished sums (a latitude of weight zero has no arcs)
     const float omega = a.omega_rel[w.own / w.c_own] * a.omega_ref;
@@ -750,15 +850,7 @@ nattn_bwd_dkdv_patch(BandArgs a, const float *__restrict__ q, const float *__res
         at.set(w, w.rmin + ch.row, ch.col);
         rq.load(w, at, qs, nd);
         rg.load(w, at, gs, ne);
-        if (w.tid < 2 * G::CAP) {
-            const float *p = at.cg ? Ds : ls;
-            if constexpr (MODE == kWide) {
-                rs = load_at<f32x4>(p, at.off[0] - 4u * unsigned(at.cg) * unsigned(w.plane_walk));
-            } else {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) rs[i] = p[at.off[i]];
-            }
-        }
+        if (w.tid < 2 * G::CAP) rs = at.stat(w, at.cg ? Ds : ls);
     };
     const int tr_at = G::start(4 * g + (n >> 2)), row_at = G::start(n);
     __syncthreads();
@@ -770,88 +862,96 @@ nattn_bwd_dkdv_patch(BandArgs a, const float *__restrict__ q, const float *__res
     OwnPoint<G> ok, ov;
     ok.read(sh.a + tr_at + 4 * slot);
     ov.read(sh.b + tr_at + 4 * slot);
-    f32x4 khi[D / 16], klo[D / 16], vhi[D / 16], vlo[D / 16];
-#pragma unroll
-    for (int mt = 0; mt < D / 16; ++mt) khi[mt] = klo[mt] = vhi[mt] = vlo[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int X0 = 0; X0 < w.total; X0 += G::CAP) {
-        __syncthreads();
-        rq.store(at, sh.a, nd);
-        rg.store(at, sh.b, ne);
-        if (w.tid < 2 * G::CAP) {
-            if (at.cg == 0) *reinterpret_cast<f32x4 *>(sh.L + 4 * at.x) = rs * -kLog2e;
-            else *reinterpret_cast<f32x4 *>(sh.D + 4 * at.x) = rs;
-        }
-        __syncthreads();
-        const int list = ch.list, first = ch.first, end = ch.first + ch.cnt, ntile = (ch.cnt + 3) >> 2;
-        if (X0 + G::CAP < w.total) fetch(X0 + G::CAP);
-        auto step = [&](int t, auto count) {
-            constexpr int N = decltype(count)::value;
-            TileRef tr[2];
-            float pr[8], ds[8];
-#pragma unroll
-            for (int i = 0; i < N; ++i) tr[i].get(list, first + 4 * (t + i), end, n, g);
-#pragma unroll
-            for (int i = 0; i < N; ++i) {
-                const unsigned arc = sh.rows.arc[w.sub][tr[i].row].x;
-                const f32x4 L = *reinterpret_cast<const f32x4 *>(sh.L + 4 * tr[i].slot), Dn = *reinterpret_cast<const f32x4 *>(sh.D + 4 * tr[i].slot);
-                const f32x4 sc = dot<G>(sh.a + tr_at + 4 * tr[i].slot_n, ok), dp = dot<G>(sh.b + tr_at + 4 * tr[i].slot_n, ov);
-                bool keep[4];
-                tr[i].keep(keep, w.u, arc);
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr) {
-                    const float x = __builtin_amdgcn_exp2f(fmaf(sc[rr], c2, L[rr]));
-                    pr[4 * i + rr] = keep[rr] ? x : 0.f;
-                    ds[4 * i + rr] = keep[rr] ? x * (dp[rr] - Dn[rr]) : 0.f;
-                }
+    Sums<G> dka, dva;
+    dka.zero();
+    dva.zero();
+    for (;;) {
+        for (int X0 = 0; X0 < w.total; X0 += G::CAP) {
+            __syncthreads();
+            rq.store(at, sh.a, nd);
+            rg.store(at, sh.b, ne);
+            if (w.tid < 2 * G::CAP) {
+                if (at.cg == 0) *reinterpret_cast<f32x4 *>(sh.L + 4 * at.x) = rs * -kLog2e;
+                else *reinterpret_cast<f32x4 *>(sh.D + 4 * at.x) = rs;
             }
+            __syncthreads();
+            const int list = ch.list, first = ch.first, end = ch.first + ch.cnt, ntile = (ch.cnt + 3) >> 2;
+            if (X0 + G::CAP < w.total) fetch(X0 + G::CAP);
+            auto step = [&](int t, auto count) {
+                constexpr int N = decltype(count)::value;
+                TileRef tr[2];
+                float pr[8], ds[8];
 #pragma unroll
-            for (int i = 4 * N; i < 8; ++i) pr[i] = ds[i] = 0.f;
-            bf16x8 p[kTerms];
-            cut(pr, p);
-            sum<G>(sh.b + row_at + 4 * tr[0].slot, sh.b + row_at + 4 * tr[N - 1].slot, p, vhi, vlo);
-            cut(ds, p);
-            sum<G>(sh.a + row_at + 4 * tr[0].slot, sh.a + row_at + 4 * tr[N - 1].slot, p, khi, klo);
-        };
-        int t = 0;
-        for (; t + 1 < ntile; t += 2) step(t, std::integral_constant<int, 2>());
-        if (t < ntile) step(t, std::integral_constant<int, 1>());
-        settle(khi);
-        settle(klo);
-        settle(vhi);
-        settle(vlo);
-    }
+                for (int i = 0; i < N; ++i) tr[i].get(list, first + 4 * (t + i), end, n, g);
 #pragma unroll
-    for (int mt = 0; mt < D / 16; ++mt) {
-        khi[mt] += klo[mt];
-        vhi[mt] += vlo[mt];
+                for (int i = 0; i < N; ++i) {
+                    const unsigned arc = sh.rows.arc[w.sub][tr[i].row].x;
+                    const f32x4 L = *reinterpret_cast<const f32x4 *>(sh.L + 4 * tr[i].slot), Dn = *reinterpret_cast<const f32x4 *>(sh.D + 4 * tr[i].slot);
+                    const f32x4 sc = dot<G>(sh.a + tr_at + 4 * tr[i].slot_n, ok), dp = dot<G>(sh.b + tr_at + 4 * tr[i].slot_n, ov);
+                    bool keep[4];
+                    tr[i].keep(keep, w.u, arc);
+#pragma unroll
+                    for (int rr = 0; rr < 4; ++rr) {
+                        const float x = __builtin_amdgcn_exp2f(fmaf(sc[rr], c2, L[rr]));
+                        pr[4 * i + rr] = keep[rr] ? x : 0.f;
+                        ds[4 * i + rr] = keep[rr] ? x * (dp[rr] - Dn[rr]) : 0.f;
+                    }
+                }
+#pragma unroll
+                for (int i = 4 * N; i < 8; ++i) pr[i] = ds[i] = 0.f;
+                bf16x8 p[kTerms];
+                cut(pr, p);
+                dva.add(sh.b + row_at + 4 * tr[0].slot, sh.b + row_at + 4 * tr[N - 1].slot, p);
+                cut(ds, p);
+                dka.add(sh.a + row_at + 4 * tr[0].slot, sh.a + row_at + 4 * tr[N - 1].slot, p);
+            };
+            int t = 0;
+            for (; t + 1 < ntile; t += 2) step(t, std::integral_constant<int, 2>());
+            if (t < ntile) step(t, std::integral_constant<int, 1>());
+            dka.wait();
+            dva.wait();
+        }
+        if (!w.more) break;
+        ++w.seg;                           // more walked rows than the tables hold: the next part of them
+        w.set_part(a);
+        __syncthreads();
+        ch.start(a, w, sh.rows);
+        if (w.total > 0) fetch(0);
     }
-    const unsigned again = not_finite(khi, w.active) | not_finite(vhi, w.active);
+    dka.join_terms();
+    dva.join_terms();
+    const unsigned again = not_finite(dka.hi, w.active) | not_finite(dva.hi, w.active);
     __syncthreads();
-    put_results<G>(khi, omega * a.scale, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
-    put_results<G>(vhi, omega, again >> n & 1, reinterpret_cast<float *>(sh.b), w);
+    put_results<G>(dka.hi, omega * a.scale, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
+    put_results<G>(dva.hi, omega, again >> n & 1, reinterpret_cast<float *>(sh.b), w);
     __syncthreads();
     store_results<G>(dk + size_t(w.bh) * nd * w.plane_own, nd, reinterpret_cast<const float *>(sh.a), w, vec);
     store_results<G>(dv + size_t(w.bh) * ne * w.plane_own, ne, reinterpret_cast<const float *>(sh.b), w, vec);
-    exact_dkdv<float, PatchWhere>(again, w.wave);
+    exact_dkdv<T, PatchWhere>(again, w.wave);
 }
 
 inline double pair_count(const double (&p)[4], int nbh) { return nbh * (p[0] + p[1] + p[2] + p[3]); }
 
 // Calls f with the geometry for a head dimension
 enum Launch { kFwd, kDq, kDkdv };
-template <Launch WHICH, class F>
+template <class T, Launch WHICH, class F>
 void by_shape(int dmax, F &&f)
 {
-    if (dmax <= 16) f(Geo<16, 32, 4>());
-    else if (dmax <= 32) f(Geo<32, 16, WHICH == kDq ? 4 : 3>());
-    else f(Geo<64, 16, 2>());
+    if constexpr (sizeof(T) == 4) {
+        if (dmax <= 16) f(Geo<T, 16, 32, 4>());
+        else if (dmax <= 32) f(Geo<T, 32, 16, WHICH == kDq ? 4 : 3>());
+        else f(Geo<T, 64, 16, 2>());
+    } else {
+        if (dmax <= 16) f(Geo<T, 16, 64, 4>());
+        else if (dmax <= 32) f(Geo<T, 32, 32, 4>());
+        else f(Geo<T, 64, 32, 3>());
+    }
 }
 struct PatchLaunch {
     BandArgs a;
     dim3 grid;
 };
-template <class G>
-PatchLaunch patch_launch(const S2DeviceTables &t, const S2BandSide &b, int nbh, int d, int e, float scale)
+inline PatchLaunch patch_launch(const S2DeviceTables &t, const S2BandSide &b, int nbh, int d, int e, float scale)
 {
     const S2BandSide::Patches &p = b.patches;
     return {{b, t.omega_rel, t.ln_omega_ref, t.omega_ref, scale, nbh, d, e, p.seg, p.row_rec, p.patch, p.npatch},
@@ -861,44 +961,44 @@ inline bool raise_lds(const void *f, size_t bytes) { return hipFuncSetAttribute(
 
 }  // namespace
 
-template <int MODE>
-int PatchSet<MODE>::configure()
+template <class T, int MODE>
+int PatchKernels<T, MODE>::configure()
 {
     bool bad = false;
     for (int d : {16, 32, 64}) {
-        by_shape<kFwd>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_fwd_patch<decltype(g), MODE>), sizeof(Shared<decltype(g)>)); });
-        by_shape<kDq>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dq_patch<decltype(g), MODE>), sizeof(SharedDq<decltype(g)>)); });
-        by_shape<kDkdv>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dkdv_patch<decltype(g), MODE>), sizeof(SharedDkdv<decltype(g)>)); });
+        by_shape<T, kFwd>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_fwd_patch<decltype(g), MODE>), sizeof(Shared<decltype(g)>)); });
+        by_shape<T, kDq>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dq_patch<decltype(g), MODE>), sizeof(SharedDq<decltype(g)>)); });
+        by_shape<T, kDkdv>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dkdv_patch<decltype(g), MODE>), sizeof(SharedDkdv<decltype(g)>)); });
     }
     return bad;
 }
-template <int MODE>
-void PatchSet<MODE>::fwd(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k, const float *v,
-                         float *out, float *lse, hipStream_t st)
+template <class T, int MODE>
+void PatchKernels<T, MODE>::fwd(const S2DeviceTables &t, int nbh, int d, int e, float scale, const T *q, const T *k, const T *v, T *out, float *lse,
+                                hipStream_t st)
 {
-    by_shape<kFwd>(d > e ? d : e, [&](auto g) {
+    const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale);
+    by_shape<T, kFwd>(d > e ? d : e, [&](auto g) {
         using G = decltype(g);
-        const PatchLaunch l = patch_launch<G>(t, t.side_out, nbh, d, e, scale);
         hipLaunchKernelGGL((nattn_fwd_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(Shared<G>), st, l.a, q, k, v, out, lse);
     });
 }
-template <int MODE>
-void PatchSet<MODE>::dq(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k, const float *v,
-                        const float *o, const float *lse, const float *go, float *dq, float *Dws, hipStream_t st)
+template <class T, int MODE>
+void PatchKernels<T, MODE>::dq(const S2DeviceTables &t, int nbh, int d, int e, float scale, const T *q, const T *k, const T *v, const T *o,
+                               const float *lse, const T *go, T *dq, float *Dws, hipStream_t st)
 {
-    by_shape<kDq>(d > e ? d : e, [&](auto g) {
+    const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale);
+    by_shape<T, kDq>(d > e ? d : e, [&](auto g) {
         using G = decltype(g);
-        const PatchLaunch l = patch_launch<G>(t, t.side_out, nbh, d, e, scale);
         hipLaunchKernelGGL((nattn_bwd_dq_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(SharedDq<G>), st, l.a, q, k, v, o, lse, go, dq, Dws);
     });
 }
-template <int MODE>
-void PatchSet<MODE>::dkdv(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k, const float *v,
-                          const float *lse, const float *go, const float *Dws, float *dk, float *dv, hipStream_t st)
+template <class T, int MODE>
+void PatchKernels<T, MODE>::dkdv(const S2DeviceTables &t, int nbh, int d, int e, float scale, const T *q, const T *k, const T *v, const float *lse,
+                                 const T *go, const float *Dws, T *dk, T *dv, hipStream_t st)
 {
-    by_shape<kDkdv>(d > e ? d : e, [&](auto g) {
+    const PatchLaunch l = patch_launch(t, t.side_in, nbh, d, e, scale);
+    by_shape<T, kDkdv>(d > e ? d : e, [&](auto g) {
         using G = decltype(g);
-        const PatchLaunch l = patch_launch<G>(t, t.side_in, nbh, d, e, scale);
         hipLaunchKernelGGL((nattn_bwd_dkdv_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(SharedDkdv<G>), st, l.a, q, k, v, lse, go, Dws, dk, dv);
     });
 }

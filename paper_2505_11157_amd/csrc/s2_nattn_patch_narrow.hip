@@ -1,4 +1,4 @@
-// float32 patch kernels, staging mode kNarrow.
+// Patch kernels of float32 tensors, staging mode kNarrow.
 #include "s2_nattn_patch_impl.h"
 
-template struct PatchSet<kNarrow>;
+template struct PatchKernels<float, kNarrow>;

@@ -1,4 +1,4 @@
-// float32 patch kernels, staging mode kRagged.
+// Patch kernels of float32 tensors, staging mode kRagged.
 #include "s2_nattn_patch_impl.h"
 
-template struct PatchSet<kRagged>;
+template struct PatchKernels<float, kRagged>;

@@ -1,4 +1,4 @@
-// float32 patch kernels, staging mode kWide.
+// Patch kernels of float32 tensors, staging mode kWide.
 #include "s2_nattn_patch_impl.h"
 
-template struct PatchSet<kWide>;
+template struct PatchKernels<float, kWide>;

@@ -19,18 +19,20 @@ static int check(const s2_grid::Patches &p, const std::vector<int> &blo, const s
     const int n_own = int(blo.size()), bmax = int(arc.size() / blo.size());
     std::vector<int> seen(size_t(n_own) * nU, 0);
     for (const int2 &wg : p.list) {
-        const int4 s0 = p.seg[2 * wg.x], s1 = p.seg[2 * wg.x + 1];
-        const int rows = 1 << s0.y, W = 16 >> s0.y, total = s1.x;
-        if (s0.w > 128) return 1;
+        const int4 s0 = p.seg[2 * wg.x];
+        const int rows = 1 << s0.y, W = 16 >> s0.y;
         for (int wave = 0; wave < kS2PatchWaves; ++wave)
             for (int n = 0; n < 16; ++n) {
                 const int own = s0.x + n / W, wc = wg.y + wave * W, u = wc + n % W;
                 if (own >= n_own || u >= nU || n / W >= rows) continue;
                 ++seen[size_t(own) * nU + u];
                 std::map<std::pair<int, int>, int> met;
-                for (int i = 0; i < s0.w; ++i) {
-                    const S2PatchRow &r = p.rows[s1.y + i];
-                    const int end = i + 1 < s0.w ? p.rows[s1.y + i + 1].before : total;
+                for (int part = wg.x;; ++part) {
+                const int4 t0 = p.seg[2 * part], t1 = p.seg[2 * part + 1];
+                if (t0.x != s0.x || t0.y != s0.y || t0.w > kS2PatchRows) return 1;
+                for (int i = 0; i < t0.w; ++i) {
+                    const S2PatchRow &r = p.rows[t1.y + i];
+                    const int end = i + 1 < t0.w ? p.rows[t1.y + i + 1].before : t1.x;
                     for (int X = r.before; X < end; ++X) {
                         const int col = r.col + 4 * X + wg.y, d = col + 3 - wc - int(short(r.uni & 0xffff));
                         if (col < -2 * nU || col + 3 + 2 * nU >= 1 << 22 || col >= 1 << 17 || col < -(1 << 17)) return 2;    // what wrap_col and a list entry hold
@@ -39,9 +41,11 @@ static int check(const s2_grid::Patches &p, const std::vector<int> &blo, const s
                         for (int j = 0; j < 4; ++j)
                             if (rel + j < (a >> 16)) {
                                 if (!listed) return 3;
-                                ++met[{s0.z + i, ((col + j) % nU + nU) % nU}];
+                                ++met[{t0.z + i, ((col + j) % nU + nU) % nU}];
                             }
                     }
+                }
+                if (t1.z == 0) break;
                 }
                 size_t want = 0;
                 for (int b = 0; b < bn[own]; ++b) {
