@@ -1,5 +1,5 @@
-// Products with channel matrices (1x1 convolutions), float32 on the matrix cores (v_mfma_f32_32x32x2_f32), shared by the
-// attention sub-block and the DISCO convolution:
+// Products with channel matrices (1x1 convolutions) of float32 tensors on the bf16 matrix cores (three terms per value, s2_bf16_terms.h;
+// v_mfma_f32_32x32x16_bf16), shared by the attention sub-block and the DISCO convolution:
 //   forward / input gradients   C[b][m][n] = sum_k A(m, k) X[b][k][n] + bias[m] + R[b][m][n]
 //   weight gradients            dW[m][k] = sum_{b, n} dY[b][m][n] X[b][k][n],  dbias[m] = sum_{b, n} dY[b][m][n]
 // One launch takes up to three products side by side (q, k and v from the same X), and a forward product may sum over up
@@ -7,71 +7,98 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "s2_bf16_terms.h"
 #include "s2_internal.h"
 
 namespace {
 
+using namespace s2terms;
+
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
-__device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c)
+__device__ __forceinline__ f32x16 mma32(bf16x8 a, bf16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
+
+template <int MT>
+__device__ __forceinline__ bool not_finite(const f32x16 (&acc)[MT])
 {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+    float t = 0.f;
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) t = fmaf(acc[i][e], 0.f, t);
+    return __builtin_expect(!(t == 0.f), 0);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
 // Products with a matrix.  A workgroup of four wavefronts owns 32 MT rows and 128 grid points; a wavefront owns 32 of
-// the points and all the rows (MT accumulators).  The matrix goes through LDS in double-buffered slices of 16 along k
-// ([k][m], rows 33 mod 64 words apart: the two k rows one instruction reads lie 33 banks apart, and the transposing
-// store spreads over the banks); X does not: lane (column, half) reads X[k0 + 2 j + half][n0 + column] straight into
-// the operand, a whole slice ahead of its use, every element once, in 128-byte row pieces.
-// Bound by the matrix cores (MT instructions of 64 cycles per LDS word and lane), 60 to 67 % busy over the launch by the counters.  The rows per
-// workgroup follow M, so 64-row products leave no half of a tile empty, and any k fits: 64 x 576 onto 4 x 33024 points went
-// from 230 us (128-row tiles, X through LDS) to 118 us, three 128 x 128 products of one X from 3 x 56 us to 135 us, their
-// sum back from 167 us to 125 us.
+// the points and all the rows (MT accumulators).  The matrix goes through LDS in double-buffered slices of 16 along k, cut into
+// its three terms on the way ([term][m][16 k], rows 48 bytes apart: the 16 rows that one 16-byte read serves together lie in
+// different banks); X does not: lane (column, half) reads X[k0 + 8 half + j][n0 + column] straight into registers, a whole slice
+// ahead of its use, every element once, in 128-byte row pieces, and cuts it there.
+// Bound by the matrix cores (6 MT instructions of 32 cycles per slice and wavefront; eight fp32 ones of 64 cycles before) and, for
+// few products of one X, by the memory X and the results pass through.  The rows per
+// workgroup follow M, so 64-row products leave no half of a tile empty, and any k fits.  On the fp32 matrix cores
+// before: 64 x 576 onto 4 x 33024 points 112 -> 82 us, three 128 x 128 products of one X 136 -> 101 us, their sum back 125 -> 92 us.
+// (In a loop of whole layers part of that is lost: the card then lowers its clock, 2.37 -> 2.14 GHz with these products.)
 constexpr int kSlice = 16;
-constexpr int slice_pitch(int m) { return (m + 30) / 64 * 64 + 33; }      // smallest p >= m with p = 33 mod 64
+constexpr int kRow = 24;                                   // bf16 values per row of a slice in LDS
 
 template <bool TRANS, int MT>
-__device__ __forceinline__ void product_strip(const S2ChannelProduct &a, int strip, int strips_per_batch, int set, int m0, float *lds)
+__device__ __forceinline__ void product_strip(const S2ChannelProduct &a, int strip, int strips_per_batch, int set, int m0, __bf16 *lds)
 {
-    constexpr int MB = 32 * MT, PITCH = slice_pitch(MB), PIECES = MB * kSlice / 4, NP = (PIECES + 255) / 256;
+    constexpr int MB = 32 * MT, PIECES = MB * kSlice / (TRANS ? 8 : 4), NP = (PIECES + 255) / 256, TERM = MB * kRow, BUF = kTerms * TERM;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, kk = lane >> 5;
     const int b = strip / strips_per_batch, n = (strip - b * strips_per_batch) * 128 + wave * 32 + col;
     const bool ok = n < a.N;
-    unsigned lane_off = (unsigned(kk) * unsigned(a.N) + unsigned(ok ? n : 0)) * 4u;      // past the last column: column 0, not stored
+    unsigned lane_off = (unsigned(8 * kk) * unsigned(a.N) + unsigned(ok ? n : 0)) * 4u;      // past the last column: column 0, not stored
     asm volatile("" : "+v"(lane_off));
-    const size_t step = size_t(2) * a.N * sizeof(float);
+    const size_t step = size_t(a.N) * sizeof(float);
     const int M = a.M, K = a.K;
 
-    // where the thread's pieces of a slice of the matrix come from (rows past M: the last one, feeding results that are not
-    // stored) and go to
-    float4 rw[NP];
+    // where the thread's pieces of a slice of the matrix (4 k of a row; TRANS: 2 k of 4 rows) come from (rows past M: the last
+    // one, feeding results that are not stored) and go to
+    float4 rw[NP][TRANS ? 2 : 1];
     unsigned w_off[NP], w_at[NP];
 #pragma unroll
     for (int j = 0; j < NP; ++j) {
         const int i = min(tid + 256 * j, PIECES - 1);
         if constexpr (TRANS) {
-            const int k = i / (8 * MT), m = 4 * (i % (8 * MT));
+            const int k = 2 * (i / (8 * MT)), m = 4 * (i % (8 * MT));
             w_off[j] = unsigned(k) * unsigned(M) + unsigned(min(m0 + m, M - 4));
-            w_at[j] = k * PITCH + m;
+            w_at[j] = m * kRow + k;
         } else {
             const int m = i >> 2, k = 4 * (i & 3);
             w_off[j] = unsigned(min(m0 + m, M - 1)) * unsigned(K) + unsigned(k);
-            w_at[j] = k * PITCH + m;
+            w_at[j] = m * kRow + k;
         }
     }
     auto load_w = [&](const float *W) {
 #pragma unroll
-        for (int j = 0; j < NP; ++j) rw[j] = *reinterpret_cast<const float4 *>(W + w_off[j]);
+        for (int j = 0; j < NP; ++j) {
+            rw[j][0] = *reinterpret_cast<const float4 *>(W + w_off[j]);
+            if constexpr (TRANS) rw[j][1] = *reinterpret_cast<const float4 *>(W + M + w_off[j]);
+        }
     };
     auto store_w = [&](int buf) {
 #pragma unroll
         for (int j = 0; j < NP; ++j) {
             if (256 * (j + 1) > PIECES && tid + 256 * j >= PIECES) break;
-            float *d = lds + buf * kSlice * PITCH + w_at[j];
-            constexpr int S = TRANS ? 1 : PITCH;
-            d[0] = rw[j].x; d[S] = rw[j].y; d[2 * S] = rw[j].z; d[3 * S] = rw[j].w;
+            __bf16 *d = lds + buf * BUF + w_at[j];
+            if constexpr (TRANS) {
+                float x[4] = {rw[j][0].x, rw[j][0].y, rw[j][0].z, rw[j][0].w}, y[4] = {rw[j][1].x, rw[j][1].y, rw[j][1].z, rw[j][1].w};
+#pragma unroll
+                for (int t = 0; t < kTerms; ++t)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) *reinterpret_cast<unsigned *>(d + t * TERM + i * kRow) = cut_off(x[i], y[i]);
+            } else {
+                float x[4] = {rw[j][0].x, rw[j][0].y, rw[j][0].z, rw[j][0].w};
+#pragma unroll
+                for (int t = 0; t < kTerms; ++t) {
+                    const unsigned lo = cut_off(x[0], x[1]), hi = cut_off(x[2], x[3]);
+                    *reinterpret_cast<uint2 *>(d + t * TERM) = make_uint2(lo, hi);
+                }
+            }
         }
     };
     f32x16 acc[MT];
@@ -80,13 +107,13 @@ __device__ __forceinline__ void product_strip(const S2ChannelProduct &a, int str
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
 
-    float xa[kSlice / 2], xb[kSlice / 2];
-    auto fetch = [&](float (&x)[kSlice / 2], const char *r, size_t d) {
+    float xa[8], xb[8];
+    auto fetch = [&](float (&x)[8], const char *r, size_t d) {
         // a uniform running row pointer plus one 32-bit lane offset, opaque so that no 64-bit address per load is kept;
         // explicitly global: a flat load also counts as an LDS access, and waits for LDS would wait for it
         asm volatile("" : "+s"(r));
 #pragma unroll
-        for (int j = 0; j < kSlice / 2; ++j) {
+        for (int j = 0; j < 8; ++j) {
             x[j] = *(const __attribute__((address_space(1))) float *)(r + lane_off);
             r += d;
         }
@@ -103,7 +130,7 @@ __device__ __forceinline__ void product_strip(const S2ChannelProduct &a, int str
         if (k0 + kSlice < K) {
             k0 += kSlice;
             W += TRANS ? size_t(kSlice) * M : kSlice;
-            row += kSlice / 2 * step;
+            row += kSlice * step;
             return true;
         }
         if (seg + 1 >= end) return false;
@@ -114,28 +141,22 @@ __device__ __forceinline__ void product_strip(const S2ChannelProduct &a, int str
     };
     // Nothing branches around the requests (the compiler would wait for all of them where the paths meet): behind the
     // last slice they go to one address, for nothing.
-    auto slice = [&](float (&cur)[kSlice / 2], float (&nxt)[kSlice / 2]) {
+    auto slice = [&](float (&cur)[8], float (&nxt)[8]) {
         const bool more = advance();
         load_w(W);
         fetch(nxt, row, more ? step : 0);
         __builtin_amdgcn_sched_barrier(0);          // the requests stay in front of the arithmetic they overlap
-        const float *wl = lds + buf * kSlice * PITCH + kk * PITCH + col;
-        float w[2][4][MT];                          // operands of the matrix, read four steps ahead of their instructions
-        auto read = [&](int g) {
+        const __bf16 *wl = lds + buf * BUF + col * kRow + 8 * kk;
+        bf16x8 x[kTerms];
+        cut(cur, x);
+        constexpr int order[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};      // smallest products first
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+        for (int i = 0; i < MT; ++i) {
+            bf16x8 w[kTerms];
 #pragma unroll
-                for (int i = 0; i < MT; ++i) w[g][j][i] = wl[2 * (4 * g + j) * PITCH + 32 * i];
-        };
-        read(0);
+            for (int t = 0; t < kTerms; ++t) w[t] = *reinterpret_cast<const bf16x8 *>(wl + t * TERM + 32 * i * kRow);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            if (j == 2) {
-                read(1);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-            for (int i = 0; i < MT; ++i) acc[i] = mfma32(w[j >> 2][j & 3][i], cur[j], acc[i]);
+            for (int p = 0; p < 6; ++p) acc[i] = mma32(w[order[p][0]], x[order[p][1]], acc[i]);
         }
         store_w(buf ^ 1);
         __syncthreads();
@@ -144,6 +165,19 @@ __device__ __forceinline__ void product_strip(const S2ChannelProduct &a, int str
     };
     while (slice(xa, xb) && slice(xb, xa)) {}
     if (!ok) return;
+    if (not_finite(acc)) {
+        // an infinite (or nearly: it rounds to one) factor: its terms give NaN, so this column is summed again as it stands
+#pragma unroll 1
+        for (int m = m0 + 4 * kk; m < min(m0 + MB, M); m = (m & 3) == 3 ? m + 5 : m + 1) {
+            float t = 0.f;
+            for (int i = a.nset > 1 ? set : 0; i < end; ++i)
+                for (int k = 0; k < K; ++k)
+                    t = fmaf(TRANS ? a.W[i][size_t(k) * M + m] : a.W[i][size_t(m) * K + k], a.X[i][(size_t(b) * K + k) * a.N + n], t);
+            const size_t at = (size_t(b) * M + m) * a.N + n;
+            a.C[set][at] = (t + (a.bias[set] ? a.bias[set][m] : 0.f)) + (a.R ? a.R[at] : 0.f);
+        }
+        return;
+    }
     // per half row block all the reads (bias, residual) are issued before the first store, so that they overlap
     const float *bias = a.bias[set];
     float *Cb = a.C[set] + size_t(b) * M * a.N + n;
@@ -172,7 +206,7 @@ template <bool TRANS, int MT>
 __global__ void __launch_bounds__(256, MT == 1 ? 8 : 4)
 channel_product(S2ChannelProduct a, int strips_per_batch, int nstrips, int mblocks, int whole_groups)
 {
-    extern __shared__ float lds[];
+    extern __shared__ __attribute__((aligned(16))) __bf16 lds[];
     const int parts = a.nset * mblocks, whole = whole_groups * 8 * parts, lo = blockIdx.x & 7;
     int id = blockIdx.x;
     if (id < whole || MT == 1) {
@@ -190,20 +224,23 @@ channel_product(S2ChannelProduct a, int strips_per_batch, int nstrips, int mbloc
 // ---------------------------------------------------------------------------------------------------------------
 // Weight gradients: partial sums over a share of (batch, grid point), added in a fixed order by a second launch, so every
 // result is bit-reproducible.  A workgroup of WR x WN wavefronts owns 32 MT WR rows of dY and 32 WN rows of X, a
-// wavefront 32 MT rows of dY and 32 of X; slices of 32 grid points (whole 128-byte lines of every row) go through double-buffered
-// LDS, row by row, 36 words apart: stores and loads are 16 bytes and free of bank conflicts.  Instruction j of a group
-// of eight points contracts over points j and 4 + j, so that one 16-byte read per operand serves four instructions.  The
-// row sums of dY come from the pieces on their way to LDS.
-// Bound by the matrix cores.  Rows per workgroup by M, columns by whichever width pads K least: 64 x 576 over 4 x 33024
-// points 230 -> 111 us, three 128 x 128 3 x 56 -> 135 us (with the row sums that used to be three more launches).
-constexpr int kPoints = 32, kPitch = kPoints + 4;
+// wavefront 32 MT rows of dY and 32 of X; slices of 32 grid points (whole 128-byte lines of every row) are cut into three terms on
+// their way to LDS: [term][half of the points][row][16 points], rows 48 bytes apart, so that the 16-byte operand reads are
+// free of bank conflicts.  The next slice is on its way to the registers meanwhile.  The row sums of dY come from the pieces on
+// their way to LDS.
+// Bound by the matrix cores (12 MT instructions of 32 cycles per slice and wavefront; 16 fp32 ones of 64 cycles before) and the cutting.
+// Rows per workgroup by M, columns by whichever width pads K least.  64 x 576 over 4 x 33024 points: as long as on
+// the fp32 matrix cores (109 us; 12 wavefronts cut 256 rows for two of them on a compute unit), three 128 x 128: 135 -> 100 us.
+constexpr int kPoints = 32;
+constexpr int wgrad_lds(int rows) { return kTerms * 2 * rows * kRow * 2; }       // bytes of LDS
 
 template <int MT, int WR, int WN>
 __global__ void __launch_bounds__(64 * WR * WN)
 channel_wgrad(S2ChannelGrad a, int ktiles, int mblocks, int nsplit, float *__restrict__ part)
 {
     constexpr int YR = 32 * MT * WR, ROWS = YR + 32 * WN, NT = 64 * WR * WN, NP = (ROWS * 8 + NT - 1) / NT, NA = (YR * 8 + NT - 1) / NT;
-    __shared__ __attribute__((aligned(16))) float S[2][ROWS * kPitch];
+    constexpr int HALF = ROWS * kRow, TERM = 2 * HALF;
+    __shared__ __attribute__((aligned(16))) __bf16 lds[kTerms * TERM];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, kk = lane >> 5, M = a.M, K = a.K, N = a.N;
     const int wr = wave % WR, wn = wave / WR;
@@ -246,14 +283,19 @@ channel_wgrad(S2ChannelGrad a, int ktiles, int mblocks, int nsplit, float *__res
             r[j] = *reinterpret_cast<const float4 *>((isy ? y : x) + (off[j] - back));
         }
     };
-    auto store = [&](int buf) {
+    auto store = [&]() {
 #pragma unroll
         for (int j = 0; j < NP; ++j) {
             const int row = min((tid >> 3) + (NT / 8) * j, ROWS - 1);
             float4 v = r[j];
             if (!in) v = make_float4(0.f, 0.f, 0.f, 0.f);
             if (j < NA) bsum[j < NA ? j : 0] += (v.x + v.y) + (v.z + v.w);
-            *reinterpret_cast<float4 *>(&S[buf][row * kPitch + pc]) = v;
+            __bf16 *d = lds + (pc >> 4) * HALF + row * kRow + (pc & 15);
+#pragma unroll
+            for (int t = 0; t < kTerms; ++t) {
+                const unsigned lo = cut_off(v.x, v.y), hi = cut_off(v.z, v.w);
+                *reinterpret_cast<uint2 *>(d + t * TERM) = make_uint2(lo, hi);
+            }
         }
     };
     f32x16 acc[MT];
@@ -261,43 +303,48 @@ channel_wgrad(S2ChannelGrad a, int ktiles, int mblocks, int nsplit, float *__res
     for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
-    if (s < s_end) {
-        load(s);
-        store(0);
-    }
-    __syncthreads();
-    int buf = 0;
+    if (s < s_end) load(s);
     for (; s < s_end; ++s) {
-        const bool more = s + 1 < s_end;
-        if (more) {
+        __syncthreads();                    // everybody is done with the slice before
+        store();
+        __syncthreads();
+        if (s + 1 < s_end) {
             load(s + 1);
             __builtin_amdgcn_sched_barrier(0);
         }
-        const float *sb = &S[buf][col * kPitch + 4 * kk], *ya = sb + wr * 32 * MT * kPitch, *xa = sb + (YR + 32 * wn) * kPitch;
+        const __bf16 *sb = lds + col * kRow + 8 * kk, *ya = sb + wr * 32 * MT * kRow, *xa = sb + (YR + 32 * wn) * kRow;
+        constexpr int order[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};      // smallest products first
 #pragma unroll
-        for (int q = 0; q < kPoints / 8; ++q) {
-            const float4 x4 = *reinterpret_cast<const float4 *>(xa + 8 * q);
-            float4 y4[MT];
+        for (int q = 0; q < 2; ++q) {
+            bf16x8 x[kTerms];
 #pragma unroll
-            for (int i = 0; i < MT; ++i) y4[i] = *reinterpret_cast<const float4 *>(ya + 32 * i * kPitch + 8 * q);
+            for (int t = 0; t < kTerms; ++t) x[t] = *reinterpret_cast<const bf16x8 *>(xa + t * TERM + q * HALF);
 #pragma unroll
-            for (int i = 0; i < MT; ++i) acc[i] = mfma32(y4[i].x, x4.x, acc[i]);
+            for (int i = 0; i < MT; ++i) {
+                bf16x8 y[kTerms];
 #pragma unroll
-            for (int i = 0; i < MT; ++i) acc[i] = mfma32(y4[i].y, x4.y, acc[i]);
+                for (int t = 0; t < kTerms; ++t) y[t] = *reinterpret_cast<const bf16x8 *>(ya + t * TERM + q * HALF + 32 * i * kRow);
 #pragma unroll
-            for (int i = 0; i < MT; ++i) acc[i] = mfma32(y4[i].z, x4.z, acc[i]);
-#pragma unroll
-            for (int i = 0; i < MT; ++i) acc[i] = mfma32(y4[i].w, x4.w, acc[i]);
-        }
-        if (more) {
-            store(buf ^ 1);
-            __syncthreads();
-            buf ^= 1;
+                for (int p = 0; p < 6; ++p) acc[i] = mma32(y[order[p][0]], x[order[p][1]], acc[i]);
+            }
         }
     }
     float *P = part + (size_t(set) * nsplit + split) * (size_t(M) * K + M);
     const int k = k0 + 32 * wn + col;
-    if (k < K) {
+    if (k < K && not_finite(acc)) {              // as in the products: this column summed as it stands
+#pragma unroll 1
+        for (int i = 0; i < 16 * MT; ++i) {
+            const int m = m0 + 32 * (MT * wr + (i >> 4)) + 8 * (i >> 2 & 3) + 4 * kk + (i & 3);
+            if (m >= M) continue;
+            float t = 0.f;
+            for (long c = slices * split / nsplit; c < s_end; ++c) {
+                const int b = int(c / per), n = int(c - long(b) * per) * kPoints;
+                const float *y = dY + (size_t(b) * M + m) * N, *x = X + (size_t(b) * K + k) * N;
+                for (int p = n; p < min(n + kPoints, N); ++p) t = fmaf(y[p], x[p], t);
+            }
+            P[size_t(m) * K + k] = t;
+        }
+    } else if (k < K) {
 #pragma unroll
         for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -374,7 +421,7 @@ inline GradPlan grad_plan(int M, int K, int nset)
     p.wn = col_waves(p.mt, K);
     p.mblocks = (M + 32 * p.mt - 1) / (32 * p.mt);
     p.ktiles = (K + 32 * p.wn - 1) / (32 * p.wn);
-    const int lds = 2 * 32 * (p.mt + p.wn) * kPitch * int(sizeof(float)), want = 256 * std::min(4, 160 * 1024 / lds);
+    const int lds = wgrad_lds(32 * (p.mt + p.wn)), want = 256 * std::min(4, 160 * 1024 / lds);
     p.nsplit = std::max(8, want / (p.mblocks * p.ktiles * nset) / 8 * 8);
     return p;
 }

@@ -44,6 +44,7 @@
 #include <type_traits>
 #include <cstdlib>
 
+#include "s2_bf16_terms.h"
 #include "s2_internal.h"
 #include "s2_nattn_band.h"
 #include "s2_nattn_exact.h"
@@ -53,16 +54,12 @@
 namespace {
 
 using namespace s2walk;
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+using namespace s2terms;
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
 
 typedef unsigned short bf16raw;      // storage of a bf16 tensor
-constexpr int kTerms = 3;            // bf16 terms of a float32 value
 constexpr int kDead = kMaxRows;      // the row of a list entry that stands for no chunk: no owner has neighbors on it
 constexpr unsigned kAgain = 0x7fc0a9a1u;     // in place of the results of an owner that s2_nattn_exact.h evaluates: not to be stored
 
@@ -269,30 +266,6 @@ struct Chunks {
         cnt = __popcll(met >> sh & (~0ull >> (64 - G::CAP)));
     }
 };
-
-// two float32 values as bf16 (low half: a), rounded to nearest even, and what that leaves of them
-__device__ __forceinline__ unsigned cut_off(float &a, float &b)
-{
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
-    asm("" : "+v"(u));       // else the compiler converts each of the two once more for what follows
-    a -= __builtin_bit_cast(float, u << 16);
-    b -= __builtin_bit_cast(float, u & 0xffff0000u);
-    return u;
-}
-// float32 values as three bf16 terms, which together hold them exactly
-__device__ __forceinline__ void cut(const float (&x)[8], bf16x8 (&b)[kTerms])
-{
-    u32x4 u[kTerms];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        float lo = x[2 * i], hi = x[2 * i + 1];
-#pragma unroll
-        for (int k = 0; k < kTerms; ++k) u[k][i] = cut_off(lo, hi);
-    }
-#pragma unroll
-    for (int k = 0; k < kTerms; ++k) b[k] = __builtin_bit_cast(bf16x8, u[k]);
-}
 
 // One tensor's stage: from memory to registers, and (float32: cut into three terms) on to LDS.
 template <class G, int MODE>
