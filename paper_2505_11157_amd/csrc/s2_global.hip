@@ -229,13 +229,19 @@ __device__ __forceinline__ bool xcd_unit(int nunits, int &unit)
 // with x = log2(e) scale q.k, and the reference m_i follows the bare logits of the keys of positive weight (it moves
 // only when a logit exceeds it by more than 2^8).  lse_i = ln 2 (m_i + log2 l_i) + ln max omega.
 // UNIFORM_W: the longitude count is a multiple of 32, so a 32-key tile never straddles two latitudes.
-template <bool UNIFORM_W>
+// SPLIT = 2 is for launches with too few workgroups to fill the chip: the four wavefronts are two pairs, each pair owns
+// the same 64 queries and takes every other 32-key tile of a stage, and the pairs' (o, m, l) meet in LDS behind the
+// last stage, so a query's serial chain over the keys is half as long and the launch has twice the workgroups
+// (46 x 90, four heads: 94 us with SPLIT = 1, 64 us with SPLIT = 2; see split_waves for the line).
+template <bool UNIFORM_W, int SPLIT>
 __global__ void __launch_bounds__(256, 3)
 global_fwd(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const bf16raw *__restrict__ vt,
            const float *__restrict__ wtok, bf16raw *__restrict__ out, float *__restrict__ lse, int N, int Npad,
            int nqb, int nunits, float c2, float ln_wref)
 {
+    static_assert(SPLIT == 1 || SPLIT == 2, "a stage holds two key tiles");
     constexpr int kStage = 2 * kTileBytes + 256;     // K row tile, V^T column tile, 64 weights
+    constexpr int TILES = 4 / SPLIT;                 // query tiles of the workgroup
     __shared__ __attribute__((aligned(16))) char buf0[kStage];
     __shared__ __attribute__((aligned(16))) char buf1[kStage];
     int unit;
@@ -243,7 +249,7 @@ global_fwd(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const b
     const int bh = unit / nqb, qb = unit - bh * nqb;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, col = lane & 31, hl = lane >> 5;
-    const int qi = qb * 128 + wave * 32 + col;
+    const int part = wave / TILES, qi = (qb * TILES + wave % TILES) * 32 + col;
     bf16x8 qop[4];
     {
         const bf16raw *qp = q + (size_t(bh) * N + min(qi, N - 1)) * kD + 8 * hl;
@@ -256,15 +262,17 @@ global_fwd(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const b
     const bf16raw *vb = vt + size_t(bh) * kD * Npad;
     const int nst = Npad >> 6;
     auto request = [&](char *buf, int st) {
-        copy_row_tile(kb, 64 * st, N, buf, wave, lane);
-        copy_col_tile(vb, 64 * st, Npad, buf + kTileBytes, wave, lane);
-        if (wave == 0) copy_floats(wtok + 64 * st, buf + 2 * kTileBytes, lane);
+        const int t0 = 64 * st;
+        copy_row_tile(kb, t0, N, buf, wave, lane);
+        copy_col_tile(vb, t0, Npad, buf + kTileBytes, wave, lane);
+        if (wave == 0) copy_floats(wtok + t0, buf + 2 * kTileBytes, lane);
     };
-    bool started = false;      // has a tile with a key of positive weight been seen (wavefront-uniform)
+    bool based = false;        // has the query met a logit above -infinity: only then does m mean anything
     auto stage = [&](const char *cur, char *nxt, int st) {
         if (st + 1 < nst) request(nxt, st + 1);
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
+        for (int it = 0; it < 2 / SPLIT; ++it) {
+            const int kt = SPLIT == 1 ? it : part;
             // Keys of weight zero (the pole row of the grid of App. A.1, the padding behind the last token) have no
             // term in the sums, so they must not enter the reference maximum either: a tile without a live key is
             // skipped, and in a mixed tile (longitude count not a multiple of 32) their logits are set to -inf.
@@ -301,16 +309,15 @@ global_fwd(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const b
                 e[i] = __builtin_amdgcn_exp2f(x[i]);
                 psum += UNIFORM_W ? e[i] : e[i] * wk[i];
             }
-            const bool first = !started;
-            started = true;
             // the two half-wavefronts of a query exchange their maxima only when the reference has to move
-            if (first || __any(!(psum <= 256.f))) {
+            if (!__all(based) || __any(!(psum <= 256.f))) {
                 float mx = -INFINITY;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) mx = fmaxf(mx, x[i]);
                 mx = fmaxf(mx, __shfl_xor(mx, 32));
-                const float delta = first ? mx : (mx > 8.f ? mx : 0.f);
-                const float corr = first ? 1.f : __builtin_amdgcn_exp2f(-delta);
+                const float delta = based ? (mx > 8.f ? mx : 0.f) : (mx > -INFINITY ? mx : 0.f);
+                const float corr = based ? __builtin_amdgcn_exp2f(-delta) : 1.f;
+                based |= mx > -INFINITY;
                 m += delta;
                 l *= corr;
                 psum = 0.f;
@@ -340,7 +347,34 @@ global_fwd(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const b
         stage(buf0, buf1, st);
         if (st + 1 < nst) stage(buf1, buf0, st + 1);
     }
-    const float lt = l + __shfl_xor(l, 32);
+    float lt = l + __shfl_xor(l, 32);
+    if constexpr (SPLIT == 2) {
+        // every wavefront is past its last stage: the buffers hold the second pair's results, one wavefront each
+        constexpr int kSlot = 34 * 64;
+        static_assert(kStage >= kSlot * 4, "LDS of the partial results");
+        float *slot = reinterpret_cast<float *>(wave & 1 ? buf1 : buf0) + lane;
+        if (part == 1) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                slot[i * 64] = o0[i];
+                slot[(16 + i) * 64] = o1[i];
+            }
+            slot[32 * 64] = based ? m : -INFINITY;
+            slot[33 * 64] = lt;
+        }
+        __syncthreads();
+        if (part == 1) return;
+        // A pair without a live key has o = l = 0 and the factor 0; NaN stays NaN through the sums.
+        const float other = slot[32 * 64], top = fmaxf(based ? m : -1e30f, other);
+        const float f = based ? __builtin_amdgcn_exp2f(m - top) : 1.f, g = __builtin_amdgcn_exp2f(other - top);
+        lt = fmaf(slot[33 * 64], g, lt * f);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            o0[i] = fmaf(slot[i * 64], g, o0[i] * f);
+            o1[i] = fmaf(slot[(16 + i) * 64], g, o1[i] * f);
+        }
+        m = top;
+    }
     if (qi < N) {
         const float inv = 1.f / lt;
         bf16raw *ob = out + (size_t(bh) * N + qi) * kD + 4 * hl;
@@ -356,6 +390,28 @@ global_fwd(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const b
     }
 }
 
+// The sums of a workgroup's second pair of wavefronts are added to those of the first, through the stage buffers (one
+// for each wavefront of a pair; every wavefront is past its last stage).  True for the second pair, which is done.
+template <int TERMS, int BYTES>
+__device__ __forceinline__ bool join_pairs(f32x16 *const (&sums)[TERMS], char *buf, int part, int lane)
+{
+    static_assert(BYTES >= TERMS * 16 * 64 * 4, "LDS of the partial sums");
+    float *slot = reinterpret_cast<float *>(buf) + lane;
+    if (part == 1) {
+#pragma unroll
+        for (int t = 0; t < TERMS; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) slot[(16 * t + i) * 64] = (*sums[t])[i];
+    }
+    __syncthreads();
+    if (part == 1) return true;
+#pragma unroll
+    for (int t = 0; t < TERMS; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) (*sums[t])[i] += slot[(16 * t + i) * 64];
+    return false;
+}
+
 // Backward (App. B.4 with every token in every neighborhood).  With w_j = omega_j / max omega and
 // L_i = log2(e) (lse_i - ln max omega):  p_ij = w_j pt_ij,  pt_ij = 2^(log2(e) scale q_i.k_j - L_i),
 // dS_ij = p_ij (dout_i.v_j - D_i).  The factor w_j never enters the inner loops: the key-side kernel
@@ -365,6 +421,8 @@ global_fwd(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const b
 // Key side: a workgroup owns 128 keys (one 32-key tile per wavefront) and streams the queries in stages
 // of 64: Q and dout token-major (for S = Q K^T and dP = dout V^T, which land with lane = key,
 // registers = 16 queries), Q^T and dout^T channel-major (dV^T += dout^T Pt, dK^T += Q^T dSt), L and D.
+// SPLIT = 2: two pairs of wavefronts take every other query tile of the same 64 keys, and their sums meet in LDS.
+template <int SPLIT>
 __global__ void __launch_bounds__(256, 2)
 global_bwd_dkdv(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const bf16raw *__restrict__ v,
                 const bf16raw *__restrict__ go, const bf16raw *__restrict__ qt, const bf16raw *__restrict__ got,
@@ -380,7 +438,8 @@ global_bwd_dkdv(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, co
     const int bh = unit / nkb, kb = unit - bh * nkb;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, col = lane & 31, hl = lane >> 5;
-    const int ki = kb * 128 + wave * 32 + col;
+    constexpr int TILES = 4 / SPLIT;                 // key tiles of the workgroup
+    const int part = wave / TILES, ki = (kb * TILES + wave % TILES) * 32 + col;
     bf16x8 kop[4], vop[4];
     {
         const size_t row = (size_t(bh) * N + min(ki, N - 1)) * kD + 8 * hl;
@@ -404,7 +463,8 @@ global_bwd_dkdv(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, co
     auto stage = [&](const char *cur, char *nxt, int st) {
         if (st + 1 < nst) request(nxt, st + 1);
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int it = 0; it < 2 / SPLIT; ++it) {
+            const int h = SPLIT == 1 ? it : part;
             const float *Lp = reinterpret_cast<const float *>(cur + 4 * kTileBytes) + 32 * h + 16 * hl;
             // dP starts from -D_i (the 16 queries this lane's registers stand for)
             f32x16 s = {0}, dp;
@@ -446,6 +506,10 @@ global_bwd_dkdv(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, co
         stage(buf0, buf1, st);
         if (st + 1 < nst) stage(buf1, buf0, st + 1);
     }
+    if constexpr (SPLIT == 2) {
+        f32x16 *const sums[4] = {&dk0, &dk1, &dv0, &dv1};
+        if (join_pairs<4, kStage>(sums, wave & 1 ? buf1 : buf0, part, lane)) return;
+    }
     if (ki < N) {
         const float wk = wtok[ki], wks = wk * scale;
         const bool live = wk > 0.f;
@@ -475,7 +539,8 @@ global_bwd_dkdv(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, co
 // bounded by the logsumexp, so 2^(x - L) may overflow and inf * (w k = 0) would poison dq: the exponent is capped at
 // 100 there (a key of positive weight stays below log2(max omega / omega_j), a few tens at most), which keeps the
 // factor finite and the product with the zero row exactly zero.
-template <bool DEAD>
+// SPLIT as in the forward.
+template <bool DEAD, int SPLIT>
 __global__ void __launch_bounds__(256, 3)
 global_bwd_dq(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const bf16raw *__restrict__ v,
               const bf16raw *__restrict__ go, const bf16raw *__restrict__ ktw, const float *__restrict__ L2,
@@ -490,7 +555,8 @@ global_bwd_dq(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, cons
     const int bh = unit / nqb, qb = unit - bh * nqb;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, col = lane & 31, hl = lane >> 5;
-    const int qi = qb * 128 + wave * 32 + col;
+    constexpr int TILES = 4 / SPLIT;                 // query tiles of the workgroup
+    const int part = wave / TILES, qi = (qb * TILES + wave % TILES) * 32 + col;
     bf16x8 qop[4], gop[4];
     {
         const size_t row = (size_t(bh) * N + min(qi, N - 1)) * kD + 8 * hl;
@@ -513,7 +579,8 @@ global_bwd_dq(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, cons
     auto stage = [&](const char *cur, char *nxt, int st) {
         if (st + 1 < nst) request(nxt, st + 1);
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int it = 0; it < 2 / SPLIT; ++it) {
+            const int h = SPLIT == 1 ? it : part;
             f32x16 s = {0}, dp = nd;
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
@@ -541,6 +608,10 @@ global_bwd_dq(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, cons
         stage(buf0, buf1, st);
         if (st + 1 < nst) stage(buf1, buf0, st + 1);
     }
+    if constexpr (SPLIT == 2) {
+        f32x16 *const sums[2] = {&dq0, &dq1};
+        if (join_pairs<2, kStage>(sums, wave & 1 ? buf1 : buf0, part, lane)) return;
+    }
     if (qi < N) {
         bf16raw *dqb = dq + (size_t(bh) * N + qi) * kD + 4 * hl;
 #pragma unroll
@@ -554,6 +625,20 @@ global_bwd_dq(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, cons
     }
 }
 
+// Whether the wavefronts of a workgroup share the streamed side (SPLIT = 2).  It pays while the launch of workgroups of
+// 128 tokens leaves compute units idle or their second wavefront of a SIMD missing; beyond that the second workgroup of
+// a compute unit hides the same waits, and the split only halves the reuse of a staged tile.  Times with SPLIT = 1 -> 2,
+// in microseconds of the whole call, by the number of workgroups of 128 tokens (46 x 90 unless said):
+//     forward        33: 85 -> 50   132: 91 -> 63   264: 108 -> 81   320 (25 x 47): 38 -> 32   396: 116 -> 119
+//     query side     33: 224 -> 184   132: 235 -> 209   264: 292 -> 280   320 (25 x 47): 112 -> 110   396: 360 -> 379
+//     key side       33: 224 -> 192   132: 235 -> 220   224 (21 x 40): 67 -> 67   260 (65 x 128): 511 -> 529
+// (at most two workgroups of the key side fit a compute unit, three of the others: hence two lines).
+constexpr long kSplitBlocks = 320, kSplitBlocksKeySide = 256;
+bool split_waves(int nbh, int N, long most)
+{
+    return long(nbh) * ((N + 127) / 128) <= most;
+}
+
 int check_global(const s2_grid_t *g, int batch, int heads, int d, int dtype)
 {
     if (!g) return s2_fail(S2_ERR_INVALID_ARG, "grid is NULL");
@@ -564,7 +649,7 @@ int check_global(const s2_grid_t *g, int batch, int heads, int d, int dtype)
     if (dtype != S2_BF16) return s2_fail(S2_ERR_UNSUPPORTED, "global attention supports S2_BF16 only");
     if (d != kD) return s2_fail(S2_ERR_UNSUPPORTED, "global attention supports head dimension 64 only");
     if (!g->on_device) return s2_fail(S2_ERR_DEVICE, "grid handle has no device tables (no HIP device at init)");
-    // one workgroup per (slice, block of 128 tokens): the launch grid must fit 31 bits
+    // one workgroup per (slice, block of 128 tokens), two where the launch is split (few): the grid must fit 31 bits
     const long nunits = long(batch) * heads * ((long(g->nlat_in) * g->nlon_in + 127) / 128);
     if (nunits > (1l << 30)) return s2_fail(S2_ERR_INVALID_ARG, "batch*heads*tokens too large for one launch");
     return S2_OK;
@@ -616,8 +701,10 @@ extern "C" int s2_attn_global_fwd(const s2_grid_t *g, int batch, int heads, int 
     pa.stat_op = -1;
     launch_prepare(pa, 1, nbh, N, Npad, st);
     S2TraceScope tr("global_fwd", double(nbh) * N * N, st);
-    const int nqb = (N + 127) / 128, nunits = nbh * nqb;
-    auto kern = g->nlon_in % 32 == 0 ? global_fwd<true> : global_fwd<false>;
+    const bool split = split_waves(nbh, N, kSplitBlocks), uniform = g->nlon_in % 32 == 0;
+    const int tokens = split ? 64 : 128, nqb = (N + tokens - 1) / tokens, nunits = nbh * nqb;
+    auto kern = split ? (uniform ? global_fwd<true, 2> : global_fwd<false, 2>)
+                      : (uniform ? global_fwd<true, 1> : global_fwd<false, 1>);
     hipLaunchKernelGGL(kern, dim3(8 * ((nunits + 7) / 8)), dim3(256), 0, st, static_cast<const bf16raw *>(q),
                        static_cast<const bf16raw *>(k), static_cast<const bf16raw *>(workspace), g->dev_w_tok,
                        static_cast<bf16raw *>(out), lse, N, Npad, nqb, nunits, scale * kLog2e, g->dt.ln_omega_ref);
@@ -660,19 +747,23 @@ extern "C" int s2_attn_global_bwd(const s2_grid_t *g, int batch, int heads, int 
     pa.ln_wref = g->dt.ln_omega_ref;
     launch_prepare(pa, 3, nbh, N, Npad, st);
     const float c2 = scale * kLog2e;
-    const int nblk = (N + 127) / 128, nunits = nbh * nblk;
-    const dim3 grid(8 * ((nunits + 7) / 8));
     {
-    S2TraceScope tr("global_bwd_dkdv", double(nbh) * N * N, st);
-    hipLaunchKernelGGL(global_bwd_dkdv, grid, dim3(256), 0, st, static_cast<const bf16raw *>(q),
-                       static_cast<const bf16raw *>(k), static_cast<const bf16raw *>(v),
-                       static_cast<const bf16raw *>(dout), qt, got, g->dev_w_tok, L2, Dv,
-                       static_cast<bf16raw *>(dk), static_cast<bf16raw *>(dv), N, Npad, nblk, nunits, c2, scale);
+        S2TraceScope tr("global_bwd_dkdv", double(nbh) * N * N, st);
+        const bool split = split_waves(nbh, N, kSplitBlocksKeySide);
+        const int tokens = split ? 64 : 128, nblk = (N + tokens - 1) / tokens, nunits = nbh * nblk;
+        hipLaunchKernelGGL(split ? global_bwd_dkdv<2> : global_bwd_dkdv<1>, dim3(8 * ((nunits + 7) / 8)), dim3(256), 0,
+                           st, static_cast<const bf16raw *>(q), static_cast<const bf16raw *>(k),
+                           static_cast<const bf16raw *>(v), static_cast<const bf16raw *>(dout), qt, got, g->dev_w_tok,
+                           L2, Dv, static_cast<bf16raw *>(dk), static_cast<bf16raw *>(dv), N, Npad, nblk, nunits, c2,
+                           scale);
     }
     S2TraceScope tr("global_bwd_dq", double(nbh) * N * N, st);
     const bool dead = Npad != N || !g->zero_lat.empty();      // keys of weight zero exist
-    auto dq_kernel = dead ? global_bwd_dq<true> : global_bwd_dq<false>;
-    hipLaunchKernelGGL(dq_kernel, grid, dim3(256), 0, st, static_cast<const bf16raw *>(q),
+    const bool split = split_waves(nbh, N, kSplitBlocks);
+    const int tokens = split ? 64 : 128, nblk = (N + tokens - 1) / tokens, nunits = nbh * nblk;
+    auto dq_kernel = split ? (dead ? global_bwd_dq<true, 2> : global_bwd_dq<false, 2>)
+                           : (dead ? global_bwd_dq<true, 1> : global_bwd_dq<false, 1>);
+    hipLaunchKernelGGL(dq_kernel, dim3(8 * ((nunits + 7) / 8)), dim3(256), 0, st, static_cast<const bf16raw *>(q),
                        static_cast<const bf16raw *>(k), static_cast<const bf16raw *>(v),
                        static_cast<const bf16raw *>(dout), kt, L2, Dv, static_cast<bf16raw *>(dq), N, Npad, nblk,
                        nunits, c2, scale);
