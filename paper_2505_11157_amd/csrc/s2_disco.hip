@@ -16,6 +16,7 @@
 #include <cmath>
 #include <cstring>
 #include <initializer_list>
+#include <map>
 #include <new>
 #include <utility>
 
@@ -23,11 +24,16 @@
 
 namespace {
 
-// One direction of the contraction with psi as disco_gather walks it: for every owner latitude a list of chunks, a chunk
-// being some rows (or parts of long ones) that fit into a wavefront's share of LDS and the (row, offset) entries on them, sorted by the interval
-// j <= r K / theta < j + 1 in which only the hats j and j + 1 differ from zero.
-struct GatherRow {
-    int lat, left, ncols, base;       // walked latitude, staged columns in front of the first owner's (may be negative), staged columns, LDS position
+// One direction of the contraction with psi as disco_gather walks it: for every group of kGroup owner latitudes a list of
+// chunks, a chunk being some rows (or parts of long ones) that fit into a workgroup's share of LDS and, for each latitude of
+// the group, the (row, offset) entries on them, sorted by the interval j <= r K / theta < j + 1 in which only the hats j and
+// j + 1 differ from zero.
+constexpr int kGroup = 4;
+struct GatherPiece {                  // 64 (W + 1) staged columns of a row at most: i0 .. i0 + n - 1 of it
+    int lat, left;                    // walked latitude, staged columns in front of the first owner's (may be negative)
+    int i0, n;
+    int base, sub;                    // the row's LDS position, its columns of one remainder mod P
+    int pad[2];
 };
 struct GatherEntry {
     int plus, minus;                  // LDS byte offsets of the columns +d and -d of owner 0
@@ -35,11 +41,11 @@ struct GatherEntry {
 };
 struct GatherTables {
     void *blob = nullptr;
-    const int *chunk_of = nullptr;    // [owner latitudes + 1]
-    const int *chunk = nullptr;       // [chunks][K + 3]: first row, end row, first entry, end of the entries of interval j
-    const GatherRow *row = nullptr;
+    const int *chunk_of = nullptr;    // [groups + 1]
+    const int *chunk = nullptr;       // [chunks][2 + kGroup (K + 1)]: first piece, end piece; per latitude: first entry, end of interval j
+    const GatherPiece *piece = nullptr;
     const GatherEntry *entry = nullptr;
-    const int *order = nullptr;       // owner latitudes, heaviest first
+    const int *order = nullptr;       // groups, heaviest first
     int lds_bytes = 0, W = 1;         // 0: not available; owners per lane
 };
 
@@ -119,24 +125,33 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // multiply-adds per channel instead of 2 K multiply-adds (a dense contraction with the basis on the matrix cores, 16 rows
 // for 9 functions, took 0.62 ms on 129 x 256 with 4 x 64 channels).  Which two accumulators an entry goes to is known at
 // compile time: the entries of a chunk are sorted by interval and the loop over the intervals is unrolled.
-// One wavefront: 64 W consecutive owners of one latitude, four channels.  It stages the rows of a chunk for itself,
-// position-major with the four channels of a column side by side, so that a neighbor is one 16-byte LDS read per lane at
+// One workgroup: 64 W consecutive owners of four neighboring latitudes, one each for its wavefronts, and four channels.
+// Neighboring latitudes meet nearly the same rows, so the rows are staged once for the four, and a latitude's entries come in
+// one or two chunks, in fewer and longer runs of one interval, than where a wavefront stages for itself.  129 x 256 with 4 x 64
+// channels, K = 9: 180 us that way, 171 us in groups, 157 us with the LDS reads of two entries waiting together.  Bound there:
+// the 16-byte LDS reads (80 us at 128 bytes a clock and compute unit; two neighbors of four channels each take 32 bytes, whatever
+// the order) and behind them, hardly overlapped, the staging (13 us), the results (30 us) and the runs' starts (19 us); the
+// polar groups, one workgroup of 55 us, are started first.  More than one quad of channels to a workgroup: 168 us and up.
+// Staged position-major with the four channels of a column side by side, so that a neighbor is one 16-byte LDS read per lane at
 // consecutive addresses; with P walked columns per owner the columns of one remainder mod P lie together, and where the owner
 // grid is the finer one (C owner columns per walked column) the owner latitudes are its classes of every C-th column.  Entries and basis
-// values are uniform and come through the scalar cache.  Bound: the vector ALU (13 instructions per entry and owner; busy 49 % of
-// the launch on 129 x 256 with 4 x 64 channels, K = 9) before the 16-byte LDS reads (30 %); results leave at 1.6 TB/s there.
+// values are uniform and come through the scalar cache.
 template <int K, int W>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(64 * kGroup, 3)
 disco_gather(GatherTables t, int P, int C, int nlon_own, int nlon_walk, int nlat_own, int nlat_walk, int nch,
              const float *__restrict__ x, float *__restrict__ out)
 {
+    // 168 registers at three wavefronts a SIMD (what LDS holds): pieces under way, and whether two entries' values fit
+    constexpr int kFree = (112 - 4 * K * W) / (4 * (W + 1)), D = kFree < 1 ? 1 : kFree > 4 ? 4 : kFree;
+    constexpr bool kTwo = 4 * K * W <= 104;
     extern __shared__ __attribute__((aligned(16))) f32x4 xs[];
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ntile = (nlon_own + 64 * W - 1) / (64 * W), nquad = (nch + 3) / 4;
     int id = blockIdx.x;
     const int tile = id % ntile; id /= ntile;
-    const int quad = id % nquad, lat = t.order[id / nquad];
+    const int quad = id % nquad, grp = t.order[id / nquad], lat = grp * kGroup + wave;
     const int u0 = tile * 64 * W;
+    const float inv_walk = 1.f / float(nlon_walk), inv_p = 1.f / float(P);
     const size_t plane_walk = size_t(nlat_walk) * nlon_walk, plane_own = size_t(nlat_own / C) * nlon_own * C;
     const float *xc[4];
 #pragma unroll
@@ -147,58 +162,97 @@ disco_gather(GatherTables t, int P, int C, int nlon_own, int nlon_walk, int nlat
     for (int k = 0; k < K; ++k)
 #pragma unroll
         for (int i = 0; i < W; ++i) acc[k][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const char *lds = reinterpret_cast<const char *>(xs) + 16 * lane;
-    const int c_end = t.chunk_of[lat + 1];
-    for (int ci = t.chunk_of[lat]; ci < c_end; ++ci) {
-        const int *ch = t.chunk + size_t(ci) * (K + 3);
-        const int r_end = ch[1];
-        __syncthreads();                                 // one wavefront: its reads of the previous chunk are done
-        for (int r = ch[0]; r < r_end; ++r) {
-            const GatherRow row = t.row[r];
-            const size_t at = size_t(row.lat) * nlon_walk;
-            const int sub = row.ncols / P;
-            int first = u0 * P - row.left;               // in (-nlon, 2 nlon)
-            first = first < 0 ? first + nlon_walk : first;
-            for (int i0 = 0; i0 < row.ncols; i0 += 192) {
-                float v[3][4];
+    // The pieces of a chunk are dealt out to the wavefronts.  (x + 1/2) / n in float32 has the right whole part here: x stays
+    // within some thousand columns above the circle's.
+    float v[D][W + 1][4];                                // pieces under way from memory
+    auto request = [&](int piece, int end) {
 #pragma unroll
-                for (int b = 0; b < 3; ++b) {
-                    int col = first + min(i0 + 64 * b + lane, row.ncols - 1);
-                    col = col >= 2 * nlon_walk ? col % nlon_walk : col >= nlon_walk ? col - nlon_walk : col;
+        for (int s = 0; s < D; ++s) {
+            if (piece + s * kGroup >= end) break;
+            const GatherPiece m = t.piece[piece + s * kGroup];
+            const size_t at = size_t(m.lat) * nlon_walk;
+            int first = u0 * P - m.left;                 // in (-nlon, 2 nlon)
+            first = (first < 0 ? first + nlon_walk : first) + m.i0;
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) v[b][c] = xc[c][at + col];
-                }
+            for (int b = 0; b <= W; ++b) {
+                int col = first + min(64 * b + lane, m.n - 1);
+                col -= __mul24(int((float(col) + 0.5f) * inv_walk), nlon_walk);
 #pragma unroll
-                for (int b = 0; b < 3; ++b) {
-                    const int i = i0 + 64 * b + lane;
-                    const int pos = P == 1 ? i : P == 2 ? (i & 1) * sub + (i >> 1) : (i % P) * sub + i / P;
-                    if (i < row.ncols) xs[row.base + pos] = f32x4{v[b][0], v[b][1], v[b][2], v[b][3]};
-                }
+                for (int c = 0; c < 4; ++c) v[s][b][c] = xc[c][at + col];
             }
         }
+    };
+    auto place = [&](int piece, int end) {
+#pragma unroll
+        for (int s = 0; s < D; ++s) {
+            if (piece + s * kGroup >= end) break;
+            const GatherPiece m = t.piece[piece + s * kGroup];
+#pragma unroll
+            for (int b = 0; b <= W; ++b) {
+                const int i = m.i0 + 64 * b + lane, q = int((float(i) + 0.5f) * inv_p);
+                if (64 * b + lane < m.n) xs[m.base + __mul24(i - __mul24(q, P), m.sub) + q] = f32x4{v[s][b][0], v[s][b][1], v[s][b][2], v[s][b][3]};
+            }
+        }
+    };
+    const char *lds = reinterpret_cast<const char *>(xs) + 16 * lane;
+    constexpr int kChunk = 2 + kGroup * (K + 1);
+    const int c_end = t.chunk_of[grp + 1];
+    for (int ci = t.chunk_of[grp]; ci < c_end; ++ci) {
+        const int *ch = t.chunk + size_t(ci) * kChunk, p_end = ch[1];
+        int p = ch[0] + wave;
+        request(p, p_end);
+        __syncthreads();                                 // the reads of the previous chunk are done
+        place(p, p_end);
+        for (p += D * kGroup; p < p_end; p += D * kGroup) {
+            request(p, p_end);
+            place(p, p_end);
+        }
         __syncthreads();
-        int e = ch[2];
-        GatherEntry next = t.entry[e];                   // one ahead (the table ends with a spare entry)
+        ch += 2 + wave * (K + 1);
+        int e = ch[0];
+        GatherEntry n0 = t.entry[e], n1 = t.entry[e + 1];        // two ahead (the table ends with two spare entries)
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-            const int e_end = ch[3 + j];
-            for (; e < e_end; ++e) {
-                const GatherEntry en = next;
-                next = t.entry[e + 1];
+            const int e_end = ch[1 + j];
+            auto add = [&](const GatherEntry &en, const f32x4 &a, const f32x4 &b, int i) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const float s = a[c] + b[c];
+                    acc[j][i][c] = fmaf(en.lo, s, acc[j][i][c]);
+                    if (j + 1 < K) acc[j + 1 < K ? j + 1 : 0][i][c] = fmaf(en.hi, s, acc[j + 1 < K ? j + 1 : 0][i][c]);
+                }
+            };
+            auto at = [&](int pos, int i) { return *reinterpret_cast<const f32x4 *>(lds + pos + 1024 * i); };
+            for (; kTwo && e + 1 < e_end; e += 2) {              // two at a time: their LDS reads wait together
+                const GatherEntry e0 = n0, e1 = n1;
+                f32x4 a0[W], b0[W], a1[W], b1[W];
 #pragma unroll
                 for (int i = 0; i < W; ++i) {
-                    const f32x4 a = *reinterpret_cast<const f32x4 *>(lds + en.plus + 1024 * i);
-                    const f32x4 b = *reinterpret_cast<const f32x4 *>(lds + en.minus + 1024 * i);
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const float s = a[c] + b[c];
-                        acc[j][i][c] = fmaf(en.lo, s, acc[j][i][c]);
-                        if (j + 1 < K) acc[j + 1 < K ? j + 1 : 0][i][c] = fmaf(en.hi, s, acc[j + 1 < K ? j + 1 : 0][i][c]);
-                    }
+                    a0[i] = at(e0.plus, i);
+                    b0[i] = at(e0.minus, i);
                 }
+#pragma unroll
+                for (int i = 0; i < W; ++i) {
+                    a1[i] = at(e1.plus, i);
+                    b1[i] = at(e1.minus, i);
+                }
+                n0 = t.entry[e + 2];
+                n1 = t.entry[e + 3];
+#pragma unroll
+                for (int i = 0; i < W; ++i) add(e0, a0[i], b0[i], i);
+#pragma unroll
+                for (int i = 0; i < W; ++i) add(e1, a1[i], b1[i], i);
+            }
+            for (; e < e_end; ++e) {
+                const GatherEntry en = n0;
+                n0 = n1;
+                n1 = t.entry[e + 2];
+#pragma unroll
+                for (int i = 0; i < W; ++i) add(en, at(en.plus, i), at(en.minus, i), i);
             }
         }
     }
+    if (lat >= nlat_own) return;
 #pragma unroll
     for (int i = 0; i < W; ++i) {
         const int u = u0 + 64 * i + lane;
@@ -308,14 +362,15 @@ void by_count(int n, F &&f)       // f(K) for the basis count n = 1 .. kMaxBasis
 void launch_gather(const GatherTables &t, int K, int P, int C, int nlon_own, int nlon_walk, int nlat_own, int nlat_walk, int nch,
                    const float *x, float *out, hipStream_t st)
 {
-    const unsigned blocks = unsigned((nlon_own + 64 * t.W - 1) / (64 * t.W)) * unsigned((nch + 3) / 4) * unsigned(nlat_own);
+    const unsigned blocks = unsigned((nlon_own + 64 * t.W - 1) / (64 * t.W)) * unsigned((nch + 3) / 4) *
+                            unsigned((nlat_own + kGroup - 1) / kGroup);
     by_count(K, [&](auto k) {
         constexpr int KK = decltype(k)::value;
         if (t.W == 2)
-            hipLaunchKernelGGL((disco_gather<KK, 2>), dim3(blocks), dim3(64), size_t(t.lds_bytes), st, t, P, C, nlon_own, nlon_walk,
+            hipLaunchKernelGGL((disco_gather<KK, 2>), dim3(blocks), dim3(64 * kGroup), size_t(t.lds_bytes), st, t, P, C, nlon_own, nlon_walk,
                                nlat_own, nlat_walk, nch, x, out);
         else
-            hipLaunchKernelGGL((disco_gather<KK, 1>), dim3(blocks), dim3(64), size_t(t.lds_bytes), st, t, P, C, nlon_own, nlon_walk,
+            hipLaunchKernelGGL((disco_gather<KK, 1>), dim3(blocks), dim3(64 * kGroup), size_t(t.lds_bytes), st, t, P, C, nlon_own, nlon_walk,
                                nlat_own, nlat_walk, nch, x, out);
     });
 }
@@ -340,7 +395,7 @@ int upload(void *&blob, size_t *off, std::initializer_list<std::pair<const void 
 }
 
 // psi of one row as pairs of input offsets +d and -d for the owner class sc of C (input offset d leads to walked column
-// (sc - d) / C of owner 0, where C divides sc - d): f(first column, second column, psi of +-d, factor), only for offsets with a
+// (sc - d) / C of owner 0, where C divides sc - d): f(first column, second column, psi of +-d, factor, d), only for offsets with a
 // hat that is not zero.  A column of its own (d = 0, half a turn on an even circle, one of the two not on the walked grid) is
 // both columns, and the factor is one half.
 template <class F>
@@ -356,15 +411,16 @@ void for_offsets(const float *psi, int cnt, int nlon_in, int K, int KP, int C, i
         const bool once = d == 0 || (full && 2 * d == nlon_in), one = (sc - d) % C == 0, two = !once && (sc + d) % C == 0;
         if (!one && !two) continue;
         const int first = one ? (sc - d) / C : (sc + d) / C, second = two ? (sc + d) / C : first;
-        f(first, second, j, p, one && two ? 1.f : 0.5f);
+        f(first, second, j, p, one && two ? 1.f : 0.5f, d);
     }
 }
 
-// A wavefront's share of LDS: twelve of them on a compute unit.  Longer rows are staged in parts: with a larger share for the
-// polar rows the wavefronts of every latitude would have it (721 x 1440, 32 channels, K = 4: z 1.33 against 0.77 ms), and a launch of
-// their own would run by itself as long as its longest wavefront (361 x 720: z 276 -> 424 us).  From nine walked columns per
+// A workgroup's share of LDS: three of them on a compute unit.  Longer rows are staged in parts: with a larger share for the
+// polar rows the workgroups of every latitude would have it (where a
+// wavefront staged for itself, 721 x 1440, 32 channels, K = 4: z 1.33 against 0.77 ms), and a launch of
+// their own would run by itself as long as its longest workgroup (361 x 720: z 276 -> 424 us).  From nine walked columns per
 // owner on, even a part with a single offset takes more; it may up to what needs no raised limit.
-constexpr int kGatherLds = 13 * 1024, kGatherLdsMost = 64 * 1024;
+constexpr int kGatherLds = 52 * 1024, kGatherLdsMost = 64 * 1024;
 
 // Tables for owners on `nlat_own` latitudes (classes of latitudes); walked(lat, f) calls f(walked latitude, psi of its input
 // offsets 0 .. nlon_in / 2 at [offset * KP + k], offset count of the arc) for every row of owner latitude lat.  P walked columns
@@ -377,37 +433,46 @@ int build_gather(GatherTables &t, int K, int KP, int P, int C, int nlat_own, int
     // two owners per lane halve the staged columns that are not owners' own; one where a second set would mostly be idle
     t.W = nlon_own % 128 > 0 && nlon_own % 128 <= 64 ? 1 : 2;
     std::vector<int> chunk_of(1, 0), chunk, order;
-    std::vector<GatherRow> rows;
+    std::vector<GatherPiece> pieces;
     std::vector<GatherEntry> entries;
     std::vector<std::pair<long, int>> cost;
     int most = 0;
-    for (int lat = 0; lat < nlat_own; ++lat) {
+    struct Pair {
+        int first, second, j;
+        float lo, hi;
+        int d, owner;                                            // offset, latitude of the group
+    };
+    for (int grp = 0; grp * kGroup < nlat_own; ++grp) {
         const size_t first_entry = entries.size();
-        std::vector<std::vector<GatherEntry>> by_interval(K);
-        int row0 = int(rows.size()), base = 0;
+        std::vector<std::vector<GatherEntry>> by_interval(kGroup * K);
+        int piece0 = int(pieces.size()), base = 0;
         auto flush = [&]() {
-            if (int(rows.size()) == row0) return;
-            chunk.push_back(row0);
-            chunk.push_back(int(rows.size()));
-            chunk.push_back(int(entries.size()));
-            for (auto &v : by_interval) {
-                entries.insert(entries.end(), v.begin(), v.end());
+            if (int(pieces.size()) == piece0) return;
+            chunk.push_back(piece0);
+            chunk.push_back(int(pieces.size()));
+            for (int i = 0; i < kGroup * K; ++i) {
+                if (i % K == 0) chunk.push_back(int(entries.size()));
+                entries.insert(entries.end(), by_interval[i].begin(), by_interval[i].end());
                 chunk.push_back(int(entries.size()));
-                v.clear();
+                by_interval[i].clear();
             }
             most = std::max(most, base * 16);
-            row0 = int(rows.size());
+            piece0 = int(pieces.size());
             base = 0;
         };
-        walked(lat, [&](int wl, const float *psi, int cnt) {
-            struct Pair {
-                int first, second, j;
-                float lo, hi;
-            };
-            std::vector<Pair> pairs;
-            for_offsets(psi, cnt, nlon_walk * C, K, KP, C, lat % C, [&](int first, int second, int j, const float *p, float f) {
-                pairs.push_back({first, second, j, f * p[j], j + 1 < K ? f * p[j + 1] : 0.f});
+        std::map<int, std::vector<Pair>> rows;                   // by walked latitude
+        for (int o = 0; o < kGroup && grp * kGroup + o < nlat_own; ++o) {
+            const int lat = grp * kGroup + o;
+            walked(lat, [&](int wl, const float *psi, int cnt) {
+                for_offsets(psi, cnt, nlon_walk * C, K, KP, C, lat % C, [&](int first, int second, int j, const float *p, float f, int d) {
+                    rows[wl].push_back({first, second, j, f * p[j], j + 1 < K ? f * p[j + 1] : 0.f, d, o});
+                });
             });
+        }
+        for (auto &row : rows) {
+            const int wl = row.first;
+            std::vector<Pair> &pairs = row.second;
+            std::stable_sort(pairs.begin(), pairs.end(), [](const Pair &a, const Pair &b) { return a.d < b.d; });
             // Staged columns for the offsets lo .. hi of 64 W owners, owner by owner those of one remainder mod P together.
             struct Window {
                 int left, sub;
@@ -445,7 +510,8 @@ int build_gather(GatherTables &t, int K, int KP, int P, int C, int nlat_own, int
                 int at[2][2];                                    // LDS position and left margin of either column's window
                 for (int s = 0; s < (one ? 1 : 2); ++s) {
                     const Window w(lo[s], hi[s], P, owners);
-                    rows.push_back({wl, w.left, w.sub * P, base});
+                    for (int i0 = 0, n = w.sub * P, most = 64 * (t.W + 1); i0 < n; i0 += most)
+                        pieces.push_back({wl, w.left, i0, std::min(most, n - i0), base, w.sub, {}});
                     at[s][0] = base;
                     at[s][1] = w.left;
                     base += w.sub * P;
@@ -456,26 +522,26 @@ int build_gather(GatherTables &t, int K, int KP, int P, int C, int nlat_own, int
                 };
                 for (; i < end; ++i) {
                     const Pair &p = pairs[i];
-                    by_interval[p.j].push_back({place(0, p.first), place(1, p.second), p.lo, p.hi});
+                    by_interval[p.owner * K + p.j].push_back({place(0, p.first), place(1, p.second), p.lo, p.hi});
                 }
             }
-        });
+        }
         flush();
-        chunk_of.push_back(int(chunk.size() / (K + 3)));
-        cost.push_back({-long(entries.size() - first_entry), lat});
+        chunk_of.push_back(int(chunk.size() / (2 + kGroup * (K + 1))));
+        cost.push_back({-long(entries.size() - first_entry), grp});
     }
     if (most > kGatherLdsMost) return 0;
-    entries.push_back({0, 0, 0.f, 0.f});
+    entries.resize(entries.size() + 2, {0, 0, 0.f, 0.f});
     std::stable_sort(cost.begin(), cost.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
     for (auto &c : cost) order.push_back(c.second);
     size_t off[6];
-    if (upload(t.blob, off, {{chunk_of.data(), chunk_of.size() * 4}, {chunk.data(), chunk.size() * 4}, {rows.data(), rows.size() * sizeof(GatherRow)},
+    if (upload(t.blob, off, {{chunk_of.data(), chunk_of.size() * 4}, {chunk.data(), chunk.size() * 4}, {pieces.data(), pieces.size() * sizeof(GatherPiece)},
                              {entries.data(), entries.size() * sizeof(GatherEntry)}, {order.data(), order.size() * 4}}))
         return S2_ERR_ALLOC;
     char *b = static_cast<char *>(t.blob);
     t.chunk_of = reinterpret_cast<const int *>(b);
     t.chunk = reinterpret_cast<const int *>(b + off[1]);
-    t.row = reinterpret_cast<const GatherRow *>(b + off[2]);
+    t.piece = reinterpret_cast<const GatherPiece *>(b + off[2]);
     t.entry = reinterpret_cast<const GatherEntry *>(b + off[3]);
     t.order = reinterpret_cast<const int *>(b + off[4]);
     t.lds_bytes = std::max(most, 16);
@@ -492,7 +558,7 @@ int build_planes(PlaneTables &t, int K, int KP, int C, int nlat_own, int nlat_wa
     std::vector<std::pair<long, int>> cost;
     for (int lat = 0; lat < nlat_own; ++lat) {
         walked(lat, [&](int wl, const float *psi, int cnt) {
-            for_offsets(psi, cnt, nlon_walk * C, K, KP, C, lat % C, [&](int one, int two, int j, const float *p, float f) {
+            for_offsets(psi, cnt, nlon_walk * C, K, KP, C, lat % C, [&](int one, int two, int j, const float *p, float f, int) {
                 auto col = [&](int x) { return (x % nlon_walk + nlon_walk) % nlon_walk; };
                 for (int k = j; k <= j + 1 && k < K; ++k)
                     if (p[k] != 0.f) terms.push_back({(long(k) * nlat_walk + wl) * nlon_walk, col(one), col(two), f * p[k], 0});
