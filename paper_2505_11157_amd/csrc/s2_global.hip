@@ -166,37 +166,72 @@ __device__ __forceinline__ int lds_row_of_token(int t)
 // deposits its 16 bytes at base + 16 i, i.e. one instruction fills eight consecutive rows), so the
 // swizzle and the row permutation are applied on the source side: lane i fetches the piece that belongs
 // at physical position i.  Wavefront w of the four copies rows 16 w .. 16 w + 15 of every tile.
-typedef __attribute__((address_space(1))) const void *gptr_t;
 typedef __attribute__((address_space(3))) void *lptr_t;
 
-// token-major tile: LDS row r holds token tok0 + (r & 32) + perm_row(r & 31), clamped to N - 1
-__device__ __forceinline__ void copy_row_tile(const bf16raw *base, int tok0, int N, char *tile, int wave, int lane)
+// Copies straight to LDS, 16 or 4 bytes a lane, lane after lane from dst on, written out: the uniform base stays in scalar
+// registers and the lane's offset in one vector register.  From the compiler's own form it made the 64-bit address anew for
+// each copy and, not seeing which buffer a copy goes to, waited for copies under way within the stage (65 x 128, 32 slices:
+// forward 670 -> 628 us, with the backward 2767 -> 2630 us; 46 x 90, four: 63 -> 60 and 196 -> 174 us).  It does not know of
+// these copies: landed() waits for the wavefront's copies and LDS reads, then for the other wavefronts of the workgroup.
+// (Three buffers in turn, waiting for the older copies only, gained nothing: with small launches the chain of one tile is
+// what takes the time, with large ones the LDS of the third buffer costs a workgroup of the compute unit, 643 us.)
+__device__ __forceinline__ int lds_at(char *p)
 {
+    return int(reinterpret_cast<uintptr_t>((lptr_t)p));
+}
+__device__ __forceinline__ void copy16(const char *base, int off, int dst)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(dst) : "memory", "m0");
+}
+__device__ __forceinline__ void copy4(const char *base, int off, int dst)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(base), "s"(dst) : "memory", "m0");
+}
+// An operand loaded the ordinary way is waited for here, not by the compiler behind the copies in the loop that uses it.
+template <class T>
+__device__ __forceinline__ void arrived(T &x)
+{
+    asm volatile("" : "+v"(x));
+}
+__device__ __forceinline__ void landed()
+{
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+// What a lane fetches of the tiles of a stage: a stage moves the uniform base of a copy, the offsets stay.
+struct Copies {
+    int wave, lane, token[2], piece[2], col[2], N, Npad;
+    __device__ __forceinline__ Copies(int wave, int lane, int N, int Npad) : wave(wave), lane(lane), N(N), Npad(Npad)
+    {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int r = 16 * wave + 8 * h + (lane >> 3);
-        const int c = (lane & 7) ^ ((r >> 1) & 7);
-        const int t = (r & 32) | perm_row(r & 31);
-        const char *src = reinterpret_cast<const char *>(base + size_t(min(tok0 + t, N - 1)) * kD) + 16 * c;
-        __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(tile + 2048 * wave + 1024 * h), 16, 0, 0);
+        for (int h = 0; h < 2; ++h) {
+            const int r = 16 * wave + 8 * h + (lane >> 3);
+            piece[h] = 16 * ((lane & 7) ^ ((r >> 1) & 7));
+            token[h] = (r & 32) | perm_row(r & 31);
+            col[h] = (lane >> 3) * Npad * int(sizeof(bf16raw)) + piece[h];
+        }
     }
-}
-// channel-major tile from a transposed operand [64][Npad] (Npad a multiple of 64: always in bounds)
-__device__ __forceinline__ void copy_col_tile(const bf16raw *base, int tok0, int Npad, char *tile, int wave, int lane)
-{
+    // token-major tile: LDS row r holds token tok0 + (r & 32) + perm_row(r & 31), clamped to N - 1
+    __device__ __forceinline__ void rows(const bf16raw *base, int tok0, char *tile) const
+    {
+        const char *at = reinterpret_cast<const char *>(base + size_t(tok0) * kD);
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int r = 16 * wave + 8 * h + (lane >> 3);
-        const int c = (lane & 7) ^ ((r >> 1) & 7);
-        const char *src = reinterpret_cast<const char *>(base + size_t(r) * Npad + tok0 + 8 * c);
-        __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(tile + 2048 * wave + 1024 * h), 16, 0, 0);
+        for (int h = 0; h < 2; ++h)
+            copy16(at, (min(token[h], N - 1 - tok0) << 7) + piece[h], lds_at(tile) + 2048 * wave + 1024 * h);
     }
-}
-// 64 consecutive floats (one wavefront, lane = element)
-__device__ __forceinline__ void copy_floats(const float *src, char *dst, int lane)
-{
-    __builtin_amdgcn_global_load_lds((gptr_t)(src + lane), (lptr_t)dst, 4, 0, 0);
-}
+    // channel-major tile from a transposed operand [64][Npad] (Npad a multiple of 64: always in bounds)
+    __device__ __forceinline__ void cols(const bf16raw *base, int tok0, char *tile) const
+    {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            copy16(reinterpret_cast<const char *>(base + size_t(16 * wave + 8 * h) * Npad + tok0), col[h],
+                   lds_at(tile) + 2048 * wave + 1024 * h);
+    }
+    // 64 consecutive floats (one wavefront, lane = element)
+    __device__ __forceinline__ void floats(const float *src, char *dst) const
+    {
+        copy4(reinterpret_cast<const char *>(src), 4 * lane, lds_at(dst));
+    }
+};
 __device__ __forceinline__ bf16x8 lds8(const char *p)
 {
     return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(p));
@@ -261,11 +296,12 @@ global_fwd(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const b
     const bf16raw *kb = k + size_t(bh) * N * kD;
     const bf16raw *vb = vt + size_t(bh) * kD * Npad;
     const int nst = Npad >> 6;
+    const Copies copies(wave, lane, N, Npad);
     auto request = [&](char *buf, int st) {
         const int t0 = 64 * st;
-        copy_row_tile(kb, t0, N, buf, wave, lane);
-        copy_col_tile(vb, t0, Npad, buf + kTileBytes, wave, lane);
-        if (wave == 0) copy_floats(wtok + t0, buf + 2 * kTileBytes, lane);
+        copies.rows(kb, t0, buf);
+        copies.cols(vb, t0, buf + kTileBytes);
+        if (wave == 0) copies.floats(wtok + t0, buf + 2 * kTileBytes);
     };
     bool based = false;        // has the query met a logit above -infinity: only then does m mean anything
     auto stage = [&](const char *cur, char *nxt, int st) {
@@ -339,10 +375,12 @@ global_fwd(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const b
                 o1 = mfma(col_operand(cur + kTileBytes, col, hl, 1, kt, j), pb, o1);
             }
         }
-        __syncthreads();   // everybody is done with `cur`, and the copies into `nxt` have landed
+        landed();          // everybody is done with `cur`, and the copies into `nxt` have landed
     };
     request(buf0, 0);
-    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) arrived(qop[ks]);
+    landed();
     for (int st = 0; st < nst; st += 2) {
         stage(buf0, buf1, st);
         if (st + 1 < nst) stage(buf1, buf0, st + 1);
@@ -451,14 +489,15 @@ global_bwd_dkdv(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, co
     const bf16raw *qtb = qt + size_t(bh) * kD * Npad, *gtb = got + size_t(bh) * kD * Npad;
     const float *Lb = L2 + size_t(bh) * Npad, *Db = Dv + size_t(bh) * Npad;
     const int nst = Npad >> 6;
+    const Copies copies(wave, lane, N, Npad);
     auto request = [&](char *buf, int st) {
         const int t0 = 64 * st;
-        copy_row_tile(qb, t0, N, buf, wave, lane);
-        copy_row_tile(gb, t0, N, buf + kTileBytes, wave, lane);
-        copy_col_tile(qtb, t0, Npad, buf + 2 * kTileBytes, wave, lane);
-        copy_col_tile(gtb, t0, Npad, buf + 3 * kTileBytes, wave, lane);
-        if (wave == 0) copy_floats(Lb + t0, buf + 4 * kTileBytes, lane);
-        if (wave == 1) copy_floats(Db + t0, buf + 4 * kTileBytes + 256, lane);
+        copies.rows(qb, t0, buf);
+        copies.rows(gb, t0, buf + kTileBytes);
+        copies.cols(qtb, t0, buf + 2 * kTileBytes);
+        copies.cols(gtb, t0, buf + 3 * kTileBytes);
+        if (wave == 0) copies.floats(Lb + t0, buf + 4 * kTileBytes);
+        if (wave == 1) copies.floats(Db + t0, buf + 4 * kTileBytes + 256);
     };
     auto stage = [&](const char *cur, char *nxt, int st) {
         if (st + 1 < nst) request(nxt, st + 1);
@@ -498,10 +537,15 @@ global_bwd_dkdv(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, co
                 dk1 = mfma(col_operand(cur + 2 * kTileBytes, col, hl, 1, h, j), sb, dk1);
             }
         }
-        __syncthreads();   // everybody is done with `cur`, and the copies into `nxt` have landed
+        landed();          // everybody is done with `cur`, and the copies into `nxt` have landed
     };
     request(buf0, 0);
-    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        arrived(kop[ks]);
+        arrived(vop[ks]);
+    }
+    landed();
     for (int st = 0; st < nst; st += 2) {
         stage(buf0, buf1, st);
         if (st + 1 < nst) stage(buf1, buf0, st + 1);
@@ -563,18 +607,20 @@ global_bwd_dq(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, cons
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) { qop[ks] = ld8(q + row + 16 * ks); gop[ks] = ld8(go + row + 16 * ks); }
     }
-    const float Lq = L2[size_t(bh) * Npad + min(qi, N - 1)], Dq = Dv[size_t(bh) * Npad + min(qi, N - 1)];
+    float Lq = L2[size_t(bh) * Npad + min(qi, N - 1)];
+    const float Dq = Dv[size_t(bh) * Npad + min(qi, N - 1)];
     f32x16 dq0 = {0}, dq1 = {0}, nd;     // nd: -D_q in every register, the start value of dout.v
 #pragma unroll
     for (int i = 0; i < 16; ++i) nd[i] = Dq;
     const bf16raw *kb = k + size_t(bh) * N * kD, *vb = v + size_t(bh) * N * kD;
     const bf16raw *ktb = ktw + size_t(bh) * kD * Npad;
     const int nst = Npad >> 6;
+    const Copies copies(wave, lane, N, Npad);
     auto request = [&](char *buf, int st) {
         const int t0 = 64 * st;
-        copy_row_tile(kb, t0, N, buf, wave, lane);
-        copy_row_tile(vb, t0, N, buf + kTileBytes, wave, lane);
-        copy_col_tile(ktb, t0, Npad, buf + 2 * kTileBytes, wave, lane);
+        copies.rows(kb, t0, buf);
+        copies.rows(vb, t0, buf + kTileBytes);
+        copies.cols(ktb, t0, buf + 2 * kTileBytes);
     };
     auto stage = [&](const char *cur, char *nxt, int st) {
         if (st + 1 < nst) request(nxt, st + 1);
@@ -600,10 +646,17 @@ global_bwd_dq(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, cons
                 dq1 = mfma(col_operand(cur + 2 * kTileBytes, col, hl, 1, h, j), sb, dq1);
             }
         }
-        __syncthreads();   // everybody is done with `cur`, and the copies into `nxt` have landed
+        landed();          // everybody is done with `cur`, and the copies into `nxt` have landed
     };
     request(buf0, 0);
-    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        arrived(qop[ks]);
+        arrived(gop[ks]);
+    }
+    arrived(Lq);
+    arrived(nd);
+    landed();
     for (int st = 0; st < nst; st += 2) {
         stage(buf0, buf1, st);
         if (st + 1 < nst) stage(buf1, buf0, st + 1);
