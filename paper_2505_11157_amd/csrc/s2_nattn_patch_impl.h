@@ -30,14 +30,14 @@
 // five of them on a compute unit, whose barriers do not coincide (eight wavefronts, stages twice as long: dk/dv 0.72 against
 // 0.70 ms; all of LDS for one workgroup: 1.43).
 // Measured (129 x 256, 32 slices, forward / dq / dk,dv, ms; before: fp32 matrix cores and vector kernels):
-//   d = 16  0.42 / 0.52 / 0.65 -> 0.30 / 0.34 / 0.40        d = 32  0.66 / 0.83 / 1.03 -> 0.45 / 0.51 / 0.69
-//   d = 64  1.49 / 1.95 / 2.48 -> 0.93 / 1.07 / 1.30
+//   d = 16  0.42 / 0.52 / 0.65 -> 0.29 / 0.32 / 0.39        d = 32  0.66 / 0.83 / 1.03 -> 0.43 / 0.50 / 0.68
+//   d = 64  1.49 / 1.95 / 2.48 -> 0.90 / 1.05 / 1.28
 //
 // bf16 tensors are one term; probabilities and dS, which multiply them, are cut into three, so that every product is the float32
 // one (share of `out` and dv that are not the correctly rounded result: 1e-4 to 4e-4; with two terms 2e-3).  Before, bf16 tiles
 // of one row; d = 32 on 64 n longitudes: kernels that rounded the forward's probabilities to bf16:
-//   d = 16  0.29 / 0.34 / 0.41 -> 0.20 / 0.21 / 0.27        d = 32  0.28 / 0.35 / 0.51 -> 0.24 / 0.26 / 0.34
-//   d = 64  0.83 / 1.17 / 1.12 -> 0.42 / 0.47 / 0.56
+//   d = 16  0.29 / 0.34 / 0.41 -> 0.19 / 0.21 / 0.26        d = 32  0.28 / 0.35 / 0.51 -> 0.24 / 0.26 / 0.34
+//   d = 64  0.83 / 1.17 / 1.12 -> 0.41 / 0.47 / 0.56
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -645,7 +645,7 @@ nattn_fwd_patch(BandArgs a, const typename G::T *__restrict__ q, const typename 
                     }
                 }
                 bf16x8 p[kTerms];
-                cut(x, p);
+                cut<true>(x, p);
                 acc.add(sh.b + row_at + 4 * tr[0].slot, sh.b + row_at + 4 * tr[N - 1].slot, p);
             };
             int t = 0;
@@ -763,7 +763,7 @@ nattn_bwd_dq_patch(BandArgs a, const typename G::T *__restrict__ q, const typena
 #pragma unroll
                 for (int i = 4 * N; i < 8; ++i) x[i] = 0.f;
                 bf16x8 p[kTerms];
-                cut(x, p);
+                cut<true>(x, p);
                 acc.add(sh.a + row_at + 4 * tr[0].slot, sh.a + row_at + 4 * tr[N - 1].slot, p);
             };
             int t = 0;
@@ -873,9 +873,9 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
 #pragma unroll
                 for (int i = 4 * N; i < 8; ++i) pr[i] = ds[i] = 0.f;
                 bf16x8 p[kTerms];
-                cut(pr, p);
+                cut<true>(pr, p);
                 dva.add(sh.b + row_at + 4 * tr[0].slot, sh.b + row_at + 4 * tr[N - 1].slot, p);
-                cut(ds, p);
+                cut<true>(ds, p);
                 dka.add(sh.a + row_at + 4 * tr[0].slot, sh.a + row_at + 4 * tr[N - 1].slot, p);
             };
             int t = 0;
@@ -905,18 +905,20 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
 
 inline double pair_count(const double (&p)[4], int nbh) { return nbh * (p[0] + p[1] + p[2] + p[3]); }
 
-// Calls f with the geometry for a head dimension
+// Calls f with the geometry for a head dimension.  More workgroups on a compute unit count for more than longer stages (twice the
+// chunks per stage: float32 d = 32 0.56 / 0.65 / 0.73 ms, bf16 d = 32 0.27 / 0.35 / 0.40); the register limits are the loosest that do not
+// cost a workgroup, the tightest without spilled registers (bf16 d = 32: dq 0.28 -> 0.26 ms at five wavefronts, dk/dv 0.45 there).
 enum Launch { kFwd, kDq, kDkdv };
 template <class T, Launch WHICH, class F>
 void by_shape(int dmax, F &&f)
 {
     if constexpr (sizeof(T) == 4) {
-        if (dmax <= 16) f(Geo<T, 16, 32, 4>());
+        if (dmax <= 16) f(Geo<T, 16, 32, WHICH == kDkdv ? 4 : 3>());
         else if (dmax <= 32) f(Geo<T, 32, 16, WHICH == kDq ? 4 : 3>());
         else f(Geo<T, 64, 16, 2>());
     } else {
         if (dmax <= 16) f(Geo<T, 16, 64, 4>());
-        else if (dmax <= 32) f(Geo<T, 32, 32, 4>());
+        else if (dmax <= 32) f(Geo<T, 32, 32, WHICH == kDq ? 5 : 4>());
         else f(Geo<T, 64, 32, 3>());
     }
 }
