@@ -224,13 +224,66 @@ static void build_sides(s2_grid *g)
         }
 }
 
+// The bands of owner rows whose walked rows are c classes of a finer grid's latitudes, with the latitudes as walked rows: offsets in
+// their columns, from column c u.  False where a latitude's classes do not make one arc (or 16 bits do not hold it).
+static bool whole_latitudes(std::vector<int> &blo, std::vector<int> &bn, std::vector<int2> &arc, int nU, int c)
+{
+    const int n_own = int(blo.size()), bmax = int(arc.size() / blo.size()), nW = nU * c, most = (bmax + c - 2) / c + 1;
+    if (nW >= 1 << 15) return false;
+    std::vector<int> lo(n_own, 0), n(n_own, 0);
+    std::vector<int2> out(size_t(n_own) * most, make_int2(0, 0));
+    std::vector<char> met(nW);
+    for (int v = 0; v < n_own; ++v) {
+        if (bn[v] <= 0) continue;
+        lo[v] = blo[v] / c;
+        n[v] = (blo[v] + bn[v] - 1) / c - lo[v] + 1;
+        for (int i = 0; i < n[v]; ++i) {
+            int total = 0, first = 1 << 30, last = -(1 << 30);
+            bool circles = false;
+            auto each = [&](auto f) {
+                for (int s = 0; s < c; ++s) {
+                    const int b = (lo[v] + i) * c + s - blo[v];
+                    if (b >= 0 && b < bn[v] && arc[size_t(v) * bmax + b].y > 0) f(s, arc[size_t(v) * bmax + b]);
+                }
+            };
+            each([&](int s, int2 a) {
+                total += std::min(a.y, nU);
+                first = std::min(first, c * a.x + s);
+                last = std::max(last, c * (a.x + a.y - 1) + s);
+                circles |= a.y >= nU;
+            });
+            if (total == 0 || total == nW) {
+                first = 0;
+            } else if (circles || last - first + 1 != total) {           // counted on the circle
+                std::fill(met.begin(), met.end(), 0);
+                each([&](int s, int2 a) {
+                    for (int k = 0; k < std::min(a.y, nU); ++k) met[size_t(((c * (a.x + k) + s) % nW + nW) % nW)] = 1;
+                });
+                int starts = 0;
+                for (int x = 0; x < nW; ++x)
+                    if (met[x] && !met[(x + nW - 1) % nW]) {
+                        first = x > 0 ? x - nW : 0;
+                        ++starts;
+                    }
+                if (starts != 1) return false;
+            }
+            out[size_t(v) * most + i] = make_int2(first, total);
+        }
+    }
+    blo = lo;
+    bn = n;
+    arc = out;
+    return true;
+}
+
 // Segments and workgroups of the patch kernels for one kind of owners.  A wavefront owns 16 points, 1 x 16, 2 x 8 or 4 x 4 rows x
 // columns: a square patch meets the fewest walked columns where arcs are short; where they are long, owners of one row share
 // more of theirs.  Each group of four rows takes the shape with the fewest chunks of four columns to walk (counted, not measured).
 static void build_patches(const std::vector<int> &blo, const std::vector<int> &bn, const std::vector<int2> &arc, int nU, const float *omega,
-                          int c_walk, s2_grid::Patches &p)
+                          int c_walk, int step, s2_grid::Patches &p)
 {
-    const int n_own = int(blo.size()), bmax = int(arc.size() / blo.size()), ngrp = (n_own + 3) / 4;
+    const int n_own = int(blo.size()), bmax = int(arc.size() / blo.size()), ngrp = (n_own + 3) / 4, nW = nU * step;
+    p.step = step;
     struct Row {
         int lo, hi;
         bool any;
@@ -267,7 +320,7 @@ static void build_patches(const std::vector<int> &blo, const std::vector<int> &b
             for (int f = 4 * s; f < std::min(4 * s + 4, n_own); f += 1 << lg) {
                 walk(f, std::min(f + (1 << lg), n_own), rmin, rows);
                 for (const Row &r : rows)
-                    if (r.any) chunks += std::min((W + r.hi - r.lo + 3) / 4.0, (nU + 3) / 4.0) / W;
+                    if (r.any) chunks += std::min((step * (W - 1) + r.hi - r.lo + 4) / 4.0, (nW + 3) / 4.0) / W;
             }
             if (least < 0.0 || chunks < least) {
                 least = chunks;
@@ -279,7 +332,7 @@ static void build_patches(const std::vector<int> &blo, const std::vector<int> &b
     p.rows.clear();
     // A row of whole circles, every column once: no owner's mask excludes anything.  Offsets stay within 16 bits.
     constexpr unsigned kAlways = 0xffff8000u;
-    const bool once = nU % 4 == 0 && nU <= 32000;
+    const bool once = nW % 4 == 0 && nW <= 32000;
     for (int s = 0; s < ngrp; ++s) {
         const int lg = shape[s], OW = std::min(kS2PatchWaves * (16 >> lg), nU);
         seg_of[s] = int(p.seg.size() / 2);
@@ -298,8 +351,8 @@ static void build_patches(const std::vector<int> &blo, const std::vector<int> &b
                 }
                 bool always = once && r.any;
                 for (int k = 0; k < l - f; ++k) {
-                    always &= r.own[k].y >= nU;
-                    if (r.own[k].y >= nU) r.own[k] = make_int2(-(nU / 2), nU);
+                    always &= r.own[k].y >= nW;
+                    if (r.own[k].y >= nW) r.own[k] = make_int2(-(nW / 2), nW);
                 }
                 r.lo = 1 << 30;
                 r.hi = -(1 << 30);
@@ -317,7 +370,7 @@ static void build_patches(const std::vector<int> &blo, const std::vector<int> &b
                 o.omega = omega ? omega[(rmin + int(i)) / c_walk] : 1.f;
                 for (int k = 0; k < l - f; ++k) o.arc[k] = always ? kAlways : pack(r.own[k].x, r.own[k].y);
                 p.rows.push_back(o);
-                before += !r.any ? 0 : always ? nU / 4 : (OW + r.hi - c0 + 3) / 4;
+                before += !r.any ? 0 : always ? nW / 4 : (step * (OW - 1) + r.hi - c0 + 4) / 4;
             }
             p.seg.push_back(make_int4(f, lg, rows.empty() ? 0 : rmin + part, int(rows.size()) - part));
             p.seg.push_back(make_int4(before, at, 0, 0));
@@ -448,6 +501,7 @@ static int upload_tables(s2_grid *g)
         q.row_rec = reinterpret_cast<const int4 *>(base + parts[22 + 3 * i].off);
         q.patch = ap(23 + 3 * i);
         q.npatch = int(p.list.size());
+        q.step = p.step;
     }
     g->on_device = true;
     return S2_OK;
@@ -755,8 +809,12 @@ extern "C" int s2_grid_init(int grid_type, int nlat_in, int nlon_in, int nlat_ou
         std::vector<float> omega(nlat_in);
         for (int h = 0; h < nlat_in; ++h) omega[h] = float(g->omega_in[h] / most);
         const int nU = std::min(nlon_in, nlon_out);
-        build_patches(g->vo_lo, g->vo_n, g->vo_arc, nU, omega.data(), g->pscale, g->vo_patch);
-        build_patches(g->vi_lo, g->vi_n, g->vi_arc, nU, nullptr, g->upscale, g->vi_patch);
+        for (int i = 0; i < 2; ++i) {
+            std::vector<int> lo = i ? g->vi_lo : g->vo_lo, n = i ? g->vi_n : g->vo_n;
+            std::vector<int2> arc = i ? g->vi_arc : g->vo_arc;
+            const int c = i ? g->upscale : g->pscale, step = c > 1 && whole_latitudes(lo, n, arc, nU, c) ? c : 1;
+            build_patches(lo, n, arc, nU, i ? nullptr : omega.data(), step > 1 ? 1 : c, step, i ? g->vi_patch : g->vo_patch);
+        }
     }
     int rc = upload_tables(g);
     if (rc != S2_OK) { delete g; return rc; }

@@ -30,11 +30,13 @@ struct S2BandSide {
         const int4 *row_rec;  // 2 per walked row of a segment: S2PatchRow
         const int2 *patch;    // workgroups of a slice, heaviest first: segment, first column
         int npatch;
+        // walked columns per owner column: 1, the rows are classes; c_walk, they are whole latitudes and offsets count their columns
+        int step;
     } patches;
 };
 
 // A walked row as the owners of a segment see it.  The columns that any of a workgroup's owners meets on it are cut into chunks
-// of four; the chunks of all rows are numbered in order.  Columns are relative to the workgroup's first.
+// of four; the chunks of all rows are numbered in order.  Columns are relative to the workgroup's first (times step).
 constexpr int kS2PatchWaves = 4;         // wavefronts of a workgroup
 constexpr int kS2PatchRows = 128;        // walked rows of a part of a segment
 struct S2PatchRow {
@@ -102,6 +104,7 @@ struct s2_grid {
         std::vector<int4> seg;
         std::vector<S2PatchRow> rows;
         std::vector<int2> list;
+        int step = 1;
     } vo_patch, vi_patch;
     int band_max = 0, tband_max = 0;
     // the band and arc tables exactly as eq. (5) gives them (introspection); the tables above, which the kernels

@@ -9,7 +9,7 @@ inline int s2_band_mode(const S2BandSide &b, int d, int e, size_t element)
 {
     if (d != e || (d != 16 && d != 32 && d != 64)) return kRagged;
     const size_t slice = size_t(d) * b.nlat_walk * b.nU * b.c_walk * element;
-    return b.c_walk == 1 && b.nU % 4 == 0 && slice < size_t(1) << 32 ? kWide : kNarrow;
+    return b.c_walk == b.patches.step && b.nU * b.patches.step % 4 == 0 && slice < size_t(1) << 32 ? kWide : kNarrow;
 }
 // f(set) with the launchers of a staging mode
 template <template <int> class Set, class F>

@@ -15,8 +15,11 @@
 // columns where 16 points of one row meet 72; near the poles, where arcs are long, a row is as good.  The columns that any owner of
 // a workgroup meets are cut into chunks of four, numbered row by row (S2PatchRow), and staged CAP at a time.  Of each stage a
 // wavefront lists the chunks its own points meet, four of which are a tile of 16 keys, whatever rows they lie on; masks are per
-// element, from the arc of the owner's row.  Rows of one longitude count nU on both sides: classes of a finer grid are rows of
-// their own (S2BandSide).
+// element, from the arc of the owner's row.  Owner rows have the smaller longitude count nU of the two grids: classes of a finer
+// owner grid are rows of their own (S2BandSide).  Walked rows are whole latitudes, of step columns per owner column: with rows of one
+// class of a finer walked grid, a chunk was four loads of every second column (257 x 512 -> 129 x 256, 8 slices, d = 32: forward
+// 0.329, dq 0.347 ms, now 0.175 and 0.197; the mirror image's dk/dv 0.397, now 0.258).  Where a latitude's classes make no single
+// arc, or 16 bits do not hold its columns, the rows stay classes (step 1).
 //
 // LDS holds a stage as [term][channel][chunk]: channel rows as in memory.  First products (S^T = K Q^T and dP) read it through
 // ds_read_b64_tr_b16, which turns 4 channels x 16 keys on the way to the registers; in the second (O^T += V P^T) the 8 contraction
@@ -30,7 +33,7 @@
 // five of them on a compute unit, whose barriers do not coincide (eight wavefronts, stages twice as long: dk/dv 0.72 against
 // 0.70 ms; all of LDS for one workgroup: 1.43).
 // Measured (129 x 256, 32 slices, forward / dq / dk,dv, ms; before: fp32 matrix cores and vector kernels):
-//   d = 16  0.42 / 0.52 / 0.65 -> 0.29 / 0.32 / 0.39        d = 32  0.66 / 0.83 / 1.03 -> 0.43 / 0.50 / 0.68
+//   d = 16  0.42 / 0.52 / 0.65 -> 0.29 / 0.32 / 0.39        d = 32  0.66 / 0.83 / 1.03 -> 0.43 / 0.49 / 0.67
 //   d = 64  1.49 / 1.95 / 2.48 -> 0.90 / 1.05 / 1.28
 //
 // bf16 tensors are one term; probabilities and dS, which multiply them, are cut into three, so that every product is the float32
@@ -123,8 +126,9 @@ struct PatchWhere {
     bool active;                     // the lane's owner is a point
     size_t plane_own, plane_walk, own_at;
     int nlon_walk, c_own, c_walk, n_own;
+    int step, nW, su, stride;         // columns of a walked row, of them per owner column; step * u; from one to the next in memory
     int seg, rmin, nrows, total, rows_at, more;
-    float inv_nU;
+    float inv_nW;
     __device__ __forceinline__ size_t row_at(int row) const
     {
         if (c_own == 1) return size_t(row) * nU;
@@ -167,12 +171,16 @@ struct PatchWhere {
         nlon_walk = nU * c_walk;
         plane_own = size_t(a.b.nlat_own) * nU * c_own;
         plane_walk = size_t(a.b.nlat_walk) * nlon_walk;
-        inv_nU = 1.f / float(nU);
+        step = a.b.patches.step;
+        nW = nU * step;
+        stride = step == 1 ? c_walk : 1;
+        inv_nW = 1.f / float(nW);
         const bool row_ok = first + sub < n_own;
         set_row(row_ok ? first + sub : first);
         W0 = at.y;
         wc = W0 + wave * W;
         u = wc + (n & (W - 1));
+        su = step * u;
         active = row_ok && u < nU;
     }
     __device__ __forceinline__ size_t walk_at(int r) const
@@ -181,6 +189,8 @@ struct PatchWhere {
         const int lat = r / c_walk;
         return size_t(lat) * nlon_walk + (r - lat * c_walk);
     }
+    // row r of the patch tables
+    __device__ __forceinline__ size_t row_walked(int r) const { return stride == 1 ? size_t(r) * nlon_walk : walk_at(r); }
     // the chunk of the workgroup's own points that holds the points 4 j .. 4 j + 3 of this wavefront
     __device__ __forceinline__ int own_slot(int j, int nw) const
     {
@@ -247,8 +257,8 @@ struct Chunks {
             ++r;
             at += X >= p ? 1 : 0;
         }
-        const int u = t.uni[at], c = t.col[at] + 4 * X + w.W0, d = c + 3 - w.wc - int(short(u & 0xffff));
-        const bool need = X0 + w.lane < w.total && w.wc < w.nU && unsigned(d) < (unsigned(u) >> 16) + w.W + 2;
+        const int u = t.uni[at], c = t.col[at] + 4 * X + w.step * w.W0, d = c + 3 - w.step * w.wc - int(short(u & 0xffff));
+        const bool need = X0 + w.lane < w.total && w.wc < w.nU && unsigned(d) < (unsigned(u) >> 16) + w.step * (w.W - 1) + 3;
         met = __ballot(need);
         const int ones = __builtin_amdgcn_mbcnt_hi(unsigned(met >> 32), __builtin_amdgcn_mbcnt_lo(unsigned(met), 0));
         entry = c << 14 | at << 6 | (w.lane & (G::CAP - 1));
@@ -281,12 +291,12 @@ struct Place {
     __device__ __forceinline__ void set(const PatchWhere &w, int row, int col)
     {
         if constexpr (WIDE) {
-            const unsigned c = unsigned(wrap_col(col + 2 * w.nU, w.nU, w.inv_nU));
-            off[0] = unsigned(sizeof(typename G::T)) * (unsigned(cg) * unsigned(w.plane_walk) + unsigned(row) * unsigned(w.nU) + c);
+            const unsigned c = unsigned(wrap_col(col + 2 * w.nW, w.nW, w.inv_nW));
+            off[0] = unsigned(sizeof(typename G::T)) * (unsigned(cg) * unsigned(w.plane_walk) + unsigned(row) * unsigned(w.nW) + c);
         } else {
-            const unsigned at = unsigned(w.walk_at(row));
+            const unsigned at = unsigned(w.row_walked(row));
 #pragma unroll
-            for (int i = 0; i < 4; ++i) off[i] = at + unsigned(w.c_walk) * unsigned(wrap_col(col + i + 2 * w.nU, w.nU, w.inv_nU));
+            for (int i = 0; i < 4; ++i) off[i] = at + unsigned(w.stride) * unsigned(wrap_col(col + i + 2 * w.nW, w.nW, w.inv_nW));
         }
     }
     // the same place in a float32 plane
@@ -506,10 +516,10 @@ struct TileRef {
         row = at + g < end ? m >> 6 & 255 : kDead;
         col = m >> 14;
     }
-    // keep[rr]: is column col + rr a neighbor of owner u
-    __device__ __forceinline__ void keep(bool (&keep)[4], int u, unsigned arc) const
+    // keep[rr]: is column col + rr a neighbor of the owner at walked column su
+    __device__ __forceinline__ void keep(bool (&keep)[4], int su, unsigned arc) const
     {
-        const unsigned rel = unsigned(col - (u + int(short(arc & 0xffff))));
+        const unsigned rel = unsigned(col - (su + int(short(arc & 0xffff))));
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) keep[rr] = rel + rr < (arc >> 16);
     }
@@ -617,7 +627,7 @@ nattn_fwd_patch(BandArgs a, const typename G::T *__restrict__ q, const typename 
                     const f32x4 sc = dot<G>(sh.a + tr_at + 4 * tr[i].slot_n, own);
                     omega[i] = __builtin_bit_cast(float, arc.y);
                     bool keep[4];
-                    tr[i].keep(keep, w.u, arc.x);
+                    tr[i].keep(keep, w.su, arc.x);
 #pragma unroll
                     for (int rr = 0; rr < 4; ++rr) x[4 * i + rr] = keep[rr] ? sc[rr] : -INFINITY;
                 }
@@ -753,7 +763,7 @@ nattn_bwd_dq_patch(BandArgs a, const typename G::T *__restrict__ q, const typena
                     const uint2 arc = sh.rows.arc[w.sub][tr[i].row];
                     const f32x4 sc = dot<G>(sh.a + tr_at + 4 * tr[i].slot_n, oq), dp = dot<G>(sh.b + tr_at + 4 * tr[i].slot_n, og);
                     bool keep[4];
-                    tr[i].keep(keep, w.u, arc.x);
+                    tr[i].keep(keep, w.su, arc.x);
 #pragma unroll
                     for (int rr = 0; rr < 4; ++rr) {
                         const float ds = __builtin_bit_cast(float, arc.y) * __builtin_amdgcn_exp2f(fmaf(sc[rr], c2, -L2)) * (dp[rr] - dsum);
@@ -862,7 +872,7 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
                     const f32x4 L = *reinterpret_cast<const f32x4 *>(sh.L + 4 * tr[i].slot), Dn = *reinterpret_cast<const f32x4 *>(sh.D + 4 * tr[i].slot);
                     const f32x4 sc = dot<G>(sh.a + tr_at + 4 * tr[i].slot_n, ok), dp = dot<G>(sh.b + tr_at + 4 * tr[i].slot_n, ov);
                     bool keep[4];
-                    tr[i].keep(keep, w.u, arc);
+                    tr[i].keep(keep, w.su, arc);
 #pragma unroll
                     for (int rr = 0; rr < 4; ++rr) {
                         const float x = __builtin_amdgcn_exp2f(fmaf(sc[rr], c2, L[rr]));

@@ -14,9 +14,11 @@ int s2_nattn_mfma_configure() { return 0; }
 int s2_nattn_band_configure() { return 0; }
 int s2_static_scratch_setup(int) { return 0; }
 
-static int check(const s2_grid::Patches &p, const std::vector<int> &blo, const std::vector<int> &bn, const std::vector<int2> &arc, int nU)
+static int check(const s2_grid::Patches &p, const std::vector<int> &blo, const std::vector<int> &bn, const std::vector<int2> &arc, int nU, int c_walk)
 {
     const int n_own = int(blo.size()), bmax = int(arc.size() / blo.size());
+    const int S = p.step, nW = S * nU;
+    if (S != c_walk) return 7;               // whole latitudes, at these sizes
     std::vector<int> seen(size_t(n_own) * nU, 0);
     for (const int2 &wg : p.list) {
         const int4 s0 = p.seg[2 * wg.x];
@@ -34,14 +36,15 @@ static int check(const s2_grid::Patches &p, const std::vector<int> &blo, const s
                     const S2PatchRow &r = p.rows[t1.y + i];
                     const int end = i + 1 < t0.w ? p.rows[t1.y + i + 1].before : t1.x;
                     for (int X = r.before; X < end; ++X) {
-                        const int col = r.col + 4 * X + wg.y, d = col + 3 - wc - int(short(r.uni & 0xffff));
-                        if (col < -2 * nU || col + 3 + 2 * nU >= 1 << 22 || col >= 1 << 17 || col < -(1 << 17)) return 2;    // what wrap_col and a list entry hold
-                        const unsigned a = r.arc[n / W], rel = unsigned(col - (u + int(short(a & 0xffff))));
-                        const bool listed = unsigned(d) < (unsigned(r.uni) >> 16) + W + 2;
+                        const int col = r.col + 4 * X + S * wg.y, d = col + 3 - S * wc - int(short(r.uni & 0xffff));
+                        if (col < -2 * nW || col + 3 + 2 * nW >= 1 << 22 || col >= 1 << 17 || col < -(1 << 17)) return 2;    // what wrap_col and a list entry hold
+                        const unsigned a = r.arc[n / W], rel = unsigned(col - (S * u + int(short(a & 0xffff))));
+                        const bool listed = unsigned(d) < (unsigned(r.uni) >> 16) + S * (W - 1) + 3;
                         for (int j = 0; j < 4; ++j)
                             if (rel + j < (a >> 16)) {
                                 if (!listed) return 3;
-                                ++met[{t0.z + i, ((col + j) % nU + nU) % nU}];
+                                const int at = ((col + j) % nW + nW) % nW;
+                                ++met[{(t0.z + i) * S + at % S, at / S}];
                             }
                     }
                 }
@@ -68,7 +71,8 @@ int main(int argc, char **argv)
     s2_grid_t *g = nullptr;
     if (argc != 7 || s2_grid_init(atoi(argv[1]), atoi(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atof(argv[6]), &g) != S2_OK) return 100;
     const int nU = g->nlon_in < g->nlon_out ? g->nlon_in : g->nlon_out;
-    const int a = check(g->vo_patch, g->vo_lo, g->vo_n, g->vo_arc, nU), b = check(g->vi_patch, g->vi_lo, g->vi_n, g->vi_arc, nU);
+    const int a = check(g->vo_patch, g->vo_lo, g->vo_n, g->vo_arc, nU, g->pscale),
+              b = check(g->vi_patch, g->vi_lo, g->vi_n, g->vi_arc, nU, g->upscale);
     s2_grid_destroy(g);
     printf("%d %d\n", a, b);
     return a ? a : b ? 10 + b : 0;
