@@ -917,9 +917,10 @@ inline double pair_count(const double (&p)[4], int nbh) { return nbh * (p[0] + p
 
 // Calls f with the geometry for a head dimension.  More workgroups on a compute unit count for more than longer stages (twice the
 // chunks per stage: float32 d = 32 0.56 / 0.65 / 0.73 ms, bf16 d = 32 0.27 / 0.35 / 0.40); the register limits are the loosest that do not
-// cost a workgroup, the tightest without spilled registers (bf16 d = 32: dq 0.28 -> 0.26 ms at five wavefronts, dk/dv 0.45 there).
+// cost a workgroup, the tightest without spilled registers (bf16 d = 32 at five
+// wavefronts: forward 0.25 -> 0.24, dq 0.28 -> 0.26, dk/dv 0.34 -> 0.45 ms).
 enum Launch { kFwd, kDq, kDkdv };
-template <class T, Launch WHICH, class F>
+template <class T, int MODE, Launch WHICH, class F>
 void by_shape(int dmax, F &&f)
 {
     if constexpr (sizeof(T) == 4) {
@@ -928,7 +929,7 @@ void by_shape(int dmax, F &&f)
         else f(Geo<T, 64, 16, 2>());
     } else {
         if (dmax <= 16) f(Geo<T, 16, 64, 4>());
-        else if (dmax <= 32) f(Geo<T, 32, 32, WHICH == kDq ? 5 : 4>());
+        else if (dmax <= 32) f(Geo<T, 32, 32, MODE == kWide && WHICH != kDkdv ? 5 : 4>());
         else f(Geo<T, 64, 32, 3>());
     }
 }
@@ -951,9 +952,9 @@ int PatchKernels<T, MODE>::configure()
 {
     bool bad = false;
     for (int d : {16, 32, 64}) {
-        by_shape<T, kFwd>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_fwd_patch<decltype(g), MODE>), sizeof(Shared<decltype(g)>)); });
-        by_shape<T, kDq>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dq_patch<decltype(g), MODE>), sizeof(SharedDq<decltype(g)>)); });
-        by_shape<T, kDkdv>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dkdv_patch<decltype(g), MODE>), sizeof(SharedDkdv<decltype(g)>)); });
+        by_shape<T, MODE, kFwd>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_fwd_patch<decltype(g), MODE>), sizeof(Shared<decltype(g)>)); });
+        by_shape<T, MODE, kDq>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dq_patch<decltype(g), MODE>), sizeof(SharedDq<decltype(g)>)); });
+        by_shape<T, MODE, kDkdv>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dkdv_patch<decltype(g), MODE>), sizeof(SharedDkdv<decltype(g)>)); });
     }
     return bad;
 }
@@ -962,7 +963,7 @@ void PatchKernels<T, MODE>::fwd(const S2DeviceTables &t, int nbh, int d, int e, 
                                 hipStream_t st)
 {
     const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale);
-    by_shape<T, kFwd>(d > e ? d : e, [&](auto g) {
+    by_shape<T, MODE, kFwd>(d > e ? d : e, [&](auto g) {
         using G = decltype(g);
         hipLaunchKernelGGL((nattn_fwd_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(Shared<G>), st, l.a, q, k, v, out, lse);
     });
@@ -972,7 +973,7 @@ void PatchKernels<T, MODE>::dq(const S2DeviceTables &t, int nbh, int d, int e, f
                                const float *lse, const T *go, T *dq, float *Dws, hipStream_t st)
 {
     const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale);
-    by_shape<T, kDq>(d > e ? d : e, [&](auto g) {
+    by_shape<T, MODE, kDq>(d > e ? d : e, [&](auto g) {
         using G = decltype(g);
         hipLaunchKernelGGL((nattn_bwd_dq_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(SharedDq<G>), st, l.a, q, k, v, o, lse, go, dq, Dws);
     });
@@ -982,7 +983,7 @@ void PatchKernels<T, MODE>::dkdv(const S2DeviceTables &t, int nbh, int d, int e,
                                  const T *go, const float *Dws, T *dk, T *dv, hipStream_t st)
 {
     const PatchLaunch l = patch_launch(t, t.side_in, nbh, d, e, scale);
-    by_shape<T, kDkdv>(d > e ? d : e, [&](auto g) {
+    by_shape<T, MODE, kDkdv>(d > e ? d : e, [&](auto g) {
         using G = decltype(g);
         hipLaunchKernelGGL((nattn_bwd_dkdv_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(SharedDkdv<G>), st, l.a, q, k, v, lse, go, Dws, dk, dv);
     });
