@@ -189,6 +189,9 @@ struct PatchWhere {
         const int lat = r / c_walk;
         return size_t(lat) * nlon_walk + (r - lat * c_walk);
     }
+    // do four points of an owner row lie side by side; kWide: at a multiple of four, in rows of a multiple of four
+    template <int MODE>
+    __device__ __forceinline__ bool own_pieces() const { return c_own == 1 && (MODE == kWide ? nU % 4 == 0 : nU >= 4); }
     // row r of the patch tables
     __device__ __forceinline__ size_t row_walked(int r) const { return stride == 1 ? size_t(r) * nlon_walk : walk_at(r); }
     // the chunk of the workgroup's own points that holds the points 4 j .. 4 j + 3 of this wavefront
@@ -277,11 +280,16 @@ struct Chunks {
     }
 };
 
-// One tensor's stage: from memory to registers, and (float32: cut into three terms) on to LDS.
+// One tensor's stage.  Pieces of four elements, also where rows are no multiple of four long (kNarrow, kRagged: at any alignment,
+// a piece astride the end of its row element by element, with all of the wavefront's): as four loads each, 154 x 306, 4 slices, d = 64,
+// bf16, forward 196 us, now 130; 179 x 358, 6 slices, d = 32, bf16, forward and backward 859 -> 595; around the seam of circles of
+// some thirty longitudes, where most pieces are apart, 24.3 -> 25.4.
+// From memory to registers, and (float32: cut into three terms) on to LDS.
 template <class G, int MODE>
 struct Place {
     static constexpr bool WIDE = MODE == kWide;
     unsigned off[WIDE ? 1 : 4];      // kWide: byte offset of the thread's first piece in the slice; else elements in a channel plane
+    bool apart;                      // not kWide: a chunk of the wavefront's is not four elements side by side (uniform; else off[0] only)
     int x, cg;                       // the thread's chunk and first channel
     __device__ __forceinline__ void init(const PatchWhere &w)
     {
@@ -295,8 +303,12 @@ struct Place {
             off[0] = unsigned(sizeof(typename G::T)) * (unsigned(cg) * unsigned(w.plane_walk) + unsigned(row) * unsigned(w.nW) + c);
         } else {
             const unsigned at = unsigned(w.row_walked(row));
+            const int c = wrap_col(col + 2 * w.nW, w.nW, w.inv_nW);
+            apart = w.stride > 1 || __any(c + 4 > w.nW);
+            off[0] = at + unsigned(w.stride) * unsigned(c);
+            if (!apart) return;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) off[i] = at + unsigned(w.stride) * unsigned(wrap_col(col + i + 2 * w.nW, w.nW, w.inv_nW));
+            for (int i = 1; i < 4; ++i) off[i] = at + unsigned(w.stride) * unsigned(wrap_col(col + i + 2 * w.nW, w.nW, w.inv_nW));
         }
     }
     // the same place in a float32 plane
@@ -305,6 +317,8 @@ struct Place {
         f32x4 s;
         if constexpr (WIDE) {
             s = load_at<f32x4>(plane, off[0] / unsigned(sizeof(typename G::T)) * 4u - 4u * unsigned(cg) * unsigned(w.plane_walk));
+        } else if (!apart) {
+            __builtin_memcpy(&s, plane + off[0], sizeof s);
         } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i) s[i] = plane[off[i]];
@@ -320,30 +334,41 @@ struct Stage {
     Piece r[G::NP];
     __device__ __forceinline__ void load(const PatchWhere &w, const P &at, const T *slice, int nch)
     {
+        if constexpr (P::WIDE) {
 #pragma unroll
-        for (int j = 0; j < G::NP; ++j) {
-            if constexpr (P::WIDE) {
-                r[j] = load_at<Piece>(slice + size_t(j * G::NG) * w.plane_walk, at.off[0]);
-            } else {
+            for (int j = 0; j < G::NP; ++j) r[j] = load_at<Piece>(slice + size_t(j * G::NG) * w.plane_walk, at.off[0]);
+        } else {
+            auto channel = [&](int j) {
                 const int c = at.cg + j * G::NG;
-                const T *p = slice + size_t(MODE == kRagged ? imin(c, nch - 1) : c) * w.plane_walk;
+                return slice + size_t(MODE == kRagged ? imin(c, nch - 1) : c) * w.plane_walk;
+            };
+            if (!at.apart) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) r[j][i] = p[at.off[i]];
+                for (int j = 0; j < G::NP; ++j) __builtin_memcpy(&r[j], channel(j) + at.off[0], sizeof r[j]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < G::NP; ++j) {
+                    const T *p = channel(j);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) r[j][i] = p[at.off[i]];
+                }
             }
         }
     }
-    // the workgroup's own points; vec: its rows are contiguous and their length a multiple of four
+    // the workgroup's own points; vec: its rows are contiguous
     __device__ __forceinline__ void load_own(const PatchWhere &w, const T *slice, int nch, bool vec)
     {
         const int h = 2 - here_s(w.lg), tid = here_v(w.tid), x = tid & (G::OWN - 1), cg = tid / G::CAP, sub = (x / G::NW) >> h;
         const int row = w.first + sub < w.n_own ? w.first + sub : w.first, u = w.W0 + 4 * (x - G::NW * (sub << h));
         const T *p = slice + w.row_at(row);
+        if (!P::WIDE) vec = vec && !__any(u < w.nU && u + 4 > w.nU);       // a row that ends within a piece
 #pragma unroll
         for (int j = 0; j < G::NP; ++j) {
             const int c = cg + j * G::NG;
             const T *pc = p + size_t(MODE == kRagged ? imin(c, nch - 1) : c) * w.plane_own;
             if (vec) {
-                r[j] = *reinterpret_cast<const Piece *>(pc + (u < w.nU ? u : 0));
+                if constexpr (P::WIDE) r[j] = *reinterpret_cast<const Piece *>(pc + (u < w.nU ? u : 0));
+                else __builtin_memcpy(&r[j], pc + (u < w.nU ? u : 0), sizeof r[j]);
             } else {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) r[j][i] = pc[size_t(w.c_own) * imin(u + i, w.nU - 1)];
@@ -536,7 +561,7 @@ __device__ __forceinline__ void put_results(const f32x4 (&acc)[G::D / 16], float
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) p[(16 * mt + rr) * G::PITCH] = again ? __builtin_bit_cast(float, kAgain) : acc[mt][rr] * factor;
 }
-template <class G>
+template <class G, int MODE>
 __device__ __forceinline__ void store_results(typename G::T *slice, int nch, const float *tile, const PatchWhere &w, bool vec)
 {
     const int h = 2 - here_s(w.lg), tid = here_v(w.tid), x = tid % G::OWN, c0 = tid / G::OWN, sub = (x / G::NW) >> h, u = w.W0 + 4 * (x - G::NW * (sub << h));
@@ -556,7 +581,8 @@ __device__ __forceinline__ void store_results(typename G::T *slice, int nch, con
         if constexpr (sizeof(T) == 4) y = __builtin_bit_cast(f32x4, r);
         else y = __builtin_bit_cast(u16x4, __builtin_convertvector(__builtin_bit_cast(f32x4, r), bf16x4));
         if (vec && skip == 0) {
-            *reinterpret_cast<decltype(y) *>(p) = y;
+            if constexpr (MODE == kWide) *reinterpret_cast<decltype(y) *>(p) = y;
+            else __builtin_memcpy(p, &y, sizeof y);
         } else {
             T *pk = p;
 #pragma unroll
@@ -580,7 +606,7 @@ nattn_fwd_patch(BandArgs a, const typename G::T *__restrict__ q, const typename 
     PatchWhere w;
     w.set(a);
     const int n = w.n, g = w.g, nd = MODE == kRagged ? a.d : D, ne = MODE == kRagged ? a.e : D;
-    const bool vec = w.c_own == 1 && w.nU % 4 == 0;
+    const bool vec = w.own_pieces<MODE>();
     const T *qs = q + size_t(w.bh) * nd * w.plane_own, *ks = k + size_t(w.bh) * nd * w.plane_walk, *vs = v + size_t(w.bh) * ne * w.plane_walk;
     Place<G, MODE> at;
     at.init(w);
@@ -682,7 +708,7 @@ nattn_fwd_patch(BandArgs a, const typename G::T *__restrict__ q, const typename 
             fmaf(m - whole, 0.6931471805599453f, logf(ldexpf(lt * a.omega_ref, int(whole))));
     }
     __syncthreads();
-    store_results<G>(out + size_t(w.bh) * ne * w.plane_own, ne, reinterpret_cast<const float *>(sh.a), w, vec);
+    store_results<G, MODE>(out + size_t(w.bh) * ne * w.plane_own, ne, reinterpret_cast<const float *>(sh.a), w, vec);
     exact_fwd<T, PatchWhere>(again, w.wave);
 }
 
@@ -701,7 +727,7 @@ nattn_bwd_dq_patch(BandArgs a, const typename G::T *__restrict__ q, const typena
     PatchWhere w;
     w.set(a);
     const int n = w.n, g = w.g, nd = MODE == kRagged ? a.d : D, ne = MODE == kRagged ? a.e : D;
-    const bool vec = w.c_own == 1 && w.nU % 4 == 0;
+    const bool vec = w.own_pieces<MODE>();
     const float c2 = a.scale * kLog2e;
     const T *qs = q + size_t(w.bh) * nd * w.plane_own, *gs = go + size_t(w.bh) * ne * w.plane_own, *os = o_ + size_t(w.bh) * ne * w.plane_own;
     const T *ks = k + size_t(w.bh) * nd * w.plane_walk, *vs = v + size_t(w.bh) * ne * w.plane_walk;
@@ -793,7 +819,7 @@ nattn_bwd_dq_patch(BandArgs a, const typename G::T *__restrict__ q, const typena
     __syncthreads();
     put_results<G>(acc.hi, a.scale * a.omega_ref, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
     __syncthreads();
-    store_results<G>(dq + size_t(w.bh) * nd * w.plane_own, nd, reinterpret_cast<const float *>(sh.a), w, vec);
+    store_results<G, MODE>(dq + size_t(w.bh) * nd * w.plane_own, nd, reinterpret_cast<const float *>(sh.a), w, vec);
     exact_dq<T, PatchWhere>(again, w.wave);
 }
 
@@ -813,7 +839,7 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
     PatchWhere w;
     w.set(a);
     const int n = w.n, g = w.g, nd = MODE == kRagged ? a.d : D, ne = MODE == kRagged ? a.e : D;
-    const bool vec = w.c_own == 1 && w.nU % 4 == 0;
+    const bool vec = w.own_pieces<MODE>();
     const float c2 = a.scale * kLog2e;
     const T *ks = k + size_t(w.bh) * nd * w.plane_own, *vs = v + size_t(w.bh) * ne * w.plane_own;
     const T *qs = q + size_t(w.bh) * nd * w.plane_walk, *gs = go + size_t(w.bh) * ne * w.plane_walk;
@@ -908,8 +934,8 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
     put_results<G>(dka.hi, omega * a.scale, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
     put_results<G>(dva.hi, omega, again >> n & 1, reinterpret_cast<float *>(sh.b), w);
     __syncthreads();
-    store_results<G>(dk + size_t(w.bh) * nd * w.plane_own, nd, reinterpret_cast<const float *>(sh.a), w, vec);
-    store_results<G>(dv + size_t(w.bh) * ne * w.plane_own, ne, reinterpret_cast<const float *>(sh.b), w, vec);
+    store_results<G, MODE>(dk + size_t(w.bh) * nd * w.plane_own, nd, reinterpret_cast<const float *>(sh.a), w, vec);
+    store_results<G, MODE>(dv + size_t(w.bh) * ne * w.plane_own, ne, reinterpret_cast<const float *>(sh.b), w, vec);
     exact_dkdv<T, PatchWhere>(again, w.wave);
 }
 
