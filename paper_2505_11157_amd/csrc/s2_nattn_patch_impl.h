@@ -944,19 +944,21 @@ inline double pair_count(const double (&p)[4], int nbh) { return nbh * (p[0] + p
 // Calls f with the geometry for a head dimension.  More workgroups on a compute unit count for more than longer stages (twice the
 // chunks per stage: float32 d = 32 0.56 / 0.65 / 0.73 ms, bf16 d = 32 0.27 / 0.35 / 0.40); the register limits are the loosest that do not
 // cost a workgroup, the tightest without spilled registers (bf16 d = 32 at five
-// wavefronts: forward 0.25 -> 0.24, dq 0.28 -> 0.26, dk/dv 0.34 -> 0.45 ms).
+// wavefronts: forward 0.25 -> 0.24, dq 0.28 -> 0.26, dk/dv 0.34 -> 0.45 ms).  Odd
+// rows take more of them for addresses (128 x 254, 16 slices: dk/dv, float32 d = 16 held to four 0.235 ms, to three 0.217; bf16 d = 64 held to
+// three 0.515, to two 0.429; bf16 d = 32 to four 0.214, to three 0.220).
 enum Launch { kFwd, kDq, kDkdv };
 template <class T, int MODE, Launch WHICH, class F>
 void by_shape(int dmax, F &&f)
 {
     if constexpr (sizeof(T) == 4) {
-        if (dmax <= 16) f(Geo<T, 16, 32, WHICH == kDkdv ? 4 : 3>());
+        if (dmax <= 16) f(Geo<T, 16, 32, MODE == kWide && WHICH == kDkdv ? 4 : 3>());
         else if (dmax <= 32) f(Geo<T, 32, 16, WHICH == kDq ? 4 : 3>());
         else f(Geo<T, 64, 16, 2>());
     } else {
         if (dmax <= 16) f(Geo<T, 16, 64, 4>());
         else if (dmax <= 32) f(Geo<T, 32, 32, MODE == kWide && WHICH != kDkdv ? 5 : 4>());
-        else f(Geo<T, 64, 32, 3>());
+        else f(Geo<T, 64, 32, MODE != kWide && WHICH == kDkdv ? 2 : 3>());
     }
 }
 struct PatchLaunch {
