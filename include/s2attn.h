@@ -117,16 +117,14 @@ size_t s2_nattn_bwd_workspace_bytes(const s2_grid_t *g, int batch, int heads, in
  * Layouts (contiguous): q, out [batch][heads][d][nlat_out][nlon_out] (out has
  * d_v channels); k [batch][heads][d_qk][nlat_in][nlon_in]; v likewise with d_v;
  * lse float32 [batch][heads][nlat_out][nlon_out].
- * dtype: S2_F32 (float32 tensors, float32 arithmetic throughout) or S2_BF16 (q, k, v, out bf16; up to 64 channels the
- * products run on the bf16 matrix cores with float32 accumulation and softmax - probabilities enter them as bf16 on equal
- * grids with d_qk = d_v = 32 and a longitude count that is a multiple of 64, as exact sums of three bf16 terms on all other
- * shapes; above 64 channels, or with more than 128 walked latitudes per output latitude, float32 arithmetic on bf16 loads;
- * lse float32 either way).
+ * dtype: S2_F32 (float32 tensors; up to 64 channels the products run on the bf16 matrix cores, every value as an exact sum of
+ * three bf16 terms, with what is left out of a product below 2^-26 of it) or S2_BF16 (q, k, v, out bf16; up to 64 channels the
+ * products run on the bf16 matrix cores, probabilities as exact sums of three bf16 terms; above, float32 arithmetic on bf16
+ * loads).  Accumulation, softmax and lse are float32 either way.
  * d_qk, d_v in [1, 128].
  * Non-finite inputs (both directions): a NaN or an infinity at a point reaches the results whose sums hold that point
- * and no others.  Exception: with d_qk = d_v = 32, float32 tensors on equal, 2:1 and 1:2 grids and bf16 tensors on
- * equal grids with a longitude count that is a multiple of 64 may also lose results of points close by (masked
- * products there are multiplied by zero).
+ * and no others.  Exception: with d_qk = d_v = 32, float32 tensors on grids of 2^15 or more longitudes may also lose
+ * results of points close by (masked products there are multiplied by zero).
  * Errors: S2_ERR_INVALID_ARG (NULL or not 16-byte aligned pointers, sizes < 1),
  * S2_ERR_UNSUPPORTED (dtype, head dims), S2_ERR_DEVICE (host-only handle or
  * launch failure).

@@ -14,7 +14,7 @@
 // consecutive longitude offsets centred on w' = 0 (cnt odd), or the whole
 // circle (cnt == nlon_in).  tband_*/tcnt hold the same numbers indexed by the
 // input latitude (input point -> output latitudes), used by the dk/dv gather.
-// The same relation as the tile kernels walk it (s2_nattn_walk.h), for one kind of owners: outputs (forward, dq) or inputs
+// The same relation as rows of one longitude count, for one kind of owners: outputs (forward, dq) or inputs
 // (dk/dv).  Where the longitude counts of the two grids differ, the latitudes of the finer one are cut into interleaved
 // classes, so that owner rows and walked rows all have nU = min(nlon_in, nlon_out) columns: owner row v is latitude
 // v / c_own, longitudes c_own * u + v % c_own; the same for walked rows with c_walk.
