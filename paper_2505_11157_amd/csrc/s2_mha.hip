@@ -11,22 +11,24 @@
 #include <algorithm>
 #include <initializer_list>
 
+#include <type_traits>
+
 #include "s2_nattn_kernels.h"
 
 namespace {
 
-// block-wide sum of one value per thread (256 threads), result in every thread; fixed order
+// Sum over a workgroup of THREADS, the same in every thread, in a fixed order
+template <int THREADS>
 __device__ __forceinline__ float block_sum(float x, float *red)
 {
-    const int tid = threadIdx.x;
-    red[tid] = x;
-    __syncthreads();
 #pragma unroll
-    for (int s = 128; s > 0; s >>= 1) {
-        if (tid < s) red[tid] += red[tid + s];
-        __syncthreads();
-    }
-    const float r = red[0];
+    for (int s = 32; s > 0; s >>= 1) x += __shfl_xor(x, s);
+    const int tid = threadIdx.x;
+    if ((tid & 63) == 0) red[tid >> 6] = x;
+    __syncthreads();
+    float r = red[0];
+#pragma unroll
+    for (int i = 1; i < THREADS / 64; ++i) r += red[i];
     __syncthreads();
     return r;
 }
@@ -34,78 +36,107 @@ __device__ __forceinline__ float block_sum(float x, float *red)
 // Instance normalisation: one workgroup per (batch, channel): mean and 1 / sqrt(var + eps) over the N grid points
 // (two passes: the moments are taken about the mean), then xn = gamma xhat + beta + pos.  N is a multiple of 4 and the
 // rows are 16-byte aligned: 16-byte accesses, each lane with four running sums (one per component) that are added in a
-// fixed order.
+// fixed order.  A row of up to 4 KEEP THREADS points is read once and kept in registers: short ones by 256 threads (28 x 48,
+// 512 rows: 1024 threads 2 us more of 52), longer ones by 1024; KEEP = 0: what is longer still, read three times.  Bound: memory (129 x 256, 4 x 128 channels: 256 threads that read three times 51 us, 30 with the row
+// kept; backward 59, 45).
+constexpr int kNormKeep = 9;
+template <class F>
+void by_row(int N, F &&f)       // f(threads, KEEP)
+{
+    using std::integral_constant;
+    if (N <= 4 * kNormKeep * 256) f(integral_constant<int, 256>(), integral_constant<int, kNormKeep>());
+    else if (N <= 4 * kNormKeep * 1024) f(integral_constant<int, 1024>(), integral_constant<int, kNormKeep>());
+    else f(integral_constant<int, 1024>(), integral_constant<int, 0>());
+}
 __device__ __forceinline__ float sum4(float4 a) { return (a.x + a.y) + (a.z + a.w); }
 
-__global__ void __launch_bounds__(256)
+// f(r, i) for the pieces i of a row of n4 that are this thread's, r = 0, 1, ... (in registers where KEEP says so)
+template <int THREADS, int KEEP, class F>
+__device__ __forceinline__ void pieces(int n4, F &&f)
+{
+    if constexpr (KEEP > 0) {
+#pragma unroll
+        for (int r = 0; r < KEEP; ++r) {
+            const int i = threadIdx.x + r * THREADS;
+            if (i < n4) f(r, i);
+        }
+    } else {
+#pragma unroll 4
+        for (int i = threadIdx.x; i < n4; i += THREADS) f(0, i);
+    }
+}
+
+template <int THREADS, int KEEP>
+__global__ void __launch_bounds__(THREADS)
 mha_instnorm_fwd(int C, int N, float eps, const float *__restrict__ x, const float *__restrict__ gamma,
                  const float *__restrict__ beta, const float *__restrict__ pos, float *__restrict__ mean,
                  float *__restrict__ rstd, float *__restrict__ xn)
 {
-    __shared__ float red[256];
-    const int bc = blockIdx.x, c = bc % C, tid = threadIdx.x, n4 = N >> 2;
+    __shared__ float red[THREADS / 64];
+    const int bc = blockIdx.x, c = bc % C, n4 = N >> 2;
     const float4 *xr = reinterpret_cast<const float4 *>(x + size_t(bc) * N);
+    float4 kept[KEEP > 0 ? KEEP : 1];
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 4
-    for (int i = tid; i < n4; i += 256) {
-        const float4 a = xr[i];
+    if (KEEP > 0) pieces<THREADS, KEEP>(n4, [&](int r, int i) { kept[r] = xr[i]; });
+    auto at = [&](int r, int i) { return KEEP > 0 ? kept[r] : xr[i]; };
+    pieces<THREADS, KEEP>(n4, [&](int r, int i) {
+        const float4 a = at(r, i);
         s.x += a.x; s.y += a.y; s.z += a.z; s.w += a.w;
-    }
-    const float mu = block_sum(sum4(s), red) / float(N);
+    });
+    const float mu = block_sum<THREADS>(sum4(s), red) / float(N);
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 4
-    for (int i = tid; i < n4; i += 256) {
-        const float4 a = xr[i];
+    pieces<THREADS, KEEP>(n4, [&](int r, int i) {
+        const float4 a = at(r, i);
         const float dx = a.x - mu, dy = a.y - mu, dz = a.z - mu, dw = a.w - mu;
         v.x = fmaf(dx, dx, v.x); v.y = fmaf(dy, dy, v.y); v.z = fmaf(dz, dz, v.z); v.w = fmaf(dw, dw, v.w);
-    }
-    const float rs = 1.f / sqrtf(block_sum(sum4(v), red) / float(N) + eps);
-    if (tid == 0) { mean[bc] = mu; rstd[bc] = rs; }
+    });
+    const float rs = 1.f / sqrtf(block_sum<THREADS>(sum4(v), red) / float(N) + eps);
+    if (threadIdx.x == 0) { mean[bc] = mu; rstd[bc] = rs; }
     const float ga = gamma ? gamma[c] : 1.f, be = beta ? beta[c] : 0.f;
     const float4 *pr = pos ? reinterpret_cast<const float4 *>(pos + size_t(c) * N) : nullptr;
     float4 *o = reinterpret_cast<float4 *>(xn + size_t(bc) * N);
-#pragma unroll 4
-    for (int i = tid; i < n4; i += 256) {
-        const float4 a = xr[i], p = pr ? pr[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+    pieces<THREADS, KEEP>(n4, [&](int r, int i) {
+        const float4 a = at(r, i), p = pr ? pr[i] : make_float4(0.f, 0.f, 0.f, 0.f);
         o[i] = make_float4(fmaf(ga, (a.x - mu) * rs, be) + p.x, fmaf(ga, (a.y - mu) * rs, be) + p.y,
                            fmaf(ga, (a.z - mu) * rs, be) + p.z, fmaf(ga, (a.w - mu) * rs, be) + p.w);
-    }
+    });
 }
 
 // dx = dy + rstd (dxhat - mean(dxhat) - xhat mean(dxhat xhat)), dxhat = gamma dxn; one workgroup per (batch, channel).
 // The two sums over the row, of dxn and of dxn xhat, are kept for the gradients of beta and gamma.
-__global__ void __launch_bounds__(256)
+template <int THREADS, int KEEP>
+__global__ void __launch_bounds__(THREADS)
 mha_instnorm_bwd(int C, int N, const float *__restrict__ x, const float *__restrict__ gamma, const float *__restrict__ mean,
                  const float *__restrict__ rstd, const float *__restrict__ dxn, const float *__restrict__ dy,
                  float *__restrict__ dx, float *__restrict__ sums)
 {
-    __shared__ float red[256];
-    const int bc = blockIdx.x, c = bc % C, tid = threadIdx.x, n4 = N >> 2;
+    __shared__ float red[THREADS / 64];
+    const int bc = blockIdx.x, c = bc % C, n4 = N >> 2;
     const float mu = mean[bc], rs = rstd[bc], ga = gamma ? gamma[c] : 1.f;
     const float4 *xr = reinterpret_cast<const float4 *>(x + size_t(bc) * N);
     const float4 *gr = reinterpret_cast<const float4 *>(dxn + size_t(bc) * N);
     const float4 *yr = reinterpret_cast<const float4 *>(dy + size_t(bc) * N);
+    float4 kg[KEEP > 0 ? KEEP : 1], ka[KEEP > 0 ? KEEP : 1];
+    if (KEEP > 0) pieces<THREADS, KEEP>(n4, [&](int r, int i) { kg[r] = gr[i]; ka[r] = xr[i]; });
     float4 s1 = make_float4(0.f, 0.f, 0.f, 0.f), s2 = s1;
-#pragma unroll 2
-    for (int i = tid; i < n4; i += 256) {
-        const float4 g = gr[i], a = xr[i];
+    pieces<THREADS, KEEP>(n4, [&](int r, int i) {
+        const float4 g = KEEP > 0 ? kg[r] : gr[i], a = KEEP > 0 ? ka[r] : xr[i];
         s1.x += g.x; s1.y += g.y; s1.z += g.z; s1.w += g.w;
         s2.x = fmaf(g.x, (a.x - mu) * rs, s2.x); s2.y = fmaf(g.y, (a.y - mu) * rs, s2.y);
         s2.z = fmaf(g.z, (a.z - mu) * rs, s2.z); s2.w = fmaf(g.w, (a.w - mu) * rs, s2.w);
-    }
-    const float t1 = block_sum(sum4(s1), red), t2 = block_sum(sum4(s2), red);
+    });
+    const float t1 = block_sum<THREADS>(sum4(s1), red), t2 = block_sum<THREADS>(sum4(s2), red);
     const float m1 = ga * t1 / float(N), m2 = ga * t2 / float(N);
-    if (tid == 0) {
+    if (threadIdx.x == 0) {
         sums[bc] = t1;
         sums[gridDim.x + bc] = t2;
     }
     float4 *o = reinterpret_cast<float4 *>(dx + size_t(bc) * N);
-#pragma unroll 2
-    for (int i = tid; i < n4; i += 256) {
-        const float4 g = gr[i], a = xr[i], y = yr[i];
+    pieces<THREADS, KEEP>(n4, [&](int r, int i) {
+        const float4 g = KEEP > 0 ? kg[r] : gr[i], a = KEEP > 0 ? ka[r] : xr[i], y = yr[i];
         o[i] = make_float4(y.x + rs * (ga * g.x - m1 - (a.x - mu) * rs * m2), y.y + rs * (ga * g.y - m1 - (a.y - mu) * rs * m2),
                            y.z + rs * (ga * g.z - m1 - (a.z - mu) * rs * m2), y.w + rs * (ga * g.w - m1 - (a.w - mu) * rs * m2));
-    }
+    });
 }
 
 // dbeta[c] = sum_b sum_n dxn, dgamma[c] = sum_b sum_n dxn xhat, from the row sums of mha_instnorm_bwd
@@ -211,8 +242,10 @@ extern "C" int s2_mha_fwd(const s2_grid_t *g, int batch, int channels, int heads
     const Layout L = layout(g, batch, C, heads);
     {
         S2TraceScope tr("mha_instnorm_fwd", 0.0, st);
-        hipLaunchKernelGGL(mha_instnorm_fwd, dim3(batch * C), dim3(256), 0, st, C, N, eps, x, p->gamma, p->beta, p->pos,
+        by_row(N, [&](auto threads, auto keep) {
+            hipLaunchKernelGGL((mha_instnorm_fwd<decltype(threads)::value, decltype(keep)::value>), dim3(batch * C), dim3(threads), 0, st, C, N, eps, x, p->gamma, p->beta, p->pos,
                            ws + L.mean, ws + L.rstd, ws + L.xn);
+        });
     }
     {
         S2TraceScope tr("mha_gemm qkv", 0.0, st);
@@ -270,8 +303,10 @@ extern "C" int s2_mha_bwd(const s2_grid_t *g, int batch, int channels, int heads
         if (grads->pos)
             hipLaunchKernelGGL(mha_batch_sum, dim3(unsigned((size_t(C) * N / 4 + 255) / 256)), dim3(256), 0, st, batch,
                                size_t(C) * N / 4, reinterpret_cast<const float4 *>(ws + L.dxn), grads->pos);
-        hipLaunchKernelGGL(mha_instnorm_bwd, dim3(batch * C), dim3(256), 0, st, C, N, x, p->gamma, ws + L.mean, ws + L.rstd,
+        by_row(N, [&](auto threads, auto keep) {
+            hipLaunchKernelGGL((mha_instnorm_bwd<decltype(threads)::value, decltype(keep)::value>), dim3(batch * C), dim3(threads), 0, st, C, N, x, p->gamma, ws + L.mean, ws + L.rstd,
                            ws + L.dxn, dy, dx, ws + L.sums);
+        });
         if (grads->gamma || grads->beta)
             hipLaunchKernelGGL(mha_affine_grads, dim3((C + 255) / 256), dim3(256), 0, st, batch, C, ws + L.sums, grads->gamma,
                                grads->beta);
