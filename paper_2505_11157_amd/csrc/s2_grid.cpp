@@ -810,10 +810,20 @@ extern "C" int s2_grid_init(int grid_type, int nlat_in, int nlon_in, int nlat_ou
         for (int h = 0; h < nlat_in; ++h) omega[h] = float(g->omega_in[h] / most);
         const int nU = std::min(nlon_in, nlon_out);
         for (int i = 0; i < 2; ++i) {
-            std::vector<int> lo = i ? g->vi_lo : g->vo_lo, n = i ? g->vi_n : g->vo_n;
-            std::vector<int2> arc = i ? g->vi_arc : g->vo_arc;
-            const int c = i ? g->upscale : g->pscale, step = c > 1 && whole_latitudes(lo, n, arc, nU, c) ? c : 1;
-            build_patches(lo, n, arc, nU, i ? nullptr : omega.data(), step > 1 ? 1 : c, step, i ? g->vi_patch : g->vo_patch);
+            const std::vector<int> &lo = i ? g->vi_lo : g->vo_lo, &n = i ? g->vi_n : g->vo_n;
+            const std::vector<int2> &arc = i ? g->vi_arc : g->vo_arc;
+            const float *w = i ? nullptr : omega.data();
+            s2_grid::Patches &p = i ? g->vi_patch : g->vo_patch;
+            const int c = i ? g->upscale : g->pscale;
+            if (c > 1) {
+                std::vector<int> wlo = lo, wn = n;
+                std::vector<int2> warc = arc;
+                if (whole_latitudes(wlo, wn, warc, nU, c)) {
+                    build_patches(wlo, wn, warc, nU, w, 1, c, p);
+                    continue;
+                }
+            }
+            build_patches(lo, n, arc, nU, w, c, 1, p);
         }
     }
     int rc = upload_tables(g);

@@ -10,7 +10,6 @@
 // to xn in one, the weight and bias gradients of the three projections in one.
 #include <algorithm>
 #include <initializer_list>
-
 #include <type_traits>
 
 #include "s2_nattn_kernels.h"
