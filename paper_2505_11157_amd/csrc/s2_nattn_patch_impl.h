@@ -28,8 +28,8 @@
 // pieces of whole rows (4-byte loads and stores of 16 points x 4 channels from the lanes: 40 % of the d = 64 launches).
 //
 // What bounds it: issue of vector and matrix instructions, which hardly overlap on a SIMD (a tile is 12 matrix instructions of 16
-// cycles and some 75 vector ones of 2.3, d = 32 forward), and the stalls around the two barriers of a stage; 129 x 256, 32 slices,
-// d = 32: matrix pipes busy 26 % of the forward, vector ALUs 42 %.  Workgroups of four wavefronts and small stages leave three to
+// cycles and some 70 vector ones of 2.4 to 4.2, d = 32 forward), and the stalls around the two barriers of a stage; 129 x 256, 32 slices,
+// d = 32: matrix pipes busy 29 % of the forward, vector ALUs some 50 %, LDS 39 %.  Workgroups of four wavefronts and small stages leave three to
 // five of them on a compute unit, whose barriers do not coincide (eight wavefronts, stages twice as long: dk/dv 0.72 against
 // 0.70 ms; all of LDS for one workgroup: 1.43).
 // Measured (129 x 256, 32 slices, forward / dq / dk,dv, ms; before: fp32 matrix cores and vector kernels):
