@@ -64,7 +64,7 @@ typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
 
 typedef unsigned short bf16raw;      // storage of a bf16 tensor
 constexpr int kDead = kMaxRows;      // the row of a list entry that stands for no chunk: no owner has neighbors on it
-constexpr unsigned kAgain = 0x7fc0a9a1u;     // in place of the results of an owner that s2_nattn_exact.h evaluates: not to be stored
+constexpr unsigned kAgain = 0x7fc0a9a1u;     // in place of a result that s2_nattn_exact.h evaluates: not to be stored
 
 // Channels, chunks per stage, wavefronts per SIMD the registers are held to.
 template <class T_, int D_, int CAP_, int WAVES_>
@@ -200,7 +200,7 @@ struct PatchWhere {
         const int h = 2 - here_s(lg);    // log2(chunks per row of a wavefront)
         return (j >> h) * (nw << h) + (wave << h) + (j & ((1 << h) - 1));
     }
-    // f(u) for every owner whose bit is set, with the row set to the owner's
+    // f(i, u) for every owner i whose bit is set, with the row set to the owner's
     template <class F>
     __device__ __forceinline__ void each(unsigned owners, F &&f)
     {
@@ -208,7 +208,7 @@ struct PatchWhere {
         for (; owners; owners &= owners - 1) {
             const int i = __builtin_ctz(owners);
             set_row(first + i / W);
-            f(wc + (i & (W - 1)));
+            f(i, wc + (i & (W - 1)));
         }
     }
 };
@@ -446,6 +446,17 @@ struct OwnPoint {
         }
     }
 };
+// owners (bit n) with a NaN among their channels
+template <class G>
+__device__ __forceinline__ unsigned own_nan(const OwnPoint<G> &o)
+{
+    bool b = false;
+#pragma unroll
+    for (int s = 0; s < G::KC; ++s)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) b |= float(o.v[s][0][j]) != float(o.v[s][0][j]);
+    return owner_bits(b);
+}
 // (chunks' columns) . (the lane's own point), smallest products first; p: the lane's place in the staged tensor
 template <class G>
 __device__ __forceinline__ f32x4 dot(const __bf16 *p, const OwnPoint<G> &o)
@@ -550,7 +561,8 @@ struct TileRef {
     }
 };
 
-// The results of the workgroup's owners, by way of LDS: acc[mt][rr] is channel 16 mt + 4 g + rr of the lane's owner.
+// The results of the workgroup's owners, by way of LDS: acc[mt][rr] is channel 16 mt + 4 g + rr of the lane's owner.  again: those that
+// are not finite are to be evaluated (marked).
 template <class G>
 __device__ __forceinline__ void put_results(const f32x4 (&acc)[G::D / 16], float factor, bool again, float *tile, const PatchWhere &w)
 {
@@ -559,7 +571,14 @@ __device__ __forceinline__ void put_results(const f32x4 (&acc)[G::D / 16], float
 #pragma unroll
     for (int mt = 0; mt < G::D / 16; ++mt)
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) p[(16 * mt + rr) * G::PITCH] = again ? __builtin_bit_cast(float, kAgain) : acc[mt][rr] * factor;
+        for (int rr = 0; rr < 4; ++rr)
+            p[(16 * mt + rr) * G::PITCH] = again && !(fabsf(acc[mt][rr]) < INFINITY) ? __builtin_bit_cast(float, kAgain) : acc[mt][rr] * factor;
+}
+// is the lane's channel of the wavefront's owner i marked
+template <class G>
+__device__ __forceinline__ bool marked(const float *tile, const PatchWhere &w, int i)
+{
+    return __builtin_bit_cast(unsigned, tile[imin(w.lane, G::D - 1) * G::PITCH + 4 * w.own_slot(i >> 2, G::NW) + (i & 3)]) == kAgain;
 }
 template <class G, int MODE>
 __device__ __forceinline__ void store_results(typename G::T *slice, int nch, const float *tile, const PatchWhere &w, bool vec)
@@ -698,10 +717,15 @@ nattn_fwd_patch(BandArgs a, const typename G::T *__restrict__ q, const typename 
     }
     acc.join_terms();
     const float lt = group_sum(l);
-    const unsigned again = not_finite(acc.hi, w.active);     // owners whose sums took in a non-finite value (s2_nattn_exact.h)
+    // owners whose sums took in a non-finite value (s2_nattn_exact.h); where it is a NaN of their own the sums are right
+    unsigned again = not_finite(acc.hi, w.active), no_lse = 0;
+    if (any_owner(again)) {
+        again &= ~own_nan(own);
+        no_lse = again & owner_bits(lt != lt);
+    }
     __syncthreads();
     put_results<G>(acc.hi, 1.f / lt, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
-    if (w.active && g == 0 && !(again >> n & 1)) {
+    if (w.active && g == 0 && !(no_lse >> n & 1)) {
         // the whole part of m goes into the logarithm, so that its value and the sum are no larger than the result
         const float whole = fminf(fmaxf(rintf(m), -60.f), 60.f);
         lse[size_t(w.bh) * w.plane_own + w.own_at + size_t(w.c_own) * w.u] =
@@ -709,7 +733,7 @@ nattn_fwd_patch(BandArgs a, const typename G::T *__restrict__ q, const typename 
     }
     __syncthreads();
     store_results<G, MODE>(out + size_t(w.bh) * ne * w.plane_own, ne, reinterpret_cast<const float *>(sh.a), w, vec);
-    exact_fwd<T, PatchWhere>(again, w.wave);
+    exact_fwd<T, PatchWhere>(again, no_lse, w.wave, [&](const PatchWhere &at, int i) { return marked<G>(reinterpret_cast<const float *>(sh.a), at, i); });
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -815,12 +839,13 @@ nattn_bwd_dq_patch(BandArgs a, const typename G::T *__restrict__ q, const typena
         if (w.total > 0) fetch(0);
     }
     acc.join_terms();
-    const unsigned again = not_finite(acc.hi, w.active);
+    unsigned again = not_finite(acc.hi, w.active);
+    if (any_owner(again)) again &= ~(own_nan(oq) | owner_bits(dsum != dsum || L2 != L2));       // (these are NaN throughout, as they are)
     __syncthreads();
     put_results<G>(acc.hi, a.scale * a.omega_ref, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
     __syncthreads();
     store_results<G, MODE>(dq + size_t(w.bh) * nd * w.plane_own, nd, reinterpret_cast<const float *>(sh.a), w, vec);
-    exact_dq<T, PatchWhere>(again, w.wave);
+    exact_dq<T, PatchWhere>(again, w.wave, [&](const PatchWhere &at, int i) { return marked<G>(reinterpret_cast<const float *>(sh.a), at, i); });
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -929,14 +954,21 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
     }
     dka.join_terms();
     dva.join_terms();
-    const unsigned again = not_finite(dka.hi, w.active) | not_finite(dva.hi, w.active);
+    unsigned again_k = not_finite(dka.hi, w.active), again_v = not_finite(dva.hi, w.active);
+    if (any_owner(again_k | again_v)) {
+        const unsigned nan = own_nan(ok);                    // (these are NaN throughout, as they are)
+        again_k &= ~(nan | own_nan(ov));
+        again_v &= ~nan;
+    }
     __syncthreads();
-    put_results<G>(dka.hi, omega * a.scale, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
-    put_results<G>(dva.hi, omega, again >> n & 1, reinterpret_cast<float *>(sh.b), w);
+    put_results<G>(dka.hi, omega * a.scale, again_k >> n & 1, reinterpret_cast<float *>(sh.a), w);
+    put_results<G>(dva.hi, omega, again_v >> n & 1, reinterpret_cast<float *>(sh.b), w);
     __syncthreads();
     store_results<G, MODE>(dk + size_t(w.bh) * nd * w.plane_own, nd, reinterpret_cast<const float *>(sh.a), w, vec);
     store_results<G, MODE>(dv + size_t(w.bh) * ne * w.plane_own, ne, reinterpret_cast<const float *>(sh.b), w, vec);
-    exact_dkdv<T, PatchWhere>(again, w.wave);
+    exact_dkdv<T, PatchWhere>(
+        again_k | again_v, w.wave, [&](const PatchWhere &at, int i) { return marked<G>(reinterpret_cast<const float *>(sh.a), at, i); },
+        [&](const PatchWhere &at, int i) { return marked<G>(reinterpret_cast<const float *>(sh.b), at, i); });
 }
 
 inline double pair_count(const double (&p)[4], int nbh) { return nbh * (p[0] + p[1] + p[2] + p[3]); }
