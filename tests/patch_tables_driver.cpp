@@ -18,7 +18,7 @@ static int check(const s2_grid::Patches &p, const std::vector<int> &blo, const s
 {
     const int n_own = int(blo.size()), bmax = int(arc.size() / blo.size());
     const int S = p.step, nW = S * nU;
-    if (S != c_walk) return 7;               // whole latitudes, at these sizes
+    if (S != (c_walk * nU < 1 << 15 ? c_walk : 1)) return 7;      // whole latitudes wherever 16 bits hold their columns, else classes
     std::vector<int> seen(size_t(n_own) * nU, 0);
     for (const int2 &wg : p.list) {
         const int4 s0 = p.seg[2 * wg.x];

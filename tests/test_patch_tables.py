@@ -11,7 +11,9 @@ CSRC = os.path.join(ROOT, "paper_2505_11157_amd", "csrc")
 # has, more walked rows than a table, row counts that leave a segment incomplete, classes of a finer grid on either side, a grid without its pole row
 SHAPES = [(0, 17, 32, 17, 32, 0.39), (0, 33, 64, 33, 64, 0.13), (0, 18, 35, 18, 35, 0.5), (0, 9, 12, 9, 12, 3.1), (1, 9, 7, 9, 7, 0.9),
           (1, 6, 4, 6, 4, 1.2), (0, 37, 72, 37, 72, 0.2), (1, 24, 50, 24, 50, 1.4), (0, 33, 64, 17, 32, 0.4), (0, 17, 32, 33, 64, 0.4),
-          (0, 19, 57, 9, 19, 0.6), (0, 9, 11, 19, 33, 0.7), (2, 20, 40, 20, 40, 0.5), (3, 21, 44, 11, 22, 0.8), (0, 129, 256, 129, 256, 0.0982), (0, 300, 6, 300, 6, 2.9), (0, 150, 4, 75, 4, 3.1)]
+          (0, 19, 57, 9, 19, 0.6), (0, 9, 11, 19, 33, 0.7), (2, 20, 40, 20, 40, 0.5), (3, 21, 44, 11, 22, 0.8), (0, 129, 256, 129, 256, 0.0982), (0, 300, 6, 300, 6, 2.9), (0, 150, 4, 75, 4, 3.1),
+          # on either side of what 16 bits hold: the longest circle, and rows that stay classes of a finer latitude
+          (1, 2, 32764, 2, 32764, 0.003), (1, 3, 40000, 3, 20000, 0.003), (1, 3, 20000, 3, 40000, 0.003), (1, 2, 32766, 2, 16383, 0.003)]
 
 
 @pytest.fixture(scope="module")
