@@ -25,19 +25,13 @@ bool s2_nattn_patch_supported(const S2DeviceTables &t, int d, int e)
     return d <= 64 && e <= 64 && t.band_rows_ok && !s2_debug_flag(S2_DEBUG_NO_MFMA);
 }
 
-// Names of the launches in the trace: those of the kernels that these replaced, so that records compare from version to
-// version.
-static bool streams(const S2DeviceTables &t, int d, int e)
-{
-    return s2_nattn_stream_supported(t, d, e) && s2_nattn_stream_dq_supported(t, d, e) && s2_nattn_stream_dkdv_supported(t, d, e);
-}
 static double pair_count(const double (&p)[4], int nbh) { return nbh * (p[0] + p[1] + p[2] + p[3]); }
 
 int s2_nattn_fwd_patch(const S2DeviceTables &t, int nbh, int d, int e, float scale, const float *q, const float *k,
                        const float *v, float *out, float *lse, hipStream_t st)
 {
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
-    S2TraceScope tr(streams(t, d, e) ? "nattn_fwd_stream" : "nattn_fwd_band", pair_count(t.fwd_pairs, nbh), st);
+    S2TraceScope tr("nattn_fwd_patch", pair_count(t.fwd_pairs, nbh), st);
     s2_by_band_mode<PatchSet>(s2_band_mode(t.side_out, d, e, sizeof(float)), [&](auto set) { set.fwd(t, nbh, d, e, scale, q, k, v, out, lse, st); });
     return 0;
 }
@@ -47,28 +41,22 @@ int s2_nattn_bwd_patch(const S2DeviceTables &t, int nbh, int d, int e, float sca
                        float *Dws, hipStream_t st)
 {
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
-    const bool s = streams(t, d, e);
     {
-        S2TraceScope tr(s ? "nattn_bwd_dq_stream" : "nattn_bwd_dq_band", pair_count(t.fwd_pairs, nbh), st);
+        S2TraceScope tr("nattn_bwd_dq_patch", pair_count(t.fwd_pairs, nbh), st);
         s2_by_band_mode<PatchSet>(s2_band_mode(t.side_out, d, e, sizeof(float)), [&](auto set) { set.dq(t, nbh, d, e, scale, q, k, v, o, lse, go, dq, Dws, st); });
     }
-    S2TraceScope tr(s ? "nattn_bwd_dkdv_stream" : "nattn_bwd_dkdv_band", pair_count(t.bwd_pairs, nbh), st);
+    S2TraceScope tr("nattn_bwd_dkdv_patch", pair_count(t.bwd_pairs, nbh), st);
     s2_by_band_mode<PatchSet>(s2_band_mode(t.side_in, d, e, sizeof(float)), [&](auto set) { set.dkdv(t, nbh, d, e, scale, q, k, v, lse, go, Dws, dk, dv, st); });
     return 0;
 }
 
-// (names, as above)
-static bool was_fast(const S2DeviceTables &t, int d, int e)
-{
-    return d == 32 && e == 32 && t.nlat_in == t.nlat_out && t.nlon_in == t.nlon_out && t.nlon_in % 64 == 0;
-}
 static const unsigned short *in16(const void *p) { return static_cast<const unsigned short *>(p); }
 
 int s2_nattn_fwd_patch_bf16(const S2DeviceTables &t, int nbh, int d, int e, float scale, const void *q, const void *k, const void *v,
                             void *out, float *lse, hipStream_t st)
 {
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
-    S2TraceScope tr(was_fast(t, d, e) ? "nattn_fwd_bf16" : "nattn_fwd_tile", pair_count(t.fwd_pairs, nbh), st);
+    S2TraceScope tr("nattn_fwd_patch", pair_count(t.fwd_pairs, nbh), st);
     s2_by_band_mode<PatchSet16>(s2_band_mode(t.side_out, d, e, 2), [&](auto set) {
         set.fwd(t, nbh, d, e, scale, in16(q), in16(k), in16(v), static_cast<unsigned short *>(out), lse, st);
     });
@@ -78,7 +66,7 @@ int s2_nattn_bwd_dq_patch_bf16(const S2DeviceTables &t, int nbh, int d, int e, f
                                const void *o, const float *lse, const void *go, void *dq, float *Dws, hipStream_t st)
 {
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
-    S2TraceScope tr(was_fast(t, d, e) ? "nattn_bwd_dq_bf16" : "nattn_bwd_dq_tile", pair_count(t.fwd_pairs, nbh), st);
+    S2TraceScope tr("nattn_bwd_dq_patch", pair_count(t.fwd_pairs, nbh), st);
     s2_by_band_mode<PatchSet16>(s2_band_mode(t.side_out, d, e, 2), [&](auto set) {
         set.dq(t, nbh, d, e, scale, in16(q), in16(k), in16(v), in16(o), lse, in16(go), static_cast<unsigned short *>(dq), Dws, st);
     });
@@ -88,7 +76,7 @@ int s2_nattn_bwd_dkdv_patch_bf16(const S2DeviceTables &t, int nbh, int d, int e,
                                  const float *lse, const void *go, const float *Dws, void *dk, void *dv, hipStream_t st)
 {
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
-    S2TraceScope tr(was_fast(t, d, e) ? "nattn_bwd_dkdv_bf16" : "nattn_bwd_dkdv_tile", pair_count(t.bwd_pairs, nbh), st);
+    S2TraceScope tr("nattn_bwd_dkdv_patch", pair_count(t.bwd_pairs, nbh), st);
     s2_by_band_mode<PatchSet16>(s2_band_mode(t.side_in, d, e, 2), [&](auto set) {
         set.dkdv(t, nbh, d, e, scale, in16(q), in16(k), in16(v), lse, in16(go), Dws, static_cast<unsigned short *>(dk), static_cast<unsigned short *>(dv), st);
     });

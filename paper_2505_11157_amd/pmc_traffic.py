@@ -71,9 +71,6 @@ def main():
            "bytes_per_launch": {}, "read_write_MB": {}}
     for n, fd, wd in args.cfg:
         f, w = per_kernel(fd, "FETCH_SIZE"), per_kernel(wd, "WRITE_SIZE")
-        for k in [k for k in f if k.endswith("_patch")]:      # one launch of each per pass, under any of the trace's names for it
-            for name in ("stream", "band", "tile", "bf16"):
-                f[k[:-5] + name], w[k[:-5] + name] = f[k], w.get(k, 0.0)
         keep = [k for k in f if k.startswith(("nattn_", "global_", "prepare_", "disco_", "s2_", "mha_"))]
         res["bytes_per_launch"][n] = {k: (f[k] * kf + w.get(k, 0.0) * kw) * 1024.0 for k in keep}
         res["read_write_MB"][n] = {k: [round(f[k] * kf * 1024.0 / 1e6, 1), round(w.get(k, 0.0) * kw * 1024.0 / 1e6, 1)] for k in keep}

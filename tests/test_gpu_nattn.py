@@ -328,23 +328,29 @@ def test_peaked_softmax_vector_kernels_on_dense_latitudes():
 
 @pytest.mark.parametrize("which", ["cfg3", "small11", "small13"])
 def test_streaming_kernels_take_the_light_latitudes(which):
-    # the launches the library reports for one forward + backward: streaming kernels for the light latitudes
-    # wherever the shape allows them, never the one-wavefront kernels
+    # the launches the library reports for one forward + backward: the patch kernels; without them streaming kernels for the light
+    # latitudes wherever the shape allows them, never the one-wavefront kernels
     if which == "cfg3":
         c, arrs = make_inputs(3)
         arrs = [a[:2] for a in arrs]
         c = dict(c, batch=1, heads=2)
     else:
         c, arrs = make_inputs(SMALL[int(which[5:])], seed=9)
-    S.s2_trace_reset()
-    S.s2_trace_enable(True)
-    try:
-        run_case(c, arrs, [])
-        torch.cuda.synchronize()
-        names = {n for n, _, _ in S.s2_trace_entries()}
-    finally:
-        S.s2_trace_enable(False)
+
+    def launches(slices):
         S.s2_trace_reset()
+        S.s2_trace_enable(True)
+        try:
+            run_case(c, arrs, slices, case=which + "-launches")
+            torch.cuda.synchronize()
+            return {n for n, _, _ in S.s2_trace_entries()}
+        finally:
+            S.s2_trace_enable(False)
+            S.s2_trace_reset()
+
+    assert launches([]) == {"nattn_fwd_patch", "nattn_bwd_dq_patch", "nattn_bwd_dkdv_patch"}
+    with debug_switches(S.S2_DEBUG_NO_BAND):
+        names = launches([1])
     assert {"nattn_fwd_stream", "nattn_bwd_dq_stream", "nattn_bwd_dkdv_stream"} <= names, names
     assert not any("1 wave" in n for n in names), names
 

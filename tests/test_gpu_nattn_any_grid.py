@@ -75,7 +75,7 @@ def test_any_grid_many_slices_bf16(lon, d, batch):
     # staged: four columns at a time (76 longitudes), column by column (75), and with channels missing
     c, arrs = make_inputs(dict(_c(0, 41, lon, 41, lon, 0.3, heads=8, d=d), batch=batch, dtype="bf16"), seed=4600 + d)
     names = _launches(lambda: run_bf16(c, arrs, [0, 8 * batch - 1], "any-many-bf16[%d,d%d,b%d]" % (lon, d, batch)))
-    assert names == {"nattn_fwd_tile", "nattn_bwd_dq_tile", "nattn_bwd_dkdv_tile"}, names
+    assert names == {"nattn_fwd_patch", "nattn_bwd_dq_patch", "nattn_bwd_dkdv_patch"}, names
 
 
 @pytest.mark.parametrize("lon", [76, 75])
@@ -84,7 +84,7 @@ def test_any_grid_many_slices_f32(lon, d):
     # 32 slices: two owner tiles per wavefront (16 channels: in the forward and dq)
     c, arrs = make_inputs(dict(_c(0, 41, lon, 41, lon, 0.3, heads=8, d=d), batch=4), seed=4700 + d)
     names = _launches(lambda: run_case(c, arrs, [0, 31], C=C_DERIVED, case="any-many[%d,d%d]" % (lon, d)))
-    assert names == {"nattn_fwd_band", "nattn_bwd_dq_band", "nattn_bwd_dkdv_band"}, names
+    assert names == {"nattn_fwd_patch", "nattn_bwd_dq_patch", "nattn_bwd_dkdv_patch"}, names
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -94,10 +94,9 @@ def test_value_width_other_than_key_width(d, e, dtype):
         c, arrs = make_inputs(dict(SHAPES[ci], d=max(d, e), heads=heads, dtype=dtype), seed=4800 + d)
         c["d"] = d
         arrs = [np.ascontiguousarray(a[:, :n]) for a, n in zip(arrs, (d, d, e, e))]
-        kind = "tile" if dtype == "bf16" else "band"
         run = (lambda: run_bf16(c, arrs, [0, heads - 1], "e%d-bf16" % ci)) if dtype == "bf16" else \
             (lambda: run_case(c, arrs, [0, heads - 1], C=C_DERIVED, case="e%d" % ci))
-        assert _launches(run) == {"nattn_fwd_" + kind, "nattn_bwd_dq_" + kind, "nattn_bwd_dkdv_" + kind}
+        assert _launches(run) == {"nattn_fwd_patch", "nattn_bwd_dq_patch", "nattn_bwd_dkdv_patch"}
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])

@@ -117,7 +117,7 @@ def test_bf16_matrix_core_path(ci):
     finally:
         S.s2_trace_enable(False)
         S.s2_trace_reset()
-    assert names and all(n.split("<")[0] in ("nattn_fwd_bf16", "nattn_bwd_dq_bf16", "nattn_bwd_dkdv_bf16") for n in names), names
+    assert names == {"nattn_fwd_patch", "nattn_bwd_dq_patch", "nattn_bwd_dkdv_patch"}, names
 
 
 # head widths 16 and 64, and d = 32 on longitude counts that are multiples of 16 but not of 64 (whole circles near the poles,
@@ -139,7 +139,7 @@ def test_bf16_band_tile_path(ci):
     finally:
         S.s2_trace_enable(False)
         S.s2_trace_reset()
-    assert names == {"nattn_fwd_tile", "nattn_bwd_dq_tile", "nattn_bwd_dkdv_tile"}, names
+    assert names == {"nattn_fwd_patch", "nattn_bwd_dq_patch", "nattn_bwd_dkdv_patch"}, names
 
 
 @pytest.mark.parametrize("ci", range(len(ANY)))

@@ -37,13 +37,16 @@ def reference(g, q, k, v, dout, scale):
     return out, lse, dq, dk, dv
 
 
-# cutoffs of a few and of some hundred offsets; equal grids, 2:1, 1:2, either side of 2^15
-@pytest.mark.parametrize("theta", [0.0015, 0.012])
-@pytest.mark.parametrize("lon_in,lon_out,d,dtype", [(32768, 32768, 32, "f32"), (65536, 32768, 32, "f32"), (32768, 65536, 32, "f32"),
-                                                    (32772, 32772, 16, "f32"), (32768, 32768, 32, "bf16"), (40000, 20000, 32, "f32"),
-                                                    (40000, 20000, 16, "bf16"), (20000, 40000, 24, "f32"), (20000, 40000, 32, "bf16"),
-                                                    (32764, 32764, 32, "f32")])
-def test_long_circles(lon_in, lon_out, d, dtype, theta):
+# cutoffs of a few and of some hundred offsets; equal grids, 2:1, 1:2, either side of 2^15; what runs (of the forward: of all three)
+@pytest.mark.parametrize("lon_in,lon_out,d,dtype,theta,kernels", [
+    (32768, 32768, 32, "f32", 0.0015, "stream"), (32768, 32768, 32, "f32", 0.012, "tiled<8 waves>"),
+    (65536, 32768, 32, "f32", 0.0015, "tiled<1 wave>"), (65536, 32768, 32, "f32", 0.012, "tiled<8 waves>"),
+    (32768, 65536, 32, "f32", 0.0015, "tiled<1 wave>"), (32768, 65536, 32, "f32", 0.012, "tiled<8 waves>"),
+    (32772, 32772, 16, "f32", 0.0015, "generic"), (32768, 32768, 32, "bf16", 0.012, "generic"),
+    (40000, 20000, 32, "f32", 0.0015, "patch"), (40000, 20000, 32, "f32", 0.012, "patch"), (40000, 20000, 16, "bf16", 0.012, "patch"),
+    (20000, 40000, 24, "f32", 0.0015, "patch"), (20000, 40000, 24, "f32", 0.012, "patch"), (20000, 40000, 32, "bf16", 0.012, "patch"),
+    (32764, 32764, 32, "f32", 0.0015, "patch"), (32764, 32764, 32, "f32", 0.012, "patch")])
+def test_long_circles(lon_in, lon_out, d, dtype, theta, kernels):
     nlat, B = 3, 2
     g = S.s2_grid_init(1, nlat, lon_in, nlat, lon_out, theta)
     cast = torch.float32 if dtype == "f32" else torch.bfloat16
@@ -51,8 +54,17 @@ def test_long_circles(lon_in, lon_out, d, dtype, theta):
     rnd = lambda n: torch.randn(1, B, d, nlat, n, generator=gen, device="cuda:0").to(cast)
     q, k, v, dout = rnd(lon_out), rnd(lon_in), rnd(lon_in), rnd(lon_out)
     scale = 1 / math.sqrt(d)
-    out, lse = S.s2_nattn_fwd(g, q, k, v, scale)
-    got = (out, lse) + tuple(S.s2_nattn_bwd(g, q, k, v, out, lse, dout, scale))
+    S.s2_trace_reset()
+    S.s2_trace_enable(True)
+    try:
+        out, lse = S.s2_nattn_fwd(g, q, k, v, scale)
+        got = (out, lse) + tuple(S.s2_nattn_bwd(g, q, k, v, out, lse, dout, scale))
+        torch.cuda.synchronize()
+        names = {n for n, _, _ in S.s2_trace_entries()}
+    finally:
+        S.s2_trace_enable(False)
+        S.s2_trace_reset()
+    assert "nattn_fwd_" + kernels in names and all(kernels.split("<")[0] in n or "dkdv2_tiled" in n for n in names), names
     want = reference(g, *(x[0] for x in (q, k, v, dout)), scale)
     assert S.s2_grid_device_flags(g) == 0
     for name, a, r in zip(("out", "lse", "dq", "dk", "dv"), got, want):
