@@ -19,5 +19,3 @@ void s2_by_band_mode(int mode, F &&f)
     else if (mode == kNarrow) f(Set<kNarrow>());
     else f(Set<kRagged>());
 }
-// compute units of the device, for rules on the size of a launch
-unsigned s2_compute_units();

@@ -2,17 +2,6 @@
 #include "s2_nattn_kernels.h"
 #include "s2_nattn_patch.h"
 
-unsigned s2_compute_units()
-{
-    static const unsigned ncu = [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
-            n = 256;
-        return unsigned(n);
-    }();
-    return ncu;
-}
-
 // the matrix-core kernels for any grid pair, of both element types
 int s2_nattn_band_configure()
 {

@@ -45,7 +45,6 @@
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
-#include <cstdlib>
 
 #include "s2_bf16_terms.h"
 #include "s2_internal.h"
@@ -970,8 +969,6 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
         again_k | again_v, w.wave, [&](const PatchWhere &at, int i) { return marked<G>(reinterpret_cast<const float *>(sh.a), at, i); },
         [&](const PatchWhere &at, int i) { return marked<G>(reinterpret_cast<const float *>(sh.b), at, i); });
 }
-
-inline double pair_count(const double (&p)[4], int nbh) { return nbh * (p[0] + p[1] + p[2] + p[3]); }
 
 // Calls f with the geometry for a head dimension.  More workgroups on a compute unit count for more than longer stages (twice the
 // chunks per stage: float32 d = 32 0.56 / 0.65 / 0.73 ms, bf16 d = 32 0.27 / 0.35 / 0.40); the register limits are the loosest that do not

@@ -41,7 +41,6 @@ __device__ __forceinline__ void settle(f32x4 (&a)[N])
 }
 
 __device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }
-__device__ __forceinline__ int imax(int a, int b) { return a > b ? a : b; }
 
 // x mod n for 0 <= x < 2^22: the float32 quotient is off by at most one
 __device__ __forceinline__ int wrap_col(int x, int n, float inv_n)
@@ -61,10 +60,6 @@ struct BandArgs {
     const int2 *patch;
     int npatch;
 };
-
-// is channel c one of the tensor's nch
-template <int MODE>
-__device__ __forceinline__ bool has(int c, int nch) { return MODE != kRagged || c < nch; }
 
 template <class V>
 __device__ __forceinline__ V load_at(const void *row, unsigned off)
