@@ -295,15 +295,15 @@ int s2_grid_device_flags(const s2_grid_t *g, unsigned *flags);
  * Test-only dispatch switches (not part of the method; nothing else steers the dispatch: the library reads no
  * environment variables).  Sets the bits of set_bits, clears those of clear_bits, returns the new word; process
  * wide, takes effect on the next attention call.
- *   S2_DEBUG_NO_MFMA        dense polar latitudes go to the split vector kernels instead of the matrix cores
+ *   S2_DEBUG_NO_MFMA        neighborhood attention stays off the matrix cores (as S2_DEBUG_NO_BAND)
  *   S2_DEBUG_NO_STREAM      light latitudes go to the one-wavefront kernels instead of the streaming kernels
- *   S2_DEBUG_NO_ROW_GROUPS  matrix-core kernels never start a second set of wavefronts per workgroup
+ *   S2_DEBUG_NO_ROW_GROUPS  no effect: the kernels that it steered are gone
  *   S2_DEBUG_FAIL_LAUNCH    the launchers of the tuned neighborhood kernels report failure before launching
  *                           anything: s2_nattn_fwd / s2_nattn_bwd then return S2_ERR_DEVICE
  *   S2_DEBUG_FORCE_BAND     the forward of float32 tensors with d = e = 32 on upsampling grids runs on the matrix-core patches too,
  *                           like every other pair of widths up to 64 (by default on the split vector kernel)
- *   S2_DEBUG_NO_BAND        the matrix-core kernels for any grid pair and width are never used, on float32 or bf16 tensors
- *                           (all but d = e = 32: shape-agnostic kernels)
+ *   S2_DEBUG_NO_BAND        the matrix-core patches are never used, on float32 or bf16 tensors: the kernels of longer circles take
+ *                           their place (float32 with d = e = 32: streaming and split vector kernels, else shape-agnostic ones)
  */
 enum { S2_DEBUG_NO_MFMA = 1, S2_DEBUG_NO_STREAM = 2, S2_DEBUG_NO_ROW_GROUPS = 4, S2_DEBUG_FAIL_LAUNCH = 8, S2_DEBUG_FORCE_BAND = 16, S2_DEBUG_NO_BAND = 32 };
 unsigned s2_debug_control(unsigned set_bits, unsigned clear_bits);

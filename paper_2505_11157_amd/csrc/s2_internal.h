@@ -124,24 +124,19 @@ struct s2_grid {
     S2DeviceTables dt{};
 };
 
-// Class table for the split vector kernels.  `dense_taken`: another kernel has taken the latitudes above the
-// coarse threshold (classes 0-2 of the coarse table = class 0 of the fine one).  If the coarse split would start
-// so few wavefronts that most SIMDs hold fewer than eight, the copy `t` is switched to the fine split.
-inline void s2_pick_split(S2DeviceTables &t, bool fwd, int nbh, int nseg, bool dense_taken)
+// Class table for the split vector kernels.  If the coarse split would start so few wavefronts that most SIMDs hold
+// fewer than eight, the copy `t` is switched to the fine split.
+inline void s2_pick_split(S2DeviceTables &t, bool fwd, int nbh, int nseg)
 {
     int *c = fwd ? t.fwd_cls : t.bwd_cls;
     double *p = fwd ? t.fwd_pairs : t.bwd_pairs;
-    if (dense_taken) {
-        c[0] = c[1] = c[2] = 0;
-        p[0] = p[1] = p[2] = 0.0;
-    }
     const long waves = long(nbh) * nseg * (8 * c[0] + 4 * c[1] + 2 * c[2] + c[3]);
     if (waves >= 8192) return;
     const int *cf = fwd ? t.fwd_cls_fine : t.bwd_cls_fine;
     const double *pf = fwd ? t.fwd_pairs_fine : t.bwd_pairs_fine;
     for (int i = 0; i < 4; ++i) {
-        c[i] = dense_taken && i == 0 ? 0 : cf[i];
-        p[i] = dense_taken && i == 0 ? 0.0 : pf[i];
+        c[i] = cf[i];
+        p[i] = pf[i];
     }
 }
 
@@ -165,13 +160,12 @@ bool s2_debug_flag(unsigned bit);
 int s2_nattn_tiled_configure();
 int s2_nattn_bwd_tiled_configure();
 int s2_nattn_stream_configure();
-int s2_nattn_mfma_configure();
 int s2_nattn_band_configure();
 
 // great-circle angle between two points given by their colatitudes and their difference in longitude (float64)
 double s2_great_circle(double colat_a, double colat_b, double dphi);
 
-// Channel matrices on the fp32 matrix cores (s2_channel.hip), all tensors [batch][channels][N] contiguous and 16-byte
+// Channel matrices on the matrix cores (s2_channel.hip), all tensors [batch][channels][N] contiguous and 16-byte
 // aligned, M, K and N multiples of 16.
 //   s2_channel_product: nset products side by side, C[i] = A[i] X[i] + bias[i], or (nset = 1) one over npair pairs,
 //                       C[0] = sum_i A[i] X[i] + bias[0] + R;  A = W (M x K) or W^T (trans, W is K x M)

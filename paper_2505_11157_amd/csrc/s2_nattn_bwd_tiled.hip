@@ -881,7 +881,7 @@ int s2_nattn_bwd_tiled_configure()
 
 namespace {
 
-// Upsampling grids: the split vector kernels in their class view (no matrix-core or streaming launches).
+// Upsampling grids: the split vector kernels in their class view (no streaming launches).
 int bwd_tiled_up(const S2DeviceTables &t_all, int nbh, float scale, const float *q, const float *k, const float *v,
                  const float *o, const float *lse, const float *go, float *dq, float *dk, float *dv, float *Dws,
                  hipStream_t st)
@@ -890,7 +890,7 @@ int bwd_tiled_up(const S2DeviceTables &t_all, int nbh, float scale, const float 
     const int nseg_o = ((t_all.nlon_in + kSegB - 1) / kSegB) * t_all.upscale, nseg_i = (t_all.nlon_in + kSegB - 1) / kSegB;
     {
         S2DeviceTables t = t_all;
-        s2_pick_split(t, true, nbh, nseg_o, false);
+        s2_pick_split(t, true, nbh, nseg_o);
         const int nsplit = t.fwd_cls[0] + t.fwd_cls[1] + t.fwd_cls[2];
         const size_t lds_wave = 2 * GeoB<1>::TILE * sizeof(float);
         if (nsplit > 0) {
@@ -911,7 +911,7 @@ int bwd_tiled_up(const S2DeviceTables &t_all, int nbh, float scale, const float 
         }
     }
     S2DeviceTables t = t_all;
-    s2_pick_split(t, false, nbh, nseg_i, false);
+    s2_pick_split(t, false, nbh, nseg_i);
     const int nsplit = t.bwd_cls[0] + t.bwd_cls[1] + t.bwd_cls[2];
     const size_t lds_wave = (2 * GeoB<1>::TILE + 2 * GeoB<1>::PITCH) * sizeof(float);
     if (nsplit > 0) {
@@ -943,22 +943,9 @@ int s2_nattn_bwd_tiled(const S2DeviceTables &t, int nbh, int d, int e, float sca
     const int nseg_o = (t.nlon_out + kSegB - 1) / kSegB;
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
     const bool no_stream = s2_debug_flag(S2_DEBUG_NO_STREAM);   // test-only: one-wave kernels instead
-    // dense polar latitudes: dq on the matrix cores; the vector kernels see the remaining latitudes
     const S2DeviceTables &t_all = t;
     S2DeviceTables t_dq = t_all;
-    const int nm = s2_nattn_fwd_mfma_rows(t_all, d, e);
-    if (nm > 0) {
-        if (s2_nattn_bwd_dq_mfma(t_all, nbh, nm, scale, q, k, v, o, lse, go, dq, Dws, st)) return -1;
-        t_dq.row_order = t_all.row_order + nm;
-    }
-    if (s2_nattn_stream_dq_supported(t_all, d, e)) {
-        if (nm > 0) {
-            t_dq.fwd_cls[0] = t_dq.fwd_cls[1] = t_dq.fwd_cls[2] = 0;
-            t_dq.fwd_pairs[0] = t_dq.fwd_pairs[1] = t_dq.fwd_pairs[2] = 0.0;
-        }
-    } else {
-        s2_pick_split(t_dq, true, nbh, nseg_o, nm > 0);
-    }
+    if (!s2_nattn_stream_dq_supported(t_all, d, e)) s2_pick_split(t_dq, true, nbh, nseg_o);
     const int nsplit_o = t_dq.fwd_cls[0] + t_dq.fwd_cls[1] + t_dq.fwd_cls[2];
     auto run_dq = [&](auto k8, auto k1, size_t lds_wave) {
         if (nsplit_o > 0) {
@@ -971,7 +958,7 @@ int s2_nattn_bwd_tiled(const S2DeviceTables &t, int nbh, int d, int e, float sca
             hipLaunchKernelGGL(k8, dim3((unsigned)nblk), dim3(64 * kWavesB), lds, st, t_dq, nbh, 1, scale, q, k, v, o, lse,
                                go, dq, Dws);
         }
-        const long nrows = t.nlat_out - nm - nsplit_o;
+        const long nrows = t.nlat_out - nsplit_o;
         if (nrows > 0 && !no_stream && s2_nattn_stream_dq_supported(t_dq, d, e))
             return s2_nattn_bwd_dq_stream(t_dq, nbh, scale, q, k, v, o, lse, go, dq, Dws, st);
         if (nrows <= 0) return 0;
@@ -990,7 +977,7 @@ int s2_nattn_bwd_tiled(const S2DeviceTables &t, int nbh, int d, int e, float sca
     if (t_all.pscale == 2) {
         const int nseg_i = (t_all.nlon_in + kSegB - 1) / kSegB;
         S2DeviceTables t = t_all;
-        s2_pick_split(t, false, nbh, nseg_i, false);
+        s2_pick_split(t, false, nbh, nseg_i);
         const int nsplit_i = t.bwd_cls[0] + t.bwd_cls[1] + t.bwd_cls[2];
         const size_t lds_wave = (2 * kTile2 + 2 * kPitch2) * sizeof(float);
         if (nsplit_i > 0) {
@@ -1012,21 +999,8 @@ int s2_nattn_bwd_tiled(const S2DeviceTables &t, int nbh, int d, int e, float sca
         return 0;
     }
     const int nseg_i = (t.nlon_in + kSegB - 1) / kSegB;
-    // dense polar input latitudes: dk/dv on the matrix cores
     S2DeviceTables t_kv = t_all;
-    const int nmi = s2_nattn_bwd_dkdv_mfma_rows(t_all, d, e);
-    if (nmi > 0) {
-        if (s2_nattn_bwd_dkdv_mfma(t_all, nbh, nmi, scale, q, k, v, lse, go, Dws, dk, dv, st)) return -1;
-        t_kv.trow_order = t_all.trow_order + nmi;
-    }
-    if (s2_nattn_stream_dkdv_supported(t_all, d, e)) {
-        if (nmi > 0) {
-            t_kv.bwd_cls[0] = t_kv.bwd_cls[1] = t_kv.bwd_cls[2] = 0;
-            t_kv.bwd_pairs[0] = t_kv.bwd_pairs[1] = t_kv.bwd_pairs[2] = 0.0;
-        }
-    } else {
-        s2_pick_split(t_kv, false, nbh, nseg_i, nmi > 0);
-    }
+    if (!s2_nattn_stream_dkdv_supported(t_all, d, e)) s2_pick_split(t_kv, false, nbh, nseg_i);
     const int nsplit_i = t_kv.bwd_cls[0] + t_kv.bwd_cls[1] + t_kv.bwd_cls[2];
     const size_t lds_wave = (2 * GeoB<1>::TILE + 2 * GeoB<1>::PITCH) * sizeof(float);
     if (nsplit_i > 0) {
@@ -1040,7 +1014,7 @@ int s2_nattn_bwd_tiled(const S2DeviceTables &t, int nbh, int d, int e, float sca
         hipLaunchKernelGGL(k8, dim3((unsigned)nblk), dim3(64 * kWavesB), lds, st, t_kv, nbh, 1, scale, q, k, v, lse, go,
                            Dws, dk, dv);
     }
-    const long nrows = t.nlat_in - nmi - nsplit_i;
+    const long nrows = t.nlat_in - nsplit_i;
     if (nrows > 0 && !no_stream && s2_nattn_stream_dkdv_supported(t_kv, d, e))
         return s2_nattn_bwd_dkdv_stream(t_kv, nbh, scale, q, k, v, lse, go, Dws, dk, dv, st);
     if (nrows <= 0) return 0;

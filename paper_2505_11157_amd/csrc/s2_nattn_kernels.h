@@ -34,19 +34,6 @@ int s2_nattn_bwd_tiled(const S2DeviceTables &t, int nbh, int d, int e, float sca
                        const float *v, const float *o, const float *lse, const float *go, float *dq, float *dk,
                        float *dv, float *Dws, hipStream_t st);
 
-// Forward on the fp32 matrix cores for the heaviest output latitudes (dense neighborhoods near the
-// poles): number of leading latitudes of row_order it takes (0 if the shape does not qualify), and the launch.
-int s2_nattn_fwd_mfma_rows(const S2DeviceTables &t, int d, int e);
-int s2_nattn_fwd_mfma(const S2DeviceTables &t, int nbh, int nrows, float scale, const float *q, const float *k,
-                      const float *v, float *out, float *lse, hipStream_t st);
-int s2_nattn_bwd_dq_mfma(const S2DeviceTables &t, int nbh, int nrows, float scale, const float *q, const float *k,
-                         const float *v, const float *o, const float *lse, const float *go, float *dq, float *Dws,
-                         hipStream_t st);
-int s2_nattn_bwd_dkdv_mfma_rows(const S2DeviceTables &t, int d, int e);
-int s2_nattn_bwd_dkdv_mfma(const S2DeviceTables &t, int nbh, int nrows, float scale, const float *q, const float *k,
-                           const float *v, const float *lse, const float *go, const float *Dws, float *dk, float *dv,
-                           hipStream_t st);
-
 // Streaming kernels for the light latitudes (last class) on equal grids: each input latitude is staged in LDS once
 // per workgroup and shared by the wavefronts that walk down consecutive output latitudes.
 bool s2_nattn_stream_supported(const S2DeviceTables &t, int d, int e);

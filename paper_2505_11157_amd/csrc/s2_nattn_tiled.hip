@@ -464,9 +464,9 @@ constexpr size_t fwd_tiled_lds()
 }
 
 template <int D, int PS, bool UP = false>
-int launch_fwd_tiled(const S2DeviceTables &t, int skip_rows, int nbh, float qscale, const float *q, const float *k,
+int launch_fwd_tiled(const S2DeviceTables &t, int nbh, float qscale, const float *q, const float *k,
                      const float *v, float *out, float *lse, hipStream_t st)
-{   // t.row_order already points past the skip_rows latitudes another kernel has taken
+{
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
     const int nseg = UP ? ((t.nlon_in + kSeg - 1) / kSeg) * t.upscale : (t.nlon_out + kSeg - 1) / kSeg;
     const int nsplit = t.fwd_cls[0] + t.fwd_cls[1] + t.fwd_cls[2];   // latitudes split over several wavefronts
@@ -486,7 +486,7 @@ int launch_fwd_tiled(const S2DeviceTables &t, int skip_rows, int nbh, float qsca
     }
     // the rest: one wavefront per workgroup
     const int first_row = mode == 1 ? 0 : nsplit;
-    const long nrows = t.nlat_out - skip_rows - first_row;
+    const long nrows = t.nlat_out - first_row;
     const bool no_stream = s2_debug_flag(S2_DEBUG_NO_STREAM);   // test-only: one-wave kernel instead
     if (!UP && nrows > 0 && mode == 0 && !no_stream && s2_nattn_stream_supported(t, D, D))
         return s2_nattn_fwd_stream(t, nbh, qscale, q, k, v, out, lse, st);
@@ -526,24 +526,11 @@ int s2_nattn_fwd_tiled(const S2DeviceTables &t, int nbh, int d, int e, float sca
     if (t.upscale > 1) {
         // upsampling: every class of output longitudes is an equal-grid problem for the split vector kernels
         S2DeviceTables tu = t;
-        s2_pick_split(tu, true, nbh, ((t.nlon_in + kSeg - 1) / kSeg) * t.upscale, false);
-        return launch_fwd_tiled<32, 1, true>(tu, 0, nbh, qscale, q, k, v, out, lse, st);
+        s2_pick_split(tu, true, nbh, ((t.nlon_in + kSeg - 1) / kSeg) * t.upscale);
+        return launch_fwd_tiled<32, 1, true>(tu, nbh, qscale, q, k, v, out, lse, st);
     }
-    // dense polar latitudes go to the matrix-core kernel; the vector kernels see the remaining latitudes
     S2DeviceTables tv = t;
-    const int nm = s2_nattn_fwd_mfma_rows(t, d, e);
-    if (nm > 0) {
-        if (s2_nattn_fwd_mfma(t, nbh, nm, scale, q, k, v, out, lse, st)) return -1;
-        tv.row_order = t.row_order + nm;
-    }
-    if (s2_nattn_stream_supported(t, d, e)) {
-        if (nm > 0) {
-            tv.fwd_cls[0] = tv.fwd_cls[1] = tv.fwd_cls[2] = 0;
-            tv.fwd_pairs[0] = tv.fwd_pairs[1] = tv.fwd_pairs[2] = 0.0;
-        }
-    } else {
-        s2_pick_split(tv, true, nbh, (t.nlon_out + kSeg - 1) / kSeg, nm > 0);
-    }
-    if (t.pscale == 1) return launch_fwd_tiled<32, 1>(tv, nm, nbh, qscale, q, k, v, out, lse, st);
-    return launch_fwd_tiled<32, 2>(tv, nm, nbh, qscale, q, k, v, out, lse, st);
+    if (!s2_nattn_stream_supported(t, d, e)) s2_pick_split(tv, true, nbh, (t.nlon_out + kSeg - 1) / kSeg);
+    if (t.pscale == 1) return launch_fwd_tiled<32, 1>(tv, nbh, qscale, q, k, v, out, lse, st);
+    return launch_fwd_tiled<32, 2>(tv, nbh, qscale, q, k, v, out, lse, st);
 }

@@ -11,7 +11,6 @@
 int s2_nattn_tiled_configure() { return 0; }
 int s2_nattn_bwd_tiled_configure() { return 0; }
 int s2_nattn_stream_configure() { return 0; }
-int s2_nattn_mfma_configure() { return 0; }
 int s2_nattn_band_configure() { return 0; }
 int s2_mha_configure() { return 0; }
 int s2_static_scratch_setup(int) { return 0; }

@@ -187,8 +187,7 @@ def test_deterministic_and_roll_equivariant():
     rolled = [np.roll(a, 1, axis=-1) for a in arrs]
     r3 = run_case(c, rolled, [])
     # shift invariance in longitude (App. B.3): exact in the vector kernels, whose summation order moves with
-    # the output; the matrix-core kernel for the polar latitudes sums in fixed column tiles, so there the
-    # rolled result agrees to rounding only
+    # the output; the patch kernels sum in tiles at fixed columns, so there the rolled result agrees to rounding only
     for a, b in zip(r1, r3):
         ra = np.roll(a, 1, axis=-1)
         assert np.abs(ra - b).max() <= 2e-6 + 1e-5 * np.abs(ra).max()
@@ -241,17 +240,15 @@ class debug_switches:
 
 
 def test_vector_kernels_cover_dense_latitudes_too():
-    # S2_DEBUG_NO_MFMA sends the polar latitudes through the split vector kernels instead of the matrix-core
-    # kernels: same parity bar
+    # S2_DEBUG_NO_MFMA sends every latitude through the vector kernels, the polar ones through the split ones: same parity bar
     c, arrs = make_inputs(2)
     with debug_switches(S.S2_DEBUG_NO_MFMA):
         run_case(c, arrs, [0, 7], case="cfg2-no-mfma")
 
 
 def test_one_wave_kernels_on_streaming_shapes():
-    # S2_DEBUG_NO_STREAM keeps the light latitudes on the one-wavefront kernels, S2_DEBUG_NO_MFMA the dense ones on
-    # the split vector kernels: the paths a shape takes when the streaming / matrix-core kernels do not apply, checked
-    # here on a shape where they do
+    # S2_DEBUG_NO_STREAM keeps the light latitudes on the one-wavefront kernels, S2_DEBUG_NO_MFMA all off the matrix cores: the paths a
+    # shape takes when the patch and streaming kernels do not apply, checked here on a shape where they do
     c, arrs = make_inputs(SMALL[11], seed=5)
     with debug_switches(S.S2_DEBUG_NO_MFMA | S.S2_DEBUG_NO_STREAM):
         run_case(c, arrs, [0, 2], case="edge11-no-mfma-no-stream")
@@ -261,9 +258,8 @@ def test_one_wave_kernels_on_streaming_shapes():
 
 
 def test_tuned_kernels_where_band_tiles_are_the_default():
-    # equal grids with d = 32 whose light latitudes lack the streaming structure run on the band-tile matrix-core
-    # kernels by default; S2_DEBUG_NO_BAND keeps them on the matrix-core + one-wavefront kernels tuned for d = 32
-    # (what such shapes ran on before, and still run on when the longitude count is not a multiple of 64)
+    # equal grids with d = 32, with and without the structure that the streaming kernels ask for; S2_DEBUG_NO_BAND keeps them on the
+    # vector kernels written for d = 32 (which circles of 2^15 and more longitudes run on)
     with debug_switches(S.S2_DEBUG_NO_BAND):
         c, arrs = make_inputs(2)
         run_case(c, arrs, range(c["batch"] * c["heads"]), case="cfg2-no-band")
@@ -300,10 +296,8 @@ def test_launcher_failure_is_reported():
 
 # Peaked softmax: q and k scaled by 6 put the logits tens of units apart (nearly one-hot probabilities), so the lazily
 # moved reference maximum of every kernel family has to move many times; a negative scale flips which logits are the
-# large ones.  Shapes: matrix-core + streaming (65x256), split vector kernels on a 2:1 grid, band tiles
-# (d = 12, 2:1; d = 64), the grid of App. A.1 with its zero-weight pole row on the tuned (equal, 2:1, upsampling) and the
-# band-tile kernels (a pole logit far above all others must not drown the positive-weight terms), upsampling in
-# the class view.
+# large ones.  Shapes: 65x256, 2:1 grids, d = 12 and 64, the grid of App. A.1 with its zero-weight pole row on equal, 2:1 and upsampling
+# grids (a pole logit far above all others must not drown the positive-weight terms), upsampling in the class view.
 PEAKED = [13, 9, 3, 4, 17, 16, 18, 25, 31, 32]
 
 
@@ -318,8 +312,7 @@ def test_peaked_softmax(ci, sign):
 
 
 def test_peaked_softmax_vector_kernels_on_dense_latitudes():
-    # the same on the split 8-wave and one-wave vector kernels for the shape whose dense latitudes normally run on the
-    # matrix cores and whose light ones on the streaming kernels
+    # the same on the split 8-wave and one-wave vector kernels
     c, arrs = make_inputs(SMALL[13], seed=613)
     arrs = [arrs[0] * np.float32(6.0), arrs[1] * np.float32(6.0), arrs[2], arrs[3]]
     with debug_switches(S.S2_DEBUG_NO_MFMA | S.S2_DEBUG_NO_STREAM):
