@@ -116,7 +116,7 @@ SMALL = [
     dict(kind="nattn", grid_type=0, nlat_in=33, nlon_in=64, nlat_out=33, nlon_out=1, theta=0.3, batch=1, heads=2, d=8, dtype="f32"),
     dict(kind="nattn", grid_type=1, nlat_in=2, nlon_in=1, nlat_out=2, nlon_out=1, theta=0.2, batch=1, heads=1, d=1, dtype="f32"),
     dict(kind="nattn", grid_type=0, nlat_in=20, nlon_in=96, nlat_out=10, nlon_out=32, theta=0.35, batch=1, heads=2, d=32, dtype="f32"),
-    # tuned kernels (d = 32) with ragged last segments, equal grids and 2:1 downsampling, 3 and 9 slices
+    # d = 32, shapes of the kernels written for that width (VECTOR below): ragged last segments, equal grids and 2:1, 3 and 9 slices
     dict(kind="nattn", grid_type=1, nlat_in=24, nlon_in=100, nlat_out=24, nlon_out=100, theta=0.4, batch=3, heads=1, d=32, dtype="f32"),
     dict(kind="nattn", grid_type=0, nlat_in=19, nlon_in=152, nlat_out=10, nlon_out=76, theta=0.3, batch=3, heads=3, d=32, dtype="f32"),
     dict(kind="nattn", grid_type=0, nlat_in=21, nlon_in=192, nlat_out=21, nlon_out=192, theta=0.6, batch=1, heads=2, d=32, dtype="f32"),
@@ -128,21 +128,20 @@ SMALL = [
     dict(kind="nattn", grid_type=0, nlat_in=33, nlon_in=192, nlat_out=33, nlon_out=192, theta=0.3, batch=9, heads=2, d=32, dtype="f32"),
     # a handful of light latitudes with bands of three rows (two wavefronts per workgroup, more segments than fit)
     dict(kind="nattn", grid_type=0, nlat_in=9, nlon_in=256, nlat_out=9, nlon_out=256, theta=0.5, batch=1, heads=2, d=32, dtype="f32"),
-    # the equiangular grid as the paper prints it (no south pole, zero weight on the pole row): band tiles, tuned
-    # equal-grid and tuned 2:1 kernels
+    # the equiangular grid as the paper prints it (no south pole, zero weight on the pole row): equal grids and 2:1
     dict(kind="nattn", grid_type=2, nlat_in=16, nlon_in=32, nlat_out=16, nlon_out=32, theta=0.45, batch=1, heads=2, d=8, dtype="f32"),
     dict(kind="nattn", grid_type=2, nlat_in=64, nlon_in=256, nlat_out=64, nlon_out=256, theta=4 * math.pi / 64, batch=1, heads=2, d=32, dtype="f32"),
     dict(kind="nattn", grid_type=2, nlat_in=40, nlon_in=160, nlat_out=20, nlon_out=80, theta=0.35, batch=1, heads=3, d=32, dtype="f32"),
-    # Gauss-Lobatto grid (both poles, Gaussian spacing): band tiles and tuned kernels
+    # Gauss-Lobatto grid (both poles, Gaussian spacing)
     dict(kind="nattn", grid_type=3, nlat_in=17, nlon_in=32, nlat_out=17, nlon_out=32, theta=0.45, batch=1, heads=2, d=8, dtype="f32"),
     dict(kind="nattn", grid_type=3, nlat_in=65, nlon_in=256, nlat_out=65, nlon_out=256, theta=4 * math.pi / 64, batch=1, heads=2, d=32, dtype="f32"),
-    # upsampling (nlon_out = 2, 3, 4 x nlon_in), narrow grids: band tiles with one row per longitude class
+    # upsampling (nlon_out = 2, 3, 4 x nlon_in), narrow grids
     dict(kind="nattn", grid_type=0, nlat_in=9, nlon_in=16, nlat_out=17, nlon_out=32, theta=0.5, batch=1, heads=2, d=8, dtype="f32"),
     dict(kind="nattn", grid_type=1, nlat_in=12, nlon_in=24, nlat_out=16, nlon_out=72, theta=0.4, batch=2, heads=1, d=32, dtype="f32"),
     dict(kind="nattn", grid_type=0, nlat_in=9, nlon_in=20, nlat_out=17, nlon_out=80, theta=0.6, batch=1, heads=1, d=5, dtype="f32"),
     dict(kind="nattn", grid_type=0, nlat_in=6, nlon_in=10, nlat_out=9, nlon_out=20, theta=math.pi, batch=1, heads=1, d=3, dtype="f32"),
-    # upsampling on the tuned kernels (d = 32, at least 72 input longitudes, a multiple of 4): every class of output
-    # longitudes as an equal-grid problem; 2x, 3x, 4x, nine slices, a ragged last segment, full circles at the poles
+    # upsampling with d = 32 and at least 72 input longitudes, a multiple of 4 (the forward on the split vector kernel: every class of
+    # output longitudes as an equal-grid problem); 2x, 3x, 4x, nine slices, a ragged last segment, full circles at the poles
     dict(kind="nattn", grid_type=0, nlat_in=13, nlon_in=76, nlat_out=25, nlon_out=152, theta=0.5, batch=3, heads=3, d=32, dtype="f32"),
     dict(kind="nattn", grid_type=1, nlat_in=12, nlon_in=72, nlat_out=16, nlon_out=216, theta=0.4, batch=1, heads=2, d=32, dtype="f32"),
     dict(kind="nattn", grid_type=0, nlat_in=17, nlon_in=132, nlat_out=33, nlon_out=528, theta=0.3, batch=1, heads=1, d=32, dtype="f32"),
@@ -150,7 +149,7 @@ SMALL = [
     # larger and odd longitude ratios (8x, 5x)
     dict(kind="nattn", grid_type=0, nlat_in=7, nlon_in=72, nlat_out=9, nlon_out=576, theta=0.7, batch=1, heads=2, d=32, dtype="f32"),
     dict(kind="nattn", grid_type=1, nlat_in=10, nlon_in=84, nlat_out=6, nlon_out=420, theta=0.45, batch=2, heads=1, d=32, dtype="f32"),
-    # upsampling on the grid of App. A.1 (zero-weight pole row): band tiles and the class view
+    # upsampling on the grid of App. A.1 (zero-weight pole row)
     dict(kind="nattn", grid_type=2, nlat_in=8, nlon_in=16, nlat_out=12, nlon_out=32, theta=0.7, batch=1, heads=2, d=8, dtype="f32"),
     dict(kind="nattn", grid_type=2, nlat_in=12, nlon_in=72, nlat_out=16, nlon_out=144, theta=0.5, batch=1, heads=2, d=32, dtype="f32"),
 ]
@@ -162,12 +161,34 @@ def test_streaming_with_many_slices():
              d=32, dtype="f32")
     c, arrs = make_inputs(c, seed=77)
     run_case(c, arrs, [0, 83, 159], case="many-slices")
+    with debug_switches(S.S2_DEBUG_NO_BAND):
+        run_case(c, arrs, [0, 83, 159], case="many-slices-streaming")
 
 
 @pytest.mark.parametrize("ci", range(len(SMALL)))
 def test_parity_edge_shapes(ci):
     c, arrs = make_inputs(SMALL[ci], seed=200 + ci)
     run_case(c, arrs, range(c["batch"] * c["heads"]), case="edge%d" % ci)
+
+
+# the shapes that the streaming kernels and the split vector kernels take, which circles of 2^15 and more longitudes run on
+VECTOR = [i for i, c in enumerate(SMALL) if c["d"] == 32 and c["nlon_in"] % 4 == 0 and c["nlon_out"] % 4 == 0 and
+          min(c["nlon_in"], c["nlon_out"]) >= 72 and c["nlon_in"] // c["nlon_out"] <= 2]
+
+
+@pytest.mark.parametrize("ci", VECTOR)
+def test_parity_edge_shapes_on_the_vector_kernels(ci):
+    c, arrs = make_inputs(SMALL[ci], seed=200 + ci)
+    S.s2_trace_reset()
+    S.s2_trace_enable(True)
+    try:
+        with debug_switches(S.S2_DEBUG_NO_BAND):
+            run_case(c, arrs, range(c["batch"] * c["heads"]), case="edge%d-vector" % ci)
+        names = {n for n, _, _ in S.s2_trace_entries()}
+    finally:
+        S.s2_trace_enable(False)
+        S.s2_trace_reset()
+    assert all("_stream" in n or "_tiled" in n for n in names) and any("dkdv" in n for n in names), names
 
 
 def test_value_width_differs_from_key_width():
@@ -394,11 +415,17 @@ def test_hip_graph_replays_match_eager():
             assert torch.equal(a, b), "replay %d: %s differs from the eager result" % (rep, name)
 
 
+@pytest.mark.parametrize("switch", [0, S.S2_DEBUG_NO_BAND])
 @pytest.mark.parametrize("ci", [9, 26])
-def test_repeated_launches_bit_identical(ci):
-    # split kernels with nine slices (2:1 grid; upsampling): 1000 forward + backward launches on the same inputs give
-    # the same bits every time.  (Regression test: without a wait for the wavefront's own LDS reads before the next
-    # LDS-direct copy into the same buffer, dk of the 2:1 case differed in about 3 of 1000 launches.)
+def test_repeated_launches_bit_identical(ci, switch):
+    # 1000 forward + backward launches on the same inputs give the same bits every time, on the patch kernels and on the split
+    # kernels (2:1 grid with nine slices; upsampling).  (Regression test of the latter: without a wait for the wavefront's own LDS reads
+    # before the next LDS-direct copy into the same buffer, dk of the 2:1 case differed in about 3 of 1000 launches.)
+    with debug_switches(switch):
+        repeated_launches(ci)
+
+
+def repeated_launches(ci):
     c, arrs = make_inputs(SMALL[ci], seed=200 + ci)
     g = _grid(grid_dict(c))
     B, H, d = c["batch"], c["heads"], c["d"]
