@@ -7,7 +7,7 @@
 // 1 - |r K / theta_cutoff - k|): isotropic filters that vanish on the rim of the disk); the paper leaves the basis
 // open.  The contraction with psi is disco_gather below; grids with too many input columns per output column for it take a gather
 // per point (lanes on consecutive longitudes, the basis values of a (latitude, offset) uniform over a wavefront).  The channel mixing is a
-// channel matrix on the fp32 matrix cores.  Backward: psi is applied to dy through the transposed
+// channel matrix on the matrix cores.  Backward: psi is applied to dy through the transposed
 // neighborhood (the same kernel on the transposed tables, no atomics) and the channel mixing follows,
 //     dx[b, c] = sum_{o, k} weight[o, c, k] (psi_k^T dy)[b, o];
 // or, where that is cheaper (transposed_first), the channels are mixed first and psi^T gathers dx from the K planes of dz

@@ -2,8 +2,9 @@
 #pragma once
 #include "s2_internal.h"
 
-// Staging mode: kWide, four columns at a time with 32-bit offsets into a slice; kNarrow, column by column of one channel at a
-// time; kRagged, kNarrow with channel counts that are not the kernel's.
+// Staging mode, all in pieces of four columns: kWide, rows of a multiple of four columns side by side and 32-bit offsets into a slice, so
+// that no piece ends with its row; kNarrow, any rows, pieces at any alignment, and element by element where a piece ends with its row
+// or its columns lie apart (classes of a finer grid); kRagged, kNarrow with channel counts that are not the kernel's.
 enum { kWide, kNarrow, kRagged };
 inline int s2_band_mode(const S2BandSide &b, int d, int e, size_t element)
 {

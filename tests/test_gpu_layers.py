@@ -46,8 +46,8 @@ def close(x, ref, what, case, abs_sum=None):
 
 
 MHA_CASES = [
-    # (grid, batch, channels, heads): d = 32 on 192 / 256 longitudes runs the matrix-core and streaming attention kernels,
-    # d = 16 and 64 the fp32 band tiles; 48 and 160 channels leave row tiles of the channel products ragged
+    # (grid, batch, channels, heads): head widths 16, 32 and 64 of the attention; 48 and 160 channels leave row tiles of the channel
+    # products ragged
     (dict(grid_type=0, nlat_in=17, nlon_in=32, nlat_out=17, nlon_out=32, theta=0.5), 2, 32, 2),
     (dict(grid_type=1, nlat_in=16, nlon_in=48, nlat_out=16, nlon_out=48, theta=0.4), 1, 48, 3),
     (dict(grid_type=0, nlat_in=33, nlon_in=192, nlat_out=33, nlon_out=192, theta=0.3), 2, 64, 2),

@@ -1,4 +1,4 @@
-"""GPU parity of the tile kernels away from the longitude counts and grid pairs they were first written for: the edges of
+"""GPU parity of the patch kernels away from the longitude counts and grid pairs they were first written for: the edges of
 tiles, stages, classes and row tables, float32 and bf16 tensors, against the float64 oracle."""
 import math
 

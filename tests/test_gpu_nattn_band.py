@@ -1,6 +1,6 @@
-"""GPU parity of the fp32 band-tile matrix-core kernels on equal grids whose longitude counts are multiples of 16 (head
-dimensions 16 and 64; 32 when a test switch routes it there; every other width, count and grid pair in
-test_gpu_nattn_any_grid.py) against the float64 oracle, through the C ABI, at the stated bound
+"""GPU parity of the patch kernels on float32 tensors, equal grids whose longitude counts are multiples of 16, head
+dimensions 16, 32 and 64 (every other width, count and grid pair in test_gpu_nattn_any_grid.py; the switch set for 32 changes
+nothing on equal grids), against the float64 oracle, through the C ABI, at the stated bound
 |x - ref| <= 1e-6 + 1e-5 |ref| (plus the derived rounding allowance of test_gpu_nattn on the peaked cases)."""
 import math
 
@@ -53,7 +53,7 @@ def test_band_kernels_d32_many_slices(i):
 def test_band_kernels_random_shapes(seed):
     # seeded random equal grids (all grid types, 5 to 40 latitudes, longitude counts that are multiples of 16 from 64 to
     # 320, random cutoffs, 1 to 24 slices: few and many workgroups, ragged last groups and segments, short arcs, long
-    # arcs and whole circles in whatever mix comes up) for d = 16, 32 (routed to the band tiles) and 64; one random slice
+    # arcs and whole circles in whatever mix comes up) for d = 16, 32 and 64; one random slice
     # against the oracle
     rng = np.random.default_rng(8100 + seed)
     d = (16, 32, 64)[seed % 3]

@@ -9,9 +9,9 @@ error enters dS_ij = p_ij (dout_i.v_j - D_i) for every j at once and propagates 
 |d dq_il| <= |scale| dD_i sum_j p_ij |k_jl|,  |d dk_jl| <= |scale| sum_i p_ij dD_i |q_il|  (both sums come from the
 oracle: its forward with |k| in place of v, and the dv output of its backward with dD_i |q_i| in place of dout).
 It matters only where the softmax is nearly one-hot (a handful of elements per million on the workloads).
-Shapes with equal grids, d = e = 32 and a longitude count that is a multiple of 64 run on the kernels written for them
-(FAST); every other shape with d and e up to 64 on the tile kernels for any grid pair (TILE, ANY); wider heads on the
-shape-agnostic kernels with bf16 loads and stores (test_gpu_nattn_any_grid).  All products but those of the last run on the bf16 matrix cores.
+Every shape with d and e up to 64 runs on the patch kernels, whose products are on the bf16 matrix cores: equal grids with d = 32 and
+longitude counts that are multiples of 64 (FAST), other widths and counts (TILE), other grid pairs (ANY); wider heads on the
+shape-agnostic kernels with bf16 loads and stores (test_gpu_nattn_any_grid).
 """
 import json
 import math
@@ -90,8 +90,7 @@ def _c(gt, nlat, nlon, theta, B=1, H=2, d=32, nlat_out=None, nlon_out=None):
                 nlon_out=nlon_out or nlon, theta=theta, batch=B, heads=H, d=d, dtype="f32")
 
 
-# matrix-core path: one and several 256-longitude groups, partial last group (320, 192), arcs from one to dozens of
-# offsets and whole circles, all four grid types (the App. A.1 grid has a zero-weight pole row), a disk that covers
+# d = 32, 64 to 512 longitudes, arcs from one to dozens of offsets and whole circles, all four grid types (the App. A.1 grid has a zero-weight pole row), a disk that covers
 # the sphere
 FAST = [
     _c(0, 17, 64, 0.5), _c(1, 16, 128, 0.3, B=2, H=1), _c(0, 33, 192, 0.3, H=3), _c(0, 21, 320, 0.25),

@@ -1,4 +1,4 @@
-"""Non-finite inputs on the matrix-core tile kernels: a NaN or an infinity at a point reaches the points whose disk holds
+"""Non-finite inputs on the patch kernels: a NaN or an infinity at a point reaches the points whose disk holds
 it and no others.  The pattern of finite results must be the oracle's, and the finite results must be right, to the bounds
 of the plain cases (bf16: with the allowance that test_gpu_nattn_bf16 derives for D formed from the rounded `out`)."""
 import math
