@@ -117,8 +117,9 @@ size_t s2_nattn_bwd_workspace_bytes(const s2_grid_t *g, int batch, int heads, in
  * Layouts (contiguous): q, out [batch][heads][d][nlat_out][nlon_out] (out has
  * d_v channels); k [batch][heads][d_qk][nlat_in][nlon_in]; v likewise with d_v;
  * lse float32 [batch][heads][nlat_out][nlon_out].
- * dtype: S2_F32 (float32 tensors; up to 64 channels the products run on the bf16 matrix cores, every value as an exact sum of
- * three bf16 terms, with what is left out of a product below 2^-26 of it) or S2_BF16 (q, k, v, out bf16; up to 64 channels the
+ * dtype: S2_F32 (float32 tensors; up to 64 channels the products run on the bf16 matrix cores, every value as the sum of
+ * three bf16 terms, with what is left out of a product below 2^-26 of it.  The sum is exact for values of 2^-110 (7.7e-34) and
+ * more and within 2^-134 of smaller ones) or S2_BF16 (q, k, v, out bf16; up to 64 channels the
  * products run on the bf16 matrix cores, probabilities as exact sums of three bf16 terms; above, float32 arithmetic on bf16
  * loads).  Accumulation, softmax and lse are float32 either way.
  * d_qk, d_v in [1, 128].
@@ -215,7 +216,7 @@ int s2_attn_global_bwd(const s2_grid_t *g, int batch, int heads, int d, int dtyp
  * backward needs, so s2_mha_bwd must get the workspace of the matching s2_mha_fwd call, untouched.
  * channels and nlat*nlon must be multiples of 16 (else S2_ERR_UNSUPPORTED); x, y, dy, dx, pos and the weight
  * matrices must be 16-byte aligned (else S2_ERR_INVALID_ARG).  Every step runs in the library's own
- * kernels (channel matrices on the fp32 matrix cores); results are bit-reproducible.
+ * kernels (channel matrices on the bf16 matrix cores, three terms per value); results are bit-reproducible.
  */
 typedef struct {
     const float *gamma, *beta, *pos;

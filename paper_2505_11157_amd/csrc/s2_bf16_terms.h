@@ -1,8 +1,13 @@
 // float32 values as three bf16 terms, for float32 products on the bf16 matrix cores (device side).
 //
-// x = x0 + x1 + x2, 8 bits each, every term the rounded rest of those before: together they hold x exactly.  A product takes the six
-// of nine term products that are not below 2^-26 of it.  Six bf16 instructions take 0.37 times the cycles of the fp32 ones.
-// A value near the largest float32 rounds to an infinite first term; what is done about non-finite results is the caller's.
+// x = x0 + x1 + x2, 8 bits each, every term the rounded rest of those before: together they hold x exactly down to 2^-110, and within
+// 2^-134 below that, where the last term ends at bf16's smallest number, 2^-133 (the matrix cores take subnormal terms as they are).
+// Attention on unit-variance tensors, rms error of the result: v or dout times 2^-110 1.1e-7 as ever, 2^-114 6e-7, 2^-118 9e-6,
+// 2^-126 2e-3.  Cut from 2^16 times the value, all normal numbers would be held; the multiplication takes 1.1 to 1.4 % of every training
+// step (129 x 256, 32 slices, d = 32 1.629 -> 1.652 ms, d = 64 3.261 -> 3.304) and brings the overflow of products that much closer: not done.
+// A product takes the six of nine term products that are not below 2^-26 of it.  Six bf16 instructions take 0.37 times the cycles of
+// the fp32 ones.
+// A value of (1 - 2^-9) 2^128 or more rounds to an infinite first term; what is done about non-finite results is the caller's.
 #pragma once
 #include <hip/hip_runtime.h>
 

@@ -2,7 +2,7 @@
 // pair of grids and d, e <= 64 (rounded up to 16, 32 or 64 channels).
 //
 // Precision.  A float32 value is the sum of three bf16 terms x0 + x1 + x2 of 8 bits each, every one the rounded rest of those
-// before, and holds it exactly.  A product takes the six of nine term products that are not below 2^-26 of it, smallest first;
+// before, exactly down to 2^-110 (s2_bf16_terms.h).  A product takes the six of nine term products that are not below 2^-26 of it, smallest first;
 // sums over keys keep x0 y0 and the other five in accumulators of their own, so that a long sum takes one rounding per 32 keys at
 // its own magnitude (v_mfma_f32_16x16x32_bf16 adds its 32 products with less loss than 32 multiply-adds).  Dot products of 32
 // and sums over 256 unit-variance values, rms error: multiply-adds and the fp32 matrix cores 1.0e-7 and 2.9e-7 of the result's rms,
