@@ -126,6 +126,10 @@ size_t s2_nattn_bwd_workspace_bytes(const s2_grid_t *g, int batch, int heads, in
  * Non-finite inputs (both directions): a NaN or an infinity at a point reaches the results whose sums hold that point
  * and no others.  Exception: with d_qk = d_v = 32, float32 tensors on grids of 2^15 or more longitudes may also lose
  * results of points close by (masked products there are multiplied by zero).
+ * Longitude shifts (both directions): inputs rolled by whole steps of the grid with fewer longitudes give the rolled
+ * results up to rounding, since most kernels sum in tiles at fixed columns.  Bit for bit the same they are only where
+ * a point's sums run in the order of its offsets: the forward of float32 tensors with d_qk = d_v = 32 on upsampling
+ * grids with nlon_in >= 72, a multiple of 4.  Repeated calls on the same inputs always give the same bits.
  * Errors: S2_ERR_INVALID_ARG (NULL or not 16-byte aligned pointers, sizes < 1),
  * S2_ERR_UNSUPPORTED (dtype, head dims), S2_ERR_DEVICE (host-only handle or
  * launch failure).
