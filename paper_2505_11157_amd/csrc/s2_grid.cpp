@@ -278,15 +278,24 @@ static bool whole_latitudes(std::vector<int> &blo, std::vector<int> &bn, std::ve
 
 // Segments and workgroups of the patch kernels for one kind of owners.  A wavefront owns 16 points, 1 x 16, 2 x 8 or 4 x 4 rows x
 // columns: a square patch meets the fewest walked columns where arcs are short; where they are long, owners of one row share
-// more of theirs.  Each group of four rows takes the shape with the fewest chunks of four columns to walk (counted, not measured).
+// more of theirs.  Each group of four rows takes the shape with the fewest chunks of four columns to walk (counted, not measured), a
+// row at most as many as fill its circle.  Whole circles that chunks do not fill are not walked as such: their patch walks as many
+// columns more as its first and last owner lie apart, and where another shape saves a twentieth of the group's chunks that way, it is
+// taken (disk = sphere, float32, forward / backward, us: 7 x 14 -> 21 x 42, 32 slices, d = 64 80 / 241 -> 25 / 173; 21 x 42 -> 42 x 84, 8
+// slices, d = 32 106 / 269 -> 68 / 227; 31 x 63, 32 slices, d = 32 260 / 714 -> 248 / 668; 75 x 150, 2 slices, d = 16 454 / 1113 -> 409 / 1008;
+// for less than a twentieth, near the poles of 46 x 90 and the like, 2 to 3 % slower: longer chains of fewer wavefronts).
 static void build_patches(const std::vector<int> &blo, const std::vector<int> &bn, const std::vector<int2> &arc, int nU, const float *omega,
                           int c_walk, int step, s2_grid::Patches &p)
 {
     const int n_own = int(blo.size()), bmax = int(arc.size() / blo.size()), ngrp = (n_own + 3) / 4, nW = nU * step;
     p.step = step;
+    // A row of whole circles, every column once: no owner's mask excludes anything.  Offsets stay within 16 bits.
+    constexpr unsigned kAlways = 0xffff8000u;
+    const bool once = nW % 4 == 0 && nW <= 32000;
     struct Row {
-        int lo, hi;
-        bool any;
+        int lo, hi;                      // of the owner rows' arcs
+        bool any, always;
+        int circles;                     // owner rows that meet all of it
         int2 own[4];
     };
     auto walk = [&](int first, int last, int &rmin, std::vector<Row> &rows) {      // owner rows first .. last - 1
@@ -297,42 +306,43 @@ static void build_patches(const std::vector<int> &blo, const std::vector<int> &b
                 rmin = std::min(rmin, blo[v]);
                 rmax = std::max(rmax, blo[v] + bn[v] - 1);
             }
-        rows.assign(size_t(std::max(rmax - rmin + 1, 0)), Row{1 << 30, -(1 << 30), false, {}});
+        rows.assign(size_t(std::max(rmax - rmin + 1, 0)), Row{1 << 30, -(1 << 30), false, false, 0, {}});
         for (int v = first; v < last; ++v)
             for (int i = 0; i < bn[v]; ++i) {
                 const int2 a = arc[size_t(v) * bmax + i];
                 Row &r = rows[blo[v] + i - rmin];
                 if (a.y <= 0) continue;
-                r.own[v - first] = a;
+                r.own[v - first] = a.y >= nW ? make_int2(-(nW / 2), nW) : a;
                 r.any = true;
-                r.lo = std::min(r.lo, a.x);
-                r.hi = std::max(r.hi, a.x + a.y - 1);
+                r.circles += a.y >= nW;
+                r.lo = std::min(r.lo, r.own[v - first].x);
+                r.hi = std::max(r.hi, r.own[v - first].x + r.own[v - first].y - 1);
             }
+        for (Row &r : rows) r.always = once && r.circles == last - first;
     };
     int rmin;
     std::vector<Row> rows;
     std::vector<int> shape(ngrp, 0), seg_of(ngrp + 1, 0);
     for (int s = 0; s < ngrp; ++s) {
-        double least = -1.0;
+        double least[3] = {}, walked[3] = {};
         for (int lg = 0; lg < 3; ++lg) {
             const int W = 16 >> lg;
-            double chunks = 0.0;
             for (int f = 4 * s; f < std::min(4 * s + 4, n_own); f += 1 << lg) {
                 walk(f, std::min(f + (1 << lg), n_own), rmin, rows);
-                for (const Row &r : rows)
-                    if (r.any) chunks += std::min((step * (W - 1) + r.hi - r.lo + 4) / 4.0, (nW + 3) / 4.0) / W;
-            }
-            if (least < 0.0 || chunks < least) {
-                least = chunks;
-                shape[s] = lg;
+                for (const Row &r : rows) {
+                    if (!r.any) continue;
+                    const double n = (step * (W - 1) + r.hi - r.lo + 4) / 4.0, circle = (nW + 3) / 4.0;
+                    least[lg] += std::min(n, circle) / W;
+                    walked[lg] += (r.circles > 0 && !r.always ? n : std::min(n, circle)) / W;
+                }
             }
         }
+        auto fewest = [](const double (&x)[3]) { return int(std::min_element(x, x + 3) - x); };
+        shape[s] = fewest(least);
+        if (walked[fewest(walked)] < 0.95 * walked[shape[s]]) shape[s] = fewest(walked);
     }
     p.seg.clear();
     p.rows.clear();
-    // A row of whole circles, every column once: no owner's mask excludes anything.  Offsets stay within 16 bits.
-    constexpr unsigned kAlways = 0xffff8000u;
-    const bool once = nW % 4 == 0 && nW <= 32000;
     for (int s = 0; s < ngrp; ++s) {
         const int lg = shape[s], OW = std::min(kS2PatchWaves * (16 >> lg), nU);
         seg_of[s] = int(p.seg.size() / 2);
@@ -341,7 +351,7 @@ static void build_patches(const std::vector<int> &blo, const std::vector<int> &b
             walk(f, l, rmin, rows);
             int before = 0, at = int(p.rows.size()), part = 0;
             for (size_t i = 0; i < rows.size(); ++i) {
-                Row &r = rows[i];
+                const Row &r = rows[i];
                 if (i == size_t(part) + kS2PatchRows) {
                     p.seg.push_back(make_int4(f, lg, rmin + part, kS2PatchRows));
                     p.seg.push_back(make_int4(before, at, 1, 0));
@@ -349,28 +359,16 @@ static void build_patches(const std::vector<int> &blo, const std::vector<int> &b
                     at = int(p.rows.size());
                     before = 0;
                 }
-                bool always = once && r.any;
-                for (int k = 0; k < l - f; ++k) {
-                    always &= r.own[k].y >= nW;
-                    if (r.own[k].y >= nW) r.own[k] = make_int2(-(nW / 2), nW);
-                }
-                r.lo = 1 << 30;
-                r.hi = -(1 << 30);
-                for (int k = 0; k < l - f; ++k)
-                    if (r.own[k].y > 0) {
-                        r.lo = std::min(r.lo, r.own[k].x);
-                        r.hi = std::max(r.hi, r.own[k].x + r.own[k].y - 1);
-                    }
-                const int c0 = always || !r.any ? 0 : r.lo & ~3;
+                const int c0 = r.always || !r.any ? 0 : r.lo & ~3;
                 auto pack = [](int lo, int n) { return unsigned(lo & 0xffff) | unsigned(n) << 16; };
                 S2PatchRow o{};
                 o.col = c0 - 4 * before;
-                o.uni = int(!r.any ? 0u : always ? kAlways : pack(r.lo, r.hi - r.lo + 1));
+                o.uni = int(!r.any ? 0u : r.always ? kAlways : pack(r.lo, r.hi - r.lo + 1));
                 o.before = before;
                 o.omega = omega ? omega[(rmin + int(i)) / c_walk] : 1.f;
-                for (int k = 0; k < l - f; ++k) o.arc[k] = always ? kAlways : pack(r.own[k].x, r.own[k].y);
+                for (int k = 0; k < l - f; ++k) o.arc[k] = r.always ? kAlways : pack(r.own[k].x, r.own[k].y);
                 p.rows.push_back(o);
-                before += !r.any ? 0 : always ? nW / 4 : (step * (OW - 1) + r.hi - c0 + 4) / 4;
+                before += !r.any ? 0 : r.always ? nW / 4 : (step * (OW - 1) + r.hi - c0 + 4) / 4;
             }
             p.seg.push_back(make_int4(f, lg, rows.empty() ? 0 : rmin + part, int(rows.size()) - part));
             p.seg.push_back(make_int4(before, at, 0, 0));

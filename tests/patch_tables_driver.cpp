@@ -1,6 +1,8 @@
 // Walks the segments, rows, chunks and patches that s2_grid_init makes for the patch kernels (s2_nattn_patch_impl.h) the way the
-// kernels do, on the host, and compares what every owner meets with the arc tables: each neighbor once, and nothing else.
+// kernels do, on the host, and compares what every owner meets with the arc tables: each neighbor once, and nothing else.  Also
+// prints how many chunks more than the circle has a wavefront walks at most on a row of which an owner meets all.
 // Arguments: grid type, four sizes, theta.
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <map>
@@ -13,7 +15,8 @@ int s2_nattn_stream_configure() { return 0; }
 int s2_nattn_band_configure() { return 0; }
 int s2_static_scratch_setup(int) { return 0; }
 
-static int check(const s2_grid::Patches &p, const std::vector<int> &blo, const std::vector<int> &bn, const std::vector<int2> &arc, int nU, int c_walk)
+static int check(const s2_grid::Patches &p, const std::vector<int> &blo, const std::vector<int> &bn, const std::vector<int2> &arc, int nU, int c_walk,
+                 double &more)
 {
     const int n_own = int(blo.size()), bmax = int(arc.size() / blo.size());
     const int S = p.step, nW = S * nU;
@@ -34,11 +37,13 @@ static int check(const s2_grid::Patches &p, const std::vector<int> &blo, const s
                 for (int i = 0; i < t0.w; ++i) {
                     const S2PatchRow &r = p.rows[t1.y + i];
                     const int end = i + 1 < t0.w ? p.rows[t1.y + i + 1].before : t1.x;
+                    int walked = 0;
                     for (int X = r.before; X < end; ++X) {
                         const int col = r.col + 4 * X + S * wg.y, d = col + 3 - S * wc - int(short(r.uni & 0xffff));
                         if (col < -2 * nW || col + 3 + 2 * nW >= 1 << 22 || col >= 1 << 17 || col < -(1 << 17)) return 2;    // what wrap_col and a list entry hold
                         const unsigned a = r.arc[n / W], rel = unsigned(col - (S * u + int(short(a & 0xffff))));
                         const bool listed = unsigned(d) < (unsigned(r.uni) >> 16) + S * (W - 1) + 3;
+                        walked += listed;
                         for (int j = 0; j < 4; ++j)
                             if (rel + j < (a >> 16)) {
                                 if (!listed) return 3;
@@ -46,6 +51,7 @@ static int check(const s2_grid::Patches &p, const std::vector<int> &blo, const s
                                 ++met[{(t0.z + i) * S + at % S, at / S}];
                             }
                     }
+                    if (int(r.arc[n / W] >> 16) >= nW) more = std::max(more, walked - nW / 4.0);
                 }
                 if (t1.z == 0) break;
                 }
@@ -70,9 +76,10 @@ int main(int argc, char **argv)
     s2_grid_t *g = nullptr;
     if (argc != 7 || s2_grid_init(atoi(argv[1]), atoi(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atof(argv[6]), &g) != S2_OK) return 100;
     const int nU = g->nlon_in < g->nlon_out ? g->nlon_in : g->nlon_out;
-    const int a = check(g->vo_patch, g->vo_lo, g->vo_n, g->vo_arc, nU, g->pscale),
-              b = check(g->vi_patch, g->vi_lo, g->vi_n, g->vi_arc, nU, g->upscale);
+    double more_a = 0.0, more_b = 0.0;
+    const int a = check(g->vo_patch, g->vo_lo, g->vo_n, g->vo_arc, nU, g->pscale, more_a),
+              b = check(g->vi_patch, g->vi_lo, g->vi_n, g->vi_arc, nU, g->upscale, more_b);
     s2_grid_destroy(g);
-    printf("%d %d\n", a, b);
+    printf("%d %d %g %g\n", a, b, more_a, more_b);
     return a ? a : b ? 10 + b : 0;
 }

@@ -28,4 +28,16 @@ def driver(tmp_path_factory):
 @pytest.mark.parametrize("shape", SHAPES, ids=str)
 def test_every_owner_meets_its_neighbors_once(driver, shape):
     r = subprocess.run([driver] + [str(x) for x in shape], capture_output=True, text=True, timeout=300)
-    assert r.returncode == 0 and r.stdout.split() == ["0", "0"], (r.returncode, r.stdout, r.stderr[-500:])
+    assert r.returncode == 0 and r.stdout.split()[:2] == ["0", "0"], (r.returncode, r.stdout, r.stderr[-500:])
+
+
+@pytest.mark.parametrize("shape", [(1, 12, 27, 12, 27, 3.14159), (1, 20, 42, 20, 42, 3.14159), (1, 32, 63, 32, 63, 3.14159), (1, 32, 64, 32, 64, 3.14159),
+                                   (1, 32, 63, 64, 126, 3.14159), (1, 64, 126, 32, 63, 3.14159)], ids=str)
+def test_whole_circles_are_walked_about_once(driver, shape):
+    # a patch of 4 x 4 owners needs the 3 step columns more by which its owners lie apart and begins at a multiple of four (a patch of
+    # 1 x 16: 15 step); nothing more where chunks fill the circle
+    r = subprocess.run([driver] + [str(x) for x in shape], capture_output=True, text=True, timeout=300)
+    ratio = shape[1] // shape[3] or 1, shape[3] // shape[1] or 1
+    for more, step in zip(r.stdout.split()[2:], ratio):
+        assert float(more) <= (3 * step + 6) / 4, r.stdout
+        assert float(more) == 0 or min(shape[2], shape[4]) * step % 4
