@@ -84,7 +84,10 @@ __device__ __forceinline__ int explain(f32x16 (&acc)[MT], const unsigned (&codes
 constexpr int kSlice = 16;
 constexpr int kRow = 24;                                   // bf16 values per row of a slice in LDS
 
-template <bool TRANS, int MT>
+// FAR: grids of so many points that a lane's offset, up to 9 rows of X, takes more than 32 bits (with one row block only: they are few)
+inline bool far_rows(int N, int rows) { return 4ull * rows * N >= 1ull << 32; }
+
+template <bool TRANS, int MT, bool FAR = false>
 __device__ __forceinline__ void product_strip(const S2ChannelProduct &a, int strip, int strips_per_batch, int set, int m0, __bf16 *lds)
 {
     constexpr int MB = 32 * MT, PIECES = MB * kSlice / (TRANS ? 8 : 4), NP = (PIECES + 255) / 256, TERM = MB * kRow, BUF = kTerms * TERM;
@@ -92,7 +95,8 @@ __device__ __forceinline__ void product_strip(const S2ChannelProduct &a, int str
     const int col = lane & 31, kk = lane >> 5;
     const int b = strip / strips_per_batch, n = (strip - b * strips_per_batch) * 128 + wave * 32 + col;
     const bool ok = n < a.N;
-    unsigned lane_off = (unsigned(8 * kk) * unsigned(a.N) + unsigned(ok ? n : 0)) * 4u;      // past the last column: column 0, not stored
+    using Offset = std::conditional_t<FAR, unsigned long long, unsigned>;
+    Offset lane_off = (Offset(8 * kk) * unsigned(a.N) + unsigned(ok ? n : 0)) * 4u;      // past the last column: column 0, not stored
     asm volatile("" : "+v"(lane_off));
     const size_t step = size_t(a.N) * sizeof(float);
     const int M = a.M, K = a.K;
@@ -274,8 +278,8 @@ __device__ __forceinline__ void product_strip(const S2ChannelProduct &a, int str
 
 // Strips of the whole rounds of workgroups at MT row blocks, those of the last, partial round cut into single row blocks.
 // The workgroups of one strip of X are eight apart: they run on the same die and share its L2.
-template <bool TRANS, int MT>
-__global__ void __launch_bounds__(256, MT == 1 ? 8 : 4)
+template <bool TRANS, int MT, bool FAR = false>
+__global__ void __launch_bounds__(256, MT == 1 && !FAR ? 8 : 4)
 channel_product(S2ChannelProduct a, int strips_per_batch, int nstrips, int mblocks, int whole_groups)
 {
     extern __shared__ __attribute__((aligned(16))) __bf16 lds[];
@@ -285,7 +289,7 @@ channel_product(S2ChannelProduct a, int strips_per_batch, int nstrips, int mbloc
         id >>= 3;
         const int part = id % parts, strip = (id / parts) * 8 + lo;
         if (strip < nstrips)
-            product_strip<TRANS, MT>(a, strip, strips_per_batch, part / mblocks, (part % mblocks) * 32 * MT, lds);
+            product_strip<TRANS, MT, FAR>(a, strip, strips_per_batch, part / mblocks, (part % mblocks) * 32 * MT, lds);
     } else {
         id = (id - whole) >> 3;
         const int part = id % (parts * MT), strip = (whole_groups + id / (parts * MT)) * 8 + lo, m0 = (part % (mblocks * MT)) * 32;
@@ -530,7 +534,8 @@ inline GradPlan grad_plan(int M, int K, int nset)
 
 void s2_channel_product(bool trans, const S2ChannelProduct &a, hipStream_t st)
 {
-    const int mt = row_blocks(a.M), mblocks = (a.M + 32 * mt - 1) / (32 * mt), spb = (a.N + 127) / 128, nstrips = spb * a.batch;
+    const bool far = far_rows(a.N, 9);
+    const int mt = far ? 1 : row_blocks(a.M), mblocks = (a.M + 32 * mt - 1) / (32 * mt), spb = (a.N + 127) / 128, nstrips = spb * a.batch;
     // Four workgroups per compute unit (eight with one row block), held to by the LDS they ask for: with room for more the
     // dispatcher fills some units with five and leaves others three.
     const int occ = mt == 1 ? 8 : 4, parts = mblocks * a.nset, round = 256 * occ, groups = (nstrips + 7) / 8;
@@ -539,8 +544,10 @@ void s2_channel_product(bool trans, const S2ChannelProduct &a, hipStream_t st)
     const int whole = split ? groups - rest : groups;
     const dim3 grid(unsigned(whole + (groups - whole) * mt) * 8 * parts);
     const size_t lds = mt == 1 ? 19 * 1024 : 38 * 1024;
-#define S2_PRODUCT(T, MT) hipLaunchKernelGGL((channel_product<T, MT>), grid, dim3(256), lds, st, a, spb, nstrips, mblocks, whole)
-    switch (mt + (trans ? 4 : 0)) {
+#define S2_PRODUCT(T, ...) hipLaunchKernelGGL((channel_product<T, __VA_ARGS__>), grid, dim3(256), lds, st, a, spb, nstrips, mblocks, whole)
+    switch (far ? trans - 1 : mt + (trans ? 4 : 0)) {
+    case -1: S2_PRODUCT(false, 1, true); break;
+    case 0: S2_PRODUCT(true, 1, true); break;
     case 1: S2_PRODUCT(false, 1); break;
     case 2: S2_PRODUCT(false, 2); break;
     case 3: S2_PRODUCT(false, 3); break;
