@@ -84,8 +84,9 @@ __device__ __forceinline__ int explain(f32x16 (&acc)[MT], const unsigned (&codes
 constexpr int kSlice = 16;
 constexpr int kRow = 24;                                   // bf16 values per row of a slice in LDS
 
-// FAR: grids of so many points that a lane's offset, up to 9 rows of X, takes more than 32 bits (with one row block only: they are few)
-inline bool far_rows(int N, int rows) { return 4ull * rows * N >= 1ull << 32; }
+// FAR: grids of so many points that a lane's offset takes more than 32 bits: up to 9 rows of X here, in bytes, the rows of a tile in the
+// weight gradients, in values (with one row block only: such grids are few)
+inline bool far_rows(int N, unsigned long long of_row) { return of_row * N >= 1ull << 32; }
 
 template <bool TRANS, int MT, bool FAR = false>
 __device__ __forceinline__ void product_strip(const S2ChannelProduct &a, int strip, int strips_per_batch, int set, int m0, __bf16 *lds)
@@ -310,7 +311,7 @@ channel_product(S2ChannelProduct a, int strips_per_batch, int nstrips, int mbloc
 constexpr int kPoints = 32;
 constexpr int wgrad_lds(int rows) { return kTerms * 2 * rows * kRow * 2; }       // bytes of LDS
 
-template <int MT, int WR, int WN>
+template <int MT, int WR, int WN, bool FAR = false>
 __global__ void __launch_bounds__(64 * WR * WN)
 channel_wgrad(S2ChannelGrad a, int ktiles, int mblocks, int nsplit, float *__restrict__ part)
 {
@@ -337,13 +338,14 @@ channel_wgrad(S2ChannelGrad a, int ktiles, int mblocks, int nsplit, float *__res
     const float *dY = a.dY[set], *X = a.X[set];
 
     float4 r[NP];
-    unsigned off[NP];          // row inside the tile (rows past the end: the last one, feeding results that are not stored)
+    using Offset = std::conditional_t<FAR, unsigned long long, unsigned>;
+    Offset off[NP];            // row inside the tile (rows past the end: the last one, feeding results that are not stored)
     float bsum[NA];
     const int pc = 4 * (tid & 7);
 #pragma unroll
     for (int j = 0; j < NP; ++j) {
         const int row = min((tid >> 3) + (NT / 8) * j, ROWS - 1);
-        off[j] = unsigned(row < YR ? min(row, M - 1 - m0) : min(row - YR, K - 1 - k0)) * unsigned(N) + pc;
+        off[j] = Offset(row < YR ? min(row, M - 1 - m0) : min(row - YR, K - 1 - k0)) * unsigned(N) + pc;
     }
 #pragma unroll
     for (int j = 0; j < NA; ++j) bsum[j] = 0.f;
@@ -534,7 +536,7 @@ inline GradPlan grad_plan(int M, int K, int nset)
 
 void s2_channel_product(bool trans, const S2ChannelProduct &a, hipStream_t st)
 {
-    const bool far = far_rows(a.N, 9);
+    const bool far = far_rows(a.N, 9 * sizeof(float));
     const int mt = far ? 1 : row_blocks(a.M), mblocks = (a.M + 32 * mt - 1) / (32 * mt), spb = (a.N + 127) / 128, nstrips = spb * a.batch;
     // Four workgroups per compute unit (eight with one row block), held to by the LDS they ask for: with room for more the
     // dispatcher fills some units with five and leaves others three.
@@ -567,11 +569,19 @@ size_t s2_channel_grad_floats(int M, int K, int nset)
 
 void s2_channel_grad(const S2ChannelGrad &a, float *part, hipStream_t st)
 {
-    const GradPlan p = grad_plan(a.M, a.K, a.nset);
+    GradPlan p = grad_plan(a.M, a.K, a.nset);
+    const bool far = far_rows(a.N, 32 * std::max(p.mt, p.wn));
+    if (far) {                                   // (the splits, and with them the partial sums, stay)
+        p.mt = 1;
+        p.wn = 4;
+        p.mblocks = (a.M + 31) / 32;
+        p.ktiles = (a.K + 127) / 128;
+    }
     const dim3 grid(unsigned(p.ktiles) * p.mblocks * a.nset * p.nsplit);
-#define S2_GRAD(MT, WR, WN) \
-    hipLaunchKernelGGL((channel_wgrad<MT, WR, WN>), grid, dim3(64 * WR * WN), 0, st, a, p.ktiles, p.mblocks, p.nsplit, part)
-    if (p.mt == 1) S2_GRAD(1, 1, 4);
+#define S2_GRAD(MT, WR, WN, ...) \
+    hipLaunchKernelGGL((channel_wgrad<MT, WR, WN, ##__VA_ARGS__>), grid, dim3(64 * WR * WN), 0, st, a, p.ktiles, p.mblocks, p.nsplit, part)
+    if (far) S2_GRAD(1, 1, 4, true);
+    else if (p.mt == 1) S2_GRAD(1, 1, 4);
     else if (p.mt == 2 && p.wn == 2) S2_GRAD(1, 2, 2);
     else if (p.mt == 2 && p.wn == 4) S2_GRAD(1, 2, 4);
     else if (p.mt == 2) S2_GRAD(1, 2, 6);

@@ -32,3 +32,20 @@ def test_products_of_far_rows():
             for a, r, terms in ((y, w @ z, w.abs() @ z.abs()), (dx, omega[lat] * (w.t() @ d), omega[lat] * (w.abs().t() @ d.abs()))):
                 # 16 products and z itself, each rounded once
                 assert bool(((a[0, :, lat, cols].double() - r).abs() <= 18 * 2.0 ** -24 * terms).all()), (lat, cols)
+
+
+def test_weight_gradients_of_far_rows():
+    # 128 rows of dy, offsets counted in points
+    nlat = 513
+    dc, omega, x, w, dy = _disco(nlat, 16, 128)
+    assert 128 * nlat * 65536 >= 2 ** 32
+    _, ws = S.s2_disco_fwd(dc, x, w, None)
+    dw, db = S.s2_disco_bwd(dc, x, w, dy, ws)[1:3]
+    ref, sums = torch.zeros(128, 16, dtype=torch.float64, device="cuda:0"), torch.zeros(128, dtype=torch.float64, device="cuda:0")
+    for lat in range(0, nlat, 27):
+        d, z = dy[0, :, lat:lat + 27].double(), omega[lat:lat + 27] * x[0, :, lat:lat + 27].double()
+        ref += d.flatten(1) @ z.flatten(1).t()
+        sums += d.flatten(1).sum(1)
+    # sums of 33 million random products: of the order of their root mean square where a row is mistaken for another
+    for a, r in ((dw[:, :, 0], ref), (db, sums)):
+        assert float((a.double() - r).abs().max()) <= 1e-3 * float((r ** 2).mean().sqrt())
