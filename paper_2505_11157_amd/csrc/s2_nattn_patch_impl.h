@@ -33,7 +33,7 @@
 // five of them on a compute unit, whose barriers do not coincide (eight wavefronts, stages twice as long: dk/dv 0.72 against
 // 0.70 ms; all of LDS for one workgroup: 1.43).
 // Measured (129 x 256, 32 slices, forward / dq / dk,dv, ms; before: fp32 matrix cores and vector kernels):
-//   d = 16  0.42 / 0.52 / 0.65 -> 0.29 / 0.32 / 0.39        d = 32  0.66 / 0.83 / 1.03 -> 0.43 / 0.49 / 0.67
+//   d = 16  0.42 / 0.52 / 0.65 -> 0.29 / 0.32 / 0.39        d = 32  0.66 / 0.83 / 1.03 -> 0.42 / 0.49 / 0.63
 //   d = 64  1.49 / 1.95 / 2.48 -> 0.90 / 1.05 / 1.28
 //
 // bf16 tensors are one term; probabilities and dS, which multiply them, are cut into three, so that every product is the float32
@@ -75,11 +75,15 @@ struct Geo {
     static constexpr int ROW = 4 * UNITS;                   // bf16 values per channel row
     static constexpr int TERM = D * ROW + 16, TENSOR = TERMS * TERM;
     static constexpr int KC = D == 16 ? 1 : D / 32;
-    static constexpr int NG = NT / CAP;                     // channels staged at once
-    static constexpr int NP = D / NG;                       // pieces (4 columns of a channel) per thread and tensor
+    static constexpr int XL = CAP & -CAP, NG = NT / XL;     // chunks and channels staged at once
+    static constexpr int CJ = CAP / XL, NC = D / NG;        // pieces (4 columns of a channel) per thread and tensor: chunks, channels
+    static constexpr int LOOK = 64 / CAP * CAP;             // chunks looked up at once
     static constexpr int OWN = 4 * NW;                      // chunks of the workgroup's own points
+    // channels of them at once, pieces per thread: dealt out apart from a stage's, which may have more chunks (threads that would take
+    // the points again; 65 x 128 -> 129 x 256, 8 slices, bf16, d = 64: forward 82 -> 72 us, backward 208 -> 171)
+    static constexpr int NGO = NT / OWN, NCO = D / NGO;
     static constexpr int PITCH = 4 * OWN + 4;               // floats per channel of the results
-    static_assert(NP >= 1 && D % NG == 0 && NG >= 2 && (UNITS / 4) % 2 == 1 && OWN <= CAP && D * PITCH * 4 <= TENSOR * 2, "geometry");
+    static_assert(D % NG == 0 && D % NGO == 0 && CJ * NC >= NCO && (UNITS / 4) % 2 == 1 && OWN <= CAP && D * PITCH * 4 <= TENSOR * 2, "geometry");
     static __device__ __forceinline__ constexpr int start(int c) { return c * ROW + 8 * ((c >> 3) & 1) + 4 * (c >> 4); }
     static constexpr int UP = 16 * ROW + 4;                 // from a channel to the one 16 later
 };
@@ -97,7 +101,7 @@ struct Shared {
 };
 template <class G>
 struct SharedDq : Shared<G> {
-    float part[G::NG][G::PITCH];     // partial sums of D
+    float part[G::NGO][G::PITCH];    // partial sums of D
 };
 template <class G>
 struct SharedDkdv : Shared<G> {
@@ -211,15 +215,15 @@ struct PatchWhere {
         }
     }
 };
-// The chunks of a workgroup: looked up 64 at a time, one per lane, and staged CAP at a time.
+// The chunks of a workgroup: looked up LOOK at a time, one per lane, and staged CAP at a time.
 template <class G>
 struct Chunks {
     int P_v[2];                      // chunks before row lane, 64 + lane
     int r;
-    int entry;                       // of the 64 looked up last: the lane's chunk, its column, row and place in its stage
+    int entry;                       // of those looked up last: the lane's chunk, its column, row and place in its stage
     int list;                        // ... those that the wavefront's points meet, in order
     unsigned long long met;          // ... which they are
-    int row, col;                    // of the stage set last: the chunk that the thread stages
+    int sh;                          // of the stage set last: its place among those looked up
     int first, cnt;                  // ... where the list has its chunks, and how many
 
     __device__ __forceinline__ int before(int i) const
@@ -247,35 +251,40 @@ struct Chunks {
         P_v[0] = t.before[w.lane];
         P_v[1] = t.before[64 + w.lane];
         r = 0;
+        sh = 0;
     }
-    // the chunks X0 .. X0 + 63 (X0 < total; past the last: that one again, not met)
+    // the chunks X0 .. X0 + LOOK - 1 (X0 < total; past the last: that one again, not met)
     __device__ __forceinline__ void look(int X0, const PatchWhere &w, const RowTab &t)
     {
         const int X = imin(X0 + w.lane, w.total - 1);
         int at = r;
         while (r + 1 < w.nrows) {
             const int p = before(r + 1);
-            if (p >= X0 + 64) break;
+            if (p >= X0 + G::LOOK) break;
             ++r;
             at += X >= p ? 1 : 0;
         }
         const int u = t.uni[at], c = t.col[at] + 4 * X + w.step * w.W0, d = c + 3 - w.step * w.wc - int(short(u & 0xffff));
-        const bool need = X0 + w.lane < w.total && w.wc < w.nU && unsigned(d) < (unsigned(u) >> 16) + w.step * (w.W - 1) + 3;
+        const bool need = w.lane < G::LOOK && X0 + w.lane < w.total && w.wc < w.nU && unsigned(d) < (unsigned(u) >> 16) + w.step * (w.W - 1) + 3;
         met = __ballot(need);
         const int ones = __builtin_amdgcn_mbcnt_hi(unsigned(met >> 32), __builtin_amdgcn_mbcnt_lo(unsigned(met), 0));
-        entry = c << 14 | at << 6 | (w.lane & (G::CAP - 1));
+        entry = c << 14 | at << 6 | w.lane % G::CAP;
         list = __builtin_amdgcn_ds_permute(4 * (need ? ones : __popcll(met) + w.lane - ones), entry);
     }
-    // the stage of chunks X0 .. X0 + CAP - 1
+    // the stage of chunks X0 .. X0 + CAP - 1, stages in order
     __device__ __forceinline__ void set(int X0, const PatchWhere &w, const RowTab &t)
     {
-        const int sh = X0 & 63;
+        sh = G::LOOK == 64 ? X0 & 63 : X0 == 0 || sh + G::CAP == G::LOOK ? 0 : sh + G::CAP;
         if (sh == 0) look(X0, w, t);
-        const int e = __builtin_amdgcn_ds_bpermute(4 * (sh + (w.lane & (G::CAP - 1))), entry);
-        row = e >> 6 & 255;
-        col = e >> 14;
         first = __popcll(met & ((1ull << sh) - 1));
         cnt = __popcll(met >> sh & (~0ull >> (64 - G::CAP)));
+    }
+    // row and column of chunk i of the stage
+    __device__ __forceinline__ void get(int i, int &row, int &col) const
+    {
+        const int e = __builtin_amdgcn_ds_bpermute(4 * (sh + i), entry);
+        row = e >> 6 & 255;
+        col = e >> 14;
     }
 };
 
@@ -284,25 +293,20 @@ struct Chunks {
 // bf16, forward 196 us, now 130; 179 x 358, 6 slices, d = 32, bf16, forward and backward 859 -> 595; around the seam of circles of
 // some thirty longitudes, where most pieces are apart, 24.3 -> 25.4.
 // From memory to registers, and (float32: cut into three terms) on to LDS.
-template <class G, int MODE>
-struct Place {
+// Where a chunk is, in a channel plane (kWide: in a slice)
+template <class T, int MODE>
+struct ChunkAt {
     static constexpr bool WIDE = MODE == kWide;
-    unsigned off[WIDE ? 1 : 4];      // kWide: byte offset of the thread's first piece in the slice; else elements in a channel plane
+    unsigned off[WIDE ? 1 : 4];      // kWide: byte offset; else elements
     bool apart;                      // not kWide: a chunk of the wavefront's is not four elements side by side (uniform; else off[0] only)
-    int x, cg;                       // the thread's chunk and first channel
-    __device__ __forceinline__ void init(const PatchWhere &w)
+    // channel: its first one (kWide only)
+    __device__ __forceinline__ void set(const PatchWhere &w, int row, int col, int channel)
     {
-        x = w.tid & (G::CAP - 1);
-        cg = w.tid / G::CAP;
-    }
-    __device__ __forceinline__ void set(const PatchWhere &w, int row, int col)
-    {
+        const int c = wrap_col(col + 2 * w.nW, w.nW, w.inv_nW);
         if constexpr (WIDE) {
-            const unsigned c = unsigned(wrap_col(col + 2 * w.nW, w.nW, w.inv_nW));
-            off[0] = unsigned(sizeof(typename G::T)) * (unsigned(cg) * unsigned(w.plane_walk) + unsigned(row) * unsigned(w.nW) + c);
+            off[0] = unsigned(sizeof(T)) * (unsigned(channel) * unsigned(w.plane_walk) + unsigned(row) * unsigned(w.nW) + unsigned(c));
         } else {
             const unsigned at = unsigned(w.row_walked(row));
-            const int c = wrap_col(col + 2 * w.nW, w.nW, w.inv_nW);
             apart = w.stride > 1 || __any(c + 4 > w.nW);
             off[0] = at + unsigned(w.stride) * unsigned(c);
             if (!apart) return;
@@ -310,12 +314,12 @@ struct Place {
             for (int i = 1; i < 4; ++i) off[i] = at + unsigned(w.stride) * unsigned(wrap_col(col + i + 2 * w.nW, w.nW, w.inv_nW));
         }
     }
-    // the same place in a float32 plane
-    __device__ __forceinline__ f32x4 stat(const PatchWhere &w, const float *plane) const
+    // its values in a float32 plane
+    __device__ __forceinline__ f32x4 floats(const float *plane) const
     {
         f32x4 s;
         if constexpr (WIDE) {
-            s = load_at<f32x4>(plane, off[0] / unsigned(sizeof(typename G::T)) * 4u - 4u * unsigned(cg) * unsigned(w.plane_walk));
+            s = load_at<f32x4>(plane, off[0] / unsigned(sizeof(T)) * 4u);
         } else if (!apart) {
             __builtin_memcpy(&s, plane + off[0], sizeof s);
         } else {
@@ -325,31 +329,58 @@ struct Place {
         return s;
     }
 };
+// What a thread stages: chunks x + XL j, channels cg + NG c
+template <class G, int MODE>
+struct Place {
+    using At = ChunkAt<typename G::T, MODE>;
+    static constexpr bool WIDE = At::WIDE;
+    At at[G::CJ];
+    int x, cg;
+    __device__ __forceinline__ void init(const PatchWhere &w)
+    {
+        x = w.tid & (G::XL - 1);
+        cg = w.tid / G::XL;
+    }
+    __device__ __forceinline__ void set(const PatchWhere &w, const Chunks<G> &ch)
+    {
+#pragma unroll
+        for (int j = 0; j < G::CJ; ++j) {
+            int row, col;
+            ch.get(x + G::XL * j, row, col);
+            at[j].set(w, w.rmin + row, col, cg);
+        }
+    }
+};
 template <class G, int MODE>
 struct Stage {
     using T = typename G::T;
     using Piece = std::conditional_t<sizeof(T) == 4, f32x4, u16x4>;
     using P = Place<G, MODE>;
-    Piece r[G::NP];
-    __device__ __forceinline__ void load(const PatchWhere &w, const P &at, const T *slice, int nch)
+    Piece r[G::CJ * G::NC];          // of the workgroup's own points: the first NCO
+    __device__ __forceinline__ void load(const PatchWhere &w, const P &place, const T *slice, int nch)
     {
-        if constexpr (P::WIDE) {
 #pragma unroll
-            for (int j = 0; j < G::NP; ++j) r[j] = load_at<Piece>(slice + size_t(j * G::NG) * w.plane_walk, at.off[0]);
-        } else {
-            auto channel = [&](int j) {
-                const int c = at.cg + j * G::NG;
-                return slice + size_t(MODE == kRagged ? imin(c, nch - 1) : c) * w.plane_walk;
-            };
-            if (!at.apart) {
+        for (int j = 0; j < G::CJ; ++j) {
+            const typename P::At &at = place.at[j];
+            Piece *rj = r + j * G::NC;
+            if constexpr (P::WIDE) {
 #pragma unroll
-                for (int j = 0; j < G::NP; ++j) __builtin_memcpy(&r[j], channel(j) + at.off[0], sizeof r[j]);
+                for (int k = 0; k < G::NC; ++k) rj[k] = load_at<Piece>(slice + size_t(k * G::NG) * w.plane_walk, at.off[0]);
             } else {
+                auto channel = [&](int k) {
+                    const int c = place.cg + k * G::NG;
+                    return slice + size_t(MODE == kRagged ? imin(c, nch - 1) : c) * w.plane_walk;
+                };
+                if (!at.apart) {
 #pragma unroll
-                for (int j = 0; j < G::NP; ++j) {
-                    const T *p = channel(j);
+                    for (int k = 0; k < G::NC; ++k) __builtin_memcpy(&rj[k], channel(k) + at.off[0], sizeof rj[k]);
+                } else {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) r[j][i] = p[at.off[i]];
+                    for (int k = 0; k < G::NC; ++k) {
+                        const T *p = channel(k);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) rj[k][i] = p[at.off[i]];
+                    }
                 }
             }
         }
@@ -357,13 +388,13 @@ struct Stage {
     // the workgroup's own points; vec: its rows are contiguous
     __device__ __forceinline__ void load_own(const PatchWhere &w, const T *slice, int nch, bool vec)
     {
-        const int h = 2 - here_s(w.lg), tid = here_v(w.tid), x = tid & (G::OWN - 1), cg = tid / G::CAP, sub = (x / G::NW) >> h;
+        const int h = 2 - here_s(w.lg), tid = here_v(w.tid), x = tid & (G::OWN - 1), cg = tid / G::OWN, sub = (x / G::NW) >> h;
         const int row = w.first + sub < w.n_own ? w.first + sub : w.first, u = w.W0 + 4 * (x - G::NW * (sub << h));
         const T *p = slice + w.row_at(row);
         if (!P::WIDE) vec = vec && !__any(u < w.nU && u + 4 > w.nU);       // a row that ends within a piece
 #pragma unroll
-        for (int j = 0; j < G::NP; ++j) {
-            const int c = cg + j * G::NG;
+        for (int j = 0; j < G::NCO; ++j) {
+            const int c = cg + j * G::NGO;
             const T *pc = p + size_t(MODE == kRagged ? imin(c, nch - 1) : c) * w.plane_own;
             if (vec) {
                 if constexpr (P::WIDE) r[j] = *reinterpret_cast<const Piece *>(pc + (u < w.nU ? u : 0));
@@ -374,10 +405,10 @@ struct Stage {
             }
         }
     }
-    __device__ __forceinline__ void negate()
+    __device__ __forceinline__ void negate_own()
     {
 #pragma unroll
-        for (int j = 0; j < G::NP; ++j) {
+        for (int j = 0; j < G::NCO; ++j) {
             if constexpr (sizeof(T) == 4) r[j] = -r[j];
             else r[j] ^= static_cast<unsigned short>(0x8000);
         }
@@ -393,25 +424,34 @@ struct Stage {
             return v;
         }
     }
-    __device__ __forceinline__ void store(const P &at, __bf16 *tile, int nch) const
+    // piece v as chunk x of channel c
+    static __device__ __forceinline__ void put(__bf16 *tile, int c, int x, Piece v, int nch)
+    {
+        if (MODE == kRagged && c >= nch) v = Piece{0, 0, 0, 0};
+        __bf16 *p = tile + G::start(c) + 4 * x;
+        if constexpr (sizeof(T) == 4) {
+            float x0 = v[0], x1 = v[1], x2 = v[2], x3 = v[3];
+#pragma unroll
+            for (int k = 0; k < kTerms; ++k) {
+                const unsigned a = cut_off(x0, x1), b = cut_off(x2, x3);
+                *reinterpret_cast<u32x2 *>(p + k * G::TERM) = u32x2{a, b};
+            }
+        } else {
+            *reinterpret_cast<u16x4 *>(p) = v;
+        }
+    }
+    __device__ __forceinline__ void store(const P &place, __bf16 *tile, int nch) const
     {
 #pragma unroll
-        for (int j = 0; j < G::NP; ++j) {
-            const int c = at.cg + j * G::NG;
-            Piece v = r[j];
-            if (MODE == kRagged && c >= nch) v = Piece{0, 0, 0, 0};
-            __bf16 *p = tile + G::start(c) + 4 * at.x;
-            if constexpr (sizeof(T) == 4) {
-                float x0 = v[0], x1 = v[1], x2 = v[2], x3 = v[3];
+        for (int j = 0; j < G::CJ; ++j)
 #pragma unroll
-                for (int k = 0; k < kTerms; ++k) {
-                    const unsigned a = cut_off(x0, x1), b = cut_off(x2, x3);
-                    *reinterpret_cast<u32x2 *>(p + k * G::TERM) = u32x2{a, b};
-                }
-            } else {
-                *reinterpret_cast<u16x4 *>(p) = v;
-            }
-        }
+            for (int k = 0; k < G::NC; ++k) put(tile, place.cg + k * G::NG, place.x + G::XL * j, r[j * G::NC + k], nch);
+    }
+    __device__ __forceinline__ void store_own(const PatchWhere &w, const P &place, __bf16 *tile, int nch) const
+    {
+        const int tid = here_v(w.tid), x = G::XL == G::OWN ? place.x : tid & (G::OWN - 1), cg = G::XL == G::OWN ? place.cg : tid / G::OWN;
+#pragma unroll
+        for (int j = 0; j < G::NCO; ++j) put(tile, cg + j * G::NGO, x, r[j], nch);
     }
 };
 
@@ -634,14 +674,14 @@ nattn_fwd_patch(BandArgs a, const typename G::T *__restrict__ q, const typename 
     ch.start(a, w, sh.rows);
     auto fetch = [&](int X0) {
         ch.set(X0, w, sh.rows);
-        at.set(w, w.rmin + ch.row, ch.col);
+        at.set(w, ch);
         rk.load(w, at, ks, nd);
         rv.load(w, at, vs, ne);
     };
     const int tr_at = G::start(4 * g + (n >> 2)), row_at = G::start(n);
     __syncthreads();                    // everybody is done with what LDS held
-    if (a.scale < 0.f) rk.negate();
-    rk.store(at, sh.a, nd);
+    if (a.scale < 0.f) rk.negate_own();
+    rk.store_own(w, at, sh.a, nd);
     __syncthreads();
     if (w.total > 0) fetch(0);
     OwnPoint<G> own;
@@ -763,7 +803,7 @@ nattn_bwd_dq_patch(BandArgs a, const typename G::T *__restrict__ q, const typena
     ch.start(a, w, sh.rows);
     auto fetch = [&](int X0) {
         ch.set(X0, w, sh.rows);
-        at.set(w, w.rmin + ch.row, ch.col);
+        at.set(w, ch);
         rk.load(w, at, ks, nd);
         rv.load(w, at, vs, ne);
     };
@@ -775,11 +815,11 @@ nattn_bwd_dq_patch(BandArgs a, const typename G::T *__restrict__ q, const typena
     __syncthreads();
     f32x4 part = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < G::NP; ++j)
-        if (MODE != kRagged || at.cg + j * G::NG < ne) part += rv.value(j) * ro.value(j);
-    if (at.x < G::OWN) *reinterpret_cast<f32x4 *>(&sh.part[at.cg][4 * at.x]) = part;
-    rk.store(at, sh.a, nd);
-    rv.store(at, sh.b, ne);
+    for (int j = 0; j < G::NCO; ++j)
+        if (MODE != kRagged || w.tid / G::OWN + j * G::NGO < ne) part += rv.value(j) * ro.value(j);
+    *reinterpret_cast<f32x4 *>(&sh.part[w.tid / G::OWN][4 * (w.tid & (G::OWN - 1))]) = part;
+    rk.store_own(w, at, sh.a, nd);
+    rv.store_own(w, at, sh.b, ne);
     __syncthreads();
     if (w.total > 0) fetch(0);
     const int slot = w.own_slot(here_v(w.lane) & 3, G::NW), point = 4 * w.own_slot(here_v(w.lane) >> 2 & 3, G::NW) + (n & 3);
@@ -788,7 +828,7 @@ nattn_bwd_dq_patch(BandArgs a, const typename G::T *__restrict__ q, const typena
     og.read(sh.b + tr_at + 4 * slot);
     float dsum = 0.f;
 #pragma unroll
-    for (int i = g; i < G::NG; i += 4) dsum += sh.part[i][point];
+    for (int i = g; i < G::NGO; i += 4) dsum += sh.part[i][point];
     dsum = group_sum(dsum);
     if (w.active && g == 0) Dws[stat] = dsum;
     Sums<G> acc;
@@ -880,15 +920,21 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
     f32x4 rs = {0.f, 0.f, 0.f, 0.f};         // first threads: logsumexp or D of a chunk
     auto fetch = [&](int X0) {
         ch.set(X0, w, sh.rows);
-        at.set(w, w.rmin + ch.row, ch.col);
+        at.set(w, ch);
         rq.load(w, at, qs, nd);
         rg.load(w, at, gs, ne);
-        if (w.tid < 2 * G::CAP) rs = at.stat(w, at.cg ? Ds : ls);
+        if (w.wave < (2 * G::CAP + 63) / 64) {
+            int row, col;
+            ch.get(w.tid % G::CAP, row, col);
+            typename Place<G, MODE>::At from;
+            from.set(w, w.rmin + row, col, 0);
+            if (w.tid < 2 * G::CAP) rs = from.floats(w.tid < G::CAP ? ls : Ds);
+        }
     };
     const int tr_at = G::start(4 * g + (n >> 2)), row_at = G::start(n);
     __syncthreads();
-    rq.store(at, sh.a, nd);
-    rg.store(at, sh.b, ne);
+    rq.store_own(w, at, sh.a, nd);
+    rg.store_own(w, at, sh.b, ne);
     __syncthreads();
     if (w.total > 0) fetch(0);
     const int slot = w.own_slot(here_v(w.lane) & 3, G::NW);
@@ -904,8 +950,8 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
             rq.store(at, sh.a, nd);
             rg.store(at, sh.b, ne);
             if (w.tid < 2 * G::CAP) {
-                if (at.cg == 0) *reinterpret_cast<f32x4 *>(sh.L + 4 * at.x) = rs * -kLog2e;
-                else *reinterpret_cast<f32x4 *>(sh.D + 4 * at.x) = rs;
+                if (w.tid < G::CAP) *reinterpret_cast<f32x4 *>(sh.L + 4 * w.tid) = rs * -kLog2e;
+                else *reinterpret_cast<f32x4 *>(sh.D + 4 * (w.tid - G::CAP)) = rs;
             }
             __syncthreads();
             const int list = ch.list, first = ch.first, end = ch.first + ch.cnt, ntile = (ch.cnt + 3) >> 2;
@@ -976,13 +1022,22 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
 // wavefronts: forward 0.25 -> 0.24, dq 0.28 -> 0.26, dk/dv 0.34 -> 0.45 ms).  Odd
 // rows take more of them for addresses (128 x 254, 16 slices: dk/dv, float32 d = 16 held to four 0.235 ms, to three 0.217; bf16 d = 64 held to
 // three 0.515, to two 0.429; bf16 d = 32 to four 0.214, to three 0.220).
+// Stages of 24 chunks where that costs no workgroup, dk/dv of float32 d = 32: the four wavefronts of a workgroup meet more alike numbers of
+// whole tiles in a stage and wait less for each other, and there are a third fewer stages (129 x 256, 32 slices: 659 -> 633 us; at three
+// workgroups instead of four the forward would take 441 instead of 421, dq 521 instead of 498).  Owners that are classes of a finer
+// grid (classes) meet some 38 chunks: 24 + 14 of them make more odd tiles than 16 + 16 + 6 (257 x 512 -> 129 x 256, 8 slices: 329 -> 350).
 enum Launch { kFwd, kDq, kDkdv };
 template <class T, int MODE, Launch WHICH, class F>
-void by_shape(int dmax, F &&f)
+void by_shape(int dmax, bool classes, F &&f)
 {
     if constexpr (sizeof(T) == 4) {
         if (dmax <= 16) f(Geo<T, 16, 32, MODE == kWide && WHICH == kDkdv ? 4 : 3>());
-        else if (dmax <= 32) f(Geo<T, 32, 16, WHICH == kDq ? 4 : 3>());
+        else if (dmax <= 32) {
+            if constexpr (WHICH == kDkdv && MODE == kWide) {
+                if (!classes) return f(Geo<T, 32, 24, 3>());
+            }
+            f(Geo<T, 32, 16, WHICH == kDq ? 4 : 3>());
+        }
         else f(Geo<T, 64, 16, 2>());
     } else {
         if (dmax <= 16) f(Geo<T, 16, 64, 4>());
@@ -1009,9 +1064,10 @@ int PatchKernels<T, MODE>::configure()
 {
     bool bad = false;
     for (int d : {16, 32, 64}) {
-        by_shape<T, MODE, kFwd>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_fwd_patch<decltype(g), MODE>), sizeof(Shared<decltype(g)>)); });
-        by_shape<T, MODE, kDq>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dq_patch<decltype(g), MODE>), sizeof(SharedDq<decltype(g)>)); });
-        by_shape<T, MODE, kDkdv>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dkdv_patch<decltype(g), MODE>), sizeof(SharedDkdv<decltype(g)>)); });
+        by_shape<T, MODE, kFwd>(d, false, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_fwd_patch<decltype(g), MODE>), sizeof(Shared<decltype(g)>)); });
+        by_shape<T, MODE, kDq>(d, false, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dq_patch<decltype(g), MODE>), sizeof(SharedDq<decltype(g)>)); });
+        for (bool classes : {false, true})
+            by_shape<T, MODE, kDkdv>(d, classes, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dkdv_patch<decltype(g), MODE>), sizeof(SharedDkdv<decltype(g)>)); });
     }
     return bad;
 }
@@ -1020,7 +1076,7 @@ void PatchKernels<T, MODE>::fwd(const S2DeviceTables &t, int nbh, int d, int e, 
                                 hipStream_t st)
 {
     const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale);
-    by_shape<T, MODE, kFwd>(d > e ? d : e, [&](auto g) {
+    by_shape<T, MODE, kFwd>(d > e ? d : e, l.a.b.c_own > 1, [&](auto g) {
         using G = decltype(g);
         hipLaunchKernelGGL((nattn_fwd_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(Shared<G>), st, l.a, q, k, v, out, lse);
     });
@@ -1030,7 +1086,7 @@ void PatchKernels<T, MODE>::dq(const S2DeviceTables &t, int nbh, int d, int e, f
                                const float *lse, const T *go, T *dq, float *Dws, hipStream_t st)
 {
     const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale);
-    by_shape<T, MODE, kDq>(d > e ? d : e, [&](auto g) {
+    by_shape<T, MODE, kDq>(d > e ? d : e, l.a.b.c_own > 1, [&](auto g) {
         using G = decltype(g);
         hipLaunchKernelGGL((nattn_bwd_dq_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(SharedDq<G>), st, l.a, q, k, v, o, lse, go, dq, Dws);
     });
@@ -1040,7 +1096,7 @@ void PatchKernels<T, MODE>::dkdv(const S2DeviceTables &t, int nbh, int d, int e,
                                  const T *go, const float *Dws, T *dk, T *dv, hipStream_t st)
 {
     const PatchLaunch l = patch_launch(t, t.side_in, nbh, d, e, scale);
-    by_shape<T, MODE, kDkdv>(d > e ? d : e, [&](auto g) {
+    by_shape<T, MODE, kDkdv>(d > e ? d : e, l.a.b.c_own > 1, [&](auto g) {
         using G = decltype(g);
         hipLaunchKernelGGL((nattn_bwd_dkdv_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(SharedDkdv<G>), st, l.a, q, k, v, lse, go, Dws, dk, dv);
     });
