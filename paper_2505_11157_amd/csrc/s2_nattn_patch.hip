@@ -5,8 +5,8 @@
 // the matrix-core kernels for any grid pair, of both element types
 int s2_nattn_band_configure()
 {
-    return PatchSet<kWide>::configure() || PatchSet<kNarrow>::configure() || PatchSet<kRagged>::configure() || PatchSet16<kWide>::configure() ||
-           PatchSet16<kNarrow>::configure() || PatchSet16<kRagged>::configure();
+    return PatchSet<kWide>::configure() || PatchSet<kNarrow>::configure() || PatchSet<kRagged>::configure() || PatchSet<kPairs>::configure() ||
+           PatchSet16<kWide>::configure() || PatchSet16<kNarrow>::configure() || PatchSet16<kRagged>::configure() || PatchSet16<kPairs>::configure();
 }
 
 bool s2_nattn_patch_supported(const S2DeviceTables &t, int d, int e)

@@ -41,6 +41,10 @@
 // of one row; d = 32 on 64 n longitudes: kernels that rounded the forward's probabilities to bf16:
 //   d = 16  0.29 / 0.34 / 0.41 -> 0.19 / 0.21 / 0.26        d = 32  0.28 / 0.35 / 0.51 -> 0.24 / 0.26 / 0.34
 //   d = 64  0.83 / 1.17 / 1.12 -> 0.41 / 0.47 / 0.56
+//
+// Owners that are the two classes of a finer grid are loaded and stored by latitudes (kPairs), four columns at a time, two of either class;
+// an owner row alone is every second column of its latitude (129 x 256 -> 257 x 512, 8 slices, float32 d = 32: dq 0.268 -> 0.239 ms, the
+// mirror image's dk, dv 0.341 -> 0.316; 65 x 128 -> 129 x 256, 8 slices, bf16 d = 64: forward 72 -> 58 us, backward 171 -> 141).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -194,7 +198,7 @@ struct PatchWhere {
     }
     // do four points of an owner row lie side by side; kWide: at a multiple of four, in rows of a multiple of four
     template <int MODE>
-    __device__ __forceinline__ bool own_pieces() const { return c_own == 1 && (MODE == kWide ? nU % 4 == 0 : nU >= 4); }
+    __device__ __forceinline__ bool own_pieces() const { return c_own == 1 && (is_wide(MODE) ? nU % 4 == 0 : nU >= 4); }
     // row r of the patch tables
     __device__ __forceinline__ size_t row_walked(int r) const { return stride == 1 ? size_t(r) * nlon_walk : walk_at(r); }
     // the chunk of the workgroup's own points that holds the points 4 j .. 4 j + 3 of this wavefront
@@ -296,7 +300,7 @@ struct Chunks {
 // Where a chunk is, in a channel plane (kWide: in a slice)
 template <class T, int MODE>
 struct ChunkAt {
-    static constexpr bool WIDE = MODE == kWide;
+    static constexpr bool WIDE = is_wide(MODE);
     unsigned off[WIDE ? 1 : 4];      // kWide: byte offset; else elements
     bool apart;                      // not kWide: a chunk of the wavefront's is not four elements side by side (uniform; else off[0] only)
     // channel: its first one (kWide only)
@@ -314,12 +318,12 @@ struct ChunkAt {
             for (int i = 1; i < 4; ++i) off[i] = at + unsigned(w.stride) * unsigned(wrap_col(col + i + 2 * w.nW, w.nW, w.inv_nW));
         }
     }
-    // its values in a float32 plane
-    __device__ __forceinline__ f32x4 floats(const float *plane) const
+    // its values in a float32 plane; channel: as set
+    __device__ __forceinline__ f32x4 floats(const PatchWhere &w, const float *plane, int channel) const
     {
         f32x4 s;
         if constexpr (WIDE) {
-            s = load_at<f32x4>(plane, off[0] / unsigned(sizeof(T)) * 4u);
+            s = load_at<f32x4>(plane, off[0] / unsigned(sizeof(T)) * 4u - 4u * unsigned(channel) * unsigned(w.plane_walk));
         } else if (!apart) {
             __builtin_memcpy(&s, plane + off[0], sizeof s);
         } else {
@@ -349,6 +353,20 @@ struct Place {
             ch.get(x + G::XL * j, row, col);
             at[j].set(w, w.rmin + row, col, cg);
         }
+    }
+};
+// kPairs: the thread's piece of the workgroup's own points, four columns of a latitude of the finer grid, two of either class
+struct PairPiece {
+    int row, col;                    // the first class's row; the first column
+    int at, up;                      // place of the first class's two points among the own points' columns in LDS, from there to the other's
+    template <class G>
+    __device__ __forceinline__ void set(const PatchWhere &w, int tid)
+    {
+        const int lg = here_s(w.lg), x = tid & (G::OWN - 1), lat = x >> (5 - lg), i = x & ((32 >> lg) - 1);
+        row = w.first + 2 * lat;
+        col = 2 * w.W0 + 4 * i;
+        up = 4 * G::NW << (2 - lg);
+        at = 2 * lat * up + 2 * i;
     }
 };
 template <class G, int MODE>
@@ -388,6 +406,17 @@ struct Stage {
     // the workgroup's own points; vec: its rows are contiguous
     __device__ __forceinline__ void load_own(const PatchWhere &w, const T *slice, int nch, bool vec)
     {
+        if constexpr (MODE == kPairs) {
+            if (w.lg > 0) {
+                const int tid = here_v(w.tid);
+                PairPiece o;
+                o.template set<G>(w, tid);
+                const T *p = slice + size_t(tid / G::OWN) * w.plane_own + w.row_at(o.row < w.n_own ? o.row : w.first) + (o.col < 2 * w.nU ? o.col : 0);
+#pragma unroll
+                for (int j = 0; j < G::NCO; ++j) r[j] = *reinterpret_cast<const Piece *>(p + size_t(j * G::NGO) * w.plane_own);
+                return;
+            }
+        }
         const int h = 2 - here_s(w.lg), tid = here_v(w.tid), x = tid & (G::OWN - 1), cg = tid / G::OWN, sub = (x / G::NW) >> h;
         const int row = w.first + sub < w.n_own ? w.first + sub : w.first, u = w.W0 + 4 * (x - G::NW * (sub << h));
         const T *p = slice + w.row_at(row);
@@ -450,8 +479,46 @@ struct Stage {
     __device__ __forceinline__ void store_own(const PatchWhere &w, const P &place, __bf16 *tile, int nch) const
     {
         const int tid = here_v(w.tid), x = G::XL == G::OWN ? place.x : tid & (G::OWN - 1), cg = G::XL == G::OWN ? place.cg : tid / G::OWN;
+        if constexpr (MODE == kPairs) {
+            if (w.lg > 0) {
+                PairPiece o;
+                o.template set<G>(w, tid);
+#pragma unroll
+                for (int j = 0; j < G::NCO; ++j) {
+                    __bf16 *p = tile + G::start(cg + j * G::NGO) + o.at;
+                    if constexpr (sizeof(T) == 4) {
+                        float x0 = r[j][0], x1 = r[j][2], y0 = r[j][1], y1 = r[j][3];
+#pragma unroll
+                        for (int k = 0; k < kTerms; ++k) {
+                            *reinterpret_cast<unsigned *>(p + k * G::TERM) = cut_off(x0, x1);
+                            *reinterpret_cast<unsigned *>(p + k * G::TERM + o.up) = cut_off(y0, y1);
+                        }
+                    } else {
+                        *reinterpret_cast<unsigned *>(p) = unsigned(r[j][0]) | unsigned(r[j][2]) << 16;
+                        *reinterpret_cast<unsigned *>(p + o.up) = unsigned(r[j][1]) | unsigned(r[j][3]) << 16;
+                    }
+                }
+                return;
+            }
+        }
 #pragma unroll
         for (int j = 0; j < G::NCO; ++j) put(tile, cg + j * G::NGO, x, r[j], nch);
+    }
+    // the thread's four values of its own points' columns, each lane's kept in `to`, one row of G::PITCH floats
+    static __device__ __forceinline__ void put_floats(const PatchWhere &w, float *to, f32x4 v)
+    {
+        const int tid = here_v(w.tid);
+        if constexpr (MODE == kPairs) {
+            if (w.lg > 0) {
+                PairPiece o;
+                o.template set<G>(w, tid);
+                typedef float f32x2 __attribute__((ext_vector_type(2)));
+                *reinterpret_cast<f32x2 *>(to + o.at) = f32x2{v[0], v[2]};
+                *reinterpret_cast<f32x2 *>(to + o.at + o.up) = f32x2{v[1], v[3]};
+                return;
+            }
+        }
+        *reinterpret_cast<f32x4 *>(to + 4 * (tid & (G::OWN - 1))) = v;
     }
 };
 
@@ -622,29 +689,45 @@ __device__ __forceinline__ bool marked(const float *tile, const PatchWhere &w, i
 template <class G, int MODE>
 __device__ __forceinline__ void store_results(typename G::T *slice, int nch, const float *tile, const PatchWhere &w, bool vec)
 {
-    const int h = 2 - here_s(w.lg), tid = here_v(w.tid), x = tid % G::OWN, c0 = tid / G::OWN, sub = (x / G::NW) >> h, u = w.W0 + 4 * (x - G::NW * (sub << h));
-    if (w.first + sub >= w.n_own || u >= w.nU) return;
     using T = typename G::T;
-    T *p = slice + size_t(c0) * w.plane_own + w.row_at(w.first + sub) + size_t(w.c_own) * u;
+    const int h = 2 - here_s(w.lg), tid = here_v(w.tid), x = tid % G::OWN, c0 = tid / G::OWN;
+    int sub = (x / G::NW) >> h, u = w.W0 + 4 * (x - G::NW * (sub << h)), end = w.nU, step = w.c_own;
+    const bool two = MODE == kPairs && w.lg > 0;
+    PairPiece o;
+    if (two) {
+        o.template set<G>(w, tid);
+        sub = o.row - w.first;
+        u = o.col;
+        end = 2 * w.nU;
+        step = 1;
+    }
+    if (w.first + sub >= w.n_own || u >= end) return;
+    T *p = slice + size_t(c0) * w.plane_own + w.row_at(w.first + sub) + size_t(step) * u;
     const size_t up = size_t(G::NT / G::OWN) * w.plane_own;
 #pragma unroll
     for (int j = 0; j < G::D * G::OWN / G::NT; ++j, p += up) {
         const int c = c0 + j * (G::NT / G::OWN);
         if (c >= nch) break;
-        const u32x4 r = *reinterpret_cast<const u32x4 *>(tile + c * G::PITCH + 4 * x);
+        u32x4 r;
+        if (two) {
+            const u32x2 a = *reinterpret_cast<const u32x2 *>(tile + c * G::PITCH + o.at), b = *reinterpret_cast<const u32x2 *>(tile + c * G::PITCH + o.at + o.up);
+            r = u32x4{a[0], b[0], a[1], b[1]};
+        } else {
+            r = *reinterpret_cast<const u32x4 *>(tile + c * G::PITCH + 4 * x);
+        }
         unsigned skip = 0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) skip |= (r[k] == kAgain || u + k >= w.nU ? 1u : 0u) << k;
+        for (int k = 0; k < 4; ++k) skip |= (r[k] == kAgain || u + k >= end ? 1u : 0u) << k;
         typename Stage<G, kWide>::Piece y;
         if constexpr (sizeof(T) == 4) y = __builtin_bit_cast(f32x4, r);
         else y = __builtin_bit_cast(u16x4, __builtin_convertvector(__builtin_bit_cast(f32x4, r), bf16x4));
-        if (vec && skip == 0) {
-            if constexpr (MODE == kWide) *reinterpret_cast<decltype(y) *>(p) = y;
+        if ((vec || two) && skip == 0) {
+            if constexpr (is_wide(MODE)) *reinterpret_cast<decltype(y) *>(p) = y;
             else __builtin_memcpy(p, &y, sizeof y);
         } else {
             T *pk = p;
 #pragma unroll
-            for (int k = 0; k < 4; ++k, pk += w.c_own)
+            for (int k = 0; k < 4; ++k, pk += step)
                 if (!(skip >> k & 1)) *pk = y[k];
         }
     }
@@ -817,7 +900,7 @@ nattn_bwd_dq_patch(BandArgs a, const typename G::T *__restrict__ q, const typena
 #pragma unroll
     for (int j = 0; j < G::NCO; ++j)
         if (MODE != kRagged || w.tid / G::OWN + j * G::NGO < ne) part += rv.value(j) * ro.value(j);
-    *reinterpret_cast<f32x4 *>(&sh.part[w.tid / G::OWN][4 * (w.tid & (G::OWN - 1))]) = part;
+    Stage<G, MODE>::put_floats(w, sh.part[w.tid / G::OWN], part);
     rk.store_own(w, at, sh.a, nd);
     rv.store_own(w, at, sh.b, ne);
     __syncthreads();
@@ -923,12 +1006,14 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
         at.set(w, ch);
         rq.load(w, at, qs, nd);
         rg.load(w, at, gs, ne);
-        if (w.wave < (2 * G::CAP + 63) / 64) {
+        if constexpr (G::CJ == 1) {
+            if (w.tid < 2 * G::CAP) rs = at.at[0].floats(w, at.cg ? Ds : ls, at.cg);
+        } else if (w.wave < (2 * G::CAP + 63) / 64) {
             int row, col;
             ch.get(w.tid % G::CAP, row, col);
             typename Place<G, MODE>::At from;
             from.set(w, w.rmin + row, col, 0);
-            if (w.tid < 2 * G::CAP) rs = from.floats(w.tid < G::CAP ? ls : Ds);
+            if (w.tid < 2 * G::CAP) rs = from.floats(w, w.tid < G::CAP ? ls : Ds, 0);
         }
     };
     const int tr_at = G::start(4 * g + (n >> 2)), row_at = G::start(n);
@@ -1031,7 +1116,7 @@ template <class T, int MODE, Launch WHICH, class F>
 void by_shape(int dmax, bool classes, F &&f)
 {
     if constexpr (sizeof(T) == 4) {
-        if (dmax <= 16) f(Geo<T, 16, 32, MODE == kWide && WHICH == kDkdv ? 4 : 3>());
+        if (dmax <= 16) f(Geo<T, 16, 32, is_wide(MODE) && WHICH == kDkdv ? 4 : 3>());
         else if (dmax <= 32) {
             if constexpr (WHICH == kDkdv && MODE == kWide) {
                 if (!classes) return f(Geo<T, 32, 24, 3>());
@@ -1041,8 +1126,8 @@ void by_shape(int dmax, bool classes, F &&f)
         else f(Geo<T, 64, 16, 2>());
     } else {
         if (dmax <= 16) f(Geo<T, 16, 64, 4>());
-        else if (dmax <= 32) f(Geo<T, 32, 32, MODE == kWide && WHICH != kDkdv ? 5 : 4>());
-        else f(Geo<T, 64, 32, MODE != kWide && WHICH == kDkdv ? 2 : 3>());
+        else if (dmax <= 32) f(Geo<T, 32, 32, is_wide(MODE) && WHICH != kDkdv ? 5 : 4>());
+        else f(Geo<T, 64, 32, !is_wide(MODE) && WHICH == kDkdv ? 2 : 3>());
     }
 }
 struct PatchLaunch {
