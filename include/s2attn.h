@@ -305,8 +305,8 @@ int s2_grid_device_flags(const s2_grid_t *g, unsigned *flags);
  *   S2_DEBUG_NO_ROW_GROUPS  no effect: the kernels that it steered are gone
  *   S2_DEBUG_FAIL_LAUNCH    the launchers of the tuned neighborhood kernels report failure before launching
  *                           anything: s2_nattn_fwd / s2_nattn_bwd then return S2_ERR_DEVICE
- *   S2_DEBUG_FORCE_BAND     the forward of float32 tensors with d = e = 32 on upsampling grids runs on the matrix-core patches too,
- *                           like every other pair of widths up to 64 (by default on the split vector kernel)
+ *   S2_DEBUG_FORCE_BAND     the forward of float32 tensors with d = e = 32 on upsampling grids runs on patches of neighboring columns
+ *                           too, like every other pair of widths up to 64 (by default a wavefront's points lie on one column)
  *   S2_DEBUG_NO_BAND        the matrix-core patches are never used, on float32 or bf16 tensors: the kernels of longer circles take
  *                           their place (float32 with d = e = 32: streaming and split vector kernels, else shape-agnostic ones)
  */

@@ -384,6 +384,67 @@ static void build_patches(const std::vector<int> &blo, const std::vector<int> &b
     }
 }
 
+// Segments and workgroups of the forward by columns (S2ColumnRow).
+static void build_columns(const std::vector<int> &blo, const std::vector<int> &bn, const std::vector<int2> &arc, int nU, const float *omega,
+                          s2_grid::Columns &p)
+{
+    const int n_own = int(blo.size()), bmax = int(arc.size() / blo.size());
+    constexpr int kMost = (kS2ColumnStage - (kS2PatchWaves - 1)) & ~3;      // chunks of a piece, whole tiles; three more for the last wavefront's column
+    std::vector<int> seg_of;
+    for (int f = 0; f < n_own; f += 16) {
+        const int l = std::min(f + 16, n_own);
+        int rmin = 1 << 30, rmax = -1;
+        for (int v = f; v < l; ++v)
+            if (bn[v] > 0) {
+                rmin = std::min(rmin, blo[v]);
+                rmax = std::max(rmax, blo[v] + bn[v] - 1);
+            }
+        seg_of.push_back(int(p.seg.size() / 2));
+        int before = 0, at = int(p.rows.size());
+        auto close = [&](int more) {
+            p.seg.push_back(make_int4(f, 4, 0, int(p.rows.size()) - at));
+            p.seg.push_back(make_int4(before, at, more, 0));
+            before = 0;
+            at = int(p.rows.size());
+        };
+        for (int row = rmin; row <= rmax; ++row) {
+            S2ColumnRow o{};
+            o.row = row;
+            o.omega = omega[row];
+            int lo = 1 << 30, hi = -(1 << 30);
+            for (int v = f; v < l; ++v) {
+                const int i = row - blo[v];
+                if (i < 0 || i >= bn[v]) continue;
+                int2 a = arc[size_t(v) * bmax + i];
+                if (a.y <= 0) continue;
+                if (a.y >= nU) a = make_int2(-(nU / 2), nU);
+                o.arc[v - f] = unsigned(a.x & 0xffff) | unsigned(a.y) << 16;
+                lo = std::min(lo, a.x);
+                hi = std::max(hi, a.x + a.y - 1);
+            }
+            if (lo > hi) continue;
+            for (int left = (hi - lo) / 4 + 1; left > 0; left -= kMost, lo += 4 * kMost) {
+                if (int(p.rows.size()) - at == kS2ColumnRows) close(1);
+                const int n = std::min(left, kMost), window = n + kS2PatchWaves - 1;
+                if (before % kS2ColumnStage + window > kS2ColumnStage) before += kS2ColumnStage - before % kS2ColumnStage;
+                o.col = lo - 4 * before;
+                o.uni = int(unsigned(lo & 0xffff) | unsigned(4 * n) << 16);
+                o.before = before;
+                p.rows.push_back(o);
+                before += window;
+            }
+        }
+        close(0);
+    }
+    seg_of.push_back(int(p.seg.size() / 2));
+    const int nseg = int(seg_of.size()) - 1;
+    for (int k = 0; k < nseg; ++k) {
+        const int s = (k & 1) ? nseg - 1 - (k >> 1) : k >> 1;                          // the polar rows are the heaviest
+        for (int c = 0; c < nU; c += 4 * kS2PatchWaves)
+            for (int u = c; u < std::min(c + 4, nU); ++u) p.list.push_back(make_int2(seg_of[s], u));
+    }
+}
+
 static int upload_tables(s2_grid *g)
 {
     int ndev = 0;
@@ -447,6 +508,9 @@ static int upload_tables(s2_grid *g)
         parts.push_back({p->rows.data(), p->rows.size() * sizeof(S2PatchRow), 0});
         parts.push_back({p->list.data(), p->list.size() * sizeof(int2), 0});
     }
+    parts.push_back({g->columns.seg.data(), g->columns.seg.size() * sizeof(int4), 0});
+    parts.push_back({g->columns.rows.data(), g->columns.rows.size() * sizeof(S2ColumnRow), 0});
+    parts.push_back({g->columns.list.data(), g->columns.list.size() * sizeof(int2), 0});
     size_t total = 0;
     for (auto &p : parts) {
         p.off = total;
@@ -500,6 +564,8 @@ static int upload_tables(s2_grid *g)
         q.npatch = int(p.list.size());
         q.step = p.step;
     }
+    t.columns = {reinterpret_cast<const int4 *>(base + parts[27].off), reinterpret_cast<const int4 *>(base + parts[28].off), ap(29),
+                 int(g->columns.list.size()), 1};
     g->on_device = true;
     return S2_OK;
 }
@@ -822,6 +888,7 @@ extern "C" int s2_grid_init(int grid_type, int nlat_in, int nlon_in, int nlat_ou
             }
             build_patches(lo, n, arc, nU, w, c, 1, p);
         }
+        if (g->upscale > 1 && nU % 4 == 0 && nU >= 72) build_columns(g->vo_lo, g->vo_n, g->vo_arc, nU, omega.data(), g->columns);
     }
     int rc = upload_tables(g);
     if (rc != S2_OK) { delete g; return rc; }

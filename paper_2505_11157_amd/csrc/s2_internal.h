@@ -47,6 +47,18 @@ struct S2PatchRow {
     unsigned arc[4];          // per owner row: first offset (16 bits), length (16 bits)
 };
 
+// Walked rows as 16 owner rows of one column see them, for owners that are the classes of a finer grid: the four wavefronts of a workgroup
+// own columns four apart.  A row is walked in pieces that a stage holds, from a column that is counted from the owner's, and stages hold
+// whole pieces: every owner's sums run in the order of its own offsets, whatever its column.
+constexpr int kS2ColumnRows = 64, kS2ColumnStage = 16;
+struct S2ColumnRow {
+    int col, uni, before;     // as in S2PatchRow; the piece alone, for the first wavefront
+    int row;                  // the walked row
+    float omega;
+    int unused[3];
+    unsigned arc[16];
+};
+
 struct S2DeviceTables {
     const float *omega_rel;   // [nlat_in]   omega[h'] / max omega
     const int *band_lo;       // [nlat_out]
@@ -74,6 +86,7 @@ struct S2DeviceTables {
     int st_lo, st_hi, st_nw;
     int tst_lo, tst_hi, tst_nw;
     S2BandSide side_out, side_in;       // owners = output points, owners = input points
+    S2BandSide::Patches columns;        // side_out by columns (upsampling grids; else no workgroups)
     // the patch kernels apply: nU < 2^15
     int band_rows_ok;
     unsigned *dev_flags;      // one word in device memory: bit 0 = a bounded wait inside a kernel ran out
@@ -106,6 +119,11 @@ struct s2_grid {
         std::vector<int2> list;
         int step = 1;
     } vo_patch, vi_patch;
+    struct Columns {
+        std::vector<int4> seg;
+        std::vector<S2ColumnRow> rows;
+        std::vector<int2> list;
+    } columns;
     int band_max = 0, tband_max = 0;
     // the band and arc tables exactly as eq. (5) gives them (introspection); the tables above, which the kernels
     // use, leave out input latitudes of weight zero (listed in zero_lat)

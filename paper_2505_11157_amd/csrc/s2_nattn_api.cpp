@@ -21,7 +21,7 @@ int check_common(const s2_grid_t *g, int batch, int heads, int d_qk, int d_v, in
 int slices_at_once(const s2_grid_t *g)
 {
     const long lat = std::max(g->nlat_in, g->nlat_out), lon = std::min(g->nlon_in, g->nlon_out), classes = std::max(g->pscale, g->upscale);
-    const long threads = std::max(512 * lat * classes * ((lon + 63) / 64), 256l * std::max(g->dt.side_out.patches.npatch, g->dt.side_in.patches.npatch));
+    const long threads = std::max(512 * lat * classes * ((lon + 63) / 64), 256l * std::max({g->dt.side_out.patches.npatch, g->dt.side_in.patches.npatch, g->dt.columns.npatch}));
     return int(std::clamp(((1l << 32) - 1) / threads, 1l, 1l << 20));
 }
 size_t points_out(const s2_grid_t *g) { return size_t(g->nlat_out) * g->nlon_out; }
@@ -42,18 +42,10 @@ extern "C" size_t s2_nattn_bwd_workspace_bytes(const s2_grid_t *g, int batch, in
     return size_t(batch) * heads * g->nlat_out * g->nlon_out * sizeof(float);
 }
 
-// The patch kernels take everything up to 64 channels whose walked rows fit their tables, except the float32 forward of
-// d = e = 32 on upsampling grids: rolled in longitude, its results are the same bit for bit, which holds on the split vector
-// kernel (sums in the order of the offsets) and not on tiles at fixed columns (129 x 256 -> 257 x 512, 8 slices: 518 us there, 200
-// on the patches).
+// The patch kernels take everything up to 64 channels whose walked rows fit their tables.
 static bool use_patch(const S2DeviceTables &t, int d, int e)
 {
     return s2_nattn_patch_supported(t, d, e) && !s2_debug_flag(S2_DEBUG_NO_BAND);
-}
-static bool use_patch_fwd(const S2DeviceTables &t, int d, int e)
-{
-    const bool rolls = t.upscale > 1 && s2_nattn_fwd_tiled_supported(t, d, e) && !s2_debug_flag(S2_DEBUG_FORCE_BAND);
-    return use_patch(t, d, e) && !rolls;
 }
 
 extern "C" int s2_nattn_fwd(const s2_grid_t *g, int batch, int heads, int d_qk, int d_v, int dtype, float scale,
@@ -77,7 +69,7 @@ extern "C" int s2_nattn_fwd(const s2_grid_t *g, int batch, int heads, int d_qk, 
             auto *fwd16 = use_patch(g->dt, d_qk, d_v) ? s2_nattn_fwd_patch_bf16 : s2_nattn_fwd_generic_bf16;
             failed = fwd16(g->dt, n, d_qk, d_v, scale, qb, kb, vb, ob, lb, st);
         } else {
-            auto *fwd = use_patch_fwd(g->dt, d_qk, d_v)                  ? s2_nattn_fwd_patch
+            auto *fwd = use_patch(g->dt, d_qk, d_v)                      ? s2_nattn_fwd_patch
                         : s2_nattn_fwd_tiled_supported(g->dt, d_qk, d_v) ? s2_nattn_fwd_tiled
                                                                          : s2_nattn_fwd_generic;
             failed = fwd(g->dt, n, d_qk, d_v, scale, static_cast<const float *>(qb), static_cast<const float *>(kb),

@@ -7,7 +7,8 @@
 // or its columns lie apart (classes of a finer grid); kRagged, kNarrow with channel counts that are not the kernel's.
 // kPairs: kWide, where the owners are the two classes of a grid of twice the longitudes (an even number a class), so that four columns of a
 // latitude are two owners of either.
-enum { kWide, kNarrow, kRagged, kPairs };
+// kColumns: kNarrow, where a wavefront owns 16 rows of one column (S2ColumnRow).
+enum { kWide, kNarrow, kRagged, kPairs, kColumns };
 constexpr bool is_wide(int mode) { return mode == kWide || mode == kPairs; }
 inline int s2_band_mode(const S2BandSide &b, int d, int e, size_t element)
 {

@@ -17,3 +17,8 @@ template <int MODE>
 using PatchSet = PatchKernels<float, MODE>;
 template <int MODE>
 using PatchSet16 = PatchKernels<unsigned short, MODE>;      // bf16 tensors
+
+// The forward by columns (S2ColumnRow), float32 d = e = 32
+int s2_nattn_columns_configure();
+void s2_nattn_fwd_columns(const S2DeviceTables &t, int nbh, float scale, const float *q, const float *k, const float *v, float *out, float *lse,
+                          hipStream_t st);

@@ -6,7 +6,8 @@
 int s2_nattn_band_configure()
 {
     return PatchSet<kWide>::configure() || PatchSet<kNarrow>::configure() || PatchSet<kRagged>::configure() || PatchSet<kPairs>::configure() ||
-           PatchSet16<kWide>::configure() || PatchSet16<kNarrow>::configure() || PatchSet16<kRagged>::configure() || PatchSet16<kPairs>::configure();
+           PatchSet16<kWide>::configure() || PatchSet16<kNarrow>::configure() || PatchSet16<kRagged>::configure() || PatchSet16<kPairs>::configure() ||
+           s2_nattn_columns_configure();
 }
 
 bool s2_nattn_patch_supported(const S2DeviceTables &t, int d, int e)
@@ -21,6 +22,10 @@ int s2_nattn_fwd_patch(const S2DeviceTables &t, int nbh, int d, int e, float sca
 {
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
     S2TraceScope tr("nattn_fwd_patch", pair_count(t.fwd_pairs, nbh), st);
+    if (d == 32 && e == 32 && t.columns.npatch > 0 && !s2_debug_flag(S2_DEBUG_FORCE_BAND)) {
+        s2_nattn_fwd_columns(t, nbh, scale, q, k, v, out, lse, st);
+        return 0;
+    }
     s2_by_band_mode<PatchSet>(s2_band_mode(t.side_out, d, e, sizeof(float)), [&](auto set) { set.fwd(t, nbh, d, e, scale, q, k, v, out, lse, st); });
     return 0;
 }

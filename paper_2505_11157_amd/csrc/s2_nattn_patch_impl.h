@@ -21,6 +21,13 @@
 // 0.329, dq 0.347 ms, now 0.175 and 0.197; the mirror image's dk/dv 0.397, now 0.258).  Where a latitude's classes make no single
 // arc, or 16 bits do not hold its columns, the rows stay classes (step 1).
 //
+// Columns (kColumns).  A chunk begins at a fixed column, so that the order of a point's sums depends on where its column lies.  The
+// float32 forward of d = e = 32 on upsampling grids has results that roll with its inputs bit for bit; there a wavefront owns 16 rows
+// of one column, those of a workgroup lie four columns apart, chunks begin at columns counted from the owner's, and stages hold whole
+// rows, or pieces of long rows, of all four (S2ColumnRow): every owner meets its tiles in the same order.  129 x 256 -> 257 x 512, 8 slices:
+// vector kernels 514 us, by columns 341 (10 tiles in 5.0 stages a wavefront; patches 6.4 in 2.7 and 200 us, as near the poles 16 rows have little in
+// common); 46 x 92 -> 92 x 184 with the sphere for a disk 2591 -> 336.  At three workgroups a compute unit, with no spilled register, 365.
+//
 // LDS holds a stage as [term][channel][chunk]: channel rows as in memory.  First products (S^T = K Q^T and dP) read it through
 // ds_read_b64_tr_b16, which turns 4 channels x 16 keys on the way to the registers; in the second (O^T += V P^T) the 8 contraction
 // indices of a lane are its four keys of each of two tiles, 8-byte reads.  start(c) and UNITS (an odd multiple of four) spread both
@@ -66,7 +73,6 @@ typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
 
 typedef unsigned short bf16raw;      // storage of a bf16 tensor
-constexpr int kDead = kMaxRows;      // the row of a list entry that stands for no chunk: no owner has neighbors on it
 constexpr unsigned kAgain = 0x7fc0a9a1u;     // in place of a result that s2_nattn_exact.h evaluates: not to be stored
 
 // Channels, chunks per stage, wavefronts per SIMD the registers are held to.
@@ -92,23 +98,27 @@ struct Geo {
     static constexpr int UP = 16 * ROW + 4;                 // from a channel to the one 16 later
 };
 
-// A workgroup's rows in LDS (S2PatchRow).
+// A workgroup's rows in LDS (S2PatchRow, kColumns: S2ColumnRow).
+template <int MODE>
 struct RowTab {
-    int col[kMaxRows + 1], uni[kMaxRows + 1], before[kMaxRows];
-    uint2 arc[4][kMaxRows + 1];      // arc and the row's weight
+    static constexpr bool COLUMNS = MODE == kColumns;
+    static constexpr int ROWS = COLUMNS ? kS2ColumnRows : kMaxRows, SUBS = COLUMNS ? 16 : 4;
+    static constexpr int DEAD = ROWS;     // the row of a list entry that stands for no chunk: no owner has neighbors on it
+    int col[ROWS + 1], uni[ROWS + 1], before[ROWS], row[COLUMNS ? ROWS + 1 : 1];
+    uint2 arc[SUBS][ROWS + 1];       // arc and the row's weight
 };
-template <class G>
+template <class G, int MODE>
 struct Shared {
     __attribute__((aligned(16))) __bf16 a[G::TENSOR];
     __attribute__((aligned(16))) __bf16 b[G::TENSOR];
-    RowTab rows;
+    RowTab<MODE> rows;
 };
-template <class G>
-struct SharedDq : Shared<G> {
+template <class G, int MODE>
+struct SharedDq : Shared<G, MODE> {
     float part[G::NGO][G::PITCH];    // partial sums of D
 };
-template <class G>
-struct SharedDkdv : Shared<G> {
+template <class G, int MODE>
+struct SharedDkdv : Shared<G, MODE> {
     __attribute__((aligned(16))) float L[4 * G::CAP];
     __attribute__((aligned(16))) float D[4 * G::CAP];
 };
@@ -185,7 +195,7 @@ struct PatchWhere {
         const bool row_ok = first + sub < n_own;
         set_row(row_ok ? first + sub : first);
         W0 = at.y;
-        wc = W0 + wave * W;
+        wc = W0 + wave * (W > 4 ? W : 4);
         u = wc + (n & (W - 1));
         su = step * u;
         active = row_ok && u < nU;
@@ -202,8 +212,10 @@ struct PatchWhere {
     // row r of the patch tables
     __device__ __forceinline__ size_t row_walked(int r) const { return stride == 1 ? size_t(r) * nlon_walk : walk_at(r); }
     // the chunk of the workgroup's own points that holds the points 4 j .. 4 j + 3 of this wavefront
+    template <int MODE>
     __device__ __forceinline__ int own_slot(int j, int nw) const
     {
+        if (MODE == kColumns) return 4 * wave + j;
         const int h = 2 - here_s(lg);    // log2(chunks per row of a wavefront)
         return (j >> h) * (nw << h) + (wave << h) + (j & ((1 << h) - 1));
     }
@@ -220,8 +232,9 @@ struct PatchWhere {
     }
 };
 // The chunks of a workgroup: looked up LOOK at a time, one per lane, and staged CAP at a time.
-template <class G>
+template <class G, int MODE>
 struct Chunks {
+    using Tab = RowTab<MODE>;
     int P_v[2];                      // chunks before row lane, 64 + lane
     int r;
     int entry;                       // of those looked up last: the lane's chunk, its column, row and place in its stage
@@ -232,33 +245,40 @@ struct Chunks {
 
     __device__ __forceinline__ int before(int i) const
     {
+        if (Tab::ROWS <= 64) return __builtin_amdgcn_readlane(P_v[0], i);
         const int x = __builtin_amdgcn_readlane(P_v[0], i & 63), y = __builtin_amdgcn_readlane(P_v[1], i & 63);
         return i < 64 ? x : y;
     }
-    __device__ __forceinline__ void start(const BandArgs &a, const PatchWhere &w, RowTab &t)
+    __device__ __forceinline__ void start(const BandArgs &a, const PatchWhere &w, Tab &t)
     {
-        if (w.tid <= kMaxRows) {
-            int4 x = {0, 0, 0, 0}, y = {0, 0, 0, 0};
-            if (w.tid < w.nrows) {
-                x = a.row_rec[2 * (w.rows_at + w.tid)];
-                y = a.row_rec[2 * (w.rows_at + w.tid) + 1];
+        if (w.tid <= Tab::ROWS) {
+            constexpr int N = Tab::COLUMNS ? 6 : 2;
+            int4 x[N] = {};
+            if (w.tid < w.nrows)
+#pragma unroll
+                for (int i = 0; i < N; ++i) x[i] = a.row_rec[N * (w.rows_at + w.tid) + i];
+            t.col[w.tid] = x[0].x;
+            t.uni[w.tid] = x[0].y;
+            if (w.tid < Tab::ROWS) t.before[w.tid] = x[0].z;
+            if constexpr (Tab::COLUMNS) t.row[w.tid] = x[0].w;
+            const int omega = Tab::COLUMNS ? x[1].x : x[0].w;
+#pragma unroll
+            for (int i = 0; i < Tab::SUBS / 4; ++i) {
+                const int4 y = x[N - Tab::SUBS / 4 + i];
+                t.arc[4 * i][w.tid] = make_uint2(y.x, omega);
+                t.arc[4 * i + 1][w.tid] = make_uint2(y.y, omega);
+                t.arc[4 * i + 2][w.tid] = make_uint2(y.z, omega);
+                t.arc[4 * i + 3][w.tid] = make_uint2(y.w, omega);
             }
-            t.col[w.tid] = x.x;
-            t.uni[w.tid] = x.y;
-            if (w.tid < kMaxRows) t.before[w.tid] = x.z;
-            t.arc[0][w.tid] = make_uint2(y.x, x.w);
-            t.arc[1][w.tid] = make_uint2(y.y, x.w);
-            t.arc[2][w.tid] = make_uint2(y.z, x.w);
-            t.arc[3][w.tid] = make_uint2(y.w, x.w);
         }
         __syncthreads();
         P_v[0] = t.before[w.lane];
-        P_v[1] = t.before[64 + w.lane];
+        if (Tab::ROWS > 64) P_v[1] = t.before[64 + w.lane];
         r = 0;
         sh = 0;
     }
     // the chunks X0 .. X0 + LOOK - 1 (X0 < total; past the last: that one again, not met)
-    __device__ __forceinline__ void look(int X0, const PatchWhere &w, const RowTab &t)
+    __device__ __forceinline__ void look(int X0, const PatchWhere &w, const Tab &t)
     {
         const int X = imin(X0 + w.lane, w.total - 1);
         int at = r;
@@ -276,7 +296,7 @@ struct Chunks {
         list = __builtin_amdgcn_ds_permute(4 * (need ? ones : __popcll(met) + w.lane - ones), entry);
     }
     // the stage of chunks X0 .. X0 + CAP - 1, stages in order
-    __device__ __forceinline__ void set(int X0, const PatchWhere &w, const RowTab &t)
+    __device__ __forceinline__ void set(int X0, const PatchWhere &w, const Tab &t)
     {
         sh = G::LOOK == 64 ? X0 & 63 : X0 == 0 || sh + G::CAP == G::LOOK ? 0 : sh + G::CAP;
         if (sh == 0) look(X0, w, t);
@@ -284,10 +304,11 @@ struct Chunks {
         cnt = __popcll(met >> sh & (~0ull >> (64 - G::CAP)));
     }
     // row and column of chunk i of the stage
-    __device__ __forceinline__ void get(int i, int &row, int &col) const
+    __device__ __forceinline__ void get(int i, const PatchWhere &w, const Tab &t, int &row, int &col) const
     {
-        const int e = __builtin_amdgcn_ds_bpermute(4 * (sh + i), entry);
-        row = e >> 6 & 255;
+        const int e = __builtin_amdgcn_ds_bpermute(4 * (sh + i), entry), at = e >> 6 & 255;
+        if constexpr (Tab::COLUMNS) row = t.row[at];
+        else row = w.rmin + at;
         col = e >> 14;
     }
 };
@@ -345,13 +366,13 @@ struct Place {
         x = w.tid & (G::XL - 1);
         cg = w.tid / G::XL;
     }
-    __device__ __forceinline__ void set(const PatchWhere &w, const Chunks<G> &ch)
+    __device__ __forceinline__ void set(const PatchWhere &w, const Chunks<G, MODE> &ch, const RowTab<MODE> &t)
     {
 #pragma unroll
         for (int j = 0; j < G::CJ; ++j) {
             int row, col;
-            ch.get(x + G::XL * j, row, col);
-            at[j].set(w, w.rmin + row, col, cg);
+            ch.get(x + G::XL * j, w, t, row, col);
+            at[j].set(w, row, col, cg);
         }
     }
 };
@@ -403,9 +424,40 @@ struct Stage {
             }
         }
     }
+    // kColumns: place of point i of the thread's piece, four rows of a column, from the workgroup's first row on
+    static __device__ __forceinline__ size_t column_at(const PatchWhere &w, int x, int i)
+    {
+        const int row = w.first + 4 * (x & 3) + i, u = w.W0 + 4 * (x >> 2);
+        return w.row_at(row < w.n_own ? row : w.first) + size_t(w.c_own) * (u < w.nU ? u : w.W0);
+    }
     // the workgroup's own points; vec: its rows are contiguous
     __device__ __forceinline__ void load_own(const PatchWhere &w, const T *slice, int nch, bool vec)
     {
+        if constexpr (MODE == kColumns) {
+            const int tid = here_v(w.tid);
+            const T *p = slice + size_t(tid / G::OWN) * w.plane_own;
+            if (w.c_own == 2) {                          // both classes of a latitude side by side
+                typedef T T2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+                for (int i = 0; i < 4; i += 2) {
+                    const T *pi = p + column_at(w, tid & (G::OWN - 1), i);
+#pragma unroll
+                    for (int j = 0; j < G::NCO; ++j) {
+                        const T2 y = *reinterpret_cast<const T2 *>(pi + size_t(j * G::NGO) * w.plane_own);
+                        r[j][i] = y[0];
+                        r[j][i + 1] = y[1];
+                    }
+                }
+                return;
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const T *pi = p + column_at(w, tid & (G::OWN - 1), i);
+#pragma unroll
+                for (int j = 0; j < G::NCO; ++j) r[j][i] = pi[size_t(j * G::NGO) * w.plane_own];
+            }
+            return;
+        }
         if constexpr (MODE == kPairs) {
             if (w.lg > 0) {
                 const int tid = here_v(w.tid);
@@ -650,12 +702,13 @@ struct TileRef {
     int slot, row, col;              // the lane's chunk (number g of the tile)
     int slot_n;                      // chunk n & 3 of the tile
     // the tile's chunks are entries at .. at + 3 of the list, those below end
+    template <int DEAD>
     __device__ __forceinline__ void get(int list, int at, int end, int n, int g)
     {
         const int m = __builtin_amdgcn_ds_bpermute(4 * (at + g), list);
         slot_n = __builtin_amdgcn_ds_bpermute(4 * (at + (n & 3)), list) & 63;
         slot = m & 63;
-        row = at + g < end ? m >> 6 & 255 : kDead;
+        row = at + g < end ? m >> 6 & 255 : DEAD;
         col = m >> 14;
     }
     // keep[rr]: is column col + rr a neighbor of the owner at walked column su
@@ -669,11 +722,11 @@ struct TileRef {
 
 // The results of the workgroup's owners, by way of LDS: acc[mt][rr] is channel 16 mt + 4 g + rr of the lane's owner.  again: those that
 // are not finite are to be evaluated (marked).
-template <class G>
+template <class G, int MODE>
 __device__ __forceinline__ void put_results(const f32x4 (&acc)[G::D / 16], float factor, bool again, float *tile, const PatchWhere &w)
 {
     const int lane = here_v(w.lane);
-    float *p = tile + (lane >> 4) * 4 * G::PITCH + 4 * w.own_slot(lane >> 2 & 3, G::NW) + (lane & 3);
+    float *p = tile + (lane >> 4) * 4 * G::PITCH + 4 * w.template own_slot<MODE>(lane >> 2 & 3, G::NW) + (lane & 3);
 #pragma unroll
     for (int mt = 0; mt < G::D / 16; ++mt)
 #pragma unroll
@@ -681,15 +734,37 @@ __device__ __forceinline__ void put_results(const f32x4 (&acc)[G::D / 16], float
             p[(16 * mt + rr) * G::PITCH] = again && !(fabsf(acc[mt][rr]) < INFINITY) ? __builtin_bit_cast(float, kAgain) : acc[mt][rr] * factor;
 }
 // is the lane's channel of the wavefront's owner i marked
-template <class G>
+template <class G, int MODE>
 __device__ __forceinline__ bool marked(const float *tile, const PatchWhere &w, int i)
 {
-    return __builtin_bit_cast(unsigned, tile[imin(w.lane, G::D - 1) * G::PITCH + 4 * w.own_slot(i >> 2, G::NW) + (i & 3)]) == kAgain;
+    return __builtin_bit_cast(unsigned, tile[imin(w.lane, G::D - 1) * G::PITCH + 4 * w.template own_slot<MODE>(i >> 2, G::NW) + (i & 3)]) == kAgain;
 }
 template <class G, int MODE>
 __device__ __forceinline__ void store_results(typename G::T *slice, int nch, const float *tile, const PatchWhere &w, bool vec)
 {
     using T = typename G::T;
+    if constexpr (MODE == kColumns) {
+        const int tid = here_v(w.tid), x = tid % G::OWN, c0 = tid / G::OWN;
+        if (w.W0 + 4 * (x >> 2) >= w.nU) return;
+        T *p = slice + size_t(c0) * w.plane_own;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (w.first + 4 * (x & 3) + i >= w.n_own) break;
+            T *pi = p + Stage<G, MODE>::column_at(w, x, i);
+#pragma unroll
+            for (int j = 0; j < G::NCO; ++j) {
+                const u32x2 y = *reinterpret_cast<const u32x2 *>(tile + (c0 + j * G::NGO) * G::PITCH + 4 * x + (i & 2));
+                T *pj = pi + size_t(j * G::NGO) * w.plane_own;
+                if (w.c_own == 2 && y[0] != kAgain && y[1] != kAgain) {
+                    if ((i & 1) == 0) *reinterpret_cast<u32x2 *>(pj) = y;
+                } else {
+                    const unsigned z = y[i & 1];
+                    if (z != kAgain) *pj = __builtin_bit_cast(float, z);
+                }
+            }
+        }
+        return;
+    }
     const int h = 2 - here_s(w.lg), tid = here_v(w.tid), x = tid % G::OWN, c0 = tid / G::OWN;
     int sub = (x / G::NW) >> h, u = w.W0 + 4 * (x - G::NW * (sub << h)), end = w.nU, step = w.c_own;
     const bool two = MODE == kPairs && w.lg > 0;
@@ -743,7 +818,7 @@ nattn_fwd_patch(BandArgs a, const typename G::T *__restrict__ q, const typename 
     constexpr int D = G::D;
     using T = typename G::T;
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    Shared<G> &sh = *reinterpret_cast<Shared<G> *>(lds);
+    Shared<G, MODE> &sh = *reinterpret_cast<Shared<G, MODE> *>(lds);
     PatchWhere w;
     w.set(a);
     const int n = w.n, g = w.g, nd = MODE == kRagged ? a.d : D, ne = MODE == kRagged ? a.e : D;
@@ -753,11 +828,11 @@ nattn_fwd_patch(BandArgs a, const typename G::T *__restrict__ q, const typename 
     at.init(w);
     Stage<G, MODE> rk, rv;
     rk.load_own(w, qs, nd, vec);
-    Chunks<G> ch;
+    Chunks<G, MODE> ch;
     ch.start(a, w, sh.rows);
     auto fetch = [&](int X0) {
         ch.set(X0, w, sh.rows);
-        at.set(w, ch);
+        at.set(w, ch, sh.rows);
         rk.load(w, at, ks, nd);
         rv.load(w, at, vs, ne);
     };
@@ -768,7 +843,7 @@ nattn_fwd_patch(BandArgs a, const typename G::T *__restrict__ q, const typename 
     __syncthreads();
     if (w.total > 0) fetch(0);
     OwnPoint<G> own;
-    own.read(sh.a + tr_at + 4 * w.own_slot(here_v(w.lane) & 3, G::NW));
+    own.read(sh.a + tr_at + 4 * w.template own_slot<MODE>(here_v(w.lane) & 3, G::NW));
     Sums<G> acc;
     acc.zero();
     // |scale|, its sign is on q: the largest product is the largest logit; never zero, so that a masked -inf stays one
@@ -787,7 +862,7 @@ nattn_fwd_patch(BandArgs a, const typename G::T *__restrict__ q, const typename 
                 TileRef tr[2];
                 float x[8], omega[2];
 #pragma unroll
-                for (int i = 0; i < N; ++i) tr[i].get(list, first + 4 * (t + i), end, n, g);
+                for (int i = 0; i < N; ++i) tr[i].template get<RowTab<MODE>::DEAD>(list, first + 4 * (t + i), end, n, g);
 #pragma unroll
                 for (int i = 0; i < N; ++i) {
                     const uint2 arc = sh.rows.arc[w.sub][tr[i].row];
@@ -846,7 +921,7 @@ nattn_fwd_patch(BandArgs a, const typename G::T *__restrict__ q, const typename 
         no_lse = again & owner_bits(lt != lt);
     }
     __syncthreads();
-    put_results<G>(acc.hi, 1.f / lt, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
+    put_results<G, MODE>(acc.hi, 1.f / lt, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
     if (w.active && g == 0 && !(no_lse >> n & 1)) {
         // the whole part of m goes into the logarithm, so that its value and the sum are no larger than the result
         const float whole = fminf(fmaxf(rintf(m), -60.f), 60.f);
@@ -855,7 +930,7 @@ nattn_fwd_patch(BandArgs a, const typename G::T *__restrict__ q, const typename 
     }
     __syncthreads();
     store_results<G, MODE>(out + size_t(w.bh) * ne * w.plane_own, ne, reinterpret_cast<const float *>(sh.a), w, vec);
-    exact_fwd<T, PatchWhere>(again, no_lse, w.wave, [&](const PatchWhere &at, int i) { return marked<G>(reinterpret_cast<const float *>(sh.a), at, i); });
+    exact_fwd<T, PatchWhere>(again, no_lse, w.wave, [&](const PatchWhere &at, int i) { return marked<G, MODE>(reinterpret_cast<const float *>(sh.a), at, i); });
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -869,7 +944,7 @@ nattn_bwd_dq_patch(BandArgs a, const typename G::T *__restrict__ q, const typena
     constexpr int D = G::D;
     using T = typename G::T;
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    SharedDq<G> &sh = *reinterpret_cast<SharedDq<G> *>(lds);
+    SharedDq<G, MODE> &sh = *reinterpret_cast<SharedDq<G, MODE> *>(lds);
     PatchWhere w;
     w.set(a);
     const int n = w.n, g = w.g, nd = MODE == kRagged ? a.d : D, ne = MODE == kRagged ? a.e : D;
@@ -882,11 +957,11 @@ nattn_bwd_dq_patch(BandArgs a, const typename G::T *__restrict__ q, const typena
     Stage<G, MODE> rk, rv;
     rk.load_own(w, qs, nd, vec);
     rv.load_own(w, gs, ne, vec);
-    Chunks<G> ch;
+    Chunks<G, MODE> ch;
     ch.start(a, w, sh.rows);
     auto fetch = [&](int X0) {
         ch.set(X0, w, sh.rows);
-        at.set(w, ch);
+        at.set(w, ch, sh.rows);
         rk.load(w, at, ks, nd);
         rv.load(w, at, vs, ne);
     };
@@ -905,7 +980,7 @@ nattn_bwd_dq_patch(BandArgs a, const typename G::T *__restrict__ q, const typena
     rv.store_own(w, at, sh.b, ne);
     __syncthreads();
     if (w.total > 0) fetch(0);
-    const int slot = w.own_slot(here_v(w.lane) & 3, G::NW), point = 4 * w.own_slot(here_v(w.lane) >> 2 & 3, G::NW) + (n & 3);
+    const int slot = w.template own_slot<MODE>(here_v(w.lane) & 3, G::NW), point = 4 * w.template own_slot<MODE>(here_v(w.lane) >> 2 & 3, G::NW) + (n & 3);
     OwnPoint<G> oq, og;
     oq.read(sh.a + tr_at + 4 * slot);
     og.read(sh.b + tr_at + 4 * slot);
@@ -929,7 +1004,7 @@ nattn_bwd_dq_patch(BandArgs a, const typename G::T *__restrict__ q, const typena
                 TileRef tr[2];
                 float x[8];
 #pragma unroll
-                for (int i = 0; i < N; ++i) tr[i].get(list, first + 4 * (t + i), end, n, g);
+                for (int i = 0; i < N; ++i) tr[i].template get<RowTab<MODE>::DEAD>(list, first + 4 * (t + i), end, n, g);
 #pragma unroll
                 for (int i = 0; i < N; ++i) {
                     const uint2 arc = sh.rows.arc[w.sub][tr[i].row];
@@ -964,10 +1039,10 @@ nattn_bwd_dq_patch(BandArgs a, const typename G::T *__restrict__ q, const typena
     unsigned again = not_finite(acc.hi, w.active);
     if (any_owner(again)) again &= ~(own_nan(oq) | owner_bits(dsum != dsum || L2 != L2));       // (these are NaN throughout, as they are)
     __syncthreads();
-    put_results<G>(acc.hi, a.scale * a.omega_ref, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
+    put_results<G, MODE>(acc.hi, a.scale * a.omega_ref, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
     __syncthreads();
     store_results<G, MODE>(dq + size_t(w.bh) * nd * w.plane_own, nd, reinterpret_cast<const float *>(sh.a), w, vec);
-    exact_dq<T, PatchWhere>(again, w.wave, [&](const PatchWhere &at, int i) { return marked<G>(reinterpret_cast<const float *>(sh.a), at, i); });
+    exact_dq<T, PatchWhere>(again, w.wave, [&](const PatchWhere &at, int i) { return marked<G, MODE>(reinterpret_cast<const float *>(sh.a), at, i); });
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -982,7 +1057,7 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
     constexpr int D = G::D;
     using T = typename G::T;
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    SharedDkdv<G> &sh = *reinterpret_cast<SharedDkdv<G> *>(lds);
+    SharedDkdv<G, MODE> &sh = *reinterpret_cast<SharedDkdv<G, MODE> *>(lds);
     PatchWhere w;
     w.set(a);
     const int n = w.n, g = w.g, nd = MODE == kRagged ? a.d : D, ne = MODE == kRagged ? a.e : D;
@@ -998,21 +1073,21 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
     Stage<G, MODE> rq, rg;
     rq.load_own(w, ks, nd, vec);
     rg.load_own(w, vs, ne, vec);
-    Chunks<G> ch;
+    Chunks<G, MODE> ch;
     ch.start(a, w, sh.rows);
     f32x4 rs = {0.f, 0.f, 0.f, 0.f};         // first threads: logsumexp or D of a chunk
     auto fetch = [&](int X0) {
         ch.set(X0, w, sh.rows);
-        at.set(w, ch);
+        at.set(w, ch, sh.rows);
         rq.load(w, at, qs, nd);
         rg.load(w, at, gs, ne);
         if constexpr (G::CJ == 1) {
             if (w.tid < 2 * G::CAP) rs = at.at[0].floats(w, at.cg ? Ds : ls, at.cg);
         } else if (w.wave < (2 * G::CAP + 63) / 64) {
             int row, col;
-            ch.get(w.tid % G::CAP, row, col);
+            ch.get(w.tid % G::CAP, w, sh.rows, row, col);
             typename Place<G, MODE>::At from;
-            from.set(w, w.rmin + row, col, 0);
+            from.set(w, row, col, 0);
             if (w.tid < 2 * G::CAP) rs = from.floats(w, w.tid < G::CAP ? ls : Ds, 0);
         }
     };
@@ -1022,7 +1097,7 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
     rg.store_own(w, at, sh.b, ne);
     __syncthreads();
     if (w.total > 0) fetch(0);
-    const int slot = w.own_slot(here_v(w.lane) & 3, G::NW);
+    const int slot = w.template own_slot<MODE>(here_v(w.lane) & 3, G::NW);
     OwnPoint<G> ok, ov;
     ok.read(sh.a + tr_at + 4 * slot);
     ov.read(sh.b + tr_at + 4 * slot);
@@ -1046,7 +1121,7 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
                 TileRef tr[2];
                 float pr[8], ds[8];
 #pragma unroll
-                for (int i = 0; i < N; ++i) tr[i].get(list, first + 4 * (t + i), end, n, g);
+                for (int i = 0; i < N; ++i) tr[i].template get<RowTab<MODE>::DEAD>(list, first + 4 * (t + i), end, n, g);
 #pragma unroll
                 for (int i = 0; i < N; ++i) {
                     const unsigned arc = sh.rows.arc[w.sub][tr[i].row].x;
@@ -1091,14 +1166,14 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
         again_v &= ~nan;
     }
     __syncthreads();
-    put_results<G>(dka.hi, omega * a.scale, again_k >> n & 1, reinterpret_cast<float *>(sh.a), w);
-    put_results<G>(dva.hi, omega, again_v >> n & 1, reinterpret_cast<float *>(sh.b), w);
+    put_results<G, MODE>(dka.hi, omega * a.scale, again_k >> n & 1, reinterpret_cast<float *>(sh.a), w);
+    put_results<G, MODE>(dva.hi, omega, again_v >> n & 1, reinterpret_cast<float *>(sh.b), w);
     __syncthreads();
     store_results<G, MODE>(dk + size_t(w.bh) * nd * w.plane_own, nd, reinterpret_cast<const float *>(sh.a), w, vec);
     store_results<G, MODE>(dv + size_t(w.bh) * ne * w.plane_own, ne, reinterpret_cast<const float *>(sh.b), w, vec);
     exact_dkdv<T, PatchWhere>(
-        again_k | again_v, w.wave, [&](const PatchWhere &at, int i) { return marked<G>(reinterpret_cast<const float *>(sh.a), at, i); },
-        [&](const PatchWhere &at, int i) { return marked<G>(reinterpret_cast<const float *>(sh.b), at, i); });
+        again_k | again_v, w.wave, [&](const PatchWhere &at, int i) { return marked<G, MODE>(reinterpret_cast<const float *>(sh.a), at, i); },
+        [&](const PatchWhere &at, int i) { return marked<G, MODE>(reinterpret_cast<const float *>(sh.b), at, i); });
 }
 
 // Calls f with the geometry for a head dimension.  More workgroups on a compute unit count for more than longer stages (twice the
@@ -1149,10 +1224,10 @@ int PatchKernels<T, MODE>::configure()
 {
     bool bad = false;
     for (int d : {16, 32, 64}) {
-        by_shape<T, MODE, kFwd>(d, false, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_fwd_patch<decltype(g), MODE>), sizeof(Shared<decltype(g)>)); });
-        by_shape<T, MODE, kDq>(d, false, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dq_patch<decltype(g), MODE>), sizeof(SharedDq<decltype(g)>)); });
+        by_shape<T, MODE, kFwd>(d, false, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_fwd_patch<decltype(g), MODE>), sizeof(Shared<decltype(g), MODE>)); });
+        by_shape<T, MODE, kDq>(d, false, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dq_patch<decltype(g), MODE>), sizeof(SharedDq<decltype(g), MODE>)); });
         for (bool classes : {false, true})
-            by_shape<T, MODE, kDkdv>(d, classes, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dkdv_patch<decltype(g), MODE>), sizeof(SharedDkdv<decltype(g)>)); });
+            by_shape<T, MODE, kDkdv>(d, classes, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dkdv_patch<decltype(g), MODE>), sizeof(SharedDkdv<decltype(g), MODE>)); });
     }
     return bad;
 }
@@ -1163,7 +1238,7 @@ void PatchKernels<T, MODE>::fwd(const S2DeviceTables &t, int nbh, int d, int e, 
     const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale);
     by_shape<T, MODE, kFwd>(d > e ? d : e, l.a.b.c_own > 1, [&](auto g) {
         using G = decltype(g);
-        hipLaunchKernelGGL((nattn_fwd_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(Shared<G>), st, l.a, q, k, v, out, lse);
+        hipLaunchKernelGGL((nattn_fwd_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(Shared<G, MODE>), st, l.a, q, k, v, out, lse);
     });
 }
 template <class T, int MODE>
@@ -1173,7 +1248,7 @@ void PatchKernels<T, MODE>::dq(const S2DeviceTables &t, int nbh, int d, int e, f
     const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale);
     by_shape<T, MODE, kDq>(d > e ? d : e, l.a.b.c_own > 1, [&](auto g) {
         using G = decltype(g);
-        hipLaunchKernelGGL((nattn_bwd_dq_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(SharedDq<G>), st, l.a, q, k, v, o, lse, go, dq, Dws);
+        hipLaunchKernelGGL((nattn_bwd_dq_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(SharedDq<G, MODE>), st, l.a, q, k, v, o, lse, go, dq, Dws);
     });
 }
 template <class T, int MODE>
@@ -1183,6 +1258,6 @@ void PatchKernels<T, MODE>::dkdv(const S2DeviceTables &t, int nbh, int d, int e,
     const PatchLaunch l = patch_launch(t, t.side_in, nbh, d, e, scale);
     by_shape<T, MODE, kDkdv>(d > e ? d : e, l.a.b.c_own > 1, [&](auto g) {
         using G = decltype(g);
-        hipLaunchKernelGGL((nattn_bwd_dkdv_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(SharedDkdv<G>), st, l.a, q, k, v, lse, go, Dws, dk, dv);
+        hipLaunchKernelGGL((nattn_bwd_dkdv_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(SharedDkdv<G, MODE>), st, l.a, q, k, v, lse, go, Dws, dk, dv);
     });
 }
