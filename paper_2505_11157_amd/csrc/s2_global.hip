@@ -25,6 +25,8 @@
 // p_ij = omega_j exp(s_ij - lse_i), dS_ij = p_ij (dout_i.v_j - D_i);
 // one kernel owns 32 keys per wavefront and streams query tiles (dk, dv), one
 // owns 32 queries per wavefront and streams key tiles (dq): no atomics.
+#include <type_traits>
+
 #include "s2_internal.h"
 
 namespace {
@@ -248,14 +250,22 @@ __device__ __forceinline__ bf16x8 col_operand(const char *tile, int col, int hl,
     return lds8(tile + rt * 4096 + swz(col, 4 * half + 2 * hl + j));
 }
 
-// Workgroups are numbered so that each of the eight XCDs (which take consecutive workgroup ids in turn)
-// works through one contiguous piece of the (slice, block) list: the operands of the few slices an XCD
-// has in flight then stay in its own L2.  Returns false for the padding ids at the end of the launch.
-__device__ __forceinline__ bool xcd_unit(int nunits, int &unit)
+// Units of 128 tokens of a slice.  Workgroups are numbered so that each of the eight XCDs (which take consecutive workgroup ids in turn)
+// works through one contiguous piece of the (slice, unit) list: the operands of the few slices an XCD
+// has in flight then stay in its own L2.  Of its piece an XCD takes the first `whole` units in one workgroup each, the others in two of
+// 64 tokens.
+struct Units {
+    int all, per_slice, per_xcd, whole, tokens;
+};
+// f(split, unit of a slice's, slice) for the workgroup's share: split = 1, unit in units of 128 tokens, or 2, of 64
+template <class F>
+__device__ __forceinline__ void take_unit(const Units &u, F &&f)
 {
-    const int per = (nunits + 7) >> 3;
-    unit = int(blockIdx.x & 7) * per + int(blockIdx.x >> 3);
-    return unit < nunits && int(blockIdx.x >> 3) < per;
+    const int i = int(blockIdx.x >> 3), j = i - u.whole, k = j < 0 ? i : u.whole + (j >> 1), unit = int(blockIdx.x & 7) * u.per_xcd + k;
+    if (k >= u.per_xcd || unit >= u.all) return;
+    const int bh = unit / u.per_slice, q = unit - bh * u.per_slice;
+    if (j < 0) f(std::integral_constant<int, 1>(), q, bh);
+    else if (128 * q + 64 * (j & 1) < u.tokens) f(std::integral_constant<int, 2>(), 2 * q + (j & 1), bh);
 }
 
 // Forward.  A workgroup owns 128 queries of one slice (one 32-query MFMA tile per wavefront) and streams
@@ -267,21 +277,16 @@ __device__ __forceinline__ bool xcd_unit(int nunits, int &unit)
 // SPLIT = 2 is for launches with too few workgroups to fill the chip: the four wavefronts are two pairs, each pair owns
 // the same 64 queries and takes every other 32-key tile of a stage, and the pairs' (o, m, l) meet in LDS behind the
 // last stage, so a query's serial chain over the keys is half as long and the launch has twice the workgroups
-// (46 x 90, four heads: 94 us with SPLIT = 1, 64 us with SPLIT = 2; see split_waves for the line).
+// (46 x 90, four heads: 94 us with SPLIT = 1, 64 us with SPLIT = 2; see split_units for the line).
+constexpr int kStageFwd = 2 * kTileBytes + 256;      // K row tile, V^T column tile, 64 weights
 template <bool UNIFORM_W, int SPLIT>
-__global__ void __launch_bounds__(256, 3)
-global_fwd(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const bf16raw *__restrict__ vt,
-           const float *__restrict__ wtok, bf16raw *__restrict__ out, float *__restrict__ lse, int N, int Npad,
-           int nqb, int nunits, float c2, float ln_wref)
+__device__ __forceinline__ void
+forward_unit(char *buf0, char *buf1, int qb, int bh, const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const bf16raw *__restrict__ vt,
+             const float *__restrict__ wtok, bf16raw *__restrict__ out, float *__restrict__ lse, int N, int Npad, float c2, float ln_wref)
 {
     static_assert(SPLIT == 1 || SPLIT == 2, "a stage holds two key tiles");
-    constexpr int kStage = 2 * kTileBytes + 256;     // K row tile, V^T column tile, 64 weights
+    constexpr int kStage = kStageFwd;
     constexpr int TILES = 4 / SPLIT;                 // query tiles of the workgroup
-    __shared__ __attribute__((aligned(16))) char buf0[kStage];
-    __shared__ __attribute__((aligned(16))) char buf1[kStage];
-    int unit;
-    if (!xcd_unit(nunits, unit)) return;
-    const int bh = unit / nqb, qb = unit - bh * nqb;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, col = lane & 31, hl = lane >> 5;
     const int part = wave / TILES, qi = (qb * TILES + wave % TILES) * 32 + col;
@@ -427,6 +432,17 @@ global_fwd(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const b
         if (hl == 0) lse[size_t(bh) * N + qi] = (m + log2f(lt)) * 0.6931471805599453f + ln_wref;
     }
 }
+template <bool UNIFORM_W>
+__global__ void __launch_bounds__(256, 3)
+global_fwd(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const bf16raw *__restrict__ vt, const float *__restrict__ wtok,
+           bf16raw *__restrict__ out, float *__restrict__ lse, int N, int Npad, Units units, float c2, float ln_wref)
+{
+    __shared__ __attribute__((aligned(16))) char buf0[kStageFwd];
+    __shared__ __attribute__((aligned(16))) char buf1[kStageFwd];
+    take_unit(units, [&](auto split, int qb, int bh) {
+        forward_unit<UNIFORM_W, decltype(split)::value>(buf0, buf1, qb, bh, q, k, vt, wtok, out, lse, N, Npad, c2, ln_wref);
+    });
+}
 
 // The sums of a workgroup's second pair of wavefronts are added to those of the first, through the stage buffers (one
 // for each wavefront of a pair; every wavefront is past its last stage).  True for the second pair, which is done.
@@ -460,20 +476,15 @@ __device__ __forceinline__ bool join_pairs(f32x16 *const (&sums)[TERMS], char *b
 // of 64: Q and dout token-major (for S = Q K^T and dP = dout V^T, which land with lane = key,
 // registers = 16 queries), Q^T and dout^T channel-major (dV^T += dout^T Pt, dK^T += Q^T dSt), L and D.
 // SPLIT = 2: two pairs of wavefronts take every other query tile of the same 64 keys, and their sums meet in LDS.
+constexpr int kStageDkdv = 4 * kTileBytes + 512;     // Q, dout row tiles; Q^T, dout^T column tiles; L, D
 template <int SPLIT>
-__global__ void __launch_bounds__(256, 2)
-global_bwd_dkdv(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const bf16raw *__restrict__ v,
-                const bf16raw *__restrict__ go, const bf16raw *__restrict__ qt, const bf16raw *__restrict__ got,
-                const float *__restrict__ wtok, const float *__restrict__ L2, const float *__restrict__ Dv,
-                bf16raw *__restrict__ dk, bf16raw *__restrict__ dv, int N, int Npad, int nkb, int nunits, float c2,
-                float scale)
+__device__ __forceinline__ void
+dkdv_unit(char *buf0, char *buf1, int kb, int bh, const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const bf16raw *__restrict__ v,
+          const bf16raw *__restrict__ go, const bf16raw *__restrict__ qt, const bf16raw *__restrict__ got, const float *__restrict__ wtok,
+          const float *__restrict__ L2, const float *__restrict__ Dv, bf16raw *__restrict__ dk, bf16raw *__restrict__ dv, int N, int Npad, float c2,
+          float scale)
 {
-    constexpr int kStage = 4 * kTileBytes + 512;     // Q, dout row tiles; Q^T, dout^T column tiles; L, D
-    __shared__ __attribute__((aligned(16))) char buf0[kStage];
-    __shared__ __attribute__((aligned(16))) char buf1[kStage];
-    int unit;
-    if (!xcd_unit(nunits, unit)) return;
-    const int bh = unit / nkb, kb = unit - bh * nkb;
+    constexpr int kStage = kStageDkdv;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, col = lane & 31, hl = lane >> 5;
     constexpr int TILES = 4 / SPLIT;                 // key tiles of the workgroup
@@ -575,6 +586,17 @@ global_bwd_dkdv(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, co
         }
     }
 }
+__global__ void __launch_bounds__(256, 2)
+global_bwd_dkdv(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const bf16raw *__restrict__ v, const bf16raw *__restrict__ go,
+                const bf16raw *__restrict__ qt, const bf16raw *__restrict__ got, const float *__restrict__ wtok, const float *__restrict__ L2,
+                const float *__restrict__ Dv, bf16raw *__restrict__ dk, bf16raw *__restrict__ dv, int N, int Npad, Units units, float c2, float scale)
+{
+    __shared__ __attribute__((aligned(16))) char buf0[kStageDkdv];
+    __shared__ __attribute__((aligned(16))) char buf1[kStageDkdv];
+    take_unit(units, [&](auto split, int kb, int bh) {
+        dkdv_unit<decltype(split)::value>(buf0, buf1, kb, bh, q, k, v, go, qt, got, wtok, L2, Dv, dk, dv, N, Npad, c2, scale);
+    });
+}
 
 // Query side: a workgroup owns 128 queries and streams the keys in stages of 64: K and V token-major
 // (S^T = K Q^T and dP^T = V dout^T land with lane = query, registers = 16 keys) and w K^T channel-major
@@ -584,19 +606,14 @@ global_bwd_dkdv(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, co
 // 100 there (a key of positive weight stays below log2(max omega / omega_j), a few tens at most), which keeps the
 // factor finite and the product with the zero row exactly zero.
 // SPLIT as in the forward.
+constexpr int kStageDq = 3 * kTileBytes;             // K, V row tiles; (w K)^T column tile
 template <bool DEAD, int SPLIT>
-__global__ void __launch_bounds__(256, 3)
-global_bwd_dq(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const bf16raw *__restrict__ v,
-              const bf16raw *__restrict__ go, const bf16raw *__restrict__ ktw, const float *__restrict__ L2,
-              const float *__restrict__ Dv, bf16raw *__restrict__ dq, int N, int Npad, int nqb, int nunits, float c2,
-              float scale)
+__device__ __forceinline__ void
+dq_unit(char *buf0, char *buf1, int qb, int bh, const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const bf16raw *__restrict__ v,
+        const bf16raw *__restrict__ go, const bf16raw *__restrict__ ktw, const float *__restrict__ L2, const float *__restrict__ Dv,
+        bf16raw *__restrict__ dq, int N, int Npad, float c2, float scale)
 {
-    constexpr int kStage = 3 * kTileBytes;           // K, V row tiles; (w K)^T column tile
-    __shared__ __attribute__((aligned(16))) char buf0[kStage];
-    __shared__ __attribute__((aligned(16))) char buf1[kStage];
-    int unit;
-    if (!xcd_unit(nunits, unit)) return;
-    const int bh = unit / nqb, qb = unit - bh * nqb;
+    constexpr int kStage = kStageDq;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, col = lane & 31, hl = lane >> 5;
     constexpr int TILES = 4 / SPLIT;                 // query tiles of the workgroup
@@ -677,6 +694,18 @@ global_bwd_dq(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, cons
         }
     }
 }
+template <bool DEAD>
+__global__ void __launch_bounds__(256, 3)
+global_bwd_dq(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const bf16raw *__restrict__ v, const bf16raw *__restrict__ go,
+              const bf16raw *__restrict__ ktw, const float *__restrict__ L2, const float *__restrict__ Dv, bf16raw *__restrict__ dq, int N, int Npad,
+              Units units, float c2, float scale)
+{
+    __shared__ __attribute__((aligned(16))) char buf0[kStageDq];
+    __shared__ __attribute__((aligned(16))) char buf1[kStageDq];
+    take_unit(units, [&](auto split, int qb, int bh) {
+        dq_unit<DEAD, decltype(split)::value>(buf0, buf1, qb, bh, q, k, v, go, ktw, L2, Dv, dq, N, Npad, c2, scale);
+    });
+}
 
 // Whether the wavefronts of a workgroup share the streamed side (SPLIT = 2).  It pays while the launch of workgroups of
 // 128 tokens leaves compute units idle or their second wavefront of a SIMD missing; beyond that the second workgroup of
@@ -687,10 +716,22 @@ global_bwd_dq(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, cons
 //     key side       33: 224 -> 192   132: 235 -> 220   224 (21 x 40): 67 -> 67   260 (65 x 128): 511 -> 529
 // (at most two workgroups of the key side fit a compute unit, three of the others: hence two lines).
 constexpr long kSplitBlocks = 320, kSplitBlocksKeySide = 256;
-bool split_waves(int nbh, int N, long most)
+// Larger launches: what an XCD's 32 compute units do not share out evenly, where that is at most half a unit for each, goes in halves, so that
+// the last compute units end half a unit after the others and not a whole one.  Forward / backward, us: 65 x 128, 32 slices (8.1
+// units for a compute unit) 634 / 2059 -> 593 / 1966; 8 slices (2.0) 223 / 667 -> 192 / 576; 46 x 90, 24 (3.1) 204 / 480 -> 178 / 427.
+constexpr int kUnitsXcd = 32;
+Units split_units(int nbh, int N, long most)
 {
-    return long(nbh) * ((N + 127) / 128) <= most;
+    Units u;
+    u.tokens = N;
+    u.per_slice = (N + 127) / 128;
+    u.all = nbh * u.per_slice;
+    u.per_xcd = (u.all + 7) / 8;
+    const int rest = u.per_xcd % kUnitsXcd;
+    u.whole = u.all <= most ? 0 : 2 * rest <= kUnitsXcd ? u.per_xcd - rest : u.per_xcd;
+    return u;
 }
+dim3 split_grid(const Units &u) { return dim3(8u * unsigned(u.whole + 2 * (u.per_xcd - u.whole))); }
 
 int check_global(const s2_grid_t *g, int batch, int heads, int d, int dtype)
 {
@@ -754,13 +795,10 @@ extern "C" int s2_attn_global_fwd(const s2_grid_t *g, int batch, int heads, int 
     pa.stat_op = -1;
     launch_prepare(pa, 1, nbh, N, Npad, st);
     S2TraceScope tr("global_fwd", double(nbh) * N * N, st);
-    const bool split = split_waves(nbh, N, kSplitBlocks), uniform = g->nlon_in % 32 == 0;
-    const int tokens = split ? 64 : 128, nqb = (N + tokens - 1) / tokens, nunits = nbh * nqb;
-    auto kern = split ? (uniform ? global_fwd<true, 2> : global_fwd<false, 2>)
-                      : (uniform ? global_fwd<true, 1> : global_fwd<false, 1>);
-    hipLaunchKernelGGL(kern, dim3(8 * ((nunits + 7) / 8)), dim3(256), 0, st, static_cast<const bf16raw *>(q),
-                       static_cast<const bf16raw *>(k), static_cast<const bf16raw *>(workspace), g->dev_w_tok,
-                       static_cast<bf16raw *>(out), lse, N, Npad, nqb, nunits, scale * kLog2e, g->dt.ln_omega_ref);
+    const Units units = split_units(nbh, N, kSplitBlocks);
+    hipLaunchKernelGGL(g->nlon_in % 32 == 0 ? global_fwd<true> : global_fwd<false>, split_grid(units), dim3(256), 0, st,
+                       static_cast<const bf16raw *>(q), static_cast<const bf16raw *>(k), static_cast<const bf16raw *>(workspace), g->dev_w_tok,
+                       static_cast<bf16raw *>(out), lse, N, Npad, units, scale * kLog2e, g->dt.ln_omega_ref);
     S2_HIP_CHECK(hipGetLastError());
     return S2_OK;
 }
@@ -802,24 +840,17 @@ extern "C" int s2_attn_global_bwd(const s2_grid_t *g, int batch, int heads, int 
     const float c2 = scale * kLog2e;
     {
         S2TraceScope tr("global_bwd_dkdv", double(nbh) * N * N, st);
-        const bool split = split_waves(nbh, N, kSplitBlocksKeySide);
-        const int tokens = split ? 64 : 128, nblk = (N + tokens - 1) / tokens, nunits = nbh * nblk;
-        hipLaunchKernelGGL(split ? global_bwd_dkdv<2> : global_bwd_dkdv<1>, dim3(8 * ((nunits + 7) / 8)), dim3(256), 0,
-                           st, static_cast<const bf16raw *>(q), static_cast<const bf16raw *>(k),
-                           static_cast<const bf16raw *>(v), static_cast<const bf16raw *>(dout), qt, got, g->dev_w_tok,
-                           L2, Dv, static_cast<bf16raw *>(dk), static_cast<bf16raw *>(dv), N, Npad, nblk, nunits, c2,
-                           scale);
+        const Units units = split_units(nbh, N, kSplitBlocksKeySide);
+        hipLaunchKernelGGL(global_bwd_dkdv, split_grid(units), dim3(256), 0, st, static_cast<const bf16raw *>(q), static_cast<const bf16raw *>(k),
+                           static_cast<const bf16raw *>(v), static_cast<const bf16raw *>(dout), qt, got, g->dev_w_tok, L2, Dv,
+                           static_cast<bf16raw *>(dk), static_cast<bf16raw *>(dv), N, Npad, units, c2, scale);
     }
     S2TraceScope tr("global_bwd_dq", double(nbh) * N * N, st);
     const bool dead = Npad != N || !g->zero_lat.empty();      // keys of weight zero exist
-    const bool split = split_waves(nbh, N, kSplitBlocks);
-    const int tokens = split ? 64 : 128, nblk = (N + tokens - 1) / tokens, nunits = nbh * nblk;
-    auto dq_kernel = split ? (dead ? global_bwd_dq<true, 2> : global_bwd_dq<false, 2>)
-                           : (dead ? global_bwd_dq<true, 1> : global_bwd_dq<false, 1>);
-    hipLaunchKernelGGL(dq_kernel, dim3(8 * ((nunits + 7) / 8)), dim3(256), 0, st, static_cast<const bf16raw *>(q),
-                       static_cast<const bf16raw *>(k), static_cast<const bf16raw *>(v),
-                       static_cast<const bf16raw *>(dout), kt, L2, Dv, static_cast<bf16raw *>(dq), N, Npad, nblk,
-                       nunits, c2, scale);
+    const Units units = split_units(nbh, N, kSplitBlocks);
+    hipLaunchKernelGGL(dead ? global_bwd_dq<true> : global_bwd_dq<false>, split_grid(units), dim3(256), 0, st, static_cast<const bf16raw *>(q),
+                       static_cast<const bf16raw *>(k), static_cast<const bf16raw *>(v), static_cast<const bf16raw *>(dout), kt, L2, Dv,
+                       static_cast<bf16raw *>(dq), N, Npad, units, c2, scale);
     S2_HIP_CHECK(hipGetLastError());
     return S2_OK;
 }
