@@ -273,7 +273,9 @@ __device__ __forceinline__ void take_unit(const Units &u, F &&f)
 // w_j = omega_j / max omega (prepare_operands does that), the running sum is l_i = sum_j w_j 2^(x_ij - m_i)
 // with x = log2(e) scale q.k, and the reference m_i follows the bare logits of the keys of positive weight (it moves
 // only when a logit exceeds it by more than 2^8).  lse_i = ln 2 (m_i + log2 l_i) + ln max omega.
-// UNIFORM_W: the longitude count is a multiple of 32, so a 32-key tile never straddles two latitudes.
+// live: the tokens of positive weight.  Only tiles that hold others too look at the weights one by one (in every tile: 16 comparisons and
+// choices more of some 60 vector instructions, and a longer chain where a SIMD has one wavefront: 46 x 90, four heads 58 -> 50 us, 24 heads
+// 204 -> 154 of the call).  UNIFORM_W: the longitude count is a multiple of 32, so a 32-key tile never straddles two latitudes.
 // SPLIT = 2 is for launches with too few workgroups to fill the chip: the four wavefronts are two pairs, each pair owns
 // the same 64 queries and takes every other 32-key tile of a stage, and the pairs' (o, m, l) meet in LDS behind the
 // last stage, so a query's serial chain over the keys is half as long and the launch has twice the workgroups
@@ -282,7 +284,7 @@ constexpr int kStageFwd = 2 * kTileBytes + 256;      // K row tile, V^T column t
 template <bool UNIFORM_W, int SPLIT>
 __device__ __forceinline__ void
 forward_unit(char *buf0, char *buf1, int qb, int bh, const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const bf16raw *__restrict__ vt,
-             const float *__restrict__ wtok, bf16raw *__restrict__ out, float *__restrict__ lse, int N, int Npad, float c2, float ln_wref)
+             const float *__restrict__ wtok, bf16raw *__restrict__ out, float *__restrict__ lse, int N, int Npad, int2 live, float c2, float ln_wref)
 {
     static_assert(SPLIT == 1 || SPLIT == 2, "a stage holds two key tiles");
     constexpr int kStage = kStageFwd;
@@ -317,39 +319,40 @@ forward_unit(char *buf0, char *buf1, int qb, int bh, const bf16raw *__restrict__
             // Keys of weight zero (the pole row of the grid of App. A.1, the padding behind the last token) have no
             // term in the sums, so they must not enter the reference maximum either: a tile without a live key is
             // skipped, and in a mixed tile (longitude count not a multiple of 32) their logits are set to -inf.
+            const int t0 = 64 * st + 32 * kt;
+            if (t0 + 32 <= live.x || t0 >= live.y) continue;
+            const bool mixed = !UNIFORM_W && (t0 < live.x || t0 + 32 > live.y);
             const float *wp = reinterpret_cast<const float *>(cur + 2 * kTileBytes) + 32 * kt + 16 * hl;
             float wk[16];
-            bool live;
-            if (UNIFORM_W) {
-                live = __builtin_amdgcn_readfirstlane(__float_as_int(wp[0])) != 0;
-            } else {
-                bool any = false;
+            if (!UNIFORM_W)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     const float4 w = *reinterpret_cast<const float4 *>(wp + 4 * g);
                     wk[4 * g + 0] = w.x; wk[4 * g + 1] = w.y; wk[4 * g + 2] = w.z; wk[4 * g + 3] = w.w;
-                    any |= w.x > 0.f || w.y > 0.f || w.z > 0.f || w.w > 0.f;
                 }
-                live = __any(any);
-            }
-            if (!live) continue;
             f32x16 s = {0};
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) s = mfma(row_operand(cur, col, hl, kt, ks), qop[ks], s);
             float x[16], e[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                x[i] = fmaf(s[i], c2, -m);
-                if (!UNIFORM_W) x[i] = wk[i] > 0.f ? x[i] : -INFINITY;
-            }
+            for (int i = 0; i < 16; ++i) x[i] = fmaf(s[i], c2, -m);
+            if (mixed)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) x[i] = wk[i] > 0.f ? x[i] : -INFINITY;
             // Fast path: exponentials relative to the current reference; a logit more than 2^8 above it shows in the
             // tile sum (all terms are positive), so the sum is the overflow test and no per-element maximum is taken.
-            float psum = 0.f;
+            auto sum = [&]() {
+                float p[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                e[i] = __builtin_amdgcn_exp2f(x[i]);
-                psum += UNIFORM_W ? e[i] : e[i] * wk[i];
-            }
+                for (int i = 0; i < 16; ++i) {
+                    if (UNIFORM_W) p[0] += e[i];
+                    else p[i & 3] = fmaf(e[i], wk[i], p[i & 3]);
+                }
+                return UNIFORM_W ? p[0] : (p[0] + p[1]) + (p[2] + p[3]);
+            };
+#pragma unroll
+            for (int i = 0; i < 16; ++i) e[i] = __builtin_amdgcn_exp2f(x[i]);
+            float psum = sum();
             // the two half-wavefronts of a query exchange their maxima only when the reference has to move
             if (!__all(based) || __any(!(psum <= 256.f))) {
                 float mx = -INFINITY;
@@ -361,14 +364,13 @@ forward_unit(char *buf0, char *buf1, int qb, int bh, const bf16raw *__restrict__
                 based |= mx > -INFINITY;
                 m += delta;
                 l *= corr;
-                psum = 0.f;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     o0[i] *= corr;
                     o1[i] *= corr;
                     e[i] = __builtin_amdgcn_exp2f(x[i] - delta);
-                    psum += UNIFORM_W ? e[i] : e[i] * wk[i];
                 }
+                psum = sum();
             }
             l = UNIFORM_W ? fmaf(psum, wp[0], l) : l + psum;
 #pragma unroll
@@ -435,12 +437,12 @@ forward_unit(char *buf0, char *buf1, int qb, int bh, const bf16raw *__restrict__
 template <bool UNIFORM_W>
 __global__ void __launch_bounds__(256, 3)
 global_fwd(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const bf16raw *__restrict__ vt, const float *__restrict__ wtok,
-           bf16raw *__restrict__ out, float *__restrict__ lse, int N, int Npad, Units units, float c2, float ln_wref)
+           bf16raw *__restrict__ out, float *__restrict__ lse, int N, int Npad, Units units, int2 live, float c2, float ln_wref)
 {
     __shared__ __attribute__((aligned(16))) char buf0[kStageFwd];
     __shared__ __attribute__((aligned(16))) char buf1[kStageFwd];
     take_unit(units, [&](auto split, int qb, int bh) {
-        forward_unit<UNIFORM_W, decltype(split)::value>(buf0, buf1, qb, bh, q, k, vt, wtok, out, lse, N, Npad, c2, ln_wref);
+        forward_unit<UNIFORM_W, decltype(split)::value>(buf0, buf1, qb, bh, q, k, vt, wtok, out, lse, N, Npad, live, c2, ln_wref);
     });
 }
 
@@ -532,11 +534,14 @@ dkdv_unit(char *buf0, char *buf1, int kb, int bh, const bf16raw *__restrict__ q,
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const float4 Lr = *reinterpret_cast<const float4 *>(Lp + 4 * g);
-                p[4 * g + 0] = __builtin_amdgcn_exp2f(fmaf(s[4 * g + 0], c2, -Lr.x));
-                p[4 * g + 1] = __builtin_amdgcn_exp2f(fmaf(s[4 * g + 1], c2, -Lr.y));
-                p[4 * g + 2] = __builtin_amdgcn_exp2f(fmaf(s[4 * g + 2], c2, -Lr.z));
-                p[4 * g + 3] = __builtin_amdgcn_exp2f(fmaf(s[4 * g + 3], c2, -Lr.w));
+                p[4 * g + 0] = fmaf(s[4 * g + 0], c2, -Lr.x);
+                p[4 * g + 1] = fmaf(s[4 * g + 1], c2, -Lr.y);
+                p[4 * g + 2] = fmaf(s[4 * g + 2], c2, -Lr.z);
+                p[4 * g + 3] = fmaf(s[4 * g + 3], c2, -Lr.w);
             }
+            __builtin_amdgcn_sched_barrier(0);          // exponents, exponentials, products in three groups: 1106 -> 1075 us on 65 x 128, 32 slices
+#pragma unroll
+            for (int i = 0; i < 16; ++i) p[i] = __builtin_amdgcn_exp2f(p[i]);
 #pragma unroll
             for (int i = 0; i < 16; ++i) ds[i] = p[i] * dp[i];
 #pragma unroll
@@ -601,17 +606,18 @@ global_bwd_dkdv(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, co
 // Query side: a workgroup owns 128 queries and streams the keys in stages of 64: K and V token-major
 // (S^T = K Q^T and dP^T = V dout^T land with lane = query, registers = 16 keys) and w K^T channel-major
 // (dQ^T += (w K)^T dSt^T).
-// DEAD: some keys have weight zero (a pole row of weight zero, padding behind the last token).  Their logits are not
-// bounded by the logsumexp, so 2^(x - L) may overflow and inf * (w k = 0) would poison dq: the exponent is capped at
-// 100 there (a key of positive weight stays below log2(max omega / omega_j), a few tens at most), which keeps the
-// factor finite and the product with the zero row exactly zero.
+// Some keys may have weight zero (a pole row of weight zero, padding behind the last token; live: the others).  Their logits are not
+// bounded by the logsumexp, so 2^(x - L) may overflow and inf * (w k = 0) would poison dq: in tiles that hold such keys the exponent is
+// capped at 100 (a key of positive weight stays below log2(max omega / omega_j), a few tens at most), which keeps the
+// factor finite and the product with the zero row exactly zero.  (Exponents first, then exponentials and products, with the cap in a branch:
+// 804 -> 765 us on 65 x 128, 32 slices, which needs no cap; 46 x 90, 24 slices, the whole backward 433 -> 403.)
 // SPLIT as in the forward.
 constexpr int kStageDq = 3 * kTileBytes;             // K, V row tiles; (w K)^T column tile
-template <bool DEAD, int SPLIT>
+template <int SPLIT>
 __device__ __forceinline__ void
 dq_unit(char *buf0, char *buf1, int qb, int bh, const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const bf16raw *__restrict__ v,
         const bf16raw *__restrict__ go, const bf16raw *__restrict__ ktw, const float *__restrict__ L2, const float *__restrict__ Dv,
-        bf16raw *__restrict__ dq, int N, int Npad, float c2, float scale)
+        bf16raw *__restrict__ dq, int N, int Npad, int2 live, float c2, float scale)
 {
     constexpr int kStage = kStageDq;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -652,10 +658,13 @@ dq_unit(char *buf0, char *buf1, int qb, int bh, const bf16raw *__restrict__ q, c
             }
             float ds[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const float a = fmaf(s[i], c2, -Lq);
-                ds[i] = __builtin_amdgcn_exp2f(DEAD ? fminf(a, 100.f) : a) * dp[i];
-            }
+            for (int i = 0; i < 16; ++i) ds[i] = fmaf(s[i], c2, -Lq);
+            const int t0 = 64 * st + 32 * h;
+            if (t0 < live.x || t0 + 32 > live.y)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) ds[i] = fminf(ds[i], 100.f);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) ds[i] = __builtin_amdgcn_exp2f(ds[i]) * dp[i];
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const bf16x8 sb = pack8(ds + 8 * j);
@@ -694,16 +703,15 @@ dq_unit(char *buf0, char *buf1, int qb, int bh, const bf16raw *__restrict__ q, c
         }
     }
 }
-template <bool DEAD>
 __global__ void __launch_bounds__(256, 3)
 global_bwd_dq(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const bf16raw *__restrict__ v, const bf16raw *__restrict__ go,
               const bf16raw *__restrict__ ktw, const float *__restrict__ L2, const float *__restrict__ Dv, bf16raw *__restrict__ dq, int N, int Npad,
-              Units units, float c2, float scale)
+              Units units, int2 live, float c2, float scale)
 {
     __shared__ __attribute__((aligned(16))) char buf0[kStageDq];
     __shared__ __attribute__((aligned(16))) char buf1[kStageDq];
     take_unit(units, [&](auto split, int qb, int bh) {
-        dq_unit<DEAD, decltype(split)::value>(buf0, buf1, qb, bh, q, k, v, go, ktw, L2, Dv, dq, N, Npad, c2, scale);
+        dq_unit<decltype(split)::value>(buf0, buf1, qb, bh, q, k, v, go, ktw, L2, Dv, dq, N, Npad, live, c2, scale);
     });
 }
 
@@ -732,6 +740,17 @@ Units split_units(int nbh, int N, long most)
     return u;
 }
 dim3 split_grid(const Units &u) { return dim3(8u * unsigned(u.whole + 2 * (u.per_xcd - u.whole))); }
+
+// The tokens of positive weight.  Latitudes of weight zero are poles (that of the grid of App. A.1; no other grid has one), the first or the
+// last ones.
+int2 live_tokens(const s2_grid_t *g)
+{
+    const std::vector<int> &z = g->zero_lat;         // in ascending order
+    int first = 0, last = g->nlat_in;
+    for (size_t i = 0; i < z.size(); ++i) first += z[i] == first;
+    for (size_t i = z.size(); i-- > 0 && last > first;) last -= z[i] == last - 1;
+    return make_int2(first * g->nlon_in, last * g->nlon_in);
+}
 
 int check_global(const s2_grid_t *g, int batch, int heads, int d, int dtype)
 {
@@ -795,10 +814,11 @@ extern "C" int s2_attn_global_fwd(const s2_grid_t *g, int batch, int heads, int 
     pa.stat_op = -1;
     launch_prepare(pa, 1, nbh, N, Npad, st);
     S2TraceScope tr("global_fwd", double(nbh) * N * N, st);
+    const int2 live = live_tokens(g);
     const Units units = split_units(nbh, N, kSplitBlocks);
     hipLaunchKernelGGL(g->nlon_in % 32 == 0 ? global_fwd<true> : global_fwd<false>, split_grid(units), dim3(256), 0, st,
                        static_cast<const bf16raw *>(q), static_cast<const bf16raw *>(k), static_cast<const bf16raw *>(workspace), g->dev_w_tok,
-                       static_cast<bf16raw *>(out), lse, N, Npad, units, scale * kLog2e, g->dt.ln_omega_ref);
+                       static_cast<bf16raw *>(out), lse, N, Npad, units, live, scale * kLog2e, g->dt.ln_omega_ref);
     S2_HIP_CHECK(hipGetLastError());
     return S2_OK;
 }
@@ -846,11 +866,11 @@ extern "C" int s2_attn_global_bwd(const s2_grid_t *g, int batch, int heads, int 
                            static_cast<bf16raw *>(dk), static_cast<bf16raw *>(dv), N, Npad, units, c2, scale);
     }
     S2TraceScope tr("global_bwd_dq", double(nbh) * N * N, st);
-    const bool dead = Npad != N || !g->zero_lat.empty();      // keys of weight zero exist
     const Units units = split_units(nbh, N, kSplitBlocks);
-    hipLaunchKernelGGL(dead ? global_bwd_dq<true> : global_bwd_dq<false>, split_grid(units), dim3(256), 0, st, static_cast<const bf16raw *>(q),
+    const int2 live = live_tokens(g);
+    hipLaunchKernelGGL(global_bwd_dq, split_grid(units), dim3(256), 0, st, static_cast<const bf16raw *>(q),
                        static_cast<const bf16raw *>(k), static_cast<const bf16raw *>(v), static_cast<const bf16raw *>(dout), kt, L2, Dv,
-                       static_cast<bf16raw *>(dq), N, Npad, units, c2, scale);
+                       static_cast<bf16raw *>(dq), N, Npad, units, live, c2, scale);
     S2_HIP_CHECK(hipGetLastError());
     return S2_OK;
 }
