@@ -276,6 +276,42 @@ static bool whole_latitudes(std::vector<int> &blo, std::vector<int> &bn, std::ve
     return true;
 }
 
+// The lists of workgroups for launches so small that the longest of them bounds the launch (s2_split_list).  Workgroups of 0.6 times the
+// most chunks and more go in two (four) parts of two patches (one): the wavefronts that share a patch take a half (a quarter) of a stage's tiles,
+// which makes a stage some 1.6 (2.3) times as fast, so that the rest are about as long as what becomes of the longest.  From 0.4 times on: as
+// good for one slice, for two and more 5 to 30 % slower; from 0.8 on 10 % slower for one.  Heaviest first.
+static void split_patches(int nU, s2_grid::Patches &p)
+{
+    std::vector<int> chunks;             // of the list's workgroups, the further parts of their segments among them
+    for (const int2 &at : p.list) {
+        int t = at.x, n = p.seg[2 * t + 1].x;
+        while (p.seg[2 * t + 1].z) n += p.seg[2 * ++t + 1].x;
+        chunks.push_back(n);
+    }
+    const int most = chunks.empty() ? 0 : *std::max_element(chunks.begin(), chunks.end());
+    for (int i = 0; i < 2; ++i) {
+        const int share_lg = 1 + i;
+        double sum = 0.0;
+        std::vector<std::pair<double, int2>> order;
+        for (size_t k = 0; k < p.list.size(); ++k) {
+            const int2 at = p.list[k];
+            const int W = 16 >> p.seg[2 * at.x].y;
+            if (chunks[k] < 0.6 * most) {
+                order.push_back({double(chunks[k]), at});
+                sum += chunks[k];
+                continue;
+            }
+            for (int c = at.y; c < std::min(nU, at.y + kS2PatchWaves * W); c += (kS2PatchWaves * W) >> share_lg)
+                order.push_back({chunks[k] / (i ? 2.3 : 1.6), make_int2(at.x, c | share_lg << 16)});
+            sum += (i ? 3.0 : 2.0) * chunks[k];
+        }
+        std::stable_sort(order.begin(), order.end(), [](const auto &a, const auto &b) { return a.first > b.first; });
+        p.split[i].clear();
+        for (const auto &o : order) p.split[i].push_back(o.second);
+        p.split_work[i] = most > 0 ? sum / most : 0.0;
+    }
+}
+
 // Segments and workgroups of the patch kernels for one kind of owners.  A wavefront owns 16 points, 1 x 16, 2 x 8 or 4 x 4 rows x
 // columns: a square patch meets the fewest walked columns where arcs are short; where they are long, owners of one row share
 // more of theirs.  Each group of four rows takes the shape with the fewest chunks of four columns to walk (counted, not measured), a
@@ -382,6 +418,7 @@ static void build_patches(const std::vector<int> &blo, const std::vector<int> &b
             if (t == seg_of[s] || p.seg[2 * t - 1].z == 0)                             // else a further part of the one before
                 for (int c = 0; c < nU; c += kS2PatchWaves * (16 >> shape[s])) p.list.push_back(make_int2(t, c));
     }
+    split_patches(nU, p);
 }
 
 // Segments and workgroups of the forward by columns (S2ColumnRow).
@@ -508,6 +545,8 @@ static int upload_tables(s2_grid *g)
         parts.push_back({p->rows.data(), p->rows.size() * sizeof(S2PatchRow), 0});
         parts.push_back({p->list.data(), p->list.size() * sizeof(int2), 0});
     }
+    for (const s2_grid::Patches *p : {&g->vo_patch, &g->vi_patch})
+        for (const auto &l : p->split) parts.push_back({l.data(), l.size() * sizeof(int2), 0});
     parts.push_back({g->columns.seg.data(), g->columns.seg.size() * sizeof(int4), 0});
     parts.push_back({g->columns.rows.data(), g->columns.rows.size() * sizeof(S2ColumnRow), 0});
     parts.push_back({g->columns.list.data(), g->columns.list.size() * sizeof(int2), 0});
@@ -563,8 +602,9 @@ static int upload_tables(s2_grid *g)
         q.patch = ap(23 + 3 * i);
         q.npatch = int(p.list.size());
         q.step = p.step;
+        for (int j = 0; j < 2; ++j) q.split[j] = {ap(27 + 2 * i + j), int(p.split[j].size()), p.split_work[j]};
     }
-    t.columns = {reinterpret_cast<const int4 *>(base + parts[27].off), reinterpret_cast<const int4 *>(base + parts[28].off), ap(29),
+    t.columns = {reinterpret_cast<const int4 *>(base + parts[31].off), reinterpret_cast<const int4 *>(base + parts[32].off), ap(33),
                  int(g->columns.list.size()), 1};
     g->on_device = true;
     return S2_OK;

@@ -32,6 +32,13 @@ struct S2BandSide {
         int npatch;
         // walked columns per owner column: 1, the rows are classes; c_walk, they are whole latitudes and offsets count their columns
         int step;
+        // for small launches: the same points, those of heavy workgroups in workgroups of two patches and of one, which two and four
+        // wavefronts share
+        struct Split {
+            const int2 *list;     // segment, first column + (log2(wavefronts that share a patch) << 16)
+            int n;
+            double work;          // of a slice, in workgroups as heavy as the heaviest unsplit one; parts two or three times what they were
+        } split[2];
     } patches;
 };
 
@@ -116,8 +123,9 @@ struct s2_grid {
     struct Patches {
         std::vector<int4> seg;
         std::vector<S2PatchRow> rows;
-        std::vector<int2> list;
+        std::vector<int2> list, split[2];
         int step = 1;
+        double split_work[2] = {};
     } vo_patch, vi_patch;
     struct Columns {
         std::vector<int4> seg;

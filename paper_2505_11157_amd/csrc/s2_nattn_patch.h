@@ -4,7 +4,7 @@
 #include "s2_internal.h"
 #include "s2_nattn_band.h"
 
-template <class T, int MODE>
+template <class T, int MODE, bool SPLIT = false>
 struct PatchKernels {
     static int configure();
     static void fwd(const S2DeviceTables &t, int nbh, int d, int e, float scale, const T *q, const T *k, const T *v, T *out, float *lse, hipStream_t st);
@@ -17,6 +17,12 @@ template <int MODE>
 using PatchSet = PatchKernels<float, MODE>;
 template <int MODE>
 using PatchSet16 = PatchKernels<unsigned short, MODE>;      // bf16 tensors
+
+// The same on the lists where wavefronts share patches (S2BandSide::Patches::split)
+template <int MODE>
+using SplitSet = PatchKernels<float, MODE, true>;
+template <int MODE>
+using SplitSet16 = PatchKernels<unsigned short, MODE, true>;
 
 // The forward by columns (S2ColumnRow), float32 d = e = 32
 int s2_nattn_columns_configure();

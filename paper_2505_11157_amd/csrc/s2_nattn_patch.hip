@@ -7,12 +7,30 @@ int s2_nattn_band_configure()
 {
     return PatchSet<kWide>::configure() || PatchSet<kNarrow>::configure() || PatchSet<kRagged>::configure() || PatchSet<kPairs>::configure() ||
            PatchSet16<kWide>::configure() || PatchSet16<kNarrow>::configure() || PatchSet16<kRagged>::configure() || PatchSet16<kPairs>::configure() ||
+           SplitSet<kWide>::configure() || SplitSet<kNarrow>::configure() || SplitSet<kRagged>::configure() || SplitSet<kPairs>::configure() ||
+           SplitSet16<kWide>::configure() || SplitSet16<kNarrow>::configure() || SplitSet16<kRagged>::configure() || SplitSet16<kPairs>::configure() ||
            s2_nattn_columns_configure();
 }
 
 bool s2_nattn_patch_supported(const S2DeviceTables &t, int d, int e)
 {
     return d <= 64 && e <= 64 && t.band_rows_ok && !s2_debug_flag(S2_DEBUG_NO_MFMA);
+}
+
+// f(set) with the launchers for owners of a side, of float32 or bf16 tensors
+template <class F>
+static void on_patches(const S2BandSide &b, int nbh, int d, int e, F &&f)
+{
+    const int mode = s2_band_mode(b, d, e, sizeof(float));
+    if (s2_split_list(b.patches, nbh)) s2_by_band_mode<SplitSet>(mode, f);
+    else s2_by_band_mode<PatchSet>(mode, f);
+}
+template <class F>
+static void on_patches16(const S2BandSide &b, int nbh, int d, int e, F &&f)
+{
+    const int mode = s2_band_mode(b, d, e, 2);
+    if (s2_split_list(b.patches, nbh)) s2_by_band_mode<SplitSet16>(mode, f);
+    else s2_by_band_mode<PatchSet16>(mode, f);
 }
 
 static double pair_count(const double (&p)[4], int nbh) { return nbh * (p[0] + p[1] + p[2] + p[3]); }
@@ -26,7 +44,7 @@ int s2_nattn_fwd_patch(const S2DeviceTables &t, int nbh, int d, int e, float sca
         s2_nattn_fwd_columns(t, nbh, scale, q, k, v, out, lse, st);
         return 0;
     }
-    s2_by_band_mode<PatchSet>(s2_band_mode(t.side_out, d, e, sizeof(float)), [&](auto set) { set.fwd(t, nbh, d, e, scale, q, k, v, out, lse, st); });
+    on_patches(t.side_out, nbh, d, e, [&](auto set) { set.fwd(t, nbh, d, e, scale, q, k, v, out, lse, st); });
     return 0;
 }
 
@@ -37,10 +55,10 @@ int s2_nattn_bwd_patch(const S2DeviceTables &t, int nbh, int d, int e, float sca
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
     {
         S2TraceScope tr("nattn_bwd_dq_patch", pair_count(t.fwd_pairs, nbh), st);
-        s2_by_band_mode<PatchSet>(s2_band_mode(t.side_out, d, e, sizeof(float)), [&](auto set) { set.dq(t, nbh, d, e, scale, q, k, v, o, lse, go, dq, Dws, st); });
+        on_patches(t.side_out, nbh, d, e, [&](auto set) { set.dq(t, nbh, d, e, scale, q, k, v, o, lse, go, dq, Dws, st); });
     }
     S2TraceScope tr("nattn_bwd_dkdv_patch", pair_count(t.bwd_pairs, nbh), st);
-    s2_by_band_mode<PatchSet>(s2_band_mode(t.side_in, d, e, sizeof(float)), [&](auto set) { set.dkdv(t, nbh, d, e, scale, q, k, v, lse, go, Dws, dk, dv, st); });
+    on_patches(t.side_in, nbh, d, e, [&](auto set) { set.dkdv(t, nbh, d, e, scale, q, k, v, lse, go, Dws, dk, dv, st); });
     return 0;
 }
 
@@ -51,7 +69,7 @@ int s2_nattn_fwd_patch_bf16(const S2DeviceTables &t, int nbh, int d, int e, floa
 {
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
     S2TraceScope tr("nattn_fwd_patch", pair_count(t.fwd_pairs, nbh), st);
-    s2_by_band_mode<PatchSet16>(s2_band_mode(t.side_out, d, e, 2), [&](auto set) {
+    on_patches16(t.side_out, nbh, d, e, [&](auto set) {
         set.fwd(t, nbh, d, e, scale, in16(q), in16(k), in16(v), static_cast<unsigned short *>(out), lse, st);
     });
     return 0;
@@ -61,7 +79,7 @@ int s2_nattn_bwd_dq_patch_bf16(const S2DeviceTables &t, int nbh, int d, int e, f
 {
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
     S2TraceScope tr("nattn_bwd_dq_patch", pair_count(t.fwd_pairs, nbh), st);
-    s2_by_band_mode<PatchSet16>(s2_band_mode(t.side_out, d, e, 2), [&](auto set) {
+    on_patches16(t.side_out, nbh, d, e, [&](auto set) {
         set.dq(t, nbh, d, e, scale, in16(q), in16(k), in16(v), in16(o), lse, in16(go), static_cast<unsigned short *>(dq), Dws, st);
     });
     return 0;
@@ -71,7 +89,7 @@ int s2_nattn_bwd_dkdv_patch_bf16(const S2DeviceTables &t, int nbh, int d, int e,
 {
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
     S2TraceScope tr("nattn_bwd_dkdv_patch", pair_count(t.bwd_pairs, nbh), st);
-    s2_by_band_mode<PatchSet16>(s2_band_mode(t.side_in, d, e, 2), [&](auto set) {
+    on_patches16(t.side_in, nbh, d, e, [&](auto set) {
         set.dkdv(t, nbh, d, e, scale, in16(q), in16(k), in16(v), lse, in16(go), Dws, static_cast<unsigned short *>(dk), static_cast<unsigned short *>(dv), st);
     });
     return 0;

@@ -52,6 +52,13 @@
 // Owners that are the two classes of a finer grid are loaded and stored by latitudes (kPairs), four columns at a time, two of either class;
 // an owner row alone is every second column of its latitude (129 x 256 -> 257 x 512, 8 slices, float32 d = 32: dq 0.268 -> 0.239 ms, the
 // mirror image's dk, dv 0.341 -> 0.316; 65 x 128 -> 129 x 256, 8 slices, bf16 d = 64: forward 72 -> 58 us, backward 171 -> 141).
+//
+// Shared patches (Geo::SPLIT).  Of a small launch the workgroups near the poles are what is left when all others are done, a chain of stages
+// with one wavefront on each SIMD (64 x 128, theta 7 pi / 64, float32 d = 32: 38 us for one slice, 5.5 for each further one of many).
+// There two or all four wavefronts of heavy workgroups own one patch: each takes a part of every stage's tiles, and their sums meet in LDS
+// at the end (split_patches; s2_split_list has the rule and figures).  These kernels have registers and LDS for longer stages than the others, as
+// barriers count for more than workgroups on a compute unit.  One slice, forward / backward, us: 64 x 128 38 / 101 -> 24 / 56,
+// bf16 25 / 60 -> 15 / 36; 129 x 256, theta 4 pi / 128, d = 64 70 / 177 -> 55 / 130; 33 x 64, theta 4 pi / 33, d = 32 19 / 48 -> 13 / 29.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -75,10 +82,11 @@ typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short bf16raw;      // storage of a bf16 tensor
 constexpr unsigned kAgain = 0x7fc0a9a1u;     // in place of a result that s2_nattn_exact.h evaluates: not to be stored
 
-// Channels, chunks per stage, wavefronts per SIMD the registers are held to.
-template <class T_, int D_, int CAP_, int WAVES_>
+// Channels, chunks per stage, wavefronts per SIMD the registers are held to; SPLIT: wavefronts share patches (S2BandSide::Patches::split).
+template <class T_, int D_, int CAP_, int WAVES_, bool SPLIT_ = false>
 struct Geo {
     using T = T_;
+    static constexpr bool SPLIT = SPLIT_;
     static constexpr int TERMS = sizeof(T) == 4 ? kTerms : 1;
     static constexpr int D = D_, NW = kS2PatchWaves, CAP = CAP_, WAVES = WAVES_, NT = 64 * NW;
     static constexpr int UNITS = CAP + 4;                   // 8-byte units per channel row
@@ -139,6 +147,9 @@ __device__ __forceinline__ int here_s(int x)
 // Place of a workgroup and of a lane's owner
 struct PatchWhere {
     int nU, first, lg, W, W0, wc, bh, lane, wave, n, g, tid, sub, u;
+    int pw, own_end;                 // the workgroup's patch that the wavefront works on; end of the workgroup's own columns
+    int share, share_lg;             // its number among the wavefronts of that patch, log2 of how many these are
+    bool lead;                       // the first of them, whose the results are
     int own;                         // the lane's owner row
     bool active;                     // the lane's owner is a point
     size_t plane_own, plane_walk, own_at;
@@ -162,6 +173,7 @@ struct PatchWhere {
         const int4 s0 = a.seg[2 * seg], s1 = a.seg[2 * seg + 1];
         rmin = s0.z; nrows = s0.w; total = s1.x; rows_at = s1.y; more = s1.z;
     }
+    template <bool SPLIT = false>
     __device__ __forceinline__ void set(const BandArgs &a, int thread = threadIdx.x)
     {
         nU = a.b.nU;
@@ -194,8 +206,13 @@ struct PatchWhere {
         inv_nW = 1.f / float(nW);
         const bool row_ok = first + sub < n_own;
         set_row(row_ok ? first + sub : first);
-        W0 = at.y;
-        wc = W0 + wave * (W > 4 ? W : 4);
+        W0 = SPLIT ? at.y & 0xffff : at.y;
+        share_lg = SPLIT ? __builtin_amdgcn_readfirstlane(at.y >> 16) : 0;
+        share = wave & ((1 << share_lg) - 1);
+        lead = !SPLIT || share == 0;
+        pw = wave >> share_lg;
+        own_end = SPLIT ? imin(nU, W0 + (kS2PatchWaves >> share_lg) * W) : nU;
+        wc = W0 + pw * (W > 4 ? W : 4);
         u = wc + (n & (W - 1));
         su = step * u;
         active = row_ok && u < nU;
@@ -213,12 +230,17 @@ struct PatchWhere {
     __device__ __forceinline__ size_t row_walked(int r) const { return stride == 1 ? size_t(r) * nlon_walk : walk_at(r); }
     // the chunk of the workgroup's own points that holds the points 4 j .. 4 j + 3 of this wavefront
     template <int MODE>
-    __device__ __forceinline__ int own_slot(int j, int nw) const
+    __device__ __forceinline__ int own_slot(int j, int nw) const { return slot_of<MODE>(j, nw, pw); }
+    template <int MODE>
+    __device__ __forceinline__ int slot_of(int j, int nw, int patch) const
     {
-        if (MODE == kColumns) return 4 * wave + j;
+        if (MODE == kColumns) return 4 * patch + j;
         const int h = 2 - here_s(lg);    // log2(chunks per row of a wavefront)
-        return (j >> h) * (nw << h) + (wave << h) + (j & ((1 << h) - 1));
+        return (j >> h) * (nw << h) + (patch << h) + (j & ((1 << h) - 1));
     }
+    // the wavefront's part of a stage's key tiles
+    __device__ __forceinline__ int tiles_from(int ntile) const { return ntile * share >> share_lg; }
+    __device__ __forceinline__ int tiles_to(int ntile) const { return ntile * (share + 1) >> share_lg; }
     // f(i, u) for every owner i whose bit is set, with the row set to the owner's
     template <class F>
     __device__ __forceinline__ void each(unsigned owners, F &&f)
@@ -231,6 +253,12 @@ struct PatchWhere {
         }
     }
 };
+struct SplitWhere : PatchWhere {
+    __device__ __forceinline__ void set(const BandArgs &a, int thread = threadIdx.x) { PatchWhere::set<true>(a, thread); }
+};
+template <class G>
+using WhereOf = std::conditional_t<G::SPLIT, SplitWhere, PatchWhere>;
+
 // The chunks of a workgroup: looked up LOOK at a time, one per lane, and staged CAP at a time.
 template <class G, int MODE>
 struct Chunks {
@@ -733,6 +761,30 @@ __device__ __forceinline__ void put_results(const f32x4 (&acc)[G::D / 16], float
         for (int rr = 0; rr < 4; ++rr)
             p[(16 * mt + rr) * G::PITCH] = again && !(fabsf(acc[mt][rr]) < INFINITY) ? __builtin_bit_cast(float, kAgain) : acc[mt][rr] * factor;
 }
+// SPLIT: the sums of the wavefronts that share a patch, added up in the first of them in the order of their numbers; LDS is free before, and
+// after the next barrier again
+template <class G, int MODE>
+__device__ __forceinline__ void put_shares(const f32x4 (&acc)[G::D / 16], float *tile, const PatchWhere &w)
+{
+    float *p = tile + 4 * w.g * G::PITCH + 4 * w.template slot_of<MODE>(w.lane >> 2 & 3, G::NW, w.wave) + (w.lane & 3);
+#pragma unroll
+    for (int mt = 0; mt < G::D / 16; ++mt)
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) p[(16 * mt + rr) * G::PITCH] = acc[mt][rr];
+}
+template <class G, int MODE>
+__device__ __forceinline__ void add_shares(f32x4 (&acc)[G::D / 16], const float *tile, const PatchWhere &w)
+{
+    if (!w.lead) return;
+#pragma unroll 1
+    for (int i = 1; i < 1 << w.share_lg; ++i) {
+        const float *p = tile + 4 * w.g * G::PITCH + 4 * w.template slot_of<MODE>(w.lane >> 2 & 3, G::NW, w.wave + i) + (w.lane & 3);
+#pragma unroll
+        for (int mt = 0; mt < G::D / 16; ++mt)
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) acc[mt][rr] += p[(16 * mt + rr) * G::PITCH];
+    }
+}
 // is the lane's channel of the wavefront's owner i marked
 template <class G, int MODE>
 __device__ __forceinline__ bool marked(const float *tile, const PatchWhere &w, int i)
@@ -766,14 +818,14 @@ __device__ __forceinline__ void store_results(typename G::T *slice, int nch, con
         return;
     }
     const int h = 2 - here_s(w.lg), tid = here_v(w.tid), x = tid % G::OWN, c0 = tid / G::OWN;
-    int sub = (x / G::NW) >> h, u = w.W0 + 4 * (x - G::NW * (sub << h)), end = w.nU, step = w.c_own;
+    int sub = (x / G::NW) >> h, u = w.W0 + 4 * (x - G::NW * (sub << h)), end = w.own_end, step = w.c_own;
     const bool two = MODE == kPairs && w.lg > 0;
     PairPiece o;
     if (two) {
         o.template set<G>(w, tid);
         sub = o.row - w.first;
         u = o.col;
-        end = 2 * w.nU;
+        end = 2 * w.own_end;
         step = 1;
     }
     if (w.first + sub >= w.n_own || u >= end) return;
@@ -819,10 +871,10 @@ nattn_fwd_patch(BandArgs a, const typename G::T *__restrict__ q, const typename 
     using T = typename G::T;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     Shared<G, MODE> &sh = *reinterpret_cast<Shared<G, MODE> *>(lds);
-    PatchWhere w;
+    WhereOf<G> w;
     w.set(a);
     const int n = w.n, g = w.g, nd = MODE == kRagged ? a.d : D, ne = MODE == kRagged ? a.e : D;
-    const bool vec = w.own_pieces<MODE>();
+    const bool vec = w.template own_pieces<MODE>();
     const T *qs = q + size_t(w.bh) * nd * w.plane_own, *ks = k + size_t(w.bh) * nd * w.plane_walk, *vs = v + size_t(w.bh) * ne * w.plane_walk;
     Place<G, MODE> at;
     at.init(w);
@@ -900,9 +952,10 @@ nattn_fwd_patch(BandArgs a, const typename G::T *__restrict__ q, const typename 
                 cut<true>(x, p);
                 acc.add(sh.b + row_at + 4 * tr[0].slot, sh.b + row_at + 4 * tr[N - 1].slot, p);
             };
-            int t = 0;
-            for (; t + 1 < ntile; t += 2) step(t, std::integral_constant<int, 2>());
-            if (t < ntile) step(t, std::integral_constant<int, 1>());
+            int t = G::SPLIT ? w.tiles_from(ntile) : 0;
+            const int t_end = G::SPLIT ? w.tiles_to(ntile) : ntile;
+            for (; t + 1 < t_end; t += 2) step(t, std::integral_constant<int, 2>());
+            if (t < t_end) step(t, std::integral_constant<int, 1>());
             acc.wait();
         }
         if (!w.more) break;
@@ -913,16 +966,37 @@ nattn_fwd_patch(BandArgs a, const typename G::T *__restrict__ q, const typename 
         if (w.total > 0) fetch(0);
     }
     acc.join_terms();
-    const float lt = group_sum(l);
+    float lt = group_sum(l);
+    if (G::SPLIT && w.share_lg > 0) {
+        float *tile = reinterpret_cast<float *>(sh.a), *stat = reinterpret_cast<float *>(sh.b);      // per wavefront: 16 references, 16 sums
+        __syncthreads();
+        if (g == 0) {
+            stat[32 * w.wave + n] = m;
+            stat[32 * w.wave + 16 + n] = lt;
+        }
+        __syncthreads();
+        const float *of = stat + 32 * (w.wave - w.share) + n;
+        float most = m;
+        for (int i = 0; i < 1 << w.share_lg; ++i) most = fmaxf(most, of[32 * i]);
+        lt = 0.f;
+        for (int i = 0; i < 1 << w.share_lg; ++i) lt = fmaf(of[32 * i + 16], __builtin_amdgcn_exp2f(of[32 * i] - most), lt);
+        const float corr = __builtin_amdgcn_exp2f(m - most);
+        m = most;
+#pragma unroll
+        for (auto &x : acc.hi) x *= corr;
+        put_shares<G, MODE>(acc.hi, tile, w);
+        __syncthreads();
+        add_shares<G, MODE>(acc.hi, tile, w);
+    }
     // owners whose sums took in a non-finite value (s2_nattn_exact.h); where it is a NaN of their own the sums are right
-    unsigned again = not_finite(acc.hi, w.active), no_lse = 0;
+    unsigned again = not_finite(acc.hi, w.active && w.lead), no_lse = 0;
     if (any_owner(again)) {
         again &= ~own_nan(own);
         no_lse = again & owner_bits(lt != lt);
     }
     __syncthreads();
-    put_results<G, MODE>(acc.hi, 1.f / lt, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
-    if (w.active && g == 0 && !(no_lse >> n & 1)) {
+    if (w.lead) put_results<G, MODE>(acc.hi, 1.f / lt, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
+    if (w.active && w.lead && g == 0 && !(no_lse >> n & 1)) {
         // the whole part of m goes into the logarithm, so that its value and the sum are no larger than the result
         const float whole = fminf(fmaxf(rintf(m), -60.f), 60.f);
         lse[size_t(w.bh) * w.plane_own + w.own_at + size_t(w.c_own) * w.u] =
@@ -930,7 +1004,7 @@ nattn_fwd_patch(BandArgs a, const typename G::T *__restrict__ q, const typename 
     }
     __syncthreads();
     store_results<G, MODE>(out + size_t(w.bh) * ne * w.plane_own, ne, reinterpret_cast<const float *>(sh.a), w, vec);
-    exact_fwd<T, PatchWhere>(again, no_lse, w.wave, [&](const PatchWhere &at, int i) { return marked<G, MODE>(reinterpret_cast<const float *>(sh.a), at, i); });
+    exact_fwd<T, WhereOf<G>>(again, no_lse, w.wave, [&](const WhereOf<G> &at, int i) { return marked<G, MODE>(reinterpret_cast<const float *>(sh.a), at, i); });
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -945,10 +1019,10 @@ nattn_bwd_dq_patch(BandArgs a, const typename G::T *__restrict__ q, const typena
     using T = typename G::T;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     SharedDq<G, MODE> &sh = *reinterpret_cast<SharedDq<G, MODE> *>(lds);
-    PatchWhere w;
+    WhereOf<G> w;
     w.set(a);
     const int n = w.n, g = w.g, nd = MODE == kRagged ? a.d : D, ne = MODE == kRagged ? a.e : D;
-    const bool vec = w.own_pieces<MODE>();
+    const bool vec = w.template own_pieces<MODE>();
     const float c2 = a.scale * kLog2e;
     const T *qs = q + size_t(w.bh) * nd * w.plane_own, *gs = go + size_t(w.bh) * ne * w.plane_own, *os = o_ + size_t(w.bh) * ne * w.plane_own;
     const T *ks = k + size_t(w.bh) * nd * w.plane_walk, *vs = v + size_t(w.bh) * ne * w.plane_walk;
@@ -988,7 +1062,7 @@ nattn_bwd_dq_patch(BandArgs a, const typename G::T *__restrict__ q, const typena
 #pragma unroll
     for (int i = g; i < G::NGO; i += 4) dsum += sh.part[i][point];
     dsum = group_sum(dsum);
-    if (w.active && g == 0) Dws[stat] = dsum;
+    if (w.active && w.lead && g == 0) Dws[stat] = dsum;
     Sums<G> acc;
     acc.zero();
     for (;;) {
@@ -1023,9 +1097,10 @@ nattn_bwd_dq_patch(BandArgs a, const typename G::T *__restrict__ q, const typena
                 cut<true>(x, p);
                 acc.add(sh.a + row_at + 4 * tr[0].slot, sh.a + row_at + 4 * tr[N - 1].slot, p);
             };
-            int t = 0;
-            for (; t + 1 < ntile; t += 2) step(t, std::integral_constant<int, 2>());
-            if (t < ntile) step(t, std::integral_constant<int, 1>());
+            int t = G::SPLIT ? w.tiles_from(ntile) : 0;
+            const int t_end = G::SPLIT ? w.tiles_to(ntile) : ntile;
+            for (; t + 1 < t_end; t += 2) step(t, std::integral_constant<int, 2>());
+            if (t < t_end) step(t, std::integral_constant<int, 1>());
             acc.wait();
         }
         if (!w.more) break;
@@ -1036,13 +1111,20 @@ nattn_bwd_dq_patch(BandArgs a, const typename G::T *__restrict__ q, const typena
         if (w.total > 0) fetch(0);
     }
     acc.join_terms();
-    unsigned again = not_finite(acc.hi, w.active);
+    if (G::SPLIT && w.share_lg > 0) {
+        float *tile = reinterpret_cast<float *>(sh.a);
+        __syncthreads();
+        put_shares<G, MODE>(acc.hi, tile, w);
+        __syncthreads();
+        add_shares<G, MODE>(acc.hi, tile, w);
+    }
+    unsigned again = not_finite(acc.hi, w.active && w.lead);
     if (any_owner(again)) again &= ~(own_nan(oq) | owner_bits(dsum != dsum || L2 != L2));       // (these are NaN throughout, as they are)
     __syncthreads();
-    put_results<G, MODE>(acc.hi, a.scale * a.omega_ref, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
+    if (w.lead) put_results<G, MODE>(acc.hi, a.scale * a.omega_ref, again >> n & 1, reinterpret_cast<float *>(sh.a), w);
     __syncthreads();
     store_results<G, MODE>(dq + size_t(w.bh) * nd * w.plane_own, nd, reinterpret_cast<const float *>(sh.a), w, vec);
-    exact_dq<T, PatchWhere>(again, w.wave, [&](const PatchWhere &at, int i) { return marked<G, MODE>(reinterpret_cast<const float *>(sh.a), at, i); });
+    exact_dq<T, WhereOf<G>>(again, w.wave, [&](const WhereOf<G> &at, int i) { return marked<G, MODE>(reinterpret_cast<const float *>(sh.a), at, i); });
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -1058,10 +1140,10 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
     using T = typename G::T;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     SharedDkdv<G, MODE> &sh = *reinterpret_cast<SharedDkdv<G, MODE> *>(lds);
-    PatchWhere w;
+    WhereOf<G> w;
     w.set(a);
     const int n = w.n, g = w.g, nd = MODE == kRagged ? a.d : D, ne = MODE == kRagged ? a.e : D;
-    const bool vec = w.own_pieces<MODE>();
+    const bool vec = w.template own_pieces<MODE>();
     const float c2 = a.scale * kLog2e;
     const T *ks = k + size_t(w.bh) * nd * w.plane_own, *vs = v + size_t(w.bh) * ne * w.plane_own;
     const T *qs = q + size_t(w.bh) * nd * w.plane_walk, *gs = go + size_t(w.bh) * ne * w.plane_walk;
@@ -1144,9 +1226,10 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
                 cut<true>(ds, p);
                 dka.add(sh.a + row_at + 4 * tr[0].slot, sh.a + row_at + 4 * tr[N - 1].slot, p);
             };
-            int t = 0;
-            for (; t + 1 < ntile; t += 2) step(t, std::integral_constant<int, 2>());
-            if (t < ntile) step(t, std::integral_constant<int, 1>());
+            int t = G::SPLIT ? w.tiles_from(ntile) : 0;
+            const int t_end = G::SPLIT ? w.tiles_to(ntile) : ntile;
+            for (; t + 1 < t_end; t += 2) step(t, std::integral_constant<int, 2>());
+            if (t < t_end) step(t, std::integral_constant<int, 1>());
             dka.wait();
             dva.wait();
         }
@@ -1159,21 +1242,32 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
     }
     dka.join_terms();
     dva.join_terms();
-    unsigned again_k = not_finite(dka.hi, w.active), again_v = not_finite(dva.hi, w.active);
+    if (G::SPLIT && w.share_lg > 0) {
+        float *tile_k = reinterpret_cast<float *>(sh.a), *tile_v = reinterpret_cast<float *>(sh.b);
+        __syncthreads();
+        put_shares<G, MODE>(dka.hi, tile_k, w);
+        put_shares<G, MODE>(dva.hi, tile_v, w);
+        __syncthreads();
+        add_shares<G, MODE>(dka.hi, tile_k, w);
+        add_shares<G, MODE>(dva.hi, tile_v, w);
+    }
+    unsigned again_k = not_finite(dka.hi, w.active && w.lead), again_v = not_finite(dva.hi, w.active && w.lead);
     if (any_owner(again_k | again_v)) {
         const unsigned nan = own_nan(ok);                    // (these are NaN throughout, as they are)
         again_k &= ~(nan | own_nan(ov));
         again_v &= ~nan;
     }
     __syncthreads();
-    put_results<G, MODE>(dka.hi, omega * a.scale, again_k >> n & 1, reinterpret_cast<float *>(sh.a), w);
-    put_results<G, MODE>(dva.hi, omega, again_v >> n & 1, reinterpret_cast<float *>(sh.b), w);
+    if (w.lead) {
+        put_results<G, MODE>(dka.hi, omega * a.scale, again_k >> n & 1, reinterpret_cast<float *>(sh.a), w);
+        put_results<G, MODE>(dva.hi, omega, again_v >> n & 1, reinterpret_cast<float *>(sh.b), w);
+    }
     __syncthreads();
     store_results<G, MODE>(dk + size_t(w.bh) * nd * w.plane_own, nd, reinterpret_cast<const float *>(sh.a), w, vec);
     store_results<G, MODE>(dv + size_t(w.bh) * ne * w.plane_own, ne, reinterpret_cast<const float *>(sh.b), w, vec);
-    exact_dkdv<T, PatchWhere>(
-        again_k | again_v, w.wave, [&](const PatchWhere &at, int i) { return marked<G, MODE>(reinterpret_cast<const float *>(sh.a), at, i); },
-        [&](const PatchWhere &at, int i) { return marked<G, MODE>(reinterpret_cast<const float *>(sh.b), at, i); });
+    exact_dkdv<T, WhereOf<G>>(
+        again_k | again_v, w.wave, [&](const WhereOf<G> &at, int i) { return marked<G, MODE>(reinterpret_cast<const float *>(sh.a), at, i); },
+        [&](const WhereOf<G> &at, int i) { return marked<G, MODE>(reinterpret_cast<const float *>(sh.b), at, i); });
 }
 
 // Calls f with the geometry for a head dimension.  More workgroups on a compute unit count for more than longer stages (twice the
@@ -1187,10 +1281,15 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
 // workgroups instead of four the forward would take 441 instead of 421, dq 521 instead of 498).  Owners that are classes of a finer
 // grid (classes) meet some 38 chunks: 24 + 14 of them make more odd tiles than 16 + 16 + 6 (257 x 512 -> 129 x 256, 8 slices: 329 -> 350).
 enum Launch { kFwd, kDq, kDkdv };
-template <class T, int MODE, Launch WHICH, class F>
+template <class T, int MODE, bool SPLIT, Launch WHICH, class F>
 void by_shape(int dmax, bool classes, F &&f)
 {
-    if constexpr (sizeof(T) == 4) {
+    if constexpr (SPLIT) {
+        constexpr bool F32 = sizeof(T) == 4;
+        if (dmax <= 16) f(Geo<T, 16, 64, 2, true>());
+        else if (dmax <= 32) f(Geo<T, 32, F32 ? 32 : 64, 2, true>());
+        else f(Geo<T, 64, F32 ? 16 : 64, 2, true>());
+    } else if constexpr (sizeof(T) == 4) {
         if (dmax <= 16) f(Geo<T, 16, 32, is_wide(MODE) && WHICH == kDkdv ? 4 : 3>());
         else if (dmax <= 32) {
             if constexpr (WHICH == kDkdv && MODE == kWide) {
@@ -1209,54 +1308,56 @@ struct PatchLaunch {
     BandArgs a;
     dim3 grid;
 };
-inline PatchLaunch patch_launch(const S2DeviceTables &t, const S2BandSide &b, int nbh, int d, int e, float scale)
+inline PatchLaunch patch_launch(const S2DeviceTables &t, const S2BandSide &b, int nbh, int d, int e, float scale, bool split)
 {
     const S2BandSide::Patches &p = b.patches;
-    return {{b, t.omega_rel, t.ln_omega_ref, t.omega_ref, scale, nbh, d, e, p.seg, p.row_rec, p.patch, p.npatch},
-            dim3(unsigned(p.npatch) * unsigned(nbh))};
+    const S2BandSide::Patches::Split *s = split ? s2_split_list(p, nbh) : nullptr;
+    const int n = s ? s->n : p.npatch;
+    return {{b, t.omega_rel, t.ln_omega_ref, t.omega_ref, scale, nbh, d, e, p.seg, p.row_rec, s ? s->list : p.patch, n},
+            dim3(unsigned(n) * unsigned(nbh))};
 }
 inline bool raise_lds(const void *f, size_t bytes) { return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)) != hipSuccess; }
 
 }  // namespace
 
-template <class T, int MODE>
-int PatchKernels<T, MODE>::configure()
+template <class T, int MODE, bool SPLIT>
+int PatchKernels<T, MODE, SPLIT>::configure()
 {
     bool bad = false;
     for (int d : {16, 32, 64}) {
-        by_shape<T, MODE, kFwd>(d, false, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_fwd_patch<decltype(g), MODE>), sizeof(Shared<decltype(g), MODE>)); });
-        by_shape<T, MODE, kDq>(d, false, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dq_patch<decltype(g), MODE>), sizeof(SharedDq<decltype(g), MODE>)); });
+        by_shape<T, MODE, SPLIT, kFwd>(d, false, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_fwd_patch<decltype(g), MODE>), sizeof(Shared<decltype(g), MODE>)); });
+        by_shape<T, MODE, SPLIT, kDq>(d, false, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dq_patch<decltype(g), MODE>), sizeof(SharedDq<decltype(g), MODE>)); });
         for (bool classes : {false, true})
-            by_shape<T, MODE, kDkdv>(d, classes, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dkdv_patch<decltype(g), MODE>), sizeof(SharedDkdv<decltype(g), MODE>)); });
+            by_shape<T, MODE, SPLIT, kDkdv>(d, classes, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dkdv_patch<decltype(g), MODE>), sizeof(SharedDkdv<decltype(g), MODE>)); });
     }
     return bad;
 }
-template <class T, int MODE>
-void PatchKernels<T, MODE>::fwd(const S2DeviceTables &t, int nbh, int d, int e, float scale, const T *q, const T *k, const T *v, T *out, float *lse,
+template <class T, int MODE, bool SPLIT>
+void PatchKernels<T, MODE, SPLIT>::fwd(const S2DeviceTables &t, int nbh, int d, int e, float scale, const T *q, const T *k, const T *v, T *out, float *lse,
                                 hipStream_t st)
 {
-    const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale);
-    by_shape<T, MODE, kFwd>(d > e ? d : e, l.a.b.c_own > 1, [&](auto g) {
+    const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale, SPLIT);
+    by_shape<T, MODE, SPLIT, kFwd>(d > e ? d : e, l.a.b.c_own > 1, [&](auto g) {
         using G = decltype(g);
         hipLaunchKernelGGL((nattn_fwd_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(Shared<G, MODE>), st, l.a, q, k, v, out, lse);
     });
 }
-template <class T, int MODE>
-void PatchKernels<T, MODE>::dq(const S2DeviceTables &t, int nbh, int d, int e, float scale, const T *q, const T *k, const T *v, const T *o,
+template <class T, int MODE, bool SPLIT>
+void PatchKernels<T, MODE, SPLIT>::dq(const S2DeviceTables &t, int nbh, int d, int e, float scale, const T *q, const T *k, const T *v, const T *o,
                                const float *lse, const T *go, T *dq, float *Dws, hipStream_t st)
 {
-    const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale);
-    by_shape<T, MODE, kDq>(d > e ? d : e, l.a.b.c_own > 1, [&](auto g) {
+    const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale, SPLIT);
+    by_shape<T, MODE, SPLIT, kDq>(d > e ? d : e, l.a.b.c_own > 1, [&](auto g) {
         using G = decltype(g);
         hipLaunchKernelGGL((nattn_bwd_dq_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(SharedDq<G, MODE>), st, l.a, q, k, v, o, lse, go, dq, Dws);
     });
 }
-template <class T, int MODE>
-void PatchKernels<T, MODE>::dkdv(const S2DeviceTables &t, int nbh, int d, int e, float scale, const T *q, const T *k, const T *v, const float *lse,
+template <class T, int MODE, bool SPLIT>
+void PatchKernels<T, MODE, SPLIT>::dkdv(const S2DeviceTables &t, int nbh, int d, int e, float scale, const T *q, const T *k, const T *v, const float *lse,
                                  const T *go, const float *Dws, T *dk, T *dv, hipStream_t st)
 {
-    const PatchLaunch l = patch_launch(t, t.side_in, nbh, d, e, scale);
-    by_shape<T, MODE, kDkdv>(d > e ? d : e, l.a.b.c_own > 1, [&](auto g) {
+    const PatchLaunch l = patch_launch(t, t.side_in, nbh, d, e, scale, SPLIT);
+    by_shape<T, MODE, SPLIT, kDkdv>(d > e ? d : e, l.a.b.c_own > 1, [&](auto g) {
         using G = decltype(g);
         hipLaunchKernelGGL((nattn_bwd_dkdv_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(SharedDkdv<G, MODE>), st, l.a, q, k, v, lse, go, Dws, dk, dv);
     });

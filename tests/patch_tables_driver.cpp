@@ -1,5 +1,5 @@
 // Walks the segments, rows, chunks and patches that s2_grid_init makes for the patch kernels (s2_nattn_patch_impl.h) the way the
-// kernels do, on the host, and compares what every owner meets with the arc tables: each neighbor once, and nothing else.  Also
+// kernels do, on the host (of either list of workgroups, the one for small launches too), and compares what every owner meets with the arc tables: each neighbor once, and nothing else.  Also
 // prints how many chunks more than the circle has a wavefront walks at most on a row of which an owner meets all.
 // Arguments: grid type, four sizes, theta.
 #include <algorithm>
@@ -15,17 +15,19 @@ int s2_nattn_stream_configure() { return 0; }
 int s2_nattn_band_configure() { return 0; }
 int s2_static_scratch_setup(int) { return 0; }
 
-static int check(const s2_grid::Patches &p, const std::vector<int> &blo, const std::vector<int> &bn, const std::vector<int2> &arc, int nU, int c_walk,
+static int check(const s2_grid::Patches &p, const std::vector<int2> &list, const std::vector<int> &blo, const std::vector<int> &bn, const std::vector<int2> &arc, int nU, int c_walk,
                  double &more)
 {
     const int n_own = int(blo.size()), bmax = int(arc.size() / blo.size());
     const int S = p.step, nW = S * nU;
     if (S != (c_walk * nU < 1 << 15 ? c_walk : 1)) return 7;      // whole latitudes wherever 16 bits hold their columns, else classes
     std::vector<int> seen(size_t(n_own) * nU, 0);
-    for (const int2 &wg : p.list) {
+    for (int2 wg : list) {
+        const int share = wg.y >> 16;                 // log2 of the wavefronts that share a patch
+        wg.y &= 0xffff;
         const int4 s0 = p.seg[2 * wg.x];
         const int rows = 1 << s0.y, W = 16 >> s0.y;
-        for (int wave = 0; wave < kS2PatchWaves; ++wave)
+        for (int wave = 0; wave < kS2PatchWaves >> share; ++wave)
             for (int n = 0; n < 16; ++n) {
                 const int own = s0.x + n / W, wc = wg.y + wave * W, u = wc + n % W;
                 if (own >= n_own || u >= nU || n / W >= rows) continue;
@@ -77,8 +79,13 @@ int main(int argc, char **argv)
     if (argc != 7 || s2_grid_init(atoi(argv[1]), atoi(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atof(argv[6]), &g) != S2_OK) return 100;
     const int nU = g->nlon_in < g->nlon_out ? g->nlon_in : g->nlon_out;
     double more_a = 0.0, more_b = 0.0;
-    const int a = check(g->vo_patch, g->vo_lo, g->vo_n, g->vo_arc, nU, g->pscale, more_a),
-              b = check(g->vi_patch, g->vi_lo, g->vi_n, g->vi_arc, nU, g->upscale, more_b);
+    int a = check(g->vo_patch, g->vo_patch.list, g->vo_lo, g->vo_n, g->vo_arc, nU, g->pscale, more_a),
+        b = check(g->vi_patch, g->vi_patch.list, g->vi_lo, g->vi_n, g->vi_arc, nU, g->upscale, more_b);
+    for (int i = 0; i < 2; ++i) {
+        if (a == 0) a = check(g->vo_patch, g->vo_patch.split[i], g->vo_lo, g->vo_n, g->vo_arc, nU, g->pscale, more_a);
+        if (b == 0) b = check(g->vi_patch, g->vi_patch.split[i], g->vi_lo, g->vi_n, g->vi_arc, nU, g->upscale, more_b);
+        if (a == 0 && g->vo_patch.split[i].size() <= g->vo_patch.list.size() && nU > 32) a = 8;       // the longest are split
+    }
     s2_grid_destroy(g);
     printf("%d %d %g %g\n", a, b, more_a, more_b);
     return a ? a : b ? 10 + b : 0;
