@@ -7,14 +7,16 @@
 // or its columns lie apart (classes of a finer grid); kRagged, kNarrow with channel counts that are not the kernel's.
 // kPairs: kWide, where the owners are the two classes of a grid of twice the longitudes (an even number a class), so that four columns of a
 // latitude are two owners of either.
+// kHalves: kNarrow, rows of an even length side by side, whose pieces astride the end of a row are two pairs of columns.
 // kColumns: kNarrow, where a wavefront owns 16 rows of one column (S2ColumnRow).
-enum { kWide, kNarrow, kRagged, kPairs, kColumns };
+enum { kWide, kNarrow, kRagged, kPairs, kColumns, kHalves };
 constexpr bool is_wide(int mode) { return mode == kWide || mode == kPairs; }
 inline int s2_band_mode(const S2BandSide &b, int d, int e, size_t element)
 {
     if (d != e || (d != 16 && d != 32 && d != 64)) return kRagged;
     const size_t slice = size_t(d) * b.nlat_walk * b.nU * b.c_walk * element;
-    if (b.c_walk != b.patches.step || b.nU * b.patches.step % 4 != 0 || slice >= size_t(1) << 32) return kNarrow;
+    if (b.c_walk != b.patches.step || b.nU * b.patches.step % 2 != 0) return kNarrow;
+    if (b.nU * b.patches.step % 4 != 0 || slice >= size_t(1) << 32) return kHalves;
     return b.c_own == 2 && b.nU % 2 == 0 ? kPairs : kWide;
 }
 // The list of workgroups for nbh slices: nullptr, the one where every wavefront has a patch of its own; or one of those for launches that their
@@ -38,5 +40,6 @@ void s2_by_band_mode(int mode, F &&f)
     if (mode == kWide) f(Set<kWide>());
     else if (mode == kNarrow) f(Set<kNarrow>());
     else if (mode == kRagged) f(Set<kRagged>());
+    else if (mode == kHalves) f(Set<kHalves>());
     else f(Set<kPairs>());
 }

@@ -5,10 +5,10 @@
 // the matrix-core kernels for any grid pair, of both element types
 int s2_nattn_band_configure()
 {
-    return PatchSet<kWide>::configure() || PatchSet<kNarrow>::configure() || PatchSet<kRagged>::configure() || PatchSet<kPairs>::configure() ||
-           PatchSet16<kWide>::configure() || PatchSet16<kNarrow>::configure() || PatchSet16<kRagged>::configure() || PatchSet16<kPairs>::configure() ||
-           SplitSet<kWide>::configure() || SplitSet<kNarrow>::configure() || SplitSet<kRagged>::configure() || SplitSet<kPairs>::configure() ||
-           SplitSet16<kWide>::configure() || SplitSet16<kNarrow>::configure() || SplitSet16<kRagged>::configure() || SplitSet16<kPairs>::configure() ||
+    return PatchSet<kWide>::configure() || PatchSet<kNarrow>::configure() || PatchSet<kRagged>::configure() || PatchSet<kPairs>::configure() || PatchSet<kHalves>::configure() ||
+           PatchSet16<kWide>::configure() || PatchSet16<kNarrow>::configure() || PatchSet16<kRagged>::configure() || PatchSet16<kPairs>::configure() || PatchSet16<kHalves>::configure() ||
+           SplitSet<kWide>::configure() || SplitSet<kNarrow>::configure() || SplitSet<kRagged>::configure() || SplitSet<kPairs>::configure() || SplitSet<kHalves>::configure() ||
+           SplitSet16<kWide>::configure() || SplitSet16<kNarrow>::configure() || SplitSet16<kRagged>::configure() || SplitSet16<kPairs>::configure() || SplitSet16<kHalves>::configure() ||
            s2_nattn_columns_configure();
 }
 

@@ -342,7 +342,9 @@ struct Chunks {
 };
 
 // One tensor's stage.  Pieces of four elements, also where rows are no multiple of four long (kNarrow, kRagged: at any alignment,
-// a piece astride the end of its row element by element, with all of the wavefront's): as four loads each, 154 x 306, 4 slices, d = 64,
+// a piece astride the end of its row element by element, with all of the wavefront's; kHalves: rows of an even length, in halves, 46 x 90, one
+// slice, d = 32, bf16, forward / backward 20 / 42 -> 15 / 32 us, 90 x 178, 32 slices, d = 64, bf16 329 / 879 -> 259 / 755, float32 630 / 1638 -> 589 /
+// 1523; decided inside of kNarrow, odd rows lost 2 to 5 %): as four loads each, 154 x 306, 4 slices, d = 64,
 // bf16, forward 196 us, now 130; 179 x 358, 6 slices, d = 32, bf16, forward and backward 859 -> 595; around the seam of circles of
 // some thirty longitudes, where most pieces are apart, 24.3 -> 25.4.
 // From memory to registers, and (float32: cut into three terms) on to LDS.
@@ -360,9 +362,13 @@ struct ChunkAt {
             off[0] = unsigned(sizeof(T)) * (unsigned(channel) * unsigned(w.plane_walk) + unsigned(row) * unsigned(w.nW) + unsigned(c));
         } else {
             const unsigned at = unsigned(w.row_walked(row));
-            apart = w.stride > 1 || __any(c + 4 > w.nW);
+            apart = (MODE != kHalves && w.stride > 1) || __any(c + 4 > w.nW);
             off[0] = at + unsigned(w.stride) * unsigned(c);
             if (!apart) return;
+            if constexpr (MODE == kHalves) {     // (chunks begin at multiples of four, less whole rows)
+                off[2] = at + unsigned(wrap_col(col + 2 + 2 * w.nW, w.nW, w.inv_nW));
+                return;
+            }
 #pragma unroll
             for (int i = 1; i < 4; ++i) off[i] = at + unsigned(w.stride) * unsigned(wrap_col(col + i + 2 * w.nW, w.nW, w.inv_nW));
         }
@@ -375,6 +381,11 @@ struct ChunkAt {
             s = load_at<f32x4>(plane, off[0] / unsigned(sizeof(T)) * 4u - 4u * unsigned(channel) * unsigned(w.plane_walk));
         } else if (!apart) {
             __builtin_memcpy(&s, plane + off[0], sizeof s);
+        } else if constexpr (MODE == kHalves) {
+            float h[4];
+            __builtin_memcpy(h, plane + off[0], 8);
+            __builtin_memcpy(h + 2, plane + off[2], 8);
+            s = f32x4{h[0], h[1], h[2], h[3]};
         } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i) s[i] = plane[off[i]];
@@ -441,6 +452,17 @@ struct Stage {
                 if (!at.apart) {
 #pragma unroll
                     for (int k = 0; k < G::NC; ++k) __builtin_memcpy(&rj[k], channel(k) + at.off[0], sizeof rj[k]);
+                } else if constexpr (MODE == kHalves) {
+                    typedef std::conditional_t<sizeof(T) == 4, u32x2, unsigned> Half;
+                    struct Halves { Half lo, hi; };
+#pragma unroll
+                    for (int k = 0; k < G::NC; ++k) {
+                        const T *p = channel(k);
+                        Halves h;
+                        __builtin_memcpy(&h.lo, p + at.off[0], sizeof(Half));
+                        __builtin_memcpy(&h.hi, p + at.off[2], sizeof(Half));
+                        rj[k] = __builtin_bit_cast(Piece, h);
+                    }
                 } else {
 #pragma unroll
                     for (int k = 0; k < G::NC; ++k) {

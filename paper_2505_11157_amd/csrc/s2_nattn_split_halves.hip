@@ -1,0 +1,4 @@
+// Patch kernels of float32 tensors whose wavefronts share patches, staging mode kHalves.
+#include "s2_nattn_patch_impl.h"
+
+template struct PatchKernels<float, kHalves, true>;
