@@ -280,11 +280,15 @@ __device__ __forceinline__ void take_unit(const Units &u, F &&f)
 // the same 64 queries and takes every other 32-key tile of a stage, and the pairs' (o, m, l) meet in LDS behind the
 // last stage, so a query's serial chain over the keys is half as long and the launch has twice the workgroups
 // (46 x 90, four heads: 94 us with SPLIT = 1, 64 us with SPLIT = 2; see split_units for the line).
+// common: the launch has units that are not split.  Probabilities are rounded to bf16 relative to the reference, which comes from the first tile
+// of live keys; the pair that does not meet that tile takes the reference from it all the same.  With a reference of its own, split units were
+// apart from unsplit ones by some 2.5e-3 of their norm (as far from float64 either way), and where a slice lies in a batch decides which it has:
+// 65 x 128, 32 slices, against no unit split 3.2e-4 -> 9e-6, 46 x 90, 24 slices, 4.0e-4 -> 1.4e-5, at the same times.
 constexpr int kStageFwd = 2 * kTileBytes + 256;      // K row tile, V^T column tile, 64 weights
 template <bool UNIFORM_W, int SPLIT>
 __device__ __forceinline__ void
 forward_unit(char *buf0, char *buf1, int qb, int bh, const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const bf16raw *__restrict__ vt,
-             const float *__restrict__ wtok, bf16raw *__restrict__ out, float *__restrict__ lse, int N, int Npad, int2 live, float c2, float ln_wref)
+             const float *__restrict__ wtok, bf16raw *__restrict__ out, float *__restrict__ lse, int N, int Npad, int2 live, float c2, float ln_wref, bool common)
 {
     static_assert(SPLIT == 1 || SPLIT == 2, "a stage holds two key tiles");
     constexpr int kStage = kStageFwd;
@@ -387,6 +391,22 @@ forward_unit(char *buf0, char *buf1, int qb, int bh, const bf16raw *__restrict__
     request(buf0, 0);
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) arrived(qop[ks]);
+    if (SPLIT == 2 && common && part != (live.x >> 5 & 1)) {
+        const int t0 = live.x & ~31;
+        const bf16raw *kp = kb + size_t(min(t0 + col, N - 1)) * kD + 8 * hl;
+        f32x16 s = {0};
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) s = mfma(ld8(kp + 16 * ks), qop[ks], s);
+        float mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int key = t0 + 8 * (i >> 2) + 4 * hl + (i & 3);
+            if (key >= live.x && key < live.y) mx = fmaxf(mx, s[i] * c2);
+        }
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        based = mx > -INFINITY;
+        m = based ? mx : 0.f;
+    }
     landed();
     for (int st = 0; st < nst; st += 2) {
         stage(buf0, buf1, st);
@@ -442,7 +462,7 @@ global_fwd(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const b
     __shared__ __attribute__((aligned(16))) char buf0[kStageFwd];
     __shared__ __attribute__((aligned(16))) char buf1[kStageFwd];
     take_unit(units, [&](auto split, int qb, int bh) {
-        forward_unit<UNIFORM_W, decltype(split)::value>(buf0, buf1, qb, bh, q, k, vt, wtok, out, lse, N, Npad, live, c2, ln_wref);
+        forward_unit<UNIFORM_W, decltype(split)::value>(buf0, buf1, qb, bh, q, k, vt, wtok, out, lse, N, Npad, live, c2, ln_wref, units.whole > 0);
     });
 }
 
