@@ -22,14 +22,14 @@ template <class F>
 static void on_patches(const S2BandSide &b, int nbh, int d, int e, F &&f)
 {
     const int mode = s2_band_mode(b, d, e, sizeof(float));
-    if (s2_split_list(b.patches, nbh)) s2_by_band_mode<SplitSet>(mode, f);
+    if (s2_split_list(b, nbh, d, e, sizeof(float))) s2_by_band_mode<SplitSet>(mode, f);
     else s2_by_band_mode<PatchSet>(mode, f);
 }
 template <class F>
 static void on_patches16(const S2BandSide &b, int nbh, int d, int e, F &&f)
 {
     const int mode = s2_band_mode(b, d, e, 2);
-    if (s2_split_list(b.patches, nbh)) s2_by_band_mode<SplitSet16>(mode, f);
+    if (s2_split_list(b, nbh, d, e, 2)) s2_by_band_mode<SplitSet16>(mode, f);
     else s2_by_band_mode<PatchSet16>(mode, f);
 }
 

@@ -12,6 +12,6 @@ void s2_nattn_fwd_columns(const S2DeviceTables &t, int nbh, float scale, const f
 {
     S2BandSide b = t.side_out;
     b.patches = t.columns;
-    const PatchLaunch l = patch_launch(t, b, nbh, ColumnGeo::D, ColumnGeo::D, scale, false);
+    const PatchLaunch l = patch_launch(t, b, nbh, ColumnGeo::D, ColumnGeo::D, scale, nullptr);
     hipLaunchKernelGGL((nattn_fwd_patch<ColumnGeo, kColumns>), l.grid, dim3(ColumnGeo::NT), sizeof(Shared<ColumnGeo, kColumns>), st, l.a, q, k, v, out, lse);
 }

@@ -1330,10 +1330,9 @@ struct PatchLaunch {
     BandArgs a;
     dim3 grid;
 };
-inline PatchLaunch patch_launch(const S2DeviceTables &t, const S2BandSide &b, int nbh, int d, int e, float scale, bool split)
+inline PatchLaunch patch_launch(const S2DeviceTables &t, const S2BandSide &b, int nbh, int d, int e, float scale, const S2BandSide::Patches::Split *s)
 {
     const S2BandSide::Patches &p = b.patches;
-    const S2BandSide::Patches::Split *s = split ? s2_split_list(p, nbh) : nullptr;
     const int n = s ? s->n : p.npatch;
     return {{b, t.omega_rel, t.ln_omega_ref, t.omega_ref, scale, nbh, d, e, p.seg, p.row_rec, s ? s->list : p.patch, n},
             dim3(unsigned(n) * unsigned(nbh))};
@@ -1358,7 +1357,7 @@ template <class T, int MODE, bool SPLIT>
 void PatchKernels<T, MODE, SPLIT>::fwd(const S2DeviceTables &t, int nbh, int d, int e, float scale, const T *q, const T *k, const T *v, T *out, float *lse,
                                 hipStream_t st)
 {
-    const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale, SPLIT);
+    const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale, SPLIT ? s2_split_list(t.side_out, nbh, d, e, sizeof(T)) : nullptr);
     by_shape<T, MODE, SPLIT, kFwd>(d > e ? d : e, l.a.b.c_own > 1, [&](auto g) {
         using G = decltype(g);
         hipLaunchKernelGGL((nattn_fwd_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(Shared<G, MODE>), st, l.a, q, k, v, out, lse);
@@ -1368,7 +1367,7 @@ template <class T, int MODE, bool SPLIT>
 void PatchKernels<T, MODE, SPLIT>::dq(const S2DeviceTables &t, int nbh, int d, int e, float scale, const T *q, const T *k, const T *v, const T *o,
                                const float *lse, const T *go, T *dq, float *Dws, hipStream_t st)
 {
-    const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale, SPLIT);
+    const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale, SPLIT ? s2_split_list(t.side_out, nbh, d, e, sizeof(T)) : nullptr);
     by_shape<T, MODE, SPLIT, kDq>(d > e ? d : e, l.a.b.c_own > 1, [&](auto g) {
         using G = decltype(g);
         hipLaunchKernelGGL((nattn_bwd_dq_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(SharedDq<G, MODE>), st, l.a, q, k, v, o, lse, go, dq, Dws);
@@ -1378,7 +1377,7 @@ template <class T, int MODE, bool SPLIT>
 void PatchKernels<T, MODE, SPLIT>::dkdv(const S2DeviceTables &t, int nbh, int d, int e, float scale, const T *q, const T *k, const T *v, const float *lse,
                                  const T *go, const float *Dws, T *dk, T *dv, hipStream_t st)
 {
-    const PatchLaunch l = patch_launch(t, t.side_in, nbh, d, e, scale, SPLIT);
+    const PatchLaunch l = patch_launch(t, t.side_in, nbh, d, e, scale, SPLIT ? s2_split_list(t.side_in, nbh, d, e, sizeof(T)) : nullptr);
     by_shape<T, MODE, SPLIT, kDkdv>(d > e ? d : e, l.a.b.c_own > 1, [&](auto g) {
         using G = decltype(g);
         hipLaunchKernelGGL((nattn_bwd_dkdv_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(SharedDkdv<G, MODE>), st, l.a, q, k, v, lse, go, Dws, dk, dv);
