@@ -5,7 +5,7 @@
 // Staging mode, all in pieces of four columns: kWide, rows of a multiple of four columns side by side and 32-bit offsets into a slice, so
 // that no piece ends with its row; kNarrow, any rows, pieces at any alignment, and element by element where a piece ends with its row
 // or its columns lie apart (classes of a finer grid); kRagged, kNarrow with channel counts that are not the kernel's.
-// kPairs: kWide, where the owners are the two classes of a grid of twice the longitudes (an even number a class), so that four columns of a
+// kPairs: kWide, where the owners are the two classes of a grid of twice the longitudes, so that four columns of a
 // latitude are two owners of either.
 // kHalves: kNarrow, rows of an even length side by side, whose pieces astride the end of a row are two pairs of columns.
 // kColumns: kNarrow, where a wavefront owns 16 rows of one column (S2ColumnRow).
@@ -17,7 +17,7 @@ inline int s2_band_mode(const S2BandSide &b, int d, int e, size_t element)
     const size_t slice = size_t(d) * b.nlat_walk * b.nU * b.c_walk * element;
     if (b.c_walk != b.patches.step || b.nU * b.patches.step % 2 != 0) return kNarrow;
     if (b.nU * b.patches.step % 4 != 0 || slice >= size_t(1) << 32) return kHalves;
-    return b.c_own == 2 && b.nU % 2 == 0 ? kPairs : kWide;
+    return b.c_own == 2 ? kPairs : kWide;      // (the walked grid is the coarser one: step 1, nU a multiple of four)
 }
 // The list of workgroups for nbh slices of d and e channels: nullptr, the one where every wavefront has a patch of its own; or one of those
 // for launches that their longest workgroup bounds.  By work (S2BandSide::Patches): parts of one patch up to 250, of two up to 400.

@@ -1300,11 +1300,12 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
 // three 0.515, to two 0.429; bf16 d = 32 to four 0.214, to three 0.220).
 // Stages of 24 chunks where that costs no workgroup, dk/dv of float32 d = 32: the four wavefronts of a workgroup meet more alike numbers of
 // whole tiles in a stage and wait less for each other, and there are a third fewer stages (129 x 256, 32 slices: 659 -> 633 us; at three
-// workgroups instead of four the forward would take 441 instead of 421, dq 521 instead of 498).  Owners that are classes of a finer
-// grid (classes) meet some 38 chunks: 24 + 14 of them make more odd tiles than 16 + 16 + 6 (257 x 512 -> 129 x 256, 8 slices: 329 -> 350).
+// workgroups instead of four the forward would take 441 instead of 421, dq 521 instead of 498).  So it is where owners are three or more classes of a
+// finer grid (192 x 384 -> 64 x 128, 8 slices: backward 299 us either way; 144 x 288 -> 36 x 72 185 -> 180); two classes are kPairs, whose owners
+// meet some 38 chunks: 24 + 14 of them make more odd tiles than 16 + 16 + 6 (257 x 512 -> 129 x 256, 8 slices: 329 -> 350).
 enum Launch { kFwd, kDq, kDkdv };
 template <class T, int MODE, bool SPLIT, Launch WHICH, class F>
-void by_shape(int dmax, bool classes, F &&f)
+void by_shape(int dmax, F &&f)
 {
     if constexpr (SPLIT) {
         constexpr bool F32 = sizeof(T) == 4;
@@ -1314,10 +1315,8 @@ void by_shape(int dmax, bool classes, F &&f)
     } else if constexpr (sizeof(T) == 4) {
         if (dmax <= 16) f(Geo<T, 16, 32, is_wide(MODE) && WHICH == kDkdv ? 4 : 3>());
         else if (dmax <= 32) {
-            if constexpr (WHICH == kDkdv && MODE == kWide) {
-                if (!classes) return f(Geo<T, 32, 24, 3>());
-            }
-            f(Geo<T, 32, 16, WHICH == kDq ? 4 : 3>());
+            if constexpr (WHICH == kDkdv && MODE == kWide) f(Geo<T, 32, 24, 3>());
+            else f(Geo<T, 32, 16, WHICH == kDq ? 4 : 3>());
         }
         else f(Geo<T, 64, 16, 2>());
     } else {
@@ -1346,10 +1345,9 @@ int PatchKernels<T, MODE, SPLIT>::configure()
 {
     bool bad = false;
     for (int d : {16, 32, 64}) {
-        by_shape<T, MODE, SPLIT, kFwd>(d, false, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_fwd_patch<decltype(g), MODE>), sizeof(Shared<decltype(g), MODE>)); });
-        by_shape<T, MODE, SPLIT, kDq>(d, false, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dq_patch<decltype(g), MODE>), sizeof(SharedDq<decltype(g), MODE>)); });
-        for (bool classes : {false, true})
-            by_shape<T, MODE, SPLIT, kDkdv>(d, classes, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dkdv_patch<decltype(g), MODE>), sizeof(SharedDkdv<decltype(g), MODE>)); });
+        by_shape<T, MODE, SPLIT, kFwd>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_fwd_patch<decltype(g), MODE>), sizeof(Shared<decltype(g), MODE>)); });
+        by_shape<T, MODE, SPLIT, kDq>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dq_patch<decltype(g), MODE>), sizeof(SharedDq<decltype(g), MODE>)); });
+        by_shape<T, MODE, SPLIT, kDkdv>(d, [&](auto g) { bad |= raise_lds(reinterpret_cast<const void *>(nattn_bwd_dkdv_patch<decltype(g), MODE>), sizeof(SharedDkdv<decltype(g), MODE>)); });
     }
     return bad;
 }
@@ -1358,7 +1356,7 @@ void PatchKernels<T, MODE, SPLIT>::fwd(const S2DeviceTables &t, int nbh, int d, 
                                 hipStream_t st)
 {
     const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale, SPLIT ? s2_split_list(t.side_out, nbh, d, e, sizeof(T)) : nullptr);
-    by_shape<T, MODE, SPLIT, kFwd>(d > e ? d : e, l.a.b.c_own > 1, [&](auto g) {
+    by_shape<T, MODE, SPLIT, kFwd>(d > e ? d : e, [&](auto g) {
         using G = decltype(g);
         hipLaunchKernelGGL((nattn_fwd_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(Shared<G, MODE>), st, l.a, q, k, v, out, lse);
     });
@@ -1368,7 +1366,7 @@ void PatchKernels<T, MODE, SPLIT>::dq(const S2DeviceTables &t, int nbh, int d, i
                                const float *lse, const T *go, T *dq, float *Dws, hipStream_t st)
 {
     const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale, SPLIT ? s2_split_list(t.side_out, nbh, d, e, sizeof(T)) : nullptr);
-    by_shape<T, MODE, SPLIT, kDq>(d > e ? d : e, l.a.b.c_own > 1, [&](auto g) {
+    by_shape<T, MODE, SPLIT, kDq>(d > e ? d : e, [&](auto g) {
         using G = decltype(g);
         hipLaunchKernelGGL((nattn_bwd_dq_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(SharedDq<G, MODE>), st, l.a, q, k, v, o, lse, go, dq, Dws);
     });
@@ -1378,7 +1376,7 @@ void PatchKernels<T, MODE, SPLIT>::dkdv(const S2DeviceTables &t, int nbh, int d,
                                  const T *go, const float *Dws, T *dk, T *dv, hipStream_t st)
 {
     const PatchLaunch l = patch_launch(t, t.side_in, nbh, d, e, scale, SPLIT ? s2_split_list(t.side_in, nbh, d, e, sizeof(T)) : nullptr);
-    by_shape<T, MODE, SPLIT, kDkdv>(d > e ? d : e, l.a.b.c_own > 1, [&](auto g) {
+    by_shape<T, MODE, SPLIT, kDkdv>(d > e ? d : e, [&](auto g) {
         using G = decltype(g);
         hipLaunchKernelGGL((nattn_bwd_dkdv_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(SharedDkdv<G, MODE>), st, l.a, q, k, v, lse, go, Dws, dk, dv);
     });

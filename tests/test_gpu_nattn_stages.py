@@ -4,8 +4,9 @@ import math
 
 import pytest
 
+import paper_2505_11157_amd as S
 from paper_2505_11157_amd.workloads import make_inputs
-from test_gpu_nattn import C_DERIVED, run_case
+from test_gpu_nattn import C_DERIVED, debug_switches, run_case
 
 pytestmark = pytest.mark.gpu
 
@@ -17,3 +18,14 @@ def test_chunk_counts(rows, chunks):
              d=32, dtype="f32")
     c, arrs = make_inputs(c, seed=6100 + 100 * rows + chunks)
     run_case(c, arrs, [0, 1], C=C_DERIVED, case="stages%dx%d" % (rows, chunks))
+
+
+@pytest.mark.parametrize("ratio", [3, 4])
+@pytest.mark.parametrize("rows,chunks", [(23, 1), (6, 4), (7, 7), (12, 8), (16, 6)])
+def test_owners_of_three_and_four_classes(rows, chunks, ratio):
+    # owners are the classes of a grid of three or four times the longitudes, each with a patch of its own
+    c = dict(kind="nattn", grid_type=1, nlat_in=rows, nlon_in=4 * chunks * ratio, nlat_out=rows, nlon_out=4 * chunks, theta=math.pi, batch=1, heads=2,
+             d=32, dtype="f32")
+    c, arrs = make_inputs(c, seed=6200 + 100 * rows + chunks)
+    with debug_switches(S.S2_DEBUG_OWN_PATCHES):
+        run_case(c, arrs, [0, 1], C=C_DERIVED, case="classes%d-%dx%d" % (ratio, rows, chunks))
