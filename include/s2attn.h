@@ -311,9 +311,10 @@ int s2_grid_device_flags(const s2_grid_t *g, unsigned *flags);
  *                           their place (float32 with d = e = 32: streaming and split vector kernels, else shape-agnostic ones)
  *   S2_DEBUG_OWN_PATCHES    every wavefront of the matrix-core patches owns a patch, also in launches so small that some would share one
  *   S2_DEBUG_HALVES         in every launch wavefronts share the patches of heavy workgroups two and two
+ *   S2_DEBUG_QUARTERS       in every launch all four wavefronts of heavy workgroups share a patch
  */
 enum { S2_DEBUG_NO_MFMA = 1, S2_DEBUG_NO_STREAM = 2, S2_DEBUG_NO_ROW_GROUPS = 4, S2_DEBUG_FAIL_LAUNCH = 8, S2_DEBUG_FORCE_BAND = 16, S2_DEBUG_NO_BAND = 32,
-       S2_DEBUG_OWN_PATCHES = 64, S2_DEBUG_HALVES = 128 };
+       S2_DEBUG_OWN_PATCHES = 64, S2_DEBUG_HALVES = 128, S2_DEBUG_QUARTERS = 256 };
 unsigned s2_debug_control(unsigned set_bits, unsigned clear_bits);
 
 /* Message for the last error on the calling thread ("" if none). */

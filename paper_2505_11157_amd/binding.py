@@ -31,6 +31,7 @@ S2_DEBUG_FORCE_BAND = 16
 S2_DEBUG_NO_BAND = 32
 S2_DEBUG_OWN_PATCHES = 64
 S2_DEBUG_HALVES = 128
+S2_DEBUG_QUARTERS = 256
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libs2attn.so")

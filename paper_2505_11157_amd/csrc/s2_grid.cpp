@@ -288,7 +288,7 @@ static void split_patches(int nU, s2_grid::Patches &p)
         while (p.seg[2 * t + 1].z) n += p.seg[2 * ++t + 1].x;
         chunks.push_back(n);
     }
-    const int most = chunks.empty() ? 0 : *std::max_element(chunks.begin(), chunks.end());
+    const int most = p.heaviest = chunks.empty() ? 0 : *std::max_element(chunks.begin(), chunks.end());
     for (int i = 0; i < 2; ++i) {
         const int share_lg = 1 + i;
         double sum = 0.0;
@@ -602,6 +602,7 @@ static int upload_tables(s2_grid *g)
         q.patch = ap(23 + 3 * i);
         q.npatch = int(p.list.size());
         q.step = p.step;
+        q.heaviest = p.heaviest;
         for (int j = 0; j < 2; ++j) q.split[j] = {ap(27 + 2 * i + j), int(p.split[j].size()), p.split_work[j]};
     }
     t.columns = {reinterpret_cast<const int4 *>(base + parts[31].off), reinterpret_cast<const int4 *>(base + parts[32].off), ap(33),

@@ -39,6 +39,7 @@ struct S2BandSide {
             int n;
             double work;          // of a slice, in workgroups as heavy as the heaviest unsplit one; parts two or three times what they were
         } split[2];
+        int heaviest;             // chunks of the heaviest unsplit workgroup
     } patches;
 };
 
@@ -126,6 +127,7 @@ struct s2_grid {
         std::vector<int2> list, split[2];
         int step = 1;
         double split_work[2] = {};
+        int heaviest = 0;
     } vo_patch, vi_patch;
     struct Columns {
         std::vector<int4> seg;

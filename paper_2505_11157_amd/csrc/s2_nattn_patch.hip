@@ -19,17 +19,17 @@ bool s2_nattn_patch_supported(const S2DeviceTables &t, int d, int e)
 
 // f(set) with the launchers for owners of a side, of float32 or bf16 tensors
 template <class F>
-static void on_patches(const S2BandSide &b, int nbh, int d, int e, F &&f)
+static void on_patches(const S2BandSide &b, int nbh, int d, int e, bool backward, F &&f)
 {
     const int mode = s2_band_mode(b, d, e, sizeof(float));
-    if (s2_split_list(b, nbh, d, e, sizeof(float))) s2_by_band_mode<SplitSet>(mode, f);
+    if (s2_split_list(b, nbh, d, e, sizeof(float), backward)) s2_by_band_mode<SplitSet>(mode, f);
     else s2_by_band_mode<PatchSet>(mode, f);
 }
 template <class F>
-static void on_patches16(const S2BandSide &b, int nbh, int d, int e, F &&f)
+static void on_patches16(const S2BandSide &b, int nbh, int d, int e, bool backward, F &&f)
 {
     const int mode = s2_band_mode(b, d, e, 2);
-    if (s2_split_list(b, nbh, d, e, 2)) s2_by_band_mode<SplitSet16>(mode, f);
+    if (s2_split_list(b, nbh, d, e, 2, backward)) s2_by_band_mode<SplitSet16>(mode, f);
     else s2_by_band_mode<PatchSet16>(mode, f);
 }
 
@@ -44,7 +44,7 @@ int s2_nattn_fwd_patch(const S2DeviceTables &t, int nbh, int d, int e, float sca
         s2_nattn_fwd_columns(t, nbh, scale, q, k, v, out, lse, st);
         return 0;
     }
-    on_patches(t.side_out, nbh, d, e, [&](auto set) { set.fwd(t, nbh, d, e, scale, q, k, v, out, lse, st); });
+    on_patches(t.side_out, nbh, d, e, false, [&](auto set) { set.fwd(t, nbh, d, e, scale, q, k, v, out, lse, st); });
     return 0;
 }
 
@@ -55,10 +55,10 @@ int s2_nattn_bwd_patch(const S2DeviceTables &t, int nbh, int d, int e, float sca
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
     {
         S2TraceScope tr("nattn_bwd_dq_patch", pair_count(t.fwd_pairs, nbh), st);
-        on_patches(t.side_out, nbh, d, e, [&](auto set) { set.dq(t, nbh, d, e, scale, q, k, v, o, lse, go, dq, Dws, st); });
+        on_patches(t.side_out, nbh, d, e, true, [&](auto set) { set.dq(t, nbh, d, e, scale, q, k, v, o, lse, go, dq, Dws, st); });
     }
     S2TraceScope tr("nattn_bwd_dkdv_patch", pair_count(t.bwd_pairs, nbh), st);
-    on_patches(t.side_in, nbh, d, e, [&](auto set) { set.dkdv(t, nbh, d, e, scale, q, k, v, lse, go, Dws, dk, dv, st); });
+    on_patches(t.side_in, nbh, d, e, true, [&](auto set) { set.dkdv(t, nbh, d, e, scale, q, k, v, lse, go, Dws, dk, dv, st); });
     return 0;
 }
 
@@ -69,7 +69,7 @@ int s2_nattn_fwd_patch_bf16(const S2DeviceTables &t, int nbh, int d, int e, floa
 {
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
     S2TraceScope tr("nattn_fwd_patch", pair_count(t.fwd_pairs, nbh), st);
-    on_patches16(t.side_out, nbh, d, e, [&](auto set) {
+    on_patches16(t.side_out, nbh, d, e, false, [&](auto set) {
         set.fwd(t, nbh, d, e, scale, in16(q), in16(k), in16(v), static_cast<unsigned short *>(out), lse, st);
     });
     return 0;
@@ -79,7 +79,7 @@ int s2_nattn_bwd_dq_patch_bf16(const S2DeviceTables &t, int nbh, int d, int e, f
 {
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
     S2TraceScope tr("nattn_bwd_dq_patch", pair_count(t.fwd_pairs, nbh), st);
-    on_patches16(t.side_out, nbh, d, e, [&](auto set) {
+    on_patches16(t.side_out, nbh, d, e, true, [&](auto set) {
         set.dq(t, nbh, d, e, scale, in16(q), in16(k), in16(v), in16(o), lse, in16(go), static_cast<unsigned short *>(dq), Dws, st);
     });
     return 0;
@@ -89,7 +89,7 @@ int s2_nattn_bwd_dkdv_patch_bf16(const S2DeviceTables &t, int nbh, int d, int e,
 {
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
     S2TraceScope tr("nattn_bwd_dkdv_patch", pair_count(t.bwd_pairs, nbh), st);
-    on_patches16(t.side_in, nbh, d, e, [&](auto set) {
+    on_patches16(t.side_in, nbh, d, e, true, [&](auto set) {
         set.dkdv(t, nbh, d, e, scale, in16(q), in16(k), in16(v), lse, in16(go), Dws, static_cast<unsigned short *>(dk), static_cast<unsigned short *>(dv), st);
     });
     return 0;

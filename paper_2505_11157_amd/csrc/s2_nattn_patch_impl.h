@@ -1355,7 +1355,7 @@ template <class T, int MODE, bool SPLIT>
 void PatchKernels<T, MODE, SPLIT>::fwd(const S2DeviceTables &t, int nbh, int d, int e, float scale, const T *q, const T *k, const T *v, T *out, float *lse,
                                 hipStream_t st)
 {
-    const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale, SPLIT ? s2_split_list(t.side_out, nbh, d, e, sizeof(T)) : nullptr);
+    const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale, SPLIT ? s2_split_list(t.side_out, nbh, d, e, sizeof(T), false) : nullptr);
     by_shape<T, MODE, SPLIT, kFwd>(d > e ? d : e, [&](auto g) {
         using G = decltype(g);
         hipLaunchKernelGGL((nattn_fwd_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(Shared<G, MODE>), st, l.a, q, k, v, out, lse);
@@ -1365,7 +1365,7 @@ template <class T, int MODE, bool SPLIT>
 void PatchKernels<T, MODE, SPLIT>::dq(const S2DeviceTables &t, int nbh, int d, int e, float scale, const T *q, const T *k, const T *v, const T *o,
                                const float *lse, const T *go, T *dq, float *Dws, hipStream_t st)
 {
-    const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale, SPLIT ? s2_split_list(t.side_out, nbh, d, e, sizeof(T)) : nullptr);
+    const PatchLaunch l = patch_launch(t, t.side_out, nbh, d, e, scale, SPLIT ? s2_split_list(t.side_out, nbh, d, e, sizeof(T), true) : nullptr);
     by_shape<T, MODE, SPLIT, kDq>(d > e ? d : e, [&](auto g) {
         using G = decltype(g);
         hipLaunchKernelGGL((nattn_bwd_dq_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(SharedDq<G, MODE>), st, l.a, q, k, v, o, lse, go, dq, Dws);
@@ -1375,7 +1375,7 @@ template <class T, int MODE, bool SPLIT>
 void PatchKernels<T, MODE, SPLIT>::dkdv(const S2DeviceTables &t, int nbh, int d, int e, float scale, const T *q, const T *k, const T *v, const float *lse,
                                  const T *go, const float *Dws, T *dk, T *dv, hipStream_t st)
 {
-    const PatchLaunch l = patch_launch(t, t.side_in, nbh, d, e, scale, SPLIT ? s2_split_list(t.side_in, nbh, d, e, sizeof(T)) : nullptr);
+    const PatchLaunch l = patch_launch(t, t.side_in, nbh, d, e, scale, SPLIT ? s2_split_list(t.side_in, nbh, d, e, sizeof(T), true) : nullptr);
     by_shape<T, MODE, SPLIT, kDkdv>(d > e ? d : e, [&](auto g) {
         using G = decltype(g);
         hipLaunchKernelGGL((nattn_bwd_dkdv_patch<G, MODE>), l.grid, dim3(G::NT), sizeof(SharedDkdv<G, MODE>), st, l.a, q, k, v, lse, go, Dws, dk, dv);

@@ -1,5 +1,5 @@
 """Small launches of the patch kernels, whose heavy workgroups go in parts that two or all four wavefronts share: the edge cases of the
-patch kernels, small themselves, run by default on quarters; here on halves and with a patch for every wavefront, the sizes at which
+patch kernels with a patch for every wavefront, by halves and by quarters (by default they run on any of these), the sizes at which
 the default changes from one to the next, and non-finite values where only one of the sharing wavefronts meets them."""
 import math
 
@@ -15,7 +15,7 @@ from paper_2505_11157_amd.workloads import make_inputs
 from test_gpu_nattn import C_DERIVED, debug_switches, run_case
 
 pytestmark = pytest.mark.gpu
-MODES = {"own": S.S2_DEBUG_OWN_PATCHES, "halves": S.S2_DEBUG_HALVES}
+MODES = {"own": S.S2_DEBUG_OWN_PATCHES, "halves": S.S2_DEBUG_HALVES, "quarters": S.S2_DEBUG_QUARTERS}
 
 
 @pytest.mark.parametrize("d", [16, 20, 32, 64])
