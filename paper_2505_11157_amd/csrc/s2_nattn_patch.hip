@@ -19,9 +19,10 @@ bool s2_nattn_patch_supported(const S2DeviceTables &t, int d, int e)
 
 // f(set) with the launchers for owners of a side, of float32 or bf16 tensors
 template <class F>
-static void on_patches(const S2BandSide &b, int nbh, int d, int e, bool backward, F &&f)
+static void on_patches(const S2BandSide &b, int nbh, int d, int e, bool backward, bool no_halves, F &&f)
 {
-    const int mode = s2_band_mode(b, d, e, sizeof(float));
+    int mode = s2_band_mode(b, d, e, sizeof(float));
+    if (mode == kHalves && no_halves) mode = kNarrow;
     if (s2_split_list(b, nbh, d, e, sizeof(float), backward)) s2_by_band_mode<SplitSet>(mode, f);
     else s2_by_band_mode<PatchSet>(mode, f);
 }
@@ -44,7 +45,7 @@ int s2_nattn_fwd_patch(const S2DeviceTables &t, int nbh, int d, int e, float sca
         s2_nattn_fwd_columns(t, nbh, scale, q, k, v, out, lse, st);
         return 0;
     }
-    on_patches(t.side_out, nbh, d, e, false, [&](auto set) { set.fwd(t, nbh, d, e, scale, q, k, v, out, lse, st); });
+    on_patches(t.side_out, nbh, d, e, false, false, [&](auto set) { set.fwd(t, nbh, d, e, scale, q, k, v, out, lse, st); });
     return 0;
 }
 
@@ -55,10 +56,13 @@ int s2_nattn_bwd_patch(const S2DeviceTables &t, int nbh, int d, int e, float sca
     if (s2_debug_flag(S2_DEBUG_FAIL_LAUNCH)) return -1;
     {
         S2TraceScope tr("nattn_bwd_dq_patch", pair_count(t.fwd_pairs, nbh), st);
-        on_patches(t.side_out, nbh, d, e, true, [&](auto set) { set.dq(t, nbh, d, e, scale, q, k, v, o, lse, go, dq, Dws, st); });
+        // Classes of a finer grid meet few chunks, of which halves save less than the registers that dq spills for them cost: 119 x 238 -> 238 x
+        // 476, 16 slices, d = 32, backward 614 us, by halves 670; of 160 such pairs 2 % in the mean.
+        const bool no_halves = t.side_out.c_own > 1 && d == 32;
+        on_patches(t.side_out, nbh, d, e, true, no_halves, [&](auto set) { set.dq(t, nbh, d, e, scale, q, k, v, o, lse, go, dq, Dws, st); });
     }
     S2TraceScope tr("nattn_bwd_dkdv_patch", pair_count(t.bwd_pairs, nbh), st);
-    on_patches(t.side_in, nbh, d, e, true, [&](auto set) { set.dkdv(t, nbh, d, e, scale, q, k, v, lse, go, Dws, dk, dv, st); });
+    on_patches(t.side_in, nbh, d, e, true, false, [&](auto set) { set.dkdv(t, nbh, d, e, scale, q, k, v, lse, go, Dws, dk, dv, st); });
     return 0;
 }
 
