@@ -253,19 +253,20 @@ __device__ __forceinline__ bf16x8 col_operand(const char *tile, int col, int hl,
 // Units of 128 tokens of a slice.  Workgroups are numbered so that each of the eight XCDs (which take consecutive workgroup ids in turn)
 // works through one contiguous piece of the (slice, unit) list: the operands of the few slices an XCD
 // has in flight then stay in its own L2.  Of its piece an XCD takes the first `whole` units in one workgroup each, the others in two of
-// 64 tokens.
+// 64 tokens.  halves: units are of 64 tokens, one workgroup each.
 struct Units {
     int all, per_slice, per_xcd, whole, tokens;
+    bool halves;
 };
 // f(split, unit of a slice's, slice) for the workgroup's share: split = 1, unit in units of 128 tokens, or 2, of 64
 template <class F>
 __device__ __forceinline__ void take_unit(const Units &u, F &&f)
 {
-    const int i = int(blockIdx.x >> 3), j = i - u.whole, k = j < 0 ? i : u.whole + (j >> 1), unit = int(blockIdx.x & 7) * u.per_xcd + k;
+    const int i = int(blockIdx.x >> 3), j = u.halves ? -1 : i - u.whole, k = j < 0 ? i : u.whole + (j >> 1), unit = int(blockIdx.x & 7) * u.per_xcd + k;
     if (k >= u.per_xcd || unit >= u.all) return;
-    const int bh = unit / u.per_slice, q = unit - bh * u.per_slice;
-    if (j < 0) f(std::integral_constant<int, 1>(), q, bh);
-    else if (128 * q + 64 * (j & 1) < u.tokens) f(std::integral_constant<int, 2>(), 2 * q + (j & 1), bh);
+    const int bh = unit / u.per_slice, q = unit - bh * u.per_slice, half = u.halves ? q : 2 * q + (j & 1);
+    if (j < 0 && !u.halves) f(std::integral_constant<int, 1>(), q, bh);
+    else if (64 * half < u.tokens) f(std::integral_constant<int, 2>(), half, bh);
 }
 
 // Forward.  A workgroup owns 128 queries of one slice (one 32-query MFMA tile per wavefront) and streams
@@ -462,7 +463,7 @@ global_fwd(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, const b
     __shared__ __attribute__((aligned(16))) char buf0[kStageFwd];
     __shared__ __attribute__((aligned(16))) char buf1[kStageFwd];
     take_unit(units, [&](auto split, int qb, int bh) {
-        forward_unit<UNIFORM_W, decltype(split)::value>(buf0, buf1, qb, bh, q, k, vt, wtok, out, lse, N, Npad, live, c2, ln_wref, units.whole > 0);
+        forward_unit<UNIFORM_W, decltype(split)::value>(buf0, buf1, qb, bh, q, k, vt, wtok, out, lse, N, Npad, live, c2, ln_wref, !units.halves);
     });
 }
 
@@ -742,6 +743,8 @@ global_bwd_dq(const bf16raw *__restrict__ q, const bf16raw *__restrict__ k, cons
 //     forward        33: 85 -> 50   132: 91 -> 63   264: 108 -> 81   320 (25 x 47): 38 -> 32   396: 116 -> 119
 //     query side     33: 224 -> 184   132: 235 -> 209   264: 292 -> 280   320 (25 x 47): 112 -> 110   396: 360 -> 379
 //     key side       33: 224 -> 192   132: 235 -> 220   224 (21 x 40): 67 -> 67   260 (65 x 128): 511 -> 529
+// Split units are counted by 64 tokens: by twice the units of 128, slices that end within the first half of one had workgroups with nothing to do
+// among the others, and compute units two others (12 x 24, 48 slices: 240 workgroups among 288, backward 25.4 us; 21.1).
 // (at most two workgroups of the key side fit a compute unit, three of the others: hence two lines).
 constexpr long kSplitBlocks = 320, kSplitBlocksKeySide = 256;
 // Larger launches: what an XCD's 32 compute units do not share out evenly, where that is at most half a unit for each, goes in halves, so that
@@ -752,11 +755,12 @@ Units split_units(int nbh, int N, long most)
 {
     Units u;
     u.tokens = N;
-    u.per_slice = (N + 127) / 128;
+    u.halves = long(nbh) * ((N + 127) / 128) <= most;
+    u.per_slice = u.halves ? (N + 63) / 64 : (N + 127) / 128;
     u.all = nbh * u.per_slice;
     u.per_xcd = (u.all + 7) / 8;
     const int rest = u.per_xcd % kUnitsXcd;
-    u.whole = u.all <= most ? 0 : 2 * rest <= kUnitsXcd ? u.per_xcd - rest : u.per_xcd;
+    u.whole = !u.halves && 2 * rest <= kUnitsXcd ? u.per_xcd - rest : u.per_xcd;
     return u;
 }
 dim3 split_grid(const Units &u) { return dim3(8u * unsigned(u.whole + 2 * (u.per_xcd - u.whole))); }
