@@ -140,8 +140,8 @@ SMALL = [
     dict(kind="nattn", grid_type=1, nlat_in=12, nlon_in=24, nlat_out=16, nlon_out=72, theta=0.4, batch=2, heads=1, d=32, dtype="f32"),
     dict(kind="nattn", grid_type=0, nlat_in=9, nlon_in=20, nlat_out=17, nlon_out=80, theta=0.6, batch=1, heads=1, d=5, dtype="f32"),
     dict(kind="nattn", grid_type=0, nlat_in=6, nlon_in=10, nlat_out=9, nlon_out=20, theta=math.pi, batch=1, heads=1, d=3, dtype="f32"),
-    # upsampling with d = 32 and at least 72 input longitudes, a multiple of 4 (the forward on the split vector kernel: every class of
-    # output longitudes as an equal-grid problem); 2x, 3x, 4x, nine slices, a ragged last segment, full circles at the poles
+    # upsampling with d = 32 and at least 72 input longitudes, a multiple of 4 (the forward by columns; on the vector kernels every class of
+    # output longitudes is an equal-grid problem); 2x, 3x, 4x, nine slices, a ragged last segment, full circles at the poles
     dict(kind="nattn", grid_type=0, nlat_in=13, nlon_in=76, nlat_out=25, nlon_out=152, theta=0.5, batch=3, heads=3, d=32, dtype="f32"),
     dict(kind="nattn", grid_type=1, nlat_in=12, nlon_in=72, nlat_out=16, nlon_out=216, theta=0.4, batch=1, heads=2, d=32, dtype="f32"),
     dict(kind="nattn", grid_type=0, nlat_in=17, nlon_in=132, nlat_out=33, nlon_out=528, theta=0.3, batch=1, heads=1, d=32, dtype="f32"),

@@ -17,7 +17,7 @@ INF, NAN = float("inf"), float("nan")
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("where", ["k", "v", "v-inf", "q", "dout", "k-channel"])
 def test_upsampling_forward_of_32_channels(monkeypatch, where, dtype):
-    # float32: the split vector kernel in the forward, the patches behind it
+    # float32: the forward by columns, the patches behind it
     monkeypatch.setattr(base, "SHAPES", [base._c(0, 9, 72, 17, 144, 0.5, d=32)])
     base.test_non_finite_values_stay_in_their_neighborhoods(0, where, dtype)
 

@@ -36,7 +36,7 @@ def test_pairs(mode, i, d, dtype):
         pairs.test_pairs(i, False, d, dtype)
 
 
-@pytest.mark.parametrize("rows,chunks", [(22, 1), (6, 4), (5, 5), (47, 1), (6, 8), (7, 7), (97, 1)])
+@pytest.mark.parametrize("rows,chunks", [(22, 1), (23, 1), (6, 4), (5, 5), (47, 1), (6, 8), (7, 7), (19, 5), (12, 8), (97, 1), (3, 8), (2, 24)])
 def test_chunk_counts(rows, chunks):
     with debug_switches(S.S2_DEBUG_OWN_PATCHES):
         stages.test_chunk_counts(rows, chunks)

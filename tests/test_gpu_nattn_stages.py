@@ -1,5 +1,6 @@
 """dk and dv of float32 tensors with 32 channels: stages of 24 chunks, 48 looked up at once.  Disks that hold the sphere, with numbers of
-chunks next to one and two stages, against the float64 oracle."""
+chunks next to one and two stages, against the float64 oracle.  By default these small launches may share patches, in stages of 32 chunks;
+test_gpu_nattn_shared_patches runs them with a patch for every wavefront, on the 24."""
 import math
 
 import pytest
