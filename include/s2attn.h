@@ -130,6 +130,9 @@ size_t s2_nattn_bwd_workspace_bytes(const s2_grid_t *g, int batch, int heads, in
  * results up to rounding, since most kernels sum in tiles at fixed columns.  Bit for bit the same they are only where
  * a point's sums run in the order of its offsets: the forward of float32 tensors with d_qk = d_v = 32 on upsampling
  * grids with nlon_in >= 72, a multiple of 4.  Repeated calls on the same inputs always give the same bits.
+ * Number of slices (both directions): a (batch, head) slice has the same results up to rounding whatever the batch.  Bit for bit the
+ * same they are between calls of so many slices that no wavefronts share work: small launches (the fewer slices, the smaller the grid
+ * and the disk) of up to 64 channels add their sums up in parts, another order.
  * Errors: S2_ERR_INVALID_ARG (NULL or not 16-byte aligned pointers, sizes < 1),
  * S2_ERR_UNSUPPORTED (dtype, head dims), S2_ERR_DEVICE (host-only handle or
  * launch failure).
@@ -187,6 +190,9 @@ size_t s2_attn_global_bwd_workspace_bytes(const s2_grid_t *g, int batch, int hea
  * [batch][heads][N][d]; lse float32 [batch][heads][N].
  * dtype: S2_BF16 (bf16 tensors, MFMA with float32 accumulation, float32
  * softmax and lse); d = 64.  Other dtypes or head dimensions: S2_ERR_UNSUPPORTED.
+ * A slice's results depend on the batch up to rounding: some units of tokens of a launch, in small launches all, go to two chains of sums
+ * (between slices of one call, or of two large ones, 2e-5 of the norm, bf16 results a step apart; between a small call and a large one, whose
+ * probabilities are rounded relative to another reference, 3e-3).  Repeated calls give the same bits.
  * workspace: device scratch of at least s2_attn_global_fwd_workspace_bytes(...)
  * bytes, 256-byte aligned (S2_ERR_WORKSPACE otherwise); its contents are undefined
  * afterwards.  Tensor pointers must be 16-byte aligned (S2_ERR_INVALID_ARG).

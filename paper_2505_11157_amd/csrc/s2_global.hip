@@ -786,7 +786,7 @@ int check_global(const s2_grid_t *g, int batch, int heads, int d, int dtype)
     if (dtype != S2_BF16) return s2_fail(S2_ERR_UNSUPPORTED, "global attention supports S2_BF16 only");
     if (d != kD) return s2_fail(S2_ERR_UNSUPPORTED, "global attention supports head dimension 64 only");
     if (!g->on_device) return s2_fail(S2_ERR_DEVICE, "grid handle has no device tables (no HIP device at init)");
-    // one workgroup per (slice, block of 128 tokens), two where the launch is split (few): the grid must fit 31 bits
+    // one workgroup per unit of 128 tokens of a slice, two for units that go in halves: the grid must fit 31 bits
     const long nunits = long(batch) * heads * ((long(g->nlat_in) * g->nlon_in + 127) / 128);
     if (nunits > (1l << 30)) return s2_fail(S2_ERR_INVALID_ARG, "batch*heads*tokens too large for one launch");
     return S2_OK;

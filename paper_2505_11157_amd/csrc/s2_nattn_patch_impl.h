@@ -341,13 +341,6 @@ struct Chunks {
     }
 };
 
-// One tensor's stage.  Pieces of four elements, also where rows are no multiple of four long (kNarrow, kRagged: at any alignment,
-// a piece astride the end of its row element by element, with all of the wavefront's; kHalves: rows of an even length, in halves, 46 x 90, one
-// slice, d = 32, bf16, forward / backward 20 / 42 -> 15 / 32 us, 90 x 178, 32 slices, d = 64, bf16 329 / 879 -> 259 / 755, float32 630 / 1638 -> 589 /
-// 1523; decided inside of kNarrow, odd rows lost 2 to 5 %): as four loads each, 154 x 306, 4 slices, d = 64,
-// bf16, forward 196 us, now 130; 179 x 358, 6 slices, d = 32, bf16, forward and backward 859 -> 595; around the seam of circles of
-// some thirty longitudes, where most pieces are apart, 24.3 -> 25.4.
-// From memory to registers, and (float32: cut into three terms) on to LDS.
 // Where a chunk is, in a channel plane (kWide: in a slice)
 template <class T, int MODE>
 struct ChunkAt {
@@ -429,6 +422,12 @@ struct PairPiece {
         at = 2 * lat * up + 2 * i;
     }
 };
+// One tensor's stage, from memory to registers and (float32: cut into three terms) on to LDS.  Pieces of four elements, also where rows are no
+// multiple of four long.  kNarrow, kRagged: at any alignment, a piece astride the end of its row element by element, with all of the wavefront's: as
+// four loads each, 154 x 306, 4 slices, d = 64, bf16, forward 196 us, now 130; 179 x 358, 6 slices, d = 32, bf16, forward and backward 859 -> 595;
+// around the seam of circles of some thirty longitudes, where most pieces are apart, 24.3 -> 25.4.
+// kHalves: rows of an even length, in halves: 46 x 90, one slice, d = 32, bf16, forward / backward 20 / 42 -> 15 / 32 us, 90 x 178, 32 slices, d = 64,
+// bf16 329 / 879 -> 259 / 755, float32 630 / 1638 -> 589 / 1523; decided inside of kNarrow, odd rows lost 2 to 5 %.
 template <class G, int MODE>
 struct Stage {
     using T = typename G::T;
@@ -1294,9 +1293,10 @@ nattn_bwd_dkdv_patch(BandArgs a, const typename G::T *__restrict__ q, const type
 
 // Calls f with the geometry for a head dimension.  More workgroups on a compute unit count for more than longer stages (twice the
 // chunks per stage: float32 d = 32 0.56 / 0.65 / 0.73 ms, bf16 d = 32 0.27 / 0.35 / 0.40); the register limits are the loosest that do not
-// cost a workgroup, the tightest without spilled registers (bf16 d = 32 at five
-// wavefronts: forward 0.25 -> 0.24, dq 0.28 -> 0.26, dk/dv 0.34 -> 0.45 ms).  Odd
-// rows take more of them for addresses (128 x 254, 16 slices: dk/dv, float32 d = 16 held to four 0.235 ms, to three 0.217; bf16 d = 64 held to
+// cost a workgroup, and the tightest that spill no more than a few registers (bf16 d = 32 at five
+// wavefronts: forward 0.25 -> 0.24, dq 0.28 -> 0.26, dk/dv 0.34 -> 0.45 ms).  kHalves has the limits of kNarrow and spills 28 bytes of scratch in dq of
+// float32 d = 32, 20 in that of d = 64 and 12 and 40 in dk/dv of bf16 d = 16 and 32; one wavefront less, 230 shapes, backward: float32 d = 32 1 % slower,
+// bf16 d = 16 and 32 1 % faster.  Odd rows take more of them for addresses (128 x 254, 16 slices: dk/dv, float32 d = 16 held to four 0.235 ms, to three 0.217; bf16 d = 64 held to
 // three 0.515, to two 0.429; bf16 d = 32 to four 0.214, to three 0.220).
 // Stages of 24 chunks where that costs no workgroup, dk/dv of float32 d = 32: the four wavefronts of a workgroup meet more alike numbers of
 // whole tiles in a stage and wait less for each other, and there are a third fewer stages (129 x 256, 32 slices: 659 -> 633 us; at three
